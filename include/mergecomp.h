@@ -175,9 +175,15 @@ int mc_partition_search(const int64_t *numel, const double *bwd_time, int32_t n_
  * Device memory held by a context, with T = tiles of 4096 elements of its largest group:
  *   every algorithm   24 T bytes of reduction partials; up to 256 cached tensor-address lists with one
  *                     8-byte address per 1024 elements each (32 T bytes per list, 256 MiB at most in all)
+ *   more than one group   what mc_compress_groups / mc_decompress_sum_groups need to take all groups in one
+ *                     launch: the partials for the tiles of all groups, tables of a few bytes per tile and group,
+ *                     and up to 64 address lists of whole calls (64 MiB at most in all, or two lists)
  *   sparsifiers       6 bytes per element of the largest group for candidate values and positions
  *                     (24576 T; 153 MB for a 25.6 M element group), 12.25 T bytes of per-tile counts, 2 MiB for the
- *                     list of keys in the threshold's histogram bin, histograms and counters of about 100 KB
+ *                     list of keys in the threshold's histogram bin, histograms and counters of about 100 KB; with more
+ *                     than one group, these for every group instead of for the largest (the key list 32 KiB per tile,
+ *                     at most 2 MiB), unless that is more than 2 GiB of candidates or 512 MiB of histograms or lists,
+ *                     and not with a sampled threshold
  */
 int mc_ctx_create(mc_ctx **out, const mc_config *cfg, const int64_t *numel, int32_t n_tensors,
                   const int32_t *bounds, int32_t y);
@@ -250,8 +256,11 @@ int mc_decompress_sum(mc_ctx *ctx, int32_t group, const void *const *payloads, i
 
 /*
  * The loops of Algorithm 1 over all groups of the context in one call each, in group order, for a caller whose
- * gradients are all there already (no overlap with back-propagation) -- the same kernels as y calls of
- * mc_compress / mc_decompress_sum, without y trips through the caller's language binding.
+ * gradients are all there already (no overlap with back-propagation).  The results are those of y calls of
+ * mc_compress / mc_decompress_sum, byte for byte; the kernels cover all groups in one launch per step (one to four
+ * launches in all instead of that many per group).  Group by group, as y calls would be, go: sparsifiers with a
+ * sampled threshold or without scratch for all groups (see mc_ctx_create), calls in which a buffer that is written
+ * overlaps another buffer of the call, and calls with an argument that is not in order.
  *   grad_ptrs_all  host array, one DEVICE pointer per tensor of the MODEL (the list given to mc_ctx_create)
  *   states         host array of y DEVICE pointers, states[j] as `state` of mc_compress for group j (NULL when use_ef = 0)
  *   payloads_out   host array of y DEVICE pointers, payloads_out[j] receives group j's payload

@@ -59,7 +59,28 @@ void launch_expand_ptrs(const LaunchCtx &lc, const GroupView &g, uintptr_t *chun
     prof_end(lc, K_UPLOAD);
 }
 
-static inline uint32_t tiles_of(uint32_t n) { return (uint32_t)(((uint64_t)n + kTile - 1) / kTile); }
+// The same for the chunks of all groups (tb.list and the tables are on the device already).
+__global__ __launch_bounds__(kBlock) void expand_all_k(GroupTable tb, uint32_t tiles, uintptr_t *chunk_addr)
+{
+    const uint32_t c = blockIdx.x * kBlock + threadIdx.x;
+    if (c >= tiles * (uint32_t)kWavesPerBlock) return;
+    const GroupConst &G = tb.groups[tb.block_group[BLK_TILE][c / kWavesPerBlock]];
+    const uint32_t local = c - G.first[BLK_TILE] * (uint32_t)kWavesPerBlock, base = local * (uint32_t)kChunk;
+    if (base >= G.n) return;                           // the last tile of a group may have fewer than four chunks
+    const uint32_t s = G.chunk_seg[local];
+    const uint32_t beg = G.seg_off[s], end = G.seg_off[s + 1];
+    uintptr_t a = ((uintptr_t)s << 1) | 1u;
+    if (G.n - base >= (uint32_t)kChunk && end - base >= (uint32_t)kChunk) a = tb.list[G.first_ptr + s] + (uintptr_t)(base - beg) * sizeof(float);
+    chunk_addr[c] = a;
+}
+
+void launch_expand_all(const LaunchCtx &lc, const GroupTable &tb, uint32_t tiles, uintptr_t *chunk_addr)
+{
+    if (tiles == 0) return;
+    prof_begin(lc, K_UPLOAD);
+    MC_LAUNCH(expand_all_k, dim3((tiles * kWavesPerBlock + kBlock - 1) / kBlock), dim3(kBlock), lc, tb, tiles, chunk_addr);
+    prof_end(lc, K_UPLOAD);
+}
 
 // ---------------------------------------------------------------------------
 // The one-bit schemes, single pass: one sign bit per element of a vector p.
@@ -85,17 +106,20 @@ __device__ __forceinline__ void put_plain_header(PayloadHeader *hdr, uint32_t al
     *hdr = h;
 }
 
-template <int MODE, bool EF>
-__global__ __launch_bounds__(kBlock) void sign_compress_k(GroupView g, float *st, const StateHeader *prev, float beta,
-                                                          uint32_t *words, uint32_t nwords, double *partial,
-                                                          PayloadHeader *hdr, uint32_t algo)
+template <int MODE, bool EF, class SRC>
+__global__ __launch_bounds__(kBlock) void sign_compress_k(SRC src, float beta, uint32_t algo)
 {
     __shared__ uint64_t stage[kWavesPerBlock][kSteps];
     __shared__ double red[kWavesPerBlock];
     __shared__ double red3[MODE == SIGN_MEANS ? 3 : 1][kWavesPerBlock];
-    const Chunk c = my_chunk(g.n);
+    const CompressJob job = src.job();
+    const GroupView &g = job.g;
+    float *st = job.st;
+    uint32_t *words = reinterpret_cast<uint32_t *>(job.body());
+    const uint32_t nwords = (g.n + 31u) >> 5;
+    const Chunk c = my_chunk(g.n, job.tile);
     // SignSGD, SigNUM: the decoded values are +-1, no finalize kernel follows
-    if ((MODE == SIGN_PLAIN || MODE == SIGN_MOMENTUM) && blockIdx.x == 0 && threadIdx.x == 0) put_plain_header(hdr, algo, g.n, 1.0f);
+    if ((MODE == SIGN_PLAIN || MODE == SIGN_MOMENTUM) && job.tile == job.ntiles - 1u && threadIdx.x == 0) put_plain_header(job.hdr, algo, g.n, 1.0f);
     double acc = 0.0, acc_lo = 0.0, cnt_hi = 0.0;
     if (c.base < g.n) {
         float p[kSteps];
@@ -111,6 +135,7 @@ __global__ __launch_bounds__(kBlock) void sign_compress_k(GroupView g, float *st
             }
             store_flat(st, c, g.n, p);
         } else if (EF && MODE != SIGN_PLAIN) {
+            const StateHeader *prev = job.state_header();
             const float hi = prev->scale, lo = MODE == SIGN_MEANS ? prev->scale_lo : -hi;
             float q[kSteps];
             load_flat(st, c, g.n, q, 0.0f);
@@ -142,44 +167,46 @@ __global__ __launch_bounds__(kBlock) void sign_compress_k(GroupView g, float *st
     }
     if (MODE == SIGN_EF) {
         double t = block_sum(acc, red);
-        if (threadIdx.x == 0) partial[my_tile_index()] = t;
+        if (threadIdx.x == 0) job.partial[job.tile] = t;
     }
     if (MODE == SIGN_MEANS) {       // the three sums behind one pair of barriers, each combined in block_sum's order
         acc = wave_sum(acc); acc_lo = wave_sum(acc_lo); cnt_hi = wave_sum(cnt_hi);
         if ((threadIdx.x & 63) == 0) { red3[0][threadIdx.x >> 6] = acc; red3[1][threadIdx.x >> 6] = acc_lo; red3[2][threadIdx.x >> 6] = cnt_hi; }
         __syncthreads();
         if (threadIdx.x < 3)
-            partial[threadIdx.x * gridDim.x + my_tile_index()] = (red3[threadIdx.x][0] + red3[threadIdx.x][1]) + (red3[threadIdx.x][2] + red3[threadIdx.x][3]);
+            job.partial[threadIdx.x * job.ntiles + job.tile] = (red3[threadIdx.x][0] + red3[threadIdx.x][1]) + (red3[threadIdx.x][2] + red3[threadIdx.x][3]);
     }
 }
 
-void launch_sign_compress(const LaunchCtx &lc, int mode, const GroupView &g, bool ef, float *state_f, const StateHeader *prev,
-                          float beta, uint32_t *words, uint32_t nwords, double *partial, PayloadHeader *hdr, uint32_t algo)
+template <class SRC>
+void launch_sign_compress(const LaunchCtx &lc, int mode, const SRC &src, uint32_t tiles, bool ef, float beta, uint32_t algo)
 {
-    if (g.n == 0) return;
-    dim3 grid(tiles_of(g.n)), block(kBlock);
+    if (tiles == 0) return;
+    dim3 grid(tiles), block(kBlock);
     prof_begin(lc, K_EFSIGN_COMPRESS);
     switch (mode) {
     case SIGN_EF:
-        if (ef) MC_LAUNCH((sign_compress_k<SIGN_EF, true>), grid, block, lc, g, state_f, prev, beta, words, nwords, partial, hdr, algo);
-        else MC_LAUNCH((sign_compress_k<SIGN_EF, false>), grid, block, lc, g, state_f, prev, beta, words, nwords, partial, hdr, algo);
+        if (ef) MC_LAUNCH((sign_compress_k<SIGN_EF, true, SRC>), grid, block, lc, src, beta, algo);
+        else MC_LAUNCH((sign_compress_k<SIGN_EF, false, SRC>), grid, block, lc, src, beta, algo);
         break;
     case SIGN_MEANS:
-        if (ef) MC_LAUNCH((sign_compress_k<SIGN_MEANS, true>), grid, block, lc, g, state_f, prev, beta, words, nwords, partial, hdr, algo);
-        else MC_LAUNCH((sign_compress_k<SIGN_MEANS, false>), grid, block, lc, g, state_f, prev, beta, words, nwords, partial, hdr, algo);
+        if (ef) MC_LAUNCH((sign_compress_k<SIGN_MEANS, true, SRC>), grid, block, lc, src, beta, algo);
+        else MC_LAUNCH((sign_compress_k<SIGN_MEANS, false, SRC>), grid, block, lc, src, beta, algo);
         break;
     case SIGN_PLAIN:
-        MC_LAUNCH((sign_compress_k<SIGN_PLAIN, false>), grid, block, lc, g, state_f, prev, beta, words, nwords, partial, hdr, algo);
+        MC_LAUNCH((sign_compress_k<SIGN_PLAIN, false, SRC>), grid, block, lc, src, beta, algo);
         break;
     default:
-        MC_LAUNCH((sign_compress_k<SIGN_MOMENTUM, true>), grid, block, lc, g, state_f, prev, beta, words, nwords, partial, hdr, algo);
+        MC_LAUNCH((sign_compress_k<SIGN_MOMENTUM, true, SRC>), grid, block, lc, src, beta, algo);
         break;
     }
     prof_end(lc, K_EFSIGN_COMPRESS);
 }
+template void launch_sign_compress<OneCompress>(const LaunchCtx &, int, const OneCompress &, uint32_t, bool, float, uint32_t);
+template void launch_sign_compress<AllCompress>(const LaunchCtx &, int, const AllCompress &, uint32_t, bool, float, uint32_t);
 
 // ---------------------------------------------------------------------------
-// One block: combine the per-block partials in a fixed order (bit-reproducible
+// One block per group: combine the per-block partials in a fixed order (bit-reproducible
 // whatever the launch geometry of the producer was), derive the group scalar,
 // write the payload header (and, for EF-Sign, the scale kept in the state).
 //   RED_MEAN_ABS: scale = (float)(sum / n)      RED_L2: norm = (float)sqrt(sum)
@@ -190,11 +217,16 @@ void launch_sign_compress(const LaunchCtx &lc, int mode, const GroupView &g, boo
 // ---------------------------------------------------------------------------
 constexpr int kFinalThreads = 1024;
 
-__global__ __launch_bounds__(kFinalThreads) void scalar_finalize_k(const double *partial, uint32_t nblocks, int mode, uint32_t n,
-                                                                   PayloadHeader *hdr, uint32_t algo, uint64_t k, uint32_t levels,
-                                                                   float *state_scale)
+template <class SRC>
+__global__ __launch_bounds__(kFinalThreads) void scalar_finalize_k(SRC src, int mode, uint32_t algo, uint32_t levels, int keep)
 {
     __shared__ double red[kFinalThreads / 64];
+    const CompressJob job = src.group_job(blockIdx.x);
+    const double *partial = job.partial;
+    const uint32_t nblocks = job.ntiles, n = job.g.n;
+    PayloadHeader *hdr = job.hdr;
+    // where the state keeps the scalar(s) of this call (EF-Sign: one float, OneBit: two)
+    float *state_scale = keep && n > 0 ? &job.state_header()->scale : nullptr;
     if (mode == RED_MEANS) {
         // the three sums side by side (their loads in flight together, one barrier), each in the fixed order of the
         // single-sum case
@@ -232,7 +264,7 @@ __global__ __launch_bounds__(kFinalThreads) void scalar_finalize_k(const double 
             const double n_hi = S[2], n_lo = (double)n - S[2];
             const float hi = n_hi > 0.0 ? (float)(S[0] / n_hi) : 0.0f, lo = n_lo > 0.0 ? (float)(S[1] / n_lo) : 0.0f;
             PayloadHeader h;
-            h.magic = kMagic; h.algo = algo; h.n = n; h.k = k; h.scale = hi; h.levels = levels;
+            h.magic = kMagic; h.algo = algo; h.n = n; h.k = 0; h.scale = hi; h.levels = levels;
             for (int i = 0; i < 24; ++i) h.pad[i] = 0;
             h.pad[0] = __float_as_uint(lo);
             *hdr = h;
@@ -273,22 +305,23 @@ __global__ __launch_bounds__(kFinalThreads) void scalar_finalize_k(const double 
         }
         if (mode == RED_ONE) scale = 1.0f;
         PayloadHeader h;
-        h.magic = kMagic; h.algo = algo; h.n = n; h.k = k; h.scale = scale; h.levels = levels;
+        h.magic = kMagic; h.algo = algo; h.n = n; h.k = 0; h.scale = scale; h.levels = levels;
         for (int i = 0; i < 24; ++i) h.pad[i] = 0;
         *hdr = h;
         if (state_scale) *state_scale = scale;
     }
 }
 
-// state_scale: where the state keeps the scalar(s) of this call (EF-Sign: one float, OneBit: two), or null
-void launch_scalar_finalize(const LaunchCtx &lc, const double *partial, uint32_t nblocks, int mode, uint32_t n,
-                            PayloadHeader *hdr, uint32_t algo, uint64_t k, uint32_t levels, float *state_scale)
+// keep: the state remembers the scalar(s)
+template <class SRC>
+void launch_scalar_finalize(const LaunchCtx &lc, const SRC &src, uint32_t groups, int mode, uint32_t algo, uint32_t levels, bool keep)
 {
     prof_begin(lc, K_SCALAR_FINALIZE);
-    MC_LAUNCH(scalar_finalize_k, dim3(1), dim3(kFinalThreads), lc, partial, nblocks, mode, n, hdr, algo, k,
-                       levels, state_scale);
+    MC_LAUNCH(scalar_finalize_k<SRC>, dim3(groups), dim3(kFinalThreads), lc, src, mode, algo, levels, keep ? 1 : 0);
     prof_end(lc, K_SCALAR_FINALIZE);
 }
+template void launch_scalar_finalize<OneCompress>(const LaunchCtx &, const OneCompress &, uint32_t, int, uint32_t, uint32_t, bool);
+template void launch_scalar_finalize<AllCompress>(const LaunchCtx &, const AllCompress &, uint32_t, int, uint32_t, uint32_t, bool);
 
 // The two stochastic quantizers, one element: what is sent and what the receiver reconstructs from it.
 // QSGD with a = |p| s / norm:  level = floor(a) + [u < a - floor(a)], code = sgn(p) level, d = code * (norm / s).
@@ -335,19 +368,22 @@ __device__ __forceinline__ float tern_decode(float smax, float p, float u, bool 
 // bytes per element over the two passes).  A zero-filled or imported state has scalar 0,
 // for which d = 0 and e = p.
 // ---------------------------------------------------------------------------
-template <bool EF, int MODE>
-__global__ __launch_bounds__(kBlock) void accum_reduce_k(GroupView g, float *st, const StateHeader *prev, uint32_t levels, uint64_t seed,
-                                                         double *partial)
+template <bool EF, int MODE, class SRC>
+__global__ __launch_bounds__(kBlock) void accum_reduce_k(SRC src, uint32_t levels, uint64_t seed)
 {
     __shared__ double red[kWavesPerBlock];
     __shared__ float redf[kWavesPerBlock];
-    const Chunk c = my_chunk(g.n);
+    const CompressJob job = src.job();
+    const GroupView &g = job.g;
+    float *st = job.st;
+    const Chunk c = my_chunk(g.n, job.tile);
     double acc = 0.0;
     float mx = 0.0f;
     if (c.base < g.n) {
         float p[kSteps];
         load_seg(g, c, p);
         if (EF) {
+            const StateHeader *prev = job.state_header();
             const float sprev = prev->scale;
             const uint32_t wprev = prev->prev_worker, iprev = prev->prev_iter;
             float q[kSteps], uni[kSteps];
@@ -373,28 +409,30 @@ __global__ __launch_bounds__(kBlock) void accum_reduce_k(GroupView g, float *st,
     }
     if (MODE == RED_L2) {
         double t = block_sum(acc, red);
-        if (threadIdx.x == 0) partial[my_tile_index()] = t;
+        if (threadIdx.x == 0) job.partial[job.tile] = t;
     } else {
         float t = block_max(mx, redf);
-        if (threadIdx.x == 0) partial[my_tile_index()] = (double)t;
+        if (threadIdx.x == 0) job.partial[job.tile] = (double)t;
     }
 }
 
-void launch_accum_reduce(const LaunchCtx &lc, const GroupView &g, bool ef, float *state_f, const StateHeader *prev, int mode,
-                         uint32_t levels, uint64_t seed, double *partial)
+template <class SRC>
+void launch_accum_reduce(const LaunchCtx &lc, const SRC &src, uint32_t tiles, bool ef, int mode, uint32_t levels, uint64_t seed)
 {
-    if (g.n == 0) return;
-    dim3 grid(tiles_of(g.n)), block(kBlock);
+    if (tiles == 0) return;
+    dim3 grid(tiles), block(kBlock);
     prof_begin(lc, K_ACCUM_REDUCE);
     if (mode == RED_L2) {
-        if (ef) MC_LAUNCH((accum_reduce_k<true, RED_L2>), grid, block, lc, g, state_f, prev, levels, seed, partial);
-        else MC_LAUNCH((accum_reduce_k<false, RED_L2>), grid, block, lc, g, state_f, prev, levels, seed, partial);
+        if (ef) MC_LAUNCH((accum_reduce_k<true, RED_L2, SRC>), grid, block, lc, src, levels, seed);
+        else MC_LAUNCH((accum_reduce_k<false, RED_L2, SRC>), grid, block, lc, src, levels, seed);
     } else {
-        if (ef) MC_LAUNCH((accum_reduce_k<true, RED_MAX_ABS>), grid, block, lc, g, state_f, prev, levels, seed, partial);
-        else MC_LAUNCH((accum_reduce_k<false, RED_MAX_ABS>), grid, block, lc, g, state_f, prev, levels, seed, partial);
+        if (ef) MC_LAUNCH((accum_reduce_k<true, RED_MAX_ABS, SRC>), grid, block, lc, src, levels, seed);
+        else MC_LAUNCH((accum_reduce_k<false, RED_MAX_ABS, SRC>), grid, block, lc, src, levels, seed);
     }
     prof_end(lc, K_ACCUM_REDUCE);
 }
+template void launch_accum_reduce<OneCompress>(const LaunchCtx &, const OneCompress &, uint32_t, bool, int, uint32_t, uint64_t);
+template void launch_accum_reduce<AllCompress>(const LaunchCtx &, const AllCompress &, uint32_t, bool, int, uint32_t, uint64_t);
 
 // p of pass B: from the state (where pass A left it) or, without error feedback, the gradient itself
 template <bool EF>
@@ -436,21 +474,25 @@ __device__ __forceinline__ void store_codes(T *codes, uint32_t n, uint32_t n_pad
 // as it is, and one thread records the group scalar and the random stream of this call in the
 // state header, from which the next call's pass A re-derives the residual (see there).
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ void remember_call(StateHeader *sh, float scale, uint32_t worker, uint32_t iter_lo)
+__device__ __forceinline__ void remember_call(const CompressJob &job, float scale, uint32_t worker, uint32_t iter_lo)
 {
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
+    if (job.tile == job.ntiles - 1u && threadIdx.x == 0) {
+        StateHeader *sh = job.state_header();
         sh->scale = scale; sh->scale_lo = 0.0f; sh->prev_worker = worker; sh->prev_iter = iter_lo;
     }
 }
 
-template <bool EF>
-__global__ __launch_bounds__(kBlock) void qsgd_encode_k(GroupView g, const float *st, StateHeader *sh, const PayloadHeader *hdr,
-                                                        int8_t *codes, uint32_t levels, uint64_t seed, uint32_t worker, uint32_t iter_lo)
+template <bool EF, class SRC>
+__global__ __launch_bounds__(kBlock) void qsgd_encode_k(SRC src, uint32_t levels, uint64_t seed, uint32_t worker, uint32_t iter_lo)
 {
     __shared__ __attribute__((aligned(16))) int8_t stage[kWavesPerBlock][kChunk];
-    const Chunk c = my_chunk(g.n);
-    const float norm = hdr->scale;
-    if (EF) remember_call(sh, norm, worker, iter_lo);
+    const CompressJob job = src.job();
+    const GroupView &g = job.g;
+    const float *st = job.st;
+    int8_t *codes = reinterpret_cast<int8_t *>(job.body());
+    const Chunk c = my_chunk(g.n, job.tile);
+    const float norm = job.hdr->scale;
+    if (EF) remember_call(job, norm, worker, iter_lo);
     if (c.base >= g.n) return;
     const QsgdScale ks(norm, levels);
     float p[kSteps];
@@ -463,26 +505,32 @@ __global__ __launch_bounds__(kBlock) void qsgd_encode_k(GroupView g, const float
     store_codes<int8_t>(codes, g.n, (g.n + 3u) & ~3u, c, code, stage[threadIdx.x >> 6]);
 }
 
-void launch_qsgd_encode(const LaunchCtx &lc, const GroupView &g, bool ef, float *state_f, StateHeader *sh, const PayloadHeader *hdr,
-                        int8_t *codes, uint32_t levels, uint64_t seed, uint32_t worker, uint32_t iter_lo)
+template <class SRC>
+void launch_qsgd_encode(const LaunchCtx &lc, const SRC &src, uint32_t tiles, bool ef, uint32_t levels, uint64_t seed, uint32_t worker, uint32_t iter_lo)
 {
-    if (g.n == 0) return;
-    dim3 grid(tiles_of(g.n)), block(kBlock);
+    if (tiles == 0) return;
+    dim3 grid(tiles), block(kBlock);
     prof_begin(lc, K_QSGD_ENCODE);
-    if (ef) MC_LAUNCH(qsgd_encode_k<true>, grid, block, lc, g, state_f, sh, hdr, codes, levels, seed, worker, iter_lo);
-    else MC_LAUNCH(qsgd_encode_k<false>, grid, block, lc, g, state_f, sh, hdr, codes, levels, seed, worker, iter_lo);
+    if (ef) MC_LAUNCH((qsgd_encode_k<true, SRC>), grid, block, lc, src, levels, seed, worker, iter_lo);
+    else MC_LAUNCH((qsgd_encode_k<false, SRC>), grid, block, lc, src, levels, seed, worker, iter_lo);
     prof_end(lc, K_QSGD_ENCODE);
 }
+template void launch_qsgd_encode<OneCompress>(const LaunchCtx &, const OneCompress &, uint32_t, bool, uint32_t, uint64_t, uint32_t, uint32_t);
+template void launch_qsgd_encode<AllCompress>(const LaunchCtx &, const AllCompress &, uint32_t, bool, uint32_t, uint64_t, uint32_t, uint32_t);
 
 // TernGrad: two bit planes (non-zero, negative)
-template <bool EF>
-__global__ __launch_bounds__(kBlock) void tern_encode_k(GroupView g, const float *st, StateHeader *sh, const PayloadHeader *hdr,
-                                                        uint32_t *planes, uint32_t nwords, uint64_t seed, uint32_t worker, uint32_t iter_lo)
+template <bool EF, class SRC>
+__global__ __launch_bounds__(kBlock) void tern_encode_k(SRC src, uint64_t seed, uint32_t worker, uint32_t iter_lo)
 {
     __shared__ uint64_t stage[kWavesPerBlock][kSteps];
-    const Chunk c = my_chunk(g.n);
-    const float smax = hdr->scale;
-    if (EF) remember_call(sh, smax, worker, iter_lo);
+    const CompressJob job = src.job();
+    const GroupView &g = job.g;
+    const float *st = job.st;
+    uint32_t *planes = reinterpret_cast<uint32_t *>(job.body());
+    const uint32_t nwords = (g.n + 31u) >> 5;
+    const Chunk c = my_chunk(g.n, job.tile);
+    const float smax = job.hdr->scale;
+    if (EF) remember_call(job, smax, worker, iter_lo);
     if (c.base >= g.n) return;
     float p[kSteps];
     load_p<EF>(g, st, c, p);
@@ -502,25 +550,31 @@ __global__ __launch_bounds__(kBlock) void tern_encode_k(GroupView g, const float
     store_plane(planes + nwords, nwords, c, bng, stage[threadIdx.x >> 6]);
 }
 
-void launch_tern_encode(const LaunchCtx &lc, const GroupView &g, bool ef, float *state_f, StateHeader *sh, const PayloadHeader *hdr,
-                        uint32_t *planes, uint32_t nwords, uint64_t seed, uint32_t worker, uint32_t iter_lo)
+template <class SRC>
+void launch_tern_encode(const LaunchCtx &lc, const SRC &src, uint32_t tiles, bool ef, uint64_t seed, uint32_t worker, uint32_t iter_lo)
 {
-    if (g.n == 0) return;
-    dim3 grid(tiles_of(g.n)), block(kBlock);
+    if (tiles == 0) return;
+    dim3 grid(tiles), block(kBlock);
     prof_begin(lc, K_TERN_ENCODE);
-    if (ef) MC_LAUNCH(tern_encode_k<true>, grid, block, lc, g, state_f, sh, hdr, planes, nwords, seed, worker, iter_lo);
-    else MC_LAUNCH(tern_encode_k<false>, grid, block, lc, g, state_f, sh, hdr, planes, nwords, seed, worker, iter_lo);
+    if (ef) MC_LAUNCH((tern_encode_k<true, SRC>), grid, block, lc, src, seed, worker, iter_lo);
+    else MC_LAUNCH((tern_encode_k<false, SRC>), grid, block, lc, src, seed, worker, iter_lo);
     prof_end(lc, K_TERN_ENCODE);
 }
+template void launch_tern_encode<OneCompress>(const LaunchCtx &, const OneCompress &, uint32_t, bool, uint64_t, uint32_t, uint32_t);
+template void launch_tern_encode<AllCompress>(const LaunchCtx &, const AllCompress &, uint32_t, bool, uint64_t, uint32_t, uint32_t);
 
 // ---------------------------------------------------------------------------
 // FP16, single pass: h = binary16(p) round-to-nearest-even, e <- p - (float)h.
 // ---------------------------------------------------------------------------
-template <bool EF>
-__global__ __launch_bounds__(kBlock) void fp16_compress_k(GroupView g, float *st, uint16_t *halves, PayloadHeader *hdr)
+template <bool EF, class SRC>
+__global__ __launch_bounds__(kBlock) void fp16_compress_k(SRC src)
 {
-    const Chunk c = my_chunk(g.n);
-    if (blockIdx.x == 0 && threadIdx.x == 0) put_plain_header(hdr, MC_ALGO_FP16, g.n, 0.0f);
+    const CompressJob job = src.job();
+    const GroupView &g = job.g;
+    float *st = job.st;
+    uint16_t *halves = reinterpret_cast<uint16_t *>(job.body());
+    const Chunk c = my_chunk(g.n, job.tile);
+    if (job.tile == job.ntiles - 1u && threadIdx.x == 0) put_plain_header(job.hdr, MC_ALGO_FP16, g.n, 0.0f);
     if (c.base >= g.n) return;
     float p[kSteps];
     load_seg(g, c, p);
@@ -556,16 +610,18 @@ __global__ __launch_bounds__(kBlock) void fp16_compress_k(GroupView g, float *st
     }
 }
 
-void launch_fp16_compress(const LaunchCtx &lc, const GroupView &g, bool ef, float *state_f, PayloadHeader *hdr,
-                          uint16_t *halves)
+template <class SRC>
+void launch_fp16_compress(const LaunchCtx &lc, const SRC &src, uint32_t tiles, bool ef)
 {
-    if (g.n == 0) return;
-    dim3 grid(tiles_of(g.n)), block(kBlock);
+    if (tiles == 0) return;
+    dim3 grid(tiles), block(kBlock);
     prof_begin(lc, K_FP16_COMPRESS);
-    if (ef) MC_LAUNCH(fp16_compress_k<true>, grid, block, lc, g, state_f, halves, hdr);
-    else MC_LAUNCH(fp16_compress_k<false>, grid, block, lc, g, state_f, halves, hdr);
+    if (ef) MC_LAUNCH((fp16_compress_k<true, SRC>), grid, block, lc, src);
+    else MC_LAUNCH((fp16_compress_k<false, SRC>), grid, block, lc, src);
     prof_end(lc, K_FP16_COMPRESS);
 }
+template void launch_fp16_compress<OneCompress>(const LaunchCtx &, const OneCompress &, uint32_t, bool);
+template void launch_fp16_compress<AllCompress>(const LaunchCtx &, const AllCompress &, uint32_t, bool);
 
 // ---------------------------------------------------------------------------
 // Decompress-and-sum of dense codes (Algorithm 1: g~ = aggregate(C^-1(Delta))):
@@ -592,15 +648,16 @@ __device__ __forceinline__ void check_header(const PayloadHeader *h, uint32_t al
 // made FP16 slower, 80.3 -> 82.5..85 us with 2, 4 or 8 workers per batch, so FP16 stays plain.)
 typedef float float4v __attribute__((ext_vector_type(4)));
 
-template <int ALGO>
-__global__ __launch_bounds__(kBlock) void dense_decompress_k(GroupView out, PayloadPtrs pl, int W, float alpha,
-                                                             uint32_t levels, int *status)
+template <int ALGO, class SRC>
+__global__ __launch_bounds__(kBlock) void dense_decompress_k(SRC src, int W, float alpha, uint32_t levels, int *status)
 {
     static_assert(ALGO == MC_ALGO_QSGD || ALGO == MC_ALGO_FP16, "one code per element");
     constexpr int kBatch = 4;
-    const Chunk c = my_chunk(out.n);
-    if (blockIdx.x == 0 && (int)threadIdx.x < W)
-        check_header(reinterpret_cast<const PayloadHeader *>(pl.p[threadIdx.x]), ALGO, out.n, status);
+    const auto job = src.template job<BLK_TILE>();
+    const GroupView &out = job.out;
+    const Chunk c = my_chunk(out.n, job.block);
+    if (job.block == job.last && (int)threadIdx.x < W)
+        check_header(reinterpret_cast<const PayloadHeader *>(job.payload_of_lane(threadIdx.x)), ALGO, out.n, status);
     if (c.base >= out.n) return;
     const uintptr_t entry = chunk_entry(out, c);
     if (ALGO == MC_ALGO_QSGD && !(entry & 15u)) {               // an address (even), and 16-byte aligned
@@ -617,11 +674,11 @@ __global__ __launch_bounds__(kBlock) void dense_decompress_k(GroupView out, Payl
             float scale[kBatch];
 #pragma unroll
             for (int b = 0; b < kBatch; ++b)
-                scale[b] = w0 + b < W ? ld_uniform(&reinterpret_cast<const PayloadHeader *>(pl.p[w0 + b])->scale) : 0.0f;
+                scale[b] = w0 + b < W ? ld_uniform(&reinterpret_cast<const PayloadHeader *>(job.payload(w0 + b))->scale) : 0.0f;
             uint32_t cw[kBatch][4];
 #pragma unroll
             for (int b = 0; b < kBatch; ++b) {
-                const uint8_t *codes = pl.p[w0 + b < W ? w0 + b : 0] + kHeaderBytes + c.base;
+                const uint8_t *codes = job.payload(w0 + b < W ? w0 + b : 0) + kHeaderBytes + c.base;
 #pragma unroll
                 for (int m = 0; m < 4; ++m) cw[b][m] = w0 + b < W ? ld_stream(reinterpret_cast<const uint32_t *>(codes + at[m])) : 0u;
             }
@@ -651,12 +708,12 @@ __global__ __launch_bounds__(kBlock) void dense_decompress_k(GroupView out, Payl
         float scale[kBatch];
 #pragma unroll
         for (int b = 0; b < kBatch; ++b)
-            scale[b] = w0 + b < W ? ld_uniform(&reinterpret_cast<const PayloadHeader *>(pl.p[w0 + b])->scale) : 0.0f;
+            scale[b] = w0 + b < W ? ld_uniform(&reinterpret_cast<const PayloadHeader *>(job.payload(w0 + b))->scale) : 0.0f;
         if (ALGO == MC_ALGO_QSGD) {
             int8_t cd[kBatch][kSteps];
 #pragma unroll
             for (int b = 0; b < kBatch; ++b) {
-                if (w0 + b < W) load_flat<int8_t>(reinterpret_cast<const int8_t *>(pl.p[w0 + b] + kHeaderBytes), c, out.n, cd[b], (int8_t)0);
+                if (w0 + b < W) load_flat<int8_t>(reinterpret_cast<const int8_t *>(job.payload(w0 + b) + kHeaderBytes), c, out.n, cd[b], (int8_t)0);
             }
 #pragma unroll
             for (int b = 0; b < kBatch; ++b) {
@@ -670,7 +727,7 @@ __global__ __launch_bounds__(kBlock) void dense_decompress_k(GroupView out, Payl
             _Float16 hv[kBatch][kSteps];
 #pragma unroll
             for (int b = 0; b < kBatch; ++b) {
-                if (w0 + b < W) load_flat<_Float16>(reinterpret_cast<const _Float16 *>(pl.p[w0 + b] + kHeaderBytes), c, out.n, hv[b], (_Float16)0.0f);
+                if (w0 + b < W) load_flat<_Float16>(reinterpret_cast<const _Float16 *>(job.payload(w0 + b) + kHeaderBytes), c, out.n, hv[b], (_Float16)0.0f);
             }
 #pragma unroll
             for (int b = 0; b < kBatch; ++b) {
@@ -711,6 +768,7 @@ __device__ __forceinline__ uint64_t transpose8x8(uint64_t x)
 
 constexpr int kSignWaveElems = 2048;                       // 64 lanes x 32 elements
 constexpr int kSignTile = kSignWaveElems * kWavesPerBlock; // 8192 elements per block
+static_assert(kSignTile == 2 * kTile, "blocks of the bit-plane decode (BLK_PLANE)");
 
 // bytes of 8 words (one per worker) -> per element the 8 workers' bits: word q byte -> 8 table indices
 __device__ __forceinline__ uint64_t gather_transpose(const uint32_t (&wd)[8], int q)
@@ -760,20 +818,21 @@ __device__ __forceinline__ float plane_term(uint32_t word, int e, float hi, floa
     return __uint_as_float((__float_as_uint(hi) & m) | (__float_as_uint(lo) & ~m));
 }
 
-template <bool TERN>
-__global__ __launch_bounds__(kBlock) void plane_decompress_k(GroupView out, PayloadPtrs pl, int W, float alpha, int *status,
-                                                             int algo, int kind)
+template <bool TERN, class SRC>
+__global__ __launch_bounds__(kBlock) void plane_decompress_k(SRC src, int W, float alpha, int *status, int algo, int kind)
 {
     __shared__ float table[256];
     __shared__ float stage[kWavesPerBlock][kChunk + 32];
     const uint32_t t = threadIdx.x;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63u;
-    if (blockIdx.x == 0 && (int)t < W)
-        check_header(reinterpret_cast<const PayloadHeader *>(pl.p[t]), algo, out.n, status);
+    const auto job = src.template job<BLK_PLANE>();
+    const GroupView &out = job.out;
+    if (job.block == job.last && (int)t < W)
+        check_header(reinterpret_cast<const PayloadHeader *>(job.payload_of_lane(t)), algo, out.n, status);
     const int Wt = W < 8 ? W : 8;
     // the plane words are asked for before the table is built: the headers' scalars, which the table waits for, and
     // the words then travel together (one-plane schemes 0.6 us, OneBit and TernGrad 1.0-1.5 us of 28-37)
-    const uint32_t wbase = my_tile_index() * (uint32_t)kSignTile + wave * (uint32_t)kSignWaveElems;
+    const uint32_t wbase = job.block * (uint32_t)kSignTile + wave * (uint32_t)kSignWaveElems;
     const uint32_t nwords = (out.n + 31u) >> 5;
     const uint32_t wi = (wbase >> 5) + lane;
     uint32_t wd[8], wn[8];
@@ -781,7 +840,7 @@ __global__ __launch_bounds__(kBlock) void plane_decompress_k(GroupView out, Payl
     for (int b = 0; b < 8; ++b) {
         wd[b] = 0u; wn[b] = 0u;
         if (b < Wt && wi < nwords) {
-            const uint32_t *plane = reinterpret_cast<const uint32_t *>(pl.p[b] + kHeaderBytes);
+            const uint32_t *plane = reinterpret_cast<const uint32_t *>(job.payload(b) + kHeaderBytes);
             wd[b] = ld_stream(plane + wi);
             if (TERN) wn[b] = ld_stream(plane + nwords + wi);
         }
@@ -793,7 +852,7 @@ __global__ __launch_bounds__(kBlock) void plane_decompress_k(GroupView out, Payl
             for (int b = 0; b < 8; ++b) {
                 if (b < Wt) {
                     float hi, lo;
-                    plane_levels(reinterpret_cast<const PayloadHeader *>(pl.p[b]), kind, hi, lo);
+                    plane_levels(reinterpret_cast<const PayloadHeader *>(job.payload(b)), kind, hi, lo);
                     acc = acc + (((t >> b) & 1u) ? hi : lo);
                 }
             }
@@ -805,7 +864,7 @@ __global__ __launch_bounds__(kBlock) void plane_decompress_k(GroupView out, Payl
 #pragma unroll
             for (int b = 0; b < 4; ++b) {
                 if (b < Wt) {
-                    const float sc = ld_uniform(&reinterpret_cast<const PayloadHeader *>(pl.p[b])->scale);
+                    const float sc = ld_uniform(&reinterpret_cast<const PayloadHeader *>(job.payload(b))->scale);
                     acc = acc + (((t >> b) & 1u) ? (((t >> (4 + b)) & 1u) ? -sc : sc) : 0.0f);
                 }
             }
@@ -815,7 +874,7 @@ __global__ __launch_bounds__(kBlock) void plane_decompress_k(GroupView out, Payl
     float s47[4] = {0.0f, 0.0f, 0.0f, 0.0f};               // TernGrad: scales of workers 4..7, added one by one
     if (TERN) {
 #pragma unroll
-        for (int b = 4; b < 8; ++b) if (b < Wt) s47[b - 4] = ld_uniform(&reinterpret_cast<const PayloadHeader *>(pl.p[b])->scale);
+        for (int b = 4; b < 8; ++b) if (b < Wt) s47[b - 4] = ld_uniform(&reinterpret_cast<const PayloadHeader *>(job.payload(b))->scale);
     }
     __syncthreads();
     if (wbase >= out.n) return;
@@ -845,9 +904,9 @@ __global__ __launch_bounds__(kBlock) void plane_decompress_k(GroupView out, Payl
     }
     if (W > 8) {
         for (int w = 8; w < W; ++w) {
-            float sc = ld_uniform(&reinterpret_cast<const PayloadHeader *>(pl.p[w])->scale), sl = -sc;
-            if (!TERN) plane_levels(reinterpret_cast<const PayloadHeader *>(pl.p[w]), kind, sc, sl);
-            const uint32_t *plane = reinterpret_cast<const uint32_t *>(pl.p[w] + kHeaderBytes);
+            float sc = ld_uniform(&reinterpret_cast<const PayloadHeader *>(job.payload(w))->scale), sl = -sc;
+            if (!TERN) plane_levels(reinterpret_cast<const PayloadHeader *>(job.payload(w)), kind, sc, sl);
+            const uint32_t *plane = reinterpret_cast<const uint32_t *>(job.payload(w) + kHeaderBytes);
             const uint32_t word = wi < nwords ? ld_stream(plane + wi) : 0u;
             const uint32_t neg = TERN && wi < nwords ? ld_stream(plane + nwords + wi) : 0u;
 #pragma unroll
@@ -892,30 +951,30 @@ __global__ __launch_bounds__(kBlock) void plane_decompress_k(GroupView out, Payl
     }
 }
 
-void launch_dense_decompress(const LaunchCtx &lc, int algo, const GroupView &out, const PayloadPtrs &pl, int W,
-                             float alpha, uint32_t levels, int *status)
+template <class SRC>
+void launch_dense_decompress(const LaunchCtx &lc, int algo, const SRC &src, uint32_t blocks, int W, float alpha, uint32_t levels, int *status)
 {
-    if (out.n == 0) return;
-    dim3 grid(tiles_of(out.n)), block(kBlock);
+    if (blocks == 0) return;
+    dim3 grid(blocks), block(kBlock);
     prof_begin(lc, K_DENSE_DECOMPRESS);
     switch (algo) {
     case MC_ALGO_EFSIGN:
     case MC_ALGO_ONEBIT:
     case MC_ALGO_SIGNSGD:
     case MC_ALGO_SIGNUM:
-        MC_LAUNCH(plane_decompress_k<false>, dim3((uint32_t)(((uint64_t)out.n + kSignTile - 1) / kSignTile)), block, lc, out, pl, W,
-                  alpha, status, algo,
+        MC_LAUNCH((plane_decompress_k<false, SRC>), grid, block, lc, src, W, alpha, status, algo,
                   algo == MC_ALGO_EFSIGN ? PLANE_SCALE : algo == MC_ALGO_ONEBIT ? PLANE_MEANS : PLANE_VOTE);
         break;
     case MC_ALGO_TERNGRAD:
-        MC_LAUNCH(plane_decompress_k<true>, dim3((uint32_t)(((uint64_t)out.n + kSignTile - 1) / kSignTile)), block, lc, out, pl, W,
-                  alpha, status, algo, PLANE_SCALE);
+        MC_LAUNCH((plane_decompress_k<true, SRC>), grid, block, lc, src, W, alpha, status, algo, PLANE_SCALE);
         break;
-    case MC_ALGO_QSGD: MC_LAUNCH(dense_decompress_k<MC_ALGO_QSGD>, grid, block, lc, out, pl, W, alpha, levels, status); break;
-    default: MC_LAUNCH(dense_decompress_k<MC_ALGO_FP16>, grid, block, lc, out, pl, W, alpha, levels, status); break;
+    case MC_ALGO_QSGD: MC_LAUNCH((dense_decompress_k<MC_ALGO_QSGD, SRC>), grid, block, lc, src, W, alpha, levels, status); break;
+    default: MC_LAUNCH((dense_decompress_k<MC_ALGO_FP16, SRC>), grid, block, lc, src, W, alpha, levels, status); break;
     }
     prof_end(lc, K_DENSE_DECOMPRESS);
 }
+template void launch_dense_decompress<OneDecompress>(const LaunchCtx &, int, const OneDecompress &, uint32_t, int, float, uint32_t, int *);
+template void launch_dense_decompress<AllDecompress>(const LaunchCtx &, int, const AllDecompress &, uint32_t, int, float, uint32_t, int *);
 
 // ---------------------------------------------------------------------------
 // State <-> plain residual.  EF-Sign, OneBit, QSGD and TernGrad keep p and the scalars

@@ -39,7 +39,6 @@
 
 namespace mc {
 
-static inline uint32_t tiles_of(uint32_t n) { return (uint32_t)(((uint64_t)n + kTile - 1) / kTile); }
 static inline uint32_t chunks_of(uint32_t n) { return (uint32_t)(((uint64_t)n + kChunk - 1) / kChunk); }
 
 constexpr int kWindowShift = 11;                       // keys per window bin = 2^11: what hist 3 resolves after a fast seed
@@ -161,23 +160,27 @@ __device__ __forceinline__ uint32_t put_candidates(const Chunk &c, const uint32_
 // ---------------------------------------------------------------------------
 // accumulate + candidate filter + window histogram of the candidates
 // ---------------------------------------------------------------------------
-template <int ALGO, bool EF>
-__global__ __launch_bounds__(kBlock) void sparse_accum_k(GroupView g, float *st, float momentum, SparseScratch sc, RngKey rng,
-                                                         SampleRule smp)
+template <int ALGO, bool EF, class SRC>
+__global__ __launch_bounds__(kBlock) void sparse_accum_k(SRC src, float momentum, RngKey rng, SampleRule smp)
 {
     __shared__ uint32_t hist[kBinsW];
     __shared__ uint32_t wcnt[kWavesPerBlock];
     for (int b = threadIdx.x; b < kBinsW; b += kBlock) hist[b] = 0u;
     __syncthreads();
-    const Chunk c = my_chunk(g.n);
+    const SparseJob job = src.template job<BLK_TILE>();
+    const GroupView &g = job.g;
+    float *st = job.st;
+    const SparseScratch &sc = job.sc;
+    const uint32_t order = job.blocks - 1u - job.block;          // the how-manieth of the group's blocks this is
+    const Chunk c = my_chunk(g.n, job.block);
     const uint32_t hint = *sc.hint;
     // the emit kernel of the call before is done with the list of keys in the threshold's bin: its sublists are empty again
-    if (blockIdx.x == 0 && threadIdx.x < (uint32_t)kUSub) sc.ucount[threadIdx.x * kUCountStride] = 0u;
-    if (blockIdx.x == 0 && threadIdx.x == 0) sc.sync[0] = 0u;       // and nobody waits at a grid-wide barrier of that call any more
+    if (order == 0 && threadIdx.x < (uint32_t)kUSub) sc.ucount[threadIdx.x * kUCountStride] = 0u;
+    if (order == 0 && threadIdx.x == 0) sc.sync[0] = 0u;       // and nobody waits at a grid-wide barrier of that call any more
     // The radix levels are cleared by the kernels that use them -- unless a call gave up at a barrier (MC_ERR_DEVICE):
     // what it left behind must not enter this call's counts.
     {
-        const uint32_t i = blockIdx.x * (uint32_t)kBlock + threadIdx.x;
+        const uint32_t i = order * (uint32_t)kBlock + threadIdx.x;
         if (i < (uint32_t)(kHistOpen - kHist1)) sc.hist[kHist1 + i] = 0u;
     }
     uint32_t run = 0;
@@ -236,9 +239,9 @@ __global__ __launch_bounds__(kBlock) void sparse_accum_k(GroupView g, float *st,
     if (c.lane == 0) wcnt[threadIdx.x >> 6] = run;
     __syncthreads();
     if (threadIdx.x == 0)       // candidates of the tile's four chunks, 16 bits each (a chunk holds at most 1024)
-        sc.tile_runs[my_tile_index()] = (uint64_t)wcnt[0] | ((uint64_t)wcnt[1] << 16) | ((uint64_t)wcnt[2] << 32) | ((uint64_t)wcnt[3] << 48);
-    flush_fine(hist, sc.hist + kHistW + (blockIdx.x % kWinCopies) * kBinsW, kBinsW - 1);
-    if (threadIdx.x == kBlock - 1 && hist[kBinsW - 1]) atomicAdd(&sc.hist[kHistOpen + (blockIdx.x & (kOpenCopies - 1))], hist[kBinsW - 1]);
+        sc.tile_runs[job.block] = (uint64_t)wcnt[0] | ((uint64_t)wcnt[1] << 16) | ((uint64_t)wcnt[2] << 32) | ((uint64_t)wcnt[3] << 48);
+    flush_fine(hist, sc.hist + kHistW + (order % kWinCopies) * kBinsW, kBinsW - 1);
+    if (threadIdx.x == kBlock - 1 && hist[kBinsW - 1]) atomicAdd(&sc.hist[kHistOpen + (order & (kOpenCopies - 1))], hist[kBinsW - 1]);
 }
 
 // ---------------------------------------------------------------------------
@@ -827,8 +830,8 @@ __global__ __launch_bounds__(kBlock) void cand_emit_k(uint32_t n, uint32_t ntile
 // Both kernels are bound by memory latency, not by traffic, so each asks for its tile's candidates as soon
 // as it knows how many there are, before it waits for anything else.
 // ---------------------------------------------------------------------------
-constexpr int kSelThreads = 1024, kSelWaves = kSelThreads / 64;      // select: 16 tiles per block (the window is read once per block)
-constexpr int kEmitThreads = kBlock, kEmitWaves = kWavesPerBlock;    // emit: 4 tiles per block
+constexpr int kSelThreads = 1024, kSelWaves = kSelTiles;      // select: 16 tiles per block (the window is read once per block)
+constexpr int kEmitThreads = kBlock, kEmitWaves = kEmitTiles;    // emit: 4 tiles per block
 constexpr int kSyncArrive = 0, kSyncRoutes = 32, kSyncLastBin = 40, kSyncLastCands = 41;     // words of SparseScratch::sync (mc_api.hip reads the last three)
 
 struct TileRuns { uint32_t r0, r1, r2, total; };       // running sums of the candidates of a tile's four chunks
@@ -957,8 +960,15 @@ __device__ __forceinline__ void publish_hint(const SparseScratch &sc, uint32_t T
 // block wrote before the barrier visible to every block after it.  The wait is bounded: should the count never
 // come (it always does when the blocks are resident together), the block flags the failure and leaves, and so
 // does every later wait.
+// A single block (blocks = 1) has only its own wavefronts to wait for, and to see its own atomics' results.
 __device__ __forceinline__ bool grid_barrier(uint32_t *arrive, uint32_t blocks, uint32_t round, uint32_t *dead /* LDS */, int *status, uint32_t limit)
 {
+    if (blocks == 1u) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+        __syncthreads();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        return true;
+    }
     __syncthreads();
     if (threadIdx.x == 0 && !*dead) {
         __hip_atomic_fetch_add(arrive, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
@@ -1001,17 +1011,17 @@ constexpr int kRoundTiles = 4096;      // tiles per round of the slow routes' co
 // kModeUniform: too few candidates, every element becomes one).
 template <int ALGO, bool EF, bool FROM_STATE, bool RANDOM>
 __device__ __forceinline__ void slow_routes(const GroupView &g, float *st, PayloadHeader *hdr, uint64_t k, const SparseScratch &sc,
-                                            const RngKey &rng, uint32_t mode, uint32_t lo, uint64_t need, uint32_t blocks, int *status,
+                                            const RngKey &rng, uint32_t mode, uint32_t lo, uint64_t need, uint32_t me, uint32_t blocks,
+                                            uint32_t &round, int *status,
                                             uint32_t *hist /* 2048 words of LDS */, uint32_t *pfx /* 2 * kRoundTiles words of LDS */,
-                                            uint32_t *small /* 64 words of LDS */)
+                                            uint32_t *small /* 64 words of LDS; word 4, "a barrier was not passed", cleared by the caller */)
 {
     uint32_t *res = small, *dead = small + 4, *wsum = small + 8;      // wsum: 2 * kSelWaves words
     const uint32_t t = threadIdx.x, lane = t & 63u, wave = __builtin_amdgcn_readfirstlane(t >> 6);
-    const uint32_t n = g.n, ntiles = (n + (uint32_t)kTile - 1u) / (uint32_t)kTile;
-    const uint32_t nw = blocks * kSelWaves, gw = blockIdx.x * kSelWaves + wave;
+    const uint32_t n = g.n, ntiles = tiles_in(n);
+    const uint32_t nw = blocks * kSelWaves, gw = me * kSelWaves + wave;
     const bool uniform = (mode & kModeUniform) != 0u;
-    if (t == 0) *dead = 0u;
-    uint32_t round = 0, T, bin;
+    uint32_t T, bin;
     auto runs_of = [&](uint32_t tile) { return uniform ? uniform_runs(tile, n) : sc.tile_runs[tile]; };
     for (int b = t; b < kBins1; b += kSelThreads) hist[b] = 0u;
     __syncthreads();
@@ -1069,7 +1079,7 @@ __device__ __forceinline__ void slow_routes(const GroupView &g, float *st, Paylo
         __syncthreads();
         flush_fine(hist, sc.hist + kHist2, kBins2);
         if (!grid_barrier(sc.sync + kSyncArrive, blocks, ++round, dead, status, sc.spin_limit)) return;
-        if (blockIdx.x == 0) for (int b = t; b < kBins1; b += kSelThreads) sc.hist[kHist1 + b] = 0u;    // every block has resolved level 1
+        if (me == 0) for (int b = t; b < kBins1; b += kSelThreads) sc.hist[kHist1 + b] = 0u;    // every block has resolved level 1
         resolve_block<kBins2>(sc.hist + kHist2, need, bin, need, res);
         lo += bin << 10;
         for (int b = t; b < kBins3; b += kSelThreads) hist[b] = 0u;
@@ -1085,7 +1095,7 @@ __device__ __forceinline__ void slow_routes(const GroupView &g, float *st, Paylo
     __syncthreads();
     flush_fine(hist, sc.hist + kHist3, kBins3);
     if (!grid_barrier(sc.sync + kSyncArrive, blocks, ++round, dead, status, sc.spin_limit)) return;
-    if (!(mode & kModeFast) && blockIdx.x == 0) for (int b = t; b < kBins2; b += kSelThreads) sc.hist[kHist2 + b] = 0u;
+    if (!(mode & kModeFast) && me == 0) for (int b = t; b < kBins2; b += kSelThreads) sc.hist[kHist2 + b] = 0u;
     resolve_block<kBins3>(sc.hist + kHist3, need, bin, need, res);
     T = lo + bin;
     // ---- kept candidates per tile
@@ -1099,10 +1109,10 @@ __device__ __forceinline__ void slow_routes(const GroupView &g, float *st, Paylo
         if (lane == 0) sc.tile_cnt[tile] = ngt | (neq << 16);              // a tile holds at most 4096 candidates
     }
     if (!grid_barrier(sc.sync + kSyncArrive, blocks, ++round, dead, status, sc.spin_limit)) return;
-    if (blockIdx.x == 0) for (int b = t; b < kBins3; b += kSelThreads) sc.hist[kHist3 + b] = 0u;
+    if (me == 0) for (int b = t; b < kBins3; b += kSelThreads) sc.hist[kHist3 + b] = 0u;
     uint32_t *idx = reinterpret_cast<uint32_t *>(reinterpret_cast<uint8_t *>(hdr) + kHeaderBytes);
     float *val = reinterpret_cast<float *>(idx + k);
-    if (blockIdx.x == 0 && t == 0) {
+    if (me == 0 && t == 0) {
         put_sparse_header(hdr, ALGO, n, k);
         SelectState s;
         s.lo = T; s.mode = mode; s.need = need;
@@ -1286,15 +1296,19 @@ __device__ __forceinline__ uint32_t select_tile(const SparseScratch &sc, TileAhe
 }
 
 // The select kernel: sixteen tiles per block, one wavefront each; the window is read once per block.
-__global__ __launch_bounds__(kSelThreads) void lean_select_k(GroupView g, uint64_t k, SparseScratch sc)
+template <class SRC>
+__global__ __launch_bounds__(kSelThreads) void lean_select_k(SRC src)
 {
     __shared__ uint32_t wtot[kSelWaves];
     __shared__ uint32_t verdict[8];              // found, bin, rest lo, rest hi, candidates lo, hi, keys in the bin
     __shared__ UEntry members[kSelWaves][kMemberBuf];
     __shared__ uint32_t wabove[kSelWaves];
     const uint32_t t = threadIdx.x, lane = t & 63u, wave = __builtin_amdgcn_readfirstlane(t >> 6);
-    const uint32_t ntiles = (g.n + (uint32_t)kTile - 1u) / (uint32_t)kTile;
-    const uint32_t tile = blockIdx.x * kSelWaves + wave;
+    const SparseJob job = src.template job<BLK_SELECT>();
+    const SparseScratch &sc = job.sc;
+    const uint64_t k = job.k;
+    const uint32_t ntiles = tiles_in(job.g.n);
+    const uint32_t tile = job.block * kSelWaves + wave;
     // everything is asked for up front: what there is to know of the tile, the hint record, the window
     TileAhead a0;
     look_ahead(sc, tile, tile < ntiles, a0);
@@ -1334,8 +1348,8 @@ __global__ __launch_bounds__(kSelThreads) void lean_select_k(GroupView g, uint64
     __syncthreads();
     const bool found = verdict[0] != 0u;
     const uint32_t bin = verdict[1];
-    const bool first = blockIdx.x == 0 && t == 0;
-    if (first) {
+    const bool first = job.block == 0 && t == 0;
+    if (first && job.reports) {
         sc.sync[kSyncLastBin] = found ? verdict[6] : 0u;                // diagnostics (mc_select_stats)
         sc.sync[kSyncLastCands] = verdict[4];
     }
@@ -1364,7 +1378,7 @@ __global__ __launch_bounds__(kSelThreads) void lean_select_k(GroupView g, uint64
             uint32_t sum = 0;
 #pragma unroll
             for (int w = 0; w < kSelWaves; ++w) sum += wabove[w];
-            sc.blk_cnt[blockIdx.x] = sum;                          // sixteen tiles hold at most 65536 candidates
+            sc.blk_cnt[job.block] = sum;                          // sixteen tiles hold at most 65536 candidates
         }
         return;
     }
@@ -1383,15 +1397,68 @@ __global__ __launch_bounds__(kSelThreads) void lean_select_k(GroupView g, uint64
 // tiles per wavefront: 13 .. 30 us instead of 7 .. 10), inside the emit kernel to 108 registers and two rounds of
 // blocks.  On the lean route this kernel reads one word and leaves (4 us).
 template <int ALGO, bool EF, bool FROM_STATE, bool RANDOM>
-__global__ __launch_bounds__(kSelThreads) void sparse_slow_k(GroupView g, float *st, PayloadHeader *hdr, uint64_t k, SparseScratch sc,
-                                                             RngKey rng, int *status)
+__global__ __launch_bounds__(kSelThreads) void sparse_slow_k(OneSparse src, RngKey rng, int *status)
 {
     __shared__ __attribute__((aligned(16))) uint32_t hist[kBins1];
     __shared__ uint32_t pfx[2 * kRoundTiles];
     __shared__ uint32_t small[64];
-    const SelectState s0 = sc.sel[0];
+    const SelectState s0 = src.sc.sel[0];
     if (s0.mode & kModeLean) return;
-    slow_routes<ALGO, EF, FROM_STATE, RANDOM>(g, st, hdr, k, sc, rng, s0.mode, s0.lo, s0.need, gridDim.x, status, hist, pfx, small);
+    if (threadIdx.x == 0) small[4] = 0u;
+    __syncthreads();
+    uint32_t round = 0;
+    slow_routes<ALGO, EF, FROM_STATE, RANDOM>(src.g, src.st, src.hdr, src.k, src.sc, rng, s0.mode, s0.lo, s0.need, blockIdx.x, gridDim.x, round,
+                                              status, hist, pfx, small);
+}
+
+// The same for a launch over all groups.  Every block looks at the verdicts of all groups, 1024 at a time, and lists
+// those that need more than the window.  A group of at most kSoloTiles tiles is one block's work -- no barrier
+// between blocks, and many such groups at once, as in a first call of a layer-wise partition --, a larger one that of
+// all blocks, one group after the other.
+constexpr uint32_t kSoloTiles = 64;
+template <int ALGO, bool EF, bool FROM_STATE, bool RANDOM>
+__global__ __launch_bounds__(kSelThreads) void sparse_slow_all_k(AllSparse src, RngKey rng, int *status)
+{
+    __shared__ __attribute__((aligned(16))) uint32_t hist[kBins1];
+    __shared__ uint32_t pfx[2 * kRoundTiles];
+    __shared__ uint32_t small[64];
+    __shared__ uint32_t slow[kSelThreads];
+    __shared__ uint32_t waves[kSelWaves];
+    const uint32_t t = threadIdx.x, lane = t & 63u, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    uint32_t round = 0;
+    for (uint32_t q0 = 0; q0 < src.tb.y; q0 += kSelThreads) {
+        const uint32_t q = q0 + t;
+        bool need = false;
+        if (q < src.tb.y) need = src.tb.groups[q].n != 0u && !(src.all.sel[(size_t)q * 4].mode & kModeLean);
+        const uint64_t b = __builtin_amdgcn_ballot_w64(need);
+        if (lane == 0) waves[wave] = (uint32_t)__popcll(b);
+        if (t == 0) small[4] = 0u;
+        __syncthreads();
+        uint32_t before = 0, count = 0;
+#pragma unroll
+        for (int w = 0; w < kSelWaves; ++w) { if ((uint32_t)w < wave) before += waves[w]; count += waves[w]; }
+        if (need) slow[before + lanes_below(b)] = q;
+        __syncthreads();
+        if (count == 0) continue;
+        for (int large = 0; large < 2; ++large) {
+            uint32_t turn = 0;                       // which of the small groups this is: block `turn` takes it
+            for (uint32_t i = 0; i < count; ++i) {
+                const uint32_t g = __builtin_amdgcn_readfirstlane(slow[i]);
+                const bool solo = tiles_in(src.tb.groups[g].n) <= kSoloTiles;
+                if (solo == (large != 0)) continue;
+                if (solo && turn++ % gridDim.x != blockIdx.x) continue;
+                const SparseJob job = src.group_job(g);
+                const SelectState s0 = job.sc.sel[0];
+                const uint32_t passed = round;       // the barriers that all blocks have passed together: a solo group's do not count
+                slow_routes<ALGO, EF, FROM_STATE, RANDOM>(job.g, job.st, job.hdr, job.k, job.sc, rng, s0.mode, s0.lo, s0.need,
+                                                          solo ? 0u : blockIdx.x, solo ? 1u : gridDim.x, round, status, hist, pfx, small);
+                if (solo) round = passed;
+                __syncthreads();                     // the next group uses the same LDS
+                if (small[4]) return;                // a barrier was not passed
+            }
+        }
+        __syncthreads();
+    }
 }
 
 // Emit, lean route.  One candidate per lane (a chunk's head): gt0 / eq0 count the keys above / equal to T before it
@@ -1466,9 +1533,8 @@ constexpr int kUPer = 4;
 constexpr int kUSpec = 4 * kUPer;      // ... which covers the first kUSpec entries of every sublist
 static_assert(4 * kUSub == kEmitThreads, "four threads per sublist");
 
-template <int ALGO, bool EF>
-__global__ __launch_bounds__(kEmitThreads) void lean_emit_k(uint32_t n, uint32_t ntiles, float *st, PayloadHeader *hdr, uint64_t k,
-                                                            SparseScratch sc)
+template <int ALGO, bool EF, class SRC>
+__global__ __launch_bounds__(kEmitThreads) void lean_emit_k(SRC src)
 {
     __shared__ uint32_t hist[kBins3], coarse[64];          // the listed keys' 11 open bits, and the same 32 bins at a time
     __shared__ uint32_t small[4];
@@ -1476,13 +1542,22 @@ __global__ __launch_bounds__(kEmitThreads) void lean_emit_k(uint32_t n, uint32_t
     __shared__ uint32_t cgt[kEmitWaves + 1], ceq[kEmitWaves + 1];
     __shared__ uint32_t red[kEmitWaves];
     const uint32_t t = threadIdx.x, lane = t & 63u, wave = __builtin_amdgcn_readfirstlane(t >> 6);
-    const uint32_t tile = blockIdx.x * kEmitWaves + wave;
+    const SparseJob job = src.template job<BLK_EMIT>();
+    const SparseScratch &sc = job.sc;
+    float *st = job.st;
+    PayloadHeader *hdr = job.hdr;
+    const uint64_t k = job.k;
+    const uint32_t n = job.g.n, ntiles = tiles_in(n);
+    const uint32_t tile = job.block * kEmitWaves + wave;
     const bool live = tile < ntiles;
     // ---- everything that needs no other load to be located is asked for now
     const uint64_t runs = live ? sc.tile_runs[tile] : 0ull;
     const SelectState s0 = sc.sel[0];
     const uint32_t ucnt = wave == 0 ? sc.ucount[lane * kUCountStride] : 0u;
-    UEntry spec[kUPer];                                    // entries (t % 4) kUPer ... of sublist t / 4, if it has that many
+    // entries (t % 4) kUPer ... of sublist t / 4, if it has that many.  (A group of fewer tiles than kUSub has as many
+    // sublists as tiles; what is read past them, of the next groups' or of the padding behind the last, is not used.
+    // A condition around these loads cost the kernel 0.8 us of 11.)
+    UEntry spec[kUPer];
 #pragma unroll
     for (int i = 0; i < kUPer; ++i) spec[i] = sc.ulist[(size_t)(t / 4u) * kUCap + (t % 4u) * kUPer + i];
     uint32_t hb[kWavesPerBlock], hl[kWavesPerBlock];
@@ -1510,10 +1585,10 @@ __global__ __launch_bounds__(kEmitThreads) void lean_emit_k(uint32_t n, uint32_t
     // keys above the bin in the select blocks (sixteen tiles each) before this tile's, then in the tiles before it in its own
     const uint32_t sblock = tile / (uint32_t)kSelWaves, sfirst = sblock * (uint32_t)kSelWaves;
     uint32_t before = 0;
-    for (uint32_t b = t; b < blockIdx.x / (uint32_t)(kSelWaves / kEmitWaves); b += kEmitThreads) before += sc.blk_cnt[b];
+    for (uint32_t b = t; b < job.block / (uint32_t)(kSelWaves / kEmitWaves); b += kEmitThreads) before += sc.blk_cnt[b];
     uint32_t mine = live && sfirst + lane < tile ? sc.tile_cnt[sfirst + lane] : 0u;
     // the select kernel is done with the window: all blocks clear it together
-    for (uint32_t b = blockIdx.x * kEmitThreads + t; b < (uint32_t)(kWinCopies * kBinsW + kOpenCopies); b += gridDim.x * kEmitThreads)
+    for (uint32_t b = job.block * kEmitThreads + t; b < (uint32_t)(kWinCopies * kBinsW + kOpenCopies); b += job.blocks * kEmitThreads)
         sc.hist[b < (uint32_t)(kWinCopies * kBinsW) ? kHistW + b : kHistOpen - kWinCopies * kBinsW + b] = 0u;
     if (!(s0.mode & kModeLean)) return;                 // (the slow routes have written the payload themselves)
     const uint32_t lo = s0.lo;
@@ -1579,7 +1654,7 @@ __global__ __launch_bounds__(kEmitThreads) void lean_emit_k(uint32_t n, uint32_t
     __syncthreads();
     const uint32_t T = lo + small[0], need = small[1];
     // the list's kept keys, by where they lie: before this block, or in its tile j (bucket j + 1)
-    const uint32_t first = blockIdx.x * (uint32_t)(kEmitWaves * kTile);
+    const uint32_t first = job.block * (uint32_t)(kEmitWaves * kTile);
     auto classify = [&](const UEntry &x) {
         const uint32_t key = x.bits & 0x7FFFFFFFu;
         if (key >= T) {
@@ -1600,7 +1675,7 @@ __global__ __launch_bounds__(kEmitThreads) void lean_emit_k(uint32_t n, uint32_t
     mine = wave_total(wave_scan_incl(mine));
     if (lane == 0) red[wave] = before;
     __syncthreads();
-    if (blockIdx.x == 0 && t == 0) { put_sparse_header(hdr, ALGO, n, k); publish_hint(sc, T); record_sent_key<ALGO, EF>(st, T); }
+    if (job.block == 0 && t == 0) { put_sparse_header(hdr, ALGO, n, k); publish_hint(sc, T); record_sent_key<ALGO, EF>(st, T); }
     if (!live) return;
     uint64_t gt0 = mine;
     uint32_t eq0;
@@ -1661,37 +1736,55 @@ __global__ __launch_bounds__(kEmitThreads) void lean_emit_k(uint32_t n, uint32_t
     }
 }
 
-template <int ALGO, bool EF, bool CAPPED>
-static void sparse_compress_t(const LaunchCtx &lc, const GroupView &g, float *st, float momentum, uint64_t k, uint64_t need,
-                              PayloadHeader *hdr, const SparseScratch &sc, const RngKey &rng, const SampleRule &smp,
-                              uint32_t sync_blocks, int *status)
+// the slow routes of one group, or of all
+template <int ALGO, bool EF>
+static void launch_slow(const LaunchCtx &lc, uint32_t blocks, const OneSparse &src, const RngKey &rng, int *status)
 {
-    constexpr bool FS = (ALGO == MC_ALGO_DGC) || EF;
-    constexpr bool RND = ALGO == MC_ALGO_RANDK;
-    const uint32_t nt = tiles_of(g.n), nch = chunks_of(g.n);
-    const uint32_t sblocks = (nch + 15) / 16 < 256 ? (nch + 15) / 16 : 256;      // enough to stream the group in a refill
-    dim3 grid(nt), block(kBlock), cgrid((nt + kWavesPerBlock - 1) / kWavesPerBlock);
+    MC_LAUNCH((sparse_slow_k<ALGO, EF, ALGO == MC_ALGO_DGC || EF, ALGO == MC_ALGO_RANDK>), dim3(blocks), dim3(kSelThreads), lc, src, rng, status);
+}
+template <int ALGO, bool EF>
+static void launch_slow(const LaunchCtx &lc, uint32_t blocks, const AllSparse &src, const RngKey &rng, int *status)
+{
+    MC_LAUNCH((sparse_slow_all_k<ALGO, EF, ALGO == MC_ALGO_DGC || EF, ALGO == MC_ALGO_RANDK>), dim3(blocks), dim3(kSelThreads), lc, src, rng, status);
+}
+
+template <int ALGO, bool EF, class SRC>
+static void sparse_compress_t(const LaunchCtx &lc, const SRC &src, const SparseBlocks &nb, const SparseCall &call)
+{
+    const RngKey rng{call.seed, call.worker, call.iter_lo};
     prof_begin(lc, K_SPARSE_ACCUM);
-    MC_LAUNCH((sparse_accum_k<ALGO, EF>), grid, block, lc, g, st, momentum, sc, rng, smp);
+    MC_LAUNCH((sparse_accum_k<ALGO, EF, SRC>), dim3(nb.tiles), dim3(kBlock), lc, src, call.momentum, rng, (SampleRule{0u, 0u, 0u}));
     prof_end(lc, K_SPARSE_ACCUM);
-    if (!CAPPED) {
-        // the two-kernel tail; its slow routes run on at most `sync_blocks` blocks, which the device holds at once
-        const uint32_t sblocks = (nt + kSelWaves - 1) / kSelWaves, eblocks = (nt + kEmitWaves - 1) / kEmitWaves;
-        // the slow routes run on blocks that the device holds at once: one per compute unit
-        const uint32_t sync = std::max(1u, std::min(std::min(sync_blocks, sblocks), (uint32_t)(kRoundTiles / kSelWaves)));
-        prof_begin(lc, K_LEAN_SELECT);
-        MC_LAUNCH(lean_select_k, dim3(sblocks), dim3(kSelThreads), lc, g, k, sc);
-        prof_end(lc, K_LEAN_SELECT);
-        prof_begin(lc, K_SPARSE_SLOW);
-        MC_LAUNCH((sparse_slow_k<ALGO, EF, FS, RND>), dim3(sync), dim3(kSelThreads), lc, g, st, hdr, k, sc, rng, status);
-        prof_end(lc, K_SPARSE_SLOW);
-        prof_begin(lc, K_LEAN_EMIT);
-        MC_LAUNCH((lean_emit_k<ALGO, EF>), dim3(eblocks), dim3(kEmitThreads), lc, g.n, nt, st, hdr, k, sc);
-        prof_end(lc, K_LEAN_EMIT);
-        return;
-    }
+    // the two-kernel tail; its slow routes run on blocks that the device holds at once: one per compute unit
+    const uint32_t sync = std::max(1u, std::min(std::min(call.sync_blocks, nb.select), (uint32_t)(kRoundTiles / kSelWaves)));
+    prof_begin(lc, K_LEAN_SELECT);
+    MC_LAUNCH(lean_select_k<SRC>, dim3(nb.select), dim3(kSelThreads), lc, src);
+    prof_end(lc, K_LEAN_SELECT);
+    prof_begin(lc, K_SPARSE_SLOW);
+    launch_slow<ALGO, EF>(lc, sync, src, rng, call.status);
+    prof_end(lc, K_SPARSE_SLOW);
+    prof_begin(lc, K_LEAN_EMIT);
+    MC_LAUNCH((lean_emit_k<ALGO, EF, SRC>), dim3(nb.emit), dim3(kEmitThreads), lc, src);
+    prof_end(lc, K_LEAN_EMIT);
+}
+
+// DGC with a sampled threshold, one group: src.k is the payload's capacity, the threshold the sample_need-th largest key of the
+// sample, which starts at sample_first
+static void sampled_dgc(const LaunchCtx &lc, const OneSparse &src, const SparseCall &call)
+{
+    const GroupView &g = src.g;
+    const SparseScratch &sc = src.sc;
+    const RngKey rng{call.seed, call.worker, call.iter_lo};
+    const uint32_t stride = call.sample_stride;
+    const SampleRule smp{stride, call.sample_first, stride > 1 ? (uint32_t)((1ull << 32) / stride) : 0u};
+    const uint32_t nt = tiles_in(g.n), nch = chunks_of(g.n);
+    const uint32_t sblocks = (nch + 15) / 16 < 256 ? (nch + 15) / 16 : 256;      // enough to stream the group in a refill
+    dim3 block(kBlock), cgrid((nt + kWavesPerBlock - 1) / kWavesPerBlock);
+    prof_begin(lc, K_SPARSE_ACCUM);
+    MC_LAUNCH((sparse_accum_k<MC_ALGO_DGC, true, OneSparse>), dim3(nt), block, lc, src, call.momentum, rng, smp);
+    prof_end(lc, K_SPARSE_ACCUM);
     prof_begin(lc, K_SPARSE_SEED);
-    MC_LAUNCH((sparse_seed_k<FS, RND>), dim3(sblocks), dim3(kSeedThreads), lc, g, st, need, sc, rng, smp);
+    MC_LAUNCH((sparse_seed_k<true, false>), dim3(sblocks), dim3(kSeedThreads), lc, g, src.st, call.sample_need, sc, rng, smp);
     prof_end(lc, K_SPARSE_SEED);
     prof_begin(lc, K_CAND_HIST2);
     MC_LAUNCH(cand_hist_k<2>, cgrid, block, lc, g.n, nt, sc, smp);
@@ -1703,29 +1796,23 @@ static void sparse_compress_t(const LaunchCtx &lc, const GroupView &g, float *st
     MC_LAUNCH(cand_count_k, cgrid, block, lc, g.n, nt, sc);
     prof_end(lc, K_CAND_COUNT);
     prof_begin(lc, K_CAND_EMIT);
-    MC_LAUNCH((cand_emit_k<ALGO, EF, CAPPED>), cgrid, block, lc, g.n, nt, st, hdr, k, sc);
+    MC_LAUNCH((cand_emit_k<MC_ALGO_DGC, true, true>), cgrid, block, lc, g.n, nt, src.st, src.hdr, src.k, sc);
     prof_end(lc, K_CAND_EMIT);
 }
+static void sampled_dgc(const LaunchCtx &, const AllSparse &, const SparseCall &) {}      // (never asked for: the sampled threshold is taken group by group)
 
-// k: entries of the payload (the exact k, or the capacity when the threshold comes from a sample);
-// sample_stride > 0: DGC with a sampled threshold, the sample starts at sample_first and the threshold is its
-// sample_need-th largest key
-void launch_sparse_compress(const LaunchCtx &lc, int algo, const GroupView &g, bool ef, float *state_f, float momentum,
-                            uint64_t k, PayloadHeader *hdr, const SparseScratch &sc, uint64_t seed, uint32_t worker, uint32_t iter_lo,
-                            uint32_t sample_stride, uint32_t sample_first, uint64_t sample_need, uint32_t sync_blocks, int *status)
+template <class SRC>
+void launch_sparse_compress(const LaunchCtx &lc, int algo, const SRC &src, const SparseBlocks &nb, bool ef, const SparseCall &call)
 {
-    if (g.n == 0) return;
-    const RngKey rng{seed, worker, iter_lo};
-    SampleRule smp{0u, 0u, 0u};
-    if (algo == MC_ALGO_DGC && sample_stride) {
-        smp.stride = sample_stride; smp.first = sample_first;
-        smp.inv = sample_stride > 1 ? (uint32_t)((1ull << 32) / sample_stride) : 0u;
-        sparse_compress_t<MC_ALGO_DGC, true, true>(lc, g, state_f, momentum, k, sample_need, hdr, sc, rng, smp, sync_blocks, status);
-    } else if (algo == MC_ALGO_DGC) sparse_compress_t<MC_ALGO_DGC, true, false>(lc, g, state_f, momentum, k, k, hdr, sc, rng, smp, sync_blocks, status);
-    else if (algo == MC_ALGO_RANDK) sparse_compress_t<MC_ALGO_RANDK, true, false>(lc, g, state_f, momentum, k, k, hdr, sc, rng, smp, sync_blocks, status);
-    else if (ef) sparse_compress_t<MC_ALGO_TOPK, true, false>(lc, g, state_f, momentum, k, k, hdr, sc, rng, smp, sync_blocks, status);
-    else sparse_compress_t<MC_ALGO_TOPK, false, false>(lc, g, state_f, momentum, k, k, hdr, sc, rng, smp, sync_blocks, status);
+    if (nb.tiles == 0) return;
+    if (algo == MC_ALGO_DGC && call.sample_stride) sampled_dgc(lc, src, call);
+    else if (algo == MC_ALGO_DGC) sparse_compress_t<MC_ALGO_DGC, true>(lc, src, nb, call);
+    else if (algo == MC_ALGO_RANDK) sparse_compress_t<MC_ALGO_RANDK, true>(lc, src, nb, call);
+    else if (ef) sparse_compress_t<MC_ALGO_TOPK, true>(lc, src, nb, call);
+    else sparse_compress_t<MC_ALGO_TOPK, false>(lc, src, nb, call);
 }
+template void launch_sparse_compress<OneSparse>(const LaunchCtx &, int, const OneSparse &, const SparseBlocks &, bool, const SparseCall &);
+template void launch_sparse_compress<AllSparse>(const LaunchCtx &, int, const AllSparse &, const SparseBlocks &, bool, const SparseCall &);
 
 // ---------------------------------------------------------------------------
 // Sparse decompress-and-sum.  Every worker's indices ascend, so a 4096-element
@@ -1744,17 +1831,20 @@ constexpr int kSparseRounds = 3;
 
 // k64: entries a payload has room for (the exact k, or the capacity when DGC takes its threshold from a sample: the
 // header then says how many are in use and repeats the capacity)
-__global__ __launch_bounds__(kBlock) void sparse_decompress_k(int algo, GroupView out, PayloadPtrs pl, int W, float alpha,
-                                                              uint64_t k64, uint32_t ntiles, int *status, int capped)
+template <class SRC>
+__global__ __launch_bounds__(kBlock) void sparse_decompress_k(int algo, SRC src, int W, float alpha, int *status, int capped)
 {
     __shared__ float acc[kTile];
+    const auto job = src.template job<BLK_TILE>();
+    const GroupView &out = job.out;
+    const uint64_t k64 = job.k;
     const uint32_t k = (uint32_t)k64;
-    if (blockIdx.x == 0 && (int)threadIdx.x < W) {
-        const PayloadHeader *h = reinterpret_cast<const PayloadHeader *>(pl.p[threadIdx.x]);
+    if (job.block == job.last && (int)threadIdx.x < W) {
+        const PayloadHeader *h = reinterpret_cast<const PayloadHeader *>(job.payload_of_lane(threadIdx.x));
         const bool fits = capped ? h->k <= k64 && h->levels == (uint32_t)k64 : h->k == k64;
         if (h->magic != kMagic || h->algo != (uint32_t)algo || h->n != (uint64_t)out.n || !fits) *status = 1;
     }
-    const uint32_t tile = my_tile_index();
+    const uint32_t tile = job.block;
     const uint32_t tb = tile * (uint32_t)kTile;
     const uint32_t t = threadIdx.x;
     const Chunk c = my_chunk(out.n, tile);
@@ -1764,7 +1854,7 @@ __global__ __launch_bounds__(kBlock) void sparse_decompress_k(int algo, GroupVie
         // (the per-batch test below only sees its own eight), and zero-filled as with one batch
         bool any = false;
         for (int w = 0; w < W; ++w) {
-            const uint32_t *dir = reinterpret_cast<const uint32_t *>(pl.p[w] + kHeaderBytes + 8u * k64);
+            const uint32_t *dir = reinterpret_cast<const uint32_t *>(job.payload(w) + kHeaderBytes + 8u * k64);
             const uint32_t f = ld_uniform(dir + tile), l = ld_uniform(dir + tile + 1u);
             any = any || (l < k ? l : k) > (f < k ? f : k);
         }
@@ -1785,7 +1875,7 @@ __global__ __launch_bounds__(kBlock) void sparse_decompress_k(int algo, GroupVie
             lo[b] = hi[b] = 0;
             if (w0 + b < W) {
                 // block-uniform addresses, kept on the scalar path whatever the compiler makes of the rest
-                const uint32_t *dir = reinterpret_cast<const uint32_t *>(pl.p[w0 + b] + kHeaderBytes + 8u * k64);
+                const uint32_t *dir = reinterpret_cast<const uint32_t *>(job.payload(w0 + b) + kHeaderBytes + 8u * k64);
                 const uint32_t f = ld_uniform(dir + tile), l = ld_uniform(dir + tile + 1u);
                 lo[b] = f < k ? f : k;
                 hi[b] = l < k ? l : k;
@@ -1820,7 +1910,7 @@ __global__ __launch_bounds__(kBlock) void sparse_decompress_k(int algo, GroupVie
                 float vv[kSparseBatch];
 #pragma unroll
                 for (int b = 0; b < kSparseBatch; ++b) {
-                    const uint32_t *idx = reinterpret_cast<const uint32_t *>(pl.p[b < W ? b : 0] + kHeaderBytes);
+                    const uint32_t *idx = reinterpret_cast<const uint32_t *>(job.payload(b < W ? b : 0) + kHeaderBytes);
                     const float *val = reinterpret_cast<const float *>(idx + k);
                     const uint32_t e = lo[b] + c.lane;
                     ix[b] = 0xFFFFFFFFu; vv[b] = 0.0f;
@@ -1857,7 +1947,7 @@ __global__ __launch_bounds__(kBlock) void sparse_decompress_k(int algo, GroupVie
         float vv[kSparseBatch][kSparseRounds];
 #pragma unroll
         for (int b = 0; b < kSparseBatch; ++b) {
-            const uint32_t *idx = reinterpret_cast<const uint32_t *>(pl.p[w0 + b < W ? w0 + b : 0] + kHeaderBytes);
+            const uint32_t *idx = reinterpret_cast<const uint32_t *>(job.payload(w0 + b < W ? w0 + b : 0) + kHeaderBytes);
             const float *val = reinterpret_cast<const float *>(idx + k);
 #pragma unroll
             for (int r = 0; r < kSparseRounds; ++r) {
@@ -1875,7 +1965,7 @@ __global__ __launch_bounds__(kBlock) void sparse_decompress_k(int algo, GroupVie
                     if (ix[b][r] != 0xFFFFFFFFu && local < (uint32_t)kTile) acc[local] = acc[local] + vv[b][r];
                 }
                 // more than 1024 entries of one worker in the tile
-                const uint32_t *idx = reinterpret_cast<const uint32_t *>(pl.p[w0 + b] + kHeaderBytes);
+                const uint32_t *idx = reinterpret_cast<const uint32_t *>(job.payload(w0 + b) + kHeaderBytes);
                 const float *val = reinterpret_cast<const float *>(idx + k);
                 for (uint32_t e = lo[b] + kSparseRounds * kBlock + t; e < hi[b]; e += kBlock) {
                     const uint32_t l2 = idx[e] - tb;
@@ -1893,14 +1983,15 @@ __global__ __launch_bounds__(kBlock) void sparse_decompress_k(int algo, GroupVie
     store_seg(out, c, v, entry);
 }
 
-void launch_sparse_decompress(const LaunchCtx &lc, int algo, const GroupView &out, const PayloadPtrs &pl, int W,
-                              float alpha, uint64_t k, int *status, bool capped)
+template <class SRC>
+void launch_sparse_decompress(const LaunchCtx &lc, int algo, const SRC &src, uint32_t tiles, int W, float alpha, int *status, bool capped)
 {
-    if (out.n == 0) return;
-    const uint32_t nt = tiles_of(out.n);
+    if (tiles == 0) return;
     prof_begin(lc, K_SPARSE_DECOMPRESS);
-    MC_LAUNCH(sparse_decompress_k, dim3(nt), dim3(kBlock), lc, algo, out, pl, W, alpha, k, nt, status, capped ? 1 : 0);
+    MC_LAUNCH(sparse_decompress_k<SRC>, dim3(tiles), dim3(kBlock), lc, algo, src, W, alpha, status, capped ? 1 : 0);
     prof_end(lc, K_SPARSE_DECOMPRESS);
 }
+template void launch_sparse_decompress<OneDecompress>(const LaunchCtx &, int, const OneDecompress &, uint32_t, int, float, int *, bool);
+template void launch_sparse_decompress<AllDecompress>(const LaunchCtx &, int, const AllDecompress &, uint32_t, int, float, int *, bool);
 
 }  // namespace mc

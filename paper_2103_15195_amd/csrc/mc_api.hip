@@ -18,6 +18,7 @@ namespace {
 constexpr uint64_t kMaxGroupElems = (1ull << 32) - (1ull << 24);
 constexpr uint32_t kBarrierSpinLimit = 1u << 21;     // polls (about a microsecond each) before a block of the slow selection routes gives up waiting
 constexpr int kPtrSlots = 256;           // cached device copies of per-call tensor address lists
+constexpr int kAllSlots = 64;            // ... and of the address lists of calls over all groups
 
 struct Group {
     int32_t t0 = 0, t1 = 0;              // tensor range [t0, t1) of the model's list
@@ -36,6 +37,17 @@ struct PtrSlot {
     uintptr_t *dev = nullptr;            // tensor addresses
     uintptr_t *dev_chunk = nullptr;      // per-chunk direct addresses derived from them
 };
+
+// The address list of a call over all groups.  W = 0: compress (tensors, a state and a payload per group), else
+// decompress-and-sum (tensors, W payloads per group).
+struct AllSlot {
+    int32_t W = -1;
+    uint64_t stamp = 0;
+    bool apart = false;                  // no buffer that the call writes overlaps another of its buffers
+    std::vector<uintptr_t> host;
+    uintptr_t *dev = nullptr, *dev_chunk = nullptr;
+};
+struct Span { uintptr_t from, to; bool written; };
 
 // ---- scratch of the allocation-free entry point (mc_compress_static) ------------------------------------
 // The per-tile reduction partials of the dense compressors (three arrays of one double per 4096-element tile:
@@ -93,6 +105,20 @@ struct mc_ctx {
     void *static_scratch = nullptr;     // this device's copy of the file-scope scratch array (mc_compress_static)
     std::vector<PtrSlot> slots;
     std::vector<uintptr_t> want;        // the address list of the call in progress (reserved at creation)
+    // calls over all groups (contexts of more than one)
+    bool own_scratch = false;           // sparsifiers: every group has a part of the scratch of its own
+    GroupConst *d_groups = nullptr;
+    uint32_t *d_block_group[BLK_KINDS] = {};
+    uint32_t all_blocks[BLK_KINDS] = {};
+    uint32_t last_group = 0;            // the last group that holds elements
+    size_t all_live = 0;
+    std::vector<int64_t> tensor_numel;  // elements of every tensor of the model
+    std::vector<uint32_t> first_tile, first_sub;       // per group, of its part of the sparsifiers' scratch
+    std::vector<AllSlot> all_slots;
+    std::vector<uintptr_t> want_all;
+    std::vector<Span> spans;
+    const SelectState *last_sel = nullptr;             // what the most recent sparse mc_compress recorded of its selection
+    uintptr_t *d_slots = nullptr, *d_all_slots = nullptr;     // the memory behind `slots` and `all_slots`
     uint64_t clock = 0;
     uint32_t sync_blocks = 1;           // blocks of 1024 threads the device holds at once for sure: one per compute unit
     Profiler prof;
@@ -185,6 +211,7 @@ struct DeviceGuard {
     ~DeviceGuard() { if (switched) (void)hipSetDevice(prev); }
 };
 
+static size_t lines(size_t addresses) { return (addresses + 31) / 32 * 32; }      // a table's size in addresses, so that the next one starts on a line
 static bool is_sparse(int algo) { return algo == MC_ALGO_TOPK || algo == MC_ALGO_DGC || algo == MC_ALGO_RANDK; }
 // n-element vectors of a group's state: the residual (DGC: v and u; SigNUM: the momentum; SignSGD: nothing)
 static uint32_t state_vectors(int algo) { return algo == MC_ALGO_DGC ? 2u : algo == MC_ALGO_SIGNSGD ? 0u : 1u; }
@@ -336,10 +363,8 @@ int mc_ctx_destroy(mc_ctx *ctx)
         if (g.d_seg_off) (void)hipFree(g.d_seg_off);
         if (g.d_chunk_seg) (void)hipFree(g.d_chunk_seg);
     }
-    for (PtrSlot &s : ctx->slots) {
-        if (s.dev) (void)hipFree(s.dev);
-        if (s.dev_chunk) (void)hipFree(s.dev_chunk);
-    }
+    void *tables[] = {ctx->d_slots, ctx->d_all_slots, ctx->d_groups, ctx->d_block_group[0], ctx->d_block_group[1], ctx->d_block_group[2], ctx->d_block_group[3]};
+    for (void *b : tables) if (b) (void)hipFree(b);
     if (ctx->d_partial) (void)hipFree(ctx->d_partial);
     void *sparse_bufs[] = {ctx->sparse.hist, ctx->sparse.sel, ctx->d_hints, ctx->sparse.cand_bits, ctx->sparse.cand_loc,
                            ctx->sparse.tile_runs, ctx->sparse.tile_cnt, ctx->sparse.blk_cnt, ctx->sparse.ulist, ctx->sparse.ucount,
@@ -384,6 +409,7 @@ int mc_ctx_create(mc_ctx **out, const mc_config *cfg, const int64_t *numel, int3
     int rc = MC_OK;
     try {
         ctx->groups.resize(y);
+        ctx->tensor_numel.assign(numel, numel + n_tensors);
         uint64_t goff = 0;
         for (int32_t j = 0; j < y && rc == MC_OK; ++j) {
             Group &g = ctx->groups[j];
@@ -414,28 +440,73 @@ int mc_ctx_create(mc_ctx **out, const mc_config *cfg, const int64_t *numel, int3
             ctx->max_live = std::max(ctx->max_live, g.live.size());
         }
         const size_t tiles = std::max<size_t>(ctx->max_tiles, 1);
-        if (rc == MC_OK && hipMalloc(&ctx->d_partial, 3 * tiles * sizeof(double)) != hipSuccess) rc = MC_ERR_ALLOC;
+        // ---- what a launch over all groups needs to know of them
+        const bool many = y > 1;
+        size_t all_tiles = 0, subs = 0;
+        std::vector<GroupConst> table((size_t)y);
+        ctx->first_tile.resize((size_t)y);
+        ctx->first_sub.resize((size_t)y);
+        std::vector<uint32_t> block_group[BLK_KINDS];
+        for (int32_t j = 0; j < y; ++j) {
+            const Group &g = ctx->groups[j];
+            const uint32_t nt = tiles_in(g.n);
+            const uint32_t blocks[BLK_KINDS] = {nt, plane_blocks(g.n), sparse_blocks(g.n).select, sparse_blocks(g.n).emit};
+            GroupConst &c = table[j];
+            c.seg_off = g.d_seg_off; c.chunk_seg = g.d_chunk_seg;
+            c.goff = g.goff; c.k = g.k; c.n = g.n; c.nseg = (uint32_t)g.live.size();
+            c.first_ptr = (uint32_t)ctx->all_live; c.first_sub = (uint32_t)subs;
+            ctx->first_tile[j] = (uint32_t)all_tiles; ctx->first_sub[j] = (uint32_t)subs;
+            for (int b = 0; b < BLK_KINDS; ++b) {
+                c.first[b] = ctx->all_blocks[b];
+                if (many) block_group[b].insert(block_group[b].end(), blocks[b], (uint32_t)j);
+                ctx->all_blocks[b] += blocks[b];
+            }
+            all_tiles += nt;
+            subs += std::min<uint32_t>(nt, kUSub);
+            ctx->all_live += g.live.size();
+            if (g.n) ctx->last_group = (uint32_t)j;
+        }
+        if (many && rc == MC_OK) {
+            if (hipMalloc(&ctx->d_groups, table.size() * sizeof(GroupConst)) != hipSuccess) rc = MC_ERR_ALLOC;
+            else if (hipMemcpy(ctx->d_groups, table.data(), table.size() * sizeof(GroupConst), hipMemcpyHostToDevice) != hipSuccess) rc = MC_ERR_DEVICE;
+            for (int b = 0; b < BLK_KINDS && rc == MC_OK; ++b) {
+                const size_t bytes = block_group[b].size() * sizeof(uint32_t);
+                if (bytes == 0) continue;
+                if (hipMalloc(&ctx->d_block_group[b], bytes) != hipSuccess) rc = MC_ERR_ALLOC;
+                else if (hipMemcpy(ctx->d_block_group[b], block_group[b].data(), bytes, hipMemcpyHostToDevice) != hipSuccess) rc = MC_ERR_DEVICE;
+            }
+        }
+        const size_t hist_words = kHistWords, slot_bytes = 6u * (size_t)kTile;
+        // A part of the scratch for every group lets the sparsifiers' calls over all groups run as one launch per step; a
+        // model for which that is more than 2 GiB of candidates (350 M elements) or a quarter of that in histograms or key
+        // lists is large enough per group to be taken one group at a time, in scratch of the size of the largest.
+        ctx->own_scratch = many && is_sparse(cfg->algo) && !cfg->dgc_sample_ppm && all_tiles > 0 && all_tiles * slot_bytes <= (size_t(2) << 30) &&
+                           (size_t)y * hist_words * sizeof(uint32_t) <= (size_t(512) << 20) && subs * kUCap * sizeof(UEntry) <= (size_t(512) << 20);
+        const size_t parts = ctx->own_scratch ? (size_t)y : 1, stiles = ctx->own_scratch ? all_tiles : tiles;
+        const size_t lists = ctx->own_scratch ? subs + kUSub : (size_t)kUSub;      // (the emit kernel looks at kUSub sublists of any group)
+        if (rc == MC_OK && hipMalloc(&ctx->d_partial, 3 * std::max(tiles, many ? all_tiles : 0) * sizeof(double)) != hipSuccess) rc = MC_ERR_ALLOC;
         if (rc == MC_OK && hipMalloc(&ctx->d_status, sizeof(int)) != hipSuccess) rc = MC_ERR_ALLOC;
         if (rc == MC_OK && hipMemset(ctx->d_status, 0, sizeof(int)) != hipSuccess) rc = MC_ERR_DEVICE;
         if (rc == MC_OK && is_sparse(cfg->algo)) {
             SparseScratch &sp = ctx->sparse;
-            const size_t hist_bytes = kHistWords * sizeof(uint32_t);
-            const size_t chunks = tiles * kWavesPerBlock, slots = chunks * kChunk;
-            if (hipMalloc(&sp.hist, hist_bytes) != hipSuccess || hipMalloc(&sp.sel, 4 * sizeof(SelectState)) != hipSuccess ||
+            const size_t hist_bytes = parts * hist_words * sizeof(uint32_t), sel_bytes = parts * 4 * sizeof(SelectState);
+            const size_t slots = stiles * kTile, count_bytes = parts * kUSub * kUCountStride * sizeof(uint32_t);
+            if (hipMalloc(&sp.hist, hist_bytes) != hipSuccess || hipMalloc(&sp.sel, sel_bytes) != hipSuccess ||
                 hipMalloc(&ctx->d_hints, (size_t)y * kHintWorkers * kHintWords * sizeof(uint32_t)) != hipSuccess ||
                 hipMalloc(&sp.cand_bits, slots * sizeof(uint32_t)) != hipSuccess ||
                 hipMalloc(&sp.cand_loc, slots * sizeof(uint16_t)) != hipSuccess ||
-                hipMalloc(&sp.tile_runs, tiles * sizeof(uint64_t)) != hipSuccess ||
-                hipMalloc(&sp.tile_cnt, tiles * sizeof(uint32_t)) != hipSuccess ||
-                hipMalloc(&sp.blk_cnt, (tiles + kWavesPerBlock - 1) / kWavesPerBlock * sizeof(uint32_t)) != hipSuccess ||
-                hipMalloc(&sp.ulist, (size_t)kUSub * kUCap * sizeof(UEntry)) != hipSuccess ||
-                hipMalloc(&sp.ucount, (size_t)kUSub * kUCountStride * sizeof(uint32_t)) != hipSuccess ||
+                hipMalloc(&sp.tile_runs, stiles * sizeof(uint64_t)) != hipSuccess ||
+                hipMalloc(&sp.tile_cnt, stiles * sizeof(uint32_t)) != hipSuccess ||
+                hipMalloc(&sp.blk_cnt, stiles * sizeof(uint32_t)) != hipSuccess ||
+                hipMalloc(&sp.ulist, lists * kUCap * sizeof(UEntry)) != hipSuccess ||
+                hipMalloc(&sp.ucount, count_bytes) != hipSuccess ||
                 hipMalloc(&sp.sync, 64 * sizeof(uint32_t)) != hipSuccess) rc = MC_ERR_ALLOC;
-            else if (hipMemset(sp.hist, 0, hist_bytes) != hipSuccess || hipMemset(sp.sel, 0, 4 * sizeof(SelectState)) != hipSuccess ||
+            else if (hipMemset(sp.hist, 0, hist_bytes) != hipSuccess || hipMemset(sp.sel, 0, sel_bytes) != hipSuccess ||
                      hipMemset(ctx->d_hints, 0, (size_t)y * kHintWorkers * kHintWords * sizeof(uint32_t)) != hipSuccess ||
-                     hipMemset(sp.tile_runs, 0, tiles * sizeof(uint64_t)) != hipSuccess ||
-                     hipMemset(sp.ucount, 0, (size_t)kUSub * kUCountStride * sizeof(uint32_t)) != hipSuccess ||
+                     hipMemset(sp.tile_runs, 0, stiles * sizeof(uint64_t)) != hipSuccess ||
+                     hipMemset(sp.ucount, 0, count_bytes) != hipSuccess ||
                      hipMemset(sp.sync, 0, 64 * sizeof(uint32_t)) != hipSuccess) rc = MC_ERR_DEVICE;
+            ctx->last_sel = sp.sel;
             int cus = 0;
             if (rc == MC_OK && (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ctx->device) != hipSuccess || cus < 1)) rc = MC_ERR_DEVICE;
             ctx->sync_blocks = (uint32_t)std::max(cus, 1);
@@ -443,16 +514,32 @@ int mc_ctx_create(mc_ctx **out, const mc_config *cfg, const int64_t *numel, int3
         }
         if (rc == MC_OK) {
             // the per-chunk address tables of all slots together stay below 256 MiB
-            const size_t per_slot = tiles * kWavesPerBlock * sizeof(uintptr_t);
-            ctx->slots.resize(std::min<size_t>(kPtrSlots, std::max<size_t>(4, (size_t(256) << 20) / per_slot)));
+            const size_t chunks = lines(tiles * kWavesPerBlock), per_slot = lines(std::max<size_t>(ctx->max_live, 1)) + chunks;
+            ctx->slots.resize(std::min<size_t>(kPtrSlots, std::max<size_t>(4, (size_t(256) << 20) / (chunks * sizeof(uintptr_t)))));
+            if (hipMalloc(&ctx->d_slots, ctx->slots.size() * per_slot * sizeof(uintptr_t)) != hipSuccess) rc = MC_ERR_ALLOC;
+            uintptr_t *at = ctx->d_slots;
             for (PtrSlot &s : ctx->slots) {
-                if (hipMalloc(&s.dev, std::max<size_t>(ctx->max_live, 1) * sizeof(uintptr_t)) != hipSuccess ||
-                    hipMalloc(&s.dev_chunk, tiles * kWavesPerBlock * sizeof(uintptr_t)) != hipSuccess) { rc = MC_ERR_ALLOC; break; }
+                s.dev = at; s.dev_chunk = at + (per_slot - chunks);
+                at += per_slot;
                 s.host.reserve(ctx->max_live);
             }
             ctx->want.reserve(ctx->max_live);
             ctx->prof.pending.reserve(1024);
             ctx->prof.pool.reserve(2048);
+        }
+        if (rc == MC_OK && many && all_tiles > 0) {
+            // lists of calls over all groups: a decompress-and-sum of the most workers needs the longest; 64 MiB in all
+            const size_t most = lines(ctx->all_live + (size_t)kMaxWorkers * y), chunks = lines(all_tiles * kWavesPerBlock);
+            ctx->all_slots.resize(std::min<size_t>(kAllSlots, std::max<size_t>(2, (size_t(64) << 20) / ((most + chunks) * sizeof(uintptr_t)))));
+            if (hipMalloc(&ctx->d_all_slots, ctx->all_slots.size() * (most + chunks) * sizeof(uintptr_t)) != hipSuccess) rc = MC_ERR_ALLOC;
+            uintptr_t *at = ctx->d_all_slots;
+            for (AllSlot &s : ctx->all_slots) {
+                s.dev = at; s.dev_chunk = at + most;
+                at += most + chunks;
+                s.host.reserve(most);
+            }
+            ctx->want_all.reserve(most);
+            ctx->spans.reserve(most);
         }
         // the device address of the static scratch array, looked up here with the context's device current
         if (rc == MC_OK && !(ctx->static_scratch = static_scratch_for(ctx->device))) rc = MC_ERR_DEVICE;
@@ -534,7 +621,105 @@ static GroupView group_view(mc_ctx *ctx, const LaunchCtx &lc, int32_t group, con
     return gv;
 }
 
+static GroupTable all_table(const mc_ctx *ctx, const AllSlot &slot)
+{
+    GroupTable tb{ctx->d_groups, {}, slot.dev, slot.dev_chunk, (uint32_t)ctx->all_live, (uint32_t)ctx->groups.size()};
+    for (int b = 0; b < BLK_KINDS; ++b) tb.block_group[b] = ctx->d_block_group[b];
+    return tb;
+}
+
+// The slot of the list in ctx->want_all (its buffers in ctx->spans), uploaded if it has not been seen before.
+static const AllSlot &all_slot(mc_ctx *ctx, const LaunchCtx &lc, int32_t W)
+{
+    const std::vector<uintptr_t> &want = ctx->want_all;
+    AllSlot *victim = &ctx->all_slots[0];
+    for (AllSlot &s : ctx->all_slots) {
+        if (s.W == W && s.host.size() == want.size() && std::memcmp(s.host.data(), want.data(), want.size() * sizeof(uintptr_t)) == 0) {
+            s.stamp = ++ctx->clock;
+            return s;
+        }
+        if (s.stamp < victim->stamp) victim = &s;
+    }
+    victim->W = W;
+    victim->stamp = ++ctx->clock;
+    victim->host = want;
+    // One group after the other, a call may use a buffer that an earlier group wrote; all at once it may not.
+    std::vector<Span> &spans = ctx->spans;
+    std::sort(spans.begin(), spans.end(), [](const Span &a, const Span &b) { return a.from < b.from; });
+    uintptr_t any = 0, written = 0;                  // how far the buffers so far reach, and those of them that are written
+    victim->apart = true;
+    for (const Span &s : spans) {
+        if (s.from == s.to) continue;
+        if (s.from < (s.written ? any : written)) { victim->apart = false; break; }
+        any = std::max(any, s.to);
+        if (s.written) written = std::max(written, s.to);
+    }
+    if (victim->apart) {
+        launch_upload_ptrs(lc, want.data(), victim->dev, (uint32_t)want.size());
+        launch_expand_all(lc, all_table(ctx, *victim), ctx->all_blocks[BLK_TILE], victim->dev_chunk);
+    }
+    return *victim;
+}
 static int check_launch() { return hipGetLastError() == hipSuccess ? MC_OK : MC_ERR_DEVICE; }
+
+}  // extern "C"
+
+static uint32_t qsgd_levels(const mc_config &cfg) { return cfg.algo == MC_ALGO_QSGD ? (1u << (cfg.qsgd_bits - 1)) - 1u : 0u; }
+
+template <class SRC>
+static void decompress_launch(mc_ctx *ctx, const LaunchCtx &lc, const SRC &src, uint32_t tiles, uint32_t planes, int32_t W, float alpha)
+{
+    const mc_config &cfg = ctx->cfg;
+    if (is_sparse(cfg.algo)) { launch_sparse_decompress(lc, cfg.algo, src, tiles, W, alpha, ctx->d_status, cfg.dgc_sample_ppm != 0); return; }
+    const bool by_word = cfg.algo != MC_ALGO_QSGD && cfg.algo != MC_ALGO_FP16;       // bit planes: 8192 elements per block
+    launch_dense_decompress(lc, cfg.algo, src, by_word ? planes : tiles, W, alpha, qsgd_levels(cfg), ctx->d_status);
+}
+
+// The kernels of a dense compressor over one group or all: `tiles` blocks of 4096 elements, `groups` groups.
+template <class SRC>
+static void dense_compress(const mc_config &cfg, const LaunchCtx &lc, const SRC &src, uint32_t tiles, uint32_t groups, uint32_t worker, uint32_t iter_lo)
+{
+    const bool ef = cfg.use_ef != 0;
+    const uint32_t levels = qsgd_levels(cfg), algo = (uint32_t)cfg.algo;
+    switch (cfg.algo) {
+    case MC_ALGO_EFSIGN:
+    case MC_ALGO_ONEBIT:
+    {
+        const bool means = cfg.algo == MC_ALGO_ONEBIT;
+        launch_sign_compress(lc, means ? SIGN_MEANS : SIGN_EF, src, tiles, ef, 0.0f, algo);
+        launch_scalar_finalize(lc, src, groups, means ? RED_MEANS : RED_MEAN_ABS, algo, 0, ef);
+    }
+        break;
+    case MC_ALGO_SIGNSGD:
+    case MC_ALGO_SIGNUM:
+        launch_sign_compress(lc, cfg.algo == MC_ALGO_SIGNSGD ? SIGN_PLAIN : SIGN_MOMENTUM, src, tiles, ef, cfg.dgc_momentum, algo);
+        break;
+    case MC_ALGO_QSGD:
+        launch_accum_reduce(lc, src, tiles, ef, RED_L2, levels, cfg.seed);
+        launch_scalar_finalize(lc, src, groups, RED_L2, algo, levels, false);
+        launch_qsgd_encode(lc, src, tiles, ef, levels, cfg.seed, worker, iter_lo);
+        break;
+    case MC_ALGO_TERNGRAD:
+        launch_accum_reduce(lc, src, tiles, ef, RED_MAX_ABS, 0, cfg.seed);
+        launch_scalar_finalize(lc, src, groups, RED_MAX_ABS, algo, 0, false);
+        launch_tern_encode(lc, src, tiles, ef, cfg.seed, worker, iter_lo);
+        break;
+    default:
+        launch_fp16_compress(lc, src, tiles, ef);
+        break;
+    }
+}
+// the payload of an empty group: its header
+static void empty_compress(const mc_config &cfg, const LaunchCtx &lc, PayloadHeader *hdr)
+{
+    const bool votes = cfg.algo == MC_ALGO_SIGNSGD || cfg.algo == MC_ALGO_SIGNUM;
+    launch_scalar_finalize(lc, OneCompress{GroupView{}, nullptr, hdr, nullptr}, 1, votes ? RED_ONE : -1, (uint32_t)cfg.algo, qsgd_levels(cfg), false);
+}
+static SparseCall sparse_call(const mc_ctx *ctx, uint32_t worker, uint64_t iter)
+{
+    SparseCall c{ctx->cfg.dgc_momentum, ctx->cfg.seed, worker, (uint32_t)iter, ctx->sync_blocks, ctx->d_status};
+    return c;
+}
 
 // partial: the per-tile reduction partials (three arrays of one double per tile of the group); prof: the context's
 // profiler, or null for a call that must not create events
@@ -554,70 +739,85 @@ static int compress_impl(mc_ctx *ctx, int32_t group, uint32_t worker, uint64_t i
     LaunchCtx lc{static_cast<hipStream_t>(stream), prof, nullptr, nullptr};
     (void)hipGetLastError();
     PayloadHeader *hdr = static_cast<PayloadHeader *>(payload_out);
-    uint8_t *body = static_cast<uint8_t *>(payload_out) + kHeaderBytes;
-    StateHeader *sh = static_cast<StateHeader *>(state);
     float *sf = state ? reinterpret_cast<float *>(static_cast<uint8_t *>(state) + kHeaderBytes) : nullptr;
-    const uint32_t n = G.n, nwords = (uint32_t)(((uint64_t)n + 31) / 32);
-    const uint32_t tiles = (uint32_t)(((uint64_t)n + kTile - 1) / kTile);
-    const uint32_t levels = cfg.algo == MC_ALGO_QSGD ? (1u << (cfg.qsgd_bits - 1)) - 1u : 0u;
+    const uint32_t n = G.n;
 
     if (n == 0) {   // nothing to encode: the payload is its header
-        const bool votes = cfg.algo == MC_ALGO_SIGNSGD || cfg.algo == MC_ALGO_SIGNUM;
-        launch_scalar_finalize(lc, partial, 0, votes ? RED_ONE : -1, 0, hdr, (uint32_t)cfg.algo, 0, levels, nullptr);
+        empty_compress(cfg, lc, hdr);
         return check_launch();
     }
     GroupView gv = group_view(ctx, lc, group, G, reinterpret_cast<const void *const *>(grad_ptrs));
-    switch (cfg.algo) {
-    case MC_ALGO_EFSIGN:
-        launch_sign_compress(lc, SIGN_EF, gv, ef, sf, sh, 0.0f, reinterpret_cast<uint32_t *>(body), nwords, partial, hdr, MC_ALGO_EFSIGN);
-        launch_scalar_finalize(lc, partial, tiles, RED_MEAN_ABS, n, hdr, MC_ALGO_EFSIGN, 0, 0, ef ? &sh->scale : nullptr);
-        break;
-    case MC_ALGO_ONEBIT:
-        launch_sign_compress(lc, SIGN_MEANS, gv, ef, sf, sh, 0.0f, reinterpret_cast<uint32_t *>(body), nwords, partial, hdr, MC_ALGO_ONEBIT);
-        launch_scalar_finalize(lc, partial, tiles, RED_MEANS, n, hdr, MC_ALGO_ONEBIT, 0, 0, ef ? &sh->scale : nullptr);
-        break;
-    case MC_ALGO_SIGNSGD:
-    case MC_ALGO_SIGNUM:
-        launch_sign_compress(lc, cfg.algo == MC_ALGO_SIGNSGD ? SIGN_PLAIN : SIGN_MOMENTUM, gv, ef, sf, sh, cfg.dgc_momentum,
-                             reinterpret_cast<uint32_t *>(body), nwords, partial, hdr, (uint32_t)cfg.algo);
-        break;
-    case MC_ALGO_QSGD:
-        launch_accum_reduce(lc, gv, ef, sf, sh, RED_L2, levels, cfg.seed, partial);
-        launch_scalar_finalize(lc, partial, tiles, RED_L2, n, hdr, MC_ALGO_QSGD, 0, levels, nullptr);
-        launch_qsgd_encode(lc, gv, ef, sf, sh, hdr, reinterpret_cast<int8_t *>(body), levels, cfg.seed, worker, (uint32_t)iter);
-        break;
-    case MC_ALGO_TERNGRAD:
-        launch_accum_reduce(lc, gv, ef, sf, sh, RED_MAX_ABS, 0, cfg.seed, partial);
-        launch_scalar_finalize(lc, partial, tiles, RED_MAX_ABS, n, hdr, MC_ALGO_TERNGRAD, 0, 0, nullptr);
-        launch_tern_encode(lc, gv, ef, sf, sh, hdr, reinterpret_cast<uint32_t *>(body), nwords, cfg.seed, worker, (uint32_t)iter);
-        break;
-    case MC_ALGO_FP16:
-        launch_fp16_compress(lc, gv, ef, sf, hdr, reinterpret_cast<uint16_t *>(body));
-        break;
-    case MC_ALGO_TOPK:
-    case MC_ALGO_DGC:
-    case MC_ALGO_RANDK:
-    {
-        SparseScratch sp = ctx->sparse;
-        // a context may compress for several simulated workers whose thresholds differ: each keeps its own hint
-        sp.hint = ctx->d_hints + ((size_t)group * kHintWorkers + worker % kHintWorkers) * kHintWords;
-        ctx->last_hint = sp.hint;
-        uint32_t stride = 0, first = 0;
-        uint64_t need = 0;
-        if (cfg.dgc_sample_ppm) {       // sample: every stride-th element from `first`; threshold = its need-th largest key
-            stride = std::max<uint32_t>(1u, 1000000u / cfg.dgc_sample_ppm);
-            first = philox_word(cfg.seed, worker, (uint32_t)iter, G.goff) % stride;
-            const uint64_t m = n > first ? ((uint64_t)n - first + stride - 1) / stride : 0;
-            need = m ? std::max<uint64_t>(1, (uint64_t)(((unsigned __int128)m * cfg.ratio_ppm) / 1000000u)) : 0;
-        }
-        launch_sparse_compress(lc, cfg.algo, gv, ef, sf, cfg.dgc_momentum, G.k, hdr, sp, cfg.seed, worker, (uint32_t)iter,
-                               stride, first, need, ctx->sync_blocks, ctx->d_status);
+    if (!is_sparse(cfg.algo)) {
+        dense_compress(cfg, lc, OneCompress{gv, sf, hdr, partial}, tiles_in(n), 1, worker, (uint32_t)iter);
+        return check_launch();
     }
-        break;
-    default: return MC_ERR_INVALID_ARG;
+    SparseScratch sp = ctx->sparse;
+    // a context may compress for several simulated workers whose thresholds differ: each keeps its own hint
+    sp.hint = ctx->d_hints + (worker % kHintWorkers) * kHintWords;
+    if (ctx->own_scratch) sp = scratch_of(sp, (uint32_t)group, ctx->first_tile[group], ctx->first_sub[group]);
+    else sp.hint += (size_t)group * kHintWorkers * kHintWords;
+    ctx->last_hint = sp.hint;
+    ctx->last_sel = sp.sel;
+    SparseCall call = sparse_call(ctx, worker, iter);
+    if (cfg.dgc_sample_ppm) {       // sample: every stride-th element from `first`; threshold = its need-th largest key
+        const uint32_t stride = std::max<uint32_t>(1u, 1000000u / cfg.dgc_sample_ppm);
+        const uint32_t first = philox_word(cfg.seed, worker, (uint32_t)iter, G.goff) % stride;
+        const uint64_t m = n > first ? ((uint64_t)n - first + stride - 1) / stride : 0;
+        call.sample_stride = stride;
+        call.sample_first = first;
+        call.sample_need = m ? std::max<uint64_t>(1, (uint64_t)(((unsigned __int128)m * cfg.ratio_ppm) / 1000000u)) : 0;
     }
+    launch_sparse_compress(lc, cfg.algo, OneSparse{gv, sf, hdr, G.k, sp}, sparse_blocks(n), ef, call);
     return check_launch();
 }
+
+// All groups of one worker with one launch per step.  Returns 1 if the call has to be taken group by group instead: where
+// the context keeps no scratch for that, where an argument is not in order (the loop stops at the first such group), or
+// where buffers overlap so that the order of the groups matters.
+static int compress_all(mc_ctx *ctx, uint32_t worker, uint64_t iter, const float *const *grads, void *const *states, void *const *payloads,
+                        void *stream)
+{
+    const mc_config &cfg = ctx->cfg;
+    const size_t y = ctx->groups.size();
+    const bool ef = cfg.use_ef != 0, sparse = is_sparse(cfg.algo);
+    if (ctx->all_slots.empty() || (sparse && !ctx->own_scratch) || !grads) return 1;
+    std::vector<uintptr_t> &want = ctx->want_all;        // (both reserved at creation: no allocation here)
+    std::vector<Span> &spans = ctx->spans;
+    want.clear();
+    spans.clear();
+    bool plain = true;
+    auto add = [&](const void *p, size_t bytes, uintptr_t align, bool written) {
+        const uintptr_t a = reinterpret_cast<uintptr_t>(p);
+        plain = plain && a != 0 && (a & (align - 1u)) == 0;
+        want.push_back(a);
+        spans.push_back({a, a + bytes, written});
+    };
+    for (const Group &G : ctx->groups) for (int32_t rel : G.live) add(grads[G.t0 + rel], sizeof(float) * (size_t)ctx->tensor_numel[G.t0 + rel], 4, false);
+    for (size_t j = 0; j < y; ++j) {
+        if (ef) add(states[j], mc_state_bytes(ctx, (int32_t)j), 16, true);
+        else want.push_back(0);
+    }
+    for (size_t j = 0; j < y; ++j) add(payloads[j], mc_payload_bytes(ctx, (int32_t)j), 16, true);
+    if (!plain) return 1;
+    LaunchCtx lc{static_cast<hipStream_t>(stream), &ctx->prof, nullptr, nullptr};
+    (void)hipGetLastError();
+    const AllSlot &slot = all_slot(ctx, lc, 0);
+    if (!slot.apart) return 1;
+    const GroupTable tb = all_table(ctx, slot);
+    if (sparse) {
+        SparseScratch sp = ctx->sparse;
+        sp.hint = ctx->d_hints + (worker % kHintWorkers) * kHintWords;
+        const SparseScratch last = scratch_of(sp, ctx->last_group, ctx->first_tile[ctx->last_group], ctx->first_sub[ctx->last_group]);
+        ctx->last_hint = last.hint;
+        ctx->last_sel = last.sel;
+        const SparseBlocks nb{ctx->all_blocks[BLK_TILE], ctx->all_blocks[BLK_SELECT], ctx->all_blocks[BLK_EMIT]};
+        launch_sparse_compress(lc, cfg.algo, AllSparse{tb, sp, ctx->last_group}, nb, ef, sparse_call(ctx, worker, iter));
+    } else dense_compress(cfg, lc, AllCompress{tb, ctx->d_partial}, ctx->all_blocks[BLK_TILE], (uint32_t)y, worker, (uint32_t)iter);
+    for (size_t j = 0; j < y; ++j) if (ctx->groups[j].n == 0) empty_compress(cfg, lc, static_cast<PayloadHeader *>(payloads[j]));
+    return check_launch();
+}
+
+extern "C" {
 
 int mc_compress(mc_ctx *ctx, int32_t group, uint32_t worker, uint64_t iter, const float *const *grad_ptrs, void *state,
                 void *payload_out, void *stream)
@@ -662,12 +862,35 @@ int mc_decompress_sum(mc_ctx *ctx, int32_t group, const void *const *payloads, i
     LaunchCtx lc{static_cast<hipStream_t>(stream), &ctx->prof, nullptr, nullptr};
     (void)hipGetLastError();
     GroupView gv = group_view(ctx, lc, group, G, reinterpret_cast<const void *const *>(out_ptrs));
-    const mc_config &cfg = ctx->cfg;
-    if (is_sparse(cfg.algo)) launch_sparse_decompress(lc, cfg.algo, gv, pl, W, alpha, G.k, ctx->d_status, cfg.dgc_sample_ppm != 0);
-    else {
-        const uint32_t levels = cfg.algo == MC_ALGO_QSGD ? (1u << (cfg.qsgd_bits - 1)) - 1u : 0u;
-        launch_dense_decompress(lc, cfg.algo, gv, pl, W, alpha, levels, ctx->d_status);
-    }
+    decompress_launch(ctx, lc, OneDecompress{gv, pl, G.k}, tiles_in(G.n), plane_blocks(G.n), W, alpha);
+    return check_launch();
+}
+
+// All groups with one launch; 1 if the call has to be taken group by group (see compress_all).
+static int decompress_all(mc_ctx *ctx, const void *const *payloads, int32_t W, float alpha, float *const *outs, void *stream)
+{
+    const size_t y = ctx->groups.size();
+    if (ctx->all_slots.empty() || !outs) return 1;
+    std::vector<uintptr_t> &want = ctx->want_all;
+    std::vector<Span> &spans = ctx->spans;
+    want.clear();
+    spans.clear();
+    bool plain = true;
+    auto add = [&](const void *p, size_t bytes, uintptr_t align, bool written) {
+        const uintptr_t a = reinterpret_cast<uintptr_t>(p);
+        plain = plain && a != 0 && (a & (align - 1u)) == 0;
+        want.push_back(a);
+        spans.push_back({a, a + bytes, written});
+    };
+    for (const Group &G : ctx->groups) for (int32_t rel : G.live) add(outs[G.t0 + rel], sizeof(float) * (size_t)ctx->tensor_numel[G.t0 + rel], 4, true);
+    for (size_t j = 0; j < y; ++j)
+        for (int32_t w = 0; w < W; ++w) add(payloads[(size_t)w * y + j], mc_payload_bytes(ctx, (int32_t)j), 16, false);
+    if (!plain) return 1;
+    LaunchCtx lc{static_cast<hipStream_t>(stream), &ctx->prof, nullptr, nullptr};
+    (void)hipGetLastError();
+    const AllSlot &slot = all_slot(ctx, lc, W);
+    if (!slot.apart) return 1;
+    decompress_launch(ctx, lc, AllDecompress{all_table(ctx, slot), W}, ctx->all_blocks[BLK_TILE], ctx->all_blocks[BLK_PLANE], W, alpha);
     return check_launch();
 }
 
@@ -675,6 +898,8 @@ int mc_compress_groups(mc_ctx *ctx, uint32_t worker, uint64_t iter, const float 
                        void *const *payloads_out, void *stream)
 {
     if (!ctx || !payloads_out || (ctx->cfg.use_ef && !states)) return MC_ERR_INVALID_ARG;
+    const int done = compress_all(ctx, worker, iter, grad_ptrs_all, states, payloads_out, stream);
+    if (done != 1) return done;
     for (size_t j = 0; j < ctx->groups.size(); ++j) {
         const Group &G = ctx->groups[j];
         const int rc = compress_impl(ctx, (int32_t)j, worker, iter, grad_ptrs_all ? grad_ptrs_all + G.t0 : nullptr, states ? states[j] : nullptr,
@@ -688,6 +913,8 @@ int mc_decompress_sum_groups(mc_ctx *ctx, const void *const *payloads, int32_t W
 {
     if (!ctx || !payloads || W < 1) return MC_ERR_INVALID_ARG;
     if (W > kMaxWorkers) return MC_ERR_RANGE;
+    const int done = decompress_all(ctx, payloads, W, alpha, out_ptrs_all, stream);
+    if (done != 1) return done;
     const size_t y = ctx->groups.size();
     const void *one[kMaxWorkers];
     for (size_t j = 0; j < y; ++j) {
@@ -710,8 +937,7 @@ static int state_convert(mc_ctx *ctx, int32_t group, const void *src, void *dst,
     if (nf == 0) return MC_OK;
     LaunchCtx lc{static_cast<hipStream_t>(stream), &ctx->prof, nullptr, nullptr};
     (void)hipGetLastError();
-    const uint32_t levels = ctx->cfg.algo == MC_ALGO_QSGD ? (1u << (ctx->cfg.qsgd_bits - 1)) - 1u : 0u;
-    launch_state_convert(lc, ctx->cfg.algo, to_residual, g->n, src, dst, levels, ctx->cfg.seed, g->goff);
+    launch_state_convert(lc, ctx->cfg.algo, to_residual, g->n, src, dst, qsgd_levels(ctx->cfg), ctx->cfg.seed, g->goff);
     return check_launch();
 }
 
@@ -742,7 +968,7 @@ int mc_last_select_route(mc_ctx *ctx)
     SelectState s;
     DeviceGuard on(ctx->device);
     if (hipDeviceSynchronize() != hipSuccess) return MC_ERR_DEVICE;
-    if (hipMemcpy(&s, ctx->sparse.sel, sizeof(s), hipMemcpyDeviceToHost) != hipSuccess) return MC_ERR_DEVICE;
+    if (hipMemcpy(&s, ctx->last_sel, sizeof(s), hipMemcpyDeviceToHost) != hipSuccess) return MC_ERR_DEVICE;
     return (s.mode & 8u) ? MC_SELECT_DENSE : (s.mode & 1u) ? MC_SELECT_FAST : (s.mode & 2u) ? MC_SELECT_REFILL : MC_SELECT_ABOVE;
 }
 

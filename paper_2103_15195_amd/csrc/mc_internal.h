@@ -38,6 +38,131 @@ __host__ __device__ inline size_t dgc_u_offset(uint32_t n) { return ((size_t)n +
 struct PayloadPtrs { const uint8_t *p[kMaxWorkers]; };
 struct PtrChunk { uintptr_t p[256]; };
 
+// ---- which group a block works on -----------------------------------------------------------------------------
+// A kernel covers one group (mc_compress, mc_decompress_sum), whose addresses then travel as kernel arguments, or all
+// groups of a context in one launch (the _groups calls).  In the second case the blocks of all groups are numbered
+// one group after the other, a table says which group a block belongs to, and what the group's blocks need to know
+// is split into a table that is fixed when the context is created (GroupConst) and a list of the call's addresses.
+// Kernels take the difference as a template parameter: both forms hand out the same job.
+// (Measured, compress and decompress-sum of a rank with 8 workers, launch by launch / all groups at once: 161 groups of
+// one tensor each, 25.6 M elements, EF-Sign 3170 -> 82 us, what the same elements take as one group; 270 000 elements
+// in four groups, Top-k 108 -> 32 us, in eight, QSGD 174 -> 34; two groups of 12.8 M, DGC 152 -> 133, three, QSGD 171 -> 134.
+// A table costs a kernel one more level of scalar loads: the merged model as one group keeps its arguments.)
+enum BlockKind { BLK_TILE = 0, BLK_PLANE = 1, BLK_SELECT = 2, BLK_EMIT = 3, BLK_KINDS = 4 };   // 4096 elements; 8192; 16 tiles; 4 tiles
+struct GroupConst {
+    const uint32_t *seg_off, *chunk_seg;
+    uint64_t goff, k;
+    uint32_t n, nseg;
+    uint32_t first[BLK_KINDS];    // number of the group's first block, per kind of block (BLK_TILE: its first tile)
+    uint32_t first_ptr;           // its first tensor in the list of addresses
+    uint32_t first_sub;           // sparsifiers: its first sublist of keys in the threshold's bin
+};
+struct GroupTable {
+    const GroupConst *groups;
+    const uint32_t *block_group[BLK_KINDS];
+    const uintptr_t *list;        // addresses of the call: tensors of all groups (the non-empty ones), then what the call needs per group
+    const uintptr_t *chunk_addr;  // per chunk of all groups' tiles
+    uint32_t live;                // tensors in the list
+    uint32_t y;
+};
+
+__device__ __forceinline__ GroupView view_of(const GroupTable &tb, const GroupConst *c)
+{
+    GroupView g;
+    g.seg_off = ld_uniform(&c->seg_off);
+    g.chunk_seg = ld_uniform(&c->chunk_seg);
+    g.ptrs = tb.list + ld_uniform(&c->first_ptr);
+    g.chunk_addr = tb.chunk_addr + (size_t)ld_uniform(&c->first[BLK_TILE]) * kWavesPerBlock;
+    g.nseg = ld_uniform(&c->nseg);
+    g.n = ld_uniform(&c->n);
+    g.goff = ld_uniform(&c->goff);
+    return g;
+}
+__host__ __device__ inline uint32_t tiles_in(uint32_t n) { return (uint32_t)(((uint64_t)n + kTile - 1) / kTile); }
+
+// A dense compressor's job.  The state's header lies in front of st, the payload's body behind hdr.
+struct CompressJob {
+    GroupView g;
+    float *st;                    // null when the scheme keeps no state
+    PayloadHeader *hdr;
+    double *partial;              // one double per tile (OneBit: three arrays of one per tile)
+    uint32_t tile, ntiles;
+    __device__ __forceinline__ StateHeader *state_header() const { return reinterpret_cast<StateHeader *>(st) - 1; }
+    __device__ __forceinline__ uint8_t *body() const { return reinterpret_cast<uint8_t *>(hdr) + kHeaderBytes; }
+};
+struct OneCompress {
+    GroupView g;
+    float *st;
+    PayloadHeader *hdr;
+    double *partial;
+    __device__ __forceinline__ CompressJob group_job(uint32_t) const { return {g, st, hdr, partial, 0u, tiles_in(g.n)}; }
+    __device__ __forceinline__ CompressJob job() const { return {g, st, hdr, partial, my_tile_index(), gridDim.x}; }
+};
+struct AllCompress {              // list: tensors, then y states, then y payloads
+    GroupTable tb;
+    double *partial;
+    __device__ __forceinline__ CompressJob group_job(uint32_t q) const
+    {
+        CompressJob j;
+        const GroupConst *c = tb.groups + q;
+        j.g = view_of(tb, c);
+        const uintptr_t state = ld_uniform(tb.list + tb.live + q);
+        j.st = state ? reinterpret_cast<float *>(state + kHeaderBytes) : nullptr;
+        j.hdr = reinterpret_cast<PayloadHeader *>(ld_uniform(tb.list + tb.live + tb.y + q));
+        j.partial = partial + 3u * (size_t)ld_uniform(&c->first[BLK_TILE]);
+        j.tile = 0u;
+        j.ntiles = tiles_in(j.g.n);
+        return j;
+    }
+    __device__ __forceinline__ CompressJob job() const
+    {
+        const uint32_t block = my_tile_index(), q = ld_uniform(tb.block_group[BLK_TILE] + block);
+        CompressJob j = group_job(q);
+        j.tile = block - ld_uniform(&tb.groups[q].first[BLK_TILE]);
+        return j;
+    }
+};
+
+// A decompress-and-sum's job: the output, the payloads of the group, and this block's number among the group's.
+struct OneDecompress {
+    GroupView out;
+    PayloadPtrs pl;
+    uint64_t k;
+    struct Job {
+        GroupView out;
+        const OneDecompress *src;
+        uint64_t k;
+        uint32_t block, last;
+        __device__ __forceinline__ const uint8_t *payload(int w) const { return src->pl.p[w]; }             // w: the same for the wavefront
+        __device__ __forceinline__ const uint8_t *payload_of_lane(uint32_t w) const { return src->pl.p[w]; }
+    };
+    template <int KIND> __device__ __forceinline__ Job job() const { return {out, this, k, my_tile_index(), gridDim.x - 1u}; }
+};
+struct AllDecompress {            // list: tensors, then the W payloads of group 0, of group 1, ...
+    GroupTable tb;
+    int W;
+    struct Job {
+        GroupView out;
+        const uintptr_t *pl;
+        uint64_t k;
+        uint32_t block, last;
+        __device__ __forceinline__ const uint8_t *payload(int w) const { return reinterpret_cast<const uint8_t *>(ld_uniform(pl + w)); }
+        __device__ __forceinline__ const uint8_t *payload_of_lane(uint32_t w) const { return reinterpret_cast<const uint8_t *>(pl[w]); }
+    };
+    template <int KIND> __device__ __forceinline__ Job job() const
+    {
+        Job j;
+        const uint32_t b = my_tile_index(), q = ld_uniform(tb.block_group[KIND] + b);
+        const GroupConst *c = tb.groups + q;
+        j.out = view_of(tb, c);
+        j.pl = tb.list + tb.live + (size_t)q * W;
+        j.k = ld_uniform(&c->k);
+        j.block = b - ld_uniform(&c->first[KIND]);
+        j.last = (uint32_t)(((uint64_t)j.out.n + (KIND == BLK_PLANE ? 2 * kTile : kTile) - 1) / (KIND == BLK_PLANE ? 2 * kTile : kTile)) - 1u;
+        return j;
+    }
+};
+
 // radix-select state carried between the passes of the exact top-k
 struct SelectState {
     uint32_t lo;         // the threshold key lies in [lo, lo + range of the levels still to resolve)
@@ -74,22 +199,22 @@ void prof_end(const LaunchCtx &lc, int id);
     } while (0)
 
 // ---- dense kernels (kernels_dense.hip) -----------------------------------------
+// The launchers of the path come in the two forms of a job source; `tiles` is the number of blocks of 4096 elements
+// that the launch covers (of all its groups), `groups` the number of groups.
 void launch_upload_ptrs(const LaunchCtx &lc, const uintptr_t *host, uintptr_t *dev, uint32_t count);
 void launch_expand_ptrs(const LaunchCtx &lc, const GroupView &g, uintptr_t *chunk_addr);
-void launch_sign_compress(const LaunchCtx &lc, int mode, const GroupView &g, bool ef, float *state_f, const StateHeader *prev,
-                          float beta, uint32_t *words, uint32_t nwords, double *partial, PayloadHeader *hdr, uint32_t algo);
-void launch_scalar_finalize(const LaunchCtx &lc, const double *partial, uint32_t nblocks, int mode, uint32_t n,
-                            PayloadHeader *hdr, uint32_t algo, uint64_t k, uint32_t levels, float *state_scale);
-void launch_accum_reduce(const LaunchCtx &lc, const GroupView &g, bool ef, float *state_f, const StateHeader *prev, int mode,
-                         uint32_t levels, uint64_t seed, double *partial);
-void launch_qsgd_encode(const LaunchCtx &lc, const GroupView &g, bool ef, float *state_f, StateHeader *sh, const PayloadHeader *hdr,
-                        int8_t *codes, uint32_t levels, uint64_t seed, uint32_t worker, uint32_t iter_lo);
-void launch_tern_encode(const LaunchCtx &lc, const GroupView &g, bool ef, float *state_f, StateHeader *sh, const PayloadHeader *hdr,
-                        uint32_t *planes, uint32_t nwords, uint64_t seed, uint32_t worker, uint32_t iter_lo);
-void launch_fp16_compress(const LaunchCtx &lc, const GroupView &g, bool ef, float *state_f, PayloadHeader *hdr,
-                          uint16_t *halves);
-void launch_dense_decompress(const LaunchCtx &lc, int algo, const GroupView &out, const PayloadPtrs &pl, int W,
-                             float alpha, uint32_t levels, int *status);
+void launch_expand_all(const LaunchCtx &lc, const GroupTable &tb, uint32_t tiles, uintptr_t *chunk_addr);
+template <class SRC> void launch_sign_compress(const LaunchCtx &lc, int mode, const SRC &src, uint32_t tiles, bool ef, float beta, uint32_t algo);
+template <class SRC> void launch_scalar_finalize(const LaunchCtx &lc, const SRC &src, uint32_t groups, int mode, uint32_t algo, uint32_t levels,
+                                                 bool keep);
+template <class SRC> void launch_accum_reduce(const LaunchCtx &lc, const SRC &src, uint32_t tiles, bool ef, int mode, uint32_t levels, uint64_t seed);
+template <class SRC> void launch_qsgd_encode(const LaunchCtx &lc, const SRC &src, uint32_t tiles, bool ef, uint32_t levels, uint64_t seed,
+                                             uint32_t worker, uint32_t iter_lo);
+template <class SRC> void launch_tern_encode(const LaunchCtx &lc, const SRC &src, uint32_t tiles, bool ef, uint64_t seed, uint32_t worker, uint32_t iter_lo);
+template <class SRC> void launch_fp16_compress(const LaunchCtx &lc, const SRC &src, uint32_t tiles, bool ef);
+template <class SRC> void launch_dense_decompress(const LaunchCtx &lc, int algo, const SRC &src, uint32_t blocks /* of 8192 elements for the bit planes */,
+                                                  int W, float alpha, uint32_t levels, int *status);
+inline uint32_t plane_blocks(uint32_t n) { return (uint32_t)(((uint64_t)n + 2 * kTile - 1) / (2 * kTile)); }
 void launch_state_convert(const LaunchCtx &lc, int algo, bool to_residual, uint32_t n, const void *src, void *dst, uint32_t levels,
                           uint64_t seed, uint64_t goff);
 
@@ -122,12 +247,86 @@ struct SparseScratch {
     uint32_t *sync;        // [0]: arrivals at the grid-wide barriers of the slow routes (cleared by the streaming pass); [32..36): calls per route
     uint32_t spin_limit;   // polls after which a block gives up waiting at such a barrier (mc_set_barrier_spin_limit)
 };
-// sync_blocks: how many blocks of 1024 threads the device surely holds at once (one per compute unit): the slow routes
-// of the selection run on that many blocks with grid-wide barriers between their steps
-void launch_sparse_compress(const LaunchCtx &lc, int algo, const GroupView &g, bool ef, float *state_f, float momentum,
-                            uint64_t k, PayloadHeader *hdr, const SparseScratch &sc, uint64_t seed, uint32_t worker, uint32_t iter_lo,
-                            uint32_t sample_stride, uint32_t sample_first, uint64_t sample_need, uint32_t sync_blocks, int *status);
-void launch_sparse_decompress(const LaunchCtx &lc, int algo, const GroupView &out, const PayloadPtrs &pl, int W,
-                              float alpha, uint64_t k, int *status, bool capped);
+// The part of the scratch that group number q of a launch over all groups works in: every group has its own, laid out
+// one after the other (hint records: of the worker that `all` was set up for).
+__host__ __device__ inline SparseScratch scratch_of(const SparseScratch &all, uint32_t q, uint32_t first_tile, uint32_t first_sub)
+{
+    SparseScratch s = all;
+    s.hist += (size_t)q * kHistWords;
+    s.sel += (size_t)q * 4;
+    s.hint += (size_t)q * kHintWorkers * kHintWords;
+    s.cand_bits += (size_t)first_tile * kTile;
+    s.cand_loc += (size_t)first_tile * kTile;
+    s.tile_runs += first_tile;
+    s.tile_cnt += first_tile;
+    s.blk_cnt += first_tile;
+    s.ulist += (size_t)first_sub * kUCap;
+    s.ucount += (size_t)q * kUSub * kUCountStride;
+    return s;
+}
+constexpr int kSelTiles = 16, kEmitTiles = kWavesPerBlock;     // tiles per block of the select and the emit kernel
+
+// A sparsifier's job: `block` is this block's number among the group's `blocks` of its kind (tiles: handed out last first).
+struct SparseJob {
+    GroupView g;
+    float *st;
+    PayloadHeader *hdr;
+    uint64_t k;
+    SparseScratch sc;
+    uint32_t block, blocks;
+    bool reports;                 // this group's counts are what mc_select_stats shows as the most recent call's
+};
+struct OneSparse {
+    GroupView g;
+    float *st;
+    PayloadHeader *hdr;
+    uint64_t k;
+    SparseScratch sc;
+    template <int KIND> __device__ __forceinline__ SparseJob job() const
+    {
+        return {g, st, hdr, k, sc, KIND == BLK_TILE ? my_tile_index() : blockIdx.x, gridDim.x, true};
+    }
+};
+struct AllSparse {                // list: tensors, then y states, then y payloads
+    GroupTable tb;
+    SparseScratch all;
+    uint32_t last_group;          // the last one that holds elements
+    __device__ __forceinline__ SparseJob group_job(uint32_t q) const
+    {
+        const GroupConst *c = tb.groups + q;
+        const uintptr_t state = ld_uniform(tb.list + tb.live + q);
+        return {view_of(tb, c), state ? reinterpret_cast<float *>(state + kHeaderBytes) : nullptr,
+                reinterpret_cast<PayloadHeader *>(ld_uniform(tb.list + tb.live + tb.y + q)), ld_uniform(&c->k),
+                scratch_of(all, q, ld_uniform(&c->first[BLK_TILE]), ld_uniform(&c->first_sub)), 0u, 0u, q == last_group};
+    }
+    template <int KIND> __device__ __forceinline__ SparseJob job() const
+    {
+        const uint32_t b = KIND == BLK_TILE ? my_tile_index() : blockIdx.x, q = ld_uniform(tb.block_group[KIND] + b);
+        constexpr uint32_t per = KIND == BLK_SELECT ? kSelTiles : KIND == BLK_EMIT ? kEmitTiles : 1;
+        SparseJob j = group_job(q);
+        j.block = b - ld_uniform(&tb.groups[q].first[KIND]);
+        j.blocks = (tiles_in(j.g.n) + per - 1u) / per;
+        return j;
+    }
+};
+// What a sparsifier needs besides its groups.  sync_blocks: how many blocks of 1024 threads the device surely holds at once (one per
+// compute unit): the slow routes of the selection run on that many blocks with grid-wide barriers between their steps.
+struct SparseCall {
+    float momentum;
+    uint64_t seed;
+    uint32_t worker, iter_lo, sync_blocks;
+    int *status;
+    uint32_t sample_stride = 0, sample_first = 0;      // DGC with a sampled threshold (one group only)
+    uint64_t sample_need = 0;
+};
+struct SparseBlocks { uint32_t tiles, select, emit; };          // blocks of each kind that the launches cover
+inline SparseBlocks sparse_blocks(uint32_t n)
+{
+    const uint32_t t = tiles_in(n);
+    return {t, (t + kSelTiles - 1) / kSelTiles, (t + kEmitTiles - 1) / kEmitTiles};
+}
+template <class SRC> void launch_sparse_compress(const LaunchCtx &lc, int algo, const SRC &src, const SparseBlocks &nb, bool ef, const SparseCall &call);
+template <class SRC> void launch_sparse_decompress(const LaunchCtx &lc, int algo, const SRC &src, uint32_t tiles, int W, float alpha, int *status,
+                                                   bool capped);
 
 }  // namespace mc
