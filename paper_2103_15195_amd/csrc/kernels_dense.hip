@@ -482,6 +482,22 @@ __device__ __forceinline__ void remember_call(const CompressJob &job, float scal
     }
 }
 
+// Can a chunk be encoded four consecutive elements per lane, and from where?  With error feedback p lies in the state,
+// without, in one tensor.  This form computes a Philox block in the lane that needs its four words (wide_words), and what
+// the lane has of a chunk is a word of codes, or a nibble of either plane: no words handed round, no LDS stage.  The pass
+// was bound by the vector ALU and is now bound by memory: QSGD encode of 25.6 M elements 31 -> 21 us (6.1 TB/s for its
+// 128 MB), TernGrad of 10 M 14.0 -> 8.1.  Chunks that are not whole, start inside a Philox block (a group after an odd
+// number of elements) or, without error feedback, straddle tensors take the form below it.  (Pass A in the same form
+// measured the same to 0.4 us slower: there the draws hide behind 12 bytes per element.)
+template <bool EF>
+__device__ __forceinline__ const float *wide_source(const GroupView &g, const float *st, const Chunk &c)
+{
+    if (!wide_random(c, g.goff + c.base)) return nullptr;
+    if (EF) return st + c.base;
+    const uintptr_t entry = chunk_entry(g, c);
+    return entry & 1u ? nullptr : reinterpret_cast<const float *>(entry);
+}
+
 template <bool EF, class SRC>
 __global__ __launch_bounds__(kBlock) void qsgd_encode_k(SRC src, uint32_t levels, uint64_t seed, uint32_t worker, uint32_t iter_lo)
 {
@@ -495,6 +511,21 @@ __global__ __launch_bounds__(kBlock) void qsgd_encode_k(SRC src, uint32_t levels
     if (EF) remember_call(job, norm, worker, iter_lo);
     if (c.base >= g.n) return;
     const QsgdScale ks(norm, levels);
+    if (const float *src4 = wide_source<EF>(g, st, c)) {
+        float4v p[4];
+#pragma unroll
+        for (int m = 0; m < 4; ++m) p[m] = EF ? load_wide(src4, c.lane, m) : load_wide_unaligned(src4, c.lane, m);
+        uint32_t *dst = reinterpret_cast<uint32_t *>(codes + c.base);
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+            uint32_t x[4], word = 0;
+            wide_words(seed, worker, iter_lo, g.goff + c.base, c.lane, m, x);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) word |= ((uint32_t)qsgd_code(ks, p[m][e], u01(x[e])) & 0xFFu) << (8 * e);
+            st_stream(dst + 64 * m + c.lane, word);
+        }
+        return;
+    }
     float p[kSteps];
     load_p<EF>(g, st, c, p);
     float uni[kSteps];
@@ -518,6 +549,15 @@ void launch_qsgd_encode(const LaunchCtx &lc, const SRC &src, uint32_t tiles, boo
 template void launch_qsgd_encode<OneCompress>(const LaunchCtx &, const OneCompress &, uint32_t, bool, uint32_t, uint64_t, uint32_t, uint32_t);
 template void launch_qsgd_encode<AllCompress>(const LaunchCtx &, const AllCompress &, uint32_t, bool, uint32_t, uint64_t, uint32_t, uint32_t);
 
+// or of a value over each eight lanes (0..7, 8..15, ...), in all of them
+__device__ __forceinline__ uint32_t or_of_eight(uint32_t x)
+{
+    x |= (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0xB1, 0xF, 0xF, true);      // quad_perm 1 0 3 2
+    x |= (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x4E, 0xF, 0xF, true);      // quad_perm 2 3 0 1
+    x |= (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x141, 0xF, 0xF, true);     // row_half_mirror: lane i of eight <- lane 7 - i
+    return x;
+}
+
 // TernGrad: two bit planes (non-zero, negative)
 template <bool EF, class SRC>
 __global__ __launch_bounds__(kBlock) void tern_encode_k(SRC src, uint64_t seed, uint32_t worker, uint32_t iter_lo)
@@ -532,6 +572,36 @@ __global__ __launch_bounds__(kBlock) void tern_encode_k(SRC src, uint64_t seed, 
     const float smax = job.hdr->scale;
     if (EF) remember_call(job, smax, worker, iter_lo);
     if (c.base >= g.n) return;
+    if (const float *src4 = wide_source<EF>(g, st, c)) {
+        float4v p[4];
+#pragma unroll
+        for (int m = 0; m < 4; ++m) p[m] = EF ? load_wide(src4, c.lane, m) : load_wide_unaligned(src4, c.lane, m);
+        uint32_t wz = 0, wg = 0;                 // the word of the plane that this lane stores, if any
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+            uint32_t x[4], z = 0, s = 0;         // the lane's four bits of either plane, element e in bit e
+            wide_words(seed, worker, iter_lo, g.goff + c.base, c.lane, m, x);
+#pragma unroll
+            for (int e = 3; e >= 0; --e) {
+                bool nz, neg;
+                (void)tern_decode(smax, p[m][e], u01(x[e]), true, nz, neg);
+                z = 2u * z + (nz ? 1u : 0u);
+                s = __builtin_amdgcn_alignbit(s, __float_as_uint(p[m][e]), 31);      // sign bits shifted in
+            }
+            // eight lanes' bits make a word: or-ed inside the quads, then between the two quads of eight lanes
+            const uint32_t at = 4u * (c.lane & 7u);
+            z = or_of_eight(z << at);
+            s = or_of_eight(s << at) & z;        // (a negative zero is never sent as non-zero)
+            if ((c.lane & 3u) == (uint32_t)m) { wz = z; wg = s; }
+        }
+        // word 8 m + q of the chunk's 32 is in lanes 8 q .. 8 q + 7: lane 8 q + m stores the one of the first plane, lane
+        // 8 q + 4 + m of the second
+        const uint32_t m = c.lane & 3u, q = c.lane >> 3;
+        const bool second = (c.lane & 4u) != 0u;
+        uint32_t *dst = planes + (c.base >> 5) + (second ? nwords : 0u);
+        st_stream(dst + 8u * m + q, second ? wg : wz);
+        return;
+    }
     float p[kSteps];
     load_p<EF>(g, st, c, p);
     float uni[kSteps];
@@ -646,8 +716,6 @@ __device__ __forceinline__ void check_header(const PayloadHeader *h, uint32_t al
 // so the mapping changes no result: every element still adds its workers' values in worker order.
 // (Measured, 8 workers, 25.6 M elements: QSGD 62.9 -> 54.6 us.  The same mapping with 8-byte loads
 // made FP16 slower, 80.3 -> 82.5..85 us with 2, 4 or 8 workers per batch, so FP16 stays plain.)
-typedef float float4v __attribute__((ext_vector_type(4)));
-
 template <int ALGO, class SRC>
 __global__ __launch_bounds__(kBlock) void dense_decompress_k(SRC src, int W, float alpha, uint32_t levels, int *status)
 {
