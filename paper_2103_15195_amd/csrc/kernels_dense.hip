@@ -897,35 +897,44 @@ __global__ __launch_bounds__(kBlock) void plane_decompress_k(SRC src, int W, flo
     const GroupView &out = job.out;
     if (job.block == job.last && (int)t < W)
         check_header(reinterpret_cast<const PayloadHeader *>(job.payload_of_lane(t)), algo, out.n, status);
-    const int Wt = W < 8 ? W : 8;
+    // The table takes the first kTab workers, the others are added one by one, kMore of them asked for at a time.
+    // (TernGrad's workers 4 to 7 come with the first four: 10 M elements of five workers 15.0 us when all four were added,
+    // absent or not, 14.4 now.  One plane, 16 workers, 44.5 M elements: 69 us one at a time, 73 with eight at a time.)
+    constexpr int kTab = TERN ? 4 : 8, kMore = TERN ? 4 : 1;
+    const int Wt = W < kTab ? W : kTab;
     // the plane words are asked for before the table is built: the headers' scalars, which the table waits for, and
     // the words then travel together (one-plane schemes 0.6 us, OneBit and TernGrad 1.0-1.5 us of 28-37)
     const uint32_t wbase = job.block * (uint32_t)kSignTile + wave * (uint32_t)kSignWaveElems;
     const uint32_t nwords = (out.n + 31u) >> 5;
     const uint32_t wi = (wbase >> 5) + lane;
-    uint32_t wd[8], wn[8];
+    auto load_words = [&](int w0, int count, uint32_t *words, uint32_t *second) {
 #pragma unroll
-    for (int b = 0; b < 8; ++b) {
-        wd[b] = 0u; wn[b] = 0u;
-        if (b < Wt && wi < nwords) {
-            const uint32_t *plane = reinterpret_cast<const uint32_t *>(job.payload(b) + kHeaderBytes);
-            wd[b] = ld_stream(plane + wi);
-            if (TERN) wn[b] = ld_stream(plane + nwords + wi);
+        for (int b = 0; b < count; ++b) {
+            words[b] = 0u;
+            if (TERN) second[b] = 0u;
+            if (w0 + b < W && wi < nwords) {
+                const uint32_t *plane = reinterpret_cast<const uint32_t *>(job.payload(w0 + b) + kHeaderBytes);
+                words[b] = ld_stream(plane + wi);
+                if (TERN) second[b] = ld_stream(plane + nwords + wi);
+            }
         }
-    }
+    };
+    uint32_t wd[8] = {}, wn[8] = {}, md[kMore], mn[kMore];
+    load_words(0, kTab, wd, wn);
+    if (TERN) load_words(kTab, kMore, md, mn);
     {
         if (!TERN) {
             float acc = 0.0f;
 #pragma unroll
-            for (int b = 0; b < 8; ++b) {
+            for (int b = 0; b < kTab; ++b) {
                 if (b < Wt) {
                     float hi, lo;
                     plane_levels(reinterpret_cast<const PayloadHeader *>(job.payload(b)), kind, hi, lo);
                     acc = acc + (((t >> b) & 1u) ? hi : lo);
                 }
             }
-            if (W <= 8 && kind == PLANE_VOTE) acc = vote_of(acc);
-            table[t] = W <= 8 ? alpha * acc : acc;
+            if (W <= kTab && kind == PLANE_VOTE) acc = vote_of(acc);
+            table[t] = W <= kTab ? alpha * acc : acc;
         } else {
             // entry (nz bits of workers 0..3) | (negative bits of workers 0..3) << 4: their sum, in worker order
             float acc = 0.0f;
@@ -939,54 +948,43 @@ __global__ __launch_bounds__(kBlock) void plane_decompress_k(SRC src, int W, flo
             table[t] = acc;
         }
     }
-    float s47[4] = {0.0f, 0.0f, 0.0f, 0.0f};               // TernGrad: scales of workers 4..7, added one by one
-    if (TERN) {
-#pragma unroll
-        for (int b = 4; b < 8; ++b) if (b < Wt) s47[b - 4] = ld_uniform(&reinterpret_cast<const PayloadHeader *>(job.payload(b))->scale);
-    }
     __syncthreads();
     if (wbase >= out.n) return;
     float acc[32];
-    // TernGrad: only workers 0..3 enter the transposes
-    const uint32_t wlow[8] = {wd[0], wd[1], wd[2], wd[3], 0u, 0u, 0u, 0u}, nlow[8] = {wn[0], wn[1], wn[2], wn[3], 0u, 0u, 0u, 0u};
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        // byte q of the 8 words -> rows of an 8x8 bit matrix (row = worker, column = element 8q + c)
-        const uint64_t x = TERN ? gather_transpose(wlow, q) : gather_transpose(wd, q);
+        // byte q of the words -> rows of an 8x8 bit matrix (row = worker, column = element 8q + c)
+        const uint64_t x = gather_transpose(wd, q);
         if (!TERN) {
 #pragma unroll
             for (int e = 0; e < 8; ++e) acc[8 * q + e] = table[(uint32_t)(x >> (8 * e)) & 0xFFu];
         } else {
-            // workers 0..3 through the table (their bits transposed into an index), workers 4..7 straight from their
-            // words.  An absent worker (W < 8: words and scale 0) adds +0, which changes no sum: none is ever -0.
-            const uint64_t y = gather_transpose(nlow, q) & x;         // negative only counts where non-zero
+            const uint64_t y = gather_transpose(wn, q) & x;         // negative only counts where non-zero
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 const uint32_t xe = (uint32_t)(x >> (8 * e)) & 15u, ye = (uint32_t)(y >> (8 * e)) & 15u;
-                float a = table[xe | (ye << 4)];
-#pragma unroll
-                for (int b = 4; b < 8; ++b) a = a + tern_term(wd[b], wn[b], 8 * q + e, s47[b - 4]);
-                acc[8 * q + e] = a;
+                acc[8 * q + e] = table[xe | (ye << 4)];
             }
         }
     }
-    if (W > 8) {
-        for (int w = 8; w < W; ++w) {
-            float sc = ld_uniform(&reinterpret_cast<const PayloadHeader *>(job.payload(w))->scale), sl = -sc;
-            if (!TERN) plane_levels(reinterpret_cast<const PayloadHeader *>(job.payload(w)), kind, sc, sl);
-            const uint32_t *plane = reinterpret_cast<const uint32_t *>(job.payload(w) + kHeaderBytes);
-            const uint32_t word = wi < nwords ? ld_stream(plane + wi) : 0u;
-            const uint32_t neg = TERN && wi < nwords ? ld_stream(plane + nwords + wi) : 0u;
+    for (int w0 = kTab; w0 < W; w0 += kMore) {
+        if (!TERN || w0 > kTab) load_words(w0, kMore, md, mn);
+        float hi[kMore], lo[kMore];
 #pragma unroll
-            for (int e = 0; e < 32; ++e) {
-                float d;
-                if (!TERN) d = plane_term(word, e, sc, sl);
-                else d = tern_term(word, neg, e, sc);
-                acc[e] = acc[e] + d;
+        for (int b = 0; b < kMore; ++b) {
+            const PayloadHeader *h = reinterpret_cast<const PayloadHeader *>(job.payload(w0 + b < W ? w0 + b : w0));
+            if (TERN) hi[b] = ld_uniform(&h->scale);
+            else plane_levels(h, kind, hi[b], lo[b]);
+        }
+#pragma unroll
+        for (int b = 0; b < kMore; ++b) {
+            if (w0 + b < W) {
+#pragma unroll
+                for (int e = 0; e < 32; ++e) acc[e] = acc[e] + (TERN ? tern_term(md[b], mn[b], e, hi[b]) : plane_term(md[b], e, hi[b], lo[b]));
             }
         }
     }
-    if (W > 8 || TERN) {
+    if (W > kTab || TERN) {
 #pragma unroll
         for (int e = 0; e < 32; ++e) acc[e] = alpha * (!TERN && kind == PLANE_VOTE ? vote_of(acc[e]) : acc[e]);
     }
