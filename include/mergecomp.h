@@ -305,12 +305,12 @@ int mc_set_barrier_spin_limit(mc_ctx *ctx, uint32_t polls);
  *                     two short kernels after the streaming pass
  *   MC_SELECT_DENSE   as FAST, but more than 4096 keys share that bin (many equal values): the bin
  *                     is resolved as one more radix level
- *   MC_SELECT_ABOVE   the threshold rose above the window (also a context's first call of a
- *                     (group, worker)): three radix levels over the candidates
+ *   MC_SELECT_ABOVE   the threshold rose above the window: three radix levels over the candidates (also
+ *                     reported for a context's first call of a (group, worker), which takes the steps of a refill)
  *   MC_SELECT_REFILL  fewer than k elements passed the candidate filter: the group is
- *                     streamed a second time, every element a candidate
- * The last three run as one kernel with grid-wide barriers and cost several times the first
- * (measured on a 25.6 M element group: 60 / 160 / 180-260 / 410-450 us for the whole call).
+ *                     streamed twice more
+ * The last three wait at grid-wide barriers inside a kernel and cost a few times the first
+ * (measured on a 25.6 M element group: 56 / 120 / 196 / 174 us for the whole call, a first call 176).
  * The result of mc_compress is identical on all routes; only its cost differs.
  * Returns the route, or a negative mc_status (MC_ERR_INVALID_ARG for a dense algorithm). */
 enum { MC_SELECT_ABOVE = 0, MC_SELECT_FAST = 1, MC_SELECT_REFILL = 2, MC_SELECT_DENSE = 3 };

@@ -39,7 +39,7 @@
 
 namespace mc {
 
-static inline uint32_t chunks_of(uint32_t n) { return (uint32_t)(((uint64_t)n + kChunk - 1) / kChunk); }
+__host__ __device__ static inline uint32_t chunks_of(uint32_t n) { return (uint32_t)(((uint64_t)n + kChunk - 1) / kChunk); }
 
 constexpr int kWindowShift = 11;                       // keys per window bin = 2^11: what hist 3 resolves after a fast seed
 constexpr int kBinsW = 2048, kBins1 = 2048, kBins2 = 1024, kBins3 = 1 << kWindowShift;
@@ -71,6 +71,7 @@ constexpr uint32_t kHintMargin = 3u << 19;   // 3/16 of an octave below the last
 constexpr int kHintShift = 1, kHintHold = 2, kHintCap = 3;
 constexpr uint32_t kHintShiftMax = 4u, kHintHoldCalls = 8u;      // margin at least 3/256 of an octave (0.8 %)
 constexpr uint32_t kHintCapCalls = 64u;
+constexpr uint32_t kHintSeen = 1u << 31;      // in the cap word: this (group, worker) has had a call, the filter key stands for something
 
 // How far below the threshold the next call starts filtering, after a call whose threshold lay inside the window.
 // Under error feedback the values pile up just below the threshold, in the long run those of every tensor, and a fixed
@@ -83,10 +84,10 @@ constexpr uint32_t kHintCapCalls = 64u;
 // A call whose threshold fell below the filter (a miss: a second streaming pass) resets the margin, keeps it for
 // kHintHoldCalls calls, and caps the halvings below what the margin had been halved to when it missed, one step
 // more being allowed again after every kHintCapCalls calls: a threshold that jitters by more than the tightest margin
-// costs a miss every so many calls, not every few.  cap word: steps taken off kHintShiftMax | calls left << 8.
+// costs a miss every so many calls, not every few.  cap word: steps taken off kHintShiftMax | calls left << 8 | kHintSeen.
 __device__ __forceinline__ void margin_after_hit(uint32_t *hint, uint32_t shift, uint32_t hold, uint32_t capw, uint64_t cands, uint64_t k)
 {
-    uint32_t off = capw & 0xFFu, left = capw >> 8;
+    uint32_t off = capw & 0xFFu, left = (capw & ~kHintSeen) >> 8;
     if (left) --left;
     else if (off) { --off; left = off ? kHintCapCalls : 0u; }
     const uint32_t cap = kHintShiftMax - (off < kHintShiftMax ? off : kHintShiftMax);
@@ -94,17 +95,22 @@ __device__ __forceinline__ void margin_after_hit(uint32_t *hint, uint32_t shift,
     else if (cands > 2u * k && shift < cap) ++shift;
     if (4u * cands < 5u * k && shift) --shift;
     if (shift > cap) shift = cap;
-    hint[kHintShift] = shift; hint[kHintHold] = hold; hint[kHintCap] = off | (left << 8);
+    hint[kHintShift] = shift; hint[kHintHold] = hold; hint[kHintCap] = off | (left << 8) | kHintSeen;
 }
 // below: the threshold fell below the filter (else it rose above the window, which no margin prevents)
-__device__ __forceinline__ void margin_after_miss(uint32_t *hint, uint32_t shift, bool below)
+__device__ __forceinline__ void margin_after_miss(uint32_t *hint, uint32_t shift, uint32_t capw, bool below)
 {
     hint[kHintShift] = 0u; hint[kHintHold] = kHintHoldCalls;
-    if (below && shift) hint[kHintCap] = (kHintShiftMax - (shift - 1u)) | (kHintCapCalls << 8);
+    hint[kHintCap] = (below && shift ? (kHintShiftMax - (shift - 1u)) | (kHintCapCalls << 8) : capw) | kHintSeen;
 }
+// What the streaming pass filters with: the record's key; before the first call of a (group, worker) a key that no element
+// reaches, for which the call is a refill.  (With every element a candidate the first pass took 118 us instead of 52, and
+// all later steps walked all elements.)
+__device__ __forceinline__ bool first_call(uint32_t hint, uint32_t capw) { return hint == 0u && !(capw & kHintSeen); }
 constexpr uint32_t kModeFast = 1u;      // lo / need are those of level 3 already
 constexpr uint32_t kModeUniform = 2u;   // after a refill: every element is a candidate, chunk c holds 1024 c ...
 constexpr uint32_t kModeLean = 4u;      // fast, and the keys of the threshold's window bin were listed: the emit kernel finishes alone
+constexpr uint32_t kModeFirst = 16u;    // first call of a (group, worker): a refill that is reported as "above", as first calls are
 constexpr uint32_t kModeDense = 8u;     // fast, but that bin holds too many keys to list: its 2048 keys were histogrammed instead
 
 __device__ __forceinline__ uint32_t key_of(float x) { return __float_as_uint(x) & 0x7FFFFFFFu; }
@@ -173,10 +179,10 @@ __global__ __launch_bounds__(kBlock) void sparse_accum_k(SRC src, float momentum
     const SparseScratch &sc = job.sc;
     const uint32_t order = job.blocks - 1u - job.block;          // the how-manieth of the group's blocks this is
     const Chunk c = my_chunk(g.n, job.block);
-    const uint32_t hint = *sc.hint;
+    const uint32_t hint0 = *sc.hint, hint = first_call(hint0, sc.hint[kHintCap]) ? 0xFFFFFFFFu : hint0;
     // the emit kernel of the call before is done with the list of keys in the threshold's bin: its sublists are empty again
     if (order == 0 && threadIdx.x < (uint32_t)kUSub) sc.ucount[threadIdx.x * kUCountStride] = 0u;
-    if (order == 0 && threadIdx.x == 0) sc.sync[0] = 0u;       // and nobody waits at a grid-wide barrier of that call any more
+    if (order == 0 && threadIdx.x == 0) *sc.arrive = 0u;       // and nobody waits at a grid-wide barrier of that call any more
     // The radix levels are cleared by the kernels that use them -- unless a call gave up at a barrier (MC_ERR_DEVICE):
     // what it left behind must not enter this call's counts.
     {
@@ -488,7 +494,7 @@ __global__ __launch_bounds__(kSeedThreads) void sparse_seed_k(GroupView g, const
         return;
     }
     // missed: the next calls filter with the full margin again, and keep it for a while
-    if (blockIdx.x == 0 && t == 0) margin_after_miss(sc.hint, hint_shift, !found);
+    if (blockIdx.x == 0 && t == 0) margin_after_miss(sc.hint, hint_shift, hint_cap, !found && !first_call(hint, hint_cap));
     const uint32_t ntiles = (g.n + (uint32_t)kTile - 1u) / (uint32_t)kTile;
     const uint32_t uwave = __builtin_amdgcn_readfirstlane(wave), waves = kSeedThreads / 64;
     if (found) {
@@ -818,78 +824,26 @@ __global__ __launch_bounds__(kBlock) void cand_emit_k(uint32_t n, uint32_t ntile
 //              threshold): the blocks histogram its 2048 keys, as level 3 of a radix select
 //     above    the threshold lies above the window: level 1 (bits 30..20 above the window's top) over
 //              the candidates
-//     refill   fewer than k candidates: every element becomes a candidate, level 1 over all keys
+//     refill   fewer than k candidates: levels 1 and 2 over all elements; those in or above level 1's bin
+//              become the candidates
 //   emit     lean: every block reads the whole list (it is small), finds the threshold key T and the
 //            number of keys equal to T to take with a histogram in LDS, counts the list's kept keys
 //            that lie before each of its tiles, adds the kept counts of the blocks before it, and
 //            compacts its tiles' kept candidates into the payload.  One kernel after the select: no
 //            level-3 pass, no counting pass.
-//            Otherwise the remaining radix levels, the per-tile counts and the compaction run as steps
-//            of this same kernel on as many blocks as the device surely holds at once, separated by
-//            grid-wide barriers: the rare routes cost no launch on the usual one.
+//            On the other routes the radix levels still open, the per-tile counts and the compaction run as steps of
+//            the select kernel's first blocks, at most one per compute unit, separated by grid-wide barriers; the
+//            emit kernel then only clears the window.  Written for the 57 registers that the select kernel may take
+//            without losing wavefronts (64), they cost the usual route no launch of their own: an idle slot
+//            between the two kernels was 1.2 us of 80.8 (Top-k compress, 25.6 M elements) and, with four groups, 4
+//            of 269.  Measured there without error feedback, whole call, before / after: first call 484 / 176 us,
+//            refill 398 / 174, above 241 / 196, dense 120 / 120.
 // Both kernels are bound by memory latency, not by traffic, so each asks for its tile's candidates as soon
 // as it knows how many there are, before it waits for anything else.
 // ---------------------------------------------------------------------------
 constexpr int kSelThreads = 1024, kSelWaves = kSelTiles;      // select: 16 tiles per block (the window is read once per block)
 constexpr int kEmitThreads = kBlock, kEmitWaves = kEmitTiles;    // emit: 4 tiles per block
-constexpr int kSyncArrive = 0, kSyncRoutes = 32, kSyncLastBin = 40, kSyncLastCands = 41;     // words of SparseScratch::sync (mc_api.hip reads the last three)
-
-struct TileRuns { uint32_t r0, r1, r2, total; };       // running sums of the candidates of a tile's four chunks
-__device__ __forceinline__ TileRuns decode_runs(uint64_t runs)
-{
-    TileRuns r;
-    r.r0 = (uint32_t)(runs & 0xFFFFu); r.r1 = r.r0 + (uint32_t)((runs >> 16) & 0xFFFFu);
-    r.r2 = r.r1 + (uint32_t)((runs >> 32) & 0xFFFFu); r.total = r.r2 + (uint32_t)(runs >> 48);
-    return r;
-}
-
-// ROUNDS rounds of 64 of a tile's candidates, from candidate number f0 on; candidate f0 + 64 u + lane is there if
-// that number is below the tile's total.  at: group-relative index of the element.
-template <int ROUNDS>
-struct CandBatch { uint32_t bits[ROUNDS], at[ROUNDS]; };
-
-template <int ROUNDS, bool WITH_AT>
-__device__ __forceinline__ void fetch_batch(const SparseScratch &sc, uint32_t tile, const TileRuns &r, uint32_t f0, CandBatch<ROUNDS> &c)
-{
-    const uint32_t lane = threadIdx.x & 63u;
-    size_t slot[ROUNDS];
-    bool valid[ROUNDS];
-#pragma unroll
-    for (int u = 0; u < ROUNDS; ++u) {
-        const uint32_t f = f0 + 64 * u + lane;
-        valid[u] = f < r.total;
-        const uint32_t s = (f >= r.r0) + (f >= r.r1) + (f >= r.r2);          // chunk of the tile, then slot inside it
-        const uint32_t off = f - (s == 0 ? 0u : s == 1 ? r.r0 : s == 2 ? r.r1 : r.r2);
-        const uint32_t ch = tile * (uint32_t)kWavesPerBlock + (valid[u] ? s : 0u);
-        slot[u] = valid[u] ? (size_t)ch * kChunk + off : (size_t)tile * kTile;
-        c.at[u] = ch * (uint32_t)kChunk;
-    }
-#pragma unroll
-    for (int u = 0; u < ROUNDS; ++u) {
-        c.bits[u] = 0u;
-        if (valid[u]) {
-            c.bits[u] = sc.cand_bits[slot[u]];
-            if (WITH_AT) c.at[u] += sc.cand_loc[slot[u]];
-        }
-    }
-}
-
-// Walk of a tile's candidates, 64 ROUNDS at a time (the slow routes: one memory latency per batch, so a crowded
-// tile wants large batches).  body(valid, bits, at).
-template <bool WITH_AT, int ROUNDS, typename Body>
-__device__ __forceinline__ void walk_small(const SparseScratch &sc, uint32_t tile, uint64_t runs, Body body)
-{
-    const TileRuns r = decode_runs(runs);
-    const uint32_t lane = threadIdx.x & 63u;
-    for (uint32_t f0 = 0; f0 < r.total; f0 += 64 * ROUNDS) {
-        CandBatch<ROUNDS> c;
-        fetch_batch<ROUNDS, WITH_AT>(sc, tile, r, f0, c);
-#pragma unroll
-        for (int u = 0; u < ROUNDS; ++u)
-            if (f0 + 64 * u < r.total) body(f0 + 64 * u + lane < r.total, c.bits[u], c.at[u]);
-    }
-}
-constexpr int kWalkRounds = 16, kCompactRounds = 8;      // candidates in flight per wavefront in the slow routes: 1024 when only read, 512 when placed
+constexpr int kSyncRoutes = 32, kSyncLastBin = 40, kSyncLastCands = 41;     // words of SparseScratch::sync (mc_api.hip reads the last three)
 
 // Select.  The keys inside the threshold's bin [lo, lo + 2048) -- rarely more than a few per tile -- are collected
 // in a buffer of the wavefront's own in LDS and appended to sublist `sub` with one atomic add per tile (per 64
@@ -908,36 +862,6 @@ __device__ __forceinline__ void flush_members(const SparseScratch &sc, MemberBuf
     if (lane < m.held && base + lane < kUCap) sc.ulist[(size_t)sub * kUCap + base + lane] = m.buf[lane];   // (always in range: the bin holds at most kUCap keys)
     __builtin_amdgcn_wave_barrier();
     m.held = 0u;
-}
-
-// Emit, one batch: a candidate is kept if its key is above T, or equal to T and among the first `need` such keys in
-// index order; its place in the payload is (keys above T before it) + min(keys equal to T before it, need).
-template <int ALGO, bool EF, int ROUNDS>
-__device__ __forceinline__ void emit_apply(const CandBatch<ROUNDS> &c, uint32_t total, uint32_t f0, uint32_t n, uint64_t k, float *st,
-                                           uint32_t *idx, float *val, uint32_t T, uint64_t need, uint64_t &gt_before, uint64_t &eq_before)
-{
-    const uint32_t lane = threadIdx.x & 63u;
-#pragma unroll
-    for (int u = 0; u < ROUNDS; ++u) {
-        if (f0 + 64 * u >= total) break;
-        const bool valid = f0 + 64 * u + lane < total;
-        const uint32_t key = c.bits[u] & 0x7FFFFFFFu;
-        const bool is_gt = valid && key > T, is_eq = valid && key == T;
-        const uint64_t bgt = __builtin_amdgcn_ballot_w64(is_gt), beq = __builtin_amdgcn_ballot_w64(is_eq);
-        const uint64_t gtb = gt_before + lanes_below(bgt), eqb = eq_before + lanes_below(beq);
-        if (is_gt || (is_eq && eqb < need)) {
-            const uint64_t pos = gtb + (eqb < need ? eqb : need);
-            const uint32_t i = c.at[u];
-            if (pos < k && i < n) {                  // always true for consistent scratch
-                idx[pos] = i;
-                if (ALGO == MC_ALGO_RANDK) val[pos] = st[i];      // the candidate slot holds the random key: the value is p
-                else val[pos] = __uint_as_float(c.bits[u]);
-                drop_sent<ALGO, EF>(st, n, i, is_eq);
-            }
-        }
-        gt_before += __popcll(bgt);
-        eq_before += __popcll(beq);
-    }
 }
 
 __device__ __forceinline__ void put_sparse_header(PayloadHeader *hdr, uint32_t algo, uint32_t n, uint64_t k)
@@ -986,192 +910,34 @@ __device__ __forceinline__ bool grid_barrier(uint32_t *arrive, uint32_t blocks, 
     return *dead == 0u;
 }
 
-// a radix level resolved for the whole block by its first wavefront
+// A radix level resolved by a block of 1024 threads, one or two adjacent bins each: the bin b with
+//   count(bins > b) < need <= count(bins >= b)   and   rest = need - count(bins > b)
+// (the counts stay below 2^32, there being fewer elements than that).  sums: 16 words of LDS, res: 2 words.
 template <int BINS>
-__device__ __forceinline__ void resolve_block(const uint32_t *fine, uint64_t need, uint32_t &bin, uint64_t &rest, uint32_t *res /* 3 words of LDS */)
+__device__ __forceinline__ void resolve_block(const uint32_t *fine, uint64_t need, uint32_t &bin, uint64_t &rest, uint32_t *res, uint32_t *sums)
 {
-    if (threadIdx.x < 64) {
-        uint32_t b;
-        uint64_t r;
-        resolve_wave<BINS>(fine, need, b, r);
-        if (threadIdx.x == 0) { res[0] = b; res[1] = (uint32_t)r; res[2] = (uint32_t)(r >> 32); }
+    constexpr int kPer = BINS / 1024;
+    static_assert(kPer == 1 || kPer == 2, "one or two bins per thread");
+    const uint32_t t = threadIdx.x, wave = t >> 6;
+    uint2 own = {0u, 0u};                        // the lower and the upper bin
+    if (kPer == 2) own = *reinterpret_cast<const uint2 *>(fine + 2u * t);
+    else own.x = fine[t];
+    const uint32_t both = own.x + own.y, incl = wave_scan_incl(both), total = wave_total(incl);
+    if ((t & 63u) == 0) sums[wave] = total;
+    if (t == 0) { res[0] = 0u; res[1] = 0u; }    // (an inconsistent histogram still gives a defined bin)
+    __syncthreads();
+    uint32_t above = total - incl;               // keys in the bins of higher threads
+#pragma unroll
+    for (int w = 0; w < 16; ++w) if ((uint32_t)w > wave) above += sums[w];
+    if ((uint64_t)above < need && need <= (uint64_t)above + both) {
+        const bool upper = kPer == 2 && need <= (uint64_t)above + own.y;
+        res[0] = (uint32_t)kPer * t + (upper ? 1u : 0u);
+        res[1] = (uint32_t)need - above - (kPer == 2 && !upper ? own.y : 0u);
     }
     __syncthreads();
     bin = res[0];
-    rest = (uint64_t)res[1] | ((uint64_t)res[2] << 32);
+    rest = res[1];
     __syncthreads();
-}
-
-constexpr int kRoundTiles = 4096;      // tiles per round of the slow routes' compaction: 256 blocks of 16 wavefronts at most
-
-// The routes that need more than the window: all radix levels still open, the per-tile counts and the ordered
-// compaction, as steps of one kernel of `blocks` blocks (which the device holds at once), each
-// wavefront taking tiles gw, gw + nw, ...  `mode`: what the window said (kModeFast | kModeDense: the threshold's
-// bin [lo, lo + 2048) is known but too full to list; 0: the threshold lies above lo, the window's top;
-// kModeUniform: too few candidates, every element becomes one).
-template <int ALGO, bool EF, bool FROM_STATE, bool RANDOM>
-__device__ __forceinline__ void slow_routes(const GroupView &g, float *st, PayloadHeader *hdr, uint64_t k, const SparseScratch &sc,
-                                            const RngKey &rng, uint32_t mode, uint32_t lo, uint64_t need, uint32_t me, uint32_t blocks,
-                                            uint32_t &round, int *status,
-                                            uint32_t *hist /* 2048 words of LDS */, uint32_t *pfx /* 2 * kRoundTiles words of LDS */,
-                                            uint32_t *small /* 64 words of LDS; word 4, "a barrier was not passed", cleared by the caller */)
-{
-    uint32_t *res = small, *dead = small + 4, *wsum = small + 8;      // wsum: 2 * kSelWaves words
-    const uint32_t t = threadIdx.x, lane = t & 63u, wave = __builtin_amdgcn_readfirstlane(t >> 6);
-    const uint32_t n = g.n, ntiles = tiles_in(n);
-    const uint32_t nw = blocks * kSelWaves, gw = me * kSelWaves + wave;
-    const bool uniform = (mode & kModeUniform) != 0u;
-    uint32_t T, bin;
-    auto runs_of = [&](uint32_t tile) { return uniform ? uniform_runs(tile, n) : sc.tile_runs[tile]; };
-    for (int b = t; b < kBins1; b += kSelThreads) hist[b] = 0u;
-    __syncthreads();
-    if (!(mode & kModeFast)) {
-        // ---- level 1: bits 30..20 of key - lo
-        if (!uniform) {
-            for (uint32_t tile = gw; tile < ntiles; tile += nw)
-                walk_small<false, kWalkRounds>(sc, tile, runs_of(tile), [&](bool valid, uint32_t bits, uint32_t) {
-                    const uint32_t key = bits & 0x7FFFFFFFu;
-                    if (valid && key >= lo) atomicAdd(&hist[(key - lo) >> 20], 1u);
-                });
-        } else {
-            // refill: every element becomes a candidate (chunk c holds candidates 1024 c ...)
-            const uint32_t nch = (n + (uint32_t)kChunk - 1u) / (uint32_t)kChunk;
-            for (uint32_t ch = gw; ch < nch; ch += nw) {
-                Chunk c;
-                c.base = ch * (uint32_t)kChunk;
-                c.lane = lane;
-                c.full = n - c.base >= (uint32_t)kChunk;
-                uint32_t bits[kSteps];
-                if (RANDOM) {
-                    chunk_words(rng.seed, rng.worker, rng.iter_lo, g.goff + c.base, c.lane, bits);
-#pragma unroll
-                    for (int j = 0; j < kSteps; ++j) bits[j] >>= 1;
-                } else {
-                    float v[kSteps];
-                    load_sel<FROM_STATE>(g, st, c, v);
-#pragma unroll
-                    for (int j = 0; j < kSteps; ++j) bits[j] = __float_as_uint(v[j]);
-                }
-#pragma unroll
-                for (int j = 0; j < kSteps; ++j) {
-                    const uint32_t i = c.base + 64 * j + c.lane;
-                    if (c.full || i < n) {
-                        sc.cand_bits[i] = bits[j];
-                        sc.cand_loc[i] = (uint16_t)(64 * j + c.lane);
-                        atomicAdd(&hist[(bits[j] & 0x7FFFFFFFu) >> 20], 1u);
-                    }
-                }
-            }
-        }
-        __syncthreads();
-        flush_fine(hist, sc.hist + kHist1, kBins1);
-        if (!grid_barrier(sc.sync + kSyncArrive, blocks, ++round, dead, status, sc.spin_limit)) return;
-        resolve_block<kBins1>(sc.hist + kHist1, need, bin, need, res);
-        lo += bin << 20;
-        // ---- level 2: bits 19..10
-        for (int b = t; b < kBins2; b += kSelThreads) hist[b] = 0u;
-        __syncthreads();
-        for (uint32_t tile = gw; tile < ntiles; tile += nw)
-            walk_small<false, kWalkRounds>(sc, tile, runs_of(tile), [&](bool valid, uint32_t bits, uint32_t) {
-                const uint32_t key = bits & 0x7FFFFFFFu;
-                if (valid && key >= lo && key - lo < (1u << 20)) atomicAdd(&hist[(key - lo) >> 10], 1u);
-            });
-        __syncthreads();
-        flush_fine(hist, sc.hist + kHist2, kBins2);
-        if (!grid_barrier(sc.sync + kSyncArrive, blocks, ++round, dead, status, sc.spin_limit)) return;
-        if (me == 0) for (int b = t; b < kBins1; b += kSelThreads) sc.hist[kHist1 + b] = 0u;    // every block has resolved level 1
-        resolve_block<kBins2>(sc.hist + kHist2, need, bin, need, res);
-        lo += bin << 10;
-        for (int b = t; b < kBins3; b += kSelThreads) hist[b] = 0u;
-        __syncthreads();
-    }
-    // ---- level 3: the bits still open (10 after level 2, the 11 of a window bin otherwise)
-    const uint32_t open = (mode & kModeFast) ? 1u << kWindowShift : 1u << 10;
-    for (uint32_t tile = gw; tile < ntiles; tile += nw)
-        walk_small<false, kWalkRounds>(sc, tile, runs_of(tile), [&](bool valid, uint32_t bits, uint32_t) {
-            const uint32_t key = bits & 0x7FFFFFFFu;
-            if (valid && key >= lo && key - lo < open) atomicAdd(&hist[key - lo], 1u);
-        });
-    __syncthreads();
-    flush_fine(hist, sc.hist + kHist3, kBins3);
-    if (!grid_barrier(sc.sync + kSyncArrive, blocks, ++round, dead, status, sc.spin_limit)) return;
-    if (!(mode & kModeFast) && me == 0) for (int b = t; b < kBins2; b += kSelThreads) sc.hist[kHist2 + b] = 0u;
-    resolve_block<kBins3>(sc.hist + kHist3, need, bin, need, res);
-    T = lo + bin;
-    // ---- kept candidates per tile
-    for (uint32_t tile = gw; tile < ntiles; tile += nw) {
-        uint32_t ngt = 0, neq = 0;
-        walk_small<false, kWalkRounds>(sc, tile, runs_of(tile), [&](bool valid, uint32_t bits, uint32_t) {
-            const uint32_t key = bits & 0x7FFFFFFFu;
-            ngt += __popcll(__builtin_amdgcn_ballot_w64(valid && key > T));
-            neq += __popcll(__builtin_amdgcn_ballot_w64(valid && key == T));
-        });
-        if (lane == 0) sc.tile_cnt[tile] = ngt | (neq << 16);              // a tile holds at most 4096 candidates
-    }
-    if (!grid_barrier(sc.sync + kSyncArrive, blocks, ++round, dead, status, sc.spin_limit)) return;
-    if (me == 0) for (int b = t; b < kBins3; b += kSelThreads) sc.hist[kHist3 + b] = 0u;
-    uint32_t *idx = reinterpret_cast<uint32_t *>(reinterpret_cast<uint8_t *>(hdr) + kHeaderBytes);
-    float *val = reinterpret_cast<float *>(idx + k);
-    if (me == 0 && t == 0) {
-        put_sparse_header(hdr, ALGO, n, k);
-        SelectState s;
-        s.lo = T; s.mode = mode; s.need = need;
-        sc.sel[3] = s;
-        publish_hint(sc, T);
-        record_sent_key<ALGO, EF>(st, T);
-    }
-    // ---- ordered compaction, kRoundTiles tiles at a time: every block scans the round's counts (in LDS) for the
-    // keys kept before each tile, and carries the totals of the rounds before
-    uint64_t base_gt = 0, base_eq = 0;
-    constexpr int kPer = kRoundTiles / kSelThreads;
-    for (uint32_t r0 = 0; r0 < ntiles; r0 += kRoundTiles) {
-        uint32_t cg[kPer], ce[kPer], sg = 0, se = 0;
-#pragma unroll
-        for (int i = 0; i < kPer; ++i) {
-            const uint32_t tile = r0 + t * kPer + i;
-            const uint32_t x = tile < ntiles ? sc.tile_cnt[tile] : 0u;
-            cg[i] = x & 0xFFFFu; ce[i] = x >> 16;
-            sg += cg[i]; se += ce[i];
-        }
-        uint32_t ig = sg, ie = se;                                          // inclusive scan over the block's threads
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            const uint32_t og = __shfl_up(ig, d, 64), oe = __shfl_up(ie, d, 64);
-            if (lane >= (uint32_t)d) { ig += og; ie += oe; }
-        }
-        if (lane == 63u) { wsum[wave] = ig; wsum[kSelWaves + wave] = ie; }
-        __syncthreads();
-        uint32_t wg = 0, we = 0, tg = 0, te = 0;
-#pragma unroll
-        for (int w = 0; w < kSelWaves; ++w) {
-            if ((uint32_t)w < wave) { wg += wsum[w]; we += wsum[kSelWaves + w]; }
-            tg += wsum[w]; te += wsum[kSelWaves + w];
-        }
-        uint32_t xg = wg + ig - sg, xe = we + ie - se;                       // kept before this thread's first tile, inside the round
-#pragma unroll
-        for (int i = 0; i < kPer; ++i) {
-            pfx[t * kPer + i] = xg; pfx[kRoundTiles + t * kPer + i] = xe;
-            xg += cg[i]; xe += ce[i];
-        }
-        __syncthreads();
-        for (uint32_t p = gw; p < (uint32_t)kRoundTiles && r0 + p < ntiles; p += nw) {
-            const uint32_t tile = r0 + p;
-            const TileRuns tr = decode_runs(runs_of(tile));
-            uint64_t gtb = base_gt + pfx[p], eqb = base_eq + pfx[kRoundTiles + p];
-            if (lane == 0) {
-                uint32_t *dir = payload_directory(hdr, k);
-                dir[tile] = (uint32_t)(gtb + (eqb < need ? eqb : need));
-                if (tile == ntiles - 1u) dir[ntiles] = (uint32_t)k;
-            }
-            for (uint32_t f0 = 0; f0 < tr.total; f0 += 64 * kCompactRounds) {
-                CandBatch<kCompactRounds> c;
-                fetch_batch<kCompactRounds, true>(sc, tile, tr, f0, c);
-                emit_apply<ALGO, EF, kCompactRounds>(c, tr.total, f0, n, k, st, idx, val, T, need, gtb, eqb);
-            }
-        }
-        base_gt += tg; base_eq += te;
-        __syncthreads();
-    }
 }
 
 // ---- access to the candidate slots of a tile ---------------------------------------------------------------
@@ -1202,8 +968,8 @@ __device__ __forceinline__ uint2 load_loc4(const SparseScratch &sc, uint32_t chu
 __device__ __forceinline__ uint32_t pick4(const uint32_t (&x)[4], uint32_t q) { return q == 0 ? x[0] : q == 1 ? x[1] : q == 2 ? x[2] : x[3]; }
 __device__ __forceinline__ uint32_t elem4(const uint4 &x, int j) { return j == 0 ? x.x : j == 1 ? x.y : j == 2 ? x.z : x.w; }
 __device__ __forceinline__ uint32_t loc4(const uint2 &x, int j) { return ((j < 2 ? x.x : x.y) >> (16 * (j & 1))) & 0xFFFFu; }
-// is candidate (unit v, lane, j) of a chunk with cnt candidates there?
-__device__ __forceinline__ bool in_unit(uint32_t cnt, uint32_t v, int j) { return (uint32_t)kHead + v * (uint32_t)kUnit + 4u * (threadIdx.x & 63u) + (uint32_t)j < cnt; }
+// is candidate (unit v, lane, j) of a chunk with cnt candidates there?  (head: candidates before unit 0)
+__device__ __forceinline__ bool in_unit(uint32_t cnt, uint32_t v, int j, uint32_t head = kHead) { return head + v * (uint32_t)kUnit + 4u * (threadIdx.x & 63u) + (uint32_t)j < cnt; }
 
 // The units of a tile, numbered in chunk order: unit e is unit v of chunk q.
 struct TileUnits {
@@ -1295,10 +1061,312 @@ __device__ __forceinline__ uint32_t select_tile(const SparseScratch &sc, TileAhe
     return above;
 }
 
-// The select kernel: sixteen tiles per block, one wavefront each; the window is read once per block.
-template <class SRC>
-__global__ __launch_bounds__(kSelThreads) void lean_select_k(SRC src)
+// Emit, lean route.  One candidate per lane (a chunk's head): gt0 / eq0 count the keys above / equal to T before it
+// in the whole group; returns them advanced past these 64.
+template <int ALGO, bool EF>
+__device__ __forceinline__ void emit_head(uint32_t bits, uint32_t loc, bool valid, uint32_t chunk, uint32_t n, uint32_t k, float *st,
+                                          uint32_t *idx, float *val, uint32_t T, uint32_t need, uint32_t &gt0, uint32_t &eq0)
 {
+    const uint32_t key = bits & 0x7FFFFFFFu;
+    const bool is_gt = valid && key > T, is_eq = valid && key == T;
+    const uint64_t bgt = __builtin_amdgcn_ballot_w64(is_gt), beq = __builtin_amdgcn_ballot_w64(is_eq);
+    const uint32_t gtb = gt0 + lanes_below(bgt);
+    const uint32_t eqb = eq0 + lanes_below(beq);
+    if (is_gt || (is_eq && eqb < need)) {
+        const uint32_t pos = gtb + (eqb < need ? eqb : need);
+        const uint32_t i = chunk * (uint32_t)kChunk + loc;
+        if (pos < k && i < n) {                  // always true for consistent scratch
+            idx[pos] = i;
+            if (ALGO == MC_ALGO_RANDK) val[pos] = st[i];      // the candidate slot holds the random key: the value is p
+            else val[pos] = __uint_as_float(bits);
+            drop_sent<ALGO, EF>(st, n, i, is_eq);
+        }
+    }
+    gt0 += __popcll(bgt); eq0 += __popcll(beq);
+}
+
+// ... four consecutive candidates per lane (a unit; it holds at most 256 keys above T and as many equal to it)
+template <int ALGO, bool EF, int HEAD = kHead>
+__device__ __forceinline__ void emit_unit(const uint4 &bits, const uint2 &loc, uint32_t cnt, uint32_t v, uint32_t chunk, uint32_t n,
+                                          uint32_t k, float *st, uint32_t *idx, float *val, uint32_t T, uint32_t need, uint32_t &gt0, uint32_t &eq0)
+{
+    bool isg[4], ise[4];
+    uint32_t mine = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const uint32_t key = elem4(bits, j) & 0x7FFFFFFFu;
+        const bool valid = in_unit(cnt, v, j, HEAD);
+        isg[j] = valid && key > T; ise[j] = valid && key == T;
+        mine += (isg[j] ? 1u : 0u) + (ise[j] ? 0x10000u : 0u);
+    }
+    const uint32_t inc = wave_scan_incl(mine);
+    const uint32_t tot = wave_total(inc);
+    uint32_t gtb = gt0 + ((inc - mine) & 0xFFFFu);
+    uint32_t eqb = eq0 + ((inc - mine) >> 16);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        if (isg[j] || (ise[j] && eqb < need)) {
+            const uint32_t pos = gtb + (eqb < need ? eqb : need);
+            const uint32_t i = chunk * (uint32_t)kChunk + loc4(loc, j);
+            if (pos < k && i < n) {
+                idx[pos] = i;
+                if (ALGO == MC_ALGO_RANDK) val[pos] = st[i];
+                else val[pos] = __uint_as_float(elem4(bits, j));
+                drop_sent<ALGO, EF>(st, n, i, ise[j]);
+            }
+        }
+        gtb += isg[j] ? 1u : 0u; eqb += ise[j] ? 1u : 0u;
+    }
+    gt0 += tot & 0xFFFFu; eq0 += tot >> 16;
+}
+
+// ---- the slow routes -------------------------------------------------------------------------------------------
+// A chunk's candidates in units of 256 from its first slot on, 16 bytes per lane and load.
+template <typename Body>
+__device__ __forceinline__ void each_of_chunk(const SparseScratch &sc, uint32_t chunk, uint32_t cnt, Body body)
+{
+    const uint32_t at = 4u * (threadIdx.x & 63u);
+    const uint4 *src = reinterpret_cast<const uint4 *>(sc.cand_bits + (size_t)chunk * kChunk) + (threadIdx.x & 63u);
+#pragma unroll 1
+    for (uint32_t v = 0; v < cnt; v += (uint32_t)kUnit) {
+        const uint4 x = src[v / 4u];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) body(v + at + j < cnt, elem4(x, j));
+    }
+}
+// All candidates of the group, chunks gw, gw + nw, ... to a wavefront; in no order.
+template <typename Body>
+__device__ __forceinline__ void walk_chunks(const SparseScratch &sc, uint32_t nch, uint32_t gw, uint32_t nw, Body body)
+{
+    const uint16_t *runs = reinterpret_cast<const uint16_t *>(sc.tile_runs);
+    for (uint32_t ch = gw; ch < nch; ch += nw)
+        each_of_chunk(sc, ch, (uint32_t)__builtin_amdgcn_readfirstlane((int)runs[ch]), body);
+}
+// body(valid, bits, position in the chunk) for the elements of a chunk, in index order from call to call.  Written for few
+// registers: Rand-k's words are drawn one element at a time (a block each), a chunk that straddles tensors tensor by tensor.
+template <bool FROM_STATE, bool RANDOM, typename Body>
+__device__ __forceinline__ void each_key(const GroupView &g, const float *st, const RngKey &rng, const Chunk &c, Body body)
+{
+    const uintptr_t entry = FROM_STATE || RANDOM ? 0u : chunk_entry(g, c);
+    if (RANDOM) {
+#pragma unroll 1
+        for (uint32_t at = c.lane; at < (uint32_t)kChunk; at += 64u) {
+            uint32_t w[4];
+            const uint64_t i = g.goff + c.base + at;
+            philox4x32_10(rng.seed, rng.worker, rng.iter_lo, i >> 2, w);
+            body(c.full || c.base + at < g.n, pick4(w, (uint32_t)i & 3u) >> 1, at);
+        }
+    } else if (!(entry & 1u)) {
+        float v[kSteps];
+        if (FROM_STATE) load_flat(st, c, g.n, v, 0.0f);
+        else {
+            const float *p = reinterpret_cast<const float *>(entry) + c.lane;
+#pragma unroll
+            for (int j = 0; j < kSteps; ++j) v[j] = ld_stream(p + 64 * j);
+        }
+#pragma unroll
+        for (int j = 0; j < kSteps; ++j) {
+            body(c.full || c.base + 64 * j + c.lane < g.n, __float_as_uint(v[j]), 64u * j + c.lane);
+            __builtin_amdgcn_sched_barrier(0);       // (one step after the other: side by side they need more registers than there are)
+        }
+    } else {
+        for_each_tensor_of_chunk(g, c, (uint32_t)(entry >> 1), [&](uint32_t beg, uint32_t end, uintptr_t ptr) {
+            const float *p = reinterpret_cast<const float *>(ptr);
+#pragma unroll 1
+            for (uint32_t at = c.lane; at < (uint32_t)kChunk; at += 64u) {
+                const uint32_t i = c.base + at;
+                const bool in = i >= beg && i < end;
+                body(in, in ? __float_as_uint(p[i - beg]) : 0u, at);
+            }
+        });
+    }
+}
+
+constexpr int kRoundTiles = 4096;      // tiles per round of the slow routes' compaction: 256 blocks of 16 wavefronts at most
+
+// The routes that need more than the window: all radix levels still open, the per-tile counts and the ordered
+// compaction, as steps of the first `blocks` blocks of the group's select blocks (which the device holds at once).
+// `mode`: what the window said (kModeFast | kModeDense: the threshold's bin [lo, lo + 2048) is known but too full to
+// list; 0: the threshold lies above lo, the window's top; kModeUniform: too few candidates.  Then the elements
+// themselves are streamed twice more, for level 1 and for level 2, and the second time those that reach the bin of
+// level 1 -- an eighth of an octave -- become the candidates of the later steps.)
+template <int ALGO, bool EF, bool FROM_STATE, bool RANDOM>
+__device__ __forceinline__ void slow_routes(const SparseJob &job, const RngKey &rng, uint32_t mode, uint32_t lo, uint64_t need, uint32_t blocks,
+                                            int *status, uint32_t *hist /* 2048 words of LDS */, uint32_t *pfx /* 2 * kRoundTiles words of LDS */,
+                                            uint32_t *small /* 64 words of LDS */)
+{
+    uint32_t *res = small, *dead = small + 4, *wsum = small + 8;      // wsum: 2 * kSelWaves words
+    const SparseScratch &sc = job.sc;
+    const GroupView &g = job.g;
+    float *st = job.st;
+    PayloadHeader *hdr = job.hdr;
+    const uint32_t k = (uint32_t)job.k;
+    const uint32_t t = threadIdx.x, lane = t & 63u, wave = __builtin_amdgcn_readfirstlane(t >> 6), me = job.block;
+    const uint32_t n = g.n, ntiles = tiles_in(n), nch = chunks_of(n);
+    const uint32_t nw = blocks * kSelWaves, gw = me * kSelWaves + wave;
+    const bool refill = (mode & kModeUniform) != 0u;
+    if (t == 0) *dead = 0u;
+    uint32_t round = 0, T, bin;
+    for (int b = t; b < kBins1; b += kSelThreads) hist[b] = 0u;
+    __syncthreads();
+    if (!(mode & kModeFast)) {
+        // ---- level 1: bits 30..20 of key - lo
+        if (!refill) {
+            walk_chunks(sc, nch, gw, nw, [&](bool valid, uint32_t bits) {
+                const uint32_t key = bits & 0x7FFFFFFFu;
+                if (valid && key >= lo) atomicAdd(&hist[(key - lo) >> 20], 1u);
+            });
+        } else {
+            for (uint32_t ch = gw; ch < nch; ch += nw) {
+                const Chunk c{ch * (uint32_t)kChunk, lane, n - ch * (uint32_t)kChunk >= (uint32_t)kChunk};
+                each_key<FROM_STATE, RANDOM>(g, st, rng, c, [&](bool valid, uint32_t bits, uint32_t) {
+                    if (valid) atomicAdd(&hist[(bits & 0x7FFFFFFFu) >> 20], 1u);
+                });
+            }
+        }
+        __syncthreads();
+        flush_fine(hist, sc.hist + kHist1, kBins1);
+        if (!grid_barrier(sc.arrive, blocks, ++round, dead, status, sc.spin_limit)) return;
+        resolve_block<kBins1>(sc.hist + kHist1, need, bin, need, res, wsum);
+        lo += bin << 20;
+        // ---- level 2: bits 19..10
+        for (int b = t; b < kBins2; b += kSelThreads) hist[b] = 0u;
+        __syncthreads();
+        if (!refill) {
+            walk_chunks(sc, nch, gw, nw, [&](bool valid, uint32_t bits) {
+                const uint32_t key = bits & 0x7FFFFFFFu;
+                if (valid && key >= lo && key - lo < (1u << 20)) atomicAdd(&hist[(key - lo) >> 10], 1u);
+            });
+        } else {
+            for (uint32_t ch = gw; ch < nch; ch += nw) {
+                const Chunk c{ch * (uint32_t)kChunk, lane, n - ch * (uint32_t)kChunk >= (uint32_t)kChunk};
+                uint32_t run = 0;
+                each_key<FROM_STATE, RANDOM>(g, st, rng, c, [&](bool valid, uint32_t bits, uint32_t at) {
+                    const uint32_t key = bits & 0x7FFFFFFFu;
+                    const bool in = valid && key >= lo;
+                    const uint64_t flag = __builtin_amdgcn_ballot_w64(in);
+                    if (in) {
+                        const uint32_t slot = c.base + run + lanes_below(flag);
+                        sc.cand_bits[slot] = bits;
+                        sc.cand_loc[slot] = (uint16_t)at;
+                        if (key - lo < (1u << 20)) atomicAdd(&hist[(key - lo) >> 10], 1u);
+                    }
+                    run += __popcll(flag);
+                });
+                if (lane == 0) reinterpret_cast<uint16_t *>(sc.tile_runs)[ch] = (uint16_t)run;
+            }
+        }
+        __syncthreads();
+        flush_fine(hist, sc.hist + kHist2, kBins2);
+        if (!grid_barrier(sc.arrive, blocks, ++round, dead, status, sc.spin_limit)) return;
+        if (me == 0) for (int b = t; b < kBins1; b += kSelThreads) sc.hist[kHist1 + b] = 0u;    // every block has resolved level 1
+        resolve_block<kBins2>(sc.hist + kHist2, need, bin, need, res, wsum);
+        lo += bin << 10;
+        for (int b = t; b < kBins3; b += kSelThreads) hist[b] = 0u;
+        __syncthreads();
+    }
+    // ---- level 3: the bits still open (10 after level 2, the 11 of a window bin otherwise)
+    const uint32_t open = (mode & kModeFast) ? 1u << kWindowShift : 1u << 10;
+    walk_chunks(sc, nch, gw, nw, [&](bool valid, uint32_t bits) {
+        const uint32_t key = bits & 0x7FFFFFFFu;
+        if (valid && key >= lo && key - lo < open) atomicAdd(&hist[key - lo], 1u);
+    });
+    __syncthreads();
+    flush_fine(hist, sc.hist + kHist3, kBins3);
+    if (!grid_barrier(sc.arrive, blocks, ++round, dead, status, sc.spin_limit)) return;
+    if (!(mode & kModeFast) && me == 0) for (int b = t; b < kBins2; b += kSelThreads) sc.hist[kHist2 + b] = 0u;
+    resolve_block<kBins3>(sc.hist + kHist3, need, bin, need, res, wsum);
+    T = lo + bin;
+    // ---- kept candidates per tile
+    for (uint32_t tile = gw; tile < ntiles; tile += nw) {
+        const uint64_t runs = sc.tile_runs[tile];
+        uint32_t both = 0;                                     // above T, and equal to T << 16 (a lane holds 64 of the tile's)
+#pragma unroll 1
+        for (int q = 0; q < kWavesPerBlock; ++q) {
+            const uint32_t cnt = (uint32_t)__builtin_amdgcn_readfirstlane((int)((uint32_t)(runs >> (16 * q)) & 0xFFFFu));
+            each_of_chunk(sc, tile * kWavesPerBlock + q, cnt, [&](bool valid, uint32_t bits) {
+                const uint32_t key = bits & 0x7FFFFFFFu;
+                both += (valid && key > T ? 1u : 0u) + (valid && key == T ? 0x10000u : 0u);
+            });
+        }
+        both = wave_total(wave_scan_incl(both));               // a tile holds at most 4096 of either
+        if (lane == 0) sc.tile_cnt[tile] = both;
+    }
+    if (!grid_barrier(sc.arrive, blocks, ++round, dead, status, sc.spin_limit)) return;
+    if (me == 0) for (int b = t; b < kBins3; b += kSelThreads) sc.hist[kHist3 + b] = 0u;
+    uint32_t *idx = reinterpret_cast<uint32_t *>(reinterpret_cast<uint8_t *>(hdr) + kHeaderBytes);
+    float *val = reinterpret_cast<float *>(idx + k);
+    if (me == 0 && t == 0) {
+        put_sparse_header(hdr, ALGO, n, k);
+        SelectState s;
+        s.lo = T; s.mode = mode; s.need = need;
+        sc.sel[3] = s;
+        publish_hint(sc, T);
+        record_sent_key<ALGO, EF>(st, T);
+    }
+    // ---- ordered compaction, kRoundTiles tiles at a time: every block scans the round's counts (in LDS) for the
+    // keys kept before each tile, and carries the totals of the rounds before
+    uint32_t base_gt = 0, base_eq = 0;                                       // (numbers of elements: below 2^32, as k is)
+    constexpr int kPer = kRoundTiles / kSelThreads;
+    for (uint32_t r0 = 0; r0 < ntiles; r0 += kRoundTiles) {
+        uint32_t x[kPer], sg = 0, se = 0;
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            const uint32_t tile = r0 + t * kPer + i;
+            x[i] = tile < ntiles ? sc.tile_cnt[tile] : 0u;
+            sg += x[i] & 0xFFFFu; se += x[i] >> 16;
+        }
+        const uint32_t ig = wave_scan_incl(sg), ie = wave_scan_incl(se);     // inclusive scans over the wavefront
+        if (lane == 63u) { wsum[wave] = ig; wsum[kSelWaves + wave] = ie; }
+        __syncthreads();
+        // (the sixteen wavefronts' totals, scanned in the lanes)
+        const uint32_t vg = lane < (uint32_t)kSelWaves ? wsum[lane] : 0u, ve = lane < (uint32_t)kSelWaves ? wsum[kSelWaves + lane] : 0u;
+        const uint32_t pg = wave_scan_incl(vg), pe = wave_scan_incl(ve);
+        const uint32_t wg = (uint32_t)__builtin_amdgcn_readlane((int)(pg - vg), (int)wave), we = (uint32_t)__builtin_amdgcn_readlane((int)(pe - ve), (int)wave);
+        const uint32_t tg = wave_total(pg), te = wave_total(pe);
+        uint32_t xg = wg + ig - sg, xe = we + ie - se;                       // kept before this thread's first tile, inside the round
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            pfx[t * kPer + i] = xg; pfx[kRoundTiles + t * kPer + i] = xe;
+            xg += x[i] & 0xFFFFu; xe += x[i] >> 16;
+        }
+        __syncthreads();
+        for (uint32_t p = gw; p < (uint32_t)kRoundTiles && r0 + p < ntiles; p += nw) {
+            const uint32_t tile = r0 + p;
+            const uint64_t runs = sc.tile_runs[tile];
+            uint32_t gtb = base_gt + pfx[p], eqb = base_eq + pfx[kRoundTiles + p];
+            if (lane == 0) {
+                uint32_t *dir = payload_directory(hdr, k);
+                dir[tile] = gtb + (eqb < (uint32_t)need ? eqb : (uint32_t)need);
+                if (tile == ntiles - 1u) dir[ntiles] = k;
+            }
+#pragma unroll 1
+            for (int q = 0; q < kWavesPerBlock; ++q) {
+                const uint32_t cnt = (uint32_t)__builtin_amdgcn_readfirstlane((int)((uint32_t)(runs >> (16 * q)) & 0xFFFFu));
+                const uint32_t chunk = tile * kWavesPerBlock + q;
+                const uint4 *src = reinterpret_cast<const uint4 *>(sc.cand_bits + (size_t)chunk * kChunk) + lane;
+                const uint2 *locs = reinterpret_cast<const uint2 *>(sc.cand_loc + (size_t)chunk * kChunk) + lane;
+#pragma unroll 1
+                for (uint32_t v = 0; v * kUnit < cnt; ++v)
+                    emit_unit<ALGO, EF, 0>(src[64 * v], locs[64 * v], cnt, v, chunk, n, k, st, idx, val, T, (uint32_t)need, gtb, eqb);
+            }
+        }
+        base_gt += tg; base_eq += te;
+        __syncthreads();
+    }
+}
+
+// The select kernel: sixteen tiles per block, one wavefront each; the window is read once per block.  When the window does
+// not settle the selection, the group's first blocks go on with the slow routes, which wait for one another: blocks
+// start in the order of their numbers, so at most `sync_blocks` of them -- one per compute unit -- are held at once whatever
+// the size of the group, and of several groups the earliest that is not done has all of its own running.
+template <int ALGO, bool EF, class SRC>
+__attribute__((amdgpu_waves_per_eu(8, 8)))
+__global__ __launch_bounds__(kSelThreads) void lean_select_k(SRC src, RngKey rng, uint32_t sync_blocks, int *status)
+{
+    __shared__ __attribute__((aligned(16))) uint32_t hist[kBins1];      // (these three: slow routes)
+    __shared__ uint32_t pfx[2 * kRoundTiles];
+    __shared__ uint32_t small[64];
     __shared__ uint32_t wtot[kSelWaves];
     __shared__ uint32_t verdict[8];              // found, bin, rest lo, rest hi, candidates lo, hi, keys in the bin
     __shared__ UEntry members[kSelWaves][kMemberBuf];
@@ -1348,22 +1416,31 @@ __global__ __launch_bounds__(kSelThreads) void lean_select_k(SRC src)
     __syncthreads();
     const bool found = verdict[0] != 0u;
     const uint32_t bin = verdict[1];
-    const bool first = job.block == 0 && t == 0;
+    const bool first = job.block == 0 && t == 0, fresh = first_call(hint, hint_cap);
     if (first && job.reports) {
-        sc.sync[kSyncLastBin] = found ? verdict[6] : 0u;                // diagnostics (mc_select_stats)
-        sc.sync[kSyncLastCands] = verdict[4];
+        sc.sync[kSyncLastBin] = fresh ? job.g.n : found ? verdict[6] : 0u;          // diagnostics (mc_select_stats); before a first call
+        sc.sync[kSyncLastCands] = fresh ? job.g.n : verdict[4];                     // nothing is filtered out
     }
+    uint32_t mode = found ? 0u : kModeUniform | (fresh ? kModeFirst : 0u), lo = found ? hint + (((uint32_t)kBinsW - 1u) << kWindowShift) : 0u;
+    uint64_t need = k;
     if (found && bin < (uint32_t)kBinsW - 1u) {
-        const uint32_t lo = hint + (bin << kWindowShift);
+        lo = hint + (bin << kWindowShift);
+        need = (uint64_t)verdict[2] | ((uint64_t)verdict[3] << 32);
         const bool lean = verdict[6] <= kUCap;
-        if (first) {
-            SelectState s;
-            s.lo = lo; s.mode = kModeFast | (lean ? kModeLean : kModeDense); s.need = (uint64_t)verdict[2] | ((uint64_t)verdict[3] << 32);
-            sc.sel[0] = s;
-            margin_after_hit(sc.hint, hint_shift, hint_hold, hint_cap, (uint64_t)verdict[4] | ((uint64_t)verdict[5] << 32), k);
-            atomicAdd(&sc.sync[kSyncRoutes + (lean ? MC_SELECT_FAST : MC_SELECT_DENSE)], 1u);
-        }
-        if (!lean) return;               // dense bin: too many keys to list; the slow-route kernel takes its 2048 keys as a radix level
+        mode = kModeFast | (lean ? kModeLean : kModeDense);
+        if (first) margin_after_hit(sc.hint, hint_shift, hint_hold, hint_cap, (uint64_t)verdict[4] | ((uint64_t)verdict[5] << 32), k);
+    } else if (first) {
+        // missed: the next calls filter with the full margin again, and keep it for a while
+        margin_after_miss(sc.hint, hint_shift, hint_cap, !found && !fresh);
+    }
+    if (first) {
+        SelectState s;
+        s.lo = lo; s.mode = mode; s.need = need;
+        sc.sel[0] = s;
+        const uint32_t route = (mode & kModeLean) ? MC_SELECT_FAST : (mode & kModeDense) ? MC_SELECT_DENSE : found || fresh ? MC_SELECT_ABOVE : MC_SELECT_REFILL;
+        atomicAdd(&sc.sync[kSyncRoutes + route], 1u);
+    }
+    if (mode & kModeLean) {
         uint32_t above = 0;
         if (tile < ntiles) {
             const uint32_t sub = tile & (uint32_t)(kUSub - 1);
@@ -1382,142 +1459,9 @@ __global__ __launch_bounds__(kSelThreads) void lean_select_k(SRC src)
         }
         return;
     }
-    // missed: the next calls filter with the full margin again, and keep it for a while
-    if (first) {
-        margin_after_miss(sc.hint, hint_shift, !found);
-        SelectState s;
-        s.lo = found ? hint + (((uint32_t)kBinsW - 1u) << kWindowShift) : 0u; s.mode = found ? 0u : kModeUniform; s.need = k;
-        sc.sel[0] = s;
-        atomicAdd(&sc.sync[kSyncRoutes + (found ? MC_SELECT_ABOVE : MC_SELECT_REFILL)], 1u);
-    }
-}
-
-// The slow routes, in a kernel of their own so that their registers do not weigh on the two kernels of the usual
-// route: inside the select kernel they took it to 128 registers and to spilling (one block per compute unit, or two
-// tiles per wavefront: 13 .. 30 us instead of 7 .. 10), inside the emit kernel to 108 registers and two rounds of
-// blocks.  On the lean route this kernel reads one word and leaves (4 us).
-template <int ALGO, bool EF, bool FROM_STATE, bool RANDOM>
-__global__ __launch_bounds__(kSelThreads) void sparse_slow_k(OneSparse src, RngKey rng, int *status)
-{
-    __shared__ __attribute__((aligned(16))) uint32_t hist[kBins1];
-    __shared__ uint32_t pfx[2 * kRoundTiles];
-    __shared__ uint32_t small[64];
-    const SelectState s0 = src.sc.sel[0];
-    if (s0.mode & kModeLean) return;
-    if (threadIdx.x == 0) small[4] = 0u;
-    __syncthreads();
-    uint32_t round = 0;
-    slow_routes<ALGO, EF, FROM_STATE, RANDOM>(src.g, src.st, src.hdr, src.k, src.sc, rng, s0.mode, s0.lo, s0.need, blockIdx.x, gridDim.x, round,
-                                              status, hist, pfx, small);
-}
-
-// The same for a launch over all groups.  Every block looks at the verdicts of all groups, 1024 at a time, and lists
-// those that need more than the window.  A group of at most kSoloTiles tiles is one block's work -- no barrier
-// between blocks, and many such groups at once, as in a first call of a layer-wise partition --, a larger one that of
-// all blocks, one group after the other.
-constexpr uint32_t kSoloTiles = 64;
-template <int ALGO, bool EF, bool FROM_STATE, bool RANDOM>
-__global__ __launch_bounds__(kSelThreads) void sparse_slow_all_k(AllSparse src, RngKey rng, int *status)
-{
-    __shared__ __attribute__((aligned(16))) uint32_t hist[kBins1];
-    __shared__ uint32_t pfx[2 * kRoundTiles];
-    __shared__ uint32_t small[64];
-    __shared__ uint32_t slow[kSelThreads];
-    __shared__ uint32_t waves[kSelWaves];
-    const uint32_t t = threadIdx.x, lane = t & 63u, wave = __builtin_amdgcn_readfirstlane(t >> 6);
-    uint32_t round = 0;
-    for (uint32_t q0 = 0; q0 < src.tb.y; q0 += kSelThreads) {
-        const uint32_t q = q0 + t;
-        bool need = false;
-        if (q < src.tb.y) need = src.tb.groups[q].n != 0u && !(src.all.sel[(size_t)q * 4].mode & kModeLean);
-        const uint64_t b = __builtin_amdgcn_ballot_w64(need);
-        if (lane == 0) waves[wave] = (uint32_t)__popcll(b);
-        if (t == 0) small[4] = 0u;
-        __syncthreads();
-        uint32_t before = 0, count = 0;
-#pragma unroll
-        for (int w = 0; w < kSelWaves; ++w) { if ((uint32_t)w < wave) before += waves[w]; count += waves[w]; }
-        if (need) slow[before + lanes_below(b)] = q;
-        __syncthreads();
-        if (count == 0) continue;
-        for (int large = 0; large < 2; ++large) {
-            uint32_t turn = 0;                       // which of the small groups this is: block `turn` takes it
-            for (uint32_t i = 0; i < count; ++i) {
-                const uint32_t g = __builtin_amdgcn_readfirstlane(slow[i]);
-                const bool solo = tiles_in(src.tb.groups[g].n) <= kSoloTiles;
-                if (solo == (large != 0)) continue;
-                if (solo && turn++ % gridDim.x != blockIdx.x) continue;
-                const SparseJob job = src.group_job(g);
-                const SelectState s0 = job.sc.sel[0];
-                const uint32_t passed = round;       // the barriers that all blocks have passed together: a solo group's do not count
-                slow_routes<ALGO, EF, FROM_STATE, RANDOM>(job.g, job.st, job.hdr, job.k, job.sc, rng, s0.mode, s0.lo, s0.need,
-                                                          solo ? 0u : blockIdx.x, solo ? 1u : gridDim.x, round, status, hist, pfx, small);
-                if (solo) round = passed;
-                __syncthreads();                     // the next group uses the same LDS
-                if (small[4]) return;                // a barrier was not passed
-            }
-        }
-        __syncthreads();
-    }
-}
-
-// Emit, lean route.  One candidate per lane (a chunk's head): gt0 / eq0 count the keys above / equal to T before it
-// in the whole group; returns them advanced past these 64.
-template <int ALGO, bool EF>
-__device__ __forceinline__ void emit_head(uint32_t bits, uint32_t loc, bool valid, uint32_t chunk, uint32_t n, uint64_t k, float *st,
-                                          uint32_t *idx, float *val, uint32_t T, uint32_t need, uint64_t &gt0, uint32_t &eq0)
-{
-    const uint32_t key = bits & 0x7FFFFFFFu;
-    const bool is_gt = valid && key > T, is_eq = valid && key == T;
-    const uint64_t bgt = __builtin_amdgcn_ballot_w64(is_gt), beq = __builtin_amdgcn_ballot_w64(is_eq);
-    const uint64_t gtb = gt0 + lanes_below(bgt);
-    const uint32_t eqb = eq0 + lanes_below(beq);
-    if (is_gt || (is_eq && eqb < need)) {
-        const uint64_t pos = gtb + (eqb < need ? eqb : need);
-        const uint32_t i = chunk * (uint32_t)kChunk + loc;
-        if (pos < k && i < n) {                  // always true for consistent scratch
-            idx[pos] = i;
-            if (ALGO == MC_ALGO_RANDK) val[pos] = st[i];      // the candidate slot holds the random key: the value is p
-            else val[pos] = __uint_as_float(bits);
-            drop_sent<ALGO, EF>(st, n, i, is_eq);
-        }
-    }
-    gt0 += __popcll(bgt); eq0 += __popcll(beq);
-}
-
-// ... four consecutive candidates per lane (a unit; it holds at most 256 keys above T and as many equal to it)
-template <int ALGO, bool EF>
-__device__ __forceinline__ void emit_unit(const uint4 &bits, const uint2 &loc, uint32_t cnt, uint32_t v, uint32_t chunk, uint32_t n,
-                                          uint64_t k, float *st, uint32_t *idx, float *val, uint32_t T, uint32_t need, uint64_t &gt0, uint32_t &eq0)
-{
-    bool isg[4], ise[4];
-    uint32_t mine = 0;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const uint32_t key = elem4(bits, j) & 0x7FFFFFFFu;
-        const bool valid = in_unit(cnt, v, j);
-        isg[j] = valid && key > T; ise[j] = valid && key == T;
-        mine += (isg[j] ? 1u : 0u) + (ise[j] ? 0x10000u : 0u);
-    }
-    const uint32_t inc = wave_scan_incl(mine);
-    const uint32_t tot = wave_total(inc);
-    uint64_t gtb = gt0 + ((inc - mine) & 0xFFFFu);
-    uint32_t eqb = eq0 + ((inc - mine) >> 16);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        if (isg[j] || (ise[j] && eqb < need)) {
-            const uint64_t pos = gtb + (eqb < need ? eqb : need);
-            const uint32_t i = chunk * (uint32_t)kChunk + loc4(loc, j);
-            if (pos < k && i < n) {
-                idx[pos] = i;
-                if (ALGO == MC_ALGO_RANDK) val[pos] = st[i];
-                else val[pos] = __uint_as_float(elem4(bits, j));
-                drop_sent<ALGO, EF>(st, n, i, ise[j]);
-            }
-        }
-        gtb += isg[j] ? 1u : 0u; eqb += ise[j] ? 1u : 0u;
-    }
-    gt0 += tot & 0xFFFFu; eq0 += tot >> 16;
+    const uint32_t blocks = job.blocks < sync_blocks ? job.blocks : sync_blocks;
+    if (job.block < blocks)
+        slow_routes<ALGO, EF, ALGO == MC_ALGO_DGC || EF, ALGO == MC_ALGO_RANDK>(job, rng, mode, lo, need, blocks, status, hist, pfx, small);
 }
 
 // Emit: four tiles per block, one wavefront each.  Every block reads the whole list of the keys in the threshold's
@@ -1546,7 +1490,7 @@ __global__ __launch_bounds__(kEmitThreads) void lean_emit_k(SRC src)
     const SparseScratch &sc = job.sc;
     float *st = job.st;
     PayloadHeader *hdr = job.hdr;
-    const uint64_t k = job.k;
+    const uint32_t k = (uint32_t)job.k;
     const uint32_t n = job.g.n, ntiles = tiles_in(n);
     const uint32_t tile = job.block * kEmitWaves + wave;
     const bool live = tile < ntiles;
@@ -1677,7 +1621,7 @@ __global__ __launch_bounds__(kEmitThreads) void lean_emit_k(SRC src)
     __syncthreads();
     if (job.block == 0 && t == 0) { put_sparse_header(hdr, ALGO, n, k); publish_hint(sc, T); record_sent_key<ALGO, EF>(st, T); }
     if (!live) return;
-    uint64_t gt0 = mine;
+    uint32_t gt0 = mine;
     uint32_t eq0;
 #pragma unroll
     for (int w = 0; w < kEmitWaves; ++w) gt0 += red[w];
@@ -1691,8 +1635,8 @@ __global__ __launch_bounds__(kEmitThreads) void lean_emit_k(SRC src)
     float *val = reinterpret_cast<float *>(idx + k);
     if (lane == 0) {
         uint32_t *dir = payload_directory(hdr, k);
-        dir[tile] = (uint32_t)(gt0 + (eq0 < need ? eq0 : need));
-        if (tile == ntiles - 1u) dir[ntiles] = (uint32_t)k;              // (the selection keeps exactly k)
+        dir[tile] = gt0 + (eq0 < need ? eq0 : need);
+        if (tile == ntiles - 1u) dir[ntiles] = k;              // (the selection keeps exactly k)
     }
     if (tu.total == 0) {
         // the usual tile: no chunk holds more than 64 candidates, and they are all here
@@ -1736,18 +1680,6 @@ __global__ __launch_bounds__(kEmitThreads) void lean_emit_k(SRC src)
     }
 }
 
-// the slow routes of one group, or of all
-template <int ALGO, bool EF>
-static void launch_slow(const LaunchCtx &lc, uint32_t blocks, const OneSparse &src, const RngKey &rng, int *status)
-{
-    MC_LAUNCH((sparse_slow_k<ALGO, EF, ALGO == MC_ALGO_DGC || EF, ALGO == MC_ALGO_RANDK>), dim3(blocks), dim3(kSelThreads), lc, src, rng, status);
-}
-template <int ALGO, bool EF>
-static void launch_slow(const LaunchCtx &lc, uint32_t blocks, const AllSparse &src, const RngKey &rng, int *status)
-{
-    MC_LAUNCH((sparse_slow_all_k<ALGO, EF, ALGO == MC_ALGO_DGC || EF, ALGO == MC_ALGO_RANDK>), dim3(blocks), dim3(kSelThreads), lc, src, rng, status);
-}
-
 template <int ALGO, bool EF, class SRC>
 static void sparse_compress_t(const LaunchCtx &lc, const SRC &src, const SparseBlocks &nb, const SparseCall &call)
 {
@@ -1756,13 +1688,10 @@ static void sparse_compress_t(const LaunchCtx &lc, const SRC &src, const SparseB
     MC_LAUNCH((sparse_accum_k<ALGO, EF, SRC>), dim3(nb.tiles), dim3(kBlock), lc, src, call.momentum, rng, (SampleRule{0u, 0u, 0u}));
     prof_end(lc, K_SPARSE_ACCUM);
     // the two-kernel tail; its slow routes run on blocks that the device holds at once: one per compute unit
-    const uint32_t sync = std::max(1u, std::min(std::min(call.sync_blocks, nb.select), (uint32_t)(kRoundTiles / kSelWaves)));
+    const uint32_t sync = std::max(1u, std::min(call.sync_blocks, (uint32_t)(kRoundTiles / kSelWaves)));
     prof_begin(lc, K_LEAN_SELECT);
-    MC_LAUNCH(lean_select_k<SRC>, dim3(nb.select), dim3(kSelThreads), lc, src);
+    MC_LAUNCH((lean_select_k<ALGO, EF, SRC>), dim3(nb.select), dim3(kSelThreads), lc, src, rng, sync, call.status);
     prof_end(lc, K_LEAN_SELECT);
-    prof_begin(lc, K_SPARSE_SLOW);
-    launch_slow<ALGO, EF>(lc, sync, src, rng, call.status);
-    prof_end(lc, K_SPARSE_SLOW);
     prof_begin(lc, K_LEAN_EMIT);
     MC_LAUNCH((lean_emit_k<ALGO, EF, SRC>), dim3(nb.emit), dim3(kEmitThreads), lc, src);
     prof_end(lc, K_LEAN_EMIT);

@@ -158,7 +158,7 @@ void prof_end(const LaunchCtx &lc, int id)
 static const char *kKernelNames[K_COUNT] = {
     "upload_ptrs", "efsign_compress", "scalar_finalize", "accum_reduce", "qsgd_encode", "tern_encode",
     "fp16_compress", "dense_decompress", "sparse_accum", "sparse_seed", "cand_hist2", "cand_hist3", "cand_count",
-    "cand_emit", "sparse_decompress", "state_convert", "lean_select", "lean_emit", "sparse_slow"};
+    "cand_emit", "sparse_decompress", "state_convert", "lean_select", "lean_emit"};
 
 static void prof_drain(Profiler &p)
 {
@@ -368,7 +368,7 @@ int mc_ctx_destroy(mc_ctx *ctx)
     if (ctx->d_partial) (void)hipFree(ctx->d_partial);
     void *sparse_bufs[] = {ctx->sparse.hist, ctx->sparse.sel, ctx->d_hints, ctx->sparse.cand_bits, ctx->sparse.cand_loc,
                            ctx->sparse.tile_runs, ctx->sparse.tile_cnt, ctx->sparse.blk_cnt, ctx->sparse.ulist, ctx->sparse.ucount,
-                           ctx->sparse.sync};
+                           ctx->sparse.arrive, ctx->sparse.sync};
     for (void *b : sparse_bufs) if (b) (void)hipFree(b);
     if (ctx->d_status) (void)hipFree(ctx->d_status);
     if (switched) (void)hipSetDevice(prev);
@@ -500,11 +500,13 @@ int mc_ctx_create(mc_ctx **out, const mc_config *cfg, const int64_t *numel, int3
                 hipMalloc(&sp.blk_cnt, stiles * sizeof(uint32_t)) != hipSuccess ||
                 hipMalloc(&sp.ulist, lists * kUCap * sizeof(UEntry)) != hipSuccess ||
                 hipMalloc(&sp.ucount, count_bytes) != hipSuccess ||
+                hipMalloc(&sp.arrive, parts * kUCountStride * sizeof(uint32_t)) != hipSuccess ||
                 hipMalloc(&sp.sync, 64 * sizeof(uint32_t)) != hipSuccess) rc = MC_ERR_ALLOC;
             else if (hipMemset(sp.hist, 0, hist_bytes) != hipSuccess || hipMemset(sp.sel, 0, sel_bytes) != hipSuccess ||
                      hipMemset(ctx->d_hints, 0, (size_t)y * kHintWorkers * kHintWords * sizeof(uint32_t)) != hipSuccess ||
                      hipMemset(sp.tile_runs, 0, stiles * sizeof(uint64_t)) != hipSuccess ||
                      hipMemset(sp.ucount, 0, count_bytes) != hipSuccess ||
+                     hipMemset(sp.arrive, 0, parts * kUCountStride * sizeof(uint32_t)) != hipSuccess ||
                      hipMemset(sp.sync, 0, 64 * sizeof(uint32_t)) != hipSuccess) rc = MC_ERR_DEVICE;
             ctx->last_sel = sp.sel;
             int cus = 0;
@@ -969,7 +971,7 @@ int mc_last_select_route(mc_ctx *ctx)
     DeviceGuard on(ctx->device);
     if (hipDeviceSynchronize() != hipSuccess) return MC_ERR_DEVICE;
     if (hipMemcpy(&s, ctx->last_sel, sizeof(s), hipMemcpyDeviceToHost) != hipSuccess) return MC_ERR_DEVICE;
-    return (s.mode & 8u) ? MC_SELECT_DENSE : (s.mode & 1u) ? MC_SELECT_FAST : (s.mode & 2u) ? MC_SELECT_REFILL : MC_SELECT_ABOVE;
+    return (s.mode & 8u) ? MC_SELECT_DENSE : (s.mode & 1u) ? MC_SELECT_FAST : (s.mode & 2u) && !(s.mode & 16u) ? MC_SELECT_REFILL : MC_SELECT_ABOVE;
 }
 
 int mc_select_stats(mc_ctx *ctx, mc_select_counts *out, int32_t reset)

@@ -174,7 +174,7 @@ struct SelectState {
 enum KernelId {
     K_UPLOAD = 0, K_EFSIGN_COMPRESS, K_SCALAR_FINALIZE, K_ACCUM_REDUCE, K_QSGD_ENCODE, K_TERN_ENCODE,
     K_FP16_COMPRESS, K_DENSE_DECOMPRESS, K_SPARSE_ACCUM, K_SPARSE_SEED, K_CAND_HIST2, K_CAND_HIST3, K_CAND_COUNT,
-    K_CAND_EMIT, K_SPARSE_DECOMPRESS, K_STATE_CONVERT, K_LEAN_SELECT, K_LEAN_EMIT, K_SPARSE_SLOW, K_COUNT
+    K_CAND_EMIT, K_SPARSE_DECOMPRESS, K_STATE_CONVERT, K_LEAN_SELECT, K_LEAN_EMIT, K_COUNT
 };
 
 // reduction kinds of the two-pass quantizers
@@ -244,7 +244,8 @@ struct SparseScratch {
     uint32_t *blk_cnt;     // the same per block of four tiles
     UEntry *ulist;         // kUSub sublists of kUCap entries: the candidates in the threshold's window bin
     uint32_t *ucount;      // their lengths, kUCountStride words apart; cleared by the streaming pass of the next call
-    uint32_t *sync;        // [0]: arrivals at the grid-wide barriers of the slow routes (cleared by the streaming pass); [32..36): calls per route
+    uint32_t *arrive;      // arrivals at the grid-wide barriers of the slow routes (cleared by the streaming pass), a line of its own
+    uint32_t *sync;        // [32..36): calls per route; [40], [41]: what mc_select_stats reports of the most recent call
     uint32_t spin_limit;   // polls after which a block gives up waiting at such a barrier (mc_set_barrier_spin_limit)
 };
 // The part of the scratch that group number q of a launch over all groups works in: every group has its own, laid out
@@ -262,6 +263,7 @@ __host__ __device__ inline SparseScratch scratch_of(const SparseScratch &all, ui
     s.blk_cnt += first_tile;
     s.ulist += (size_t)first_sub * kUCap;
     s.ucount += (size_t)q * kUSub * kUCountStride;
+    s.arrive += (size_t)q * kUCountStride;
     return s;
 }
 constexpr int kSelTiles = 16, kEmitTiles = kWavesPerBlock;     // tiles per block of the select and the emit kernel
