@@ -122,10 +122,25 @@ def ptr_array(tensors: Sequence) -> C.Array:
 _ptr_array = ptr_array
 
 
+_raw_stream = None
+
+
+def _current_stream() -> int:
+    """Handle of torch's current stream on the current device.  The raw lookup takes 0.2 us where building a Stream
+    object takes 3 to 4, as long as the launch that follows and half of what a small call costs the host: a one-launch
+    decompress-and-sum 8.8 -> 5.0 us."""
+    global _raw_stream
+    if _raw_stream is None:
+        import torch
+        torch.cuda.current_stream()              # initialises the device if nothing has yet
+        get, device = (getattr(torch._C, name, None) for name in ("_cuda_getCurrentRawStream", "_cuda_getDevice"))
+        _raw_stream = (lambda: get(device())) if get and device else (lambda: torch.cuda.current_stream().cuda_stream)
+    return _raw_stream()
+
+
 def _stream_handle(stream) -> Optional[int]:
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
+        return _current_stream()
     return getattr(stream, "cuda_stream", stream)
 
 

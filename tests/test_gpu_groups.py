@@ -102,3 +102,22 @@ def test_more_lists_than_are_kept():
         for j, x in enumerate((g[0], torch.cat(g[1:]))):
             bits = np.unpackbits(pay[j].cpu().numpy()[128:], bitorder="little")[:x.numel()]
             assert np.array_equal(bits, (x >= 0).cpu().numpy())
+
+
+def test_calls_go_to_the_current_stream():
+    """Without a stream argument a call goes to torch's current stream, of whichever thread and context it is made in."""
+    side = torch.cuda.Stream()
+    assert B._current_stream() == torch.cuda.current_stream().cuda_stream
+    with torch.cuda.stream(side):
+        assert B._current_stream() == side.cuda_stream
+        # ordered behind work of that stream only: the gradient is written there just before
+        ctx = B.Context("fp16", [4096, 1], [0, 1, 2], use_ef=0)
+        pay = [torch.zeros(ctx.payload_bytes(j), dtype=torch.uint8, device=DEV) for j in range(2)]
+        g = [torch.zeros(n, device=DEV) for n in (4096, 1)]
+        torch.cuda._sleep(20_000_000)
+        for t in g:
+            t.fill_(1.0)
+        ctx.mc_compress_groups(0, 0, g, None, pay)
+    side.synchronize()
+    assert bool((pay[0][128:].view(torch.float16) == 1).all()) and float(pay[1][128:].view(torch.float16)[0]) == 1.0
+    assert B._current_stream() == torch.cuda.current_stream().cuda_stream
