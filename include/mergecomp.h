@@ -285,7 +285,8 @@ int mc_state_import_residual(mc_ctx *ctx, int32_t group, const float *e_in, void
  * mc_decompress_sum since the last call saw a mismatching header, or MC_ERR_DEVICE if a
  * sparsifier's mc_compress gave up waiting at a grid-wide barrier of its rare selection routes
  * (the blocks of that kernel wait for each other, at most about two seconds, which needs them all
- * resident: other work that holds the GPU's compute units for that long can cause it; the
+ * resident: other work that holds the GPU's compute units for that long can cause it; so can a QSGD or TernGrad
+ * compress of groups of at most 2^18 elements, whose blocks wait for each other's partial sums; the
  * payload of that call is then incomplete and its error-feedback state unspecified -- import a
  * residual again before the next call; the context itself stays usable).  Clears the flag. */
 int mc_last_device_status(mc_ctx *ctx);
@@ -336,7 +337,9 @@ int mc_select_stats(mc_ctx *ctx, mc_select_counts *out, int32_t reset);
 
 /*
  * Per-kernel timing with HIP events recorded on the caller's stream around each
- * launch (off by default).  mc_profile_read synchronises the recorded events.
+ * launch (off by default).  mc_profile_read synchronises the recorded events.  While the profiler is on, EF-Sign,
+ * OneBit, QSGD and TernGrad run one kernel per step also on groups of at most 2^18 elements, which they otherwise
+ * compress in a single kernel (same results).
  *   mc_profile_select    bit i of the mask: time kernel slot i while enabled (default: all slots)
  *   mc_profile_kernels   number of kernel slots
  *   mc_profile_read      name (static string), launches and total milliseconds of slot `id`

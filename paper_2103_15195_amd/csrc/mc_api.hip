@@ -98,6 +98,7 @@ struct mc_ctx {
     uint32_t max_tiles = 0;
     size_t max_live = 0;
     double *d_partial = nullptr;
+    uint64_t *d_arrive = nullptr;       // per group: blocks of small groups that have put their partial, over all calls
     SparseScratch sparse{};
     uint32_t *d_hints = nullptr;        // candidate-filter hints: kHintWorkers per group (worker id modulo that)
     const uint32_t *last_hint = nullptr; // the record the most recent sparse mc_compress used (mc_select_stats)
@@ -366,6 +367,7 @@ int mc_ctx_destroy(mc_ctx *ctx)
     void *tables[] = {ctx->d_slots, ctx->d_all_slots, ctx->d_groups, ctx->d_block_group[0], ctx->d_block_group[1], ctx->d_block_group[2], ctx->d_block_group[3]};
     for (void *b : tables) if (b) (void)hipFree(b);
     if (ctx->d_partial) (void)hipFree(ctx->d_partial);
+    if (ctx->d_arrive) (void)hipFree(ctx->d_arrive);
     void *sparse_bufs[] = {ctx->sparse.hist, ctx->sparse.sel, ctx->d_hints, ctx->sparse.cand_bits, ctx->sparse.cand_loc,
                            ctx->sparse.tile_runs, ctx->sparse.tile_cnt, ctx->sparse.blk_cnt, ctx->sparse.ulist, ctx->sparse.ucount,
                            ctx->sparse.arrive, ctx->sparse.sync};
@@ -485,6 +487,9 @@ int mc_ctx_create(mc_ctx **out, const mc_config *cfg, const int64_t *numel, int3
         const size_t parts = ctx->own_scratch ? (size_t)y : 1, stiles = ctx->own_scratch ? all_tiles : tiles;
         const size_t lists = ctx->own_scratch ? subs + kUSub : (size_t)kUSub;      // (the emit kernel looks at kUSub sublists of any group)
         if (rc == MC_OK && hipMalloc(&ctx->d_partial, 3 * std::max(tiles, many ? all_tiles : 0) * sizeof(double)) != hipSuccess) rc = MC_ERR_ALLOC;
+        const size_t arrive_bytes = (size_t)y * kArriveStride * sizeof(uint64_t);
+        if (rc == MC_OK && hipMalloc(&ctx->d_arrive, arrive_bytes) != hipSuccess) rc = MC_ERR_ALLOC;
+        if (rc == MC_OK && hipMemset(ctx->d_arrive, 0, arrive_bytes) != hipSuccess) rc = MC_ERR_DEVICE;
         if (rc == MC_OK && hipMalloc(&ctx->d_status, sizeof(int)) != hipSuccess) rc = MC_ERR_ALLOC;
         if (rc == MC_OK && hipMemset(ctx->d_status, 0, sizeof(int)) != hipSuccess) rc = MC_ERR_DEVICE;
         if (rc == MC_OK && is_sparse(cfg->algo)) {
@@ -679,8 +684,13 @@ static void decompress_launch(mc_ctx *ctx, const LaunchCtx &lc, const SRC &src, 
 
 // The kernels of a dense compressor over one group or all: `tiles` blocks of 4096 elements, `groups` groups.
 template <class SRC>
-static void dense_compress(const mc_config &cfg, const LaunchCtx &lc, const SRC &src, uint32_t tiles, uint32_t groups, uint32_t worker, uint32_t iter_lo)
+static void dense_compress(const mc_config &cfg, const LaunchCtx &lc, const SRC &src, uint32_t tiles, uint32_t groups, uint32_t most_tiles, uint32_t worker,
+                           uint32_t iter_lo, int *status)
 {
+    // most_tiles: of any of the groups.  Small ones combine their partial sums in the kernel that makes them.
+    // (While the profiler is on every step is a kernel of its own, so that its time can be read.)
+    const Profiler *prof = static_cast<const Profiler *>(lc.prof);
+    const bool small = src.arrive && most_tiles <= kSmallTiles && !(prof && prof->on);
     const bool ef = cfg.use_ef != 0;
     const uint32_t levels = qsgd_levels(cfg), algo = (uint32_t)cfg.algo;
     switch (cfg.algo) {
@@ -688,20 +698,22 @@ static void dense_compress(const mc_config &cfg, const LaunchCtx &lc, const SRC 
     case MC_ALGO_ONEBIT:
     {
         const bool means = cfg.algo == MC_ALGO_ONEBIT;
-        launch_sign_compress(lc, means ? SIGN_MEANS : SIGN_EF, src, tiles, ef, 0.0f, algo);
-        launch_scalar_finalize(lc, src, groups, means ? RED_MEANS : RED_MEAN_ABS, algo, 0, ef);
+        launch_sign_compress(lc, means ? SIGN_MEANS : SIGN_EF, src, tiles, ef, 0.0f, algo, small);
+        if (!small) launch_scalar_finalize(lc, src, groups, means ? RED_MEANS : RED_MEAN_ABS, algo, 0, ef);
     }
         break;
     case MC_ALGO_SIGNSGD:
     case MC_ALGO_SIGNUM:
-        launch_sign_compress(lc, cfg.algo == MC_ALGO_SIGNSGD ? SIGN_PLAIN : SIGN_MOMENTUM, src, tiles, ef, cfg.dgc_momentum, algo);
+        launch_sign_compress(lc, cfg.algo == MC_ALGO_SIGNSGD ? SIGN_PLAIN : SIGN_MOMENTUM, src, tiles, ef, cfg.dgc_momentum, algo, false);
         break;
     case MC_ALGO_QSGD:
+        if (small) { launch_quantize_small(lc, RED_L2, src, tiles, ef, levels, cfg.seed, worker, iter_lo, status); break; }
         launch_accum_reduce(lc, src, tiles, ef, RED_L2, levels, cfg.seed);
         launch_scalar_finalize(lc, src, groups, RED_L2, algo, levels, false);
         launch_qsgd_encode(lc, src, tiles, ef, levels, cfg.seed, worker, iter_lo);
         break;
     case MC_ALGO_TERNGRAD:
+        if (small) { launch_quantize_small(lc, RED_MAX_ABS, src, tiles, ef, 0, cfg.seed, worker, iter_lo, status); break; }
         launch_accum_reduce(lc, src, tiles, ef, RED_MAX_ABS, 0, cfg.seed);
         launch_scalar_finalize(lc, src, groups, RED_MAX_ABS, algo, 0, false);
         launch_tern_encode(lc, src, tiles, ef, cfg.seed, worker, iter_lo);
@@ -715,7 +727,7 @@ static void dense_compress(const mc_config &cfg, const LaunchCtx &lc, const SRC 
 static void empty_compress(const mc_config &cfg, const LaunchCtx &lc, PayloadHeader *hdr)
 {
     const bool votes = cfg.algo == MC_ALGO_SIGNSGD || cfg.algo == MC_ALGO_SIGNUM;
-    launch_scalar_finalize(lc, OneCompress{GroupView{}, nullptr, hdr, nullptr}, 1, votes ? RED_ONE : -1, (uint32_t)cfg.algo, qsgd_levels(cfg), false);
+    launch_scalar_finalize(lc, OneCompress{GroupView{}, nullptr, hdr, nullptr, nullptr}, 1, votes ? RED_ONE : -1, (uint32_t)cfg.algo, qsgd_levels(cfg), false);
 }
 static SparseCall sparse_call(const mc_ctx *ctx, uint32_t worker, uint64_t iter)
 {
@@ -750,7 +762,9 @@ static int compress_impl(mc_ctx *ctx, int32_t group, uint32_t worker, uint64_t i
     }
     GroupView gv = group_view(ctx, lc, group, G, reinterpret_cast<const void *const *>(grad_ptrs));
     if (!is_sparse(cfg.algo)) {
-        dense_compress(cfg, lc, OneCompress{gv, sf, hdr, partial}, tiles_in(n), 1, worker, (uint32_t)iter);
+        // (the static entry point may not rely on what an earlier call left in its array: no count of arrivals)
+        uint64_t *arrive = partial == ctx->d_partial ? ctx->d_arrive + (size_t)group * kArriveStride : nullptr;
+        dense_compress(cfg, lc, OneCompress{gv, sf, hdr, partial, arrive}, tiles_in(n), 1, tiles_in(n), worker, (uint32_t)iter, ctx->d_status);
         return check_launch();
     }
     SparseScratch sp = ctx->sparse;
@@ -814,7 +828,8 @@ static int compress_all(mc_ctx *ctx, uint32_t worker, uint64_t iter, const float
         ctx->last_sel = last.sel;
         const SparseBlocks nb{ctx->all_blocks[BLK_TILE], ctx->all_blocks[BLK_SELECT], ctx->all_blocks[BLK_EMIT]};
         launch_sparse_compress(lc, cfg.algo, AllSparse{tb, sp, ctx->last_group}, nb, ef, sparse_call(ctx, worker, iter));
-    } else dense_compress(cfg, lc, AllCompress{tb, ctx->d_partial}, ctx->all_blocks[BLK_TILE], (uint32_t)y, worker, (uint32_t)iter);
+    } else dense_compress(cfg, lc, AllCompress{tb, ctx->d_partial, ctx->d_arrive}, ctx->all_blocks[BLK_TILE], (uint32_t)y, ctx->max_tiles, worker,
+                        (uint32_t)iter, ctx->d_status);
     for (size_t j = 0; j < y; ++j) if (ctx->groups[j].n == 0) empty_compress(cfg, lc, static_cast<PayloadHeader *>(payloads[j]));
     return check_launch();
 }

@@ -78,6 +78,12 @@ __device__ __forceinline__ GroupView view_of(const GroupTable &tb, const GroupCo
     g.goff = ld_uniform(&c->goff);
     return g;
 }
+// Groups of at most this many tiles (262 144 elements) combine their blocks' partial sums inside the compressing kernel, by
+// counting arrivals: 64 of them at one address take about a microsecond (256 blocks that wait for each other took 6 to 7,
+// thousands far longer than the launch of a kernel that combines them), and 64 partials are one per lane of the
+// wavefront that adds them, in that kernel's order.
+constexpr uint32_t kSmallTiles = 64;
+constexpr int kArriveStride = 16;             // 64-bit words between the groups' counts (a line each)
 __host__ __device__ inline uint32_t tiles_in(uint32_t n) { return (uint32_t)(((uint64_t)n + kTile - 1) / kTile); }
 
 // A dense compressor's job.  The state's header lies in front of st, the payload's body behind hdr.
@@ -86,6 +92,7 @@ struct CompressJob {
     float *st;                    // null when the scheme keeps no state
     PayloadHeader *hdr;
     double *partial;              // one double per tile (OneBit: three arrays of one per tile)
+    uint64_t *arrive;             // the group's count of blocks that have their partial ready (small groups)
     uint32_t tile, ntiles;
     __device__ __forceinline__ StateHeader *state_header() const { return reinterpret_cast<StateHeader *>(st) - 1; }
     __device__ __forceinline__ uint8_t *body() const { return reinterpret_cast<uint8_t *>(hdr) + kHeaderBytes; }
@@ -95,12 +102,14 @@ struct OneCompress {
     float *st;
     PayloadHeader *hdr;
     double *partial;
-    __device__ __forceinline__ CompressJob group_job(uint32_t) const { return {g, st, hdr, partial, 0u, tiles_in(g.n)}; }
-    __device__ __forceinline__ CompressJob job() const { return {g, st, hdr, partial, my_tile_index(), gridDim.x}; }
+    uint64_t *arrive;             // null: the call may not rely on what an earlier one left (mc_compress_static)
+    __device__ __forceinline__ CompressJob group_job(uint32_t) const { return {g, st, hdr, partial, arrive, 0u, tiles_in(g.n)}; }
+    __device__ __forceinline__ CompressJob job() const { return {g, st, hdr, partial, arrive, my_tile_index(), gridDim.x}; }
 };
 struct AllCompress {              // list: tensors, then y states, then y payloads
     GroupTable tb;
     double *partial;
+    uint64_t *arrive;             // kArriveStride words per group
     __device__ __forceinline__ CompressJob group_job(uint32_t q) const
     {
         CompressJob j;
@@ -110,6 +119,7 @@ struct AllCompress {              // list: tensors, then y states, then y payloa
         j.st = state ? reinterpret_cast<float *>(state + kHeaderBytes) : nullptr;
         j.hdr = reinterpret_cast<PayloadHeader *>(ld_uniform(tb.list + tb.live + tb.y + q));
         j.partial = partial + 3u * (size_t)ld_uniform(&c->first[BLK_TILE]);
+        j.arrive = arrive + (size_t)q * kArriveStride;
         j.tile = 0u;
         j.ntiles = tiles_in(j.g.n);
         return j;
@@ -204,7 +214,10 @@ void prof_end(const LaunchCtx &lc, int id);
 void launch_upload_ptrs(const LaunchCtx &lc, const uintptr_t *host, uintptr_t *dev, uint32_t count);
 void launch_expand_ptrs(const LaunchCtx &lc, const GroupView &g, uintptr_t *chunk_addr);
 void launch_expand_all(const LaunchCtx &lc, const GroupTable &tb, uint32_t tiles, uintptr_t *chunk_addr);
-template <class SRC> void launch_sign_compress(const LaunchCtx &lc, int mode, const SRC &src, uint32_t tiles, bool ef, float beta, uint32_t algo);
+// small: every group has at most kSmallTiles tiles and src.arrive counts
+template <class SRC> void launch_sign_compress(const LaunchCtx &lc, int mode, const SRC &src, uint32_t tiles, bool ef, float beta, uint32_t algo, bool small);
+template <class SRC> void launch_quantize_small(const LaunchCtx &lc, int mode, const SRC &src, uint32_t tiles, bool ef, uint32_t levels, uint64_t seed,
+                                                uint32_t worker, uint32_t iter_lo, int *status);
 template <class SRC> void launch_scalar_finalize(const LaunchCtx &lc, const SRC &src, uint32_t groups, int mode, uint32_t algo, uint32_t levels,
                                                  bool keep);
 template <class SRC> void launch_accum_reduce(const LaunchCtx &lc, const SRC &src, uint32_t tiles, bool ef, int mode, uint32_t levels, uint64_t seed);

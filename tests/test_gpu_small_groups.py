@@ -1,0 +1,58 @@
+"""Groups of at most 64 tiles of 4096 elements, which combine their blocks' partial sums inside the compressing kernel,
+around the sizes where that begins and ends: payload and residual against the oracle, and byte for byte against the
+kernel-per-step form (which runs while the profiler is on), also when calls for one group, for all groups and the
+static ones take turns on one context."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import oracle as O
+from paper_2103_15195_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+ALGOS = ["efsign", "onebit", "qsgd", "terngrad"]
+
+
+@pytest.mark.parametrize("ef", [0, 1])
+@pytest.mark.parametrize("n", [1, 4096, 4097, 63 * 4096 + 5, 64 * 4096, 64 * 4096 + 1])
+@pytest.mark.parametrize("algo", ALGOS)
+def test_around_the_limit(algo, n, ef):
+    ctx = B.Context(algo, [n], [0, 1], use_ef=ef, seed=9)
+    cfg = O.Config(B.ALGO_IDS[algo], seed=9, use_ef=ef)
+    state = torch.zeros(ctx.state_bytes(0), dtype=torch.uint8, device=DEV)
+    payload = torch.zeros(ctx.payload_bytes(0), dtype=torch.uint8, device=DEV)
+    held = O.new_state(cfg, n)
+    rng = np.random.default_rng([n, ef])
+    for it in range(3):
+        g = (rng.standard_normal(n) * np.exp(rng.standard_normal(n))).astype(np.float32)
+        ctx.mc_compress(0, 1, it, [torch.from_numpy(g).to(DEV)], state if ef else None, payload)
+        want, _ = O.compress(cfg, g, held, group_off=0, worker=1, it=it)
+        assert np.array_equal(payload.cpu().numpy(), want), it
+    if ef:
+        e = torch.empty(O.state_floats(cfg, n), dtype=torch.float32, device=DEV)
+        ctx.mc_state_export_residual(0, state, e)
+        assert np.array_equal(e.cpu().numpy().view(np.uint32), held.view(np.uint32))
+    assert ctx.mc_last_device_status() == B.MC_OK
+
+
+@pytest.mark.parametrize("algo", ALGOS)
+def test_all_kinds_of_calls_in_turn(algo):
+    numel, bounds = [30000, 1, 200, 262144, 5], [0, 2, 3, 4, 5]
+    a, b = (B.Context(algo, numel, bounds, seed=2) for _ in range(2))
+    a.profile_enable(True)                       # one kernel per step
+    rng = np.random.default_rng(3)
+    bufs = [([torch.zeros(c.state_bytes(j), dtype=torch.uint8, device=DEV) for j in range(4)],
+             [torch.zeros(c.payload_bytes(j), dtype=torch.uint8, device=DEV) for j in range(4)]) for c in (a, b)]
+    for it in range(9):
+        g = [torch.from_numpy(rng.standard_normal(n).astype(np.float32)).to(DEV) for n in numel]
+        for c, (st, pay) in zip((a, b), bufs):
+            if it % 3 == 1:
+                c.mc_compress_groups(0, it, g, st, pay)
+            else:
+                call = c.mc_compress_static if it % 3 == 2 and c is b else c.mc_compress
+                for j in range(4):
+                    call(j, 0, it, g[bounds[j]:bounds[j + 1]], st[j], pay[j])
+        for x, y in zip(bufs[0][0] + bufs[0][1], bufs[1][0] + bufs[1][1]):
+            assert torch.equal(x, y), it
+    assert "scalar_finalize" in a.profile_read()
