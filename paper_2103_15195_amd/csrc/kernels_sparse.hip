@@ -1827,6 +1827,10 @@ __global__ __launch_bounds__(kBlock) void sparse_decompress_k(int algo, SRC src,
             }
         }
         if (W <= kSparseBatch) {
+            // (The entries are read with ordinary loads, here and below: the tile's four wavefronts read the same lines,
+            // and neighbouring tiles share theirs.  As non-temporal loads each went to memory, behind the stores: 25.6 M
+            // elements, 8 workers, Top-k 1 % 31.3 us, now 27.3; thinly spread payloads (Rand-k) 34.3, now 26.1; 44.5 M
+            // heavy-tailed ones 50.1, now 39.3.)
             // Few entries per worker (at most one per lane): every wavefront sums its own chunk, in LDS of its own, from
             // the tile's entries of all workers -- loaded together, added worker by worker, no block barrier.  The LDS
             // operations of one wavefront complete in the order issued, so a worker's additions see the ones before.
@@ -1843,7 +1847,7 @@ __global__ __launch_bounds__(kBlock) void sparse_decompress_k(int algo, SRC src,
                     const float *val = reinterpret_cast<const float *>(idx + k);
                     const uint32_t e = lo[b] + c.lane;
                     ix[b] = 0xFFFFFFFFu; vv[b] = 0.0f;
-                    if (b < W && e < hi[b]) { ix[b] = ld_stream(idx + e); vv[b] = ld_stream(val + e); }
+                    if (b < W && e < hi[b]) { ix[b] = idx[e]; vv[b] = val[e]; }
                 }
                 float *mine = acc + (c.base - tb);
 #pragma unroll
@@ -1882,7 +1886,7 @@ __global__ __launch_bounds__(kBlock) void sparse_decompress_k(int algo, SRC src,
             for (int r = 0; r < kSparseRounds; ++r) {
                 const uint32_t e = lo[b] + r * kBlock + t;
                 ix[b][r] = 0xFFFFFFFFu; vv[b][r] = 0.0f;
-                if (w0 + b < W && e < hi[b]) { ix[b][r] = ld_stream(idx + e); vv[b][r] = ld_stream(val + e); }
+                if (w0 + b < W && e < hi[b]) { ix[b][r] = idx[e]; vv[b][r] = val[e]; }
             }
         }
 #pragma unroll
