@@ -74,13 +74,14 @@ template <typename T>
 __device__ __forceinline__ void st_stream(T *p, T v) { __builtin_nontemporal_store(v, p); }
 
 // ---- flat (contiguous) buffers -------------------------------------------
-template <typename T>
+// (STREAM: non-temporal, which is faster for what is read once)
+template <typename T, bool STREAM = true>
 __device__ __forceinline__ void load_flat(const T *buf, const Chunk &c, uint32_t n, T (&v)[kSteps], T fill)
 {
     const T *p = buf + c.base + c.lane;
     if (c.full) {
 #pragma unroll
-        for (int j = 0; j < kSteps; ++j) v[j] = ld_stream(p + 64 * j);
+        for (int j = 0; j < kSteps; ++j) v[j] = STREAM ? ld_stream(p + 64 * j) : p[64 * j];
     } else {
 #pragma unroll
         for (int j = 0; j < kSteps; ++j) v[j] = (c.base + 64 * j + c.lane < n) ? p[64 * j] : fill;
