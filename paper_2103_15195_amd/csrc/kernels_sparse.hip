@@ -31,8 +31,8 @@
 // hint was; the hint only decides how much work the later kernels have.
 // The kernels that walk the candidates give every 4096-element tile to one
 // wavefront: tiles are independent until the emit kernel adds up the kept counts
-// of the tiles before its own.  No kernel waits on another block: every dependency
-// is a kernel boundary.
+// of the tiles before its own.  On the usual route no block waits on another: every
+// dependency is a kernel boundary.
 #include <algorithm>
 
 #include "mc_internal.h"
