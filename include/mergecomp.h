@@ -173,8 +173,9 @@ int mc_partition_search(const int64_t *numel, const double *bwd_time, int32_t n_
  * segment tables and scratch for every group, and reserves the host-side lists the
  * hot calls fill, so that those allocate nothing.
  * Device memory held by a context, with T = tiles of 4096 elements of its largest group:
- *   every algorithm   24 T bytes of reduction partials; up to 256 cached tensor-address lists with one
- *                     8-byte address per 1024 elements each (32 T bytes per list, 256 MiB at most in all)
+ *   every algorithm   24 T bytes of reduction partials; cached tensor-address lists with one 8-byte address per
+ *                     1024 elements each (32 bytes per tile of the group): 32 per group, 256 in all where that is
+ *                     more, 256 MiB at most in all (or four per group)
  *   more than one group   what mc_compress_groups / mc_decompress_sum_groups need to take all groups in one
  *                     launch: the partials for the tiles of all groups, tables of a few bytes per tile and group,
  *                     and up to 64 address lists of whole calls (64 MiB at most in all, or two lists)

@@ -17,7 +17,10 @@ namespace {
 
 constexpr uint64_t kMaxGroupElems = (1ull << 32) - (1ull << 24);
 constexpr uint32_t kBarrierSpinLimit = 1u << 21;     // polls (about a microsecond each) before a block of the slow selection routes gives up waiting
-constexpr int kPtrSlots = 256;           // cached device copies of per-call tensor address lists
+// Cached device copies of per-call tensor address lists: per group at least kGroupSlots, in all at least kPtrSlots.  (With 256
+// for all groups together a layer-wise training step -- 161 groups, two gradients and an output each -- replaced every
+// list before it came round again, two launches more in every call.)
+constexpr int kPtrSlots = 256, kGroupSlots = 32;
 constexpr int kAllSlots = 64;            // ... and of the address lists of calls over all groups
 
 struct Group {
@@ -31,8 +34,7 @@ struct Group {
 };
 
 struct PtrSlot {
-    int32_t group = -1;
-    uint64_t stamp = 0;
+    uint64_t stamp = 0;                  // 0: never used
     std::vector<uintptr_t> host;
     uintptr_t *dev = nullptr;            // tensor addresses
     uintptr_t *dev_chunk = nullptr;      // per-chunk direct addresses derived from them
@@ -104,7 +106,8 @@ struct mc_ctx {
     const uint32_t *last_hint = nullptr; // the record the most recent sparse mc_compress used (mc_select_stats)
     int *d_status = nullptr;
     void *static_scratch = nullptr;     // this device's copy of the file-scope scratch array (mc_compress_static)
-    std::vector<PtrSlot> slots;
+    std::vector<PtrSlot> slots;         // group_slots per group, one group after the other
+    size_t group_slots = 0;
     std::vector<uintptr_t> want;        // the address list of the call in progress (reserved at creation)
     // calls over all groups (contexts of more than one)
     bool own_scratch = false;           // sparsifiers: every group has a part of the scratch of its own
@@ -520,15 +523,22 @@ int mc_ctx_create(mc_ctx **out, const mc_config *cfg, const int64_t *numel, int3
             sp.spin_limit = kBarrierSpinLimit;
         }
         if (rc == MC_OK) {
-            // the per-chunk address tables of all slots together stay below 256 MiB
-            const size_t chunks = lines(tiles * kWavesPerBlock), per_slot = lines(std::max<size_t>(ctx->max_live, 1)) + chunks;
-            ctx->slots.resize(std::min<size_t>(kPtrSlots, std::max<size_t>(4, (size_t(256) << 20) / (chunks * sizeof(uintptr_t)))));
-            if (hipMalloc(&ctx->d_slots, ctx->slots.size() * per_slot * sizeof(uintptr_t)) != hipSuccess) rc = MC_ERR_ALLOC;
+            // the per-chunk address tables of all slots together stay below 256 MiB (or four lists per group)
+            size_t words = 0;                    // of one slot of every group
+            for (const Group &g : ctx->groups) words += lines(g.live.size()) + lines((size_t)tiles_in(g.n) * kWavesPerBlock);
+            words = std::max<size_t>(words, 32);
+            ctx->group_slots = std::min<size_t>(std::max<size_t>(kGroupSlots, kPtrSlots / (size_t)y), std::max<size_t>(4, (size_t(256) << 20) / (words * sizeof(uintptr_t))));
+            ctx->slots.resize(ctx->group_slots * (size_t)y);
+            if (hipMalloc(&ctx->d_slots, ctx->group_slots * words * sizeof(uintptr_t)) != hipSuccess) rc = MC_ERR_ALLOC;
             uintptr_t *at = ctx->d_slots;
-            for (PtrSlot &s : ctx->slots) {
-                s.dev = at; s.dev_chunk = at + (per_slot - chunks);
-                at += per_slot;
-                s.host.reserve(ctx->max_live);
+            for (size_t i = 0; i < ctx->slots.size(); ++i) {
+                const Group &g = ctx->groups[i / ctx->group_slots];
+                PtrSlot &s = ctx->slots[i];
+                s.dev = at;
+                at += lines(g.live.size());
+                s.dev_chunk = at;
+                at += lines((size_t)tiles_in(g.n) * kWavesPerBlock);
+                s.host.reserve(g.live.size());
             }
             ctx->want.reserve(ctx->max_live);
             ctx->prof.pending.reserve(1024);
@@ -605,10 +615,10 @@ static GroupView group_view(mc_ctx *ctx, const LaunchCtx &lc, int32_t group, con
     want.clear();
     for (int32_t rel : g.live) want.push_back(reinterpret_cast<uintptr_t>(ptrs[rel]));
     GroupView gv{g.d_seg_off, g.d_chunk_seg, nullptr, nullptr, (uint32_t)g.live.size(), g.n, g.goff};
-    PtrSlot *victim = &ctx->slots[0];
-    for (PtrSlot &s : ctx->slots) {
-        if (s.group == group && s.host.size() == want.size() &&
-            std::memcmp(s.host.data(), want.data(), want.size() * sizeof(uintptr_t)) == 0) {
+    PtrSlot *const own = &ctx->slots[(size_t)group * ctx->group_slots], *victim = own;
+    for (size_t i = 0; i < ctx->group_slots; ++i) {
+        PtrSlot &s = own[i];
+        if (s.stamp && std::memcmp(s.host.data(), want.data(), want.size() * sizeof(uintptr_t)) == 0) {      // (a group's lists have one length)
             s.stamp = ++ctx->clock;
             gv.ptrs = s.dev;
             gv.chunk_addr = s.dev_chunk;
@@ -616,7 +626,6 @@ static GroupView group_view(mc_ctx *ctx, const LaunchCtx &lc, int32_t group, con
         }
         if (s.stamp < victim->stamp) victim = &s;
     }
-    victim->group = group;
     victim->stamp = ++ctx->clock;
     victim->host = want;
     gv.ptrs = victim->dev;
