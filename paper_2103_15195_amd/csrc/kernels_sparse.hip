@@ -947,7 +947,7 @@ __device__ __forceinline__ void resolve_block(const uint32_t *fine, uint64_t nee
 // heads of a tile's four chunks are asked for before the number of candidates is known (what lies beyond it is
 // masked out afterwards; most chunks hold fewer than 64), and a crowded chunk costs one more round of loads, not
 // one per 64 candidates.  Candidate number o >= 64 of a chunk is held by lane ((o - 64) % 256) / 4 of unit (o - 64) / 256.
-constexpr int kHead = 64, kUnit = 256;
+constexpr int kHead = kCandHead, kUnit = kCandUnit;
 __device__ __forceinline__ uint32_t load_head_bits(const SparseScratch &sc, uint32_t chunk)
 {
     return sc.cand_bits[(size_t)chunk * kChunk + (threadIdx.x & 63u)];

@@ -498,7 +498,7 @@ int mc_ctx_create(mc_ctx **out, const mc_config *cfg, const int64_t *numel, int3
         if (rc == MC_OK && is_sparse(cfg->algo)) {
             SparseScratch &sp = ctx->sparse;
             const size_t hist_bytes = parts * hist_words * sizeof(uint32_t), sel_bytes = parts * 4 * sizeof(SelectState);
-            const size_t slots = stiles * kTile, count_bytes = parts * kUSub * kUCountStride * sizeof(uint32_t);
+            const size_t slots = stiles * kTile + kCandPad, count_bytes = parts * kUSub * kUCountStride * sizeof(uint32_t);
             if (hipMalloc(&sp.hist, hist_bytes) != hipSuccess || hipMalloc(&sp.sel, sel_bytes) != hipSuccess ||
                 hipMalloc(&ctx->d_hints, (size_t)y * kHintWorkers * kHintWords * sizeof(uint32_t)) != hipSuccess ||
                 hipMalloc(&sp.cand_bits, slots * sizeof(uint32_t)) != hipSuccess ||

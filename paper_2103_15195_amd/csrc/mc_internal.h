@@ -245,6 +245,11 @@ constexpr int kUSub = 64;
 constexpr uint32_t kUCap = 4096;      // keys in the threshold's window bin that the two-kernel route takes; a sublist holds as many
 constexpr int kUCountStride = 32;     // words between sublist counters (one 128-byte line each)
 struct UEntry { uint32_t idx, bits; };       // group-relative index, candidate bits
+// Candidate slots behind the last chunk of the scratch.  A chunk's 1024 slots are read as a head of 64 and units of 256,
+// masked after the load: a chunk with more than 64 + 3 * 256 candidates reads up to slot 64 + 4 * 256 - 1, of the chunk
+// after it, and the scratch's last chunk into these.
+constexpr int kCandHead = 64, kCandUnit = 256;
+constexpr int kCandPad = kCandHead + (kChunk - kCandHead + kCandUnit - 1) / kCandUnit * kCandUnit - kChunk;
 
 struct SparseScratch {
     uint32_t *hist;        // kHistWords counters; each level is cleared by a later kernel of the same call

@@ -1,0 +1,81 @@
+"""The library's host code without a device: mc_api.hip linked with tests/host/no_device.hip, whose allocator counts (and
+refuses beyond a limit) and whose launchers count what a call consists of.  No kernel runs here."""
+import ctypes as C
+import os
+import subprocess
+
+import pytest
+
+from paper_2103_15195_amd import binding as B
+from paper_2103_15195_amd import build as hip_build
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+TILE = 4096
+NO_LIMIT = 2 ** 64 - 1
+
+
+@pytest.fixture(scope="module")
+def built(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("host"))
+    flags = [f for f in hip_build.HIPCC_FLAGS if f not in ("-shared", "-O3")]
+    objects, jobs = [], []
+    for src in (os.path.join(hip_build.CSRC, "mc_api.hip"), os.path.join(HERE, "host", "no_device.hip")):
+        objects.append(os.path.join(out, os.path.basename(src) + ".o"))
+        jobs.append(subprocess.Popen([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), "-O1", "-c", *flags, "-o", objects[-1], src],
+                                     stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True))
+    for job in jobs:
+        text, _ = job.communicate()
+        assert job.returncode == 0, text
+    path = os.path.join(out, "libhostonly.so")
+    subprocess.run(["g++", "-shared", "-Wl,-Bsymbolic", "-Wl,-z,defs", "-o", path, *objects, "-lpthread"], check=True)
+    return path
+
+
+class Buffer:
+    """Stands for a tensor: an address."""
+    def __init__(self, at):
+        self.at = at
+
+    def data_ptr(self):
+        return self.at
+
+
+@pytest.fixture
+def host(built, monkeypatch):
+    """The counters; while it is in use the binding drives the library without a device."""
+    monkeypatch.setattr(B, "LIB_PATH", built)
+    monkeypatch.setattr(B, "_lib", None)
+    L = B.lib()
+    L.nd_reset.argtypes = [C.c_size_t]
+    L.nd_held.restype = C.c_size_t
+    L.nd_denied.restype = L.nd_bad_free.restype = L.nd_launches.restype = L.nd_allocated.restype = C.c_long
+    L.nd_launches.argtypes = [C.c_char_p]
+    L.nd_allocated.argtypes = [C.c_size_t]
+    L.nd_reset(NO_LIMIT)
+    held = L.nd_held()
+    yield L
+    assert L.nd_held() == held and L.nd_bad_free() == 0          # everything a test allocated is given back
+
+
+def launches(L, *what):
+    return [L.nd_launches(w.encode()) for w in what]
+
+
+@pytest.mark.parametrize("algo", ["topk", "dgc", "randk"])
+@pytest.mark.parametrize("numel,bounds", [([4 * TILE], [0, 1]), ([3 * TILE, 5 * TILE], [0, 1, 2]), ([100, 2 * TILE - 1], [0, 1, 2])])
+def test_candidate_arrays_cover_what_the_kernels_read(host, algo, numel, bounds):
+    """The select and emit kernels read a chunk of 1024 candidate slots as a head of 64 and units of 256, masking what lies
+    beyond the chunk's candidates after the load: a chunk with more than 64 + 3 x 256 reads 64 + 4 x 256 slots, the
+    scratch's last one past its own 1024."""
+    furthest = 0
+    for cnt in range(1025):
+        units = max(0, -(-(cnt - 64) // 256))
+        furthest = max(furthest, 64 + 256 * units)               # slots that the loads of this chunk cover
+    assert furthest == 1088
+    tiles = sum(-(-n // TILE) for n in numel)                    # of all groups: every group has its part of the scratch
+    read = (tiles * TILE - 1024) + furthest
+    ctx = B.Context(algo, numel, bounds)
+    most = tiles * TILE + 1024                                   # (exact sizes: none but the candidate arrays lie in between)
+    assert any(host.nd_allocated(4 * s) for s in range(read, most)), "values"
+    assert any(host.nd_allocated(2 * s) for s in range(read, most)), "positions"
+    ctx.close()
