@@ -515,17 +515,17 @@ __device__ __forceinline__ void load_p(const GroupView &g, const float *st, cons
 // measured slower; the two-byte codes of FP16 cover a whole line and are stored directly).
 template <typename T>
 __device__ __forceinline__ void store_codes(T *codes, uint32_t n, uint32_t n_padded, const Chunk &c,
-                                            const T (&v)[kSteps], T *stage /* kChunk entries, wave-private */)
+                                            const T (&v)[kSteps], uint4 *stage /* room for kChunk entries, wave-private; read 16 bytes at a time */)
 {
+    static_assert(alignof(uint4) == 16, "the stage is read with 16-byte LDS loads");
     if (c.full) {
 #pragma unroll
-        for (int j = 0; j < kSteps; ++j) stage[64 * j + c.lane] = v[j];
+        for (int j = 0; j < kSteps; ++j) reinterpret_cast<T *>(stage)[64 * j + c.lane] = v[j];
         __builtin_amdgcn_wave_barrier();
         constexpr int kVec = (int)(kChunk * sizeof(T) / 16 / kWave);     // 16-byte vectors per lane
-        const uint4 *src = reinterpret_cast<const uint4 *>(stage);
         uint4 *dst = reinterpret_cast<uint4 *>(codes + c.base);
 #pragma unroll
-        for (int r = 0; r < kVec; ++r) dst[r * 64 + c.lane] = src[r * 64 + c.lane];
+        for (int r = 0; r < kVec; ++r) dst[r * 64 + c.lane] = stage[r * 64 + c.lane];
         __builtin_amdgcn_wave_barrier();
     } else {
 #pragma unroll
@@ -569,7 +569,7 @@ __device__ __forceinline__ const float *wide_source(const GroupView &g, const fl
 template <bool EF, class SRC>
 __global__ __launch_bounds__(kBlock) void qsgd_encode_k(SRC src, uint32_t levels, uint64_t seed, uint32_t worker, uint32_t iter_lo)
 {
-    __shared__ __attribute__((aligned(16))) int8_t stage[kWavesPerBlock][kChunk];
+    __shared__ uint4 stage[kWavesPerBlock][kChunk / 16];
     const CompressJob job = src.job();
     const GroupView &g = job.g;
     const float *st = job.st;
@@ -723,7 +723,7 @@ __global__ __launch_bounds__(kBlock) void quantize_small_k(SRC src, uint32_t lev
     __shared__ float redf[kWavesPerBlock];
     __shared__ float scalar;
     __shared__ int late;
-    __shared__ uint64_t stage[kWavesPerBlock][MODE == RED_L2 ? kChunk / 8 : kSteps];
+    __shared__ uint4 stage[kWavesPerBlock][MODE == RED_L2 ? kChunk / 16 : kSteps / 2];       // a chunk's codes, or the 64-bit ballots of its steps
     const CompressJob job = src.job();
     const GroupView &g = job.g;
     const Chunk c = my_chunk(g.n, job.tile);
@@ -768,13 +768,13 @@ __global__ __launch_bounds__(kBlock) void quantize_small_k(SRC src, uint32_t lev
         int8_t code[kSteps];
 #pragma unroll
         for (int j = 0; j < kSteps; ++j) code[j] = (int8_t)qsgd_code(ks, p[j], uni[j]);
-        store_codes<int8_t>(reinterpret_cast<int8_t *>(job.body()), g.n, (g.n + 3u) & ~3u, c, code, reinterpret_cast<int8_t *>(stage[wave]));
+        store_codes<int8_t>(reinterpret_cast<int8_t *>(job.body()), g.n, (g.n + 3u) & ~3u, c, code, stage[wave]);
     } else {
         uint32_t *planes = reinterpret_cast<uint32_t *>(job.body());
         uint64_t bnz[kSteps], bng[kSteps];
         tern_planes(c, g.n, scale, p, uni, bnz, bng);
-        store_plane(planes, nwords, c, bnz, stage[wave]);
-        store_plane(planes + nwords, nwords, c, bng, stage[wave]);
+        store_plane(planes, nwords, c, bnz, reinterpret_cast<uint64_t *>(stage[wave]));
+        store_plane(planes + nwords, nwords, c, bng, reinterpret_cast<uint64_t *>(stage[wave]));
     }
 }
 
