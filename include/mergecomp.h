@@ -289,7 +289,8 @@ int mc_state_import_residual(mc_ctx *ctx, int32_t group, const float *e_in, void
  * resident: other work that holds the GPU's compute units for that long can cause it; so can a QSGD or TernGrad
  * compress of groups of at most 2^18 elements, whose blocks wait for each other's partial sums; the
  * payload of that call is then incomplete and its error-feedback state unspecified -- import a
- * residual again before the next call; the context itself stays usable).  Clears the flag. */
+ * residual again before the next call; the context itself stays usable; where both happened, this is what
+ * is returned).  Clears the flag. */
 int mc_last_device_status(mc_ctx *ctx);
 
 /* For tests of the error path above: how often a block looks at a grid-wide barrier before it gives up

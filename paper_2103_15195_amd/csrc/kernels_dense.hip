@@ -747,7 +747,7 @@ __global__ __launch_bounds__(kBlock) void quantize_small_k(SRC src, uint32_t lev
             uint32_t looks = 0;
             while (__hip_atomic_load(job.arrive, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < all) {
                 __builtin_amdgcn_s_sleep(4);
-                if (++looks > kWaitLooks) { there = false; *status = 2; break; }
+                if (++looks > kWaitLooks) { there = false; raise_flag(status, FLAG_GAVE_UP); break; }
             }
             late = there ? 0 : 1;
         }
@@ -866,7 +866,7 @@ template void launch_fp16_compress<AllCompress>(const LaunchCtx &, const AllComp
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ void check_header(const PayloadHeader *h, uint32_t algo, uint32_t n, int *status)
 {
-    if (h->magic != kMagic || h->algo != algo || h->n != (uint64_t)n) *status = 1;
+    if (h->magic != kMagic || h->algo != algo || h->n != (uint64_t)n) raise_flag(status, FLAG_PAYLOAD);
 }
 
 // Workers are taken in batches: all loads of a batch (header scalars and codes)

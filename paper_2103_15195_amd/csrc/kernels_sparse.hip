@@ -902,7 +902,7 @@ __device__ __forceinline__ bool grid_barrier(uint32_t *arrive, uint32_t blocks, 
         // blocks doing that every few hundred cycles starve the blocks still at work (phases of 60-120 us instead of 10)
         while (__hip_atomic_load(arrive, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
             __builtin_amdgcn_s_sleep(32);
-            if (spins++ >= limit) { *dead = 1u; *status = 2; break; }
+            if (spins++ >= limit) { *dead = 1u; raise_flag(status, FLAG_GAVE_UP); break; }
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     }
@@ -1771,7 +1771,7 @@ __global__ __launch_bounds__(kBlock) void sparse_decompress_k(int algo, SRC src,
     if (job.block == job.last && (int)threadIdx.x < W) {
         const PayloadHeader *h = reinterpret_cast<const PayloadHeader *>(job.payload_of_lane(threadIdx.x));
         const bool fits = capped ? h->k <= k64 && h->levels == (uint32_t)k64 : h->k == k64;
-        if (h->magic != kMagic || h->algo != (uint32_t)algo || h->n != (uint64_t)out.n || !fits) *status = 1;
+        if (h->magic != kMagic || h->algo != (uint32_t)algo || h->n != (uint64_t)out.n || !fits) raise_flag(status, FLAG_PAYLOAD);
     }
     const uint32_t tile = job.block;
     const uint32_t tb = tile * (uint32_t)kTile;

@@ -985,7 +985,7 @@ int mc_last_device_status(mc_ctx *ctx)
     if (hipDeviceSynchronize() != hipSuccess) return MC_ERR_DEVICE;
     if (hipMemcpy(&flag, ctx->d_status, sizeof(int), hipMemcpyDeviceToHost) != hipSuccess) return MC_ERR_DEVICE;
     if (flag && hipMemset(ctx->d_status, 0, sizeof(int)) != hipSuccess) return MC_ERR_DEVICE;
-    return flag == 2 ? MC_ERR_DEVICE : flag ? MC_ERR_PAYLOAD : MC_OK;
+    return flag == FLAG_GAVE_UP ? MC_ERR_DEVICE : flag ? MC_ERR_PAYLOAD : MC_OK;
 }
 
 int mc_last_select_route(mc_ctx *ctx)

@@ -35,6 +35,11 @@ static_assert(sizeof(StateHeader) == kHeaderBytes, "state header is one 128-byte
 // on a 128-byte line (a chunk's stores then cover whole lines).
 __host__ __device__ inline size_t dgc_u_offset(uint32_t n) { return ((size_t)n + 31u) & ~(size_t)31u; }
 
+// What the kernels leave for mc_last_device_status.  The larger one stays: a call that gave up waiting leaves a payload that a
+// decompress-and-sum then finds wrong, and a state of which the caller has to know.
+enum DeviceFlag { FLAG_PAYLOAD = 1, FLAG_GAVE_UP = 2 };
+__device__ __forceinline__ void raise_flag(int *status, DeviceFlag f) { atomicMax(status, (int)f); }
+
 struct PayloadPtrs { const uint8_t *p[kMaxWorkers]; };
 struct PtrChunk { uintptr_t p[256]; };
 
