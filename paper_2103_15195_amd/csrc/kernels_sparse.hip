@@ -184,11 +184,10 @@ __global__ __launch_bounds__(kBlock) void sparse_accum_k(SRC src, float momentum
     if (order == 0 && threadIdx.x < (uint32_t)kUSub) sc.ucount[threadIdx.x * kUCountStride] = 0u;
     if (order == 0 && threadIdx.x == 0) *sc.arrive = 0u;       // and nobody waits at a grid-wide barrier of that call any more
     // The radix levels are cleared by the kernels that use them -- unless a call gave up at a barrier (MC_ERR_DEVICE):
-    // what it left behind must not enter this call's counts.
-    {
-        const uint32_t i = order * (uint32_t)kBlock + threadIdx.x;
-        if (i < (uint32_t)(kHistOpen - kHist1)) sc.hist[kHist1 + i] = 0u;
-    }
+    // what it left behind must not enter this call's counts.  (A group of fewer tiles than it takes blocks to clear them at
+    // once goes round again.)
+    for (uint32_t i = order * (uint32_t)kBlock + threadIdx.x; i < (uint32_t)(kHistOpen - kHist1); i += job.blocks * (uint32_t)kBlock)
+        sc.hist[kHist1 + i] = 0u;
     uint32_t run = 0;
     if (c.base < g.n) {
         float p[kSteps];

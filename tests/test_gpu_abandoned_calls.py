@@ -28,3 +28,36 @@ def test_a_bad_payload_does_not_hide_an_abandoned_call():
     assert ctx.mc_last_device_status() == B.MC_ERR_PAYLOAD
     ctx.mc_set_barrier_spin_limit(0)
     ctx.close()
+
+
+@pytest.mark.parametrize("tiles", [17, 18, 19, 20, 33])
+def test_an_abandoned_call_leaves_no_counts_behind(tiles):
+    """A call that gave up after its blocks had counted the threshold bin's keys one by one (the route of heavy ties), and
+    then calls that take the same route: none of those counts may enter theirs.  From 17 tiles on the route waits."""
+    n, ppm = tiles * 4096 - 5, 100000
+    ctx = B.Context("topk", [n], [0, 1], use_ef=0, ratio_ppm=ppm, seed=1)
+    ocfg = O.Config(O.TOPK, use_ef=0, ratio_ppm=ppm, seed=1)
+    pay = torch.zeros(ctx.payload_bytes(0), dtype=torch.uint8, device=H.DEV)
+    rng = np.random.default_rng(tiles)
+
+    def call(it, tie_key):
+        # 30 % of the elements have one magnitude, which is where the threshold of the largest 10 % falls
+        g = (rng.standard_normal(n) * 1e-3).astype(np.float32)
+        tie = rng.random(n) < 0.3
+        g[tie] = np.uint32(tie_key).view(np.float32) * np.where(rng.random(int(tie.sum())) < 0.5, 1, -1).astype(np.float32)
+        ctx.mc_compress(0, 0, it, H.device_tensors(g, [n]), None, pay)
+        return O.compress(ocfg, g, None, group_off=0, worker=0, it=it)[0]
+
+    one = 0x3F800000
+    for it in range(2):
+        assert np.array_equal(call(it, one), pay.cpu().numpy())
+    assert ctx.mc_last_select_route() == B.MC_SELECT_DENSE
+    ctx.mc_set_barrier_spin_limit(1)
+    call(2, one + 1900)                          # counted near the top of a bin of 2048 keys
+    assert ctx.mc_last_device_status() == B.MC_ERR_DEVICE
+    ctx.mc_set_barrier_spin_limit(0)
+    for it in (3, 4):
+        assert np.array_equal(call(it, one + 100), pay.cpu().numpy()), it
+        assert ctx.mc_last_select_route() == B.MC_SELECT_DENSE
+    assert ctx.mc_last_device_status() == B.MC_OK
+    ctx.close()
