@@ -126,6 +126,9 @@ __device__ __forceinline__ uint64_t arrive_at(uint64_t *count)
     __builtin_amdgcn_s_waitcnt(0);             // the partials are written through before the count says so
     return __hip_atomic_fetch_add(count, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+// The other end: after the count has been seen complete, before the partials are read.  (They bypass the caches, so nothing
+// has to be invalidated; but relaxed loads of different addresses are otherwise free to be moved before the count's.)
+__device__ __forceinline__ void all_arrived() { __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup"); }
 // one wavefront, N <= 64 partials: their sum (maximum) in the order of scalar_finalize_k, in all lanes
 template <bool MAX>
 __device__ __forceinline__ double combine_partials(const double *partial, uint32_t N)
@@ -221,6 +224,7 @@ __global__ __launch_bounds__(kBlock) void sign_compress_k(SRC src, float beta, u
         before = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)before) |
                  ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(before >> 32)) << 32);
         if (before % job.ntiles != job.ntiles - 1u) return;
+        all_arrived();
         const uint32_t N = job.ntiles, n = g.n;
         const double a = combine_partials<false>(job.partial, N);
         float hi, lo = 0.0f;
@@ -751,6 +755,7 @@ __global__ __launch_bounds__(kBlock) void quantize_small_k(SRC src, uint32_t lev
             }
             late = there ? 0 : 1;
         }
+        all_arrived();
         const double S = combine_partials<MODE == RED_MAX_ABS>(job.partial, job.ntiles);
         if (threadIdx.x == 0) scalar = MODE == RED_L2 ? (float)sqrt(S) : (float)S;
     }
