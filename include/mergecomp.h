@@ -286,8 +286,7 @@ int mc_state_import_residual(mc_ctx *ctx, int32_t group, const float *e_in, void
  * mc_decompress_sum since the last call saw a mismatching header, or MC_ERR_DEVICE if a
  * sparsifier's mc_compress gave up waiting at a grid-wide barrier of its rare selection routes
  * (the blocks of that kernel wait for each other, at most about two seconds, which needs them all
- * resident: other work that holds the GPU's compute units for that long can cause it; so can a QSGD or TernGrad
- * compress of groups of at most 2^18 elements, whose blocks wait for each other's partial sums; the
+ * resident: other work that holds the GPU's compute units for that long can cause it; the
  * payload of that call is then incomplete and its error-feedback state unspecified -- import a
  * residual again before the next call; the context itself stays usable; where both happened, this is what
  * is returned).  Clears the flag. */
@@ -296,8 +295,10 @@ int mc_last_device_status(mc_ctx *ctx);
 /* For tests of the error path above: how often a block looks at a grid-wide barrier before it gives up
  * (0 = the default, 2^21 looks of about a microsecond; 1 = after the first look, which makes every
  * mc_compress that takes one of the rare routes on more than one block report MC_ERR_DEVICE while all its
- * kernels still end normally).  Applies to the calls issued afterwards.  Errors: MC_ERR_INVALID_ARG
- * (null, dense algorithm). */
+ * kernels still end normally).  QSGD and TernGrad: how often a block of a group of at most 2^18 elements
+ * looks for the other blocks' partial sums (0 = the default, 2^10) before it leaves its share to the block
+ * that comes last; the results are the same and no error arises.  Applies to the calls issued afterwards.
+ * Errors: MC_ERR_INVALID_ARG (null, an algorithm that does not wait). */
 int mc_set_barrier_spin_limit(mc_ctx *ctx, uint32_t polls);
 
 /* Diagnostic for the sparsifiers (Top-k, DGC, Rand-k; Section 5.1 names their selection as the

@@ -713,26 +713,37 @@ template void launch_tern_encode<AllCompress>(const LaunchCtx &, const AllCompre
 // ---------------------------------------------------------------------------
 // The two-pass quantizers on a small group, in one kernel: p stays in registers between the passes, and in place of the two
 // kernel boundaries the group's blocks (64 at most, which start one after the other and fit a fraction of the device)
-// wait until all have put their partial.  The wait is bounded: should the count never come, the block flags the failure
-// and leaves without encoding.
+// wait until all have put their partial.
 // (QSGD compress, 1 .. 64 tiles: 11.7 .. 13.2 -> 8.6 .. 10.0 us, TernGrad 11.8 -> 9.2 .. 10.3; eight groups of 34 k
 // elements in one launch, QSGD with the decompress-and-sum: 29.0 -> 22.6.)
+// No block has to be running for another to finish: one that has looked `looks` times in vain (the rest of the group has
+// found no room on the device for about a millisecond) hands its tile over and leaves, and the block that arrives last,
+// which never waits, encodes what was handed over besides its own.  (That a block may go round for another tile costs
+// QSGD 0.1 us a call, TernGrad nothing; the encode written out a second time for it 0 and 0.25.)
 // ---------------------------------------------------------------------------
-constexpr uint32_t kWaitLooks = 1u << 21;      // about a microsecond each
+// One thread of a block that gives up: the tiles it still has to encode (its own, or none).  The last block takes the word after
+// its own arrival, so if the count is not complete after the hand-over, the tile will be found; if it is, the tile is
+// taken back unless the last block was faster.  Either way the word is 0 when all blocks have left.
+__device__ __forceinline__ uint64_t hand_over(const CompressJob &job, uint64_t all)
+{
+    const uint64_t bit = 1ull << job.tile;
+    __hip_atomic_fetch_or(job.handed_over(), bit, __ATOMIC_SEQ_CST, __HIP_MEMORY_SCOPE_AGENT);      // (p in the state has to be seen with it)
+    if (__hip_atomic_load(job.arrive, __ATOMIC_SEQ_CST, __HIP_MEMORY_SCOPE_AGENT) < all) return 0;
+    return __hip_atomic_fetch_and(job.handed_over(), ~bit, __ATOMIC_SEQ_CST, __HIP_MEMORY_SCOPE_AGENT) & bit;
+}
 
 template <bool EF, int MODE, class SRC>
-__global__ __launch_bounds__(kBlock) void quantize_small_k(SRC src, uint32_t levels, uint64_t seed, uint32_t worker, uint32_t iter_lo, int *status)
+__global__ __launch_bounds__(kBlock) void quantize_small_k(SRC src, uint32_t levels, uint64_t seed, uint32_t worker, uint32_t iter_lo, uint32_t looks)
 {
     __shared__ double red[kWavesPerBlock];
     __shared__ float redf[kWavesPerBlock];
     __shared__ float scalar;
-    __shared__ int late;
+    __shared__ uint64_t todo;                    // the tiles that this block encodes, one bit each
     __shared__ uint4 stage[kWavesPerBlock][MODE == RED_L2 ? kChunk / 16 : kSteps / 2];       // a chunk's codes, or the 64-bit ballots of its steps
-    const CompressJob job = src.job();
+    CompressJob job = src.job();
     const GroupView &g = job.g;
-    const Chunk c = my_chunk(g.n, job.tile);
-    const bool any = c.base < g.n;
     const uint32_t nwords = (g.n + 31u) >> 5, wave = threadIdx.x >> 6;
+    Chunk c = my_chunk(g.n, job.tile);
     float p[kSteps];
     accumulate<EF, MODE>(job, c, levels, seed, p);
     double acc = 0.0;
@@ -744,64 +755,75 @@ __global__ __launch_bounds__(kBlock) void quantize_small_k(SRC src, uint32_t lev
     }
     const double part = MODE == RED_L2 ? block_sum(acc, red) : (double)block_max(mx, redf);
     if (threadIdx.x < 64) {
-        bool there = true;
+        uint64_t mine = 1ull << job.tile;
         if (threadIdx.x == 0) {
             put_partial(job.partial + job.tile, part);
-            const uint64_t all = (arrive_at(job.arrive) / job.ntiles + 1u) * job.ntiles;
-            uint32_t looks = 0;
-            while (__hip_atomic_load(job.arrive, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < all) {
-                __builtin_amdgcn_s_sleep(4);
-                if (++looks > kWaitLooks) { there = false; raise_flag(status, FLAG_GAVE_UP); break; }
-            }
-            late = there ? 0 : 1;
+            const uint64_t before = arrive_at(job.arrive), all = (before / job.ntiles + 1u) * job.ntiles;
+            if (before + 1u == all) mine |= __hip_atomic_exchange(job.handed_over(), 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            else
+                for (uint32_t look = 0; __hip_atomic_load(job.arrive, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < all; ++look) {
+                    if (look >= looks) { mine = hand_over(job, all); break; }
+                    __builtin_amdgcn_s_sleep(4);
+                }
         }
         all_arrived();
-        const double S = combine_partials<MODE == RED_MAX_ABS>(job.partial, job.ntiles);
-        if (threadIdx.x == 0) scalar = MODE == RED_L2 ? (float)sqrt(S) : (float)S;
+        const double S = combine_partials<MODE == RED_MAX_ABS>(job.partial, job.ntiles);       // (after a hand-over: of no use)
+        if (threadIdx.x == 0) { scalar = MODE == RED_L2 ? (float)sqrt(S) : (float)S; todo = mine; }
     }
     __syncthreads();
-    if (late) return;
     const float scale = scalar;
-    if (job.tile == job.ntiles - 1u && threadIdx.x == 0)
-        put_plain_header(job.hdr, MODE == RED_L2 ? MC_ALGO_QSGD : MC_ALGO_TERNGRAD, g.n, scale, 0.0f, MODE == RED_L2 ? levels : 0u);
-    if (EF) remember_call(job, scale, worker, iter_lo);
-    if (!any) return;
-    float uni[kSteps];
-    chunk_uniforms(seed, worker, iter_lo, g.goff + c.base, c.lane, uni);
-    if (MODE == RED_L2) {
-        const QsgdScale ks(scale, levels);
-        int8_t code[kSteps];
+    uint64_t left = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)todo) |
+                    ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(todo >> 32)) << 32);
+    if (!left) return;
+    for (;;) {                                   // its own tile, then those handed over
+        if (job.tile == job.ntiles - 1u && threadIdx.x == 0)
+            put_plain_header(job.hdr, MODE == RED_L2 ? MC_ALGO_QSGD : MC_ALGO_TERNGRAD, g.n, scale, 0.0f, MODE == RED_L2 ? levels : 0u);
+        if (EF) remember_call(job, scale, worker, iter_lo);
+        if (c.base < g.n) {
+            float uni[kSteps];
+            chunk_uniforms(seed, worker, iter_lo, g.goff + c.base, c.lane, uni);
+            if (MODE == RED_L2) {
+                const QsgdScale ks(scale, levels);
+                int8_t code[kSteps];
 #pragma unroll
-        for (int j = 0; j < kSteps; ++j) code[j] = (int8_t)qsgd_code(ks, p[j], uni[j]);
-        store_codes<int8_t>(reinterpret_cast<int8_t *>(job.body()), g.n, (g.n + 3u) & ~3u, c, code, stage[wave]);
-    } else {
-        uint32_t *planes = reinterpret_cast<uint32_t *>(job.body());
-        uint64_t bnz[kSteps], bng[kSteps];
-        tern_planes(c, g.n, scale, p, uni, bnz, bng);
-        store_plane(planes, nwords, c, bnz, reinterpret_cast<uint64_t *>(stage[wave]));
-        store_plane(planes + nwords, nwords, c, bng, reinterpret_cast<uint64_t *>(stage[wave]));
+                for (int j = 0; j < kSteps; ++j) code[j] = (int8_t)qsgd_code(ks, p[j], uni[j]);
+                store_codes<int8_t>(reinterpret_cast<int8_t *>(job.body()), g.n, (g.n + 3u) & ~3u, c, code, stage[wave]);
+            } else {
+                uint32_t *planes = reinterpret_cast<uint32_t *>(job.body());
+                uint64_t bnz[kSteps], bng[kSteps];
+                tern_planes(c, g.n, scale, p, uni, bnz, bng);
+                store_plane(planes, nwords, c, bnz, reinterpret_cast<uint64_t *>(stage[wave]));
+                store_plane(planes + nwords, nwords, c, bng, reinterpret_cast<uint64_t *>(stage[wave]));
+            }
+        }
+        left &= ~(1ull << job.tile);
+        if (!left) return;
+        job.tile = (uint32_t)__builtin_ctzll(left);
+        c = my_chunk(g.n, job.tile);
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");      // p of that tile, as the block that left it stored it
+        if (c.base < g.n) load_p<EF>(g, job.st, c, p);
     }
 }
 
 template <class SRC>
 void launch_quantize_small(const LaunchCtx &lc, int mode, const SRC &src, uint32_t tiles, bool ef, uint32_t levels, uint64_t seed, uint32_t worker,
-                           uint32_t iter_lo, int *status)
+                           uint32_t iter_lo, uint32_t looks)
 {
     if (tiles == 0) return;
     dim3 grid(tiles), block(kBlock);
     const int slot = mode == RED_L2 ? K_QSGD_ENCODE : K_TERN_ENCODE;
     prof_begin(lc, slot);
     if (mode == RED_L2) {
-        if (ef) MC_LAUNCH((quantize_small_k<true, RED_L2, SRC>), grid, block, lc, src, levels, seed, worker, iter_lo, status);
-        else MC_LAUNCH((quantize_small_k<false, RED_L2, SRC>), grid, block, lc, src, levels, seed, worker, iter_lo, status);
+        if (ef) MC_LAUNCH((quantize_small_k<true, RED_L2, SRC>), grid, block, lc, src, levels, seed, worker, iter_lo, looks);
+        else MC_LAUNCH((quantize_small_k<false, RED_L2, SRC>), grid, block, lc, src, levels, seed, worker, iter_lo, looks);
     } else {
-        if (ef) MC_LAUNCH((quantize_small_k<true, RED_MAX_ABS, SRC>), grid, block, lc, src, levels, seed, worker, iter_lo, status);
-        else MC_LAUNCH((quantize_small_k<false, RED_MAX_ABS, SRC>), grid, block, lc, src, levels, seed, worker, iter_lo, status);
+        if (ef) MC_LAUNCH((quantize_small_k<true, RED_MAX_ABS, SRC>), grid, block, lc, src, levels, seed, worker, iter_lo, looks);
+        else MC_LAUNCH((quantize_small_k<false, RED_MAX_ABS, SRC>), grid, block, lc, src, levels, seed, worker, iter_lo, looks);
     }
     prof_end(lc, slot);
 }
-template void launch_quantize_small<OneCompress>(const LaunchCtx &, int, const OneCompress &, uint32_t, bool, uint32_t, uint64_t, uint32_t, uint32_t, int *);
-template void launch_quantize_small<AllCompress>(const LaunchCtx &, int, const AllCompress &, uint32_t, bool, uint32_t, uint64_t, uint32_t, uint32_t, int *);
+template void launch_quantize_small<OneCompress>(const LaunchCtx &, int, const OneCompress &, uint32_t, bool, uint32_t, uint64_t, uint32_t, uint32_t, uint32_t);
+template void launch_quantize_small<AllCompress>(const LaunchCtx &, int, const AllCompress &, uint32_t, bool, uint32_t, uint64_t, uint32_t, uint32_t, uint32_t);
 
 // ---------------------------------------------------------------------------
 // FP16, single pass: h = binary16(p) round-to-nearest-even, e <- p - (float)h.

@@ -101,6 +101,7 @@ struct mc_ctx {
     size_t max_live = 0;
     double *d_partial = nullptr;
     uint64_t *d_arrive = nullptr;       // per group: blocks of small groups that have put their partial, over all calls
+    uint32_t wait_looks = kWaitLooks;   // of the small quantizer groups' blocks (mc_set_barrier_spin_limit)
     SparseScratch sparse{};
     uint32_t *d_hints = nullptr;        // candidate-filter hints: kHintWorkers per group (worker id modulo that)
     const uint32_t *last_hint = nullptr; // the record the most recent sparse mc_compress used (mc_select_stats)
@@ -694,7 +695,7 @@ static void decompress_launch(mc_ctx *ctx, const LaunchCtx &lc, const SRC &src, 
 // The kernels of a dense compressor over one group or all: `tiles` blocks of 4096 elements, `groups` groups.
 template <class SRC>
 static void dense_compress(const mc_config &cfg, const LaunchCtx &lc, const SRC &src, uint32_t tiles, uint32_t groups, uint32_t most_tiles, uint32_t worker,
-                           uint32_t iter_lo, int *status)
+                           uint32_t iter_lo, uint32_t looks)
 {
     // most_tiles: of any of the groups.  Small ones combine their partial sums in the kernel that makes them.
     // (While the profiler is on every step is a kernel of its own, so that its time can be read.)
@@ -716,13 +717,13 @@ static void dense_compress(const mc_config &cfg, const LaunchCtx &lc, const SRC 
         launch_sign_compress(lc, cfg.algo == MC_ALGO_SIGNSGD ? SIGN_PLAIN : SIGN_MOMENTUM, src, tiles, ef, cfg.dgc_momentum, algo, false);
         break;
     case MC_ALGO_QSGD:
-        if (small) { launch_quantize_small(lc, RED_L2, src, tiles, ef, levels, cfg.seed, worker, iter_lo, status); break; }
+        if (small) { launch_quantize_small(lc, RED_L2, src, tiles, ef, levels, cfg.seed, worker, iter_lo, looks); break; }
         launch_accum_reduce(lc, src, tiles, ef, RED_L2, levels, cfg.seed);
         launch_scalar_finalize(lc, src, groups, RED_L2, algo, levels, false);
         launch_qsgd_encode(lc, src, tiles, ef, levels, cfg.seed, worker, iter_lo);
         break;
     case MC_ALGO_TERNGRAD:
-        if (small) { launch_quantize_small(lc, RED_MAX_ABS, src, tiles, ef, 0, cfg.seed, worker, iter_lo, status); break; }
+        if (small) { launch_quantize_small(lc, RED_MAX_ABS, src, tiles, ef, 0, cfg.seed, worker, iter_lo, looks); break; }
         launch_accum_reduce(lc, src, tiles, ef, RED_MAX_ABS, 0, cfg.seed);
         launch_scalar_finalize(lc, src, groups, RED_MAX_ABS, algo, 0, false);
         launch_tern_encode(lc, src, tiles, ef, cfg.seed, worker, iter_lo);
@@ -773,7 +774,7 @@ static int compress_impl(mc_ctx *ctx, int32_t group, uint32_t worker, uint64_t i
     if (!is_sparse(cfg.algo)) {
         // (the static entry point may not rely on what an earlier call left in its array: no count of arrivals)
         uint64_t *arrive = partial == ctx->d_partial ? ctx->d_arrive + (size_t)group * kArriveStride : nullptr;
-        dense_compress(cfg, lc, OneCompress{gv, sf, hdr, partial, arrive}, tiles_in(n), 1, tiles_in(n), worker, (uint32_t)iter, ctx->d_status);
+        dense_compress(cfg, lc, OneCompress{gv, sf, hdr, partial, arrive}, tiles_in(n), 1, tiles_in(n), worker, (uint32_t)iter, ctx->wait_looks);
         return check_launch();
     }
     SparseScratch sp = ctx->sparse;
@@ -838,7 +839,7 @@ static int compress_all(mc_ctx *ctx, uint32_t worker, uint64_t iter, const float
         const SparseBlocks nb{ctx->all_blocks[BLK_TILE], ctx->all_blocks[BLK_SELECT], ctx->all_blocks[BLK_EMIT]};
         launch_sparse_compress(lc, cfg.algo, AllSparse{tb, sp, ctx->last_group}, nb, ef, sparse_call(ctx, worker, iter));
     } else dense_compress(cfg, lc, AllCompress{tb, ctx->d_partial, ctx->d_arrive}, ctx->all_blocks[BLK_TILE], (uint32_t)y, ctx->max_tiles, worker,
-                        (uint32_t)iter, ctx->d_status);
+                        (uint32_t)iter, ctx->wait_looks);
     for (size_t j = 0; j < y; ++j) if (ctx->groups[j].n == 0) empty_compress(cfg, lc, static_cast<PayloadHeader *>(payloads[j]));
     return check_launch();
 }
@@ -1021,8 +1022,11 @@ int mc_select_stats(mc_ctx *ctx, mc_select_counts *out, int32_t reset)
 
 int mc_set_barrier_spin_limit(mc_ctx *ctx, uint32_t polls)
 {
-    if (!ctx || !is_sparse(ctx->cfg.algo)) return MC_ERR_INVALID_ARG;
-    ctx->sparse.spin_limit = polls ? polls - 1u : kBarrierSpinLimit;       // polls = 1: give up after the first look
+    if (!ctx) return MC_ERR_INVALID_ARG;
+    // polls = 1: give up after the first look
+    if (is_sparse(ctx->cfg.algo)) ctx->sparse.spin_limit = polls ? polls - 1u : kBarrierSpinLimit;
+    else if (ctx->cfg.algo == MC_ALGO_QSGD || ctx->cfg.algo == MC_ALGO_TERNGRAD) ctx->wait_looks = polls ? polls - 1u : kWaitLooks;
+    else return MC_ERR_INVALID_ARG;
     return MC_OK;
 }
 

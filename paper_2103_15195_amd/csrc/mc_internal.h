@@ -89,6 +89,7 @@ __device__ __forceinline__ GroupView view_of(const GroupTable &tb, const GroupCo
 // wavefront that adds them, in that kernel's order.
 constexpr uint32_t kSmallTiles = 64;
 constexpr int kArriveStride = 16;             // 64-bit words between the groups' counts (a line each)
+constexpr uint32_t kWaitLooks = 1u << 10;     // looks of about a microsecond each before a waiting quantizer's block leaves its tile to the last one
 __host__ __device__ inline uint32_t tiles_in(uint32_t n) { return (uint32_t)(((uint64_t)n + kTile - 1) / kTile); }
 
 // A dense compressor's job.  The state's header lies in front of st, the payload's body behind hdr.
@@ -97,10 +98,11 @@ struct CompressJob {
     float *st;                    // null when the scheme keeps no state
     PayloadHeader *hdr;
     double *partial;              // one double per tile (OneBit: three arrays of one per tile)
-    uint64_t *arrive;             // the group's count of blocks that have their partial ready (small groups)
+    uint64_t *arrive;             // the group's count of blocks that have their partial ready (small groups); the word behind it: handed_over
     uint32_t tile, ntiles;
     __device__ __forceinline__ StateHeader *state_header() const { return reinterpret_cast<StateHeader *>(st) - 1; }
     __device__ __forceinline__ uint8_t *body() const { return reinterpret_cast<uint8_t *>(hdr) + kHeaderBytes; }
+    __device__ __forceinline__ uint64_t *handed_over() const { return arrive + 1; }      // tiles that a waiting quantizer left to the last block; 0 between calls
 };
 struct OneCompress {
     GroupView g;
@@ -222,7 +224,7 @@ void launch_expand_all(const LaunchCtx &lc, const GroupTable &tb, uint32_t tiles
 // small: every group has at most kSmallTiles tiles and src.arrive counts
 template <class SRC> void launch_sign_compress(const LaunchCtx &lc, int mode, const SRC &src, uint32_t tiles, bool ef, float beta, uint32_t algo, bool small);
 template <class SRC> void launch_quantize_small(const LaunchCtx &lc, int mode, const SRC &src, uint32_t tiles, bool ef, uint32_t levels, uint64_t seed,
-                                                uint32_t worker, uint32_t iter_lo, int *status);
+                                                uint32_t worker, uint32_t iter_lo, uint32_t looks);
 template <class SRC> void launch_scalar_finalize(const LaunchCtx &lc, const SRC &src, uint32_t groups, int mode, uint32_t algo, uint32_t levels,
                                                  bool keep);
 template <class SRC> void launch_accum_reduce(const LaunchCtx &lc, const SRC &src, uint32_t tiles, bool ef, int mode, uint32_t levels, uint64_t seed);

@@ -79,7 +79,7 @@ void launch_expand_ptrs(const LaunchCtx &, const GroupView &, uintptr_t *) { COU
 void launch_expand_all(const LaunchCtx &, const GroupTable &, uint32_t, uintptr_t *) { COUNT("expand_all"); }
 void launch_state_convert(const LaunchCtx &, int, bool, uint32_t, const void *, void *, uint32_t, uint64_t, uint64_t) { COUNT("state_convert"); }
 template <class SRC> void launch_sign_compress(const LaunchCtx &, int, const SRC &, uint32_t, bool, float, uint32_t, bool) { COUNT("compress"); }
-template <class SRC> void launch_quantize_small(const LaunchCtx &, int, const SRC &, uint32_t, bool, uint32_t, uint64_t, uint32_t, uint32_t, int *) { COUNT("compress"); }
+template <class SRC> void launch_quantize_small(const LaunchCtx &, int, const SRC &, uint32_t, bool, uint32_t, uint64_t, uint32_t, uint32_t, uint32_t) { COUNT("compress"); }
 template <class SRC> void launch_scalar_finalize(const LaunchCtx &, const SRC &, uint32_t, int, uint32_t, uint32_t, bool) { COUNT("finalize"); }
 template <class SRC> void launch_accum_reduce(const LaunchCtx &, const SRC &, uint32_t, bool, int, uint32_t, uint64_t) { COUNT("accum_reduce"); }
 template <class SRC> void launch_qsgd_encode(const LaunchCtx &, const SRC &, uint32_t, bool, uint32_t, uint64_t, uint32_t, uint32_t) { COUNT("compress"); }
@@ -90,7 +90,7 @@ template <class SRC> void launch_sparse_compress(const LaunchCtx &, int, const S
 template <class SRC> void launch_sparse_decompress(const LaunchCtx &, int, const SRC &, uint32_t, int, float, int *, bool) { COUNT("decompress"); }
 #define BOTH_FORMS(S)                                                                                                                  \
     template void launch_sign_compress<S>(const LaunchCtx &, int, const S &, uint32_t, bool, float, uint32_t, bool);                   \
-    template void launch_quantize_small<S>(const LaunchCtx &, int, const S &, uint32_t, bool, uint32_t, uint64_t, uint32_t, uint32_t, int *); \
+    template void launch_quantize_small<S>(const LaunchCtx &, int, const S &, uint32_t, bool, uint32_t, uint64_t, uint32_t, uint32_t, uint32_t); \
     template void launch_scalar_finalize<S>(const LaunchCtx &, const S &, uint32_t, int, uint32_t, uint32_t, bool);                    \
     template void launch_accum_reduce<S>(const LaunchCtx &, const S &, uint32_t, bool, int, uint32_t, uint64_t);                       \
     template void launch_qsgd_encode<S>(const LaunchCtx &, const S &, uint32_t, bool, uint32_t, uint64_t, uint32_t, uint32_t);         \

@@ -56,3 +56,38 @@ def test_all_kinds_of_calls_in_turn(algo):
         for x, y in zip(bufs[0][0] + bufs[0][1], bufs[1][0] + bufs[1][1]):
             assert torch.equal(x, y), it
     assert "scalar_finalize" in a.profile_read()
+
+
+@pytest.mark.parametrize("ef", [0, 1])
+@pytest.mark.parametrize("numel", [[2 * 4096], [3 * 4096 - 7], [63 * 4096 + 5], [64 * 4096], [5, 64 * 4096 - 3, 4097, 0, 30000]])
+@pytest.mark.parametrize("algo", ["qsgd", "terngrad"])
+def test_no_block_depends_on_another_running(algo, numel, ef):
+    """Blocks that give up at once (forced from the host: one look) leave their tiles to the group's last block: the same
+    bytes, call after call, and no error; one group per call, and all groups in one."""
+    y = len(numel)
+    ctx = B.Context(algo, numel, list(range(y + 1)), use_ef=ef, seed=4)
+    cfg = O.Config(B.ALGO_IDS[algo], seed=4, use_ef=ef)
+    ctx.mc_set_barrier_spin_limit(1)
+    state = [torch.zeros(ctx.state_bytes(j), dtype=torch.uint8, device=DEV) for j in range(y)]
+    payload = [torch.full((ctx.payload_bytes(j),), 0xAA, dtype=torch.uint8, device=DEV) for j in range(y)]
+    held = [O.new_state(cfg, n) for n in numel]
+    rng = np.random.default_rng([sum(numel), ef])
+    for it in range(6):
+        if it == 4:
+            ctx.mc_set_barrier_spin_limit(0)     # nothing of the calls before is left behind
+        g = [(rng.standard_normal(n) * np.exp(rng.standard_normal(n))).astype(np.float32) for n in numel]
+        dev = [torch.from_numpy(x).to(DEV) for x in g]
+        if it % 2:
+            ctx.mc_compress_groups(1, it, dev, state if ef else None, payload)
+        else:
+            for j in range(y):
+                ctx.mc_compress(j, 1, it, dev[j:j + 1], state[j] if ef else None, payload[j])
+        for j in range(y):
+            want, _ = O.compress(cfg, g[j], held[j], group_off=sum(numel[:j]), worker=1, it=it)
+            assert np.array_equal(payload[j].cpu().numpy(), want), (it, j)
+    for j in range(y if ef else 0):
+        if numel[j]:
+            e = torch.empty(numel[j], dtype=torch.float32, device=DEV)
+            ctx.mc_state_export_residual(j, state[j], e)
+            assert np.array_equal(e.cpu().numpy().view(np.uint32), held[j].view(np.uint32))
+    assert ctx.mc_last_device_status() == B.MC_OK

@@ -79,3 +79,17 @@ def test_candidate_arrays_cover_what_the_kernels_read(host, algo, numel, bounds)
     assert any(host.nd_allocated(4 * s) for s in range(read, most)), "values"
     assert any(host.nd_allocated(2 * s) for s in range(read, most)), "positions"
     ctx.close()
+
+
+@pytest.mark.parametrize("algo", list(B.ALGO_IDS))
+def test_who_takes_a_limit_on_waits(host, algo):
+    """The sparsifiers (their blocks wait on the rare routes) and the quantizers (on small groups); all others refuse it."""
+    ctx = B.Context(algo, [100], [0, 1])
+    if algo in ("topk", "dgc", "randk", "qsgd", "terngrad"):
+        ctx.mc_set_barrier_spin_limit(1)
+        ctx.mc_set_barrier_spin_limit(0)
+    else:
+        with pytest.raises(B.McError) as e:
+            ctx.mc_set_barrier_spin_limit(1)
+        assert e.value.status == B.MC_ERR_INVALID_ARG
+    ctx.close()
