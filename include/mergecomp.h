@@ -185,6 +185,8 @@ int mc_partition_search(const int64_t *numel, const double *bwd_time, int32_t n_
  *                     than one group, these for every group instead of for the largest (the key list 32 KiB per tile,
  *                     at most 2 MiB), unless that is more than 2 GiB of candidates or 512 MiB of histograms or lists,
  *                     and not with a sampled threshold
+ * What serves the calls over all groups only is left out where the device has no room for it; they then work group by
+ * group.
  */
 int mc_ctx_create(mc_ctx **out, const mc_config *cfg, const int64_t *numel, int32_t n_tensors,
                   const int32_t *bounds, int32_t y);

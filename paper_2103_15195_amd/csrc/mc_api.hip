@@ -117,13 +117,14 @@ struct mc_ctx {
     uint32_t all_blocks[BLK_KINDS] = {};
     uint32_t last_group = 0;            // the last group that holds elements
     size_t all_live = 0;
+    uint32_t all_subs = 0;              // sublists of keys of all groups' scratch
     std::vector<int64_t> tensor_numel;  // elements of every tensor of the model
     std::vector<uint32_t> first_tile, first_sub;       // per group, of its part of the sparsifiers' scratch
     std::vector<AllSlot> all_slots;
     std::vector<uintptr_t> want_all;
     std::vector<Span> spans;
     const SelectState *last_sel = nullptr;             // what the most recent sparse mc_compress recorded of its selection
-    uintptr_t *d_slots = nullptr, *d_all_slots = nullptr;     // the memory behind `slots` and `all_slots`
+    std::vector<void *> held;           // the context's device memory
     uint64_t clock = 0;
     uint32_t sync_blocks = 1;           // blocks of 1024 threads the device holds at once for sure: one per compute unit
     Profiler prof;
@@ -221,6 +222,137 @@ static bool is_sparse(int algo) { return algo == MC_ALGO_TOPK || algo == MC_ALGO
 // n-element vectors of a group's state: the residual (DGC: v and u; SigNUM: the momentum; SignSGD: nothing)
 static uint32_t state_vectors(int algo) { return algo == MC_ALGO_DGC ? 2u : algo == MC_ALGO_SIGNSGD ? 0u : 1u; }
 static bool always_state(int algo) { return algo == MC_ALGO_DGC || algo == MC_ALGO_SIGNUM || algo == MC_ALGO_RANDK; }
+
+// ---- device memory of a context
+template <class T>
+static bool grab(mc_ctx *ctx, T **p, size_t bytes)
+{
+    void *q = nullptr;
+    if (hipMalloc(&q, bytes) != hipSuccess) { (void)hipGetLastError(); return false; }
+    ctx->held.push_back(q);              // (reserved)
+    *p = static_cast<T *>(q);
+    return true;
+}
+template <class T>
+static int grab_zeroed(mc_ctx *ctx, T **p, size_t bytes)
+{
+    if (!grab(ctx, p, bytes)) return MC_ERR_ALLOC;
+    return hipMemset(*p, 0, bytes) == hipSuccess ? MC_OK : MC_ERR_DEVICE;
+}
+template <class T>
+static int grab_copy(mc_ctx *ctx, T **p, const std::vector<T> &host)
+{
+    if (host.empty()) return MC_OK;
+    if (!grab(ctx, p, host.size() * sizeof(T))) return MC_ERR_ALLOC;
+    return hipMemcpy(*p, host.data(), host.size() * sizeof(T), hipMemcpyHostToDevice) == hipSuccess ? MC_OK : MC_ERR_DEVICE;
+}
+// all that was allocated after the first `keep` pieces
+static void give_back(mc_ctx *ctx, size_t keep)
+{
+    for (; ctx->held.size() > keep; ctx->held.pop_back()) (void)hipFree(ctx->held.back());
+}
+
+// A part of the scratch for every group lets the sparsifiers' calls over all groups run as one launch per step; a
+// model for which that is more than 2 GiB of candidates (350 M elements) or a quarter of that in histograms or key
+// lists is large enough per group to be taken one group at a time, in scratch of the size of the largest.
+static bool own_scratch_fits(const mc_ctx *ctx)
+{
+    return is_sparse(ctx->cfg.algo) && !ctx->cfg.dgc_sample_ppm && (size_t)ctx->all_blocks[BLK_TILE] * (6u * (size_t)kTile) <= (size_t(2) << 30) &&
+           ctx->groups.size() * kHistWords * sizeof(uint32_t) <= (size_t(512) << 20) && (size_t)ctx->all_subs * kUCap * sizeof(UEntry) <= (size_t(512) << 20);
+}
+
+// Tables and scratch of a context whose groups are known.  all: also what a launch over all groups needs; own: the
+// sparsifiers' scratch for every group instead of for the largest.  After MC_ERR_ALLOC the caller gives back what there is.
+static int set_up(mc_ctx *ctx, bool all, bool own)
+{
+    const mc_config *cfg = &ctx->cfg;
+    const size_t y = ctx->groups.size(), tiles = std::max<size_t>(ctx->max_tiles, 1), all_tiles = ctx->all_blocks[BLK_TILE];
+    int rc = MC_OK;
+    ctx->own_scratch = own;
+    ctx->all_slots.clear();
+    if (all) {
+        std::vector<GroupConst> table(y);
+        std::vector<uint32_t> block_group[BLK_KINDS];
+        uint32_t ptrs = 0;
+        for (size_t j = 0; j < y; ++j) {
+            const Group &g = ctx->groups[j];
+            const uint32_t blocks[BLK_KINDS] = {tiles_in(g.n), plane_blocks(g.n), sparse_blocks(g.n).select, sparse_blocks(g.n).emit};
+            GroupConst &c = table[j];
+            c.seg_off = g.d_seg_off; c.chunk_seg = g.d_chunk_seg;
+            c.goff = g.goff; c.k = g.k; c.n = g.n; c.nseg = (uint32_t)g.live.size();
+            c.first_ptr = ptrs; c.first_sub = ctx->first_sub[j];
+            for (int b = 0; b < BLK_KINDS; ++b) {
+                c.first[b] = (uint32_t)block_group[b].size();
+                block_group[b].insert(block_group[b].end(), blocks[b], (uint32_t)j);
+            }
+            ptrs += c.nseg;
+        }
+        if ((rc = grab_copy(ctx, &ctx->d_groups, table)) != MC_OK) return rc;
+        for (int b = 0; b < BLK_KINDS; ++b) if ((rc = grab_copy(ctx, &ctx->d_block_group[b], block_group[b])) != MC_OK) return rc;
+    }
+    if (!grab(ctx, &ctx->d_partial, 3 * std::max(tiles, all ? all_tiles : 0) * sizeof(double))) return MC_ERR_ALLOC;
+    if ((rc = grab_zeroed(ctx, &ctx->d_arrive, y * kArriveStride * sizeof(uint64_t))) != MC_OK) return rc;
+    if ((rc = grab_zeroed(ctx, &ctx->d_status, sizeof(int))) != MC_OK) return rc;
+    if (is_sparse(cfg->algo)) {
+        SparseScratch &sp = ctx->sparse;
+        const size_t parts = own ? y : 1, stiles = own ? all_tiles : tiles;
+        const size_t lists = own ? ctx->all_subs + kUSub : (size_t)kUSub;      // (the emit kernel looks at kUSub sublists of any group)
+        const size_t slots = stiles * kTile + kCandPad;
+        if ((rc = grab_zeroed(ctx, &sp.hist, parts * kHistWords * sizeof(uint32_t))) != MC_OK) return rc;
+        if ((rc = grab_zeroed(ctx, &sp.sel, parts * 4 * sizeof(SelectState))) != MC_OK) return rc;
+        if ((rc = grab_zeroed(ctx, &ctx->d_hints, y * kHintWorkers * kHintWords * sizeof(uint32_t))) != MC_OK) return rc;
+        if (!grab(ctx, &sp.cand_bits, slots * sizeof(uint32_t)) || !grab(ctx, &sp.cand_loc, slots * sizeof(uint16_t)) ||
+            !grab(ctx, &sp.tile_cnt, stiles * sizeof(uint32_t)) || !grab(ctx, &sp.blk_cnt, stiles * sizeof(uint32_t)) ||
+            !grab(ctx, &sp.ulist, lists * kUCap * sizeof(UEntry))) return MC_ERR_ALLOC;
+        if ((rc = grab_zeroed(ctx, &sp.tile_runs, stiles * sizeof(uint64_t))) != MC_OK) return rc;
+        if ((rc = grab_zeroed(ctx, &sp.ucount, parts * kUSub * kUCountStride * sizeof(uint32_t))) != MC_OK) return rc;
+        if ((rc = grab_zeroed(ctx, &sp.arrive, parts * kUCountStride * sizeof(uint32_t))) != MC_OK) return rc;
+        if ((rc = grab_zeroed(ctx, &sp.sync, 64 * sizeof(uint32_t))) != MC_OK) return rc;
+        ctx->last_sel = sp.sel;
+        int cus = 0;
+        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ctx->device) != hipSuccess || cus < 1) return MC_ERR_DEVICE;
+        ctx->sync_blocks = (uint32_t)cus;
+        sp.spin_limit = kBarrierSpinLimit;
+    }
+    {
+        // the per-chunk address tables of all slots together stay below 256 MiB (or four lists per group)
+        size_t words = 0;                    // of one slot of every group
+        for (const Group &g : ctx->groups) words += lines(g.live.size()) + lines((size_t)tiles_in(g.n) * kWavesPerBlock);
+        words = std::max<size_t>(words, 32);
+        ctx->group_slots = std::min<size_t>(std::max<size_t>(kGroupSlots, kPtrSlots / y), std::max<size_t>(4, (size_t(256) << 20) / (words * sizeof(uintptr_t))));
+        ctx->slots.assign(ctx->group_slots * y, PtrSlot());
+        uintptr_t *at = nullptr;
+        if (!grab(ctx, &at, ctx->group_slots * words * sizeof(uintptr_t))) return MC_ERR_ALLOC;
+        for (size_t i = 0; i < ctx->slots.size(); ++i) {
+            const Group &g = ctx->groups[i / ctx->group_slots];
+            PtrSlot &s = ctx->slots[i];
+            s.dev = at;
+            at += lines(g.live.size());
+            s.dev_chunk = at;
+            at += lines((size_t)tiles_in(g.n) * kWavesPerBlock);
+            s.host.reserve(g.live.size());
+        }
+        ctx->want.reserve(ctx->max_live);
+        ctx->prof.pending.reserve(1024);
+        ctx->prof.pool.reserve(2048);
+    }
+    if (all) {
+        // lists of calls over all groups: a decompress-and-sum of the most workers needs the longest; 64 MiB in all
+        const size_t most = lines(ctx->all_live + (size_t)kMaxWorkers * y), chunks = lines(all_tiles * kWavesPerBlock);
+        const size_t count = std::min<size_t>(kAllSlots, std::max<size_t>(2, (size_t(64) << 20) / ((most + chunks) * sizeof(uintptr_t))));
+        uintptr_t *at = nullptr;
+        if (!grab(ctx, &at, count * (most + chunks) * sizeof(uintptr_t))) return MC_ERR_ALLOC;
+        ctx->all_slots.resize(count);
+        for (AllSlot &s : ctx->all_slots) {
+            s.dev = at; s.dev_chunk = at + most;
+            at += most + chunks;
+            s.host.reserve(most);
+        }
+        ctx->want_all.reserve(most);
+        ctx->spans.reserve(most);
+    }
+    return MC_OK;
+}
 
 extern "C" {
 
@@ -364,19 +496,7 @@ int mc_ctx_destroy(mc_ctx *ctx)
     (void)hipDeviceSynchronize();
     prof_drain(ctx->prof);
     for (hipEvent_t e : ctx->prof.pool) (void)hipEventDestroy(e);
-    for (Group &g : ctx->groups) {
-        if (g.d_seg_off) (void)hipFree(g.d_seg_off);
-        if (g.d_chunk_seg) (void)hipFree(g.d_chunk_seg);
-    }
-    void *tables[] = {ctx->d_slots, ctx->d_all_slots, ctx->d_groups, ctx->d_block_group[0], ctx->d_block_group[1], ctx->d_block_group[2], ctx->d_block_group[3]};
-    for (void *b : tables) if (b) (void)hipFree(b);
-    if (ctx->d_partial) (void)hipFree(ctx->d_partial);
-    if (ctx->d_arrive) (void)hipFree(ctx->d_arrive);
-    void *sparse_bufs[] = {ctx->sparse.hist, ctx->sparse.sel, ctx->d_hints, ctx->sparse.cand_bits, ctx->sparse.cand_loc,
-                           ctx->sparse.tile_runs, ctx->sparse.tile_cnt, ctx->sparse.blk_cnt, ctx->sparse.ulist, ctx->sparse.ucount,
-                           ctx->sparse.arrive, ctx->sparse.sync};
-    for (void *b : sparse_bufs) if (b) (void)hipFree(b);
-    if (ctx->d_status) (void)hipFree(ctx->d_status);
+    give_back(ctx, 0);
     if (switched) (void)hipSetDevice(prev);
     delete ctx;
     return MC_OK;
@@ -415,6 +535,7 @@ int mc_ctx_create(mc_ctx **out, const mc_config *cfg, const int64_t *numel, int3
     int rc = MC_OK;
     try {
         ctx->groups.resize(y);
+        ctx->held.reserve(2 * (size_t)y + 32);           // (the groups' tables, and what set_up allocates)
         ctx->tensor_numel.assign(numel, numel + n_tensors);
         uint64_t goff = 0;
         for (int32_t j = 0; j < y && rc == MC_OK; ++j) {
@@ -433,131 +554,35 @@ int mc_ctx_create(mc_ctx **out, const mc_config *cfg, const int64_t *numel, int3
             g.k = is_sparse(cfg->algo) ? topk_count(n, cfg->ratio_ppm) : 0;
             if (cfg->dgc_sample_ppm) g.k = std::min<uint64_t>(2 * g.k, n);     // sampled threshold: the payload's capacity
             goff += n;
-            if (hipMalloc(&g.d_seg_off, off.size() * sizeof(uint32_t)) != hipSuccess) { rc = MC_ERR_ALLOC; break; }
+            if (!grab(ctx, &g.d_seg_off, off.size() * sizeof(uint32_t))) { rc = MC_ERR_ALLOC; break; }
             if (hipMemcpy(g.d_seg_off, off.data(), off.size() * sizeof(uint32_t), hipMemcpyHostToDevice) != hipSuccess) { rc = MC_ERR_DEVICE; break; }
             std::vector<uint32_t> cseg((size_t)((n + kChunk - 1) / kChunk) + 1, 0u);
             for (size_t c = 0, sidx = 0; c * kChunk < n; ++c) {
                 while (off[sidx + 1] <= c * kChunk) ++sidx;
                 cseg[c] = (uint32_t)sidx;
             }
-            if (hipMalloc(&g.d_chunk_seg, cseg.size() * sizeof(uint32_t)) != hipSuccess) { rc = MC_ERR_ALLOC; break; }
+            if (!grab(ctx, &g.d_chunk_seg, cseg.size() * sizeof(uint32_t))) { rc = MC_ERR_ALLOC; break; }
             if (hipMemcpy(g.d_chunk_seg, cseg.data(), cseg.size() * sizeof(uint32_t), hipMemcpyHostToDevice) != hipSuccess) { rc = MC_ERR_DEVICE; break; }
             ctx->max_tiles = std::max<uint32_t>(ctx->max_tiles, (uint32_t)((n + kTile - 1) / kTile));
             ctx->max_live = std::max(ctx->max_live, g.live.size());
         }
-        const size_t tiles = std::max<size_t>(ctx->max_tiles, 1);
-        // ---- what a launch over all groups needs to know of them
-        const bool many = y > 1;
-        size_t all_tiles = 0, subs = 0;
-        std::vector<GroupConst> table((size_t)y);
-        ctx->first_tile.resize((size_t)y);
-        ctx->first_sub.resize((size_t)y);
-        std::vector<uint32_t> block_group[BLK_KINDS];
-        for (int32_t j = 0; j < y; ++j) {
-            const Group &g = ctx->groups[j];
-            const uint32_t nt = tiles_in(g.n);
-            const uint32_t blocks[BLK_KINDS] = {nt, plane_blocks(g.n), sparse_blocks(g.n).select, sparse_blocks(g.n).emit};
-            GroupConst &c = table[j];
-            c.seg_off = g.d_seg_off; c.chunk_seg = g.d_chunk_seg;
-            c.goff = g.goff; c.k = g.k; c.n = g.n; c.nseg = (uint32_t)g.live.size();
-            c.first_ptr = (uint32_t)ctx->all_live; c.first_sub = (uint32_t)subs;
-            ctx->first_tile[j] = (uint32_t)all_tiles; ctx->first_sub[j] = (uint32_t)subs;
-            for (int b = 0; b < BLK_KINDS; ++b) {
-                c.first[b] = ctx->all_blocks[b];
-                if (many) block_group[b].insert(block_group[b].end(), blocks[b], (uint32_t)j);
-                ctx->all_blocks[b] += blocks[b];
-            }
-            all_tiles += nt;
-            subs += std::min<uint32_t>(nt, kUSub);
+        for (const Group &g : ctx->groups) {
+            const uint32_t blocks[BLK_KINDS] = {tiles_in(g.n), plane_blocks(g.n), sparse_blocks(g.n).select, sparse_blocks(g.n).emit};
+            ctx->first_tile.push_back(ctx->all_blocks[BLK_TILE]);
+            ctx->first_sub.push_back(ctx->all_subs);
+            for (int b = 0; b < BLK_KINDS; ++b) ctx->all_blocks[b] += blocks[b];
+            ctx->all_subs += std::min<uint32_t>(blocks[BLK_TILE], kUSub);
             ctx->all_live += g.live.size();
-            if (g.n) ctx->last_group = (uint32_t)j;
-        }
-        if (many && rc == MC_OK) {
-            if (hipMalloc(&ctx->d_groups, table.size() * sizeof(GroupConst)) != hipSuccess) rc = MC_ERR_ALLOC;
-            else if (hipMemcpy(ctx->d_groups, table.data(), table.size() * sizeof(GroupConst), hipMemcpyHostToDevice) != hipSuccess) rc = MC_ERR_DEVICE;
-            for (int b = 0; b < BLK_KINDS && rc == MC_OK; ++b) {
-                const size_t bytes = block_group[b].size() * sizeof(uint32_t);
-                if (bytes == 0) continue;
-                if (hipMalloc(&ctx->d_block_group[b], bytes) != hipSuccess) rc = MC_ERR_ALLOC;
-                else if (hipMemcpy(ctx->d_block_group[b], block_group[b].data(), bytes, hipMemcpyHostToDevice) != hipSuccess) rc = MC_ERR_DEVICE;
-            }
-        }
-        const size_t hist_words = kHistWords, slot_bytes = 6u * (size_t)kTile;
-        // A part of the scratch for every group lets the sparsifiers' calls over all groups run as one launch per step; a
-        // model for which that is more than 2 GiB of candidates (350 M elements) or a quarter of that in histograms or key
-        // lists is large enough per group to be taken one group at a time, in scratch of the size of the largest.
-        ctx->own_scratch = many && is_sparse(cfg->algo) && !cfg->dgc_sample_ppm && all_tiles > 0 && all_tiles * slot_bytes <= (size_t(2) << 30) &&
-                           (size_t)y * hist_words * sizeof(uint32_t) <= (size_t(512) << 20) && subs * kUCap * sizeof(UEntry) <= (size_t(512) << 20);
-        const size_t parts = ctx->own_scratch ? (size_t)y : 1, stiles = ctx->own_scratch ? all_tiles : tiles;
-        const size_t lists = ctx->own_scratch ? subs + kUSub : (size_t)kUSub;      // (the emit kernel looks at kUSub sublists of any group)
-        if (rc == MC_OK && hipMalloc(&ctx->d_partial, 3 * std::max(tiles, many ? all_tiles : 0) * sizeof(double)) != hipSuccess) rc = MC_ERR_ALLOC;
-        const size_t arrive_bytes = (size_t)y * kArriveStride * sizeof(uint64_t);
-        if (rc == MC_OK && hipMalloc(&ctx->d_arrive, arrive_bytes) != hipSuccess) rc = MC_ERR_ALLOC;
-        if (rc == MC_OK && hipMemset(ctx->d_arrive, 0, arrive_bytes) != hipSuccess) rc = MC_ERR_DEVICE;
-        if (rc == MC_OK && hipMalloc(&ctx->d_status, sizeof(int)) != hipSuccess) rc = MC_ERR_ALLOC;
-        if (rc == MC_OK && hipMemset(ctx->d_status, 0, sizeof(int)) != hipSuccess) rc = MC_ERR_DEVICE;
-        if (rc == MC_OK && is_sparse(cfg->algo)) {
-            SparseScratch &sp = ctx->sparse;
-            const size_t hist_bytes = parts * hist_words * sizeof(uint32_t), sel_bytes = parts * 4 * sizeof(SelectState);
-            const size_t slots = stiles * kTile + kCandPad, count_bytes = parts * kUSub * kUCountStride * sizeof(uint32_t);
-            if (hipMalloc(&sp.hist, hist_bytes) != hipSuccess || hipMalloc(&sp.sel, sel_bytes) != hipSuccess ||
-                hipMalloc(&ctx->d_hints, (size_t)y * kHintWorkers * kHintWords * sizeof(uint32_t)) != hipSuccess ||
-                hipMalloc(&sp.cand_bits, slots * sizeof(uint32_t)) != hipSuccess ||
-                hipMalloc(&sp.cand_loc, slots * sizeof(uint16_t)) != hipSuccess ||
-                hipMalloc(&sp.tile_runs, stiles * sizeof(uint64_t)) != hipSuccess ||
-                hipMalloc(&sp.tile_cnt, stiles * sizeof(uint32_t)) != hipSuccess ||
-                hipMalloc(&sp.blk_cnt, stiles * sizeof(uint32_t)) != hipSuccess ||
-                hipMalloc(&sp.ulist, lists * kUCap * sizeof(UEntry)) != hipSuccess ||
-                hipMalloc(&sp.ucount, count_bytes) != hipSuccess ||
-                hipMalloc(&sp.arrive, parts * kUCountStride * sizeof(uint32_t)) != hipSuccess ||
-                hipMalloc(&sp.sync, 64 * sizeof(uint32_t)) != hipSuccess) rc = MC_ERR_ALLOC;
-            else if (hipMemset(sp.hist, 0, hist_bytes) != hipSuccess || hipMemset(sp.sel, 0, sel_bytes) != hipSuccess ||
-                     hipMemset(ctx->d_hints, 0, (size_t)y * kHintWorkers * kHintWords * sizeof(uint32_t)) != hipSuccess ||
-                     hipMemset(sp.tile_runs, 0, stiles * sizeof(uint64_t)) != hipSuccess ||
-                     hipMemset(sp.ucount, 0, count_bytes) != hipSuccess ||
-                     hipMemset(sp.arrive, 0, parts * kUCountStride * sizeof(uint32_t)) != hipSuccess ||
-                     hipMemset(sp.sync, 0, 64 * sizeof(uint32_t)) != hipSuccess) rc = MC_ERR_DEVICE;
-            ctx->last_sel = sp.sel;
-            int cus = 0;
-            if (rc == MC_OK && (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ctx->device) != hipSuccess || cus < 1)) rc = MC_ERR_DEVICE;
-            ctx->sync_blocks = (uint32_t)std::max(cus, 1);
-            sp.spin_limit = kBarrierSpinLimit;
+            if (g.n) ctx->last_group = (uint32_t)(&g - ctx->groups.data());
         }
         if (rc == MC_OK) {
-            // the per-chunk address tables of all slots together stay below 256 MiB (or four lists per group)
-            size_t words = 0;                    // of one slot of every group
-            for (const Group &g : ctx->groups) words += lines(g.live.size()) + lines((size_t)tiles_in(g.n) * kWavesPerBlock);
-            words = std::max<size_t>(words, 32);
-            ctx->group_slots = std::min<size_t>(std::max<size_t>(kGroupSlots, kPtrSlots / (size_t)y), std::max<size_t>(4, (size_t(256) << 20) / (words * sizeof(uintptr_t))));
-            ctx->slots.resize(ctx->group_slots * (size_t)y);
-            if (hipMalloc(&ctx->d_slots, ctx->group_slots * words * sizeof(uintptr_t)) != hipSuccess) rc = MC_ERR_ALLOC;
-            uintptr_t *at = ctx->d_slots;
-            for (size_t i = 0; i < ctx->slots.size(); ++i) {
-                const Group &g = ctx->groups[i / ctx->group_slots];
-                PtrSlot &s = ctx->slots[i];
-                s.dev = at;
-                at += lines(g.live.size());
-                s.dev_chunk = at;
-                at += lines((size_t)tiles_in(g.n) * kWavesPerBlock);
-                s.host.reserve(g.live.size());
-            }
-            ctx->want.reserve(ctx->max_live);
-            ctx->prof.pending.reserve(1024);
-            ctx->prof.pool.reserve(2048);
-        }
-        if (rc == MC_OK && many && all_tiles > 0) {
-            // lists of calls over all groups: a decompress-and-sum of the most workers needs the longest; 64 MiB in all
-            const size_t most = lines(ctx->all_live + (size_t)kMaxWorkers * y), chunks = lines(all_tiles * kWavesPerBlock);
-            ctx->all_slots.resize(std::min<size_t>(kAllSlots, std::max<size_t>(2, (size_t(64) << 20) / ((most + chunks) * sizeof(uintptr_t)))));
-            if (hipMalloc(&ctx->d_all_slots, ctx->all_slots.size() * (most + chunks) * sizeof(uintptr_t)) != hipSuccess) rc = MC_ERR_ALLOC;
-            uintptr_t *at = ctx->d_all_slots;
-            for (AllSlot &s : ctx->all_slots) {
-                s.dev = at; s.dev_chunk = at + most;
-                at += most + chunks;
-                s.host.reserve(most);
-            }
-            ctx->want_all.reserve(most);
-            ctx->spans.reserve(most);
+            // What only the calls over all groups need, foremost a scratch for every group, a context can do without: where the
+            // device has no room for it, it takes these calls one group at a time, in a scratch of the size of the largest.
+            const size_t tables = ctx->held.size();
+            const bool all = y > 1 && ctx->all_blocks[BLK_TILE] > 0, own = all && own_scratch_fits(ctx);
+            rc = set_up(ctx, all, own);
+            if (rc == MC_ERR_ALLOC && own) { give_back(ctx, tables); rc = set_up(ctx, all, false); }
+            if (rc == MC_ERR_ALLOC && all) { give_back(ctx, tables); rc = set_up(ctx, false, false); }
         }
         // the device address of the static scratch array, looked up here with the context's device current
         if (rc == MC_OK && !(ctx->static_scratch = static_scratch_for(ctx->device))) rc = MC_ERR_DEVICE;

@@ -93,3 +93,57 @@ def test_who_takes_a_limit_on_waits(host, algo):
             ctx.mc_set_barrier_spin_limit(1)
         assert e.value.status == B.MC_ERR_INVALID_ARG
     ctx.close()
+
+
+def groups_call(ctx, n):
+    """mc_compress_groups and mc_decompress_sum_groups (two workers) with buffers that do not overlap."""
+    at = 1 << 40
+    grads, states, payloads = [], [], []
+    for kind in (grads, states, payloads, payloads):
+        for _ in n:
+            kind.append(Buffer(at))
+            at += 1 << 32
+    ctx.mc_compress_groups(0, 0, grads, states, payloads[:len(n)], stream=0)
+    ctx.mc_decompress_sum_groups(payloads, 2, 1.0, grads, stream=0)
+
+
+@pytest.mark.parametrize("algo", ["topk", "randk", "dgc", "efsign"])
+def test_a_context_does_without_what_there_is_no_room_for(host, algo):
+    """A context of many groups allocates more than its calls for one group need.  Where the device has no room for that, it is
+    created all the same and takes the calls over all groups one group at a time."""
+    numel = [300000, 5] + [300000] * 14
+    y = len(numel)
+    bounds = list(range(y + 1))
+    ctx = B.Context(algo, numel, bounds)
+    most = host.nd_held()
+    groups_call(ctx, numel)
+    assert launches(host, "compress", "decompress") == [1, 1]
+    ctx.close()
+    ways, least = [], None                       # launches of a compress and a decompress, from the most to the least memory
+    for limit in range(most, 0, -most // 200):
+        host.nd_reset(limit)
+        try:
+            ctx = B.Context(algo, numel, bounds)
+        except B.McError as e:
+            assert e.status == B.MC_ERR_ALLOC and host.nd_held() == 0
+            break
+        assert host.nd_held() <= limit
+        groups_call(ctx, numel)
+        way = launches(host, "compress", "decompress")
+        if way not in ways:
+            ways.append(way)
+        least = limit
+        ctx.close()
+    if algo == "efsign":
+        assert ways == [[1, 1], [y, y]]
+    else:                                        # the sparsifiers' scratch goes first, and is most of what there is
+        assert ways == [[1, 1], [y, 1], [y, y]] and least < most // 2
+
+
+@pytest.mark.parametrize("algo", ["topk", "qsgd"])
+def test_a_context_that_cannot_be_created_gives_everything_back(host, algo):
+    for limit in (0, 100, 10000, 1 << 20):
+        host.nd_reset(limit)
+        with pytest.raises(B.McError) as e:
+            B.Context(algo, [4000000, 10], [0, 1, 2])
+        assert e.value.status == B.MC_ERR_ALLOC and host.nd_held() == 0 and host.nd_denied() > 0
