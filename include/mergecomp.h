@@ -174,9 +174,10 @@ int mc_partition_search(const int64_t *numel, const double *bwd_time, int32_t n_
  * hot calls fill, so that those allocate nothing.
  * Device memory held by a context, with T = tiles of 4096 elements of its largest group:
  *   every algorithm   24 T bytes of reduction partials; cached tensor-address lists with one 8-byte address per
- *                     1024 elements each (32 bytes per tile of the group): 32 per group, 256 in all where that is
- *                     more, 256 MiB at most in all (or four per group)
- *   more than one group   what mc_compress_groups / mc_decompress_sum_groups need to take all groups in one
+ *                     1024 elements each (32 bytes per tile): 256 of the size of the largest group, which any group
+ *                     uses, 256 MiB at most in all (or four)
+ *   more than one group   32 such lists for every group, 256 MiB at most in all (or four per group);
+ *                     what mc_compress_groups / mc_decompress_sum_groups need to take all groups in one
  *                     launch: the partials for the tiles of all groups, tables of a few bytes per tile and group,
  *                     and up to 64 address lists of whole calls (64 MiB at most in all, or two lists)
  *   sparsifiers       6 bytes per element of the largest group for candidate values and positions
@@ -185,8 +186,8 @@ int mc_partition_search(const int64_t *numel, const double *bwd_time, int32_t n_
  *                     than one group, these for every group instead of for the largest (the key list 32 KiB per tile,
  *                     at most 2 MiB), unless that is more than 2 GiB of candidates or 512 MiB of histograms or lists,
  *                     and not with a sampled threshold
- * What serves the calls over all groups only is left out where the device has no room for it; they then work group by
- * group.
+ * The groups' own lists and what serves the calls over all groups only are left out where the device has no room
+ * for them; those calls then work group by group.
  */
 int mc_ctx_create(mc_ctx **out, const mc_config *cfg, const int64_t *numel, int32_t n_tensors,
                   const int32_t *bounds, int32_t y);

@@ -17,9 +17,10 @@ namespace {
 
 constexpr uint64_t kMaxGroupElems = (1ull << 32) - (1ull << 24);
 constexpr uint32_t kBarrierSpinLimit = 1u << 21;     // polls (about a microsecond each) before a block of the slow selection routes gives up waiting
-// Cached device copies of per-call tensor address lists: per group at least kGroupSlots, in all at least kPtrSlots.  (With 256
-// for all groups together a layer-wise training step -- 161 groups, two gradients and an output each -- replaced every
-// list before it came round again, two launches more in every call.)
+// Cached device copies of per-call tensor address lists: kPtrSlots that any group takes, and with more than one group
+// kGroupSlots of each group's own.  (With the first alone a layer-wise training step -- 161 groups, two gradients and an
+// output each -- replaced every list before it came round again, two launches more in every call; with the second
+// alone so did a caller with more than 32 buffers in rotation for one of many groups.)
 constexpr int kPtrSlots = 256, kGroupSlots = 32;
 constexpr int kAllSlots = 64;            // ... and of the address lists of calls over all groups
 
@@ -35,6 +36,7 @@ struct Group {
 
 struct PtrSlot {
     uint64_t stamp = 0;                  // 0: never used
+    int32_t group = -1;
     std::vector<uintptr_t> host;
     uintptr_t *dev = nullptr;            // tensor addresses
     uintptr_t *dev_chunk = nullptr;      // per-chunk direct addresses derived from them
@@ -107,7 +109,7 @@ struct mc_ctx {
     const uint32_t *last_hint = nullptr; // the record the most recent sparse mc_compress used (mc_select_stats)
     int *d_status = nullptr;
     void *static_scratch = nullptr;     // this device's copy of the file-scope scratch array (mc_compress_static)
-    std::vector<PtrSlot> slots;         // group_slots per group, one group after the other
+    std::vector<PtrSlot> slots;         // group_slots per group, one group after the other, then those that any group takes
     size_t group_slots = 0;
     std::vector<uintptr_t> want;        // the address list of the call in progress (reserved at creation)
     // calls over all groups (contexts of more than one)
@@ -315,22 +317,27 @@ static int set_up(mc_ctx *ctx, bool all, bool own)
         sp.spin_limit = kBarrierSpinLimit;
     }
     {
-        // the per-chunk address tables of all slots together stay below 256 MiB (or four lists per group)
+        // slots that hold the list of any group: 256 MiB in all (or four), and every group's own: the same (or four each)
+        const size_t live = lines(ctx->max_live), chunks = lines(tiles * kWavesPerBlock);
         size_t words = 0;                    // of one slot of every group
         for (const Group &g : ctx->groups) words += lines(g.live.size()) + lines((size_t)tiles_in(g.n) * kWavesPerBlock);
-        words = std::max<size_t>(words, 32);
-        ctx->group_slots = std::min<size_t>(std::max<size_t>(kGroupSlots, kPtrSlots / y), std::max<size_t>(4, (size_t(256) << 20) / (words * sizeof(uintptr_t))));
-        ctx->slots.assign(ctx->group_slots * y, PtrSlot());
-        uintptr_t *at = nullptr;
-        if (!grab(ctx, &at, ctx->group_slots * words * sizeof(uintptr_t))) return MC_ERR_ALLOC;
+        auto fit = [](size_t most, size_t each) { return std::min(most, std::max<size_t>(4, (size_t(256) << 20) / (std::max<size_t>(each, 1) * sizeof(uintptr_t)))); };
+        const size_t common = fit(kPtrSlots, live + chunks);
+        uintptr_t *at = nullptr, *own_at = nullptr;
+        if (!grab(ctx, &at, common * (live + chunks) * sizeof(uintptr_t))) return MC_ERR_ALLOC;
+        ctx->group_slots = y > 1 ? fit(kGroupSlots, words) : 0;
+        if (words == 0 || !grab(ctx, &own_at, ctx->group_slots * words * sizeof(uintptr_t))) ctx->group_slots = 0;      // (no need, or no room)
+        ctx->slots.assign(ctx->group_slots * y + common, PtrSlot());
         for (size_t i = 0; i < ctx->slots.size(); ++i) {
-            const Group &g = ctx->groups[i / ctx->group_slots];
             PtrSlot &s = ctx->slots[i];
-            s.dev = at;
-            at += lines(g.live.size());
-            s.dev_chunk = at;
-            at += lines((size_t)tiles_in(g.n) * kWavesPerBlock);
-            s.host.reserve(g.live.size());
+            const bool own_slot = i < ctx->group_slots * y;
+            const Group *g = own_slot ? &ctx->groups[i / ctx->group_slots] : nullptr;
+            uintptr_t *&from = own_slot ? own_at : at;
+            s.dev = from;
+            from += g ? lines(g->live.size()) : live;
+            s.dev_chunk = from;
+            from += g ? lines((size_t)tiles_in(g->n) * kWavesPerBlock) : chunks;
+            s.host.reserve(g ? g->live.size() : ctx->max_live);
         }
         ctx->want.reserve(ctx->max_live);
         ctx->prof.pending.reserve(1024);
@@ -641,17 +648,23 @@ static GroupView group_view(mc_ctx *ctx, const LaunchCtx &lc, int32_t group, con
     want.clear();
     for (int32_t rel : g.live) want.push_back(reinterpret_cast<uintptr_t>(ptrs[rel]));
     GroupView gv{g.d_seg_off, g.d_chunk_seg, nullptr, nullptr, (uint32_t)g.live.size(), g.n, g.goff};
-    PtrSlot *const own = &ctx->slots[(size_t)group * ctx->group_slots], *victim = own;
-    for (size_t i = 0; i < ctx->group_slots; ++i) {
-        PtrSlot &s = own[i];
-        if (s.stamp && std::memcmp(s.host.data(), want.data(), want.size() * sizeof(uintptr_t)) == 0) {      // (a group's lists have one length)
-            s.stamp = ++ctx->clock;
-            gv.ptrs = s.dev;
-            gv.chunk_addr = s.dev_chunk;
-            return gv;
+    PtrSlot *victim = nullptr;                    // the one used longest ago among those that this group may take
+    auto look = [&](size_t from, size_t to) -> PtrSlot * {
+        for (PtrSlot *s = ctx->slots.data() + from; s != ctx->slots.data() + to; ++s) {
+            if (s->group == group && std::memcmp(s->host.data(), want.data(), want.size() * sizeof(uintptr_t)) == 0) return s;      // (a group's lists have one length)
+            if (!victim || s->stamp < victim->stamp) victim = s;
         }
-        if (s.stamp < victim->stamp) victim = &s;
+        return nullptr;
+    };
+    PtrSlot *hit = look((size_t)group * ctx->group_slots, ((size_t)group + 1) * ctx->group_slots);
+    if (!hit) hit = look(ctx->groups.size() * ctx->group_slots, ctx->slots.size());
+    if (hit) {
+        hit->stamp = ++ctx->clock;
+        gv.ptrs = hit->dev;
+        gv.chunk_addr = hit->dev_chunk;
+        return gv;
     }
+    victim->group = group;
     victim->stamp = ++ctx->clock;
     victim->host = want;
     gv.ptrs = victim->dev;

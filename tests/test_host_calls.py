@@ -45,6 +45,13 @@ def host(built, monkeypatch):
     """The counters; while it is in use the binding drives the library without a device."""
     monkeypatch.setattr(B, "LIB_PATH", built)
     monkeypatch.setattr(B, "_lib", None)
+    made = []
+
+    class Context(B.Context):
+        def __init__(self, *a, **k):
+            made.append(self)
+            super().__init__(*a, **k)
+    monkeypatch.setattr(B, "Context", Context)
     L = B.lib()
     L.nd_reset.argtypes = [C.c_size_t]
     L.nd_held.restype = C.c_size_t
@@ -54,6 +61,8 @@ def host(built, monkeypatch):
     L.nd_reset(NO_LIMIT)
     held = L.nd_held()
     yield L
+    for ctx in made:                             # by the library that made them, also after a test that failed
+        ctx.close()
     assert L.nd_held() == held and L.nd_bad_free() == 0          # everything a test allocated is given back
 
 
@@ -147,3 +156,23 @@ def test_a_context_that_cannot_be_created_gives_everything_back(host, algo):
         with pytest.raises(B.McError) as e:
             B.Context(algo, [4000000, 10], [0, 1, 2])
         assert e.value.status == B.MC_ERR_ALLOC and host.nd_held() == 0 and host.nd_denied() > 0
+
+
+@pytest.mark.parametrize("y,lists", [(1, 250), (2, 250), (8, 250), (161, 250), (8, 40)])
+def test_a_caller_may_rotate_many_buffers(host, y, lists):
+    """Address lists seen before are served from the context: as many as the caller's rotation of one group's buffers holds,
+    whatever the number of groups, also while every group has a few lists of its own in use."""
+    ctx = B.Context("signsgd", [5000] * y, list(range(y + 1)))
+    payload = Buffer(1 << 50)
+
+    def step(j, i):
+        ctx.mc_compress(j, 0, 0, [Buffer((1 << 40) + (j << 32) + (i << 20))], None, payload, stream=0)
+    for turn in range(3):
+        host.nd_reset(NO_LIMIT)
+        for i in range(lists):
+            step(0, i)
+        for j in range(1, y):
+            for i in range(3):
+                step(j, i)
+    assert launches(host, "upload", "expand") == [0, 0]
+    ctx.close()
