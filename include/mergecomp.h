@@ -179,7 +179,7 @@ int mc_partition_search(const int64_t *numel, const double *bwd_time, int32_t n_
  *   more than one group   32 such lists for every group, 256 MiB at most in all (or four per group);
  *                     what mc_compress_groups / mc_decompress_sum_groups need to take all groups in one
  *                     launch: the partials for the tiles of all groups, tables of a few bytes per tile and group,
- *                     and up to 64 address lists of whole calls (64 MiB at most in all, or two lists)
+ *                     and up to 256 address lists of whole calls (256 MiB at most in all, or two lists)
  *   sparsifiers       6 bytes per element of the largest group for candidate values and positions
  *                     (24576 T; 153 MB for a 25.6 M element group), 12.25 T bytes of per-tile counts, 2 MiB for the
  *                     list of keys in the threshold's histogram bin, histograms and counters of about 100 KB; with more

@@ -22,7 +22,7 @@ constexpr uint32_t kBarrierSpinLimit = 1u << 21;     // polls (about a microseco
 // output each -- replaced every list before it came round again, two launches more in every call; with the second
 // alone so did a caller with more than 32 buffers in rotation for one of many groups.)
 constexpr int kPtrSlots = 256, kGroupSlots = 32;
-constexpr int kAllSlots = 64;            // ... and of the address lists of calls over all groups
+constexpr int kAllSlots = 256;           // ... and of the address lists of calls over all groups (64 simulated workers use 65)
 
 struct Group {
     int32_t t0 = 0, t1 = 0;              // tensor range [t0, t1) of the model's list
@@ -344,9 +344,9 @@ static int set_up(mc_ctx *ctx, bool all, bool own)
         ctx->prof.pool.reserve(2048);
     }
     if (all) {
-        // lists of calls over all groups: a decompress-and-sum of the most workers needs the longest; 64 MiB in all
+        // lists of calls over all groups: a decompress-and-sum of the most workers needs the longest; 256 MiB in all
         const size_t most = lines(ctx->all_live + (size_t)kMaxWorkers * y), chunks = lines(all_tiles * kWavesPerBlock);
-        const size_t count = std::min<size_t>(kAllSlots, std::max<size_t>(2, (size_t(64) << 20) / ((most + chunks) * sizeof(uintptr_t))));
+        const size_t count = std::min<size_t>(kAllSlots, std::max<size_t>(2, (size_t(256) << 20) / ((most + chunks) * sizeof(uintptr_t))));
         uintptr_t *at = nullptr;
         if (!grab(ctx, &at, count * (most + chunks) * sizeof(uintptr_t))) return MC_ERR_ALLOC;
         ctx->all_slots.resize(count);

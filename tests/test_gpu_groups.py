@@ -95,7 +95,7 @@ def test_more_lists_than_are_kept():
     """More address lists than the context keeps, so that the oldest are replaced; and again the first ones."""
     numel, bounds = [5000, 3, 9000], [0, 1, 3]
     ctx = B.Context("signsgd", numel, bounds)
-    grads = [[torch.randn(n, device=DEV) for n in numel] for _ in range(70)]
+    grads = [[torch.randn(n, device=DEV) for n in numel] for _ in range(300)]
     pay = [torch.zeros(ctx.payload_bytes(j), dtype=torch.uint8, device=DEV) for j in range(2)]
     for g in grads + grads[:5]:
         ctx.mc_compress_groups(0, 0, g, None, pay)

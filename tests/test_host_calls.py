@@ -176,3 +176,18 @@ def test_a_caller_may_rotate_many_buffers(host, y, lists):
                 step(j, i)
     assert launches(host, "upload", "expand") == [0, 0]
     ctx.close()
+
+
+@pytest.mark.parametrize("y,lists", [(2, 65), (161, 65), (2, 200)])
+def test_calls_over_all_groups_may_rotate_many_buffers(host, y, lists):
+    """The same for the lists of whole calls: the most workers that can be decompressed, each with buffers of its own."""
+    ctx = B.Context("signsgd", [5000] * y, list(range(y + 1)))
+
+    def tensors(i):
+        return [Buffer((1 << 40) + (i << 30) + (j << 20)) for j in range(y)]
+    for turn in range(3):
+        host.nd_reset(NO_LIMIT)
+        for i in range(lists):
+            ctx.mc_compress_groups(i, 0, tensors(2 * i), None, tensors(2 * i + 1), stream=0)
+    assert launches(host, "upload", "expand_all", "expand", "compress") == [0, 0, 0, lists]
+    ctx.close()
