@@ -859,7 +859,10 @@ static int compress_all(mc_ctx *ctx, uint32_t worker, uint64_t iter, const float
     for (const Group &G : ctx->groups) for (int32_t rel : G.live) add(grads[G.t0 + rel], sizeof(float) * (size_t)ctx->tensor_numel[G.t0 + rel], 4, false);
     for (size_t j = 0; j < y; ++j) {
         if (ef) add(states[j], mc_state_bytes(ctx, (int32_t)j), 16, true);
-        else want.push_back(0);
+        else {                                   // not used, but refused if it could not be one
+            plain = plain && !(states && (reinterpret_cast<uintptr_t>(states[j]) & 15u));
+            want.push_back(0);
+        }
     }
     for (size_t j = 0; j < y; ++j) add(payloads[j], mc_payload_bytes(ctx, (int32_t)j), 16, true);
     if (!plain) return 1;

@@ -191,3 +191,26 @@ def test_calls_over_all_groups_may_rotate_many_buffers(host, y, lists):
             ctx.mc_compress_groups(i, 0, tensors(2 * i), None, tensors(2 * i + 1), stream=0)
     assert launches(host, "upload", "expand_all", "expand", "compress") == [0, 0, 0, lists]
     ctx.close()
+
+
+@pytest.mark.parametrize("algo,use_ef", [("efsign", 0), ("signsgd", 0), ("qsgd", 0), ("topk", 0), ("topk", 1), ("fp16", 1)])
+@pytest.mark.parametrize("bad", ["grad", "state", "payload"])
+@pytest.mark.parametrize("off", [None, 1, 2, 8])
+def test_the_same_arguments_are_refused_for_all_groups_as_for_one(host, algo, use_ef, bad, off):
+    """An address of one group is null or off by some bytes: the call over all groups returns what the group's own does,
+    after the groups before it.  (A state that is not used has to be aligned too, if there is one.)"""
+    y = 3
+    ctx = B.Context(algo, [5000] * y, list(range(y + 1)), use_ef=use_ef)
+    at = {kind: [(1 << 40) + (i << 36) + (j << 32) for j in range(y)] for i, kind in enumerate(("grad", "state", "payload"))}
+    at[bad][1] = at[bad][1] + off if off else 0
+    grads, states, payloads = ((C.c_void_p * y)(*at[kind]) for kind in ("grad", "state", "payload"))
+
+    def one(j):
+        return host.mc_compress(ctx._h, j, 0, 0, C.byref(grads, 8 * j), states[j], payloads[j], None)
+    alone = [one(j) for j in range(y)]
+    assert alone[0] == alone[2] == B.MC_OK
+    host.nd_reset(NO_LIMIT)
+    assert host.mc_compress_groups(ctx._h, 0, 0, grads, states, payloads, None) == alone[1]
+    if alone[1] != B.MC_OK:
+        assert alone[1] == B.MC_ERR_INVALID_ARG and launches(host, "compress") == [1]
+    ctx.close()
