@@ -125,6 +125,15 @@ _ptr_array = ptr_array
 _raw_stream = None
 
 
+def _forget_raw_stream() -> None:
+    global _raw_stream
+    _raw_stream = None
+
+
+# In a forked child torch refuses a device that the parent has initialised; only torch's own lookup says so.
+os.register_at_fork(after_in_child=_forget_raw_stream)
+
+
 def _current_stream() -> int:
     """Handle of torch's current stream on the current device.  The raw lookup takes 0.2 us where building a Stream
     object takes 3 to 4, as long as the launch that follows and half of what a small call costs the host: a one-launch
