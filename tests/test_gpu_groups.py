@@ -4,6 +4,7 @@ import numpy as np
 import pytest
 import torch
 
+from oracle import oracle as O
 from paper_2103_15195_amd import binding as B
 
 pytestmark = pytest.mark.gpu
@@ -121,3 +122,51 @@ def test_calls_go_to_the_current_stream():
     side.synchronize()
     assert bool((pay[0][128:].view(torch.float16) == 1).all()) and float(pay[1][128:].view(torch.float16)[0]) == 1.0
     assert B._current_stream() == torch.cuda.current_stream().cuda_stream
+
+
+@pytest.mark.parametrize("W", [5, 9, 17, 64])
+@pytest.mark.parametrize("algo", list(B.ALGO_IDS))
+def test_sums_of_many_workers(algo, W):
+    """More workers than the decode kernels take at a time (four; eight of one bit plane or of a sparsifier)."""
+    ctx = B.Context(algo, SIZES, list(range(len(SIZES) + 1)), ratio_ppm=20000, seed=5)
+    y, own = ctx.y, 3
+    whole, pay = buffers(ctx, ctx.payload_bytes, own)
+    _, st = buffers(ctx, ctx.state_bytes, own)
+    rng = np.random.default_rng(W)
+    for w in range(own):
+        ctx.mc_compress_groups(w, 0, tensors(rng, 10.0 ** -w, 0), st[w] if ctx.cfg.use_ef else None, pay[w])
+    order = [int(w) for w in rng.integers(0, own, W)]            # the workers' payloads are three in turn
+    out = [[torch.full((n,), 7.0, device=DEV) for n in SIZES] for _ in range(2)]
+    for j in range(y):
+        ctx.mc_decompress_sum(j, [pay[w][j] for w in order], 1.0 / W, [out[0][j]])
+    ctx.mc_decompress_sum_groups([pay[w][j] for w in order for j in range(y)], W, 1.0 / W, out[1])
+    assert all(torch.equal(a.view(torch.int32), b.view(torch.int32)) for a, b in zip(*out))
+    assert ctx.mc_last_device_status() == B.MC_OK
+
+
+@pytest.mark.parametrize("algo", ["topk", "dgc", "randk"])
+def test_groups_that_share_the_scratch(algo):
+    """More groups of 64 tiles than a context keeps key lists for (512 MiB): scratch of the size of the largest, which the
+    groups of a call use in turn."""
+    numel = [64 * 4096 - 1] * 255 + [64 * 4096, 70000, 3]
+    y = len(numel)
+    a, b = (B.Context(algo, numel, list(range(y + 1)), ratio_ppm=1000, seed=6) for _ in range(2))
+    (pa, one_p), (pb, all_p) = buffers(a, a.payload_bytes, 1), buffers(b, b.payload_bytes, 1)
+    (sa, one_s), (sb, all_s) = buffers(a, a.state_bytes, 1), buffers(b, b.state_bytes, 1)
+    a.profile_enable(True)
+    b.profile_enable(True)
+    for it in range(3):
+        g = list(torch.randn(sum(numel), device=DEV, generator=torch.Generator(DEV).manual_seed(it)).split(numel))
+        for j in range(y):
+            a.mc_compress(j, 0, it, [g[j]], one_s[0][j], one_p[0][j])
+        b.mc_compress_groups(0, it, g, all_s[0], all_p[0])
+        assert torch.equal(pa, pb) and torch.equal(sa, sb), it
+    assert a.profile_read()["lean_select"]["launches"] == b.profile_read()["lean_select"]["launches"] == 3 * y
+    # ... and the last groups against the oracle
+    cfg = O.Config(B.ALGO_IDS[algo], ratio_ppm=1000, seed=6)
+    for j in (y - 3, y - 2, y - 1):
+        held = O.new_state(cfg, numel[j])
+        for it in range(3):
+            x = torch.randn(sum(numel), device=DEV, generator=torch.Generator(DEV).manual_seed(it)).split(numel)[j].cpu().numpy()
+            want, _ = O.compress(cfg, x, held, group_off=sum(numel[:j]), worker=0, it=it)
+        assert np.array_equal(one_p[0][j].cpu().numpy()[:want.size], want), j
