@@ -34,6 +34,7 @@
 // of the tiles before its own.  On the usual route no block waits on another: every
 // dependency is a kernel boundary.
 #include <algorithm>
+#include <type_traits>
 
 #include "mc_internal.h"
 
@@ -342,14 +343,6 @@ __device__ __forceinline__ bool resolve_lds(const uint32_t *fine, uint64_t need,
     return hit != 0;
 }
 
-// the vector the selection works on: v / p kept in the state, or the gradient itself
-template <bool FROM_STATE>
-__device__ __forceinline__ void load_sel(const GroupView &g, const float *st, const Chunk &c, float (&p)[kSteps])
-{
-    if (FROM_STATE) load_flat(st, c, g.n, p, 0.0f);
-    else load_seg(g, c, p);
-}
-
 // ---------------------------------------------------------------------------
 // The candidates of one tile, walked by one wavefront in index order.  `runs`
 // holds the candidate counts of the tile's four chunks (16 bits each); the slots of
@@ -449,9 +442,7 @@ __device__ __forceinline__ TileJob my_tile(const SparseScratch &sc, uint32_t n, 
 // ---------------------------------------------------------------------------
 constexpr int kSeedThreads = 1024;
 
-template <bool FROM_STATE, bool RANDOM>
-__global__ __launch_bounds__(kSeedThreads) void sparse_seed_k(GroupView g, const float *st, uint64_t k, SparseScratch sc, RngKey rng,
-                                                              SampleRule smp)
+__global__ __launch_bounds__(kSeedThreads) void sparse_seed_k(uint32_t n, const float *v, uint64_t k, SparseScratch sc, SampleRule smp)
 {
     __shared__ uint32_t hist[kBins1];
     __shared__ __attribute__((aligned(16))) uint32_t wbins[kBinsW];
@@ -494,7 +485,7 @@ __global__ __launch_bounds__(kSeedThreads) void sparse_seed_k(GroupView g, const
     }
     // missed: the next calls filter with the full margin again, and keep it for a while
     if (blockIdx.x == 0 && t == 0) margin_after_miss(sc.hint, hint_shift, hint_cap, !found && !first_call(hint, hint_cap));
-    const uint32_t ntiles = (g.n + (uint32_t)kTile - 1u) / (uint32_t)kTile;
+    const uint32_t ntiles = (n + (uint32_t)kTile - 1u) / (uint32_t)kTile;
     const uint32_t uwave = __builtin_amdgcn_readfirstlane(wave), waves = kSeedThreads / 64;
     if (found) {
         // ---- above the window
@@ -515,30 +506,21 @@ __global__ __launch_bounds__(kSeedThreads) void sparse_seed_k(GroupView g, const
         return;
     }
     // ---- refill
-    const uint32_t nch = (g.n + (uint32_t)kChunk - 1u) / (uint32_t)kChunk;
+    const uint32_t nch = (n + (uint32_t)kChunk - 1u) / (uint32_t)kChunk;
     for (uint32_t ch = blockIdx.x * waves + uwave; ch < nch; ch += gridDim.x * waves) {
         Chunk c;
         c.base = ch * (uint32_t)kChunk;
         c.lane = lane;
-        c.full = g.n - c.base >= (uint32_t)kChunk;
-        uint32_t bits[kSteps];
-        if (RANDOM) {
-            chunk_words(rng.seed, rng.worker, rng.iter_lo, g.goff + c.base, c.lane, bits);
-#pragma unroll
-            for (int j = 0; j < kSteps; ++j) bits[j] >>= 1;
-        } else {
-            float v[kSteps];
-            load_sel<FROM_STATE>(g, st, c, v);
-#pragma unroll
-            for (int j = 0; j < kSteps; ++j) bits[j] = __float_as_uint(v[j]);
-        }
+        c.full = n - c.base >= (uint32_t)kChunk;
+        float x[kSteps];
+        load_flat(v, c, n, x, 0.0f);
 #pragma unroll
         for (int j = 0; j < kSteps; ++j) {
             uint32_t i = c.base + 64 * j + c.lane;
-            if (c.full || i < g.n) {
-                sc.cand_bits[i] = bits[j];
+            if (c.full || i < n) {
+                sc.cand_bits[i] = __float_as_uint(x[j]);
                 sc.cand_loc[i] = (uint16_t)(64 * j + c.lane);
-                if (in_sample(smp, i)) atomicAdd(&hist[(bits[j] & 0x7FFFFFFFu) >> 20], 1u);
+                if (in_sample(smp, i)) atomicAdd(&hist[key_of(x[j]) >> 20], 1u);
             }
         }
     }
@@ -701,47 +683,18 @@ __device__ __forceinline__ void record_sent_key(float *st, uint32_t T)
         reinterpret_cast<StateHeader *>(reinterpret_cast<uint8_t *>(st) - kHeaderBytes)->sent_key = ALGO == MC_ALGO_RANDK ? 0xFFFFFFFFu : T;
 }
 
-// The walk of one tile's candidates that both emit kernels share: gt_before / eq_before are the numbers of keys
-// above / equal to T among all candidates before this tile.
-template <int ALGO, bool EF>
-__device__ __forceinline__ void emit_tile(const SparseScratch &sc, uint32_t tile, uint64_t runs, uint32_t n, uint64_t k, float *st,
-                                          uint32_t *idx, float *val, uint32_t T, uint64_t need, uint64_t gt_before, uint64_t eq_before)
-{
-    tile_walk<true>(sc, tile, runs, [&](bool valid, uint32_t chunk, uint32_t b, uint32_t loc) {
-        const uint32_t key = b & 0x7FFFFFFFu;
-        const bool is_gt = valid && key > T, is_eq = valid && key == T;
-        const uint64_t bgt = __builtin_amdgcn_ballot_w64(is_gt), beq = __builtin_amdgcn_ballot_w64(is_eq);
-        const uint64_t gtb = gt_before + lanes_below(bgt), eqb = eq_before + lanes_below(beq);
-        if (is_gt || (is_eq && eqb < need)) {
-            const uint64_t pos = gtb + (eqb < need ? eqb : need);
-            const uint32_t i = chunk * (uint32_t)kChunk + loc;
-            if (pos < k && i < n) {                  // exact selection: always true for consistent scratch; CAPPED: room left
-                idx[pos] = i;
-                if (ALGO == MC_ALGO_RANDK) val[pos] = st[i];      // the candidate slot holds the random key: the value is p
-                else val[pos] = __uint_as_float(b);
-                if (ALGO == MC_ALGO_DGC) { st[i] = 0.0f; st[dgc_u_offset(n) + i] = 0.0f; }   // momentum factor masking
-                else if (EF) st[i] = 0.0f;
-            }
-        }
-        gt_before += __popcll(bgt);
-        eq_before += __popcll(beq);
-    });
-}
-
-// CAPPED (DGC with a sampled threshold): T comes from the sample, so the number of keys >= T varies.
-// k is then the payload's capacity: all keys above T are kept in index order while there is room, then
+// DGC with a sampled threshold: T comes from the sample, so the number of keys >= T varies.
+// cap is the payload's capacity: all keys above T are kept in index order while there is room, then
 // keys equal to T; the header records how many entries were kept and unused entries are zeroed.
-template <int ALGO, bool EF, bool CAPPED>
-__global__ __launch_bounds__(kBlock) void cand_emit_k(uint32_t n, uint32_t ntiles, float *st, PayloadHeader *hdr, uint64_t k,
+__global__ __launch_bounds__(kBlock) void cand_emit_k(uint32_t n, uint32_t ntiles, float *st, PayloadHeader *hdr, uint64_t cap,
                                                       SparseScratch sc)
 {
     __shared__ uint64_t sgt[kWavesPerBlock], seq[kWavesPerBlock], stg[kWavesPerBlock], ste[kWavesPerBlock];
     TileJob job = my_tile(sc, n, ntiles);
     const SelectState s3 = sc.sel[3];
     const uint32_t T = s3.lo;
-    uint64_t need = s3.need;
     uint32_t *idx = reinterpret_cast<uint32_t *>(reinterpret_cast<uint8_t *>(hdr) + kHeaderBytes);
-    float *val = reinterpret_cast<float *>(idx + k);
+    float *val = reinterpret_cast<float *>(idx + cap);
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t lane = threadIdx.x & 63u;
     // kept-before of this wavefront inside the block
@@ -750,22 +703,20 @@ __global__ __launch_bounds__(kBlock) void cand_emit_k(uint32_t n, uint32_t ntile
         const uint32_t x = sc.tile_cnt[blockIdx.x * kWavesPerBlock + lane];
         wg = x & 0xFFFFu; we = x >> 16;
     }
-    // kept-before of this block: sum over the blocks before it (CAPPED: and over all blocks), eight loads in
-    // flight per thread
+    // kept-before of this block: sum over the blocks before it, and over all blocks, eight loads in flight per thread
     uint64_t ag = 0, ae = 0, tg = 0, te = 0;
-    const uint32_t upto = CAPPED ? gridDim.x : blockIdx.x;
-    for (uint32_t b0 = 0; b0 < upto; b0 += 8 * kBlock) {
+    for (uint32_t b0 = 0; b0 < gridDim.x; b0 += 8 * kBlock) {
         uint32_t x[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
             const uint32_t b = b0 + u * kBlock + threadIdx.x;
-            x[u] = b < upto ? sc.blk_cnt[b] : 0u;
+            x[u] = b < gridDim.x ? sc.blk_cnt[b] : 0u;
         }
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
             const uint32_t b = b0 + u * kBlock + threadIdx.x;
             if (b < blockIdx.x) { ag += x[u] & 0xFFFFu; ae += x[u] >> 16; }
-            if (CAPPED) { tg += x[u] & 0xFFFFu; te += x[u] >> 16; }
+            tg += x[u] & 0xFFFFu; te += x[u] >> 16;
         }
     }
     if (blockIdx.x == 0)
@@ -774,40 +725,52 @@ __global__ __launch_bounds__(kBlock) void cand_emit_k(uint32_t n, uint32_t ntile
     for (int m = 32; m >= 1; m >>= 1) {
         ag += __shfl_xor(ag, m, 64); ae += __shfl_xor(ae, m, 64);
         wg += __shfl_xor(wg, m, 64); we += __shfl_xor(we, m, 64);
-        if (CAPPED) { tg += __shfl_xor(tg, m, 64); te += __shfl_xor(te, m, 64); }
+        tg += __shfl_xor(tg, m, 64); te += __shfl_xor(te, m, 64);
     }
     if (lane == 0) { sgt[wave] = ag; seq[wave] = ae; stg[wave] = tg; ste[wave] = te; }
     __syncthreads();
     uint64_t gt_before = (sgt[0] + sgt[1]) + (sgt[2] + sgt[3]) + wg;
     uint64_t eq_before = (seq[0] + seq[1]) + (seq[2] + seq[3]) + we;
-    uint64_t kept = k;
-    if (CAPPED) {
-        const uint64_t all_gt = (stg[0] + stg[1]) + (stg[2] + stg[3]), all_eq = (ste[0] + ste[1]) + (ste[2] + ste[3]);
-        const uint64_t kept_gt = all_gt < k ? all_gt : k;
-        need = all_eq < k - kept_gt ? all_eq : k - kept_gt;
-        kept = kept_gt + need;
-        // entries of the payload that stay unused are zero
-        for (uint64_t pos = kept + (uint64_t)blockIdx.x * kBlock + threadIdx.x; pos < k; pos += (uint64_t)gridDim.x * kBlock) {
-            idx[pos] = 0u;
-            val[pos] = 0.0f;
-        }
+    const uint64_t all_gt = (stg[0] + stg[1]) + (stg[2] + stg[3]), all_eq = (ste[0] + ste[1]) + (ste[2] + ste[3]);
+    const uint64_t kept_gt = all_gt < cap ? all_gt : cap, need = all_eq < cap - kept_gt ? all_eq : cap - kept_gt, kept = kept_gt + need;
+    // entries of the payload that stay unused are zero
+    for (uint64_t pos = kept + (uint64_t)blockIdx.x * kBlock + threadIdx.x; pos < cap; pos += (uint64_t)gridDim.x * kBlock) {
+        idx[pos] = 0u;
+        val[pos] = 0.0f;
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         PayloadHeader h;
-        h.magic = kMagic; h.algo = ALGO; h.n = n; h.k = kept; h.scale = 0.0f; h.levels = CAPPED ? (uint32_t)k : 0u;
+        h.magic = kMagic; h.algo = MC_ALGO_DGC; h.n = n; h.k = kept; h.scale = 0.0f; h.levels = (uint32_t)cap;
         for (int i = 0; i < 24; ++i) h.pad[i] = 0;
         *hdr = h;
         // this kernel zeroes what it keeps in place: the next streaming pass has nothing to mask
-        if (ALGO == MC_ALGO_DGC || EF) reinterpret_cast<StateHeader *>(reinterpret_cast<uint8_t *>(st) - kHeaderBytes)->sent_key = 0xFFFFFFFFu;
+        reinterpret_cast<StateHeader *>(reinterpret_cast<uint8_t *>(st) - kHeaderBytes)->sent_key = 0xFFFFFFFFu;
     }
     if (s3.mode & kModeUniform) job.runs = job.tile < ntiles ? uniform_runs(job.tile, n) : 0ull;
     if (lane == 0 && job.tile < ntiles) {
-        uint32_t *dir = payload_directory(hdr, k);
-        const uint64_t at = gt_before + (eq_before < need ? eq_before : need);      // CAPPED: there may be no room for all of them
+        uint32_t *dir = payload_directory(hdr, cap);
+        const uint64_t at = gt_before + (eq_before < need ? eq_before : need);      // (there may be no room for all of them)
         dir[job.tile] = (uint32_t)(at < kept ? at : kept);
         if (job.tile == ntiles - 1u) dir[ntiles] = (uint32_t)kept;
     }
-    emit_tile<ALGO, EF>(sc, job.tile, job.runs, n, k, st, idx, val, T, need, gt_before, eq_before);
+    // the tile's candidates: gt_before / eq_before are the numbers of keys above / equal to T among all candidates before them
+    tile_walk<true>(sc, job.tile, job.runs, [&](bool valid, uint32_t chunk, uint32_t b, uint32_t loc) {
+        const uint32_t key = b & 0x7FFFFFFFu;
+        const bool is_gt = valid && key > T, is_eq = valid && key == T;
+        const uint64_t bgt = __builtin_amdgcn_ballot_w64(is_gt), beq = __builtin_amdgcn_ballot_w64(is_eq);
+        const uint64_t gtb = gt_before + lanes_below(bgt), eqb = eq_before + lanes_below(beq);
+        if (is_gt || (is_eq && eqb < need)) {
+            const uint64_t pos = gtb + (eqb < need ? eqb : need);
+            const uint32_t i = chunk * (uint32_t)kChunk + loc;
+            if (pos < cap && i < n) {                // while there is room
+                idx[pos] = i;
+                val[pos] = __uint_as_float(b);
+                st[i] = 0.0f; st[dgc_u_offset(n) + i] = 0.0f;      // momentum factor masking
+            }
+        }
+        gt_before += __popcll(bgt);
+        eq_before += __popcll(beq);
+    });
 }
 
 // ---------------------------------------------------------------------------
@@ -1712,7 +1675,7 @@ static void sampled_dgc(const LaunchCtx &lc, const OneSparse &src, const SparseC
     MC_LAUNCH((sparse_accum_k<MC_ALGO_DGC, true, OneSparse>), dim3(nt), block, lc, src, call.momentum, rng, smp);
     prof_end(lc, K_SPARSE_ACCUM);
     prof_begin(lc, K_SPARSE_SEED);
-    MC_LAUNCH((sparse_seed_k<true, false>), dim3(sblocks), dim3(kSeedThreads), lc, g, src.st, call.sample_need, sc, rng, smp);
+    MC_LAUNCH(sparse_seed_k, dim3(sblocks), dim3(kSeedThreads), lc, g.n, src.st, call.sample_need, sc, smp);
     prof_end(lc, K_SPARSE_SEED);
     prof_begin(lc, K_CAND_HIST2);
     MC_LAUNCH(cand_hist_k<2>, cgrid, block, lc, g.n, nt, sc, smp);
@@ -1724,17 +1687,17 @@ static void sampled_dgc(const LaunchCtx &lc, const OneSparse &src, const SparseC
     MC_LAUNCH(cand_count_k, cgrid, block, lc, g.n, nt, sc);
     prof_end(lc, K_CAND_COUNT);
     prof_begin(lc, K_CAND_EMIT);
-    MC_LAUNCH((cand_emit_k<MC_ALGO_DGC, true, true>), cgrid, block, lc, g.n, nt, src.st, src.hdr, src.k, sc);
+    MC_LAUNCH(cand_emit_k, cgrid, block, lc, g.n, nt, src.st, src.hdr, src.k, sc);
     prof_end(lc, K_CAND_EMIT);
 }
-static void sampled_dgc(const LaunchCtx &, const AllSparse &, const SparseCall &) {}      // (never asked for: the sampled threshold is taken group by group)
 
 template <class SRC>
 void launch_sparse_compress(const LaunchCtx &lc, int algo, const SRC &src, const SparseBlocks &nb, bool ef, const SparseCall &call)
 {
     if (nb.tiles == 0) return;
-    if (algo == MC_ALGO_DGC && call.sample_stride) sampled_dgc(lc, src, call);
-    else if (algo == MC_ALGO_DGC) sparse_compress_t<MC_ALGO_DGC, true>(lc, src, nb, call);
+    // (the sampled threshold is taken group by group: compress_all never asks for it)
+    if constexpr (std::is_same_v<SRC, OneSparse>) if (algo == MC_ALGO_DGC && call.sample_stride) { sampled_dgc(lc, src, call); return; }
+    if (algo == MC_ALGO_DGC) sparse_compress_t<MC_ALGO_DGC, true>(lc, src, nb, call);
     else if (algo == MC_ALGO_RANDK) sparse_compress_t<MC_ALGO_RANDK, true>(lc, src, nb, call);
     else if (ef) sparse_compress_t<MC_ALGO_TOPK, true>(lc, src, nb, call);
     else sparse_compress_t<MC_ALGO_TOPK, false>(lc, src, nb, call);
