@@ -137,7 +137,7 @@ os.register_at_fork(after_in_child=_forget_raw_stream)
 def _current_stream() -> int:
     """Handle of torch's current stream on the current device.  The raw lookup takes 0.2 us where building a Stream
     object takes 3 to 4, as long as the launch that follows and half of what a small call costs the host: a one-launch
-    decompress-and-sum 8.8 -> 5.0 us."""
+    decompress-and-sum 8.8 -> 4.6 us."""
     global _raw_stream
     if _raw_stream is None:
         import torch

@@ -6,7 +6,7 @@
 // All kernels are HBM-streaming: each operand is touched once per pass with
 // lane-consecutive 4-byte accesses (256 contiguous bytes per wave instruction),
 // sign / ternary planes are packed with 64-lane ballots, group scalars are
-// reduced per block in LDS and combined by a one-block finalize kernel.
+// reduced per block in LDS and combined by a one-block finalize kernel (in groups of at most 64 tiles by the kernel itself).
 #include <cstddef>
 
 #include "mc_internal.h"

@@ -14,17 +14,17 @@
 //                group) is copied, in index order, into the candidate slots of its
 //                1024-element chunk, and counted in a *window* histogram: 2048 bins of
 //                2048 keys each, starting at the hint (the last bin also takes all above)
-//   seed         reads the window.  Usual case: the k-th largest key falls in one of its
-//                bins, which leaves 11 bits to resolve (fast mode).  Otherwise all blocks
-//                build a level-1 histogram (top 11 bits of key - lo) of the candidates
-//                above the window, or, if the hint left fewer than k candidates (first
-//                call, or the distribution moved down), of every element (refill)
-//   hist 2       only after a seed that was not fast: bits 19..10 of key - lo
-//   hist 3       the bits still open (11 after a fast seed, else 10)
-//   count        resolves level 3 (threshold key T, number of keys == T to take),
-//                counts kept candidates per tile, publishes the next hint
-//   emit         ordered compaction of the kept candidates into (idx, val); kept
-//                entries leave the residual
+//   select       every block reads the window.  Usual case: the k-th largest key falls in one
+//                of its bins; candidates above that bin are counted, the few inside it
+//                listed.  Otherwise (the threshold left the window, a bin of very many
+//                equal keys, a first call) the group's first blocks finish the selection
+//                and the payload themselves, with grid-wide barriers between the steps
+//   emit         usual case: the threshold key T and the number of keys == T to take from
+//                the list; ordered compaction of the kept candidates into (idx, val)
+//
+// DGC with a threshold from a sample has a payload of varying length and keeps a kernel per step: seed (reads the
+// window; where that does not settle it, level 1 of a radix select), two kernels for levels 2 and 3, count (kept candidates
+// per tile), emit.
 //
 // If at least k elements have key >= hint, the k-th largest key T is >= hint, so
 // every element with key >= T is a candidate and the result is exact whatever the
@@ -48,18 +48,18 @@ constexpr int kBinsW = 2048, kBins1 = 2048, kBins2 = 1024, kBins3 = 1 << kWindow
 // atomics on one address serialise (tens of nanoseconds each on this part), so only
 // the bins themselves are updated -- no shared summary counters -- and a level is
 // resolved by a wavefront that reads all its bins.
-// The window histogram is kept in kWinCopies copies, a block adding to the copy of its index, and the seed sums
-// them.  The flush of the streaming pass is one multi-lane add per block and 128-byte line of bins, and adds to one
+// The window histogram is kept in kWinCopies copies, a block adding to the copy of its index, and the select
+// kernel sums them.  The flush of the streaming pass is one multi-lane add per block and 128-byte line of bins, and adds to one
 // line queue up behind each other (about 5 ns each): when the candidates are spread evenly over the tiles, every
 // block holds some of nearly every bin between the hint and the threshold, and with a single copy the pass took
 // 132 us instead of 54 (all tensors of one scale).  One bin per line was tried first (62 us, but the adds of a wave
-// no longer coalesce: +2..4 us on clustered candidates and a 2048-line gather in the seed); copies keep the adds
+// no longer coalesce: +2..4 us on clustered candidates and a 2048-line gather in the select kernel); copies keep the adds
 // coalesced.  Measured, Top-k compress on clustered / evenly spread candidates: 2 copies 87.6 / 125.6 us, 4 copies
-// 88.4 / 97.5, 8 copies 89.7 / 99.0, 16 copies 93.3 / 101.7, 32 copies 106 / 114 (the seed reads them all).
+// 88.4 / 97.5, 8 copies 89.7 / 99.0, 16 copies 93.3 / 101.7, 32 copies 106 / 114 (the select kernel reads them all).
 constexpr int kHistW = 0, kHist1 = kHistW + kBinsW * kWinCopies, kHist2 = kHist1 + kBins1, kHist3 = kHist2 + kBins2;
 // The window's open last bin takes a count from nearly every block (all keys above the window), and
 // adds from thousands of blocks to one address queue up behind each other for tens of microseconds:
-// its count is spread over kOpenCopies words, chosen by the block index, which the seed sums.
+// its count is spread over kOpenCopies words, chosen by the block index, which the select kernel sums.
 constexpr int kOpenCopies = 64, kHistOpen = kHist3 + kBins3;
 static_assert(kHistOpen + kOpenCopies == kHistWords, "histogram scratch layout");
 constexpr uint32_t kHintMargin = 3u << 19;   // 3/16 of an octave below the last threshold
@@ -1511,7 +1511,7 @@ __global__ __launch_bounds__(kEmitThreads) void lean_emit_k(SRC src)
     if (t <= (uint32_t)kEmitWaves) { cgt[t] = 0u; ceq[t] = 0u; }
     __syncthreads();
     const uint32_t spec_n = ulen[t / 4u] > (t % 4u) * kUPer ? min(ulen[t / 4u] - (t % 4u) * kUPer, (uint32_t)kUPer) : 0u;      // of spec[], this many exist
-    const uint32_t more = min(upre[kUSub], kUCap);       // (nothing, when no sublist holds more than four entries)
+    const uint32_t more = min(upre[kUSub], kUCap);       // (nothing, when no sublist holds more than kUSpec entries)
     // further entry e: entry kUSpec + (e - upre[s]) of the sublist s that is the last to start at or before e
     auto further = [&](uint32_t e) {
         uint32_t sl = 0;
@@ -1716,7 +1716,7 @@ template void launch_sparse_compress<AllSparse>(const LaunchCtx &, int, const Al
 // tables before this one could start: 5 of 38 us.)
 // ---------------------------------------------------------------------------
 constexpr int kSparseBatch = 8;    // workers whose entries are in flight together
-// rounds of 256 entries per worker fetched up front (with 4 the kernel needs 74 vector registers and 6 wavefronts
+// rounds of 256 entries per worker and tile fetched up front (with 4 the kernel needs 74 vector registers and 6 wavefronts
 // fit a SIMD; with 3, 58 and 8: measured 0.7 .. 1.9 us faster, 2 rounds no better)
 constexpr int kSparseRounds = 3;
 
@@ -1859,7 +1859,7 @@ __global__ __launch_bounds__(kBlock) void sparse_decompress_k(int algo, SRC src,
                     const uint32_t local = ix[b][r] - tb;
                     if (ix[b][r] != 0xFFFFFFFFu && local < (uint32_t)kTile) acc[local] = acc[local] + vv[b][r];
                 }
-                // more than 1024 entries of one worker in the tile
+                // more than 768 entries of one worker in the tile
                 const uint32_t *idx = reinterpret_cast<const uint32_t *>(job.payload(w0 + b) + kHeaderBytes);
                 const float *val = reinterpret_cast<const float *>(idx + k);
                 for (uint32_t e = lo[b] + kSparseRounds * kBlock + t; e < hi[b]; e += kBlock) {
