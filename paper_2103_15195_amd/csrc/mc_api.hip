@@ -326,7 +326,8 @@ static int set_up(mc_ctx *ctx, bool all, bool own)
         uintptr_t *at = nullptr, *own_at = nullptr;
         if (!grab(ctx, &at, common * (live + chunks) * sizeof(uintptr_t))) return MC_ERR_ALLOC;
         ctx->group_slots = y > 1 ? fit(kGroupSlots, words) : 0;
-        if (words == 0 || !grab(ctx, &own_at, ctx->group_slots * words * sizeof(uintptr_t))) ctx->group_slots = 0;      // (no need, or no room)
+        const size_t own_bytes = ctx->group_slots * words * sizeof(uintptr_t);
+        if (own_bytes == 0 || !grab(ctx, &own_at, own_bytes)) ctx->group_slots = 0;      // (no need, or no room)
         ctx->slots.assign(ctx->group_slots * y + common, PtrSlot());
         for (size_t i = 0; i < ctx->slots.size(); ++i) {
             PtrSlot &s = ctx->slots[i];
