@@ -722,8 +722,8 @@ template void launch_tern_encode<AllCompress>(const LaunchCtx &, const AllCompre
 // 0.03 us a call; the encode written out a second time for it 0.25 with TernGrad.)
 // ---------------------------------------------------------------------------
 // One thread of a block that gives up: the tiles it still has to encode (its own, or none).  The last block looks at the word
-// after its own arrival, and takes it if it is not 0, so if the count is not complete after the hand-over, the tile will be found; if it is, the tile is
-// taken back unless the last block was faster.  Either way the word is 0 when all blocks have left.
+// after its own arrival, and takes it if it is not 0: if the count is not complete after the hand-over, the tile will be
+// found; if it is, the tile is taken back unless the last block was faster.  Either way the word is 0 when all have left.
 __device__ __forceinline__ uint64_t hand_over(const CompressJob &job, uint64_t all)
 {
     const uint64_t bit = 1ull << job.tile;
