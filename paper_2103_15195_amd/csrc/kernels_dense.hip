@@ -896,11 +896,6 @@ template void launch_fp16_compress<AllCompress>(const LaunchCtx &, const AllComp
 // pass, every payload read once, the dense result written once through the
 // segment table.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ void check_header(const PayloadHeader *h, uint32_t algo, uint32_t n, int *status)
-{
-    if (h->magic != kMagic || h->algo != algo || h->n != (uint64_t)n) raise_flag(status, FLAG_PAYLOAD);
-}
-
 // Workers are taken in batches: all loads of a batch (header scalars and codes)
 // are issued before the first is used, so a wavefront pays the HBM latency once
 // per batch instead of once per worker.
@@ -918,11 +913,10 @@ __global__ __launch_bounds__(kBlock) void dense_decompress_k(SRC src, int W, flo
 {
     static_assert(ALGO == MC_ALGO_QSGD || ALGO == MC_ALGO_FP16, "one code per element");
     constexpr int kBatch = 4;
+    if (blockIdx.x == 0) { src.check({ALGO, false, false}, W, status); return; }
     const auto job = src.template job<BLK_TILE>();
     const GroupView &out = job.out;
     const Chunk c = my_chunk(out.n, job.block);
-    if (job.block == job.last && (int)threadIdx.x < W)
-        check_header(reinterpret_cast<const PayloadHeader *>(job.payload_of_lane(threadIdx.x)), ALGO, out.n, status);
     if (c.base >= out.n) return;
     const uintptr_t entry = chunk_entry(out, c);
     if (ALGO == MC_ALGO_QSGD && !(entry & 15u)) {               // an address (even), and 16-byte aligned
@@ -936,17 +930,22 @@ __global__ __launch_bounds__(kBlock) void dense_decompress_k(SRC src, int W, flo
 #pragma unroll
             for (int e = 0; e < 4; ++e) acc[m][e] = 0.0f;
         for (int w0 = 0; w0 < W; w0 += kBatch) {
+            const uint8_t *pl[kBatch];
+            job.template payloads<kBatch>(w0, W, pl);
             float scale[kBatch];
 #pragma unroll
-            for (int b = 0; b < kBatch; ++b)
-                scale[b] = w0 + b < W ? ld_uniform(&reinterpret_cast<const PayloadHeader *>(job.payload(w0 + b))->scale) : 0.0f;
+            for (int b = 0; b < kBatch; ++b) {
+            scale[b] = 0.0f;
+            if (w0 + b < W) scale[b] = ld_uniform(&reinterpret_cast<const PayloadHeader *>(pl[b])->scale);
+        }
             uint32_t cw[kBatch][4];
 #pragma unroll
             for (int b = 0; b < kBatch; ++b) {
-                const uint8_t *codes = job.payload(w0 + b < W ? w0 + b : 0) + kHeaderBytes + c.base;
+                const global_ptr<const uint8_t> codes = in_global(pl[b]) + kHeaderBytes + c.base;
 #pragma unroll
-                for (int m = 0; m < 4; ++m) cw[b][m] = w0 + b < W ? ld_stream(reinterpret_cast<const uint32_t *>(codes + at[m])) : 0u;
+                for (int m = 0; m < 4; ++m) cw[b][m] = w0 + b < W ? __builtin_nontemporal_load((global_ptr<const uint32_t>)(codes + at[m])) : 0u;
             }
+            hold(scale);
 #pragma unroll
             for (int b = 0; b < kBatch; ++b) {
                 if (w0 + b < W) {
@@ -958,11 +957,11 @@ __global__ __launch_bounds__(kBlock) void dense_decompress_k(SRC src, int W, flo
                 }
             }
         }
-        float *p = reinterpret_cast<float *>(entry);
+        const global_ptr<float> p = in_global(reinterpret_cast<float *>(entry));
 #pragma unroll
         for (int m = 0; m < 4; ++m) {
             float4v v = {alpha * acc[m][0], alpha * acc[m][1], alpha * acc[m][2], alpha * acc[m][3]};
-            __builtin_nontemporal_store(v, reinterpret_cast<float4v *>(p + at[m]));
+            __builtin_nontemporal_store(v, (global_ptr<float4v>)(p + at[m]));
         }
         return;
     }
@@ -970,16 +969,21 @@ __global__ __launch_bounds__(kBlock) void dense_decompress_k(SRC src, int W, flo
 #pragma unroll
     for (int j = 0; j < kSteps; ++j) acc[j] = 0.0f;
     for (int w0 = 0; w0 < W; w0 += kBatch) {
+        const uint8_t *pl[kBatch];
+        job.template payloads<kBatch>(w0, W, pl);
         float scale[kBatch];
 #pragma unroll
-        for (int b = 0; b < kBatch; ++b)
-            scale[b] = w0 + b < W ? ld_uniform(&reinterpret_cast<const PayloadHeader *>(job.payload(w0 + b))->scale) : 0.0f;
+        for (int b = 0; b < kBatch; ++b) {
+            scale[b] = 0.0f;
+            if (w0 + b < W) scale[b] = ld_uniform(&reinterpret_cast<const PayloadHeader *>(pl[b])->scale);
+        }
         if (ALGO == MC_ALGO_QSGD) {
             int8_t cd[kBatch][kSteps];
 #pragma unroll
             for (int b = 0; b < kBatch; ++b) {
-                if (w0 + b < W) load_flat<int8_t>(reinterpret_cast<const int8_t *>(job.payload(w0 + b) + kHeaderBytes), c, out.n, cd[b], (int8_t)0);
+                if (w0 + b < W) load_flat<int8_t>(reinterpret_cast<const int8_t *>(pl[b] + kHeaderBytes), c, out.n, cd[b], (int8_t)0);
             }
+            hold(scale);
 #pragma unroll
             for (int b = 0; b < kBatch; ++b) {
                 if (w0 + b < W) {
@@ -992,7 +996,7 @@ __global__ __launch_bounds__(kBlock) void dense_decompress_k(SRC src, int W, flo
             _Float16 hv[kBatch][kSteps];
 #pragma unroll
             for (int b = 0; b < kBatch; ++b) {
-                if (w0 + b < W) load_flat<_Float16>(reinterpret_cast<const _Float16 *>(job.payload(w0 + b) + kHeaderBytes), c, out.n, hv[b], (_Float16)0.0f);
+                if (w0 + b < W) load_flat<_Float16>(reinterpret_cast<const _Float16 *>(pl[b] + kHeaderBytes), c, out.n, hv[b], (_Float16)0.0f);
             }
 #pragma unroll
             for (int b = 0; b < kBatch; ++b) {
@@ -1031,6 +1035,7 @@ __device__ __forceinline__ uint64_t transpose8x8(uint64_t x)
     return x;
 }
 
+constexpr int kPlaneBatch = 8;                             // workers whose planes are asked for together
 constexpr int kSignWaveElems = 2048;                       // 64 lanes x 32 elements
 constexpr int kSignTile = kSignWaveElems * kWavesPerBlock; // 8192 elements per block
 static_assert(kSignTile == 2 * kTile, "blocks of the bit-plane decode (BLK_PLANE)");
@@ -1045,19 +1050,13 @@ __device__ __forceinline__ uint64_t gather_transpose(const uint32_t (&wd)[8], in
     return transpose8x8((uint64_t)lo | ((uint64_t)hi << 32));
 }
 
-// TERN = false: the one-plane schemes (2^8 sums of the first 8 workers' +-level).  TERN = true: TernGrad
-// (non-zero and negative planes; a worker contributes 0, +s or -s): the table holds the 2^8 possible sums
-// of workers 0..3, indexed by their four non-zero and four negative bits, and workers 4..7 are added one
-// by one, so that every element sees the sequence of fp32 additions ((0 + d_0) + d_1) + ... of a plain
-// loop.  (A table of all 3^8 sums of 8 workers needs 26 KB of LDS per block and a kernel of its own to
-// fill it, and measured slower; a second table over workers 0..5, 4096 entries filled from the first,
-// 35.5 against 36.0 us.)
+// TERN = false: the one-plane schemes (2^8 sums of the first 8 workers' +-level).  TERN = true: TernGrad (non-zero and
+// negative planes; a worker contributes 0, +s or -s): no table, every worker is added by itself (add_terns).
 // what a set / clear bit of worker w decodes to (one-plane schemes)
-__device__ __forceinline__ void plane_levels(const PayloadHeader *h, int kind, float &hi, float &lo)
+__device__ __forceinline__ void plane_levels(float scale, float scale_lo, int kind, float &hi, float &lo)
 {
-    // (scalar loads: as vector loads they queue behind the compute unit's stores, and every block waits for them)
-    hi = kind == PLANE_VOTE ? 1.0f : ld_uniform(&h->scale);
-    lo = kind == PLANE_MEANS ? __uint_as_float(ld_uniform(&h->pad[0])) : -hi;
+    hi = kind == PLANE_VOTE ? 1.0f : scale;
+    lo = kind == PLANE_MEANS ? scale_lo : -hi;
 }
 __device__ __forceinline__ float vote_of(float tally) { return tally > 0.0f ? 1.0f : (tally < 0.0f ? -1.0f : 0.0f); }
 
@@ -1083,106 +1082,138 @@ __device__ __forceinline__ float plane_term(uint32_t word, int e, float hi, floa
     return __uint_as_float((__float_as_uint(hi) & m) | (__float_as_uint(lo) & ~m));
 }
 
+// A worker's word added to the sums of its 32 elements.  Where the two levels are +s and -s, bits e and e + 16 are made the
+// signs of two halves +-1.0 (a shift and one three-input bit operation for both), and each sum is one mixed-precision
+// multiply-add, half x float + float: the product +-s is exact, so the one rounding is that of the addition.  (s goes to a
+// vector register: an operand from a scalar one makes most vector instructions take twice the cycles on this part.)
+typedef _Float16 half2v __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ void add_signs(float (&acc)[32], uint32_t word, float s)
+{
+    asm("" : "+v"(s));
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+        const half2v h = __builtin_bit_cast(half2v, (~(word << (15 - e)) & 0x80008000u) | 0x3C003C00u);
+        acc[e] = __builtin_fmaf((float)h.x, s, acc[e]);
+        acc[e + 16] = __builtin_fmaf((float)h.y, s, acc[e + 16]);
+    }
+}
+// TernGrad's two words the same way: the half of an element is its non-zero bit as bit 14 -- 2.0, or 0 -- and its negative
+// bit as the sign, multiplied by s / 2.  The bits of even elements are laid next to each other in one word, those of odd ones
+// in another, so that here too one shift and one mask make two halves.
+__device__ __forceinline__ void add_terns(float (&acc)[32], uint32_t nz, uint32_t ng, float half_s)
+{
+    asm("" : "+v"(half_s));
+    const uint32_t even = (nz & 0x55555555u) | ((ng << 1) & 0xAAAAAAAAu), odd = ((nz >> 1) & 0x55555555u) | (ng & 0xAAAAAAAAu);
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+        const half2v h = __builtin_bit_cast(half2v, (e & 1 ? odd << (15 - e) : even << (14 - e)) & 0xC000C000u);
+        acc[e] = __builtin_fmaf((float)h.x, half_s, acc[e]);
+        acc[e + 16] = __builtin_fmaf((float)h.y, half_s, acc[e + 16]);
+    }
+}
+// Whether that gives what an addition of 0, +s or -s gives: s / 2 has to be exact, and 0 times it has to be 0.
+__device__ __forceinline__ bool halves_exactly(float s) { return 0.5f * s + 0.5f * s == s && fabsf(s) < __builtin_inff(); }
+
 template <bool TERN, class SRC>
 __global__ __launch_bounds__(kBlock) void plane_decompress_k(SRC src, int W, float alpha, int *status, int algo, int kind)
 {
-    __shared__ float table[256];
+    __shared__ float table[TERN ? 1 : 256];
     __shared__ float stage[kWavesPerBlock][kChunk + 32];
     const uint32_t t = threadIdx.x;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63u;
+    if (blockIdx.x == 0) { src.check({(uint32_t)algo, false, false}, W, status); return; }
     const auto job = src.template job<BLK_PLANE>();
     const GroupView &out = job.out;
-    if (job.block == job.last && (int)t < W)
-        check_header(reinterpret_cast<const PayloadHeader *>(job.payload_of_lane(t)), algo, out.n, status);
-    // The table takes the first kTab workers, the others are added one by one, kMore of them asked for at a time.
-    // (TernGrad's workers 4 to 7 come with the first four: 10 M elements of five workers 15.0 us when all four were added,
-    // absent or not, 14.4 now.  One plane, 16 workers, 44.5 M elements: 69 us one at a time, 73 with eight at a time.)
-    constexpr int kTab = TERN ? 4 : 8, kMore = TERN ? 4 : 1;
-    const int Wt = W < kTab ? W : kTab;
-    // the plane words are asked for before the table is built: the headers' scalars, which the table waits for, and
-    // the words then travel together (one-plane schemes 0.6 us, OneBit and TernGrad 1.0-1.5 us of 28-37)
     const uint32_t wbase = job.block * (uint32_t)kSignTile + wave * (uint32_t)kSignWaveElems;
     const uint32_t nwords = (out.n + 31u) >> 5;
     const uint32_t wi = (wbase >> 5) + lane;
-    auto load_words = [&](int w0, int count, uint32_t *words, uint32_t *second) {
+    // What is needed of the eight workers from w0 on, asked for together: the header's scalars on the scalar path (as vector
+    // loads they would queue behind the compute unit's stores), the words of the planes on the vector path.
+    struct Batch { const uint8_t *pl[kPlaneBatch]; float scale[kPlaneBatch], scale_lo[kPlaneBatch]; uint32_t word[kPlaneBatch], second[kPlaneBatch]; };
+    auto fetch = [&](int w0, Batch &x) {
+        job.template payloads<kPlaneBatch>(w0, W, x.pl);
 #pragma unroll
-        for (int b = 0; b < count; ++b) {
-            words[b] = 0u;
-            if (TERN) second[b] = 0u;
-            if (w0 + b < W && wi < nwords) {
-                const uint32_t *plane = reinterpret_cast<const uint32_t *>(job.payload(w0 + b) + kHeaderBytes);
-                // (ordinary loads for TernGrad: 25.6 M elements, 8 workers 37.6 -> 32.1 us; with one plane 27.2 against 28.1)
-                words[b] = TERN ? plane[wi] : ld_stream(plane + wi);
-                if (TERN) second[b] = plane[nwords + wi];
-            }
-        }
-    };
-    uint32_t wd[8] = {}, wn[8] = {}, md[kMore], mn[kMore];
-    load_words(0, kTab, wd, wn);
-    if (TERN) load_words(kTab, kMore, md, mn);
-    {
-        if (!TERN) {
-            float acc = 0.0f;
-#pragma unroll
-            for (int b = 0; b < kTab; ++b) {
-                if (b < Wt) {
-                    float hi, lo;
-                    plane_levels(reinterpret_cast<const PayloadHeader *>(job.payload(b)), kind, hi, lo);
-                    acc = acc + (((t >> b) & 1u) ? hi : lo);
-                }
-            }
-            if (W <= kTab && kind == PLANE_VOTE) acc = vote_of(acc);
-            table[t] = W <= kTab ? alpha * acc : acc;
-        } else {
-            // entry (nz bits of workers 0..3) | (negative bits of workers 0..3) << 4: their sum, in worker order
-            float acc = 0.0f;
-#pragma unroll
-            for (int b = 0; b < 4; ++b) {
-                if (b < Wt) {
-                    const float sc = ld_uniform(&reinterpret_cast<const PayloadHeader *>(job.payload(b))->scale);
-                    acc = acc + (((t >> b) & 1u) ? (((t >> (4 + b)) & 1u) ? -sc : sc) : 0.0f);
-                }
-            }
-            table[t] = acc;
-        }
-    }
-    __syncthreads();
-    if (wbase >= out.n) return;
-    float acc[32];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        // byte q of the words -> rows of an 8x8 bit matrix (row = worker, column = element 8q + c)
-        const uint64_t x = gather_transpose(wd, q);
-        if (!TERN) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) acc[8 * q + e] = table[(uint32_t)(x >> (8 * e)) & 0xFFu];
-        } else {
-            const uint64_t y = gather_transpose(wn, q) & x;         // negative only counts where non-zero
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const uint32_t xe = (uint32_t)(x >> (8 * e)) & 15u, ye = (uint32_t)(y >> (8 * e)) & 15u;
-                acc[8 * q + e] = table[xe | (ye << 4)];
-            }
-        }
-    }
-    for (int w0 = kTab; w0 < W; w0 += kMore) {
-        if (!TERN || w0 > kTab) load_words(w0, kMore, md, mn);
-        float hi[kMore], lo[kMore];
-#pragma unroll
-        for (int b = 0; b < kMore; ++b) {
-            const PayloadHeader *h = reinterpret_cast<const PayloadHeader *>(job.payload(w0 + b < W ? w0 + b : w0));
-            if (TERN) hi[b] = ld_uniform(&h->scale);
-            else plane_levels(h, kind, hi[b], lo[b]);
-        }
-#pragma unroll
-        for (int b = 0; b < kMore; ++b) {
+        for (int b = 0; b < kPlaneBatch; ++b) {
+            const PayloadHeader *h = reinterpret_cast<const PayloadHeader *>(x.pl[b]);
+            x.scale[b] = x.scale_lo[b] = 0.0f;
             if (w0 + b < W) {
+                x.scale[b] = ld_uniform(&h->scale);
+                if (!TERN) x.scale_lo[b] = __uint_as_float(ld_uniform(&h->pad[0]));
+            }
+        }
 #pragma unroll
-                for (int e = 0; e < 32; ++e) acc[e] = acc[e] + (TERN ? tern_term(md[b], mn[b], e, hi[b]) : plane_term(md[b], e, hi[b], lo[b]));
+        for (int b = 0; b < kPlaneBatch; ++b) {
+            x.word[b] = x.second[b] = 0u;
+            if (w0 + b < W && wi < nwords) {
+                const global_ptr<const uint32_t> plane = in_global(reinterpret_cast<const uint32_t *>(x.pl[b] + kHeaderBytes));
+                // (ordinary loads for TernGrad: 25.6 M elements, 8 workers 37.6 -> 32.1 us; with one plane 27.2 against 28.1)
+                x.word[b] = TERN ? plane[wi] : __builtin_nontemporal_load(plane + wi);
+                if (TERN) x.second[b] = plane[nwords + wi];
+            }
+        }
+        hold(x.scale);
+        if (!TERN) hold(x.scale_lo);
+    };
+    Batch x;
+    fetch(0, x);
+    float acc[32];
+    if (!TERN) {
+        // the table takes the first eight workers
+        float sum = 0.0f;
+#pragma unroll
+        for (int b = 0; b < kPlaneBatch; ++b) {
+            float hi, lo;
+            plane_levels(x.scale[b], x.scale_lo[b], kind, hi, lo);
+            sum = b < W ? sum + (((t >> b) & 1u) ? hi : lo) : sum;
+        }
+        if (W <= kPlaneBatch && kind == PLANE_VOTE) sum = vote_of(sum);
+        table[t] = W <= kPlaneBatch ? alpha * sum : sum;
+        __syncthreads();
+        if (wbase >= out.n) return;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            // byte q of the words -> rows of an 8x8 bit matrix (row = worker, column = element 8q + c)
+            const uint64_t m = gather_transpose(x.word, q);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) acc[8 * q + e] = table[(uint32_t)(m >> (8 * e)) & 0xFFu];
+        }
+    } else {
+        if (wbase >= out.n) return;
+#pragma unroll
+        for (int e = 0; e < 32; ++e) acc[e] = 0.0f;
+    }
+    // the further workers (TernGrad: all), one by one
+#pragma unroll 1
+    for (int w0 = TERN ? 0 : kPlaneBatch; w0 < W; w0 += kPlaneBatch) {
+        if (w0) fetch(w0, x);
+        if (TERN) {
+            bool exact = true;
+#pragma unroll
+            for (int b = 0; b < kPlaneBatch; ++b) exact = exact && halves_exactly(x.scale[b]);
+#pragma unroll
+            for (int b = 0; b < kPlaneBatch; ++b) {
+                if (w0 + b >= W) break;
+                if (exact) { add_terns(acc, x.word[b], x.second[b], 0.5f * x.scale[b]); continue; }
+#pragma unroll
+                for (int e = 0; e < 32; ++e) acc[e] = acc[e] + tern_term(x.word[b], x.second[b], e, x.scale[b]);
+            }
+        } else {
+            bool signs = kind != PLANE_MEANS;
+            if (kind == PLANE_SCALE)
+#pragma unroll
+                for (int b = 0; b < kPlaneBatch; ++b) signs = signs && x.scale[b] == x.scale[b];      // (a NaN would keep its sign)
+#pragma unroll
+            for (int b = 0; b < kPlaneBatch; ++b) {
+                if (w0 + b >= W) break;
+                float hi, lo;
+                plane_levels(x.scale[b], x.scale_lo[b], kind, hi, lo);
+                if (signs) { add_signs(acc, x.word[b], hi); continue; }
+#pragma unroll
+                for (int e = 0; e < 32; ++e) acc[e] = acc[e] + plane_term(x.word[b], e, hi, lo);
             }
         }
     }
-    if (W > kTab || TERN) {
+    if (W > kPlaneBatch || TERN) {
 #pragma unroll
         for (int e = 0; e < 32; ++e) acc[e] = alpha * (!TERN && kind == PLANE_VOTE ? vote_of(acc[e]) : acc[e]);
     }
@@ -1219,7 +1250,7 @@ template <class SRC>
 void launch_dense_decompress(const LaunchCtx &lc, int algo, const SRC &src, uint32_t blocks, int W, float alpha, uint32_t levels, int *status)
 {
     if (blocks == 0) return;
-    dim3 grid(blocks), block(kBlock);
+    dim3 grid(blocks + 1), block(kBlock);           // (the first checks the headers)
     prof_begin(lc, K_DENSE_DECOMPRESS);
     switch (algo) {
     case MC_ALGO_EFSIGN:

@@ -1706,19 +1706,59 @@ template void launch_sparse_compress<OneSparse>(const LaunchCtx &, int, const On
 template void launch_sparse_compress<AllSparse>(const LaunchCtx &, int, const AllSparse &, const SparseBlocks &, bool, const SparseCall &);
 
 // ---------------------------------------------------------------------------
-// Sparse decompress-and-sum.  Every worker's indices ascend, so a 4096-element
-// output tile owns one contiguous run of each list, and the directory that ends a
-// payload says where that run starts and ends.  A block accumulates its tile in LDS,
-// one worker after the other in ascending worker order -- the same order of fp32
-// additions as a dense sum, since adding the +0 of an absent entry changes nothing --
-// and writes it once.  No atomics, no pre-zeroed output, bit-reproducible.
-// (The directory replaced a kernel that recorded the runs of all payloads in per-call
-// tables before this one could start: 5 of 38 us.)
+// Sparse decompress-and-sum.  Every worker's indices ascend, so a 4096-element output tile owns one contiguous run of
+// each list, and the directory that ends a payload says where that run starts and ends.  A wavefront accumulates its
+// chunk of the tile in LDS of its own, one worker after the other in ascending worker order -- the same order of fp32
+// additions as a dense sum, since adding the +0 of an absent entry changes nothing -- and writes it once.  No atomics in
+// memory, no pre-zeroed output, no block barrier, bit-reproducible.
+// The additions are LDS additions without a result (they round and keep subnormals as the vector ALU's do): those of one
+// wavefront are carried out in the order issued, so a worker's see the ones before and the wavefront waits for none.
+// (A directory replaced a kernel that recorded the runs of all payloads in per-call tables before this one could start: 5 of
+// 38 us.  Before, the block's wavefronts shared a tile's entries of a worker where one had more than 64, with a read, an
+// addition, a write and a block barrier per worker: FIGURES.)
 // ---------------------------------------------------------------------------
 constexpr int kSparseBatch = 8;    // workers whose entries are in flight together
-// rounds of 256 entries per worker and tile fetched up front (with 4 the kernel needs 74 vector registers and 6 wavefronts
-// fit a SIMD; with 3, 58 and 8: measured 0.7 .. 1.9 us faster, 2 rounds no better)
-constexpr int kSparseRounds = 3;
+
+// Entries [from[b], to[b]) of workers b0 .. b0 + NB - 1 of a batch, ROUNDS of 64 of each asked for at once; of these, those
+// in the chunk at `base` are added to its sums.
+template <int NB, int ROUNDS>
+__device__ __forceinline__ void add_entries(const uint8_t *const (&pl)[kSparseBatch], int b0, uint32_t k, const uint32_t (&from)[kSparseBatch],
+                                            const uint32_t (&to)[kSparseBatch], uint32_t base, float *sums /* LDS, kChunk */)
+{
+    const uint32_t lane = threadIdx.x & 63u;
+    uint32_t ix[NB][ROUNDS];
+    float vv[NB][ROUNDS];
+    auto fetch = [&](int b, uint32_t at) {
+        // (Ordinary loads: the tile's four wavefronts read the same lines, and neighbouring tiles share theirs.  As
+        // non-temporal loads each went to memory, behind the stores: 25.6 M elements, 8 workers, Top-k 1 % 31.3 us, then
+        // 27.3; thinly spread payloads (Rand-k) 34.3, then 26.1; 44.5 M heavy-tailed ones 50.1, then 39.3.)
+        const global_ptr<const uint32_t> idx = in_global(reinterpret_cast<const uint32_t *>(pl[b0 + b] + kHeaderBytes));
+        const global_ptr<const float> val = (global_ptr<const float>)(idx + k);
+#pragma unroll
+        for (int r = 0; r < ROUNDS; ++r) {
+            ix[b][r] = 0xFFFFFFFFu; vv[b][r] = 0.0f;
+            if (at + 64u * r < to[b0 + b]) {                 // (the same for the wavefront)
+                const uint32_t e = at + 64u * r + lane;
+                if (e < to[b0 + b]) { ix[b][r] = idx[e]; vv[b][r] = val[e]; }
+            }
+        }
+    };
+    auto add = [&](int b) {
+#pragma unroll
+        for (int r = 0; r < ROUNDS; ++r) {
+            const uint32_t local = ix[b][r] - base;          // an absent entry (all ones) lands far outside
+            if (local < (uint32_t)kChunk) __hip_atomic_fetch_add(sums + local, vv[b][r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+        __builtin_amdgcn_wave_barrier();
+    };
+#pragma unroll
+    for (int b = 0; b < NB; ++b) fetch(b, from[b0 + b]);
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        add(b);
+        for (uint32_t at = from[b0 + b] + 64u * ROUNDS; at < to[b0 + b]; at += 64u * ROUNDS) { fetch(b, at); add(b); }
+    }
+}
 
 // k64: entries a payload has room for (the exact k, or the capacity when DGC takes its threshold from a sample: the
 // header then says how many are in use and repeats the capacity)
@@ -1726,156 +1766,90 @@ template <class SRC>
 __global__ __launch_bounds__(kBlock) void sparse_decompress_k(int algo, SRC src, int W, float alpha, int *status, int capped)
 {
     __shared__ float acc[kTile];
+    if (blockIdx.x == 0) { src.check({(uint32_t)algo, true, capped != 0}, W, status); return; }
     const auto job = src.template job<BLK_TILE>();
     const GroupView &out = job.out;
     const uint64_t k64 = job.k;
     const uint32_t k = (uint32_t)k64;
-    if (job.block == job.last && (int)threadIdx.x < W) {
-        const PayloadHeader *h = reinterpret_cast<const PayloadHeader *>(job.payload_of_lane(threadIdx.x));
-        const bool fits = capped ? h->k <= k64 && h->levels == (uint32_t)k64 : h->k == k64;
-        if (h->magic != kMagic || h->algo != (uint32_t)algo || h->n != (uint64_t)out.n || !fits) raise_flag(status, FLAG_PAYLOAD);
-    }
     const uint32_t tile = job.block;
-    const uint32_t tb = tile * (uint32_t)kTile;
-    const uint32_t t = threadIdx.x;
     const Chunk c = my_chunk(out.n, tile);
-    const uintptr_t entry = chunk_entry(out, c);        // needed last, asked for first: overlaps with the table loads
-    if (W > kSparseBatch) {
-        // more workers than one batch: the tiles that no worker has an entry for are found first, over all batches
-        // (the per-batch test below only sees its own eight), and zero-filled as with one batch
-        bool any = false;
-        for (int w = 0; w < W; ++w) {
-            const uint32_t *dir = reinterpret_cast<const uint32_t *>(job.payload(w) + kHeaderBytes + 8u * k64);
-            const uint32_t f = ld_uniform(dir + tile), l = ld_uniform(dir + tile + 1u);
-            any = any || (l < k ? l : k) > (f < k ? f : k);
-        }
-        if (!any) {
-            if (c.base >= out.n) return;
-            float z[kSteps];
-#pragma unroll
-            for (int j = 0; j < kSteps; ++j) z[j] = alpha * 0.0f;
-            store_seg_rot(out, c, z, entry, chunk_rotation(entry));
-            return;
-        }
-    }
-    for (int w0 = 0; w0 < W; w0 += kSparseBatch) {
-        // issue the loads of a batch of workers before the first LDS update
-        uint32_t lo[kSparseBatch], hi[kSparseBatch];
-#pragma unroll
-        for (int b = 0; b < kSparseBatch; ++b) {
-            lo[b] = hi[b] = 0;
-            if (w0 + b < W) {
-                // block-uniform addresses, kept on the scalar path whatever the compiler makes of the rest
-                const uint32_t *dir = reinterpret_cast<const uint32_t *>(job.payload(w0 + b) + kHeaderBytes + 8u * k64);
-                const uint32_t f = ld_uniform(dir + tile), l = ld_uniform(dir + tile + 1u);
-                lo[b] = f < k ? f : k;
-                hi[b] = l < k ? l : k;
-                // inconsistent payload (a directory that does not ascend): a tile holds at most 4096 entries
-                if (hi[b] < lo[b] || hi[b] - lo[b] > (uint32_t)kTile) hi[b] = lo[b];
-            }
-        }
-        if (W <= kSparseBatch) {          // most tiles hold no kept entry at all: they are just zero-filled
-            bool any = false;
-#pragma unroll
-            for (int b = 0; b < kSparseBatch; ++b) any = any || hi[b] > lo[b];
-            if (!any) {
-                if (c.base >= out.n) return;
-                float z[kSteps];
-#pragma unroll
-                for (int j = 0; j < kSteps; ++j) z[j] = alpha * 0.0f;
-                // whole lines per wave store (measured: -0.5 us; the same rotation on the path below costs 3 us)
-                store_seg_rot(out, c, z, entry, chunk_rotation(entry));
-                return;
-            }
-        }
-        if (W <= kSparseBatch) {
-            // (The entries are read with ordinary loads, here and below: the tile's four wavefronts read the same lines,
-            // and neighbouring tiles share theirs.  As non-temporal loads each went to memory, behind the stores: 25.6 M
-            // elements, 8 workers, Top-k 1 % 31.3 us, now 27.3; thinly spread payloads (Rand-k) 34.3, now 26.1; 44.5 M
-            // heavy-tailed ones 50.1, now 39.3.)
-            // Few entries per worker (at most one per lane): every wavefront sums its own chunk, in LDS of its own, from
-            // the tile's entries of all workers -- loaded together, added worker by worker, no block barrier.  The LDS
-            // operations of one wavefront complete in the order issued, so a worker's additions see the ones before.
-            bool light = true;
-#pragma unroll
-            for (int b = 0; b < kSparseBatch; ++b) light = light && hi[b] - lo[b] <= 64u;
-            if (light) {
-                if (c.base >= out.n) return;
-                uint32_t ix[kSparseBatch];
-                float vv[kSparseBatch];
-#pragma unroll
-                for (int b = 0; b < kSparseBatch; ++b) {
-                    const uint32_t *idx = reinterpret_cast<const uint32_t *>(job.payload(b < W ? b : 0) + kHeaderBytes);
-                    const float *val = reinterpret_cast<const float *>(idx + k);
-                    const uint32_t e = lo[b] + c.lane;
-                    ix[b] = 0xFFFFFFFFu; vv[b] = 0.0f;
-                    if (b < W && e < hi[b]) { ix[b] = idx[e]; vv[b] = val[e]; }
-                }
-                float *mine = acc + (c.base - tb);
-#pragma unroll
-                for (int j = 0; j < kSteps; ++j) mine[64 * j + c.lane] = 0.0f;
-                __builtin_amdgcn_wave_barrier();
-#pragma unroll
-                for (int b = 0; b < kSparseBatch; ++b) {
-                    const uint32_t local = ix[b] - c.base;          // an absent entry (all ones) lands far outside
-                    if (b < W && local < (uint32_t)kChunk) mine[local] = mine[local] + vv[b];
-                    __builtin_amdgcn_wave_barrier();
-                }
-                // read back in the mapping rotated onto the output's 128-byte lines (payloads spread thinly over all
-                // tiles: 37.2 -> 36.3 us; clustered ones: 32.3 -> 32.1; the same on the path below changes nothing)
-                float v[kSteps];
-                const uint32_t rot = chunk_rotation(entry);
-#pragma unroll
-                for (int j = 0; j < kSteps; ++j) v[j] = alpha * mine[rotated(j, c.lane, rot)];
-                store_seg_rot(out, c, v, entry, rot);
-                return;
-            }
-        }
-        if (w0 == 0) {
-#pragma unroll
-            for (int j = 0; j < kSteps; ++j) acc[t + kBlock * j] = 0.0f;
-            __syncthreads();
-        }
-        // the kept entries cluster in a few tensors: a tile there holds hundreds of entries per worker.
-        // Three rounds of 256 entries of every worker of the batch are requested at once.
-        uint32_t ix[kSparseBatch][kSparseRounds];
-        float vv[kSparseBatch][kSparseRounds];
-#pragma unroll
-        for (int b = 0; b < kSparseBatch; ++b) {
-            const uint32_t *idx = reinterpret_cast<const uint32_t *>(job.payload(w0 + b < W ? w0 + b : 0) + kHeaderBytes);
-            const float *val = reinterpret_cast<const float *>(idx + k);
-#pragma unroll
-            for (int r = 0; r < kSparseRounds; ++r) {
-                const uint32_t e = lo[b] + r * kBlock + t;
-                ix[b][r] = 0xFFFFFFFFu; vv[b][r] = 0.0f;
-                if (w0 + b < W && e < hi[b]) { ix[b][r] = idx[e]; vv[b][r] = val[e]; }
-            }
-        }
-#pragma unroll
-        for (int b = 0; b < kSparseBatch; ++b) {
-            if (w0 + b < W) {
-#pragma unroll
-                for (int r = 0; r < kSparseRounds; ++r) {
-                    const uint32_t local = ix[b][r] - tb;
-                    if (ix[b][r] != 0xFFFFFFFFu && local < (uint32_t)kTile) acc[local] = acc[local] + vv[b][r];
-                }
-                // more than 768 entries of one worker in the tile
-                const uint32_t *idx = reinterpret_cast<const uint32_t *>(job.payload(w0 + b) + kHeaderBytes);
-                const float *val = reinterpret_cast<const float *>(idx + k);
-                for (uint32_t e = lo[b] + kSparseRounds * kBlock + t; e < hi[b]; e += kBlock) {
-                    const uint32_t l2 = idx[e] - tb;
-                    if (l2 < (uint32_t)kTile) acc[l2] = acc[l2] + val[e];
-                }
-                __syncthreads();
-            }
-        }
-    }
     if (c.base >= out.n) return;
-    float v[kSteps];
-    const float *mine = acc + (c.base - tb) + c.lane;
+    const uintptr_t entry = chunk_entry(out, c);        // needed last, asked for first: overlaps with the table loads
+    const uint32_t rot = chunk_rotation(entry);
+    float *sums = acc + (c.base - tile * (uint32_t)kTile);
+    bool touched = false;
+#pragma unroll 1
+    for (int w0 = 0; w0 < W; w0 += kSparseBatch) {
+        // the tile's run in the list of every worker of the batch, as the directories have it; of absent workers none
+        const uint8_t *pl[kSparseBatch];
+        uint32_t lo[kSparseBatch], hi[kSparseBatch];
+        job.template payloads<kSparseBatch>(w0, W, pl);
 #pragma unroll
-    for (int j = 0; j < kSteps; ++j) v[j] = alpha * mine[64 * j];
-    store_seg(out, c, v, entry);
+        for (int b = 0; b < kSparseBatch; ++b) {
+            // block-uniform addresses, kept on the scalar path whatever the compiler makes of the rest
+            const uint32_t *dir = reinterpret_cast<const uint32_t *>(pl[b] + kHeaderBytes + 8u * k64) + tile;
+            lo[b] = hi[b] = 0u;
+            if (w0 + b < W) { lo[b] = ld_uniform(dir); hi[b] = ld_uniform(dir + 1); }
+        }
+        hold(lo);
+        hold(hi);
+        uint32_t most = 0;
+#pragma unroll
+        for (int b = 0; b < kSparseBatch; ++b) {
+            lo[b] = lo[b] < k ? lo[b] : k;
+            hi[b] = hi[b] < k ? hi[b] : k;
+            // inconsistent payload (a directory that does not ascend): a tile holds at most 4096 entries
+            if (hi[b] < lo[b] || hi[b] - lo[b] > (uint32_t)kTile) hi[b] = lo[b];
+            most = hi[b] - lo[b] > most ? hi[b] - lo[b] : most;
+        }
+        if (most == 0) continue;
+        if (!touched) {
+#pragma unroll
+            for (int j = 0; j < kSteps; ++j) sums[64 * j + c.lane] = 0.0f;
+            __builtin_amdgcn_wave_barrier();
+            touched = true;
+        }
+        // At most one entry per lane: all are looked at by each of the tile's wavefronts.
+        if (most <= 64u) { add_entries<kSparseBatch, 1>(pl, 0, k, lo, hi, c.base, sums); continue; }
+        // Else the run's part that lies in the chunk is found first, to a 64th of the run: every 64th entry of it (at most: the
+        // runs are that short) in a lane, of all workers at once.
+        uint32_t at[kSparseBatch];
+#pragma unroll
+        for (int b = 0; b < kSparseBatch; ++b) {
+            at[b] = 0u;
+            if (hi[b] > lo[b]) at[b] = in_global(reinterpret_cast<const uint32_t *>(pl[b] + kHeaderBytes))[lo[b] + ((hi[b] - lo[b]) * c.lane >> 6)];
+        }
+        most = 0;
+#pragma unroll
+        for (int b = 0; b < kSparseBatch; ++b) {
+            const uint32_t len = hi[b] - lo[b], first = lo[b];
+            const uint32_t below = (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(at[b] < c.base));                        // samples before the chunk
+            const uint32_t up_to = (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(at[b] < c.base || at[b] - c.base < (uint32_t)kChunk));      // ... or in it
+            if (len) {
+                lo[b] = below ? first + (len * (below - 1u) >> 6) + 1u : first;
+                hi[b] = up_to < 64u ? first + (len * up_to >> 6) : hi[b];
+                if (hi[b] < lo[b]) hi[b] = lo[b];             // (none between two samples)
+            }
+            most = hi[b] - lo[b] > most ? hi[b] - lo[b] : most;
+        }
+        if (most <= 128u) add_entries<kSparseBatch, 2>(pl, 0, k, lo, hi, c.base, sums);
+        else {
+            add_entries<kSparseBatch / 2, 4>(pl, 0, k, lo, hi, c.base, sums);
+            add_entries<kSparseBatch / 2, 4>(pl, kSparseBatch / 2, k, lo, hi, c.base, sums);
+        }
+    }
+    // Stored in the mapping rotated onto the output's 128-byte lines (payloads spread thinly over all tiles: 37.2 -> 36.3 us;
+    // clustered ones: 32.3 -> 32.1; where no entry lies, 0.5 us).  Most tiles hold no kept entry at all: they are just zero-filled.
+    float v[kSteps];
+    if (touched) {
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int j = 0; j < kSteps; ++j) v[j] = alpha * sums[rotated(j, c.lane, rot)];
+    } else {
+#pragma unroll
+        for (int j = 0; j < kSteps; ++j) v[j] = alpha * 0.0f;
+    }
+    store_seg_rot(out, c, v, entry, rot);
 }
 
 template <class SRC>
@@ -1883,7 +1857,7 @@ void launch_sparse_decompress(const LaunchCtx &lc, int algo, const SRC &src, uin
 {
     if (tiles == 0) return;
     prof_begin(lc, K_SPARSE_DECOMPRESS);
-    MC_LAUNCH(sparse_decompress_k<SRC>, dim3(tiles), dim3(kBlock), lc, algo, src, W, alpha, status, capped ? 1 : 0);
+    MC_LAUNCH(sparse_decompress_k<SRC>, dim3(tiles + 1) /* the first checks the headers */, dim3(kBlock), lc, algo, src, W, alpha, status, capped ? 1 : 0);
     prof_end(lc, K_SPARSE_DECOMPRESS);
 }
 template void launch_sparse_decompress<OneDecompress>(const LaunchCtx &, int, const OneDecompress &, uint32_t, int, float, int *, bool);

@@ -927,6 +927,7 @@ int mc_decompress_sum(mc_ctx *ctx, int32_t group, const void *const *payloads, i
         if (!payloads[w] || (reinterpret_cast<uintptr_t>(payloads[w]) & 15u)) return MC_ERR_INVALID_ARG;
         pl.p[w] = static_cast<const uint8_t *>(payloads[w]);
     }
+    for (int32_t w = W; w < kMaxWorkers; ++w) pl.p[w] = pl.p[0];      // (kernels read the addresses of several workers at once)
     if (G.n == 0) return MC_OK;
     LaunchCtx lc{static_cast<hipStream_t>(stream), &ctx->prof, nullptr, nullptr};
     (void)hipGetLastError();

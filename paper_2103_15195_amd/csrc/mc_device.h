@@ -44,6 +44,7 @@ struct Chunk {
 // ones, and in a model's gradient list they crowd where the small tensors are -- at the end, when the list is in
 // the order the gradients become ready, the first layers last.  Started first, they are hidden behind the rest
 // (read-only pass over the ResNet-50 list: 18.0 us instead of 19.5; 17.1 with no such chunk at all).
+// (A decompress-and-sum's grid has one block more, the first, which gets a number behind the last tile's: Expected.)
 __device__ __forceinline__ uint32_t my_tile_index() { return gridDim.x - 1u - blockIdx.x; }
 
 __device__ __forceinline__ Chunk my_chunk(uint32_t n, uint32_t tile)
@@ -68,6 +69,24 @@ __device__ __forceinline__ T ld_uniform(const T *p)
     return *(const_ptr)(uintptr_t)p;
 }
 
+// Values that are the same for the wavefront, all there from here on.  Asked for under conditions of their own ("if
+// there is a worker b"), scalar loads are waited for one after the other, a memory latency each; loaded without condition
+// and passed through here they travel together.  (Before, one directory, scale and address per worker in turn: SERIAL.)
+template <typename T>
+__device__ __forceinline__ void hold(T (&x)[4]) { asm volatile("" : "+s"(x[0]), "+s"(x[1]), "+s"(x[2]), "+s"(x[3])); }
+template <typename T>
+__device__ __forceinline__ void hold(T (&x)[8])
+{
+    asm volatile("" : "+s"(x[0]), "+s"(x[1]), "+s"(x[2]), "+s"(x[3]), "+s"(x[4]), "+s"(x[5]), "+s"(x[6]), "+s"(x[7]));
+}
+
+// An address that came out of a table or through hold() as one in device memory.  Of a generic one the compiler does not
+// know that it is not in LDS: every access then counts as an LDS access too, and waiting for either waits for both.
+template <typename T>
+using global_ptr = __attribute__((address_space(1))) T *;
+template <typename T>
+__device__ __forceinline__ global_ptr<T> in_global(T *p) { return (global_ptr<T>)(uintptr_t)p; }
+
 template <typename T>
 __device__ __forceinline__ T ld_stream(const T *p) { return __builtin_nontemporal_load(p); }
 template <typename T>
@@ -78,10 +97,10 @@ __device__ __forceinline__ void st_stream(T *p, T v) { __builtin_nontemporal_sto
 template <typename T, bool STREAM = true>
 __device__ __forceinline__ void load_flat(const T *buf, const Chunk &c, uint32_t n, T (&v)[kSteps], T fill)
 {
-    const T *p = buf + c.base + c.lane;
+    const global_ptr<const T> p = in_global(buf) + c.base + c.lane;
     if (c.full) {
 #pragma unroll
-        for (int j = 0; j < kSteps; ++j) v[j] = STREAM ? ld_stream(p + 64 * j) : p[64 * j];
+        for (int j = 0; j < kSteps; ++j) v[j] = STREAM ? __builtin_nontemporal_load(p + 64 * j) : p[64 * j];
     } else {
 #pragma unroll
         for (int j = 0; j < kSteps; ++j) v[j] = (c.base + 64 * j + c.lane < n) ? p[64 * j] : fill;
@@ -91,10 +110,10 @@ __device__ __forceinline__ void load_flat(const T *buf, const Chunk &c, uint32_t
 template <typename T>
 __device__ __forceinline__ void store_flat(T *buf, const Chunk &c, uint32_t n, const T (&v)[kSteps])
 {
-    T *p = buf + c.base + c.lane;
+    const global_ptr<T> p = in_global(buf) + c.base + c.lane;
     if (c.full) {
 #pragma unroll
-        for (int j = 0; j < kSteps; ++j) st_stream(p + 64 * j, v[j]);
+        for (int j = 0; j < kSteps; ++j) __builtin_nontemporal_store(v[j], p + 64 * j);
     } else {
 #pragma unroll
         for (int j = 0; j < kSteps; ++j) if (c.base + 64 * j + c.lane < n) p[64 * j] = v[j];
@@ -166,14 +185,14 @@ __device__ __forceinline__ void load_seg(const GroupView &g, const Chunk &c, flo
 {
     const uintptr_t entry = chunk_entry(g, c);
     if (!(entry & 1u)) {
-        const float *p = reinterpret_cast<const float *>(entry) + c.lane;
+        const global_ptr<const float> p = in_global(reinterpret_cast<const float *>(entry)) + c.lane;
 #pragma unroll
-        for (int j = 0; j < kSteps; ++j) v[j] = ld_stream(p + 64 * j);
+        for (int j = 0; j < kSteps; ++j) v[j] = __builtin_nontemporal_load(p + 64 * j);
     } else {
 #pragma unroll
         for (int j = 0; j < kSteps; ++j) v[j] = 0.0f;
         for_each_tensor_of_chunk(g, c, (uint32_t)(entry >> 1), [&](uint32_t beg, uint32_t end, uintptr_t ptr) {
-            const float *p = reinterpret_cast<const float *>(ptr);
+            const global_ptr<const float> p = in_global(reinterpret_cast<const float *>(ptr));
 #pragma unroll
             for (int j = 0; j < kSteps; ++j) {
                 const uint32_t i = c.base + 64 * j + c.lane;
@@ -190,12 +209,12 @@ __device__ __forceinline__ void load_seg(const GroupView &g, const Chunk &c, flo
 __device__ __forceinline__ void store_seg(const GroupView &g, const Chunk &c, const float (&v)[kSteps], uintptr_t entry)
 {
     if (!(entry & 1u)) {
-        float *p = reinterpret_cast<float *>(entry) + c.lane;
+        const global_ptr<float> p = in_global(reinterpret_cast<float *>(entry)) + c.lane;
 #pragma unroll
-        for (int j = 0; j < kSteps; ++j) st_stream(p + 64 * j, v[j]);
+        for (int j = 0; j < kSteps; ++j) __builtin_nontemporal_store(v[j], p + 64 * j);
     } else {
         for_each_tensor_of_chunk(g, c, (uint32_t)(entry >> 1), [&](uint32_t beg, uint32_t end, uintptr_t ptr) {
-            float *p = reinterpret_cast<float *>(ptr);
+            const global_ptr<float> p = in_global(reinterpret_cast<float *>(ptr));
 #pragma unroll
             for (int j = 0; j < kSteps; ++j) {
                 const uint32_t i = c.base + 64 * j + c.lane;
@@ -213,10 +232,10 @@ __device__ __forceinline__ void store_seg_rot(const GroupView &g, const Chunk &c
 {
     if (!(entry & 1u)) {
         // steps 0..14 at constant offsets from one address (they fold into the instructions), step 15 may wrap
-        float *p = reinterpret_cast<float *>(entry), *q = p + (c.lane + rot);
+        const global_ptr<float> p = in_global(reinterpret_cast<float *>(entry)), q = p + (c.lane + rot);
 #pragma unroll
-        for (int j = 0; j < kSteps - 1; ++j) st_stream(q + 64 * j, v[j]);
-        st_stream(p + rotated(kSteps - 1, c.lane, rot), v[kSteps - 1]);
+        for (int j = 0; j < kSteps - 1; ++j) __builtin_nontemporal_store(v[j], q + 64 * j);
+        __builtin_nontemporal_store(v[kSteps - 1], p + rotated(kSteps - 1, c.lane, rot));
     } else {
         store_seg(g, c, v, entry);
     }

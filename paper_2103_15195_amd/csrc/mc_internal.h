@@ -2,6 +2,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <hip/hip_ext.h>
+#include <stddef.h>
 #include <stdint.h>
 
 #include "../../include/mergecomp.h"
@@ -140,6 +141,21 @@ struct AllCompress {              // list: tensors, then y states, then y payloa
     }
 };
 
+// What the header of a payload has to say.  The first block of a decompress-and-sum does nothing but look at all of them: in
+// the block of a tile, field by field in front of its work, they were four memory latencies in a row, most of what a block of
+// a small group takes, and read ahead of the work and compared after it their registers cost the sparse kernel a wavefront
+// per SIMD (25.6 M elements, 8 workers: 0.6 us of 22).
+struct Expected {
+    uint32_t algo;
+    bool sparse, capped;          // the number of kept entries is fixed by the group, or at most what there is room for
+    __device__ __forceinline__ void check(const uint8_t *payload, uint32_t n, uint64_t k, int *status) const
+    {
+        const PayloadHeader *h = reinterpret_cast<const PayloadHeader *>(payload);
+        const bool fits = !sparse || (capped ? h->k <= k && h->levels == (uint32_t)k : h->k == k);
+        if (h->magic != kMagic || h->algo != algo || h->n != (uint64_t)n || !fits) raise_flag(status, FLAG_PAYLOAD);
+    }
+};
+
 // A decompress-and-sum's job: the output, the payloads of the group, and this block's number among the group's.
 struct OneDecompress {
     GroupView out;
@@ -149,11 +165,20 @@ struct OneDecompress {
         GroupView out;
         const OneDecompress *src;
         uint64_t k;
-        uint32_t block, last;
-        __device__ __forceinline__ const uint8_t *payload(int w) const { return src->pl.p[w]; }             // w: the same for the wavefront
-        __device__ __forceinline__ const uint8_t *payload_of_lane(uint32_t w) const { return src->pl.p[w]; }
+        uint32_t block;
+        // the payloads of workers w0 .. w0 + N - 1 (w0: a multiple of N); behind the last worker's some other one
+        template <int N> __device__ __forceinline__ void payloads(int w0, int, const uint8_t *(&p)[N]) const
+        {
+#pragma unroll
+            for (int b = 0; b < N; ++b) p[b] = src->pl.p[w0 + b];
+            hold(p);
+        }
     };
-    template <int KIND> __device__ __forceinline__ Job job() const { return {out, this, k, my_tile_index(), gridDim.x - 1u}; }
+    template <int KIND> __device__ __forceinline__ Job job() const { return {out, this, k, my_tile_index()}; }
+    __device__ __forceinline__ void check(const Expected &e, int W, int *status) const
+    {
+        if ((int)threadIdx.x < W) e.check(pl.p[threadIdx.x], out.n, k, status);
+    }
 };
 struct AllDecompress {            // list: tensors, then the W payloads of group 0, of group 1, ...
     GroupTable tb;
@@ -162,9 +187,13 @@ struct AllDecompress {            // list: tensors, then the W payloads of group
         GroupView out;
         const uintptr_t *pl;
         uint64_t k;
-        uint32_t block, last;
-        __device__ __forceinline__ const uint8_t *payload(int w) const { return reinterpret_cast<const uint8_t *>(ld_uniform(pl + w)); }
-        __device__ __forceinline__ const uint8_t *payload_of_lane(uint32_t w) const { return reinterpret_cast<const uint8_t *>(pl[w]); }
+        uint32_t block;
+        template <int N> __device__ __forceinline__ void payloads(int w0, int W, const uint8_t *(&p)[N]) const
+        {
+#pragma unroll
+            for (int b = 0; b < N; ++b) p[b] = reinterpret_cast<const uint8_t *>(ld_uniform(pl + (w0 + b < W ? w0 + b : 0)));
+            hold(p);
+        }
     };
     template <int KIND> __device__ __forceinline__ Job job() const
     {
@@ -175,8 +204,14 @@ struct AllDecompress {            // list: tensors, then the W payloads of group
         j.pl = tb.list + tb.live + (size_t)q * W;
         j.k = ld_uniform(&c->k);
         j.block = b - ld_uniform(&c->first[KIND]);
-        j.last = (uint32_t)(((uint64_t)j.out.n + (KIND == BLK_PLANE ? 2 * kTile : kTile) - 1) / (KIND == BLK_PLANE ? 2 * kTile : kTile)) - 1u;
         return j;
+    }
+    __device__ __forceinline__ void check(const Expected &e, int, int *status) const
+    {
+        for (uint32_t i = threadIdx.x; i < tb.y * (uint32_t)W; i += blockDim.x) {
+            const GroupConst &c = tb.groups[i / (uint32_t)W];
+            if (c.n) e.check(reinterpret_cast<const uint8_t *>(tb.list[tb.live + i]), c.n, c.k, status);
+        }
     }
 };
 
