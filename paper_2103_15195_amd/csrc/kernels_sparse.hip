@@ -1711,52 +1711,61 @@ template void launch_sparse_compress<AllSparse>(const LaunchCtx &, int, const Al
 // chunk of the tile in LDS of its own, one worker after the other in ascending worker order -- the same order of fp32
 // additions as a dense sum, since adding the +0 of an absent entry changes nothing -- and writes it once.  No atomics in
 // memory, no pre-zeroed output, no block barrier, bit-reproducible.
-// The additions are LDS additions without a result (they round and keep subnormals as the vector ALU's do): those of one
-// wavefront are carried out in the order issued, so a worker's see the ones before and the wavefront waits for none.
+// The LDS operations of one wavefront are carried out in the order issued, so a worker's additions see the ones before.
 // (A directory replaced a kernel that recorded the runs of all payloads in per-call tables before this one could start: 5 of
 // 38 us.  Before, the block's wavefronts shared a tile's entries of a worker where one had more than 64, with a read, an
-// addition, a write and a block barrier per worker: FIGURES.)
+// addition, a write and a block barrier per worker: 25.6 M elements, 8 workers, Top-k 1 % 26.0 us, now 22.9 (21.7 if nothing
+// was sent at all), 5 % 59 / 37, 16 workers 34 / 25.9; 44.5 M heavy-tailed in four calls 59 / 52.6.  With LDS additions that
+// return nothing instead of a read, an addition and a write: 40, exact too, but about a lane per clock.)
 // ---------------------------------------------------------------------------
 constexpr int kSparseBatch = 8;    // workers whose entries are in flight together
+constexpr int kSparseRounds = 4;   // rounds of 64 entries of a chunk's run, of half as many workers, where a run has more than 128
 
-// Entries [from[b], to[b]) of workers b0 .. b0 + NB - 1 of a batch, ROUNDS of 64 of each asked for at once; of these, those
-// in the chunk at `base` are added to its sums.
+// Entries from[b] .. from[b] + len[b] - 1 of workers b0 .. b0 + NB - 1 of a batch, ROUNDS of 64 of each asked for at once; of
+// these, those in the chunk at `base` are added to its sums.  No load and no addition is under a condition: a lane without an
+// entry reads the run's last one (of an empty run what lies in the payload where it would start) and adds it to a word
+// that nobody reads.  (With conditions every load waited for the one before, the registers of one path being taken for those
+// of another.)
 template <int NB, int ROUNDS>
 __device__ __forceinline__ void add_entries(const uint8_t *const (&pl)[kSparseBatch], int b0, uint32_t k, const uint32_t (&from)[kSparseBatch],
-                                            const uint32_t (&to)[kSparseBatch], uint32_t base, float *sums /* LDS, kChunk */)
+                                            const uint32_t (&len)[kSparseBatch], uint32_t base, float *sums /* LDS, kChunk and a word that nobody reads */)
 {
     const uint32_t lane = threadIdx.x & 63u;
     uint32_t ix[NB][ROUNDS];
     float vv[NB][ROUNDS];
+    // (Ordinary loads: the tile's four wavefronts read the same lines, and neighbouring tiles share theirs.  As non-temporal
+    // loads each went to memory, behind the stores: 25.6 M elements, 8 workers, Top-k 1 % 31.3 us, then 27.3; thinly spread
+    // payloads (Rand-k) 34.3, then 26.1; 44.5 M heavy-tailed ones 50.1, then 39.3.)
     auto fetch = [&](int b, uint32_t at) {
-        // (Ordinary loads: the tile's four wavefronts read the same lines, and neighbouring tiles share theirs.  As
-        // non-temporal loads each went to memory, behind the stores: 25.6 M elements, 8 workers, Top-k 1 % 31.3 us, then
-        // 27.3; thinly spread payloads (Rand-k) 34.3, then 26.1; 44.5 M heavy-tailed ones 50.1, then 39.3.)
-        const global_ptr<const uint32_t> idx = in_global(reinterpret_cast<const uint32_t *>(pl[b0 + b] + kHeaderBytes));
-        const global_ptr<const float> val = (global_ptr<const float>)(idx + k);
+        const uint32_t n = len[b0 + b];
+        const global_ptr<const uint8_t> idx = in_global(pl[b0 + b] + kHeaderBytes) + 4u * (uint64_t)from[b0 + b], val = idx + 4u * (uint64_t)k;
 #pragma unroll
         for (int r = 0; r < ROUNDS; ++r) {
-            ix[b][r] = 0xFFFFFFFFu; vv[b][r] = 0.0f;
-            if (at + 64u * r < to[b0 + b]) {                 // (the same for the wavefront)
-                const uint32_t e = at + 64u * r + lane;
-                if (e < to[b0 + b]) { ix[b][r] = idx[e]; vv[b][r] = val[e]; }
-            }
+            const uint32_t o = at + 64u * r + lane, e = 4u * (o < n ? o : n ? n - 1u : 0u);      // in bytes: 16 KiB at most
+            ix[b][r] = *(global_ptr<const uint32_t>)(idx + e);
+            vv[b][r] = *(global_ptr<const float>)(val + e);
         }
     };
-    auto add = [&](int b) {
+    auto add = [&](int b, uint32_t at) {
+        uint32_t to[ROUNDS];
+        float old[ROUNDS];
 #pragma unroll
         for (int r = 0; r < ROUNDS; ++r) {
-            const uint32_t local = ix[b][r] - base;          // an absent entry (all ones) lands far outside
-            if (local < (uint32_t)kChunk) __hip_atomic_fetch_add(sums + local, vv[b][r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            const uint32_t local = ix[b][r] - base;
+            to[r] = local < (uint32_t)kChunk && at + 64u * r + lane < len[b0 + b] ? local : (uint32_t)kChunk;
+            old[r] = sums[to[r]];
         }
+#pragma unroll
+        for (int r = 0; r < ROUNDS; ++r) sums[to[r]] = old[r] + vv[b][r];        // (a worker's entries are different elements)
         __builtin_amdgcn_wave_barrier();
     };
 #pragma unroll
-    for (int b = 0; b < NB; ++b) fetch(b, from[b0 + b]);
+    for (int b = 0; b < NB; ++b) fetch(b, 0u);
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
-        add(b);
-        for (uint32_t at = from[b0 + b] + 64u * ROUNDS; at < to[b0 + b]; at += 64u * ROUNDS) { fetch(b, at); add(b); }
+        add(b, 0u);
+        if (ROUNDS == kSparseRounds)
+            for (uint32_t at = 64u * ROUNDS; at < len[b0 + b]; at += 64u * ROUNDS) { fetch(b, at); add(b, at); }
     }
 }
 
@@ -1765,7 +1774,7 @@ __device__ __forceinline__ void add_entries(const uint8_t *const (&pl)[kSparseBa
 template <class SRC>
 __global__ __launch_bounds__(kBlock) void sparse_decompress_k(int algo, SRC src, int W, float alpha, int *status, int capped)
 {
-    __shared__ float acc[kTile];
+    __shared__ float acc[kWavesPerBlock][kChunk + 32];
     if (blockIdx.x == 0) { src.check({(uint32_t)algo, true, capped != 0}, W, status); return; }
     const auto job = src.template job<BLK_TILE>();
     const GroupView &out = job.out;
@@ -1776,7 +1785,7 @@ __global__ __launch_bounds__(kBlock) void sparse_decompress_k(int algo, SRC src,
     if (c.base >= out.n) return;
     const uintptr_t entry = chunk_entry(out, c);        // needed last, asked for first: overlaps with the table loads
     const uint32_t rot = chunk_rotation(entry);
-    float *sums = acc + (c.base - tile * (uint32_t)kTile);
+    float *sums = acc[(c.base / (uint32_t)kChunk) % (uint32_t)kWavesPerBlock];
     bool touched = false;
 #pragma unroll 1
     for (int w0 = 0; w0 < W; w0 += kSparseBatch) {
@@ -1793,14 +1802,14 @@ __global__ __launch_bounds__(kBlock) void sparse_decompress_k(int algo, SRC src,
         }
         hold(lo);
         hold(hi);
-        uint32_t most = 0;
+        uint32_t len[kSparseBatch], most = 0;
 #pragma unroll
         for (int b = 0; b < kSparseBatch; ++b) {
             lo[b] = lo[b] < k ? lo[b] : k;
             hi[b] = hi[b] < k ? hi[b] : k;
             // inconsistent payload (a directory that does not ascend): a tile holds at most 4096 entries
-            if (hi[b] < lo[b] || hi[b] - lo[b] > (uint32_t)kTile) hi[b] = lo[b];
-            most = hi[b] - lo[b] > most ? hi[b] - lo[b] : most;
+            len[b] = hi[b] < lo[b] || hi[b] - lo[b] > (uint32_t)kTile ? 0u : hi[b] - lo[b];
+            most = len[b] > most ? len[b] : most;
         }
         if (most == 0) continue;
         if (!touched) {
@@ -1809,33 +1818,34 @@ __global__ __launch_bounds__(kBlock) void sparse_decompress_k(int algo, SRC src,
             __builtin_amdgcn_wave_barrier();
             touched = true;
         }
-        // At most one entry per lane: all are looked at by each of the tile's wavefronts.
-        if (most <= 64u) { add_entries<kSparseBatch, 1>(pl, 0, k, lo, hi, c.base, sums); continue; }
+        // At most one entry per lane (of one worker, four): all are looked at by each of the tile's wavefronts.
+        const int there = W - w0;
+        if (there == 1 && most <= 64u * kSparseRounds) { add_entries<1, kSparseRounds>(pl, 0, k, lo, len, c.base, sums); continue; }
+        if (there > kSparseBatch / 2 && most <= 64u) { add_entries<kSparseBatch, 1>(pl, 0, k, lo, len, c.base, sums); continue; }
+        if (there <= kSparseBatch / 2 && most <= 64u) { add_entries<kSparseBatch / 2, 1>(pl, 0, k, lo, len, c.base, sums); continue; }
         // Else the run's part that lies in the chunk is found first, to a 64th of the run: every 64th entry of it (at most: the
         // runs are that short) in a lane, of all workers at once.
-        uint32_t at[kSparseBatch];
+        uint32_t at[kSparseBatch] = {};
+        auto sample = [&](int b) { at[b] = *(global_ptr<const uint32_t>)(in_global(pl[b] + kHeaderBytes) + 4u * (uint64_t)lo[b] + 4u * (len[b] * c.lane >> 6)); };
 #pragma unroll
-        for (int b = 0; b < kSparseBatch; ++b) {
-            at[b] = 0u;
-            if (hi[b] > lo[b]) at[b] = in_global(reinterpret_cast<const uint32_t *>(pl[b] + kHeaderBytes))[lo[b] + ((hi[b] - lo[b]) * c.lane >> 6)];
-        }
+        for (int b = 0; b < kSparseBatch / 2; ++b) sample(b);
+        if (there > kSparseBatch / 2)
+#pragma unroll
+            for (int b = kSparseBatch / 2; b < kSparseBatch; ++b) sample(b);
         most = 0;
 #pragma unroll
         for (int b = 0; b < kSparseBatch; ++b) {
-            const uint32_t len = hi[b] - lo[b], first = lo[b];
             const uint32_t below = (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(at[b] < c.base));                        // samples before the chunk
             const uint32_t up_to = (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(at[b] < c.base || at[b] - c.base < (uint32_t)kChunk));      // ... or in it
-            if (len) {
-                lo[b] = below ? first + (len * (below - 1u) >> 6) + 1u : first;
-                hi[b] = up_to < 64u ? first + (len * up_to >> 6) : hi[b];
-                if (hi[b] < lo[b]) hi[b] = lo[b];             // (none between two samples)
-            }
-            most = hi[b] - lo[b] > most ? hi[b] - lo[b] : most;
+            const uint32_t from = below ? (len[b] * (below - 1u) >> 6) + 1u : 0u, to = up_to < 64u ? len[b] * up_to >> 6 : len[b];
+            lo[b] += from;
+            len[b] = to > from ? to - from : 0u;             // (none between two samples)
+            most = len[b] > most ? len[b] : most;
         }
-        if (most <= 128u) add_entries<kSparseBatch, 2>(pl, 0, k, lo, hi, c.base, sums);
+        if (most <= 128u && there > kSparseBatch / 2) add_entries<kSparseBatch, 2>(pl, 0, k, lo, len, c.base, sums);
         else {
-            add_entries<kSparseBatch / 2, 4>(pl, 0, k, lo, hi, c.base, sums);
-            add_entries<kSparseBatch / 2, 4>(pl, kSparseBatch / 2, k, lo, hi, c.base, sums);
+            add_entries<kSparseBatch / 2, kSparseRounds>(pl, 0, k, lo, len, c.base, sums);
+            if (there > kSparseBatch / 2) add_entries<kSparseBatch / 2, kSparseRounds>(pl, kSparseBatch / 2, k, lo, len, c.base, sums);
         }
     }
     // Stored in the mapping rotated onto the output's 128-byte lines (payloads spread thinly over all tiles: 37.2 -> 36.3 us;

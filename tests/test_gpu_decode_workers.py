@@ -61,3 +61,37 @@ def test_each_field_of_a_header_is_checked(algo, byte):
         assert ctx.mc_last_device_status() == B.MC_OK
         ctx.mc_decompress_sum(0, [good] * (W - 1) + [bad], 1.0, out)
         assert ctx.mc_last_device_status() == B.MC_ERR_PAYLOAD
+
+
+RUNS = [0, 1, 63, 64, 65, 127, 128, 129, 256, 257, 511, 1023, 1024, 1025, 2500, 4096]
+
+
+@pytest.mark.parametrize("W", [1, 2, 4, 5, 8, 9, 16, 17])
+@pytest.mark.parametrize("where", ["anywhere", "one chunk", "chunk edges", "first and last"])
+def test_runs_of_a_tile(W, where):
+    """One tile in the middle with runs of very different lengths from worker to worker, spread or crowded into a part of it."""
+    n, tile = 5 * 4096 + 77, 2 * 4096
+    k = O.topk_count(n, 220000)
+    ctx = B.Context("topk", [9000, n - 9000], [0, 2], ratio_ppm=220000)
+    rng = np.random.default_rng([W, len(where)])
+    for first in (0, 5, 11):
+        sent = []
+        for w in range(W):
+            run = RUNS[(first + w) % len(RUNS)]
+            if where == "one chunk" and run <= 1024:
+                inside = tile + 1024 + rng.choice(1024, run, replace=False)
+            elif where == "chunk edges" and run <= 1024:
+                edge = np.concatenate([1024 * c + np.r_[0:128, 896:1024] for c in range(4)])
+                inside = tile + rng.choice(edge, run, replace=False)
+            elif where == "first and last" and run <= 2048:
+                inside = tile + rng.choice(np.r_[0:1024, 3072:4096], run, replace=False)
+            else:
+                inside = tile + rng.choice(4096, run, replace=False)
+            others = np.r_[0:tile, tile + 4096:n]
+            idx = np.sort(np.concatenate([inside, rng.choice(others, k - run, replace=False)])).astype(np.uint32)
+            sent.append(O.with_directory(B.ALGO_IDS["topk"], n, idx, rng.standard_normal(k).astype(np.float32)))
+        out = [torch.full((m,), 5.0, device=DEV) for m in (9000, n - 9000)]
+        ctx.mc_decompress_sum(0, [torch.from_numpy(p).to(DEV) for p in sent], 0.25, out)
+        got, want = torch.cat(out).cpu().numpy(), O.decompress_sum(sent, n, 0.25)
+        assert np.array_equal(got.view(np.uint32), want.view(np.uint32)), first
+    assert ctx.mc_last_device_status() == B.MC_OK
