@@ -1137,8 +1137,8 @@ __global__ __launch_bounds__(kBlock) void plane_decompress_k(SRC src, int W, flo
             const PayloadHeader *h = reinterpret_cast<const PayloadHeader *>(x.pl[b]);
             x.scale[b] = x.scale_lo[b] = 0.0f;
             if (w0 + b < W) {
-                x.scale[b] = ld_uniform(&h->scale);
-                if (!TERN) x.scale_lo[b] = __uint_as_float(ld_uniform(&h->pad[0]));
+                if (TERN || kind != PLANE_VOTE) x.scale[b] = ld_uniform(&h->scale);
+                if (!TERN && kind == PLANE_MEANS) x.scale_lo[b] = __uint_as_float(ld_uniform(&h->pad[0]));
             }
         }
 #pragma unroll
