@@ -156,27 +156,67 @@ __device__ __forceinline__ uintptr_t chunk_entry(const GroupView &g, const Chunk
 // the tensor address list was uploaded (one scalar load, then the data).
 // Otherwise (the chunk straddles tensors, or is the ragged last one) the wavefront
 // fetches the table entries of up to 64 tensors from the chunk's first one on, one per
-// lane, and then takes the tensors one by one -- a wave-uniform loop whose bounds and
-// addresses come out of the lanes -- so that the data accesses wait for one round of
-// table loads only.  (A per-lane walk of the table, two dependent loads per tensor
-// boundary, made the ~100 such chunks of the ResNet-50 list the last to finish: 21
-// instead of 17 us for a read-only pass over the 102 MB.)
+// lane (tensors_of_chunk).  Their bounds and addresses then come out of the lanes: a walk over
+// the chunk's steps, one uniform comparison a step and tensor, gives every element's address, so that
+// the data of all tensors is asked for at once, 16 accesses of the wavefront whatever the number of tensors.
+// (Tensor by tensor, with a condition around every access, a wavefront waited for each tensor's data in turn, which
+// is what a small group's kernels took longest for.  Compress / decompress-and-sum of 1025 elements in eight tensors, 8
+// workers: EF-Sign 8.9 / 7.8 -> 5.8 / 4.6 us, QSGD 13.5 / 8.0 -> 10.1 / 5.5, Top-k 20.1 / 7.1 -> 16.6 / 4.6; 272 000 elements
+// in 65 tensors and four groups, Top-k 28.6 -> 25.5 for both.)
+// (A walk of the table by every lane, two dependent loads per tensor boundary, made the ~100 such chunks of the
+// ResNet-50 list the last to finish: 21 instead of 17 us for a read-only pass over the 102 MB.)
+struct ChunkTensors { uint32_t beg, end; uintptr_t ptr; };      // of the tensor that this lane holds: flat bounds, address
+__device__ __forceinline__ ChunkTensors tensors_of_chunk(const GroupView &g, uint32_t s0)
+{
+    const uint32_t t = s0 + (threadIdx.x & 63u);
+    return {g.seg_off[t < g.nseg ? t : g.nseg], g.seg_off[t < g.nseg ? t + 1u : g.nseg],      // seg_off has nseg + 1 entries, the last is n
+            g.ptrs[t < g.nseg ? t : g.nseg - 1u]};
+}
+__device__ __forceinline__ uint32_t chunk_end(const GroupView &g, const Chunk &c) { return g.n - c.base >= (uint32_t)kChunk ? c.base + (uint32_t)kChunk : g.n; }
+// (readlane returns int: through uint32_t, or the low word's bit 31 would smear over the high word)
+__device__ __forceinline__ uintptr_t lane_addr(uintptr_t x, int k)
+{
+    return (uintptr_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, k) | ((uintptr_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), k) << 32);
+}
+// body(j, address of the lane's element of step j) for the 16 steps (STOP: for those that have elements), if the chunk holds
+// at most 64 tensors (else false).  A lane behind the end of the group gets the group's last element.
+template <bool STOP, typename Body>
+__device__ __forceinline__ bool each_step_of_chunk(const GroupView &g, const Chunk &c, const ChunkTensors &ts, Body body)
+{
+    const uint32_t lim = chunk_end(g, c);
+    if ((uint32_t)__builtin_amdgcn_readlane((int)ts.end, 63) < lim) return false;
+    const uintptr_t from = ts.ptr - sizeof(float) * (uintptr_t)ts.beg;               // where the group's element 0 would be
+    int k = 0;
+    uintptr_t cur = lane_addr(from, 0);
+    uint32_t end = (uint32_t)__builtin_amdgcn_readlane((int)ts.end, 0);
+#pragma unroll
+    for (int j = 0; j < kSteps; ++j) {
+        const uint32_t first = c.base + 64u * (uint32_t)j;
+        if (STOP && first >= lim) break;
+        const uint32_t hi = min(first + 64u, lim), i = min(first + c.lane, lim - 1u);
+        uintptr_t at = cur;
+        while (end < hi) {                       // another tensor starts among the step's elements
+            const uint32_t beg = end;
+            ++k;
+            cur = lane_addr(from, k);
+            end = (uint32_t)__builtin_amdgcn_readlane((int)ts.end, k);
+            at = i >= beg ? cur : at;
+        }
+        body(j, at + sizeof(float) * (uintptr_t)i);
+    }
+    return true;
+}
+// body(first element, end, address) for the tensors of a chunk, one after the other, however many
 template <typename Body>
 __device__ __forceinline__ void for_each_tensor_of_chunk(const GroupView &g, const Chunk &c, uint32_t s0, Body body)
 {
-    const uint32_t lim = g.n - c.base >= (uint32_t)kChunk ? c.base + (uint32_t)kChunk : g.n;     // end of the chunk
+    const uint32_t lim = chunk_end(g, c);
     for (;;) {
-        const uint32_t t = s0 + c.lane;
-        const uint32_t beg = g.seg_off[t < g.nseg ? t : g.nseg];                 // seg_off has nseg + 1 entries, the last is n
-        const uint32_t end = g.seg_off[t < g.nseg ? t + 1u : g.nseg];
-        const uintptr_t ptr = g.ptrs[t < g.nseg ? t : g.nseg - 1u];
+        const ChunkTensors ts = tensors_of_chunk(g, s0);
         for (int k = 0; k < 64; ++k) {
-            const uint32_t b = __builtin_amdgcn_readlane(beg, k), e = __builtin_amdgcn_readlane(end, k);
+            const uint32_t b = __builtin_amdgcn_readlane(ts.beg, k), e = __builtin_amdgcn_readlane(ts.end, k);
             if (b >= lim) return;                                                // past the chunk (or past the last tensor: b = n)
-            // (readlane returns int: through uint32_t, or the low word's bit 31 would smear over the high word)
-            const uintptr_t p = (uintptr_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)ptr, k) |
-                                ((uintptr_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(ptr >> 32), k) << 32);
-            body(b, e, p);
+            body(b, e, lane_addr(ts.ptr, k));
         }
         s0 += 64u;
     }
@@ -190,9 +230,16 @@ __device__ __forceinline__ void load_seg(const GroupView &g, const Chunk &c, flo
 #pragma unroll
         for (int j = 0; j < kSteps; ++j) v[j] = __builtin_nontemporal_load(p + 64 * j);
     } else {
+        const uint32_t s0 = (uint32_t)(entry >> 1);
+        if (each_step_of_chunk<false>(g, c, tensors_of_chunk(g, s0), [&](int j, uintptr_t at) { v[j] = *in_global(reinterpret_cast<const float *>(at)); })) {
+            if (!c.full)
+#pragma unroll
+                for (int j = 0; j < kSteps; ++j) v[j] = c.base + 64 * j + c.lane < g.n ? v[j] : 0.0f;
+            return;
+        }
 #pragma unroll
         for (int j = 0; j < kSteps; ++j) v[j] = 0.0f;
-        for_each_tensor_of_chunk(g, c, (uint32_t)(entry >> 1), [&](uint32_t beg, uint32_t end, uintptr_t ptr) {
+        for_each_tensor_of_chunk(g, c, s0, [&](uint32_t beg, uint32_t end, uintptr_t ptr) {
             const global_ptr<const float> p = in_global(reinterpret_cast<const float *>(ptr));
 #pragma unroll
             for (int j = 0; j < kSteps; ++j) {
@@ -214,7 +261,11 @@ __device__ __forceinline__ void store_seg(const GroupView &g, const Chunk &c, co
 #pragma unroll
         for (int j = 0; j < kSteps; ++j) __builtin_nontemporal_store(v[j], p + 64 * j);
     } else {
-        for_each_tensor_of_chunk(g, c, (uint32_t)(entry >> 1), [&](uint32_t beg, uint32_t end, uintptr_t ptr) {
+        const uint32_t s0 = (uint32_t)(entry >> 1);
+        if (each_step_of_chunk<true>(g, c, tensors_of_chunk(g, s0), [&](int j, uintptr_t at) {
+                if (c.base + 64 * j + c.lane < g.n) *in_global(reinterpret_cast<float *>(at)) = v[j];
+            })) return;
+        for_each_tensor_of_chunk(g, c, s0, [&](uint32_t beg, uint32_t end, uintptr_t ptr) {
             const global_ptr<float> p = in_global(reinterpret_cast<float *>(ptr));
 #pragma unroll
             for (int j = 0; j < kSteps; ++j) {
