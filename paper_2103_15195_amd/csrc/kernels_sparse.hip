@@ -1019,9 +1019,9 @@ __device__ __forceinline__ uint32_t select_tile(const SparseScratch &sc, TileAhe
 }
 
 // Emit, lean route.  One candidate per lane (a chunk's head): gt0 / eq0 count the keys above / equal to T before it
-// in the whole group; returns them advanced past these 64.
+// in the whole group; they are advanced past these 64.  Returns whether the lane's candidate was kept.
 template <int ALGO, bool EF>
-__device__ __forceinline__ void emit_head(uint32_t bits, uint32_t loc, bool valid, uint32_t chunk, uint32_t n, uint32_t k, float *st,
+__device__ __forceinline__ bool emit_head(uint32_t bits, uint32_t loc, bool valid, uint32_t chunk, uint32_t n, uint32_t k, float *st,
                                           uint32_t *idx, float *val, uint32_t T, uint32_t need, uint32_t &gt0, uint32_t &eq0)
 {
     const uint32_t key = bits & 0x7FFFFFFFu;
@@ -1029,7 +1029,8 @@ __device__ __forceinline__ void emit_head(uint32_t bits, uint32_t loc, bool vali
     const uint64_t bgt = __builtin_amdgcn_ballot_w64(is_gt), beq = __builtin_amdgcn_ballot_w64(is_eq);
     const uint32_t gtb = gt0 + lanes_below(bgt);
     const uint32_t eqb = eq0 + lanes_below(beq);
-    if (is_gt || (is_eq && eqb < need)) {
+    const bool keep = is_gt || (is_eq && eqb < need);
+    if (keep) {
         const uint32_t pos = gtb + (eqb < need ? eqb : need);
         const uint32_t i = chunk * (uint32_t)kChunk + loc;
         if (pos < k && i < n) {                  // always true for consistent scratch
@@ -1040,6 +1041,7 @@ __device__ __forceinline__ void emit_head(uint32_t bits, uint32_t loc, bool vali
         }
     }
     gt0 += __popcll(bgt); eq0 += __popcll(beq);
+    return keep;
 }
 
 // ... four consecutive candidates per lane (a unit; it holds at most 256 keys above T and as many equal to it)
@@ -1318,6 +1320,90 @@ __device__ __forceinline__ void slow_routes(const SparseJob &job, const RngKey &
     }
 }
 
+// ---- the verdict of the window, by a block of 1024 threads --------------------------------------------------------
+// The bin b with  count(bins > b) < k <= count(bins >= b), by a suffix scan over the block's threads, two bins each (the
+// counts stay below 2^32, there being fewer elements than that).
+struct WindowPart { uint32_t lower, upper, above; };      // the thread's two bins; they and all above in its wavefront
+// open: the copies of the open last bin, one per lane of the last wavefront.  CLEAR: what is read is set to 0.
+// Behind a barrier wtot holds the wavefronts' sums.
+template <bool CLEAR>
+__device__ __forceinline__ WindowPart read_window(const SparseScratch &sc, uint32_t open, uint32_t *wtot)
+{
+    const uint32_t t = threadIdx.x, lane = t & 63u, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    uint2 wsum = {0u, 0u};                       // window bins 2 t and 2 t + 1
+#pragma unroll
+    for (int r = 0; r < kWinCopies; ++r) {
+        const uint2 x = *reinterpret_cast<const uint2 *>(sc.hist + kHistW + r * kBinsW + 2 * t);
+        wsum.x += x.x; wsum.y += x.y;
+    }
+    if (CLEAR) {
+#pragma unroll
+        for (int r = 0; r < kWinCopies; ++r) *reinterpret_cast<uint2 *>(sc.hist + kHistW + r * kBinsW + 2 * t) = uint2{0u, 0u};
+        if (wave == kSelWaves - 1) sc.hist[kHistOpen + lane] = 0u;
+    }
+    if (wave == kSelWaves - 1) {
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) open += __shfl_xor(open, d, 64);
+        if (lane == 63u) wsum.y += open;         // the last bin also counts every key above the window
+    }
+    const uint32_t pair = wsum.x + wsum.y;
+    const uint32_t pre = wave_scan_incl(pair);
+    const uint32_t suf = wave_total(pre) - pre + pair;  // inclusive suffix sum: this thread's bins and all above
+    if (lane == 0) wtot[wave] = suf;
+    return {wsum.x, wsum.y, suf};
+}
+// verdict (8 words of LDS; [0] is 0): found, bin, entries to take from it (64 bits), candidates (64 bits), keys in the bin
+__device__ __forceinline__ void find_bin(const WindowPart &part, uint64_t k, const uint32_t *wtot, uint32_t *verdict)
+{
+    const uint32_t t = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(t >> 6), pair = part.lower + part.upper;
+    uint32_t suf = part.above, higher = 0, all = 0;      // candidates in the wavefronts after this one; all candidates
+#pragma unroll
+    for (int w = 0; w < kSelWaves; ++w) { if ((uint32_t)w > wave) higher += wtot[w]; all += wtot[w]; }
+    suf += higher;
+    if ((uint64_t)suf >= k && (uint64_t)(suf - pair) < k) {      // the count crosses k in one of this thread's two bins
+        const uint32_t above = suf - pair;
+        const bool upper = (uint64_t)above + part.upper >= k;
+        const uint64_t rest = k - above - (upper ? 0u : part.upper);
+        verdict[0] = 1u; verdict[1] = 2u * t + (upper ? 1u : 0u); verdict[2] = (uint32_t)rest; verdict[3] = 0u;
+        verdict[6] = upper ? part.upper : part.lower;
+    }
+    if (t == 0) { verdict[4] = all; verdict[5] = 0u; }
+}
+// The route, where it starts and how many entries it has to find; the group's first thread writes down what the next calls need.
+__device__ __forceinline__ void record_verdict(const SparseJob &job, const uint32_t *verdict, uint32_t hint, uint32_t hint_shift, uint32_t hint_hold,
+                                               uint32_t hint_cap, uint32_t &mode, uint32_t &lo, uint64_t &need)
+{
+    const SparseScratch &sc = job.sc;
+    const uint64_t k = job.k;
+    const bool found = verdict[0] != 0u;
+    const uint32_t bin = verdict[1];
+    const bool first = job.block == 0 && threadIdx.x == 0, fresh = first_call(hint, hint_cap);
+    if (first && job.reports) {
+        sc.sync[kSyncLastBin] = fresh ? job.g.n : found ? verdict[6] : 0u;          // diagnostics (mc_select_stats); before a first call
+        sc.sync[kSyncLastCands] = fresh ? job.g.n : verdict[4];                     // nothing is filtered out
+    }
+    mode = found ? 0u : kModeUniform | (fresh ? kModeFirst : 0u);
+    lo = found ? hint + (((uint32_t)kBinsW - 1u) << kWindowShift) : 0u;
+    need = k;
+    if (found && bin < (uint32_t)kBinsW - 1u) {
+        lo = hint + (bin << kWindowShift);
+        need = (uint64_t)verdict[2] | ((uint64_t)verdict[3] << 32);
+        const bool lean = verdict[6] <= kUCap;
+        mode = kModeFast | (lean ? kModeLean : kModeDense);
+        if (first) margin_after_hit(sc.hint, hint_shift, hint_hold, hint_cap, (uint64_t)verdict[4] | ((uint64_t)verdict[5] << 32), k);
+    } else if (first) {
+        // missed: the next calls filter with the full margin again, and keep it for a while
+        margin_after_miss(sc.hint, hint_shift, hint_cap, !found && !fresh);
+    }
+    if (first) {
+        SelectState s;
+        s.lo = lo; s.mode = mode; s.need = need;
+        sc.sel[0] = s;
+        const uint32_t route = (mode & kModeLean) ? MC_SELECT_FAST : (mode & kModeDense) ? MC_SELECT_DENSE : found || fresh ? MC_SELECT_ABOVE : MC_SELECT_REFILL;
+        atomicAdd(&sc.sync[kSyncRoutes + route], 1u);
+    }
+}
+
 // The select kernel: sixteen tiles per block, one wavefront each; the window is read once per block.  When the window does
 // not settle the selection, the group's first blocks go on with the slow routes, which wait for one another: blocks
 // start in the order of their numbers, so at most `sync_blocks` of them -- one per compute unit -- are held at once whatever
@@ -1344,64 +1430,14 @@ __global__ __launch_bounds__(kSelThreads) void lean_select_k(SRC src, RngKey rng
     look_ahead(sc, tile, tile < ntiles, a0);
     const uint32_t hint = *sc.hint, hint_shift = sc.hint[kHintShift], hint_hold = sc.hint[kHintHold], hint_cap = sc.hint[kHintCap];
     uint32_t open = wave == kSelWaves - 1 ? sc.hist[kHistOpen + lane] : 0u;      // (the wavefront that holds the window's last bin)
-    uint2 wsum = {0u, 0u};                       // window bins 2 t and 2 t + 1
-#pragma unroll
-    for (int r = 0; r < kWinCopies; ++r) {
-        const uint2 x = *reinterpret_cast<const uint2 *>(sc.hist + kHistW + r * kBinsW + 2 * t);
-        wsum.x += x.x; wsum.y += x.y;
-    }
-    // ---- the verdict: the bin b with  count(bins > b) < k <= count(bins >= b), by a suffix scan over the block's
-    // threads (two bins each; the counts stay below 2^32, there being fewer elements than that)
-    if (wave == kSelWaves - 1) {
-#pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) open += __shfl_xor(open, d, 64);
-        if (lane == 63u) wsum.y += open;         // the last bin also counts every key above the window
-    }
-    const uint32_t pair = wsum.x + wsum.y;
-    const uint32_t pre = wave_scan_incl(pair);
-    uint32_t suf = wave_total(pre) - pre + pair;  // inclusive suffix sum: this thread's bins and all above
-    if (lane == 0) wtot[wave] = suf;
+    const WindowPart part = read_window<false>(sc, open, wtot);
     if (t == 0) verdict[0] = 0u;
     __syncthreads();
-    uint32_t higher = 0, all = 0;                // candidates in the wavefronts after this one; all candidates
-#pragma unroll
-    for (int w = 0; w < kSelWaves; ++w) { if ((uint32_t)w > wave) higher += wtot[w]; all += wtot[w]; }
-    suf += higher;
-    if ((uint64_t)suf >= k && (uint64_t)(suf - pair) < k) {      // the count crosses k in one of this thread's two bins
-        const uint32_t above = suf - pair;
-        const bool upper = (uint64_t)above + wsum.y >= k;
-        const uint64_t rest = k - above - (upper ? 0u : wsum.y);
-        verdict[0] = 1u; verdict[1] = 2u * t + (upper ? 1u : 0u); verdict[2] = (uint32_t)rest; verdict[3] = 0u;
-        verdict[6] = upper ? wsum.y : wsum.x;
-    }
-    if (t == 0) { verdict[4] = all; verdict[5] = 0u; }
+    find_bin(part, k, wtot, verdict);
     __syncthreads();
-    const bool found = verdict[0] != 0u;
-    const uint32_t bin = verdict[1];
-    const bool first = job.block == 0 && t == 0, fresh = first_call(hint, hint_cap);
-    if (first && job.reports) {
-        sc.sync[kSyncLastBin] = fresh ? job.g.n : found ? verdict[6] : 0u;          // diagnostics (mc_select_stats); before a first call
-        sc.sync[kSyncLastCands] = fresh ? job.g.n : verdict[4];                     // nothing is filtered out
-    }
-    uint32_t mode = found ? 0u : kModeUniform | (fresh ? kModeFirst : 0u), lo = found ? hint + (((uint32_t)kBinsW - 1u) << kWindowShift) : 0u;
-    uint64_t need = k;
-    if (found && bin < (uint32_t)kBinsW - 1u) {
-        lo = hint + (bin << kWindowShift);
-        need = (uint64_t)verdict[2] | ((uint64_t)verdict[3] << 32);
-        const bool lean = verdict[6] <= kUCap;
-        mode = kModeFast | (lean ? kModeLean : kModeDense);
-        if (first) margin_after_hit(sc.hint, hint_shift, hint_hold, hint_cap, (uint64_t)verdict[4] | ((uint64_t)verdict[5] << 32), k);
-    } else if (first) {
-        // missed: the next calls filter with the full margin again, and keep it for a while
-        margin_after_miss(sc.hint, hint_shift, hint_cap, !found && !fresh);
-    }
-    if (first) {
-        SelectState s;
-        s.lo = lo; s.mode = mode; s.need = need;
-        sc.sel[0] = s;
-        const uint32_t route = (mode & kModeLean) ? MC_SELECT_FAST : (mode & kModeDense) ? MC_SELECT_DENSE : found || fresh ? MC_SELECT_ABOVE : MC_SELECT_REFILL;
-        atomicAdd(&sc.sync[kSyncRoutes + route], 1u);
-    }
+    uint32_t mode, lo;
+    uint64_t need;
+    record_verdict(job, verdict, hint, hint_shift, hint_hold, hint_cap, mode, lo, need);
     if (mode & kModeLean) {
         uint32_t above = 0;
         if (tile < ntiles) {
@@ -1642,6 +1678,125 @@ __global__ __launch_bounds__(kEmitThreads) void lean_emit_k(SRC src)
     }
 }
 
+// ---------------------------------------------------------------------------
+// Select and emit of a small group (kSmallSelTiles tiles, kSmallKept entries) in one kernel, one block per group.  On such a
+// group the two kernels do next to nothing but start, read the window and wait for two levels of loads, each.  One
+// block can hold all candidates, 16 per thread in index order, and needs no list and no counts in memory: the
+// window's verdict, a histogram of the threshold's bin in LDS, a scan over the block's wavefronts, and the entries are
+// written.  The candidates are asked for as soon as the chunks' counts are known, while the verdict is found.
+// (Compress, 1025 / 34 000 / 131 000 elements: Top-k 1 % 18.7 / 17.1 / 17.2 -> 13.1 / 13.4 / 16.0 us, 5 % 20.5 / 23.3 / 23.5 -> 13.6 /
+// 17.4 / 23.2, DGC 0.1 % 18.4 / 16.6 / 16.9 -> 13.8 / 13.5 / 13.9, Rand-k 26.7 / 28.1 / 21.2 -> 19.8 / 22.5 / 20.4; 272 000 elements in
+// four groups, Top-k 1 % with the decompress-and-sum 25.5 -> 22.5.)
+// What the window does not settle, or more candidates than the block holds, goes the way of the slow routes, alone.
+// ---------------------------------------------------------------------------
+constexpr int kSmallRounds = 16;                 // candidates per thread
+static_assert(kSmallSelTiles <= 64 && kSmallKept * 5u / 2u <= (uint32_t)kSmallRounds * kSelThreads, "");
+
+template <int ALGO, bool EF, class SRC>
+__global__ __launch_bounds__(kSelThreads) void lean_small_k(SRC src, RngKey rng, int *status)
+{
+    __shared__ __attribute__((aligned(16))) uint32_t hist[kBins1];
+    __shared__ uint32_t pfx[2 * kRoundTiles];    // (slow routes)
+    __shared__ uint32_t small[64];
+    __shared__ uint32_t wtot[kSelWaves], verdict[8];
+    __shared__ uint32_t from[kSmallSelTiles * kWavesPerBlock + 1];      // candidates of the group before each chunk
+    __shared__ uint32_t kept[kSmallSelTiles];    // entries in each tile
+    const SparseJob job = src.group_job(blockIdx.x);
+    const uint32_t n = job.g.n;
+    if (n == 0) return;
+    const uint32_t t = threadIdx.x, lane = t & 63u, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const SparseScratch &sc = job.sc;
+    const uint32_t k = (uint32_t)job.k, ntiles = tiles_in(n);
+    const uint64_t runs = wave == 0 && lane < ntiles ? sc.tile_runs[lane] : 0ull;
+    const uint32_t hint = *sc.hint, hint_shift = sc.hint[kHintShift], hint_hold = sc.hint[kHintHold], hint_cap = sc.hint[kHintCap];
+    const uint32_t open = wave == kSelWaves - 1 ? sc.hist[kHistOpen + lane] : 0u;
+    const WindowPart part = read_window<true>(sc, open, wtot);
+    for (int b = t; b < kBins3; b += kSelThreads) hist[b] = 0u;
+    if (t == 0) verdict[0] = 0u;
+    if (wave == 0) {
+        const uint32_t total = runs_total(runs), incl = wave_scan_incl(total);
+        if (lane < (uint32_t)kSmallSelTiles) {
+            uint32_t at = incl - total;
+#pragma unroll
+            for (int q = 0; q < kWavesPerBlock; ++q) { from[kWavesPerBlock * lane + q] = at; at += (uint32_t)(runs >> (16 * q)) & 0xFFFFu; }
+            kept[lane] = 0u;
+            if (lane == kSmallSelTiles - 1u) from[kWavesPerBlock * kSmallSelTiles] = at;
+        }
+    }
+    __syncthreads();
+    // Candidates wave * 64 rounds ... of the group are the wavefront's, 64 a round.
+    const uint32_t N = from[kWavesPerBlock * kSmallSelTiles];
+    const uint32_t rounds = (N + kSelThreads - 1u) / kSelThreads, first = wave * 64u * rounds + lane;
+    const bool fits = rounds <= (uint32_t)kSmallRounds;
+    uint32_t bits[kSmallRounds], at[kSmallRounds];
+    if (fits) {
+#pragma unroll
+        for (int r = 0; r < kSmallRounds; ++r) {
+            if ((uint32_t)r >= rounds) break;
+            const uint32_t p = min(first + 64u * r, N - 1u);
+            uint32_t ch = 0;                     // the last chunk that starts at or before p
+#pragma unroll
+            for (uint32_t step = kWavesPerBlock * kSmallSelTiles / 2; step >= 1; step >>= 1) if (from[ch + step] <= p) ch += step;
+            const uint32_t slot = ch * (uint32_t)kChunk + (p - from[ch]);
+            bits[r] = sc.cand_bits[slot];
+            at[r] = ch * (uint32_t)kChunk + sc.cand_loc[slot];
+        }
+    }
+    find_bin(part, k, wtot, verdict);
+    __syncthreads();
+    uint32_t mode, lo;
+    uint64_t need64;
+    record_verdict(job, verdict, hint, hint_shift, hint_hold, hint_cap, mode, lo, need64);
+    if (!(mode & kModeLean) || !fits) {
+        if (mode & kModeLean) mode = kModeFast | kModeDense;
+        slow_routes<ALGO, EF, ALGO == MC_ALGO_DGC || EF, ALGO == MC_ALGO_RANDK>(job, rng, mode, lo, need64, 1u, status, hist, pfx, small);
+        return;
+    }
+    // ---- the threshold key, and the number of keys equal to it to take
+#pragma unroll
+    for (int r = 0; r < kSmallRounds; ++r) {
+        if ((uint32_t)r >= rounds) break;
+        const uint32_t key = bits[r] & 0x7FFFFFFFu;
+        if (first + 64u * r < N && key >= lo && key - lo < (uint32_t)kBins3) atomicAdd(&hist[key - lo], 1u);
+    }
+    __syncthreads();
+    uint32_t bin;
+    resolve_block<kBins3>(hist, need64, bin, need64, small, small + 8);
+    const uint32_t T = lo + bin, need = (uint32_t)need64;
+    // ---- keys above / equal to it before this wavefront's (16 bits each: there are 16384 candidates at most)
+    uint32_t both = 0;
+#pragma unroll
+    for (int r = 0; r < kSmallRounds; ++r) {
+        if ((uint32_t)r >= rounds) break;
+        const uint32_t key = bits[r] & 0x7FFFFFFFu;
+        const bool valid = first + 64u * r < N;
+        both += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(valid && key > T)) + ((uint32_t)__popcll(__builtin_amdgcn_ballot_w64(valid && key == T)) << 16);
+    }
+    if (lane == 0) wtot[wave] = both;
+    __syncthreads();
+    const uint32_t v = lane < (uint32_t)kSelWaves ? wtot[lane] : 0u, before = (uint32_t)__builtin_amdgcn_readlane((int)(wave_scan_incl(v) - v), (int)wave);
+    uint32_t gt0 = before & 0xFFFFu, eq0 = before >> 16;
+    uint32_t *idx = reinterpret_cast<uint32_t *>(reinterpret_cast<uint8_t *>(job.hdr) + kHeaderBytes);
+    float *val = reinterpret_cast<float *>(idx + k);
+#pragma unroll
+    for (int r = 0; r < kSmallRounds; ++r) {
+        if ((uint32_t)r >= rounds) break;
+        if (emit_head<ALGO, EF>(bits[r], at[r], first + 64u * r < N, 0u, n, k, job.st, idx, val, T, need, gt0, eq0)) atomicAdd(&kept[at[r] / (uint32_t)kTile], 1u);
+    }
+    __syncthreads();
+    if (wave == 0) {
+        const uint32_t own = lane < (uint32_t)kSmallSelTiles ? kept[lane] : 0u, incl = wave_scan_incl(own);
+        uint32_t *dir = payload_directory(job.hdr, k);
+        if (lane < ntiles) dir[lane] = incl - own;
+        if (lane == 0) {
+            dir[ntiles] = k;                     // (the selection keeps exactly k)
+            put_sparse_header(job.hdr, ALGO, n, k);
+            publish_hint(sc, T);
+            record_sent_key<ALGO, EF>(job.st, T);
+        }
+    }
+}
+
 template <int ALGO, bool EF, class SRC>
 static void sparse_compress_t(const LaunchCtx &lc, const SRC &src, const SparseBlocks &nb, const SparseCall &call)
 {
@@ -1649,6 +1804,12 @@ static void sparse_compress_t(const LaunchCtx &lc, const SRC &src, const SparseB
     prof_begin(lc, K_SPARSE_ACCUM);
     MC_LAUNCH((sparse_accum_k<ALGO, EF, SRC>), dim3(nb.tiles), dim3(kBlock), lc, src, call.momentum, rng, (SampleRule{0u, 0u, 0u}));
     prof_end(lc, K_SPARSE_ACCUM);
+    if (nb.small) {
+        prof_begin(lc, K_LEAN_SELECT);
+        MC_LAUNCH((lean_small_k<ALGO, EF, SRC>), dim3(nb.small), dim3(kSelThreads), lc, src, rng, call.status);
+        prof_end(lc, K_LEAN_SELECT);
+        return;
+    }
     // the two-kernel tail; its slow routes run on blocks that the device holds at once: one per compute unit
     const uint32_t sync = std::max(1u, std::min(call.sync_blocks, (uint32_t)(kRoundTiles / kSelWaves)));
     prof_begin(lc, K_LEAN_SELECT);

@@ -118,6 +118,7 @@ struct mc_ctx {
     uint32_t *d_block_group[BLK_KINDS] = {};
     uint32_t all_blocks[BLK_KINDS] = {};
     uint32_t last_group = 0;            // the last group that holds elements
+    bool all_select_small = true;       // sparsifiers: every group's selection is one block's
     size_t all_live = 0;
     uint32_t all_subs = 0;              // sublists of keys of all groups' scratch
     std::vector<int64_t> tensor_numel;  // elements of every tensor of the model
@@ -581,6 +582,7 @@ int mc_ctx_create(mc_ctx **out, const mc_config *cfg, const int64_t *numel, int3
             for (int b = 0; b < BLK_KINDS; ++b) ctx->all_blocks[b] += blocks[b];
             ctx->all_subs += std::min<uint32_t>(blocks[BLK_TILE], kUSub);
             ctx->all_live += g.live.size();
+            ctx->all_select_small = ctx->all_select_small && selects_small(g.n, g.k);
             if (g.n) ctx->last_group = (uint32_t)(&g - ctx->groups.data());
         }
         if (rc == MC_OK) {
@@ -832,7 +834,9 @@ static int compress_impl(mc_ctx *ctx, int32_t group, uint32_t worker, uint64_t i
         call.sample_first = first;
         call.sample_need = m ? std::max<uint64_t>(1, (uint64_t)(((unsigned __int128)m * cfg.ratio_ppm) / 1000000u)) : 0;
     }
-    launch_sparse_compress(lc, cfg.algo, OneSparse{gv, sf, hdr, G.k, sp}, sparse_blocks(n), ef, call);
+    SparseBlocks nb = sparse_blocks(n);
+    if (selects_small(n, G.k) && !(prof && prof->on)) nb.small = 1;
+    launch_sparse_compress(lc, cfg.algo, OneSparse{gv, sf, hdr, G.k, sp}, nb, ef, call);
     return check_launch();
 }
 
@@ -878,7 +882,8 @@ static int compress_all(mc_ctx *ctx, uint32_t worker, uint64_t iter, const float
         const SparseScratch last = scratch_of(sp, ctx->last_group, ctx->first_tile[ctx->last_group], ctx->first_sub[ctx->last_group]);
         ctx->last_hint = last.hint;
         ctx->last_sel = last.sel;
-        const SparseBlocks nb{ctx->all_blocks[BLK_TILE], ctx->all_blocks[BLK_SELECT], ctx->all_blocks[BLK_EMIT]};
+        const SparseBlocks nb{ctx->all_blocks[BLK_TILE], ctx->all_blocks[BLK_SELECT], ctx->all_blocks[BLK_EMIT],
+                              ctx->all_select_small && !ctx->prof.on ? (uint32_t)y : 0u};
         launch_sparse_compress(lc, cfg.algo, AllSparse{tb, sp, ctx->last_group}, nb, ef, sparse_call(ctx, worker, iter));
     } else dense_compress(cfg, lc, AllCompress{tb, ctx->d_partial, ctx->d_arrive}, ctx->all_blocks[BLK_TILE], (uint32_t)y, ctx->max_tiles, worker,
                         (uint32_t)iter, ctx->wait_looks);

@@ -344,6 +344,7 @@ struct OneSparse {
     PayloadHeader *hdr;
     uint64_t k;
     SparseScratch sc;
+    __device__ __forceinline__ SparseJob group_job(uint32_t) const { return {g, st, hdr, k, sc, 0u, 1u, true}; }
     template <int KIND> __device__ __forceinline__ SparseJob job() const
     {
         return {g, st, hdr, k, sc, KIND == BLK_TILE ? my_tile_index() : blockIdx.x, gridDim.x, true};
@@ -381,7 +382,13 @@ struct SparseCall {
     uint32_t sample_stride = 0, sample_first = 0;      // DGC with a sampled threshold (one group only)
     uint64_t sample_need = 0;
 };
-struct SparseBlocks { uint32_t tiles, select, emit; };          // blocks of each kind that the launches cover
+// Groups whose selection one block finishes (lean_small_k).  A block of 1024 threads holds 16384 candidates; under the filter's
+// rules there are about 2 k, 2.5 leave room.  At both limits together (32 tiles, 5 %) the block takes as long as the two kernels,
+// 23.2 against 23.5 us, below either it is ahead.
+constexpr int kSmallSelTiles = 32;
+constexpr uint32_t kSmallKept = 6144;
+inline bool selects_small(uint32_t n, uint64_t k) { return tiles_in(n) <= (uint32_t)kSmallSelTiles && k <= kSmallKept; }
+struct SparseBlocks { uint32_t tiles, select, emit, small = 0; };          // blocks of each kind that the launches cover; small: groups, if all are such
 inline SparseBlocks sparse_blocks(uint32_t n)
 {
     const uint32_t t = tiles_in(n);

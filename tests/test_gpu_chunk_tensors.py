@@ -4,7 +4,7 @@ wavefront's steps of 64 elements, and last chunks of one element, of whole steps
 import numpy as np
 import pytest
 
-from tests.harness import run_parity
+import harness as H
 
 pytestmark = pytest.mark.gpu
 LISTS = {
@@ -26,5 +26,5 @@ LISTS = {
 def test_tensors_of_a_chunk(algo, name):
     numel = LISTS[name]
     rng = np.random.default_rng(len(numel))
-    run_parity(numel, algo, 1, 3, 3, lambda w, it: rng.standard_normal(sum(numel)).astype(np.float32), layout="misaligned" if len(numel) % 2 else "separate",
-               ratio_ppm=100000)
+    H.run_parity(numel, algo, 1, 3, 3, lambda w, it: rng.standard_normal(sum(numel)).astype(np.float32), layout="misaligned" if len(numel) % 2 else "separate",
+                 ratio_ppm=100000)
