@@ -714,8 +714,8 @@ template void launch_tern_encode<AllCompress>(const LaunchCtx &, const AllCompre
 // The two-pass quantizers on a small group, in one kernel: p stays in registers between the passes, and in place of the two
 // kernel boundaries the group's blocks (64 at most, which start one after the other and fit a fraction of the device)
 // wait until all have put their partial.
-// (QSGD compress, 1 .. 64 tiles: 11.7 .. 13.2 -> 8.6 .. 10.0 us, TernGrad 11.8 -> 9.2 .. 10.3; eight groups of 34 k
-// elements in one launch, QSGD with the decompress-and-sum: 29.0 -> 22.6.)
+// (Against a kernel per pass, before a tile was spread over more threads: QSGD compress, 1 .. 64 tiles, 11.7 .. 13.2 -> 8.6 ..
+// 10.0 us, TernGrad 11.8 -> 9.2 .. 10.3.)
 // No block has to be running for another to finish: one that has looked `looks` times in vain (the rest of the group has
 // found no room on the device for about a millisecond) hands its tile over and leaves, and the block that arrives last,
 // which never waits, encodes what was handed over besides its own.  (That a block may go round for another tile costs
@@ -732,33 +732,134 @@ __device__ __forceinline__ uint64_t hand_over(const CompressJob &job, uint64_t a
     return __hip_atomic_fetch_and(job.handed_over(), ~bit, __ATOMIC_SEQ_CST, __HIP_MEMORY_SCOPE_AGENT) & bit;
 }
 
-template <bool EF, int MODE, class SRC>
-__global__ __launch_bounds__(kBlock) void quantize_small_k(SRC src, uint32_t levels, uint64_t seed, uint32_t worker, uint32_t iter_lo, uint32_t looks)
+// The chip is nearly idle on such groups and a block takes as long as one wavefront's instructions do, so a tile is spread over
+// 1024 threads, four consecutive elements each: one Philox block per draw of a thread, a word of codes or a nibble of either
+// plane to store, and a quarter of the instructions that 16 elements per lane took.  The draws of the call itself are
+// made while the partials travel.  (Compress, 1025 / 34 000 / 262 000 elements: QSGD
+// 10.3 / 10.4 / 10.5 -> 5.2 / 6.0 / 6.4 us, TernGrad 10.1 / 10.5 / 10.6 -> 4.8 / 5.5 / 5.9; 40 tensors in 1025 elements 30.6 -> 7.3; 272 000 in
+// eight groups, QSGD 13.0 -> 7.1; 6 M in 64 groups, TernGrad 35.0 -> 28.9.)
+constexpr int kSpread = kTile / 4;               // threads
+struct Four { float x[4]; };
+__device__ __forceinline__ void load_four(const float *st, uint32_t i0, uint32_t n, Four &v)
 {
-    __shared__ double red[kWavesPerBlock];
-    __shared__ float redf[kWavesPerBlock];
+    const global_ptr<const float> p = in_global(st) + i0;
+    if (i0 < n && n - i0 >= 4u) { const float4v f = *(global_ptr<const float4v>)p; v = {f.x, f.y, f.z, f.w}; }
+    else
+#pragma unroll
+        for (uint32_t e = 0; e < 4u; ++e) v.x[e] = i0 + e < n ? p[e] : 0.0f;
+}
+// the same of the gradient; the elements of the wavefront lie in one chunk
+__device__ __forceinline__ void load_four(const GroupView &g, uint32_t i0, Four &v)
+{
+    v = {0.0f, 0.0f, 0.0f, 0.0f};
+    const uint32_t lane = threadIdx.x & 63u, span = (uint32_t)__builtin_amdgcn_readfirstlane((int)i0);
+    if (span >= g.n) return;
+    Chunk c;
+    c.base = span & ~(uint32_t)(kChunk - 1);
+    c.lane = lane;
+    c.full = g.n - c.base >= (uint32_t)kChunk;
+    const uintptr_t entry = chunk_entry(g, c);
+    if (!(entry & 1u)) {
+        const float4u f = *(global_ptr<const float4u>)(in_global(reinterpret_cast<const float *>(entry)) + (i0 - c.base));
+        v = {f.x, f.y, f.z, f.w};
+        return;
+    }
+    const uint32_t s0 = (uint32_t)(entry >> 1), lim = chunk_end(g, c);
+    uintptr_t at[4];
+    if (each_span_of_chunk<4>(tensors_of_chunk(g, s0), i0, min(span + 256u, lim), lim, at)) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v.x[e] = *in_global(reinterpret_cast<const float *>(at[e]));
+#pragma unroll
+        for (uint32_t e = 0; e < 4u; ++e) v.x[e] = i0 + e < g.n ? v.x[e] : 0.0f;
+        return;
+    }
+    for_each_tensor_of_chunk(g, c, s0, [&](uint32_t beg, uint32_t end, uintptr_t ptr) {
+        const global_ptr<const float> p = in_global(reinterpret_cast<const float *>(ptr));
+#pragma unroll
+        for (uint32_t e = 0; e < 4u; ++e) if (i0 + e >= beg && i0 + e < end) v.x[e] = p[i0 + e - beg];
+    });
+}
+// the words of the random stream for four elements from model-wide index at on
+__device__ __forceinline__ void four_words(uint64_t seed, uint32_t worker, uint32_t iter_lo, uint64_t at, uint32_t off /* at % 4, uniform */, uint32_t (&x)[4])
+{
+    philox4x32_10(seed, worker, iter_lo, at >> 2, x);
+    if (off) {                                   // the group starts inside a block: the rest is in the next one
+        uint32_t y[4];
+        philox4x32_10(seed, worker, iter_lo, (at >> 2) + 1u, y);
+        const uint32_t w[4] = {x[0], x[1], x[2], x[3]};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const uint32_t one = e + 1 < 4 ? w[(e + 1) & 3] : y[(e + 1) & 3], two = e + 2 < 4 ? w[(e + 2) & 3] : y[(e + 2) & 3],
+                           three = e + 3 < 4 ? w[(e + 3) & 3] : y[(e + 3) & 3];
+            x[e] = off == 1u ? one : off == 2u ? two : three;
+        }
+    }
+}
+
+template <bool EF, int MODE, class SRC>
+__global__ __launch_bounds__(kSpread) void quantize_small_k(SRC src, uint32_t levels, uint64_t seed, uint32_t worker, uint32_t iter_lo, uint32_t looks)
+{
+    constexpr int kWaves = kSpread / kWave;
+    __shared__ double red[kWaves];
     __shared__ float scalar;
     __shared__ uint64_t todo;                    // the tiles that this block encodes, one bit each
-    __shared__ uint4 stage[kWavesPerBlock][MODE == RED_L2 ? kChunk / 16 : kSteps / 2];       // a chunk's codes, or the 64-bit ballots of its steps
     CompressJob job = src.job();
     const GroupView &g = job.g;
-    const uint32_t nwords = (g.n + 31u) >> 5, wave = threadIdx.x >> 6;
-    Chunk c = my_chunk(g.n, job.tile);
-    float p[kSteps];
-    accumulate<EF, MODE>(job, c, levels, seed, p);
-    double acc = 0.0;
-    float mx = 0.0f;
+    const uint32_t n = g.n, nwords = (n + 31u) >> 5, t = threadIdx.x, off = (uint32_t)g.goff & 3u;
+    uint32_t i0 = job.tile * (uint32_t)kTile + 4u * t;
+    // ---- p = g + e (zeros past the end of the group), kept in the state: see accumulate
+    Four p;
+    if (EF) {
+        const StateHeader *prev = job.state_header();
+        const float sprev = prev->scale;
+        const uint32_t wprev = prev->prev_worker, iprev = prev->prev_iter;
+        Four q;
+        load_four(job.st, i0, n, q);
+        load_four(g, i0, p);
+        uint32_t x[4];
+        four_words(seed, wprev, iprev, g.goff + i0, off, x);
+        const QsgdScale ks(MODE == RED_L2 ? sprev : 0.0f, levels);
 #pragma unroll
-    for (int j = 0; j < kSteps; ++j) {           // elements past n are 0 and add nothing
-        if (MODE == RED_L2) acc += (double)p[j] * (double)p[j];
-        else mx = fmaxf(mx, fabsf(p[j]));
+        for (uint32_t e = 0; e < 4u; ++e) {
+            float d;
+            if (MODE == RED_L2) d = qsgd_decode(ks, qsgd_code(ks, q.x[e], u01(x[e])));
+            else { bool nz, neg; d = tern_decode(sprev, q.x[e], u01(x[e]), true, nz, neg); }
+            const float r = q.x[e] - d;
+            p.x[e] = i0 + e < n ? p.x[e] + r : 0.0f;
+        }
+        const global_ptr<float> to = in_global(job.st) + i0;
+        if (i0 < n && n - i0 >= 4u) *(global_ptr<float4v>)to = float4v{p.x[0], p.x[1], p.x[2], p.x[3]};
+        else
+#pragma unroll
+            for (uint32_t e = 0; e < 4u; ++e) if (i0 + e < n) to[e] = p.x[e];
+    } else load_four(g, i0, p);
+    // ---- this tile's partial
+    double acc = 0.0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {                // elements past n are 0 and add nothing
+        if (MODE == RED_L2) acc += (double)p.x[e] * (double)p.x[e];
+        else acc = (double)fmaxf((float)acc, fabsf(p.x[e]));
     }
-    const double part = MODE == RED_L2 ? block_sum(acc, red) : (double)block_max(mx, redf);
-    if (threadIdx.x < 64) {
-        uint64_t mine = 1ull << job.tile, handed = 0;
-        if (threadIdx.x == 0) {
+    acc = MODE == RED_L2 ? wave_sum(acc) : (double)wave_max((float)acc);
+    if ((t & 63u) == 0) red[t >> 6] = acc;
+    __syncthreads();
+    uint32_t x[4];                               // the draws of this call
+    if (t < 64u) {
+        double part = t < (uint32_t)kWaves ? red[t] : 0.0;
+#pragma unroll
+        for (int m = kWaves / 2; m >= 1; m >>= 1) {
+            const double o = __shfl_xor(part, m, 64);
+            part = MODE == RED_L2 ? part + o : fmax(part, o);
+        }
+        uint64_t before = 0;
+        if (t == 0) {
             put_partial(job.partial + job.tile, part);
-            const uint64_t before = arrive_at(job.arrive), all = (before / job.ntiles + 1u) * job.ntiles;
+            before = arrive_at(job.arrive);
+        }
+        four_words(seed, worker, iter_lo, g.goff + i0, off, x);
+        uint64_t mine = 1ull << job.tile, handed = 0;
+        if (t == 0) {
+            const uint64_t all = (before / job.ntiles + 1u) * job.ntiles;
             // (looked at first, in the shadow of the partials: taking it is an atomic's round trip, 0.1 us of a call)
             if (before + 1u == all) handed = __hip_atomic_load(job.handed_over(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             else
@@ -769,44 +870,48 @@ __global__ __launch_bounds__(kBlock) void quantize_small_k(SRC src, uint32_t lev
         }
         all_arrived();
         const double S = combine_partials<MODE == RED_MAX_ABS>(job.partial, job.ntiles);       // (after a hand-over: of no use)
-        if (threadIdx.x == 0) {
+        if (t == 0) {
             if (handed) mine |= __hip_atomic_exchange(job.handed_over(), 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             scalar = MODE == RED_L2 ? (float)sqrt(S) : (float)S;
             todo = mine;
         }
-    }
+    } else four_words(seed, worker, iter_lo, g.goff + i0, off, x);
     __syncthreads();
     const float scale = scalar;
     uint64_t left = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)todo) |
                     ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(todo >> 32)) << 32);
     if (!left) return;
     for (;;) {                                   // its own tile, then those handed over
-        if (job.tile == job.ntiles - 1u && threadIdx.x == 0)
-            put_plain_header(job.hdr, MODE == RED_L2 ? MC_ALGO_QSGD : MC_ALGO_TERNGRAD, g.n, scale, 0.0f, MODE == RED_L2 ? levels : 0u);
+        if (job.tile == job.ntiles - 1u && t == 0)
+            put_plain_header(job.hdr, MODE == RED_L2 ? MC_ALGO_QSGD : MC_ALGO_TERNGRAD, n, scale, 0.0f, MODE == RED_L2 ? levels : 0u);
         if (EF) remember_call(job, scale, worker, iter_lo);
-        if (c.base < g.n) {
-            float uni[kSteps];
-            chunk_uniforms(seed, worker, iter_lo, g.goff + c.base, c.lane, uni);
-            if (MODE == RED_L2) {
-                const QsgdScale ks(scale, levels);
-                int8_t code[kSteps];
+        if (MODE == RED_L2) {
+            const QsgdScale ks(scale, levels);
+            uint32_t word = 0;
 #pragma unroll
-                for (int j = 0; j < kSteps; ++j) code[j] = (int8_t)qsgd_code(ks, p[j], uni[j]);
-                store_codes<int8_t>(reinterpret_cast<int8_t *>(job.body()), g.n, (g.n + 3u) & ~3u, c, code, stage[wave]);
-            } else {
-                uint32_t *planes = reinterpret_cast<uint32_t *>(job.body());
-                uint64_t bnz[kSteps], bng[kSteps];
-                tern_planes(c, g.n, scale, p, uni, bnz, bng);
-                store_plane(planes, nwords, c, bnz, reinterpret_cast<uint64_t *>(stage[wave]));
-                store_plane(planes + nwords, nwords, c, bng, reinterpret_cast<uint64_t *>(stage[wave]));
+            for (uint32_t e = 0; e < 4u; ++e) word |= (i0 + e < n ? (uint32_t)qsgd_code(ks, p.x[e], u01(x[e])) & 0xFFu : 0u) << (8u * e);
+            if (i0 < n) in_global(reinterpret_cast<uint32_t *>(job.body()))[i0 >> 2] = word;        // (the body ends on a multiple of four codes)
+        } else {
+            uint32_t z = 0, s = 0;               // the thread's four bits of either plane
+#pragma unroll
+            for (uint32_t e = 0; e < 4u; ++e) {
+                bool nz, neg;
+                (void)tern_decode(scale, p.x[e], u01(x[e]), i0 + e < n, nz, neg);
+                z |= (nz ? 1u : 0u) << e;
+                s |= (neg ? 1u : 0u) << e;
             }
+            const uint32_t nibble = 4u * (t & 7u), w = i0 >> 5;
+            z = or_of_eight(z << nibble);
+            s = or_of_eight(s << nibble);
+            if ((t & 7u) < 2u && w < nwords) in_global(reinterpret_cast<uint32_t *>(job.body()))[(t & 1u ? nwords : 0u) + w] = t & 1u ? s : z;
         }
         left &= ~(1ull << job.tile);
         if (!left) return;
         job.tile = (uint32_t)__builtin_ctzll(left);
-        c = my_chunk(g.n, job.tile);
+        i0 = job.tile * (uint32_t)kTile + 4u * t;
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");      // p of that tile, as the block that left it stored it
-        if (c.base < g.n) load_p<EF>(g, job.st, c, p);
+        if (EF) load_four(job.st, i0, n, p); else load_four(g, i0, p);
+        four_words(seed, worker, iter_lo, g.goff + i0, off, x);
     }
 }
 
@@ -815,7 +920,7 @@ void launch_quantize_small(const LaunchCtx &lc, int mode, const SRC &src, uint32
                            uint32_t iter_lo, uint32_t looks)
 {
     if (tiles == 0) return;
-    dim3 grid(tiles), block(kBlock);
+    dim3 grid(tiles), block(kSpread);
     const int slot = mode == RED_L2 ? K_QSGD_ENCODE : K_TERN_ENCODE;
     prof_begin(lc, slot);
     if (mode == RED_L2) {

@@ -206,6 +206,27 @@ __device__ __forceinline__ bool each_step_of_chunk(const GroupView &g, const Chu
     }
     return true;
 }
+// The same for N consecutive elements per lane, i0 the lane's first, hi the end of the wavefront's: their addresses.
+template <int N>
+__device__ __forceinline__ bool each_span_of_chunk(const ChunkTensors &ts, uint32_t i0, uint32_t hi, uint32_t lim, uintptr_t (&at)[N])
+{
+    if ((uint32_t)__builtin_amdgcn_readlane((int)ts.end, 63) < lim) return false;
+    const uintptr_t from = ts.ptr - sizeof(float) * (uintptr_t)ts.beg;
+    uintptr_t cur = lane_addr(from, 0);
+    uint32_t end = (uint32_t)__builtin_amdgcn_readlane((int)ts.end, 0);
+#pragma unroll
+    for (int e = 0; e < N; ++e) at[e] = cur;
+    for (int k = 1; end < hi; ++k) {
+        const uint32_t beg = end;
+        cur = lane_addr(from, k);
+        end = (uint32_t)__builtin_amdgcn_readlane((int)ts.end, k);
+#pragma unroll
+        for (int e = 0; e < N; ++e) at[e] = min(i0 + (uint32_t)e, lim - 1u) >= beg ? cur : at[e];
+    }
+#pragma unroll
+    for (int e = 0; e < N; ++e) at[e] += sizeof(float) * (uintptr_t)min(i0 + (uint32_t)e, lim - 1u);
+    return true;
+}
 // body(first element, end, address) for the tensors of a chunk, one after the other, however many
 template <typename Body>
 __device__ __forceinline__ void for_each_tensor_of_chunk(const GroupView &g, const Chunk &c, uint32_t s0, Body body)
