@@ -144,31 +144,37 @@ __device__ __forceinline__ double combine_partials(const double *partial, uint32
 }
 
 // SMALL: the group's last block to arrive combines the partials and writes the headers, instead of a kernel after this one.
-// (EF-Sign compress, 1 .. 64 tiles: 8.0 -> 5.6 .. 5.9 us, OneBit 8.6 .. 9.2 -> 6.2 .. 7.5: a launch and a kernel boundary less.)
-template <int MODE, bool EF, class SRC, bool SMALL = false>
-__global__ __launch_bounds__(kBlock) void sign_compress_k(SRC src, float beta, uint32_t algo)
+// (EF-Sign compress, 1 .. 64 tiles: 8.0 -> 5.6 .. 5.9 us, OneBit 8.6 .. 9.2 -> 6.2 .. 7.5: a launch and a kernel boundary less.
+// With the tile spread over more threads, 33 / 34 000 / 262 000 elements: EF-Sign 5.9 / 5.9 / 6.0 -> 4.8 / 5.4 / 5.8, OneBit 7.4 / 7.5 / 8.0 ->
+// 6.2 / 6.8 / 7.5, SignSGD 3.4 / 3.6 / 3.7 -> 2.2 / 2.4 / 2.6.)
+// S: elements per lane, 16, or 4 on a launch of few tiles (kSpread threads per tile).
+template <int MODE, bool EF, class SRC, bool SMALL = false, int S = kSteps>
+__global__ __launch_bounds__(kTile / S) void sign_compress_k(SRC src, float beta, uint32_t algo)
 {
-    __shared__ uint64_t stage[kWavesPerBlock][kSteps];
-    __shared__ double red[kWavesPerBlock];
-    __shared__ double red3[MODE == SIGN_MEANS ? 3 : 1][kWavesPerBlock];
+    constexpr int kWaves = kTile / S / kWave;
+    __shared__ uint64_t stage[kWaves][S];
+    __shared__ double red[kWaves];
+    __shared__ double red3[MODE == SIGN_MEANS ? 3 : 1][kWaves];
+    constexpr bool kHeld = S != kSteps && (MODE == SIGN_EF || MODE == SIGN_MEANS);
+    __shared__ float held[kHeld ? kTile : 1];    // p of the tile, to be summed in the order of the other form
     const CompressJob job = src.job();
     const GroupView &g = job.g;
     float *st = job.st;
     uint32_t *words = reinterpret_cast<uint32_t *>(job.body());
     const uint32_t nwords = (g.n + 31u) >> 5;
-    const Chunk c = my_chunk(g.n, job.tile);
+    const Chunk c = my_chunk<S>(g.n, job.tile);
     // SignSGD, SigNUM: the decoded values are +-1, no finalize kernel follows
     if ((MODE == SIGN_PLAIN || MODE == SIGN_MOMENTUM) && job.tile == job.ntiles - 1u && threadIdx.x == 0) put_plain_header(job.hdr, algo, g.n, 1.0f);
     double acc = 0.0, acc_lo = 0.0, cnt_hi = 0.0;
     if (c.base < g.n) {
-        float p[kSteps];
+        float p[S];
         load_seg(g, c, p);
         if (MODE == SIGN_MOMENTUM) {
             const float omb = 1.0f - beta;
-            float q[kSteps];
+            float q[S];
             load_flat(st, c, g.n, q, 0.0f);
 #pragma unroll
-            for (int j = 0; j < kSteps; ++j) {
+            for (int j = 0; j < S; ++j) {
                 const float bm = beta * q[j], og = omb * p[j];
                 p[j] = bm + og;
             }
@@ -176,22 +182,23 @@ __global__ __launch_bounds__(kBlock) void sign_compress_k(SRC src, float beta, u
         } else if (EF && MODE != SIGN_PLAIN) {
             const StateHeader *prev = job.state_header();
             const float hi = prev->scale, lo = MODE == SIGN_MEANS ? prev->scale_lo : -hi;
-            float q[kSteps];
+            float q[S];
             load_flat(st, c, g.n, q, 0.0f);
 #pragma unroll
-            for (int j = 0; j < kSteps; ++j) {
+            for (int j = 0; j < S; ++j) {
                 float d = q[j] >= 0.0f ? hi : lo;
                 float e = q[j] - d;
                 p[j] = p[j] + e;
             }
             store_flat(st, c, g.n, p);
         }
-        uint64_t b[kSteps];
+        uint64_t b[S];
 #pragma unroll
-        for (int j = 0; j < kSteps; ++j) {
+        for (int j = 0; j < S; ++j) {
             bool valid = c.full || (c.base + 64 * j + c.lane < g.n);
             const bool up = valid && p[j] >= 0.0f;
             b[j] = __builtin_amdgcn_ballot_w64(up);
+            if (kHeld) { held[c.base % (uint32_t)kTile + 64 * j + c.lane] = p[j]; continue; }
             if (MODE == SIGN_EF) acc += valid ? fabs((double)p[j]) : 0.0;
             if (MODE == SIGN_MEANS) {
                 acc += up ? (double)p[j] : 0.0;
@@ -200,12 +207,27 @@ __global__ __launch_bounds__(kBlock) void sign_compress_k(SRC src, float beta, u
         }
         if (MODE == SIGN_MEANS) {
 #pragma unroll
-            for (int j = 0; j < kSteps; ++j) if (c.lane == 0) cnt_hi += (double)__popcll(b[j]);
+            for (int j = 0; j < S; ++j) if (c.lane == 0) cnt_hi += (double)__popcll(b[j]);
         }
         store_plane(words, nwords, c, b, stage[threadIdx.x >> 6]);
     }
+    if (kHeld) {
+        __syncthreads();
+        const uint32_t left = g.n - job.tile * (uint32_t)kTile;
+        if (threadIdx.x < (uint32_t)kBlock) {
+#pragma unroll
+            for (int j = 0; j < kSteps; ++j) {
+                const uint32_t i = threadIdx.x / 64u * (uint32_t)kChunk + 64u * j + c.lane;
+                const bool valid = i < left;
+                const float x = held[i];
+                const bool up = valid && x >= 0.0f;
+                if (MODE == SIGN_EF) acc += valid ? fabs((double)x) : 0.0;
+                else { acc += up ? (double)x : 0.0; acc_lo += valid && !up ? (double)x : 0.0; }
+            }
+        }
+    }
     if (MODE == SIGN_EF) {
-        double t = block_sum(acc, red);
+        double t = block_sum<kWaves>(acc, red);
         if (threadIdx.x == 0) { if (SMALL) put_partial(job.partial + job.tile, t); else job.partial[job.tile] = t; }
     }
     if (MODE == SIGN_MEANS) {       // the three sums behind one pair of barriers, each combined in block_sum's order
@@ -213,7 +235,12 @@ __global__ __launch_bounds__(kBlock) void sign_compress_k(SRC src, float beta, u
         if ((threadIdx.x & 63) == 0) { red3[0][threadIdx.x >> 6] = acc; red3[1][threadIdx.x >> 6] = acc_lo; red3[2][threadIdx.x >> 6] = cnt_hi; }
         __syncthreads();
         if (threadIdx.x < 3) {
-            const double t = (red3[threadIdx.x][0] + red3[threadIdx.x][1]) + (red3[threadIdx.x][2] + red3[threadIdx.x][3]);
+            double t = 0.0;
+#pragma unroll
+            for (int w = 0; w < kWaves; w += 4) {
+                const double four = (red3[threadIdx.x][w] + red3[threadIdx.x][w + 1]) + (red3[threadIdx.x][w + 2] + red3[threadIdx.x][w + 3]);
+                t = w ? t + four : four;
+            }
             double *to = job.partial + threadIdx.x * job.ntiles + job.tile;
             if (SMALL) put_partial(to, t); else *to = t;
         }
@@ -239,30 +266,37 @@ __global__ __launch_bounds__(kBlock) void sign_compress_k(SRC src, float beta, u
     }
 }
 
+template <int MODE, bool EF, bool SMALL, class SRC>
+static void sign_compress_t(const LaunchCtx &lc, const SRC &src, uint32_t tiles, float beta, uint32_t algo)
+{
+    constexpr uint32_t most = MODE == SIGN_EF || MODE == SIGN_MEANS ? kSpreadSumTiles : kSpreadTiles;
+    if (tiles <= most) MC_LAUNCH((sign_compress_k<MODE, EF, SRC, SMALL, kSpreadSteps>), dim3(tiles), dim3(kSpread), lc, src, beta, algo);
+    else MC_LAUNCH((sign_compress_k<MODE, EF, SRC, SMALL>), dim3(tiles), dim3(kBlock), lc, src, beta, algo);
+}
+
 template <class SRC>
 void launch_sign_compress(const LaunchCtx &lc, int mode, const SRC &src, uint32_t tiles, bool ef, float beta, uint32_t algo, bool small)
 {
     if (tiles == 0) return;
-    dim3 grid(tiles), block(kBlock);
     prof_begin(lc, K_EFSIGN_COMPRESS);
     switch (mode) {
     case SIGN_EF:
-        if (ef && small) MC_LAUNCH((sign_compress_k<SIGN_EF, true, SRC, true>), grid, block, lc, src, beta, algo);
-        else if (ef) MC_LAUNCH((sign_compress_k<SIGN_EF, true, SRC>), grid, block, lc, src, beta, algo);
-        else if (small) MC_LAUNCH((sign_compress_k<SIGN_EF, false, SRC, true>), grid, block, lc, src, beta, algo);
-        else MC_LAUNCH((sign_compress_k<SIGN_EF, false, SRC>), grid, block, lc, src, beta, algo);
+        if (ef && small) sign_compress_t<SIGN_EF, true, true>(lc, src, tiles, beta, algo);
+        else if (ef) sign_compress_t<SIGN_EF, true, false>(lc, src, tiles, beta, algo);
+        else if (small) sign_compress_t<SIGN_EF, false, true>(lc, src, tiles, beta, algo);
+        else sign_compress_t<SIGN_EF, false, false>(lc, src, tiles, beta, algo);
         break;
     case SIGN_MEANS:
-        if (ef && small) MC_LAUNCH((sign_compress_k<SIGN_MEANS, true, SRC, true>), grid, block, lc, src, beta, algo);
-        else if (ef) MC_LAUNCH((sign_compress_k<SIGN_MEANS, true, SRC>), grid, block, lc, src, beta, algo);
-        else if (small) MC_LAUNCH((sign_compress_k<SIGN_MEANS, false, SRC, true>), grid, block, lc, src, beta, algo);
-        else MC_LAUNCH((sign_compress_k<SIGN_MEANS, false, SRC>), grid, block, lc, src, beta, algo);
+        if (ef && small) sign_compress_t<SIGN_MEANS, true, true>(lc, src, tiles, beta, algo);
+        else if (ef) sign_compress_t<SIGN_MEANS, true, false>(lc, src, tiles, beta, algo);
+        else if (small) sign_compress_t<SIGN_MEANS, false, true>(lc, src, tiles, beta, algo);
+        else sign_compress_t<SIGN_MEANS, false, false>(lc, src, tiles, beta, algo);
         break;
     case SIGN_PLAIN:
-        MC_LAUNCH((sign_compress_k<SIGN_PLAIN, false, SRC>), grid, block, lc, src, beta, algo);
+        sign_compress_t<SIGN_PLAIN, false, false>(lc, src, tiles, beta, algo);
         break;
     default:
-        MC_LAUNCH((sign_compress_k<SIGN_MOMENTUM, true, SRC>), grid, block, lc, src, beta, algo);
+        sign_compress_t<SIGN_MOMENTUM, true, false>(lc, src, tiles, beta, algo);
         break;
     }
     prof_end(lc, K_EFSIGN_COMPRESS);
@@ -738,7 +772,6 @@ __device__ __forceinline__ uint64_t hand_over(const CompressJob &job, uint64_t a
 // made while the partials travel.  (Compress, 1025 / 34 000 / 262 000 elements: QSGD
 // 10.3 / 10.4 / 10.5 -> 5.2 / 6.0 / 6.4 us, TernGrad 10.1 / 10.5 / 10.6 -> 4.8 / 5.5 / 5.9; 40 tensors in 1025 elements 30.6 -> 7.3; 272 000 in
 // eight groups, QSGD 13.0 -> 7.1; 6 M in 64 groups, TernGrad 35.0 -> 28.9.)
-constexpr int kSpread = kTile / 4;               // threads
 struct Four { float x[4]; };
 __device__ __forceinline__ void load_four(const float *st, uint32_t i0, uint32_t n, Four &v)
 {
@@ -803,6 +836,7 @@ __global__ __launch_bounds__(kSpread) void quantize_small_k(SRC src, uint32_t le
     __shared__ double red[kWaves];
     __shared__ float scalar;
     __shared__ uint64_t todo;                    // the tiles that this block encodes, one bit each
+    __shared__ __attribute__((aligned(16))) float held[MODE == RED_L2 ? kTile : 4];      // p of the tile
     CompressJob job = src.job();
     const GroupView &g = job.g;
     const uint32_t n = g.n, nwords = (n + 31u) >> 5, t = threadIdx.x, off = (uint32_t)g.goff & 3u;
@@ -834,23 +868,31 @@ __global__ __launch_bounds__(kSpread) void quantize_small_k(SRC src, uint32_t le
             for (uint32_t e = 0; e < 4u; ++e) if (i0 + e < n) to[e] = p.x[e];
     } else load_four(g, i0, p);
     // ---- this tile's partial
-    double acc = 0.0;
+    double part = 0.0;                           // (wavefront 0)
+    if (MODE == RED_L2) {                        // summed in the order of accum_reduce_k: the same norm to the last bit
+        *reinterpret_cast<float4v *>(&held[4u * t]) = float4v{p.x[0], p.x[1], p.x[2], p.x[3]};
+        __syncthreads();
+        if (t < (uint32_t)kBlock) {
+            double acc = 0.0;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {                // elements past n are 0 and add nothing
-        if (MODE == RED_L2) acc += (double)p.x[e] * (double)p.x[e];
-        else acc = (double)fmaxf((float)acc, fabsf(p.x[e]));
+            for (int j = 0; j < kSteps; ++j) {   // elements past n are 0 and add nothing
+                const float v = held[t / 64u * (uint32_t)kChunk + 64u * j + (t & 63u)];
+                acc += (double)v * (double)v;
+            }
+            acc = wave_sum(acc);
+            if ((t & 63u) == 0) red[t >> 6] = acc;
+        }
+        __syncthreads();
+        part = (red[0] + red[1]) + (red[2] + red[3]);
+    } else {
+        const float mx = wave_max(fmaxf(fmaxf(fmaxf(fmaxf(0.0f, fabsf(p.x[0])), fabsf(p.x[1])), fabsf(p.x[2])), fabsf(p.x[3])));
+        if ((t & 63u) == 0) red[t >> 6] = (double)mx;
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) part = fmax(part, red[w]);
     }
-    acc = MODE == RED_L2 ? wave_sum(acc) : (double)wave_max((float)acc);
-    if ((t & 63u) == 0) red[t >> 6] = acc;
-    __syncthreads();
     uint32_t x[4];                               // the draws of this call
     if (t < 64u) {
-        double part = t < (uint32_t)kWaves ? red[t] : 0.0;
-#pragma unroll
-        for (int m = kWaves / 2; m >= 1; m >>= 1) {
-            const double o = __shfl_xor(part, m, 64);
-            part = MODE == RED_L2 ? part + o : fmax(part, o);
-        }
         uint64_t before = 0;
         if (t == 0) {
             put_partial(job.partial + job.tile, part);
@@ -936,30 +978,31 @@ template void launch_quantize_small<OneCompress>(const LaunchCtx &, int, const O
 template void launch_quantize_small<AllCompress>(const LaunchCtx &, int, const AllCompress &, uint32_t, bool, uint32_t, uint64_t, uint32_t, uint32_t, uint32_t);
 
 // ---------------------------------------------------------------------------
-// FP16, single pass: h = binary16(p) round-to-nearest-even, e <- p - (float)h.
+// FP16, single pass: h = binary16(p) round-to-nearest-even, e <- p - (float)h.  S: see sign_compress_k (33 / 34 000 / 262 000
+// elements: 4.1 / 4.0 / 4.1 -> 2.4 / 2.7 / 3.1 us).
 // ---------------------------------------------------------------------------
-template <bool EF, class SRC>
-__global__ __launch_bounds__(kBlock) void fp16_compress_k(SRC src)
+template <bool EF, class SRC, int S = kSteps>
+__global__ __launch_bounds__(kTile / S) void fp16_compress_k(SRC src)
 {
     const CompressJob job = src.job();
     const GroupView &g = job.g;
     float *st = job.st;
     uint16_t *halves = reinterpret_cast<uint16_t *>(job.body());
-    const Chunk c = my_chunk(g.n, job.tile);
+    const Chunk c = my_chunk<S>(g.n, job.tile);
     if (job.tile == job.ntiles - 1u && threadIdx.x == 0) put_plain_header(job.hdr, MC_ALGO_FP16, g.n, 0.0f);
     if (c.base >= g.n) return;
-    float p[kSteps];
+    float p[S];
     load_seg(g, c, p);
     if (EF) {
-        float e[kSteps];
+        float e[S];
         load_flat(st, c, g.n, e, 0.0f);
 #pragma unroll
-        for (int j = 0; j < kSteps; ++j) p[j] = p[j] + e[j];
+        for (int j = 0; j < S; ++j) p[j] = p[j] + e[j];
     }
-    uint16_t h[kSteps];
-    float e[kSteps];
+    uint16_t h[S];
+    float e[S];
 #pragma unroll
-    for (int j = 0; j < kSteps; ++j) {
+    for (int j = 0; j < S; ++j) {
         _Float16 hv = (_Float16)p[j];                 // v_cvt_f16_f32: round to nearest even, keeps subnormals
         h[j] = __builtin_bit_cast(uint16_t, hv);
         e[j] = p[j] - (float)hv;
@@ -970,11 +1013,11 @@ __global__ __launch_bounds__(kBlock) void fp16_compress_k(SRC src)
     if (c.full) {
         uint16_t *dst = halves + c.base + c.lane;
 #pragma unroll
-        for (int j = 0; j < kSteps; ++j) st_stream(dst + 64 * j, h[j]);
+        for (int j = 0; j < S; ++j) st_stream(dst + 64 * j, h[j]);
     } else {
         const uint32_t n_padded = (g.n + 1u) & ~1u;       // zero padding up to a multiple of 4 bytes
 #pragma unroll
-        for (int j = 0; j < kSteps; ++j) {
+        for (int j = 0; j < S; ++j) {
             const uint32_t i = c.base + 64 * j + c.lane;
             if (i < g.n) halves[i] = h[j];
             else if (i < n_padded) halves[i] = (uint16_t)0;
@@ -988,7 +1031,10 @@ void launch_fp16_compress(const LaunchCtx &lc, const SRC &src, uint32_t tiles, b
     if (tiles == 0) return;
     dim3 grid(tiles), block(kBlock);
     prof_begin(lc, K_FP16_COMPRESS);
-    if (ef) MC_LAUNCH((fp16_compress_k<true, SRC>), grid, block, lc, src);
+    if (tiles <= kSpreadTiles) {
+        if (ef) MC_LAUNCH((fp16_compress_k<true, SRC, kSpreadSteps>), grid, dim3(kSpread), lc, src);
+        else MC_LAUNCH((fp16_compress_k<false, SRC, kSpreadSteps>), grid, dim3(kSpread), lc, src);
+    } else if (ef) MC_LAUNCH((fp16_compress_k<true, SRC>), grid, block, lc, src);
     else MC_LAUNCH((fp16_compress_k<false, SRC>), grid, block, lc, src);
     prof_end(lc, K_FP16_COMPRESS);
 }

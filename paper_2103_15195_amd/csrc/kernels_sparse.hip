@@ -140,46 +140,51 @@ __device__ __forceinline__ bool in_sample(const SampleRule &r, uint32_t i)
     return rem == r.first;
 }
 
-// Copy the flagged elements of a chunk, in index order, into the chunk's candidate slots.
+// Copy the flagged elements of a wavefront, in index order, into its chunk's candidate slots from slot `run` on.
 // bits: what the later kernels see of the element (its key is bits & 0x7FFFFFFF): the value itself, or
 // for Rand-k the random key.
-__device__ __forceinline__ uint32_t put_candidates(const Chunk &c, const uint32_t (&bits)[kSteps], const uint64_t (&flag)[kSteps],
-                                                   uint32_t hint, uint32_t *cand_bits, uint16_t *cand_loc, uint32_t *hist /* LDS */,
-                                                   const SampleRule &smp)
+template <int S>
+__device__ __forceinline__ void put_candidates(const Chunk &c, const uint32_t (&bits)[S], const uint64_t (&flag)[S], uint32_t run,
+                                               uint32_t hint, uint32_t *cand_bits, uint16_t *cand_loc, uint32_t *hist /* LDS */,
+                                               const SampleRule &smp)
 {
-    uint32_t run = 0;
+    const uint32_t base = S == kSteps ? c.base : c.base & ~(uint32_t)(kChunk - 1), off = S == kSteps ? 0u : c.base & (uint32_t)(kChunk - 1);
     const uint64_t me = 1ull << c.lane;
 #pragma unroll
-    for (int j = 0; j < kSteps; ++j) {
+    for (int j = 0; j < S; ++j) {
         if (flag[j] & me) {
-            uint32_t slot = c.base + run + lanes_below(flag[j]);
+            uint32_t slot = base + run + lanes_below(flag[j]);
             cand_bits[slot] = bits[j];
-            cand_loc[slot] = (uint16_t)(64 * j + c.lane);
+            cand_loc[slot] = (uint16_t)(off + 64 * j + c.lane);
             const uint32_t bin = ((bits[j] & 0x7FFFFFFFu) - hint) >> kWindowShift;
             if (in_sample(smp, c.base + 64 * j + c.lane))
                 atomicAdd(&hist[bin < (uint32_t)kBinsW - 1u ? bin : (uint32_t)kBinsW - 1u], 1u);
         }
         run += __popcll(flag[j]);
     }
-    return run;
 }
 
 // ---------------------------------------------------------------------------
 // accumulate + candidate filter + window histogram of the candidates
 // ---------------------------------------------------------------------------
-template <int ALGO, bool EF, class SRC>
-__global__ __launch_bounds__(kBlock) void sparse_accum_k(SRC src, float momentum, RngKey rng, SampleRule smp)
+// S: elements per lane, 16, or 4 on a launch of few tiles (kSpread threads per tile): a block of a small group takes as long as one
+// wavefront's instructions.  (Compress, 33 / 34 000 / 200 000 / 2 M elements, with one copy of the window on the first two: Top-k
+// 11.9 / 11.8 / 17.0 / 20.4 -> 9.1 / 10.2 / 15.4 / 19.2 us, DGC 12.6 / 12.0 / 16.7 / 21.7 -> 9.0 / 10.3 / 14.9 / 19.9, Rand-k 18.8 / 16.7 /
+// 20.7 / 24.1 -> 15.1 / 14.4 / 18.3 / 22.1.)
+template <int ALGO, bool EF, class SRC, int S = kSteps>
+__global__ __launch_bounds__(kTile / S) void sparse_accum_k(SRC src, float momentum, RngKey rng, SampleRule smp)
 {
+    constexpr int kThreads = kTile / S, kWaves = kThreads / kWave, kQuarters = kSteps / S;      // wavefronts per chunk: one, or four
     __shared__ uint32_t hist[kBinsW];
-    __shared__ uint32_t wcnt[kWavesPerBlock];
-    for (int b = threadIdx.x; b < kBinsW; b += kBlock) hist[b] = 0u;
+    __shared__ uint32_t wcnt[kWaves];
+    for (int b = threadIdx.x; b < kBinsW; b += kThreads) hist[b] = 0u;
     __syncthreads();
     const SparseJob job = src.template job<BLK_TILE>();
     const GroupView &g = job.g;
     float *st = job.st;
     const SparseScratch &sc = job.sc;
     const uint32_t order = job.blocks - 1u - job.block;          // the how-manieth of the group's blocks this is
-    const Chunk c = my_chunk(g.n, job.block);
+    const Chunk c = my_chunk<S>(g.n, job.block);
     const uint32_t hint0 = *sc.hint, hint = first_call(hint0, sc.hint[kHintCap]) ? 0xFFFFFFFFu : hint0;
     // the emit kernel of the call before is done with the list of keys in the threshold's bin: its sublists are empty again
     if (order == 0 && threadIdx.x < (uint32_t)kUSub) sc.ucount[threadIdx.x * kUCountStride] = 0u;
@@ -187,11 +192,13 @@ __global__ __launch_bounds__(kBlock) void sparse_accum_k(SRC src, float momentum
     // The radix levels are cleared by the kernels that use them -- unless a call gave up at a barrier (MC_ERR_DEVICE):
     // what it left behind must not enter this call's counts.  (A group of fewer tiles than it takes blocks to clear them at
     // once goes round again.)
-    for (uint32_t i = order * (uint32_t)kBlock + threadIdx.x; i < (uint32_t)(kHistOpen - kHist1); i += job.blocks * (uint32_t)kBlock)
+    for (uint32_t i = order * (uint32_t)kThreads + threadIdx.x; i < (uint32_t)(kHistOpen - kHist1); i += job.blocks * (uint32_t)kThreads)
         sc.hist[kHist1 + i] = 0u;
     uint32_t run = 0;
+    uint32_t bits[S];
+    uint64_t flag[S];
     if (c.base < g.n) {
-        float p[kSteps];
+        float p[S];
         // What the last call sent leaves the memory: an element whose key was above that call's threshold key counts as 0
         // here, instead of having been set to 0 there -- one scattered 4-byte store per kept entry, each a read-modify-write
         // of a whole line in memory, was most of what the compaction cost.  (Kept entries *equal* to the threshold are still
@@ -201,12 +208,12 @@ __global__ __launch_bounds__(kBlock) void sparse_accum_k(SRC src, float momentum
         if (ALGO == MC_ALGO_DGC) {
             // momentum correction: u = m u + g ; v = v + u ; the vector compressed is v
             float *vbuf = st, *ubuf = st + dgc_u_offset(g.n);
-            float u[kSteps], v[kSteps];
+            float u[S], v[S];
             load_flat(ubuf, c, g.n, u, 0.0f);
             load_flat(vbuf, c, g.n, v, 0.0f);
             load_seg(g, c, p);
 #pragma unroll
-            for (int j = 0; j < kSteps; ++j) {
+            for (int j = 0; j < S; ++j) {
                 if (key_of(v[j]) > sent_key) { u[j] = 0.0f; v[j] = 0.0f; }       // momentum factor masking of what was sent
                 float mu = momentum * u[j];
                 u[j] = mu + p[j];
@@ -216,38 +223,51 @@ __global__ __launch_bounds__(kBlock) void sparse_accum_k(SRC src, float momentum
             store_flat(ubuf, c, g.n, u);
             store_flat(vbuf, c, g.n, v);
         } else if (EF) {
-            float e[kSteps];
+            float e[S];
             load_flat(st, c, g.n, e, 0.0f);
             load_seg(g, c, p);
 #pragma unroll
-            for (int j = 0; j < kSteps; ++j) p[j] = p[j] + (key_of(e[j]) > sent_key ? 0.0f : e[j]);
+            for (int j = 0; j < S; ++j) p[j] = p[j] + (key_of(e[j]) > sent_key ? 0.0f : e[j]);
             store_flat(st, c, g.n, p);
         } else {
             load_seg(g, c, p);
         }
-        uint32_t bits[kSteps];
         if (ALGO == MC_ALGO_RANDK) {
             chunk_words(rng.seed, rng.worker, rng.iter_lo, g.goff + c.base, c.lane, bits);
 #pragma unroll
-            for (int j = 0; j < kSteps; ++j) bits[j] >>= 1;
+            for (int j = 0; j < S; ++j) bits[j] >>= 1;
         } else {
 #pragma unroll
-            for (int j = 0; j < kSteps; ++j) bits[j] = __float_as_uint(p[j]);
+            for (int j = 0; j < S; ++j) bits[j] = __float_as_uint(p[j]);
         }
-        uint64_t flag[kSteps];
 #pragma unroll
-        for (int j = 0; j < kSteps; ++j) {
+        for (int j = 0; j < S; ++j) {
             bool valid = c.full || c.base + 64 * j + c.lane < g.n;
             flag[j] = __builtin_amdgcn_ballot_w64(valid && (bits[j] & 0x7FFFFFFFu) >= hint);
         }
-        run = put_candidates(c, bits, flag, hint, sc.cand_bits, sc.cand_loc, hist, smp);
+#pragma unroll
+        for (int j = 0; j < S; ++j) run += __popcll(flag[j]);
+        if (S == kSteps) put_candidates(c, bits, flag, 0u, hint, sc.cand_bits, sc.cand_loc, hist, smp);
     }
     if (c.lane == 0) wcnt[threadIdx.x >> 6] = run;
     __syncthreads();
-    if (threadIdx.x == 0)       // candidates of the tile's four chunks, 16 bits each (a chunk holds at most 1024)
-        sc.tile_runs[job.block] = (uint64_t)wcnt[0] | ((uint64_t)wcnt[1] << 16) | ((uint64_t)wcnt[2] << 32) | ((uint64_t)wcnt[3] << 48);
-    flush_fine(hist, sc.hist + kHistW + (order % kWinCopies) * kBinsW, kBinsW - 1);
-    if (threadIdx.x == kBlock - 1 && hist[kBinsW - 1]) atomicAdd(&sc.hist[kHistOpen + (order & (kOpenCopies - 1))], hist[kBinsW - 1]);
+    if (S != kSteps) {           // behind those of the chunk's wavefronts before this one
+        const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        uint32_t at = 0;
+#pragma unroll
+        for (int q = 0; q < kQuarters - 1; ++q) if ((uint32_t)q < wave % (uint32_t)kQuarters) at += wcnt[wave / (uint32_t)kQuarters * (uint32_t)kQuarters + (uint32_t)q];
+        if (run) put_candidates(c, bits, flag, at, hint, sc.cand_bits, sc.cand_loc, hist, smp);
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) {      // candidates of the tile's four chunks, 16 bits each (a chunk holds at most 1024)
+        uint64_t runs = 0;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) runs += (uint64_t)wcnt[w] << (16 * (w / kQuarters));
+        sc.tile_runs[job.block] = runs;
+    }
+    // (A group of few tiles has no crowd at its bins: one copy then, the only one that a kernel for small groups reads.)
+    flush_fine(hist, sc.hist + kHistW + (job.blocks <= (uint32_t)kSmallSelTiles ? 0u : order % kWinCopies) * kBinsW, kBinsW - 1);
+    if (threadIdx.x == kThreads - 1 && hist[kBinsW - 1]) atomicAdd(&sc.hist[kHistOpen + (order & (kOpenCopies - 1))], hist[kBinsW - 1]);
 }
 
 // ---------------------------------------------------------------------------
@@ -1326,19 +1346,19 @@ __device__ __forceinline__ void slow_routes(const SparseJob &job, const RngKey &
 struct WindowPart { uint32_t lower, upper, above; };      // the thread's two bins; they and all above in its wavefront
 // open: the copies of the open last bin, one per lane of the last wavefront.  CLEAR: what is read is set to 0.
 // Behind a barrier wtot holds the wavefronts' sums.
-template <bool CLEAR>
+template <int COPIES, bool CLEAR>
 __device__ __forceinline__ WindowPart read_window(const SparseScratch &sc, uint32_t open, uint32_t *wtot)
 {
     const uint32_t t = threadIdx.x, lane = t & 63u, wave = __builtin_amdgcn_readfirstlane(t >> 6);
     uint2 wsum = {0u, 0u};                       // window bins 2 t and 2 t + 1
 #pragma unroll
-    for (int r = 0; r < kWinCopies; ++r) {
+    for (int r = 0; r < COPIES; ++r) {
         const uint2 x = *reinterpret_cast<const uint2 *>(sc.hist + kHistW + r * kBinsW + 2 * t);
         wsum.x += x.x; wsum.y += x.y;
     }
     if (CLEAR) {
 #pragma unroll
-        for (int r = 0; r < kWinCopies; ++r) *reinterpret_cast<uint2 *>(sc.hist + kHistW + r * kBinsW + 2 * t) = uint2{0u, 0u};
+        for (int r = 0; r < COPIES; ++r) *reinterpret_cast<uint2 *>(sc.hist + kHistW + r * kBinsW + 2 * t) = uint2{0u, 0u};
         if (wave == kSelWaves - 1) sc.hist[kHistOpen + lane] = 0u;
     }
     if (wave == kSelWaves - 1) {
@@ -1430,7 +1450,7 @@ __global__ __launch_bounds__(kSelThreads) void lean_select_k(SRC src, RngKey rng
     look_ahead(sc, tile, tile < ntiles, a0);
     const uint32_t hint = *sc.hint, hint_shift = sc.hint[kHintShift], hint_hold = sc.hint[kHintHold], hint_cap = sc.hint[kHintCap];
     uint32_t open = wave == kSelWaves - 1 ? sc.hist[kHistOpen + lane] : 0u;      // (the wavefront that holds the window's last bin)
-    const WindowPart part = read_window<false>(sc, open, wtot);
+    const WindowPart part = read_window<kWinCopies, false>(sc, open, wtot);
     if (t == 0) verdict[0] = 0u;
     __syncthreads();
     find_bin(part, k, wtot, verdict);
@@ -1710,7 +1730,7 @@ __global__ __launch_bounds__(kSelThreads) void lean_small_k(SRC src, RngKey rng,
     const uint64_t runs = wave == 0 && lane < ntiles ? sc.tile_runs[lane] : 0ull;
     const uint32_t hint = *sc.hint, hint_shift = sc.hint[kHintShift], hint_hold = sc.hint[kHintHold], hint_cap = sc.hint[kHintCap];
     const uint32_t open = wave == kSelWaves - 1 ? sc.hist[kHistOpen + lane] : 0u;
-    const WindowPart part = read_window<true>(sc, open, wtot);
+    const WindowPart part = read_window<1, true>(sc, open, wtot);
     for (int b = t; b < kBins3; b += kSelThreads) hist[b] = 0u;
     if (t == 0) verdict[0] = 0u;
     if (wave == 0) {
@@ -1802,7 +1822,8 @@ static void sparse_compress_t(const LaunchCtx &lc, const SRC &src, const SparseB
 {
     const RngKey rng{call.seed, call.worker, call.iter_lo};
     prof_begin(lc, K_SPARSE_ACCUM);
-    MC_LAUNCH((sparse_accum_k<ALGO, EF, SRC>), dim3(nb.tiles), dim3(kBlock), lc, src, call.momentum, rng, (SampleRule{0u, 0u, 0u}));
+    if (nb.tiles <= kSpreadTiles) MC_LAUNCH((sparse_accum_k<ALGO, EF, SRC, kSpreadSteps>), dim3(nb.tiles), dim3(kSpread), lc, src, call.momentum, rng, (SampleRule{0u, 0u, 0u}));
+    else MC_LAUNCH((sparse_accum_k<ALGO, EF, SRC>), dim3(nb.tiles), dim3(kBlock), lc, src, call.momentum, rng, (SampleRule{0u, 0u, 0u}));
     prof_end(lc, K_SPARSE_ACCUM);
     if (nb.small) {
         prof_begin(lc, K_LEAN_SELECT);

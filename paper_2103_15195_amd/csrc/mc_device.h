@@ -34,10 +34,16 @@ struct GroupView {
     uint64_t goff;   // model-global flat index of element 0 (random streams only)
 };
 
+// Small groups leave most of the chip idle, and their kernels take as long as one wavefront's instructions do: they spread a
+// tile over four times as many wavefronts.  What a wavefront holds is then a quarter of a chunk, kSpreadSteps elements
+// per lane, and kSteps in what follows is whatever the array has that an element is held in.
+constexpr int kSpreadSteps = 4;
+constexpr int kSpread = kTile / kSpreadSteps;       // threads per tile
+
 struct Chunk {
-    uint32_t base;   // flat index of the chunk's first element (wave-uniform)
+    uint32_t base;   // flat index of the wavefront's first element (wave-uniform)
     uint32_t lane;
-    bool full;       // the whole chunk lies below n
+    bool full;       // all of the wavefront's elements lie below n
 };
 
 // Tiles are handed out last first (block 0 takes the last tile).  The chunks that straddle tensors are the slow
@@ -47,13 +53,14 @@ struct Chunk {
 // (A decompress-and-sum's grid has one block more, the first, which gets a number behind the last tile's: Expected.)
 __device__ __forceinline__ uint32_t my_tile_index() { return gridDim.x - 1u - blockIdx.x; }
 
+template <int S = kSteps>
 __device__ __forceinline__ Chunk my_chunk(uint32_t n, uint32_t tile)
 {
     Chunk c;
     uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    c.base = tile * (uint32_t)kTile + wave * (uint32_t)kChunk;
+    c.base = tile * (uint32_t)kTile + wave * (uint32_t)(kWave * S);
     c.lane = threadIdx.x & 63u;
-    c.full = c.base < n && n - c.base >= (uint32_t)kChunk;
+    c.full = c.base < n && n - c.base >= (uint32_t)(kWave * S);
     return c;
 }
 __device__ __forceinline__ Chunk my_chunk(uint32_t n) { return my_chunk(n, my_tile_index()); }
@@ -95,29 +102,29 @@ __device__ __forceinline__ void st_stream(T *p, T v) { __builtin_nontemporal_sto
 
 // ---- flat (contiguous) buffers -------------------------------------------
 // (STREAM: non-temporal, which is faster for what is read once)
-template <typename T, bool STREAM = true>
-__device__ __forceinline__ void load_flat(const T *buf, const Chunk &c, uint32_t n, T (&v)[kSteps], T fill)
+template <typename T, bool STREAM = true, int S>
+__device__ __forceinline__ void load_flat(const T *buf, const Chunk &c, uint32_t n, T (&v)[S], T fill)
 {
     const global_ptr<const T> p = in_global(buf) + c.base + c.lane;
     if (c.full) {
 #pragma unroll
-        for (int j = 0; j < kSteps; ++j) v[j] = STREAM ? __builtin_nontemporal_load(p + 64 * j) : p[64 * j];
+        for (int j = 0; j < S; ++j) v[j] = STREAM ? __builtin_nontemporal_load(p + 64 * j) : p[64 * j];
     } else {
 #pragma unroll
-        for (int j = 0; j < kSteps; ++j) v[j] = (c.base + 64 * j + c.lane < n) ? p[64 * j] : fill;
+        for (int j = 0; j < S; ++j) v[j] = (c.base + 64 * j + c.lane < n) ? p[64 * j] : fill;
     }
 }
 
-template <typename T>
-__device__ __forceinline__ void store_flat(T *buf, const Chunk &c, uint32_t n, const T (&v)[kSteps])
+template <typename T, int S>
+__device__ __forceinline__ void store_flat(T *buf, const Chunk &c, uint32_t n, const T (&v)[S])
 {
     const global_ptr<T> p = in_global(buf) + c.base + c.lane;
     if (c.full) {
 #pragma unroll
-        for (int j = 0; j < kSteps; ++j) __builtin_nontemporal_store(v[j], p + 64 * j);
+        for (int j = 0; j < S; ++j) __builtin_nontemporal_store(v[j], p + 64 * j);
     } else {
 #pragma unroll
-        for (int j = 0; j < kSteps; ++j) if (c.base + 64 * j + c.lane < n) p[64 * j] = v[j];
+        for (int j = 0; j < S; ++j) if (c.base + 64 * j + c.lane < n) p[64 * j] = v[j];
     }
 }
 
@@ -172,7 +179,8 @@ __device__ __forceinline__ ChunkTensors tensors_of_chunk(const GroupView &g, uin
     return {g.seg_off[t < g.nseg ? t : g.nseg], g.seg_off[t < g.nseg ? t + 1u : g.nseg],      // seg_off has nseg + 1 entries, the last is n
             g.ptrs[t < g.nseg ? t : g.nseg - 1u]};
 }
-__device__ __forceinline__ uint32_t chunk_end(const GroupView &g, const Chunk &c) { return g.n - c.base >= (uint32_t)kChunk ? c.base + (uint32_t)kChunk : g.n; }
+template <int S = kSteps>
+__device__ __forceinline__ uint32_t chunk_end(const GroupView &g, const Chunk &c) { return g.n - c.base >= (uint32_t)(kWave * S) ? c.base + (uint32_t)(kWave * S) : g.n; }
 // (readlane returns int: through uint32_t, or the low word's bit 31 would smear over the high word)
 __device__ __forceinline__ uintptr_t lane_addr(uintptr_t x, int k)
 {
@@ -180,17 +188,17 @@ __device__ __forceinline__ uintptr_t lane_addr(uintptr_t x, int k)
 }
 // body(j, address of the lane's element of step j) for the 16 steps (STOP: for those that have elements), if the chunk holds
 // at most 64 tensors (else false).  A lane behind the end of the group gets the group's last element.
-template <bool STOP, typename Body>
+template <bool STOP, int S, typename Body>
 __device__ __forceinline__ bool each_step_of_chunk(const GroupView &g, const Chunk &c, const ChunkTensors &ts, Body body)
 {
-    const uint32_t lim = chunk_end(g, c);
+    const uint32_t lim = chunk_end<S>(g, c);
     if ((uint32_t)__builtin_amdgcn_readlane((int)ts.end, 63) < lim) return false;
     const uintptr_t from = ts.ptr - sizeof(float) * (uintptr_t)ts.beg;               // where the group's element 0 would be
     int k = 0;
     uintptr_t cur = lane_addr(from, 0);
     uint32_t end = (uint32_t)__builtin_amdgcn_readlane((int)ts.end, 0);
 #pragma unroll
-    for (int j = 0; j < kSteps; ++j) {
+    for (int j = 0; j < S; ++j) {
         const uint32_t first = c.base + 64u * (uint32_t)j;
         if (STOP && first >= lim) break;
         const uint32_t hi = min(first + 64u, lim), i = min(first + c.lane, lim - 1u);
@@ -228,10 +236,10 @@ __device__ __forceinline__ bool each_span_of_chunk(const ChunkTensors &ts, uint3
     return true;
 }
 // body(first element, end, address) for the tensors of a chunk, one after the other, however many
-template <typename Body>
+template <int S = kSteps, typename Body>
 __device__ __forceinline__ void for_each_tensor_of_chunk(const GroupView &g, const Chunk &c, uint32_t s0, Body body)
 {
-    const uint32_t lim = chunk_end(g, c);
+    const uint32_t lim = chunk_end<S>(g, c);
     for (;;) {
         const ChunkTensors ts = tensors_of_chunk(g, s0);
         for (int k = 0; k < 64; ++k) {
@@ -243,27 +251,28 @@ __device__ __forceinline__ void for_each_tensor_of_chunk(const GroupView &g, con
     }
 }
 
-__device__ __forceinline__ void load_seg(const GroupView &g, const Chunk &c, float (&v)[kSteps])
+template <int S>
+__device__ __forceinline__ void load_seg(const GroupView &g, const Chunk &c, float (&v)[S])
 {
     const uintptr_t entry = chunk_entry(g, c);
     if (!(entry & 1u)) {
-        const global_ptr<const float> p = in_global(reinterpret_cast<const float *>(entry)) + c.lane;
+        const global_ptr<const float> p = in_global(reinterpret_cast<const float *>(entry)) + (S == kSteps ? 0u : c.base & (uint32_t)(kChunk - 1)) + c.lane;
 #pragma unroll
-        for (int j = 0; j < kSteps; ++j) v[j] = __builtin_nontemporal_load(p + 64 * j);
+        for (int j = 0; j < S; ++j) v[j] = __builtin_nontemporal_load(p + 64 * j);
     } else {
         const uint32_t s0 = (uint32_t)(entry >> 1);
-        if (each_step_of_chunk<false>(g, c, tensors_of_chunk(g, s0), [&](int j, uintptr_t at) { v[j] = *in_global(reinterpret_cast<const float *>(at)); })) {
+        if (each_step_of_chunk<false, S>(g, c, tensors_of_chunk(g, s0), [&](int j, uintptr_t at) { v[j] = *in_global(reinterpret_cast<const float *>(at)); })) {
             if (!c.full)
 #pragma unroll
-                for (int j = 0; j < kSteps; ++j) v[j] = c.base + 64 * j + c.lane < g.n ? v[j] : 0.0f;
+                for (int j = 0; j < S; ++j) v[j] = c.base + 64 * j + c.lane < g.n ? v[j] : 0.0f;
             return;
         }
 #pragma unroll
-        for (int j = 0; j < kSteps; ++j) v[j] = 0.0f;
-        for_each_tensor_of_chunk(g, c, s0, [&](uint32_t beg, uint32_t end, uintptr_t ptr) {
+        for (int j = 0; j < S; ++j) v[j] = 0.0f;
+        for_each_tensor_of_chunk<S>(g, c, s0, [&](uint32_t beg, uint32_t end, uintptr_t ptr) {
             const global_ptr<const float> p = in_global(reinterpret_cast<const float *>(ptr));
 #pragma unroll
-            for (int j = 0; j < kSteps; ++j) {
+            for (int j = 0; j < S; ++j) {
                 const uint32_t i = c.base + 64 * j + c.lane;
                 if (i >= beg && i < end) v[j] = p[i - beg];
             }
@@ -283,7 +292,7 @@ __device__ __forceinline__ void store_seg(const GroupView &g, const Chunk &c, co
         for (int j = 0; j < kSteps; ++j) __builtin_nontemporal_store(v[j], p + 64 * j);
     } else {
         const uint32_t s0 = (uint32_t)(entry >> 1);
-        if (each_step_of_chunk<true>(g, c, tensors_of_chunk(g, s0), [&](int j, uintptr_t at) {
+        if (each_step_of_chunk<true, kSteps>(g, c, tensors_of_chunk(g, s0), [&](int j, uintptr_t at) {
                 if (c.base + 64 * j + c.lane < g.n) *in_global(reinterpret_cast<float *>(at)) = v[j];
             })) return;
         for_each_tensor_of_chunk(g, c, s0, [&](uint32_t beg, uint32_t end, uintptr_t ptr) {
@@ -315,15 +324,16 @@ __device__ __forceinline__ void store_seg_rot(const GroupView &g, const Chunk &c
 }
 
 // ---- packed bit planes -------------------------------------------------------
-// Store the 16 ballots of a chunk (32 words) to a plane of `nwords` words.
-// `stage` is 16 uint64 of LDS private to the calling wavefront.
+// Store the ballots of a wavefront's steps (two words each) to a plane of `nwords` words.
+// `stage` is one uint64 of LDS per step, private to the calling wavefront.
+template <int S>
 __device__ __forceinline__ void store_plane(uint32_t *plane, uint32_t nwords, const Chunk &c,
-                                            const uint64_t (&ballots)[kSteps], uint64_t *stage)
+                                            const uint64_t (&ballots)[S], uint64_t *stage)
 {
 #pragma unroll
-    for (int j = 0; j < kSteps; ++j) if (c.lane == (uint32_t)j) stage[j] = ballots[j];
+    for (int j = 0; j < S; ++j) if (c.lane == (uint32_t)j) stage[j] = ballots[j];
     __builtin_amdgcn_wave_barrier();
-    if (c.lane < 32) {
+    if (c.lane < 2 * S) {
         uint32_t w = (c.base >> 5) + c.lane;
         if (w < nwords) plane[w] = reinterpret_cast<const uint32_t *>(stage)[c.lane];
     }
@@ -369,12 +379,18 @@ __device__ __forceinline__ uint32_t wave_scan_incl(uint32_t x)
 __device__ __forceinline__ uint32_t wave_total(uint32_t incl) { return (uint32_t)__builtin_amdgcn_readlane((int)incl, 63); }
 
 // all threads of the block get the block total; fixed combination order
-__device__ __forceinline__ double block_sum(double x, double *lds4)
+template <int WAVES = kWavesPerBlock>
+__device__ __forceinline__ double block_sum(double x, double *lds)
 {
     x = wave_sum(x);
-    if ((threadIdx.x & 63) == 0) lds4[threadIdx.x >> 6] = x;
+    if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = x;
     __syncthreads();
-    double t = (lds4[0] + lds4[1]) + (lds4[2] + lds4[3]);
+    double t = 0.0;
+#pragma unroll
+    for (int w = 0; w < WAVES; w += 4) {
+        const double four = (lds[w] + lds[w + 1]) + (lds[w + 2] + lds[w + 3]);
+        t = w ? t + four : four;
+    }
     __syncthreads();
     return t;
 }
@@ -435,18 +451,19 @@ __device__ __forceinline__ uint32_t quad_bcast(uint32_t x)      // value of lane
     return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, R | (R << 2) | (R << 4) | (R << 6), 0xF, 0xF, true);
 }
 
-// The Philox words of a chunk's 16 steps for this lane (element gbase + 64 j + lane in step j
+// The Philox words of the wavefront's steps (16, or 4) for this lane (element gbase + 64 j + lane in step j
 // takes word (index % 4) of block index / 4).
 // Four adjacent lanes hold four consecutive elements; when gbase is a multiple of 4 these
 // share one Philox block, so each lane computes one block per four steps (the one of step
 // 4m + lane % 4) and the four words are handed round inside the quad.
+template <int S>
 __device__ __forceinline__ void chunk_words(uint64_t seed, uint32_t worker, uint32_t iter_lo, uint64_t gbase, uint32_t lane,
-                                            uint32_t (&x)[kSteps])
+                                            uint32_t (&x)[S])
 {
     if ((gbase & 3u) == 0) {
         const uint32_t me = lane & 3u;
 #pragma unroll
-        for (int m = 0; m < kSteps / 4; ++m) {
+        for (int m = 0; m < S / 4; ++m) {
             uint32_t w[4];
             philox4x32_10(seed, worker, iter_lo, (gbase + 64u * (4 * m + me) + lane) >> 2, w);
             uint32_t y[4][4];                      // y[r][i]: word i of the block of step 4m + r
@@ -462,8 +479,8 @@ __device__ __forceinline__ void chunk_words(uint64_t seed, uint32_t worker, uint
     } else {
         // The chunk starts s = gbase % 4 elements into a Philox block (a group whose tensors before it do not add up to
         // a multiple of 4).  With v = lane + s, the element of step j sits in block B0 + 16 j + v / 4, word v % 4: the
-        // same 256 blocks as above, B0 + 16 j + q computed by lane 4 q + j % 4, plus one more, B0 + 256, that only the
-        // last s lanes need in step 15 (every lane computes it: five blocks per lane instead of the sixteen of a block
+        // same 256 blocks as above, B0 + 16 j + q computed by lane 4 q + j % 4, plus one more, B0 + 256 (of 16 steps), that only the
+        // last s lanes need in the last step (every lane computes it: five blocks per lane instead of the sixteen of a block
         // per element).  A lane with v >= 64 is served by quad 0's blocks of the next step.  The lanes that share a
         // block are no aligned quad any more, so the words travel through ds_bpermute.
         // (Measured, compress of such a group of 25.6 M elements: QSGD 118.5 -> 86.8 us, TernGrad 105.9 -> 86.0, Rand-k 94.8 -> 86.7:
@@ -472,12 +489,12 @@ __device__ __forceinline__ void chunk_words(uint64_t seed, uint32_t worker, uint
         const uint64_t B0 = (gbase - s) >> 2;
         const uint32_t me = lane & 3u, quad = lane >> 2;
         const bool over = v >= 64u;
-        uint32_t w[kSteps / 4][4], wl[4];
+        uint32_t w[S / 4][4], wl[4];
 #pragma unroll
-        for (int m = 0; m < kSteps / 4; ++m) philox4x32_10(seed, worker, iter_lo, B0 + 16u * (4 * m + me) + quad, w[m]);
-        philox4x32_10(seed, worker, iter_lo, B0 + 256u, wl);
+        for (int m = 0; m < S / 4; ++m) philox4x32_10(seed, worker, iter_lo, B0 + 16u * (4 * m + me) + quad, w[m]);
+        philox4x32_10(seed, worker, iter_lo, B0 + 16u * S, wl);
 #pragma unroll
-        for (int j = 0; j < kSteps; ++j) {
+        for (int j = 0; j < S; ++j) {
             const int m = j >> 2, r = j & 3;
             const uint32_t src = over ? (uint32_t)((j + 1) & 3) : ((v >> 2) << 2) + (uint32_t)r;     // the lane that computed the block
             uint32_t got[4];
@@ -488,7 +505,7 @@ __device__ __forceinline__ void chunk_words(uint64_t seed, uint32_t worker, uint
                 uint32_t alt[4];
 #pragma unroll
                 for (int t = 0; t < 4; ++t)
-                    alt[t] = j + 1 < kSteps ? (uint32_t)__builtin_amdgcn_ds_bpermute((int)(src << 2), (int)w[(m + 1) & 3][t]) : wl[t];
+                    alt[t] = j + 1 < S ? (uint32_t)__builtin_amdgcn_ds_bpermute((int)(src << 2), (int)w[m + 1 < S / 4 ? m + 1 : 0][t]) : wl[t];
                 const uint32_t a = i == 0 ? alt[0] : i == 1 ? alt[1] : i == 2 ? alt[2] : alt[3];
                 val = over ? a : val;
             }

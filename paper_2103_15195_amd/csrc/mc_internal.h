@@ -91,6 +91,13 @@ __device__ __forceinline__ GroupView view_of(const GroupTable &tb, const GroupCo
 constexpr uint32_t kSmallTiles = 64;
 constexpr int kArriveStride = 16;             // 64-bit words between the groups' counts (a line each)
 constexpr uint32_t kWaitLooks = 1u << 10;     // looks of about a microsecond each before a waiting quantizer's block leaves its tile to the last one
+// Launches of at most this many tiles, of all their groups, spread a tile over kSpread threads (two such blocks fit a compute
+// unit, 512 the card).  Compress of 2 / 4 / 8 M elements (489 / 977 / 1954 tiles), 16 elements per lane / spread: FP16 6.0 / 10.6 / 19.6
+// and 6.0 / 10.4 / 19.6 us, SignSGD 4.4 / 5.5 / 7.4 and 3.4 / 5.4 / 9.2, Top-k 20.4 / 24.8 / 34.5 and 19.2 / 24.4 / 35.1.
+constexpr uint32_t kSpreadTiles = 512;
+// ... and EF-Sign and OneBit, which sum p in the order of the other form: 400 000 / 1 M / 2 M elements, EF-Sign 8.1 / 8.7 / 10.0 and
+// 7.8 / 8.8 / 10.4, OneBit 9.8 / 10.5 / 11.8 and 9.6 / 10.5 / 13.0.
+constexpr uint32_t kSpreadSumTiles = 128;
 __host__ __device__ inline uint32_t tiles_in(uint32_t n) { return (uint32_t)(((uint64_t)n + kTile - 1) / kTile); }
 
 // A dense compressor's job.  The state's header lies in front of st, the payload's body behind hdr.
