@@ -1946,7 +1946,7 @@ __device__ __forceinline__ void add_entries(const uint8_t *const (&pl)[kSparseBa
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
         add(b, 0u);
-        if (ROUNDS == kSparseRounds)
+        if (ROUNDS >= kSparseRounds)
             for (uint32_t at = 64u * ROUNDS; at < len[b0 + b]; at += 64u * ROUNDS) { fetch(b, at); add(b, at); }
     }
 }
@@ -2000,11 +2000,21 @@ __global__ __launch_bounds__(kBlock) void sparse_decompress_k(int algo, SRC src,
             __builtin_amdgcn_wave_barrier();
             touched = true;
         }
-        // At most one entry per lane (of one worker, four): all are looked at by each of the tile's wavefronts.
+        // At most one entry per lane (of one to four workers, four): all are looked at by each of the tile's wavefronts.
+        // (Finding the chunk's part first is one more wait for memory, and worth it only for eight workers' longer runs.  5 % of
+        // 25 M elements, spread evenly, 2 / 3 / 5 workers: 23.9 / 25.8 / 28.1 -> 20.5 / 22.5 / 26.4 us, 4.4 M 7.8 / 7.8 / 9.7 -> 7.0 / 7.4 / 8.4.)
         const int there = W - w0;
         if (there == 1 && most <= 64u * kSparseRounds) { add_entries<1, kSparseRounds>(pl, 0, k, lo, len, c.base, sums); continue; }
         if (there > kSparseBatch / 2 && most <= 64u) { add_entries<kSparseBatch, 1>(pl, 0, k, lo, len, c.base, sums); continue; }
         if (there <= kSparseBatch / 2 && most <= 64u) { add_entries<kSparseBatch / 2, 1>(pl, 0, k, lo, len, c.base, sums); continue; }
+        if (there == 1 && most <= 128u * kSparseRounds) { add_entries<1, 2 * kSparseRounds>(pl, 0, k, lo, len, c.base, sums); continue; }
+        if (there == 2 && most <= 128u * kSparseRounds) { add_entries<2, kSparseRounds>(pl, 0, k, lo, len, c.base, sums); continue; }
+        if (there <= kSparseBatch / 2 && most <= 64u * kSparseRounds) { add_entries<kSparseBatch / 2, kSparseRounds>(pl, 0, k, lo, len, c.base, sums); continue; }
+        if (there <= 6 && most <= 64u * kSparseRounds) {
+            add_entries<kSparseBatch / 2, kSparseRounds>(pl, 0, k, lo, len, c.base, sums);
+            add_entries<2, kSparseRounds>(pl, kSparseBatch / 2, k, lo, len, c.base, sums);
+            continue;
+        }
         // Else the run's part that lies in the chunk is found first, to a 64th of the run: every 64th entry of it (at most: the
         // runs are that short) in a lane, of all workers at once.
         uint32_t at[kSparseBatch] = {};
@@ -2024,7 +2034,9 @@ __global__ __launch_bounds__(kBlock) void sparse_decompress_k(int algo, SRC src,
             len[b] = to > from ? to - from : 0u;             // (none between two samples)
             most = len[b] > most ? len[b] : most;
         }
-        if (most <= 128u && there > kSparseBatch / 2) add_entries<kSparseBatch, 2>(pl, 0, k, lo, len, c.base, sums);
+        if (there == 1) add_entries<1, 2 * kSparseRounds>(pl, 0, k, lo, len, c.base, sums);
+        else if (there == 2) add_entries<2, kSparseRounds>(pl, 0, k, lo, len, c.base, sums);
+        else if (most <= 128u && there > kSparseBatch / 2) add_entries<kSparseBatch, 2>(pl, 0, k, lo, len, c.base, sums);
         else {
             add_entries<kSparseBatch / 2, kSparseRounds>(pl, 0, k, lo, len, c.base, sums);
             if (there > kSparseBatch / 2) add_entries<kSparseBatch / 2, kSparseRounds>(pl, kSparseBatch / 2, k, lo, len, c.base, sums);

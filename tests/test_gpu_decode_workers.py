@@ -95,3 +95,9 @@ def test_runs_of_a_tile(W, where):
         got, want = torch.cat(out).cpu().numpy(), O.decompress_sum(sent, n, 0.25)
         assert np.array_equal(got.view(np.uint32), want.view(np.uint32)), first
     assert ctx.mc_last_device_status() == B.MC_OK
+
+
+@pytest.mark.parametrize("W", [3, 6, 10, 11])
+def test_runs_of_a_tile_with_other_numbers_of_workers(W):
+    for where in ("anywhere", "one chunk", "chunk edges", "first and last"):
+        test_runs_of_a_tile(W, where)
