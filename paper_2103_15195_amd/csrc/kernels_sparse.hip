@@ -1450,14 +1450,66 @@ __global__ __launch_bounds__(kSelThreads) void lean_select_k(SRC src, RngKey rng
     look_ahead(sc, tile, tile < ntiles, a0);
     const uint32_t hint = *sc.hint, hint_shift = sc.hint[kHintShift], hint_hold = sc.hint[kHintHold], hint_cap = sc.hint[kHintCap];
     uint32_t open = wave == kSelWaves - 1 ? sc.hist[kHistOpen + lane] : 0u;      // (the wavefront that holds the window's last bin)
-    const WindowPart part = read_window<kWinCopies, false>(sc, open, wtot);
+    // (As in read_window, find_bin and record_verdict, written out here: called, they cost this kernel its last registers, and
+    // with them a spill that the runtime answers with an allocation of its own on the first launch, a millisecond.)
+    uint2 wsum = {0u, 0u};                       // window bins 2 t and 2 t + 1
+#pragma unroll
+    for (int r = 0; r < kWinCopies; ++r) {
+        const uint2 x = *reinterpret_cast<const uint2 *>(sc.hist + kHistW + r * kBinsW + 2 * t);
+        wsum.x += x.x; wsum.y += x.y;
+    }
+    // ---- the verdict: the bin b with  count(bins > b) < k <= count(bins >= b), by a suffix scan over the block's
+    // threads (two bins each; the counts stay below 2^32, there being fewer elements than that)
+    if (wave == kSelWaves - 1) {
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) open += __shfl_xor(open, d, 64);
+        if (lane == 63u) wsum.y += open;         // the last bin also counts every key above the window
+    }
+    const uint32_t pair = wsum.x + wsum.y;
+    const uint32_t pre = wave_scan_incl(pair);
+    uint32_t suf = wave_total(pre) - pre + pair;  // inclusive suffix sum: this thread's bins and all above
+    if (lane == 0) wtot[wave] = suf;
     if (t == 0) verdict[0] = 0u;
     __syncthreads();
-    find_bin(part, k, wtot, verdict);
+    uint32_t higher = 0, all = 0;                // candidates in the wavefronts after this one; all candidates
+#pragma unroll
+    for (int w = 0; w < kSelWaves; ++w) { if ((uint32_t)w > wave) higher += wtot[w]; all += wtot[w]; }
+    suf += higher;
+    if ((uint64_t)suf >= k && (uint64_t)(suf - pair) < k) {      // the count crosses k in one of this thread's two bins
+        const uint32_t above = suf - pair;
+        const bool upper = (uint64_t)above + wsum.y >= k;
+        const uint64_t rest = k - above - (upper ? 0u : wsum.y);
+        verdict[0] = 1u; verdict[1] = 2u * t + (upper ? 1u : 0u); verdict[2] = (uint32_t)rest; verdict[3] = 0u;
+        verdict[6] = upper ? wsum.y : wsum.x;
+    }
+    if (t == 0) { verdict[4] = all; verdict[5] = 0u; }
     __syncthreads();
-    uint32_t mode, lo;
-    uint64_t need;
-    record_verdict(job, verdict, hint, hint_shift, hint_hold, hint_cap, mode, lo, need);
+    const bool found = verdict[0] != 0u;
+    const uint32_t bin = verdict[1];
+    const bool first = job.block == 0 && t == 0, fresh = first_call(hint, hint_cap);
+    if (first && job.reports) {
+        sc.sync[kSyncLastBin] = fresh ? job.g.n : found ? verdict[6] : 0u;          // diagnostics (mc_select_stats); before a first call
+        sc.sync[kSyncLastCands] = fresh ? job.g.n : verdict[4];                     // nothing is filtered out
+    }
+    uint32_t mode = found ? 0u : kModeUniform | (fresh ? kModeFirst : 0u), lo = found ? hint + (((uint32_t)kBinsW - 1u) << kWindowShift) : 0u;
+    uint64_t need = k;
+    if (found && bin < (uint32_t)kBinsW - 1u) {
+        lo = hint + (bin << kWindowShift);
+        need = (uint64_t)verdict[2] | ((uint64_t)verdict[3] << 32);
+        const bool lean = verdict[6] <= kUCap;
+        mode = kModeFast | (lean ? kModeLean : kModeDense);
+        if (first) margin_after_hit(sc.hint, hint_shift, hint_hold, hint_cap, (uint64_t)verdict[4] | ((uint64_t)verdict[5] << 32), k);
+    } else if (first) {
+        // missed: the next calls filter with the full margin again, and keep it for a while
+        margin_after_miss(sc.hint, hint_shift, hint_cap, !found && !fresh);
+    }
+    if (first) {
+        SelectState s;
+        s.lo = lo; s.mode = mode; s.need = need;
+        sc.sel[0] = s;
+        const uint32_t route = (mode & kModeLean) ? MC_SELECT_FAST : (mode & kModeDense) ? MC_SELECT_DENSE : found || fresh ? MC_SELECT_ABOVE : MC_SELECT_REFILL;
+        atomicAdd(&sc.sync[kSyncRoutes + route], 1u);
+    }
     if (mode & kModeLean) {
         uint32_t above = 0;
         if (tile < ntiles) {
