@@ -1064,7 +1064,7 @@ __global__ __launch_bounds__(kBlock) void dense_decompress_k(SRC src, int W, flo
 {
     static_assert(ALGO == MC_ALGO_QSGD || ALGO == MC_ALGO_FP16, "one code per element");
     constexpr int kBatch = 4;
-    if (blockIdx.x == 0) { src.check({ALGO, false, false}, W, status); return; }
+    if (blockIdx.x < SRC::kCheckers) { src.check({ALGO, false, false}, W, status); return; }
     const auto job = src.template job<BLK_TILE>();
     const GroupView &out = job.out;
     const Chunk c = my_chunk(out.n, job.block);
@@ -1272,7 +1272,7 @@ __global__ __launch_bounds__(kBlock) void plane_decompress_k(SRC src, int W, flo
     __shared__ float stage[kWavesPerBlock][kChunk + 32];
     const uint32_t t = threadIdx.x;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63u;
-    if (blockIdx.x == 0) { src.check({(uint32_t)algo, false, false}, W, status); return; }
+    if (blockIdx.x < SRC::kCheckers) { src.check({(uint32_t)algo, false, false}, W, status); return; }
     const auto job = src.template job<BLK_PLANE>();
     const GroupView &out = job.out;
     const uint32_t wbase = job.block * (uint32_t)kSignTile + wave * (uint32_t)kSignWaveElems;
@@ -1401,7 +1401,7 @@ template <class SRC>
 void launch_dense_decompress(const LaunchCtx &lc, int algo, const SRC &src, uint32_t blocks, int W, float alpha, uint32_t levels, int *status)
 {
     if (blocks == 0) return;
-    dim3 grid(blocks + 1), block(kBlock);           // (the first checks the headers)
+    dim3 grid(blocks + SRC::kCheckers), block(kBlock);           // (the first ones check the headers)
     prof_begin(lc, K_DENSE_DECOMPRESS);
     switch (algo) {
     case MC_ALGO_EFSIGN:

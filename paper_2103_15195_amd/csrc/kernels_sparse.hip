@@ -2009,7 +2009,7 @@ template <class SRC>
 __global__ __launch_bounds__(kBlock) void sparse_decompress_k(int algo, SRC src, int W, float alpha, int *status, int capped)
 {
     __shared__ float acc[kWavesPerBlock][kChunk + 32];
-    if (blockIdx.x == 0) { src.check({(uint32_t)algo, true, capped != 0}, W, status); return; }
+    if (blockIdx.x < SRC::kCheckers) { src.check({(uint32_t)algo, true, capped != 0}, W, status); return; }
     const auto job = src.template job<BLK_TILE>();
     const GroupView &out = job.out;
     const uint64_t k64 = job.k;
@@ -2113,7 +2113,7 @@ void launch_sparse_decompress(const LaunchCtx &lc, int algo, const SRC &src, uin
 {
     if (tiles == 0) return;
     prof_begin(lc, K_SPARSE_DECOMPRESS);
-    MC_LAUNCH(sparse_decompress_k<SRC>, dim3(tiles + 1) /* the first checks the headers */, dim3(kBlock), lc, algo, src, W, alpha, status, capped ? 1 : 0);
+    MC_LAUNCH(sparse_decompress_k<SRC>, dim3(tiles + SRC::kCheckers) /* the first ones check the headers */, dim3(kBlock), lc, algo, src, W, alpha, status, capped ? 1 : 0);
     prof_end(lc, K_SPARSE_DECOMPRESS);
 }
 template void launch_sparse_decompress<OneDecompress>(const LaunchCtx &, int, const OneDecompress &, uint32_t, int, float, int *, bool);

@@ -50,7 +50,7 @@ struct Chunk {
 // ones, and in a model's gradient list they crowd where the small tensors are -- at the end, when the list is in
 // the order the gradients become ready, the first layers last.  Started first, they are hidden behind the rest
 // (read-only pass over the ResNet-50 list: 18.0 us instead of 19.5; 17.1 with no such chunk at all).
-// (A decompress-and-sum's grid has one block more, the first, which gets a number behind the last tile's: Expected.)
+// (A decompress-and-sum's grid has more blocks, the first ones, which get numbers behind the last tile's: Expected.)
 __device__ __forceinline__ uint32_t my_tile_index() { return gridDim.x - 1u - blockIdx.x; }
 
 template <int S = kSteps>

@@ -149,18 +149,22 @@ struct AllCompress {              // list: tensors, then y states, then y payloa
     }
 };
 
-// What the header of a payload has to say.  The first block of a decompress-and-sum does nothing but look at all of them: in
-// the block of a tile, field by field in front of its work, they were four memory latencies in a row, most of what a block of
-// a small group takes, and read ahead of the work and compared after it their registers cost the sparse kernel a wavefront
-// per SIMD (25.6 M elements, 8 workers: 0.6 us of 22).
+// What the header of a payload has to say.  The first blocks of a decompress-and-sum do nothing but look at them, a header per
+// thread: in the block of a tile, field by field in front of its work, they were four memory latencies in a row, most of what a
+// block of a small group takes, and read ahead of the work and compared after it their registers cost the sparse kernel a
+// wavefront per SIMD (25.6 M elements, 8 workers: 0.6 us of 22).  (One block that went through the headers of all groups was
+// the last to finish where there are many: 100 000 elements in 161 / 300 groups, 16 workers, Top-k 9.6 / 15.9 -> 5.8 / 5.8 us, EF-Sign
+// 8.4 / 13.8 -> 7.0 / 7.2; 300 groups, 64 workers 62 -> 18 and 51 -> 19.)
 struct Expected {
     uint32_t algo;
     bool sparse, capped;          // the number of kept entries is fixed by the group, or at most what there is room for
     __device__ __forceinline__ void check(const uint8_t *payload, uint32_t n, uint64_t k, int *status) const
     {
         const PayloadHeader *h = reinterpret_cast<const PayloadHeader *>(payload);
-        const bool fits = !sparse || (capped ? h->k <= k && h->levels == (uint32_t)k : h->k == k);
-        if (h->magic != kMagic || h->algo != algo || h->n != (uint64_t)n || !fits) raise_flag(status, FLAG_PAYLOAD);
+        const uint64_t n_sent = h->n, k_sent = h->k;      // (all asked for before the first is looked at)
+        const uint32_t magic = h->magic, of = h->algo, levels = h->levels;
+        const bool fits = !sparse | (capped ? (k_sent <= k) & (levels == (uint32_t)k) : k_sent == k);
+        if ((magic != kMagic) | (of != algo) | (n_sent != (uint64_t)n) | !fits) raise_flag(status, FLAG_PAYLOAD);
     }
 };
 
@@ -183,6 +187,7 @@ struct OneDecompress {
         }
     };
     template <int KIND> __device__ __forceinline__ Job job() const { return {out, this, k, my_tile_index()}; }
+    static constexpr uint32_t kCheckers = 1;      // blocks that look at the headers
     __device__ __forceinline__ void check(const Expected &e, int W, int *status) const
     {
         if ((int)threadIdx.x < W) e.check(pl.p[threadIdx.x], out.n, k, status);
@@ -214,11 +219,16 @@ struct AllDecompress {            // list: tensors, then the W payloads of group
         j.block = b - ld_uniform(&c->first[KIND]);
         return j;
     }
+    // A constant: computed from the number of headers, every block would have to wait for its arguments before it knows that
+    // it is a tile's, 0.25 us of a call on small groups.
+    static constexpr uint32_t kCheckers = 16;
     __device__ __forceinline__ void check(const Expected &e, int, int *status) const
     {
-        for (uint32_t i = threadIdx.x; i < tb.y * (uint32_t)W; i += blockDim.x) {
+        for (uint32_t i = blockIdx.x * (uint32_t)kBlock + threadIdx.x; i < tb.y * (uint32_t)W; i += kCheckers * (uint32_t)kBlock) {
             const GroupConst &c = tb.groups[i / (uint32_t)W];
-            if (c.n) e.check(reinterpret_cast<const uint8_t *>(tb.list[tb.live + i]), c.n, c.k, status);
+            const uintptr_t payload = tb.list[tb.live + i];
+            const uint64_t k = c.k;
+            if (c.n) e.check(reinterpret_cast<const uint8_t *>(payload), c.n, k, status);
         }
     }
 };

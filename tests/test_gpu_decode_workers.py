@@ -101,3 +101,41 @@ def test_runs_of_a_tile(W, where):
 def test_runs_of_a_tile_with_other_numbers_of_workers(W):
     for where in ("anywhere", "one chunk", "chunk edges", "first and last"):
         test_runs_of_a_tile(W, where)
+
+
+@pytest.mark.parametrize("algo", ["qsgd", "efsign", "terngrad", "topk"])
+@pytest.mark.parametrize("W", [1, 16, 64])
+def test_every_header_of_a_call_over_all_groups_is_checked(algo, W):
+    """37 groups, empty ones among them, the first and the last: up to 2368 headers, more than the threads of one block look at.
+    One header at a time with a byte changed (at every edge of what 256 threads see, the first and the last of a group)."""
+    sizes = [0, 70, 5000, 0, 4096] + [33 + 7 * j for j in range(30)] + [9000, 0]
+    y = len(sizes)
+    cfg = O.Config(B.ALGO_IDS[algo], seed=1)
+    ctx = B.Context(algo, sizes, list(range(y + 1)), seed=1)
+    room = [(ctx.payload_bytes(j) + 15) // 16 * 16 for j in range(y)]
+    at = np.concatenate([[0], np.cumsum(room)])
+    rng = np.random.default_rng(0)
+    one = np.full(at[-1], 0xAB, np.uint8)        # (an empty group's payload is not looked at)
+    for j, n in enumerate(sizes):
+        if n:
+            p, _ = O.compress(cfg, rng.standard_normal(n).astype(np.float32), O.new_state(cfg, n))
+            one[at[j]:at[j] + p.size] = p
+    wire = torch.from_numpy(one).to(DEV).repeat(W, 1)
+    pays = B.ptr_array([wire[w, at[j]:at[j + 1]] for w in range(W) for j in range(y)])
+    outs = [torch.zeros(n, device=DEV) for n in sizes]
+    for _ in range(2):                           # (twice: a list of addresses that is new, and one that is known)
+        ctx.mc_decompress_sum_groups(pays, W, 1.0, outs)
+        assert ctx.mc_last_device_status() == B.MC_OK
+    live = [j for j in range(y) if sizes[j]]
+    flat = sorted({j * W + w for j in (live[0], live[1], live[-1]) for w in (0, W - 1)} | {i for b in range(0, y * W, 256) for i in (b - 1, b) if i >= 0})
+    for i in flat:                               # (number of the header in the order in which the call lists them)
+        j, w = divmod(i, W)
+        if not sizes[j]:
+            continue
+        for byte in (0, 4, 8):
+            wire[w, at[j] + byte] ^= 0x40
+            ctx.mc_decompress_sum_groups(pays, W, 1.0, outs)
+            assert ctx.mc_last_device_status() == B.MC_ERR_PAYLOAD, (j, w, byte)
+            wire[w, at[j] + byte] ^= 0x40
+    ctx.mc_decompress_sum_groups(pays, W, 1.0, outs)
+    assert ctx.mc_last_device_status() == B.MC_OK
