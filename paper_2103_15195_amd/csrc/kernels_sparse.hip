@@ -188,7 +188,7 @@ __global__ __launch_bounds__(kTile / S) void sparse_accum_k(SRC src, float momen
     const uint32_t hint0 = *sc.hint, hint = first_call(hint0, sc.hint[kHintCap]) ? 0xFFFFFFFFu : hint0;
     // the emit kernel of the call before is done with the list of keys in the threshold's bin: its sublists are empty again
     if (order == 0 && threadIdx.x < (uint32_t)kUSub) sc.ucount[threadIdx.x * kUCountStride] = 0u;
-    if (order == 0 && threadIdx.x == 0) *sc.arrive = 0u;       // and nobody waits at a grid-wide barrier of that call any more
+    if (order == 0 && threadIdx.x == 0) sc.arrive[0] = sc.arrive[kArriveWindow] = 0u;       // and nobody waits at a grid-wide barrier of that call any more
     // The radix levels are cleared by the kernels that use them -- unless a call gave up at a barrier (MC_ERR_DEVICE):
     // what it left behind must not enter this call's counts.  (A group of fewer tiles than it takes blocks to clear them at
     // once goes round again.)
@@ -1344,33 +1344,28 @@ __device__ __forceinline__ void slow_routes(const SparseJob &job, const RngKey &
 // The bin b with  count(bins > b) < k <= count(bins >= b), by a suffix scan over the block's threads, two bins each (the
 // counts stay below 2^32, there being fewer elements than that).
 struct WindowPart { uint32_t lower, upper, above; };      // the thread's two bins; they and all above in its wavefront
-// open: the copies of the open last bin, one per lane of the last wavefront.  CLEAR: what is read is set to 0.
+// open: the copies of the open last bin, one per lane of the last wavefront.  A small group's counts are all in the first copy.
 // Behind a barrier wtot holds the wavefronts' sums.
-template <int COPIES, bool CLEAR>
 __device__ __forceinline__ WindowPart read_window(const SparseScratch &sc, uint32_t open, uint32_t *wtot)
 {
     const uint32_t t = threadIdx.x, lane = t & 63u, wave = __builtin_amdgcn_readfirstlane(t >> 6);
-    uint2 wsum = {0u, 0u};                       // window bins 2 t and 2 t + 1
-#pragma unroll
-    for (int r = 0; r < COPIES; ++r) {
-        const uint2 x = *reinterpret_cast<const uint2 *>(sc.hist + kHistW + r * kBinsW + 2 * t);
-        wsum.x += x.x; wsum.y += x.y;
-    }
-    if (CLEAR) {
-#pragma unroll
-        for (int r = 0; r < COPIES; ++r) *reinterpret_cast<uint2 *>(sc.hist + kHistW + r * kBinsW + 2 * t) = uint2{0u, 0u};
-        if (wave == kSelWaves - 1) sc.hist[kHistOpen + lane] = 0u;
-    }
+    uint2 w = *reinterpret_cast<const uint2 *>(sc.hist + kHistW + 2 * t);       // window bins 2 t and 2 t + 1
     if (wave == kSelWaves - 1) {
 #pragma unroll
         for (int d = 32; d >= 1; d >>= 1) open += __shfl_xor(open, d, 64);
-        if (lane == 63u) wsum.y += open;         // the last bin also counts every key above the window
+        if (lane == 63u) w.y += open;            // the last bin also counts every key above the window
     }
-    const uint32_t pair = wsum.x + wsum.y;
+    const uint32_t pair = w.x + w.y;
     const uint32_t pre = wave_scan_incl(pair);
     const uint32_t suf = wave_total(pre) - pre + pair;  // inclusive suffix sum: this thread's bins and all above
     if (lane == 0) wtot[wave] = suf;
-    return {wsum.x, wsum.y, suf};
+    return {w.x, w.y, suf};
+}
+__device__ __forceinline__ void clear_window(const SparseScratch &sc)
+{
+    const uint32_t t = threadIdx.x;
+    *reinterpret_cast<uint2 *>(sc.hist + kHistW + 2 * t) = uint2{0u, 0u};
+    if (t >= (uint32_t)(kSelThreads - kOpenCopies)) sc.hist[kHistOpen + (t & 63u)] = 0u;
 }
 // verdict (8 words of LDS; [0] is 0): found, bin, entries to take from it (64 bits), candidates (64 bits), keys in the bin
 __device__ __forceinline__ void find_bin(const WindowPart &part, uint64_t k, const uint32_t *wtot, uint32_t *verdict)
@@ -1751,7 +1746,7 @@ __global__ __launch_bounds__(kEmitThreads) void lean_emit_k(SRC src)
 }
 
 // ---------------------------------------------------------------------------
-// Select and emit of a small group (kSmallSelTiles tiles, kSmallKept entries) in one kernel, one block per group.  On such a
+// Select and emit of a small group (kSmallSelTiles tiles, kSmallKept entries) in one kernel.  On such a
 // group the two kernels do next to nothing but start, read the window and wait for two levels of loads, each.  One
 // block can hold all candidates, 16 per thread in index order, and needs no list and no counts in memory: the
 // window's verdict, a histogram of the threshold's bin in LDS, a scan over the block's wavefronts, and the entries are
@@ -1759,13 +1754,17 @@ __global__ __launch_bounds__(kEmitThreads) void lean_emit_k(SRC src)
 // (Compress, 1025 / 34 000 / 131 000 elements: Top-k 1 % 18.7 / 17.1 / 17.2 -> 13.1 / 13.4 / 16.0 us, 5 % 20.5 / 23.3 / 23.5 -> 13.6 /
 // 17.4 / 23.2, DGC 0.1 % 18.4 / 16.6 / 16.9 -> 13.8 / 13.5 / 13.9, Rand-k 26.7 / 28.1 / 21.2 -> 19.8 / 22.5 / 20.4; 272 000 elements in
 // four groups, Top-k 1 % with the decompress-and-sum 25.5 -> 22.5.)
-// What the window does not settle, or more candidates than the block holds, goes the way of the slow routes, alone.
+// What the window does not settle, or more candidates than the block holds, goes the way of the slow routes, on
+// small_sel_blocks() blocks, which on the usual route do nothing but read the window.  (By the group's first block alone, as up
+// to 8 tiles, a group of 17 to 32 tiles took longer there than with the two kernels.  First call of a context, 17 / 24 / 32 tiles, Top-k:
+// two kernels 51.5 / 55.5 / 61.3 us, one block 55.3 / 66.7 / 81.0, one block for every four tiles 40.7 / 40.8 / 41.6; Rand-k 5 % of 17 /
+// 24 / 32 tiles, where every few calls miss the window: 40 / 31 / 37, 46 / 42 / 56, 36 / 30 / 33.)
 // ---------------------------------------------------------------------------
 constexpr int kSmallRounds = 16;                 // candidates per thread
 static_assert(kSmallSelTiles <= 64 && kSmallKept * 5u / 2u <= (uint32_t)kSmallRounds * kSelThreads, "");
 
 template <int ALGO, bool EF, class SRC>
-__global__ __launch_bounds__(kSelThreads) void lean_small_k(SRC src, RngKey rng, int *status)
+__global__ __launch_bounds__(kSelThreads) void lean_small_k(SRC src, RngKey rng, uint32_t sync_blocks, int *status)
 {
     __shared__ __attribute__((aligned(16))) uint32_t hist[kBins1];
     __shared__ uint32_t pfx[2 * kRoundTiles];    // (slow routes)
@@ -1773,16 +1772,17 @@ __global__ __launch_bounds__(kSelThreads) void lean_small_k(SRC src, RngKey rng,
     __shared__ uint32_t wtot[kSelWaves], verdict[8];
     __shared__ uint32_t from[kSmallSelTiles * kWavesPerBlock + 1];      // candidates of the group before each chunk
     __shared__ uint32_t kept[kSmallSelTiles];    // entries in each tile
-    const SparseJob job = src.group_job(blockIdx.x);
+    __shared__ uint32_t clears;
+    const SparseJob job = src.small_job();
     const uint32_t n = job.g.n;
-    if (n == 0) return;
+    if (job.block >= job.blocks) return;
     const uint32_t t = threadIdx.x, lane = t & 63u, wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const SparseScratch &sc = job.sc;
     const uint32_t k = (uint32_t)job.k, ntiles = tiles_in(n);
     const uint64_t runs = wave == 0 && lane < ntiles ? sc.tile_runs[lane] : 0ull;
     const uint32_t hint = *sc.hint, hint_shift = sc.hint[kHintShift], hint_hold = sc.hint[kHintHold], hint_cap = sc.hint[kHintCap];
     const uint32_t open = wave == kSelWaves - 1 ? sc.hist[kHistOpen + lane] : 0u;
-    const WindowPart part = read_window<1, true>(sc, open, wtot);
+    const WindowPart part = read_window(sc, open, wtot);
     for (int b = t; b < kBins3; b += kSelThreads) hist[b] = 0u;
     if (t == 0) verdict[0] = 0u;
     if (wave == 0) {
@@ -1796,12 +1796,15 @@ __global__ __launch_bounds__(kSelThreads) void lean_small_k(SRC src, RngKey rng,
         }
     }
     __syncthreads();
+    // The window is read by all blocks of the group: the last of them clears it.
+    uint32_t readers = job.blocks - 1u;
+    if (t == 0 && job.blocks > 1u) readers = __hip_atomic_fetch_add(sc.arrive + kArriveWindow, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     // Candidates wave * 64 rounds ... of the group are the wavefront's, 64 a round.
     const uint32_t N = from[kWavesPerBlock * kSmallSelTiles];
     const uint32_t rounds = (N + kSelThreads - 1u) / kSelThreads, first = wave * 64u * rounds + lane;
     const bool fits = rounds <= (uint32_t)kSmallRounds;
     uint32_t bits[kSmallRounds], at[kSmallRounds];
-    if (fits) {
+    if (fits && job.block == 0) {
 #pragma unroll
         for (int r = 0; r < kSmallRounds; ++r) {
             if ((uint32_t)r >= rounds) break;
@@ -1815,15 +1818,20 @@ __global__ __launch_bounds__(kSelThreads) void lean_small_k(SRC src, RngKey rng,
         }
     }
     find_bin(part, k, wtot, verdict);
+    if (t == 0) clears = readers + 1u == job.blocks ? 1u : 0u;
     __syncthreads();
+    if (clears) clear_window(sc);
     uint32_t mode, lo;
     uint64_t need64;
     record_verdict(job, verdict, hint, hint_shift, hint_hold, hint_cap, mode, lo, need64);
     if (!(mode & kModeLean) || !fits) {
         if (mode & kModeLean) mode = kModeFast | kModeDense;
-        slow_routes<ALGO, EF, ALGO == MC_ALGO_DGC || EF, ALGO == MC_ALGO_RANDK>(job, rng, mode, lo, need64, 1u, status, hist, pfx, small);
+        const uint32_t blocks = min(job.blocks, sync_blocks);
+        if (job.block < blocks)
+            slow_routes<ALGO, EF, ALGO == MC_ALGO_DGC || EF, ALGO == MC_ALGO_RANDK>(job, rng, mode, lo, need64, blocks, status, hist, pfx, small);
         return;
     }
+    if (job.block) return;
     // ---- the threshold key, and the number of keys equal to it to take
 #pragma unroll
     for (int r = 0; r < kSmallRounds; ++r) {
@@ -1877,14 +1885,15 @@ static void sparse_compress_t(const LaunchCtx &lc, const SRC &src, const SparseB
     if (nb.tiles <= kSpreadTiles) MC_LAUNCH((sparse_accum_k<ALGO, EF, SRC, kSpreadSteps>), dim3(nb.tiles), dim3(kSpread), lc, src, call.momentum, rng, (SampleRule{0u, 0u, 0u}));
     else MC_LAUNCH((sparse_accum_k<ALGO, EF, SRC>), dim3(nb.tiles), dim3(kBlock), lc, src, call.momentum, rng, (SampleRule{0u, 0u, 0u}));
     prof_end(lc, K_SPARSE_ACCUM);
+    // the slow routes run on blocks that the device holds at once: one per compute unit
+    const uint32_t sync = std::max(1u, std::min(call.sync_blocks, (uint32_t)(kRoundTiles / kSelWaves)));
     if (nb.small) {
         prof_begin(lc, K_LEAN_SELECT);
-        MC_LAUNCH((lean_small_k<ALGO, EF, SRC>), dim3(nb.small), dim3(kSelThreads), lc, src, rng, call.status);
+        MC_LAUNCH((lean_small_k<ALGO, EF, SRC>), dim3(nb.small), dim3(kSelThreads), lc, src, rng, sync, call.status);
         prof_end(lc, K_LEAN_SELECT);
         return;
     }
-    // the two-kernel tail; its slow routes run on blocks that the device holds at once: one per compute unit
-    const uint32_t sync = std::max(1u, std::min(call.sync_blocks, (uint32_t)(kRoundTiles / kSelWaves)));
+    // the two-kernel tail
     prof_begin(lc, K_LEAN_SELECT);
     MC_LAUNCH((lean_select_k<ALGO, EF, SRC>), dim3(nb.select), dim3(kSelThreads), lc, src, rng, sync, call.status);
     prof_end(lc, K_LEAN_SELECT);

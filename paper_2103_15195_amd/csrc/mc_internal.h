@@ -353,6 +353,10 @@ __host__ __device__ inline SparseScratch scratch_of(const SparseScratch &all, ui
     return s;
 }
 constexpr int kSelTiles = 16, kEmitTiles = kWavesPerBlock;     // tiles per block of the select and the emit kernel
+// Blocks of a group that lean_small_k, which is both for small groups, runs the slow routes on.  (Up to 8 tiles one block, which needs
+// no barriers, is ahead: 8 tiles, a refill and a rise in turn, Top-k 41.7 us, two blocks 45.2; 16 tiles 54.4, four blocks 49.1.)
+__host__ __device__ constexpr uint32_t small_sel_blocks(uint32_t tiles) { return tiles == 0u ? 0u : tiles <= 8u ? 1u : (tiles + kEmitTiles - 1u) / kEmitTiles; }
+constexpr int kArriveWindow = 1;                               // word behind SparseScratch::arrive: blocks of lean_small_k that have read the window
 
 // A sparsifier's job: `block` is this block's number among the group's `blocks` of its kind (tiles: handed out last first).
 struct SparseJob {
@@ -370,16 +374,17 @@ struct OneSparse {
     PayloadHeader *hdr;
     uint64_t k;
     SparseScratch sc;
-    __device__ __forceinline__ SparseJob group_job(uint32_t) const { return {g, st, hdr, k, sc, 0u, 1u, true}; }
     template <int KIND> __device__ __forceinline__ SparseJob job() const
     {
         return {g, st, hdr, k, sc, KIND == BLK_TILE ? my_tile_index() : blockIdx.x, gridDim.x, true};
     }
+    __device__ __forceinline__ SparseJob small_job() const { return {g, st, hdr, k, sc, blockIdx.x, gridDim.x, true}; }
 };
 struct AllSparse {                // list: tensors, then y states, then y payloads
     GroupTable tb;
     SparseScratch all;
     uint32_t last_group;          // the last one that holds elements
+    bool one_each;                // lean_small_k: one block for each group, so that none has to look its group up
     __device__ __forceinline__ SparseJob group_job(uint32_t q) const
     {
         const GroupConst *c = tb.groups + q;
@@ -395,6 +400,12 @@ struct AllSparse {                // list: tensors, then y states, then y payloa
         SparseJob j = group_job(q);
         j.block = b - ld_uniform(&tb.groups[q].first[KIND]);
         j.blocks = (tiles_in(j.g.n) + per - 1u) / per;
+        return j;
+    }
+    __device__ __forceinline__ SparseJob small_job() const
+    {
+        SparseJob j = one_each ? group_job(blockIdx.x) : job<BLK_EMIT>();
+        j.blocks = small_sel_blocks(tiles_in(j.g.n));
         return j;
     }
 };
@@ -414,7 +425,7 @@ struct SparseCall {
 constexpr int kSmallSelTiles = 32;
 constexpr uint32_t kSmallKept = 6144;
 inline bool selects_small(uint32_t n, uint64_t k) { return tiles_in(n) <= (uint32_t)kSmallSelTiles && k <= kSmallKept; }
-struct SparseBlocks { uint32_t tiles, select, emit, small = 0; };          // blocks of each kind that the launches cover; small: groups, if all are such
+struct SparseBlocks { uint32_t tiles, select, emit, small = 0; };          // blocks of each kind that the launches cover; small: those of lean_small_k, if all groups are such
 inline SparseBlocks sparse_blocks(uint32_t n)
 {
     const uint32_t t = tiles_in(n);

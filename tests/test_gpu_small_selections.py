@@ -82,3 +82,36 @@ def test_same_as_the_two_kernels_in_calls_of_every_kind(algo):
     assert "lean_emit" in a.profile_read()
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("algo", ALGOS)
+def test_slow_routes_of_groups_of_every_size(algo):
+    """The largest values rise and fall by turns, so that every call misses the window, and then many are equal: groups whose slow
+    routes run on one to eight blocks, each by itself and all in one call."""
+    numel = [4096 * t - 3 for t in (1, 4, 8, 9, 12, 13, 17, 29, 32)]
+    y = len(numel)
+    a, b = (B.Context(algo, numel, list(range(y + 1)), ratio_ppm=10000, seed=2) for _ in range(2))
+    cfg = O.Config(B.ALGO_IDS[algo], ratio_ppm=10000, seed=2)
+    bufs = [([torch.zeros(c.state_bytes(j), dtype=torch.uint8, device=H.DEV) for j in range(y)],
+             [torch.zeros(c.payload_bytes(j), dtype=torch.uint8, device=H.DEV) for j in range(y)]) for c in (a, b)]
+    held = [O.new_state(cfg, n) for n in numel]
+    off = np.concatenate([[0], np.cumsum(numel)])
+    rng = np.random.default_rng(5)
+    for it in range(6):
+        scale = [1.0, 20.0, 400.0, 0.01, 8000.0, 1.0][it]
+        g = [(rng.standard_normal(n) * scale).astype(np.float32) for n in numel]
+        if it >= 4:
+            g = [(np.sign(v) * scale).astype(np.float32) for v in g]
+        dev = [torch.from_numpy(v).to(H.DEV) for v in g]
+        for j in range(y):
+            a.mc_compress(j, 0, it, [dev[j]], bufs[0][0][j], bufs[0][1][j])
+        b.mc_compress_groups(0, it, dev, *bufs[1])
+        for j in range(y):
+            want, _ = O.compress(cfg, g[j], held[j], group_off=int(off[j]), worker=0, it=it)
+            assert np.array_equal(bufs[0][1][j].cpu().numpy(), want), (it, j)
+            assert torch.equal(bufs[0][1][j], bufs[1][1][j]) and torch.equal(bufs[0][0][j], bufs[1][0][j]), (it, j)
+    ra, rb = a.mc_select_stats(), b.mc_select_stats()
+    assert all(ra[r] == rb[r] for r in ("above", "fast", "refill", "dense")) and ra["fast"] < 6 * y
+    assert a.mc_last_device_status() == B.MC_OK and b.mc_last_device_status() == B.MC_OK
+    a.close()
+    b.close()
