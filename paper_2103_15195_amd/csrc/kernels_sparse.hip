@@ -1751,17 +1751,25 @@ __global__ __launch_bounds__(kEmitThreads) void lean_emit_k(SRC src)
 // block can hold all candidates, 16 per thread in index order, and needs no list and no counts in memory: the
 // window's verdict, a histogram of the threshold's bin in LDS, a scan over the block's wavefronts, and the entries are
 // written.  The candidates are asked for as soon as the chunks' counts are known, while the verdict is found.
-// (Compress, 1025 / 34 000 / 131 000 elements: Top-k 1 % 18.7 / 17.1 / 17.2 -> 13.1 / 13.4 / 16.0 us, 5 % 20.5 / 23.3 / 23.5 -> 13.6 /
-// 17.4 / 23.2, DGC 0.1 % 18.4 / 16.6 / 16.9 -> 13.8 / 13.5 / 13.9, Rand-k 26.7 / 28.1 / 21.2 -> 19.8 / 22.5 / 20.4; 272 000 elements in
-// four groups, Top-k 1 % with the decompress-and-sum 25.5 -> 22.5.)
+// (Compress, the streaming pass included, two kernels -> one.  Top-k 1 % of 1 / 8 / 17 / 32 tiles: 15.3 / 14.9 / 14.9 /
+// 14.9 -> 9.6 / 10.0 / 10.6 / 11.9 us, 4 % 18.2 / 19.2 / 19.8 / 20.0 -> 9.8 / 11.6 / 13.6 / 16.8, 131 of 32 tiles 14.5 -> 10.0, 6029 of them
+// 21.4 -> 18.0; DGC 0.1 % of 16 tiles 14.8 -> 10.3; Rand-k 1 % of 1 / 16 / 32 tiles 26.1 / 25.4 / 21.2 -> 19.8 / 16.4 / 16.7.)
 // What the window does not settle, or more candidates than the block holds, goes the way of the slow routes, on
 // small_sel_blocks() blocks, which on the usual route do nothing but read the window.  (By the group's first block alone, as up
 // to 8 tiles, a group of 17 to 32 tiles took longer there than with the two kernels.  First call of a context, 17 / 24 / 32 tiles, Top-k:
 // two kernels 51.5 / 55.5 / 61.3 us, one block 55.3 / 66.7 / 81.0, one block for every four tiles 40.7 / 40.8 / 41.6; Rand-k 5 % of 17 /
-// 24 / 32 tiles, where every few calls miss the window: 40 / 31 / 37, 46 / 42 / 56, 36 / 30 / 33.)
+// 24 / 32 tiles, where every few calls miss the window: 40 / 31 / 37, 46 / 42 / 56, 33 / 29 / 32.)
+// (More candidates than the block holds take an eighth or more of the group's elements just below the threshold, as the full margin
+// meets them in the calls after a miss: 32 tiles, 22 000 / 47 000 candidates, a rise, a refill and eight such calls 25.8 / 34.1 us each
+// with two kernels, 27.8 / 36.9 now.)
 // ---------------------------------------------------------------------------
-constexpr int kSmallRounds = 16;                 // candidates per thread
-static_assert(kSmallSelTiles <= 64 && kSmallKept * 5u / 2u <= (uint32_t)kSmallRounds * kSelThreads, "");
+// Candidates per thread: up to two, found by bisection, seven looks at the chunks' starts each; or up to 16, found chunk by chunk,
+// which takes longer where a chunk has few.  (Top-k compress, bisection for up to
+// 8192 candidates / chunk by chunk beyond 1024 / the rule: 32 tiles, 720 candidates 10.1 / 9.7 / 9.8 us, 1950 11.5 / 12.5 / 11.7, 6300 15.8 /
+// 16.0 / 15.9.  Asked for one after the other, each with a wait of its own: 9.9, 12.3, 19.1, and 24.4 instead of 18.0 for 10 900.)
+constexpr int kFewRounds = 2, kManyRounds = 16;
+constexpr uint32_t kFewCands = (uint32_t)kFewRounds * kSelThreads, kManyCands = (uint32_t)kManyRounds * kSelThreads;
+static_assert(kSmallSelTiles * kWavesPerBlock == 128 && kManyCands <= 0xFFFFu, "");
 
 template <int ALGO, bool EF, class SRC>
 __global__ __launch_bounds__(kSelThreads) void lean_small_k(SRC src, RngKey rng, uint32_t sync_blocks, int *status)
@@ -1797,73 +1805,114 @@ __global__ __launch_bounds__(kSelThreads) void lean_small_k(SRC src, RngKey rng,
     }
     __syncthreads();
     // The window is read by all blocks of the group: the last of them clears it.
-    uint32_t readers = job.blocks - 1u;
-    if (t == 0 && job.blocks > 1u) readers = __hip_atomic_fetch_add(sc.arrive + kArriveWindow, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    // Candidates wave * 64 rounds ... of the group are the wavefront's, 64 a round.
+    uint32_t readers = job.blocks;
+    if (t == 0 && job.blocks > 1u) readers = 1u + __hip_atomic_fetch_add(sc.arrive + kArriveWindow, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const uint32_t N = from[kWavesPerBlock * kSmallSelTiles];
-    const uint32_t rounds = (N + kSelThreads - 1u) / kSelThreads, first = wave * 64u * rounds + lane;
-    const bool fits = rounds <= (uint32_t)kSmallRounds;
-    uint32_t bits[kSmallRounds], at[kSmallRounds];
-    if (fits && job.block == 0) {
-#pragma unroll
-        for (int r = 0; r < kSmallRounds; ++r) {
-            if ((uint32_t)r >= rounds) break;
-            const uint32_t p = min(first + 64u * r, N - 1u);
-            uint32_t ch = 0;                     // the last chunk that starts at or before p
-#pragma unroll
-            for (uint32_t step = kWavesPerBlock * kSmallSelTiles / 2; step >= 1; step >>= 1) if (from[ch + step] <= p) ch += step;
-            const uint32_t slot = ch * (uint32_t)kChunk + (p - from[ch]);
+    uint32_t mode = 0, lo = 0, T = 0;
+    uint64_t need = 0;
+    // The route, behind the candidates' loads; true if it is the usual one and the block holds the candidates.
+    auto usual = [&] {
+        find_bin(part, k, wtot, verdict);
+        if (t == 0) clears = readers == job.blocks ? 1u : 0u;
+        __syncthreads();
+        if (clears) clear_window(sc);
+        record_verdict(job, verdict, hint, hint_shift, hint_hold, hint_cap, mode, lo, need);
+        if (N > kManyCands && (mode & kModeLean)) mode = kModeFast | kModeDense;
+        return (mode & kModeLean) != 0u;
+    };
+    auto finish = [&](auto form) {
+        constexpr bool MANY = decltype(form)::value;
+        constexpr int ROUNDS = MANY ? kManyRounds : kFewRounds;
+        // Candidates wave * 64 rounds ... are the wavefront's, 64 a round, all asked for at once.
+        const uint32_t rounds = min((N + kSelThreads - 1u) / kSelThreads, (uint32_t)ROUNDS), first = wave * 64u * rounds + lane;
+        uint32_t bits[ROUNDS], loc[ROUNDS], chunks[(ROUNDS + 3) / 4];      // (a chunk's number is below 128)
+        auto load = [&](int r, uint32_t ch, uint32_t in) {
+            const uint32_t slot = ch * (uint32_t)kChunk + in;
             bits[r] = sc.cand_bits[slot];
-            at[r] = ch * (uint32_t)kChunk + sc.cand_loc[slot];
+            loc[r] = sc.cand_loc[slot];          // (added to the chunk's start where it is used: not waited for here)
+            chunks[r / 4] = r % 4 ? chunks[r / 4] | ch << (8 * (r % 4)) : ch;
+        };
+        auto chunk = [&](int r) { return chunks[r / 4] >> (8 * (r % 4)) & 0xFFu; };
+        if (job.block == 0 && N - 1u < kManyCands) {
+            if (!MANY) {                         // by bisection: seven looks a round
+#pragma unroll
+                for (int r = 0; r < ROUNDS; ++r) {
+                    if ((uint32_t)r < rounds) {
+                        const uint32_t p = min(first + 64u * r, N - 1u);
+                        uint32_t ch = 0;         // the last chunk that starts at or before p
+#pragma unroll
+                        for (uint32_t step = kWavesPerBlock * kSmallSelTiles / 2; step >= 1; step >>= 1) if (from[ch + step] <= p) ch += step;
+                        load(r, ch, p - from[ch]);
+                    }
+                }
+            } else {                             // chunk after chunk: a round has hardly more than one
+                const uint32_t start[2] = {from[lane], from[64u + lane]}, end[2] = {from[lane + 1u], from[65u + lane]};
+                auto of = [](const uint32_t (&x)[2], uint32_t c) { return (uint32_t)__builtin_amdgcn_readlane((int)(c < 64u ? x[0] : x[1]), (int)(c & 63u)); };
+                const uint32_t p0 = min(first - lane, N - 1u);
+                uint32_t c = (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(start[0] <= p0)) + (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(start[1] <= p0)) - 1u;
+                uint32_t beg = of(start, c), lim = of(end, c);
+#pragma unroll
+                for (int r = 0; r < ROUNDS; ++r) {
+                    if ((uint32_t)r < rounds) {
+                        const uint32_t p = min(first + 64u * r, N - 1u), last = min(first - lane + 64u * r + 63u, N - 1u);
+                        uint32_t ch = c, at = beg;
+                        while (lim <= last) {    // another chunk's candidates start in this round
+                            ++c;
+                            beg = lim;
+                            lim = of(end, c);
+                            ch = p >= beg ? c : ch;
+                            at = p >= beg ? beg : at;
+                        }
+                        load(r, ch, p - at);
+                    }
+                }
+            }
         }
-    }
-    find_bin(part, k, wtot, verdict);
-    if (t == 0) clears = readers + 1u == job.blocks ? 1u : 0u;
-    __syncthreads();
-    if (clears) clear_window(sc);
-    uint32_t mode, lo;
-    uint64_t need64;
-    record_verdict(job, verdict, hint, hint_shift, hint_hold, hint_cap, mode, lo, need64);
-    if (!(mode & kModeLean) || !fits) {
-        if (mode & kModeLean) mode = kModeFast | kModeDense;
+        if (!usual()) return false;
+        if (job.block) return true;
+        // ---- the threshold key, and the number of keys equal to it to take
+#pragma unroll
+        for (int r = 0; r < ROUNDS; ++r) {
+            if ((uint32_t)r < rounds) {
+                const uint32_t key = bits[r] & 0x7FFFFFFFu;
+                if (first + 64u * r < N && key >= lo && key - lo < (uint32_t)kBins3) atomicAdd(&hist[key - lo], 1u);
+            }
+        }
+        __syncthreads();
+        uint32_t bin;
+        resolve_block<kBins3>(hist, need, bin, need, small, small + 8);
+        T = lo + bin;
+        // ---- keys above / equal to it before this wavefront's (16 bits each: there are 16384 candidates at most)
+        uint32_t both = 0;
+#pragma unroll
+        for (int r = 0; r < ROUNDS; ++r) {
+            if ((uint32_t)r < rounds) {
+                const uint32_t key = bits[r] & 0x7FFFFFFFu;
+                const bool valid = first + 64u * r < N;
+                both += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(valid && key > T)) + ((uint32_t)__popcll(__builtin_amdgcn_ballot_w64(valid && key == T)) << 16);
+            }
+        }
+        if (lane == 0) wtot[wave] = both;
+        __syncthreads();
+        const uint32_t v = lane < (uint32_t)kSelWaves ? wtot[lane] : 0u, before = (uint32_t)__builtin_amdgcn_readlane((int)(wave_scan_incl(v) - v), (int)wave);
+        uint32_t gt0 = before & 0xFFFFu, eq0 = before >> 16;
+        uint32_t *idx = reinterpret_cast<uint32_t *>(reinterpret_cast<uint8_t *>(job.hdr) + kHeaderBytes);
+        float *val = reinterpret_cast<float *>(idx + k);
+#pragma unroll
+        for (int r = 0; r < ROUNDS; ++r)
+            if ((uint32_t)r < rounds &&
+                emit_head<ALGO, EF>(bits[r], loc[r], first + 64u * r < N, chunk(r), n, k, job.st, idx, val, T, (uint32_t)need, gt0, eq0))
+                atomicAdd(&kept[chunk(r) / (uint32_t)kWavesPerBlock], 1u);
+        __syncthreads();
+        return true;
+    };
+    if (!(N <= kFewCands ? finish(std::false_type{}) : finish(std::true_type{}))) {
         const uint32_t blocks = min(job.blocks, sync_blocks);
         if (job.block < blocks)
-            slow_routes<ALGO, EF, ALGO == MC_ALGO_DGC || EF, ALGO == MC_ALGO_RANDK>(job, rng, mode, lo, need64, blocks, status, hist, pfx, small);
+            slow_routes<ALGO, EF, ALGO == MC_ALGO_DGC || EF, ALGO == MC_ALGO_RANDK>(job, rng, mode, lo, need, blocks, status, hist, pfx, small);
         return;
     }
     if (job.block) return;
-    // ---- the threshold key, and the number of keys equal to it to take
-#pragma unroll
-    for (int r = 0; r < kSmallRounds; ++r) {
-        if ((uint32_t)r >= rounds) break;
-        const uint32_t key = bits[r] & 0x7FFFFFFFu;
-        if (first + 64u * r < N && key >= lo && key - lo < (uint32_t)kBins3) atomicAdd(&hist[key - lo], 1u);
-    }
-    __syncthreads();
-    uint32_t bin;
-    resolve_block<kBins3>(hist, need64, bin, need64, small, small + 8);
-    const uint32_t T = lo + bin, need = (uint32_t)need64;
-    // ---- keys above / equal to it before this wavefront's (16 bits each: there are 16384 candidates at most)
-    uint32_t both = 0;
-#pragma unroll
-    for (int r = 0; r < kSmallRounds; ++r) {
-        if ((uint32_t)r >= rounds) break;
-        const uint32_t key = bits[r] & 0x7FFFFFFFu;
-        const bool valid = first + 64u * r < N;
-        both += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(valid && key > T)) + ((uint32_t)__popcll(__builtin_amdgcn_ballot_w64(valid && key == T)) << 16);
-    }
-    if (lane == 0) wtot[wave] = both;
-    __syncthreads();
-    const uint32_t v = lane < (uint32_t)kSelWaves ? wtot[lane] : 0u, before = (uint32_t)__builtin_amdgcn_readlane((int)(wave_scan_incl(v) - v), (int)wave);
-    uint32_t gt0 = before & 0xFFFFu, eq0 = before >> 16;
-    uint32_t *idx = reinterpret_cast<uint32_t *>(reinterpret_cast<uint8_t *>(job.hdr) + kHeaderBytes);
-    float *val = reinterpret_cast<float *>(idx + k);
-#pragma unroll
-    for (int r = 0; r < kSmallRounds; ++r) {
-        if ((uint32_t)r >= rounds) break;
-        if (emit_head<ALGO, EF>(bits[r], at[r], first + 64u * r < N, 0u, n, k, job.st, idx, val, T, need, gt0, eq0)) atomicAdd(&kept[at[r] / (uint32_t)kTile], 1u);
-    }
-    __syncthreads();
     if (wave == 0) {
         const uint32_t own = lane < (uint32_t)kSmallSelTiles ? kept[lane] : 0u, incl = wave_scan_incl(own);
         uint32_t *dir = payload_directory(job.hdr, k);

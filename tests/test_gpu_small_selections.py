@@ -84,6 +84,31 @@ def test_same_as_the_two_kernels_in_calls_of_every_kind(algo):
     b.close()
 
 
+@pytest.mark.parametrize("tiles", [8, 9, 32])            # on the slow routes: one block, three, eight
+@pytest.mark.parametrize("passed", [600, 1023, 1025, 2047, 2048, 2049, 4097, 16383, 16384, 16385, 32000])
+def test_as_many_candidates(tiles, passed):
+    """So many elements within half a percent of each other and all others far below: they and no others pass the filter,
+    spread over the group, and crowded into as few chunks as hold them."""
+    n = tiles * 4096 - 5
+    ppm = 1000000 * 600 // n
+    cfg = O.Config(O.TOPK, use_ef=0, ratio_ppm=ppm, seed=4)
+    for crowded in (False, True):
+        ctx = B.Context("topk", [n], [0, 1], use_ef=0, ratio_ppm=ppm, seed=4)
+        pay = torch.full((ctx.payload_bytes(0),), 0xAB, dtype=torch.uint8, device=H.DEV)
+        rng = np.random.default_rng([tiles, passed, crowded])
+        for it in range(4):
+            g = (rng.standard_normal(n) * 1e-4).astype(np.float32)
+            at = n - passed + np.arange(passed) if crowded else rng.permutation(n)[:passed]
+            g[at] = rng.uniform(1.0, 1.005, passed).astype(np.float32) * np.where(rng.random(passed) < 0.5, 1.0, -1.0).astype(np.float32)
+            ctx.mc_compress(0, 0, it, H.device_tensors(g, [n]), None, pay)
+            want, _ = O.compress(cfg, g, None, group_off=0, worker=0, it=it)
+            assert np.array_equal(pay.cpu().numpy(), want), (crowded, it)
+            if it:                               # (the first call of a context takes no filter)
+                assert ctx.mc_last_select_route() == B.MC_SELECT_FAST and ctx.mc_select_stats()["last_candidates"] == passed
+        assert ctx.mc_last_device_status() == B.MC_OK
+        ctx.close()
+
+
 @pytest.mark.parametrize("algo", ALGOS)
 def test_slow_routes_of_groups_of_every_size(algo):
     """The largest values rise and fall by turns, so that every call misses the window, and then many are equal: groups whose slow
