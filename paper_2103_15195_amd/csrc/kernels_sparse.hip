@@ -2011,6 +2011,7 @@ template void launch_sparse_compress<AllSparse>(const LaunchCtx &, int, const Al
 // return nothing instead of a read, an addition and a write: 40, exact too, but about a lane per clock.)
 // ---------------------------------------------------------------------------
 constexpr int kSparseBatch = 8;    // workers whose entries are in flight together
+constexpr uint32_t kNear = 768u;   // longest run of which add_entries<.., true> looks for the chunk's part where it ought to be
 constexpr int kSparseRounds = 4;   // rounds of 64 entries of a chunk's run, of half as many workers, where a run has more than 128
 
 // Entries from[b] .. from[b] + len[b] - 1 of workers b0 .. b0 + NB - 1 of a batch, ROUNDS of 64 of each asked for at once; of
@@ -2018,8 +2019,10 @@ constexpr int kSparseRounds = 4;   // rounds of 64 entries of a chunk's run, of 
 // entry reads the run's last one (of an empty run what lies in the payload where it would start) and adds it to a word
 // that nobody reads.  (With conditions every load waited for the one before, the registers of one path being taken for those
 // of another.)
-template <int NB, int ROUNDS>
-__device__ __forceinline__ void add_entries(const uint8_t *const (&pl)[kSparseBatch], int b0, uint32_t k, const uint32_t (&from)[kSparseBatch],
+// NEAR: of a run longer than that, the ROUNDS of 64 around the place where the chunk's part lies if the run is spread evenly
+// over the tile.  Whether they hold all of it, their first and last entry say; false, and nothing added, if not.
+template <int NB, int ROUNDS, bool NEAR = false>
+__device__ __forceinline__ bool add_entries(const uint8_t *const (&pl)[kSparseBatch], int b0, uint32_t k, const uint32_t (&from)[kSparseBatch],
                                             const uint32_t (&len)[kSparseBatch], uint32_t base, float *sums /* LDS, kChunk and a word that nobody reads */)
 {
     const uint32_t lane = threadIdx.x & 63u;
@@ -2028,9 +2031,16 @@ __device__ __forceinline__ void add_entries(const uint8_t *const (&pl)[kSparseBa
     // (Ordinary loads: the tile's four wavefronts read the same lines, and neighbouring tiles share theirs.  As non-temporal
     // loads each went to memory, behind the stores: 25.6 M elements, 8 workers, Top-k 1 % 31.3 us, then 27.3; thinly spread
     // payloads (Rand-k) 34.3, then 26.1; 44.5 M heavy-tailed ones 50.1, then 39.3.)
+    constexpr uint32_t kMost = 64u * ROUNDS;
+    const uint32_t eighth = 2u * (base / (uint32_t)kChunk % (uint32_t)kWavesPerBlock) + 1u;      // the chunk's middle, in eighths of the tile
+    auto skipped = [&](int b) {                  // entries of the run before those that are looked at
+        const uint32_t n = len[b0 + b], middle = n * eighth >> 3;
+        return n <= kMost || middle <= kMost / 2 ? 0u : min(middle - kMost / 2, n - kMost);
+    };
     auto fetch = [&](int b, uint32_t at) {
         const uint32_t n = len[b0 + b];
         const global_ptr<const uint8_t> idx = in_global(pl[b0 + b] + kHeaderBytes) + 4u * (uint64_t)from[b0 + b], val = idx + 4u * (uint64_t)k;
+        if (NEAR) at = skipped(b);
 #pragma unroll
         for (int r = 0; r < ROUNDS; ++r) {
             const uint32_t o = at + 64u * r + lane, e = 4u * (o < n ? o : n ? n - 1u : 0u);      // in bytes: 16 KiB at most
@@ -2044,7 +2054,7 @@ __device__ __forceinline__ void add_entries(const uint8_t *const (&pl)[kSparseBa
 #pragma unroll
         for (int r = 0; r < ROUNDS; ++r) {
             const uint32_t local = ix[b][r] - base;
-            to[r] = local < (uint32_t)kChunk && at + 64u * r + lane < len[b0 + b] ? local : (uint32_t)kChunk;
+            to[r] = local < (uint32_t)kChunk && (NEAR ? skipped(b) : at) + 64u * r + lane < len[b0 + b] ? local : (uint32_t)kChunk;
             old[r] = sums[to[r]];
         }
 #pragma unroll
@@ -2053,12 +2063,23 @@ __device__ __forceinline__ void add_entries(const uint8_t *const (&pl)[kSparseBa
     };
 #pragma unroll
     for (int b = 0; b < NB; ++b) fetch(b, 0u);
+    if (NEAR) {
+        bool missed = false;
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {           // (the entries ascend)
+            const uint32_t n = len[b0 + b], at = skipped(b);
+            missed = missed || (at && (uint32_t)__builtin_amdgcn_readlane((int)ix[b][0], 0) > base) ||
+                     (at + kMost < n && (uint32_t)__builtin_amdgcn_readlane((int)ix[b][ROUNDS - 1], 63) < base + (uint32_t)kChunk - 1u);
+        }
+        if (missed) return false;
+    }
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
         add(b, 0u);
-        if (ROUNDS >= kSparseRounds)
-            for (uint32_t at = 64u * ROUNDS; at < len[b0 + b]; at += 64u * ROUNDS) { fetch(b, at); add(b, at); }
+        if (!NEAR && ROUNDS >= kSparseRounds)
+            for (uint32_t at = kMost; at < len[b0 + b]; at += kMost) { fetch(b, at); add(b, at); }
     }
+    return true;
 }
 
 // k64: entries a payload has room for (the exact k, or the capacity when DGC takes its threshold from a sample: the
@@ -2110,20 +2131,32 @@ __global__ __launch_bounds__(kBlock) void sparse_decompress_k(int algo, SRC src,
             __builtin_amdgcn_wave_barrier();
             touched = true;
         }
-        // At most one entry per lane (of one to four workers, four): all are looked at by each of the tile's wavefronts.
-        // (Finding the chunk's part first is one more wait for memory, and worth it only for eight workers' longer runs.  5 % of
-        // 25 M elements, spread evenly, 2 / 3 / 5 workers: 23.9 / 25.8 / 28.1 -> 20.5 / 22.5 / 26.4 us, 4.4 M 7.8 / 7.8 / 9.7 -> 7.0 / 7.4 / 8.4.)
+        // Runs of at most 64 entries, of up to six workers 256, are read whole by each of the tile's wavefronts.  (Finding the
+        // chunk's part first is one more wait for memory.  5 % of 25 M elements, spread evenly, 2 / 3 / 5 workers: 23.9 / 25.8 / 28.1 ->
+        // 20.5 / 22.5 / 26.4 us, 4.4 M 7.8 / 7.8 / 9.7 -> 7.0 / 7.4 / 8.4.)
+        // Longer runs of up to six workers are read where the chunk's part ought to be, 256 entries (five and six workers:
+        // 192 while that surely holds it), which needs no such wait where the run is spread evenly over the tile, as it is but where
+        // tensors of different scales meet.  (4.4 M elements, 1 / 2 / 3 / 4 / 5 / 6 workers, found first -> so: 7 %, 6.4 / 6.8 / 8.3 / 8.2 / 8.6 / 8.6 -> 6.4 /
+        // 6.5 / 7.2 / 7.0 / 7.8 / 7.9 us, 12 % 7.3 / 7.0 / 8.2 / 8.2 / 10.0 / 10.0 -> 6.1 / 6.1 / 6.9 / 7.0 / 8.2 / 8.4; 25 M, 15 %, 1 / 3 / 6 workers 21.0 / 30.2 / 46.5
+        // -> 20.0 / 30.7 / 43.5.  Read whole up to 512, three and four workers: 7 % 7.6 / 7.7, but of 25 M elements 10 % 31.4 instead of 29.2.)
         const int there = W - w0;
-        if (there == 1 && most <= 64u * kSparseRounds) { add_entries<1, kSparseRounds>(pl, 0, k, lo, len, c.base, sums); continue; }
+        if (there == 1 && most <= kNear && add_entries<1, kSparseRounds, true>(pl, 0, k, lo, len, c.base, sums)) continue;
         if (there > kSparseBatch / 2 && most <= 64u) { add_entries<kSparseBatch, 1>(pl, 0, k, lo, len, c.base, sums); continue; }
         if (there <= kSparseBatch / 2 && most <= 64u) { add_entries<kSparseBatch / 2, 1>(pl, 0, k, lo, len, c.base, sums); continue; }
-        if (there == 1 && most <= 128u * kSparseRounds) { add_entries<1, 2 * kSparseRounds>(pl, 0, k, lo, len, c.base, sums); continue; }
-        if (there == 2 && most <= 128u * kSparseRounds) { add_entries<2, kSparseRounds>(pl, 0, k, lo, len, c.base, sums); continue; }
-        if (there <= kSparseBatch / 2 && most <= 64u * kSparseRounds) { add_entries<kSparseBatch / 2, kSparseRounds>(pl, 0, k, lo, len, c.base, sums); continue; }
-        if (there <= 6 && most <= 64u * kSparseRounds) {
+        if (there == 2 && most <= kNear && add_entries<2, kSparseRounds, true>(pl, 0, k, lo, len, c.base, sums)) continue;
+        if (there > 2 && there <= 6 && most <= 64u * kSparseRounds) {
             add_entries<kSparseBatch / 2, kSparseRounds>(pl, 0, k, lo, len, c.base, sums);
-            add_entries<2, kSparseRounds>(pl, kSparseBatch / 2, k, lo, len, c.base, sums);
+            if (there > kSparseBatch / 2) add_entries<2, kSparseRounds>(pl, kSparseBatch / 2, k, lo, len, c.base, sums);
             continue;
+        }
+        if (there > 2 && there <= kSparseBatch / 2 && most <= kNear && add_entries<kSparseBatch / 2, kSparseRounds, true>(pl, 0, k, lo, len, c.base, sums)) continue;
+        if (there > kSparseBatch / 2 && there <= 6) {
+            if (most <= 512u && add_entries<6, kSparseRounds - 1, true>(pl, 0, k, lo, len, c.base, sums)) continue;
+            if (most <= kNear && add_entries<kSparseBatch / 2, kSparseRounds, true>(pl, 0, k, lo, len, c.base, sums)) {
+                if (add_entries<2, kSparseRounds, true>(pl, kSparseBatch / 2, k, lo, len, c.base, sums)) continue;
+#pragma unroll
+                for (int b = 0; b < kSparseBatch / 2; ++b) len[b] = 0u;      // (added already)
+            }
         }
         // Else the run's part that lies in the chunk is found first, to a 64th of the run: every 64th entry of it (at most: the
         // runs are that short) in a lane, of all workers at once.

@@ -139,3 +139,42 @@ def test_every_header_of_a_call_over_all_groups_is_checked(algo, W):
             wire[w, at[j] + byte] ^= 0x40
     ctx.mc_decompress_sum_groups(pays, W, 1.0, outs)
     assert ctx.mc_last_device_status() == B.MC_OK
+
+
+def near_window(n, chunk, size):
+    """The entries of a run that are looked at for a chunk of its tile: `size` around where they lie if spread evenly."""
+    middle = n * (2 * chunk + 1) // 8
+    return 0 if n <= size or middle <= size // 2 else min(middle - size // 2, n - size)
+
+
+@pytest.mark.parametrize("W", [1, 2, 3, 4, 5, 6, 9, 12, 14])
+@pytest.mark.parametrize("n_run", [256, 257, 300, 511, 512, 513, 640, 768, 769])
+def test_long_runs_of_few_workers(W, n_run):
+    """Runs that are read where the chunk's part ought to be, of all workers the same length or nearly: spread evenly (the
+    part is there), and of one worker crowded so that a chunk's part begins or ends up to one entry beside what is read."""
+    n, tile = 5 * 4096 + 77, 2 * 4096
+    k = O.topk_count(n, 60000)
+    ctx = B.Context("topk", [9000, n - 9000], [0, 2], ratio_ppm=60000)
+    rng = np.random.default_rng([W, n_run])
+    others = np.r_[0:tile, tile + 4096:n]
+    cases = [("even", 0, 0, 0, 256)] + [(side, c, d, w, size) for side in ("begins", "ends") for c in range(4) for d in (-1, 0, 1)
+                                        for w, size in {(0, 256), (W - 1, 256), (W - 1, 192)}]
+    for side, c, d, astray, size in cases:
+        sent = []
+        for w in range(W):
+            run = n_run - (w % 3 == 1)
+            inside = np.sort(rng.choice(4096, run, replace=False))
+            if side != "even" and w == astray:
+                at = near_window(run, c, size) + (d if side == "begins" else size + d)           # entries before the edge
+                edge = 1024 * (c if side == "begins" else c + 1)
+                at = min(max(at, run - (4096 - edge)), min(run, edge), run) if 0 <= at <= run else run * edge // 4096
+                inside = np.concatenate([rng.choice(edge, at, replace=False), edge + rng.choice(4096 - edge, run - at, replace=False)])
+                if d == 0 and edge < 4096 and run > at:      # ... and the first one behind it right there
+                    inside[at] = edge if edge not in inside[at:] else inside[at]
+            idx = np.sort(np.concatenate([tile + inside, rng.choice(others, k - run, replace=False)])).astype(np.uint32)
+            sent.append(O.with_directory(B.ALGO_IDS["topk"], n, idx, rng.standard_normal(k).astype(np.float32)))
+        out = [torch.full((m,), 5.0, device=DEV) for m in (9000, n - 9000)]
+        ctx.mc_decompress_sum(0, [torch.from_numpy(p).to(DEV) for p in sent], 0.25, out)
+        got, want = torch.cat(out).cpu().numpy(), O.decompress_sum(sent, n, 0.25)
+        assert np.array_equal(got.view(np.uint32), want.view(np.uint32)), (side, c, d, astray, size)
+    assert ctx.mc_last_device_status() == B.MC_OK
