@@ -2011,6 +2011,7 @@ template void launch_sparse_compress<AllSparse>(const LaunchCtx &, int, const Al
 // return nothing instead of a read, an addition and a write: 40, exact too, but about a lane per clock.)
 // ---------------------------------------------------------------------------
 constexpr int kSparseBatch = 8;    // workers whose entries are in flight together
+constexpr int kFewWorkers = 6;
 constexpr uint32_t kNear = 768u;   // longest run of which add_entries<.., true> looks for the chunk's part where it ought to be
 constexpr int kSparseRounds = 4;   // rounds of 64 entries of a chunk's run, of half as many workers, where a run has more than 128
 
@@ -2084,7 +2085,10 @@ __device__ __forceinline__ bool add_entries(const uint8_t *const (&pl)[kSparseBa
 
 // k64: entries a payload has room for (the exact k, or the capacity when DGC takes its threshold from a sample: the
 // header then says how many are in use and repeats the capacity)
-template <class SRC>
+// FEW: up to kFewWorkers workers.  Two kernels, because every form of add_entries is a copy of its own and every copy costs both
+// registers and spilled scalars: 106 of those leave 7 wavefronts per SIMD (8 when asked for, with 154 spilled instead of 81: up to 9 %
+// slower), and with the forms for few workers in the same kernel the sum of eight took 0.5 to 2 % longer.
+template <class SRC, bool FEW>
 __global__ __launch_bounds__(kBlock) void sparse_decompress_k(int algo, SRC src, int W, float alpha, int *status, int capped)
 {
     __shared__ float acc[kWavesPerBlock][kChunk + 32];
@@ -2101,7 +2105,7 @@ __global__ __launch_bounds__(kBlock) void sparse_decompress_k(int algo, SRC src,
     float *sums = acc[(c.base / (uint32_t)kChunk) % (uint32_t)kWavesPerBlock];
     bool touched = false;
 #pragma unroll 1
-    for (int w0 = 0; w0 < W; w0 += kSparseBatch) {
+    for (int w0 = 0; w0 < (FEW ? 1 : W); w0 += kSparseBatch) {
         // the tile's run in the list of every worker of the batch, as the directories have it; of absent workers none
         const uint8_t *pl[kSparseBatch];
         uint32_t lo[kSparseBatch], hi[kSparseBatch];
@@ -2134,28 +2138,43 @@ __global__ __launch_bounds__(kBlock) void sparse_decompress_k(int algo, SRC src,
         // Runs of at most 64 entries, of up to six workers 256, are read whole by each of the tile's wavefronts.  (Finding the
         // chunk's part first is one more wait for memory.  5 % of 25 M elements, spread evenly, 2 / 3 / 5 workers: 23.9 / 25.8 / 28.1 ->
         // 20.5 / 22.5 / 26.4 us, 4.4 M 7.8 / 7.8 / 9.7 -> 7.0 / 7.4 / 8.4.)
-        // Longer runs of up to six workers are read where the chunk's part ought to be, 256 entries (five and six workers:
-        // 192 while that surely holds it), which needs no such wait where the run is spread evenly over the tile, as it is but where
-        // tensors of different scales meet.  (4.4 M elements, 1 / 2 / 3 / 4 / 5 / 6 workers, found first -> so: 7 %, 6.4 / 6.8 / 8.3 / 8.2 / 8.6 / 8.6 -> 6.4 /
-        // 6.5 / 7.2 / 7.0 / 7.8 / 7.9 us, 12 % 7.3 / 7.0 / 8.2 / 8.2 / 10.0 / 10.0 -> 6.1 / 6.1 / 6.9 / 7.0 / 8.2 / 8.4; 25 M, 15 %, 1 / 3 / 6 workers 21.0 / 30.2 / 46.5
-        // -> 20.0 / 30.7 / 43.5.  Read whole up to 512, three and four workers: 7 % 7.6 / 7.7, but of 25 M elements 10 % 31.4 instead of 29.2.)
         const int there = W - w0;
-        if (there == 1 && most <= kNear && add_entries<1, kSparseRounds, true>(pl, 0, k, lo, len, c.base, sums)) continue;
-        if (there > kSparseBatch / 2 && most <= 64u) { add_entries<kSparseBatch, 1>(pl, 0, k, lo, len, c.base, sums); continue; }
-        if (there <= kSparseBatch / 2 && most <= 64u) { add_entries<kSparseBatch / 2, 1>(pl, 0, k, lo, len, c.base, sums); continue; }
-        if (there == 2 && most <= kNear && add_entries<2, kSparseRounds, true>(pl, 0, k, lo, len, c.base, sums)) continue;
-        if (there > 2 && there <= 6 && most <= 64u * kSparseRounds) {
-            add_entries<kSparseBatch / 2, kSparseRounds>(pl, 0, k, lo, len, c.base, sums);
-            if (there > kSparseBatch / 2) add_entries<2, kSparseRounds>(pl, kSparseBatch / 2, k, lo, len, c.base, sums);
-            continue;
-        }
-        if (there > 2 && there <= kSparseBatch / 2 && most <= kNear && add_entries<kSparseBatch / 2, kSparseRounds, true>(pl, 0, k, lo, len, c.base, sums)) continue;
-        if (there > kSparseBatch / 2 && there <= 6) {
-            if (most <= 512u && add_entries<6, kSparseRounds - 1, true>(pl, 0, k, lo, len, c.base, sums)) continue;
-            if (most <= kNear && add_entries<kSparseBatch / 2, kSparseRounds, true>(pl, 0, k, lo, len, c.base, sums)) {
-                if (add_entries<2, kSparseRounds, true>(pl, kSparseBatch / 2, k, lo, len, c.base, sums)) continue;
+        if (FEW) {
+            if (there == 1 && most <= kNear && add_entries<1, kSparseRounds, true>(pl, 0, k, lo, len, c.base, sums)) continue;
+            if (there <= kSparseBatch / 2 && most <= 64u) { add_entries<kSparseBatch / 2, 1>(pl, 0, k, lo, len, c.base, sums); continue; }
+            if (there > kSparseBatch / 2 && most <= 64u) { add_entries<kFewWorkers, 1>(pl, 0, k, lo, len, c.base, sums); continue; }
+            if (there == 2 && most <= kNear && add_entries<2, kSparseRounds, true>(pl, 0, k, lo, len, c.base, sums)) continue;
+            if (there > 2 && most <= 64u * kSparseRounds) {
+                add_entries<kSparseBatch / 2, kSparseRounds>(pl, 0, k, lo, len, c.base, sums);
+                if (there > kSparseBatch / 2) add_entries<2, kSparseRounds>(pl, kSparseBatch / 2, k, lo, len, c.base, sums);
+                continue;
+            }
+            // Longer runs are read where the chunk's part ought to be, 256 entries (five and six workers: 192 while that surely
+            // holds it), which needs no such wait where the run is spread evenly over the tile, as it is but where tensors of
+            // different scales meet.  (4.4 M elements, 1 / 2 / 3 / 4 / 5 / 6 workers, found first -> so: 7 %, 6.4 / 6.8 / 8.3 / 8.2 / 8.6 / 8.6 ->
+            // 6.4 / 6.5 / 7.2 / 7.0 / 7.8 / 7.9 us, 12 % 7.3 / 7.0 / 8.2 / 8.2 / 10.0 / 10.0 -> 6.1 / 6.1 / 6.9 / 7.0 / 8.2 / 8.4; 25 M, 15 %, 1 / 3 / 6 workers
+            // 21.0 / 30.2 / 46.5 -> 20.0 / 30.7 / 43.5.  Read whole up to 512, three and four workers: 7 % 7.6 / 7.7, but of 25 M elements
+            // 10 % 31.4 instead of 29.2.)
+            if (there > 2 && there <= kSparseBatch / 2 && most <= kNear && add_entries<kSparseBatch / 2, kSparseRounds, true>(pl, 0, k, lo, len, c.base, sums)) continue;
+            if (there > kSparseBatch / 2) {
+                if (most <= 512u && add_entries<kFewWorkers, kSparseRounds - 1, true>(pl, 0, k, lo, len, c.base, sums)) continue;
+                if (most <= kNear && add_entries<kSparseBatch / 2, kSparseRounds, true>(pl, 0, k, lo, len, c.base, sums)) {
+                    if (add_entries<2, kSparseRounds, true>(pl, kSparseBatch / 2, k, lo, len, c.base, sums)) continue;
 #pragma unroll
-                for (int b = 0; b < kSparseBatch / 2; ++b) len[b] = 0u;      // (added already)
+                    for (int b = 0; b < kSparseBatch / 2; ++b) len[b] = 0u;      // (added already)
+                }
+            }
+        } else {
+            if (there == 1 && most <= 64u * kSparseRounds) { add_entries<1, kSparseRounds>(pl, 0, k, lo, len, c.base, sums); continue; }
+            if (there > kSparseBatch / 2 && most <= 64u) { add_entries<kSparseBatch, 1>(pl, 0, k, lo, len, c.base, sums); continue; }
+            if (there <= kSparseBatch / 2 && most <= 64u) { add_entries<kSparseBatch / 2, 1>(pl, 0, k, lo, len, c.base, sums); continue; }
+            if (there == 1 && most <= 128u * kSparseRounds) { add_entries<1, 2 * kSparseRounds>(pl, 0, k, lo, len, c.base, sums); continue; }
+            if (there == 2 && most <= 128u * kSparseRounds) { add_entries<2, kSparseRounds>(pl, 0, k, lo, len, c.base, sums); continue; }
+            if (there <= kSparseBatch / 2 && most <= 64u * kSparseRounds) { add_entries<kSparseBatch / 2, kSparseRounds>(pl, 0, k, lo, len, c.base, sums); continue; }
+            if (there <= 6 && most <= 64u * kSparseRounds) {
+                add_entries<kSparseBatch / 2, kSparseRounds>(pl, 0, k, lo, len, c.base, sums);
+                add_entries<2, kSparseRounds>(pl, kSparseBatch / 2, k, lo, len, c.base, sums);
+                continue;
             }
         }
         // Else the run's part that lies in the chunk is found first, to a 64th of the run: every 64th entry of it (at most: the
@@ -2179,10 +2198,10 @@ __global__ __launch_bounds__(kBlock) void sparse_decompress_k(int algo, SRC src,
         }
         if (there == 1) add_entries<1, 2 * kSparseRounds>(pl, 0, k, lo, len, c.base, sums);
         else if (there == 2) add_entries<2, kSparseRounds>(pl, 0, k, lo, len, c.base, sums);
-        else if (most <= 128u && there > kSparseBatch / 2) add_entries<kSparseBatch, 2>(pl, 0, k, lo, len, c.base, sums);
+        else if (most <= 128u && there > kSparseBatch / 2) add_entries<FEW ? kFewWorkers : kSparseBatch, 2>(pl, 0, k, lo, len, c.base, sums);
         else {
             add_entries<kSparseBatch / 2, kSparseRounds>(pl, 0, k, lo, len, c.base, sums);
-            if (there > kSparseBatch / 2) add_entries<kSparseBatch / 2, kSparseRounds>(pl, kSparseBatch / 2, k, lo, len, c.base, sums);
+            if (there > kSparseBatch / 2) add_entries<FEW ? kFewWorkers - kSparseBatch / 2 : kSparseBatch / 2, kSparseRounds>(pl, kSparseBatch / 2, k, lo, len, c.base, sums);
         }
     }
     // Stored in the mapping rotated onto the output's 128-byte lines (payloads spread thinly over all tiles: 37.2 -> 36.3 us;
@@ -2204,7 +2223,9 @@ void launch_sparse_decompress(const LaunchCtx &lc, int algo, const SRC &src, uin
 {
     if (tiles == 0) return;
     prof_begin(lc, K_SPARSE_DECOMPRESS);
-    MC_LAUNCH(sparse_decompress_k<SRC>, dim3(tiles + SRC::kCheckers) /* the first ones check the headers */, dim3(kBlock), lc, algo, src, W, alpha, status, capped ? 1 : 0);
+    const dim3 grid(tiles + SRC::kCheckers), block(kBlock);         // (the first blocks check the headers)
+    if (W <= kFewWorkers) MC_LAUNCH((sparse_decompress_k<SRC, true>), grid, block, lc, algo, src, W, alpha, status, capped ? 1 : 0);
+    else MC_LAUNCH((sparse_decompress_k<SRC, false>), grid, block, lc, algo, src, W, alpha, status, capped ? 1 : 0);
     prof_end(lc, K_SPARSE_DECOMPRESS);
 }
 template void launch_sparse_decompress<OneDecompress>(const LaunchCtx &, int, const OneDecompress &, uint32_t, int, float, int *, bool);
