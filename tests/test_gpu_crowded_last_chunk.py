@@ -1,6 +1,7 @@
 """A sparsifier whose scratch ends in a crowded chunk: the last 1024 elements of the last tile hold 832 to 1024 candidates, so
 that on the usual route the select and emit kernels read the chunk's fourth unit, of which the last part lies behind the
-chunk.  One group, and the last of two (each has its own part of the scratch)."""
+chunk.  One group, and the last of two (each has its own part of the scratch).  Those two kernels serve groups of more
+than 32 tiles; the groups of two and three tiles are selected from by the kernel for small groups, entry by entry."""
 import numpy as np
 import pytest
 import torch
@@ -14,7 +15,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("large", [832, 833, 1000, 1024])
-@pytest.mark.parametrize("numel", [[2 * 4096], [5000, 3 * 4096]])
+@pytest.mark.parametrize("numel", [[2 * 4096], [5000, 3 * 4096], [33 * 4096], [5000, 34 * 4096]])
 def test_last_chunk_is_crowded(large, numel):
     y, n = len(numel), numel[-1]
     ppm = 1000000 * 600 // n                     # k = 600 of the last group: the large values and no others are candidates
