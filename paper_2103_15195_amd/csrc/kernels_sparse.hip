@@ -1937,9 +1937,7 @@ static void sparse_compress_t(const LaunchCtx &lc, const SRC &src, const SparseB
     // the slow routes run on blocks that the device holds at once: one per compute unit
     const uint32_t sync = std::max(1u, std::min(call.sync_blocks, (uint32_t)(kRoundTiles / kSelWaves)));
     if (nb.small) {
-        prof_begin(lc, K_LEAN_SELECT);
-        MC_LAUNCH((lean_small_k<ALGO, EF, SRC>), dim3(nb.small), dim3(kSelThreads), lc, src, rng, sync, call.status);
-        prof_end(lc, K_LEAN_SELECT);
+        MC_LAUNCH((lean_small_k<ALGO, EF, SRC>), dim3(nb.small), dim3(kSelThreads), lc, src, rng, sync, call.status);      // (the profiler is off)
         return;
     }
     // the two-kernel tail
