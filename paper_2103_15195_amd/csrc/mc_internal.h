@@ -92,9 +92,12 @@ __device__ __forceinline__ GroupView view_of(const GroupTable &tb, const GroupCo
 constexpr uint32_t kSmallTiles = 64;
 constexpr int kArriveStride = 16;             // 64-bit words between the groups' counts (a line each)
 constexpr uint32_t kWaitLooks = 1u << 10;     // looks of about a microsecond each before a waiting quantizer's block leaves its tile to the last one
-// Launches of at most this many tiles, of all their groups, spread a tile over kSpread threads (two such blocks fit a compute
-// unit, 512 the card).  Compress of 2 / 4 / 8 M elements (489 / 977 / 1954 tiles), 16 elements per lane / spread: FP16 6.0 / 10.6 / 19.6
-// and 6.0 / 10.4 / 19.6 us, SignSGD 4.4 / 5.5 / 7.4 and 3.4 / 5.4 / 9.2, Top-k 20.4 / 24.8 / 34.5 and 19.2 / 24.4 / 35.1.
+// Launches of at most this many tiles, of all their groups, spread a tile over kSpread threads: two such blocks fit a compute
+// unit, 512 the card, so that up to here all of them run at once.  Compress of 256 / 500 / 800 / 1200 / 2000 tiles, 16 elements per lane
+// and spread: SigNUM 4.9 / 5.7 / 8.1 / 10.3 / 16.4 and 4.3 / 5.0 / 7.4 / 10.2 / 16.6 us, FP16 4.6 / 5.6 / 8.6 / 11.4 / 18.9 and 4.5 / 5.5 / 7.8 / 11.2 /
+// 18.7, Top-k 17.6 / 19.0 / 21.8 / 24.8 / 32.9 and 16.4 / 17.9 / 21.5 / 24.8 / 32.5, SignSGD 4.2 / 4.3 / 4.5 / 5.1 / 6.9 and 4.3 / 4.2 / 4.4 / 5.7 / 8.6.
+// (The spread form is still ahead up to about 900 tiles and clearly behind from 1200 on only where next to nothing is read besides the
+// gradient: the line is on the safe side of all of them.)
 constexpr uint32_t kSpreadTiles = 512;
 // ... and EF-Sign and OneBit, which sum p in the order of the other form: 400 000 / 1 M / 2 M elements, EF-Sign 8.1 / 8.7 / 10.0 and
 // 7.8 / 8.8 / 10.4, OneBit 9.8 / 10.5 / 11.8 and 9.6 / 10.5 / 13.0.
