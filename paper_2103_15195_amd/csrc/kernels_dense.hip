@@ -1086,9 +1086,9 @@ __global__ __launch_bounds__(kBlock) void dense_decompress_k(SRC src, int W, flo
             float scale[kBatch];
 #pragma unroll
             for (int b = 0; b < kBatch; ++b) {
-            scale[b] = 0.0f;
-            if (w0 + b < W) scale[b] = ld_uniform(&reinterpret_cast<const PayloadHeader *>(pl[b])->scale);
-        }
+                scale[b] = 0.0f;
+                if (w0 + b < W) scale[b] = ld_uniform(&reinterpret_cast<const PayloadHeader *>(pl[b])->scale);
+            }
             uint32_t cw[kBatch][4];
 #pragma unroll
             for (int b = 0; b < kBatch; ++b) {

@@ -137,10 +137,9 @@ __device__ __forceinline__ void store_flat(T *buf, const Chunk &c, uint32_t n, c
 // elements: in step j lane l holds element (64 j + l + rot) mod 1024 of the chunk, with rot chosen such
 // that element `rot` lies on a line boundary.  Every wave store then covers two whole lines; only step 15
 // wraps round to the chunk's first `rot` elements.  (Measured in the library: the one-plane decompress
-// gains 2.4-3 us of 32 and the sparse decompress 0.5 us on its zero-fill path; the TernGrad decompress and
-// the sparse one's LDS path lose 1.5-3 us, QSGD and FP16 lose up to 8 us when their code loads are rotated
-// too (they then straddle lines) and gain or lose about 1 us when only the sums are rotated with
-// ds_bpermute: those keep the plain mapping.)
+// gains 2.4-3 us of 32, the sparse decompress 0.2-0.9; both store that way.  The TernGrad decompress
+// loses 1.5 us, QSGD and FP16 lose up to 8 us when their code loads are rotated too (they then straddle
+// lines) and gain or lose about 1 us when only the sums are rotated with ds_bpermute: those keep the plain mapping.)
 constexpr uint32_t kLineElems = 32;        // 128-byte cache line
 __device__ __forceinline__ uint32_t chunk_rotation(uintptr_t entry)       // 0 for a chunk without an address of its own
 {
