@@ -6,7 +6,9 @@
 // All kernels are HBM-streaming: each operand is touched once per pass with
 // lane-consecutive 4-byte accesses (256 contiguous bytes per wave instruction),
 // sign / ternary planes are packed with 64-lane ballots, group scalars are
-// reduced per block in LDS and combined by a one-block finalize kernel (in groups of at most 64 tiles by the kernel itself).
+// reduced per block in LDS and combined by the kernel itself: in groups of at most 64 tiles by the block that arrives last, in
+// others by a block that waits for them (OneBit: a one-block kernel after it).
+#include <algorithm>
 #include <cstddef>
 
 #include "mc_internal.h"
@@ -143,12 +145,89 @@ __device__ __forceinline__ double combine_partials(const double *partial, uint32
     return acc;
 }
 
-// SMALL: the group's last block to arrive combines the partials and writes the headers, instead of a kernel after this one.
+// ---- other groups: a collector ---------------------------------------------------------------------------------------
+// The launch's last blocks wait for the partials, which is a store that goes past the die's cache, and combine them as
+// scalar_finalize_k would.  A slot is empty (all ones, which no sum is) until its tile's block has filled it, and the collector empties it
+// again, so that there is nothing to count.  It looks at the last tiles first, which are the first to be done, and when the last
+// block has stored its partial it takes about two trips to memory more, where a kernel of its own took a boundary, a start and the loads of all
+// partials.  (Compress and decompress-and-sum, that kernel -> collectors: 25.6 M elements, EF-Sign 79.8 -> 78.2 us, in 161 groups 79.6 -> 78.1, QSGD
+// in three groups 123.9 -> 122.3; 44.5 M, 16 workers, EF-Sign 142.3 -> 140.5; 10 M, TernGrad 46.5 -> 45.6.)
+constexpr uint64_t kEmptySlot = ~0ull;
+constexpr uint32_t kSlotLooks = 1u << 22;        // of about a microsecond: no call that is in order with the others of its context comes near it
+__device__ __forceinline__ void fill_slot(double *p, double v)
+{
+    const uint64_t x = __builtin_bit_cast(uint64_t, v);
+    __hip_atomic_store(reinterpret_cast<uint64_t *>(p), x == kEmptySlot ? 0x7FF8000000000000ull : x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+constexpr int kFinalThreads = 1024;
+// The sum (maximum) of n slots, in scalar_finalize_k's order: what each of its threads adds is added by itself, THREADS of the
+// block's threads standing for kFinalThreads.
+template <int THREADS, bool MAX>
+__device__ __forceinline__ double collect(double *slots, uint32_t n, double *red /* LDS, a word per wavefront of kFinalThreads */, int *status)
+{
+    constexpr int kEach = kFinalThreads / THREADS, kLoads = 4;
+    uint64_t *const from = reinterpret_cast<uint64_t *>(slots);
+    double acc[kEach];
+#pragma unroll
+    for (int v = 0; v < kEach; ++v) acc[v] = 0.0;
+    uint32_t looks = 0;
+    for (uint32_t top = (n + kFinalThreads - 1u) / kFinalThreads; top > 0u; top = top > (uint32_t)(kLoads / kEach) ? top - (uint32_t)(kLoads / kEach) : 0u) {
+        uint64_t x[kLoads];
+        auto at = [&](int l) {                   // load l: round (the highest first), share; n and more: none
+            const uint32_t r = (uint32_t)(l / kEach), i = (top - 1u - r) * (uint32_t)kFinalThreads + (uint32_t)(l % kEach * THREADS) + threadIdx.x;
+            return r < top ? i : n;
+        };
+        for (;;) {
+            bool missing = false;
+#pragma unroll
+            for (int l = 0; l < kLoads; ++l) x[l] = at(l) < n ? __hip_atomic_load(from + at(l), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0ull;
+#pragma unroll
+            for (int l = 0; l < kLoads; ++l) missing = missing || x[l] == kEmptySlot;
+            if (!missing) break;
+            if (looks++ >= kSlotLooks) { raise_flag(status, FLAG_GAVE_UP); break; }
+            __builtin_amdgcn_s_sleep(1);
+        }
+#pragma unroll
+        for (int l = 0; l < kLoads; ++l) {
+            if (at(l) < n) from[at(l)] = kEmptySlot;
+            const double y = __builtin_bit_cast(double, x[l]);
+            acc[l % kEach] = MAX ? fmax(acc[l % kEach], y) : acc[l % kEach] + y;
+        }
+    }
+#pragma unroll
+    for (int v = 0; v < kEach; ++v) {
+        double s = acc[v];
+#pragma unroll
+        for (int m = 32; m >= 1; m >>= 1) {
+            const double o = __shfl_xor(s, m, 64);
+            s = MAX ? fmax(s, o) : s + o;
+        }
+        if ((threadIdx.x & 63u) == 0) red[v * (THREADS / 64) + (int)(threadIdx.x >> 6)] = s;
+    }
+    __syncthreads();
+    double t = red[0];
+#pragma unroll 4
+    for (int w = 1; w < kFinalThreads / 64; ++w) t = MAX ? fmax(t, red[w]) : t + red[w];
+    __syncthreads();                             // (the collector may have another group)
+    return t;
+}
+// body(group's job) for the groups of this collector, the last ones first
+template <class SRC, class Body>
+__device__ __forceinline__ void each_collected(const SRC &src, Body body)
+{
+    const uint32_t collectors = gridDim.x - src.tiles(), y = src.groups();
+    for (uint32_t q = blockIdx.x - src.tiles(); q < y; q += collectors) {
+        const CompressJob job = src.group_job(y - 1u - q);
+        if (job.ntiles) body(job);
+    }
+}
+
+// HOW = COMBINE_LAST: the group's last block to arrive combines the partials and writes the headers, instead of a kernel after this one.
 // (EF-Sign compress, 1 .. 64 tiles: 8.0 -> 5.6 .. 5.9 us, OneBit 8.6 .. 9.2 -> 6.2 .. 7.5: a launch and a kernel boundary less.
 // With the tile spread over more threads, 33 / 34 000 / 262 000 elements: EF-Sign 5.9 / 5.9 / 6.0 -> 4.8 / 5.4 / 5.8, OneBit 7.4 / 7.5 / 8.0 ->
 // 6.2 / 6.8 / 7.5, SignSGD 3.4 / 3.6 / 3.7 -> 2.2 / 2.4 / 2.6.)
 // S: elements per lane, 16, or 4 on a launch of few tiles (kSpread threads per tile).
-template <int MODE, bool EF, class SRC, bool SMALL = false, int S = kSteps>
+template <int MODE, bool EF, class SRC, int HOW = COMBINE_AFTER, int S = kSteps>
 __global__ __launch_bounds__(kTile / S) void sign_compress_k(SRC src, float beta, uint32_t algo)
 {
     constexpr int kWaves = kTile / S / kWave;
@@ -157,6 +236,20 @@ __global__ __launch_bounds__(kTile / S) void sign_compress_k(SRC src, float beta
     __shared__ double red3[MODE == SIGN_MEANS ? 3 : 1][kWaves];
     constexpr bool kHeld = S != kSteps && (MODE == SIGN_EF || MODE == SIGN_MEANS);
     __shared__ float held[kHeld ? kTile : 1];    // p of the tile, to be summed in the order of the other form
+    if constexpr (HOW == COMBINE_COLLECT) {
+        static_assert(MODE == SIGN_EF, "one sum");
+        __shared__ double sums[kFinalThreads / 64];
+        if (blockIdx.x >= src.tiles()) {
+            each_collected(src, [&](const CompressJob &of) {
+                const float scale = mean_abs(collect<kTile / S, false>(of.slots, of.ntiles, sums, src.status), of.g.n);
+                if (threadIdx.x == 0) {
+                    put_plain_header(of.hdr, algo, of.g.n, scale);
+                    if (EF) of.state_header()->scale = scale;        // (every block of the group has read the last call's)
+                }
+            });
+            return;
+        }
+    }
     const CompressJob job = src.job();
     const GroupView &g = job.g;
     float *st = job.st;
@@ -228,7 +321,11 @@ __global__ __launch_bounds__(kTile / S) void sign_compress_k(SRC src, float beta
     }
     if (MODE == SIGN_EF) {
         double t = block_sum<kWaves>(acc, red);
-        if (threadIdx.x == 0) { if (SMALL) put_partial(job.partial + job.tile, t); else job.partial[job.tile] = t; }
+        if (threadIdx.x == 0) {
+            if (HOW == COMBINE_LAST) put_partial(job.partial + job.tile, t);
+            else if (HOW == COMBINE_COLLECT) fill_slot(job.slots + job.tile, t);
+            else job.partial[job.tile] = t;
+        }
     }
     if (MODE == SIGN_MEANS) {       // the three sums behind one pair of barriers, each combined in block_sum's order
         acc = wave_sum(acc); acc_lo = wave_sum(acc_lo); cnt_hi = wave_sum(cnt_hi);
@@ -241,11 +338,11 @@ __global__ __launch_bounds__(kTile / S) void sign_compress_k(SRC src, float beta
                 const double four = (red3[threadIdx.x][w] + red3[threadIdx.x][w + 1]) + (red3[threadIdx.x][w + 2] + red3[threadIdx.x][w + 3]);
                 t = w ? t + four : four;
             }
-            double *to = job.partial + threadIdx.x * job.ntiles + job.tile;
-            if (SMALL) put_partial(to, t); else *to = t;
+            const uint32_t at = threadIdx.x * job.ntiles + job.tile;
+            if (HOW == COMBINE_LAST) put_partial(job.partial + at, t); else job.partial[at] = t;
         }
     }
-    if (SMALL && threadIdx.x < 64) {             // the wavefront that put the partials
+    if (HOW == COMBINE_LAST && threadIdx.x < 64) {             // the wavefront that put the partials
         uint64_t before = 0;
         if (threadIdx.x == 0) before = arrive_at(job.arrive);
         before = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)before) |
@@ -266,43 +363,47 @@ __global__ __launch_bounds__(kTile / S) void sign_compress_k(SRC src, float beta
     }
 }
 
-template <int MODE, bool EF, bool SMALL, class SRC>
-static void sign_compress_t(const LaunchCtx &lc, const SRC &src, uint32_t tiles, float beta, uint32_t algo)
+template <int MODE, bool EF, int HOW, class SRC>
+static void sign_compress_t(const LaunchCtx &lc, const SRC &src, uint32_t tiles, uint32_t groups, float beta, uint32_t algo)
 {
     constexpr uint32_t most = MODE == SIGN_EF || MODE == SIGN_MEANS ? kSpreadSumTiles : kSpreadTiles;
-    if (tiles <= most) MC_LAUNCH((sign_compress_k<MODE, EF, SRC, SMALL, kSpreadSteps>), dim3(tiles), dim3(kSpread), lc, src, beta, algo);
-    else MC_LAUNCH((sign_compress_k<MODE, EF, SRC, SMALL>), dim3(tiles), dim3(kBlock), lc, src, beta, algo);
+    const dim3 grid(tiles + (HOW == COMBINE_COLLECT ? std::min(groups, kCollectors) : 0u));
+    if (tiles <= most) MC_LAUNCH((sign_compress_k<MODE, EF, SRC, HOW, kSpreadSteps>), grid, dim3(kSpread), lc, src, beta, algo);
+    else MC_LAUNCH((sign_compress_k<MODE, EF, SRC, HOW>), grid, dim3(kBlock), lc, src, beta, algo);
+}
+template <int MODE, bool EF, class SRC>
+static void sign_compress_how(const LaunchCtx &lc, const SRC &src, uint32_t tiles, uint32_t groups, uint32_t algo, Combine how)
+{
+    if (how == COMBINE_LAST) { sign_compress_t<MODE, EF, COMBINE_LAST>(lc, src, tiles, groups, 0.0f, algo); return; }
+    if constexpr (MODE == SIGN_EF) if (how == COMBINE_COLLECT) { sign_compress_t<MODE, EF, COMBINE_COLLECT>(lc, src, tiles, groups, 0.0f, algo); return; }
+    sign_compress_t<MODE, EF, COMBINE_AFTER>(lc, src, tiles, groups, 0.0f, algo);
 }
 
 template <class SRC>
-void launch_sign_compress(const LaunchCtx &lc, int mode, const SRC &src, uint32_t tiles, bool ef, float beta, uint32_t algo, bool small)
+void launch_sign_compress(const LaunchCtx &lc, int mode, const SRC &src, uint32_t tiles, uint32_t groups, bool ef, float beta, uint32_t algo, Combine how)
 {
     if (tiles == 0) return;
     prof_begin(lc, K_EFSIGN_COMPRESS);
     switch (mode) {
     case SIGN_EF:
-        if (ef && small) sign_compress_t<SIGN_EF, true, true>(lc, src, tiles, beta, algo);
-        else if (ef) sign_compress_t<SIGN_EF, true, false>(lc, src, tiles, beta, algo);
-        else if (small) sign_compress_t<SIGN_EF, false, true>(lc, src, tiles, beta, algo);
-        else sign_compress_t<SIGN_EF, false, false>(lc, src, tiles, beta, algo);
+        if (ef) sign_compress_how<SIGN_EF, true>(lc, src, tiles, groups, algo, how);
+        else sign_compress_how<SIGN_EF, false>(lc, src, tiles, groups, algo, how);
         break;
     case SIGN_MEANS:
-        if (ef && small) sign_compress_t<SIGN_MEANS, true, true>(lc, src, tiles, beta, algo);
-        else if (ef) sign_compress_t<SIGN_MEANS, true, false>(lc, src, tiles, beta, algo);
-        else if (small) sign_compress_t<SIGN_MEANS, false, true>(lc, src, tiles, beta, algo);
-        else sign_compress_t<SIGN_MEANS, false, false>(lc, src, tiles, beta, algo);
+        if (ef) sign_compress_how<SIGN_MEANS, true>(lc, src, tiles, groups, algo, how);
+        else sign_compress_how<SIGN_MEANS, false>(lc, src, tiles, groups, algo, how);
         break;
     case SIGN_PLAIN:
-        sign_compress_t<SIGN_PLAIN, false, false>(lc, src, tiles, beta, algo);
+        sign_compress_t<SIGN_PLAIN, false, COMBINE_AFTER>(lc, src, tiles, groups, beta, algo);
         break;
     default:
-        sign_compress_t<SIGN_MOMENTUM, true, false>(lc, src, tiles, beta, algo);
+        sign_compress_t<SIGN_MOMENTUM, true, COMBINE_AFTER>(lc, src, tiles, groups, beta, algo);
         break;
     }
     prof_end(lc, K_EFSIGN_COMPRESS);
 }
-template void launch_sign_compress<OneCompress>(const LaunchCtx &, int, const OneCompress &, uint32_t, bool, float, uint32_t, bool);
-template void launch_sign_compress<AllCompress>(const LaunchCtx &, int, const AllCompress &, uint32_t, bool, float, uint32_t, bool);
+template void launch_sign_compress<OneCompress>(const LaunchCtx &, int, const OneCompress &, uint32_t, uint32_t, bool, float, uint32_t, Combine);
+template void launch_sign_compress<AllCompress>(const LaunchCtx &, int, const AllCompress &, uint32_t, uint32_t, bool, float, uint32_t, Combine);
 
 // ---------------------------------------------------------------------------
 // One block per group: combine the per-block partials in a fixed order (bit-reproducible
@@ -314,8 +415,6 @@ template void launch_sign_compress<AllCompress>(const LaunchCtx &, int, const Al
 //   RED_MEANS   : three partial arrays (sum of the upper class, of the lower class, size of the
 //                 upper class) -> scale = mean of the upper class, second scalar = mean of the lower
 // ---------------------------------------------------------------------------
-constexpr int kFinalThreads = 1024;
-
 template <class SRC>
 __global__ __launch_bounds__(kFinalThreads) void scalar_finalize_k(SRC src, int mode, uint32_t algo, uint32_t levels, int keep)
 {
@@ -331,13 +430,13 @@ __global__ __launch_bounds__(kFinalThreads) void scalar_finalize_k(SRC src, int 
         // single-sum case
         __shared__ double red3[3][kFinalThreads / 64];
         double acc3[3] = {0.0, 0.0, 0.0};
-        for (uint32_t base = 0; base < nblocks; base += 8 * kFinalThreads) {
+        for (uint32_t rounds = (nblocks + 8u * kFinalThreads - 1u) / (8u * kFinalThreads); rounds-- > 0u;) {
             double v[3][8];
 #pragma unroll
             for (int a = 0; a < 3; ++a)
 #pragma unroll
                 for (int u = 0; u < 8; ++u) {
-                    uint32_t i = base + u * kFinalThreads + threadIdx.x;
+                    const uint32_t i = (8u * rounds + 7u - (uint32_t)u) * (uint32_t)kFinalThreads + threadIdx.x;
                     v[a][u] = i < nblocks ? partial[(size_t)a * nblocks + i] : 0.0;
                 }
 #pragma unroll
@@ -370,12 +469,12 @@ __global__ __launch_bounds__(kFinalThreads) void scalar_finalize_k(SRC src, int 
     double acc = 0.0;
     if (mode >= 0 && mode != RED_ONE) {
         // eight independent loads in flight per thread and round (one round up to 8192 partials);
-        // the order of additions depends on nblocks only
-        for (uint32_t base = 0; base < nblocks; base += 8 * kFinalThreads) {
+        // the order of additions, a collector's (the last tiles are the first to be done), depends on nblocks only
+        for (uint32_t rounds = (nblocks + 8u * kFinalThreads - 1u) / (8u * kFinalThreads); rounds-- > 0u;) {
             double v[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
-                uint32_t i = base + u * kFinalThreads + threadIdx.x;
+                const uint32_t i = (8u * rounds + 7u - (uint32_t)u) * (uint32_t)kFinalThreads + threadIdx.x;
                 v[u] = i < nblocks ? partial[i] : 0.0;
             }
 #pragma unroll
@@ -495,11 +594,21 @@ __device__ __forceinline__ void accumulate(const CompressJob &job, const Chunk &
     }
 }
 
-template <bool EF, int MODE, class SRC>
+template <bool EF, int MODE, class SRC, int HOW>
 __global__ __launch_bounds__(kBlock) void accum_reduce_k(SRC src, uint32_t levels, uint64_t seed)
 {
     __shared__ double red[kWavesPerBlock];
     __shared__ float redf[kWavesPerBlock];
+    if constexpr (HOW == COMBINE_COLLECT) {
+        __shared__ double sums[kFinalThreads / 64];
+        if (blockIdx.x >= src.tiles()) {
+            each_collected(src, [&](const CompressJob &of) {
+                const double x = collect<kBlock, MODE == RED_MAX_ABS>(of.slots, of.ntiles, sums, src.status);
+                if (threadIdx.x == 0) put_plain_header(of.hdr, MODE == RED_L2 ? MC_ALGO_QSGD : MC_ALGO_TERNGRAD, of.g.n, MODE == RED_L2 ? (float)sqrt(x) : (float)x, 0.0f, levels);
+            });
+            return;
+        }
+    }
     const CompressJob job = src.job();
     const Chunk c = my_chunk(job.g.n, job.tile);
     double acc = 0.0;
@@ -513,32 +622,32 @@ __global__ __launch_bounds__(kBlock) void accum_reduce_k(SRC src, uint32_t level
             else mx = fmaxf(mx, fabsf(p[j]));
         }
     }
-    if (MODE == RED_L2) {
-        double t = block_sum(acc, red);
-        if (threadIdx.x == 0) job.partial[job.tile] = t;
-    } else {
-        float t = block_max(mx, redf);
-        if (threadIdx.x == 0) job.partial[job.tile] = (double)t;
-    }
+    const double t = MODE == RED_L2 ? block_sum(acc, red) : (double)block_max(mx, redf);
+    if (threadIdx.x == 0) { if (HOW == COMBINE_COLLECT) fill_slot(job.slots + job.tile, t); else job.partial[job.tile] = t; }
 }
 
+template <bool EF, int MODE, class SRC>
+static void accum_reduce_t(const LaunchCtx &lc, const SRC &src, uint32_t tiles, uint32_t groups, uint32_t levels, uint64_t seed, Combine how)
+{
+    if (how == COMBINE_COLLECT) MC_LAUNCH((accum_reduce_k<EF, MODE, SRC, COMBINE_COLLECT>), dim3(tiles + std::min(groups, kCollectors)), dim3(kBlock), lc, src, levels, seed);
+    else MC_LAUNCH((accum_reduce_k<EF, MODE, SRC, COMBINE_AFTER>), dim3(tiles), dim3(kBlock), lc, src, levels, seed);
+}
 template <class SRC>
-void launch_accum_reduce(const LaunchCtx &lc, const SRC &src, uint32_t tiles, bool ef, int mode, uint32_t levels, uint64_t seed)
+void launch_accum_reduce(const LaunchCtx &lc, const SRC &src, uint32_t tiles, uint32_t groups, bool ef, int mode, uint32_t levels, uint64_t seed, Combine how)
 {
     if (tiles == 0) return;
-    dim3 grid(tiles), block(kBlock);
     prof_begin(lc, K_ACCUM_REDUCE);
     if (mode == RED_L2) {
-        if (ef) MC_LAUNCH((accum_reduce_k<true, RED_L2, SRC>), grid, block, lc, src, levels, seed);
-        else MC_LAUNCH((accum_reduce_k<false, RED_L2, SRC>), grid, block, lc, src, levels, seed);
+        if (ef) accum_reduce_t<true, RED_L2>(lc, src, tiles, groups, levels, seed, how);
+        else accum_reduce_t<false, RED_L2>(lc, src, tiles, groups, levels, seed, how);
     } else {
-        if (ef) MC_LAUNCH((accum_reduce_k<true, RED_MAX_ABS, SRC>), grid, block, lc, src, levels, seed);
-        else MC_LAUNCH((accum_reduce_k<false, RED_MAX_ABS, SRC>), grid, block, lc, src, levels, seed);
+        if (ef) accum_reduce_t<true, RED_MAX_ABS>(lc, src, tiles, groups, levels, seed, how);
+        else accum_reduce_t<false, RED_MAX_ABS>(lc, src, tiles, groups, levels, seed, how);
     }
     prof_end(lc, K_ACCUM_REDUCE);
 }
-template void launch_accum_reduce<OneCompress>(const LaunchCtx &, const OneCompress &, uint32_t, bool, int, uint32_t, uint64_t);
-template void launch_accum_reduce<AllCompress>(const LaunchCtx &, const AllCompress &, uint32_t, bool, int, uint32_t, uint64_t);
+template void launch_accum_reduce<OneCompress>(const LaunchCtx &, const OneCompress &, uint32_t, uint32_t, bool, int, uint32_t, uint64_t, Combine);
+template void launch_accum_reduce<AllCompress>(const LaunchCtx &, const AllCompress &, uint32_t, uint32_t, bool, int, uint32_t, uint64_t, Combine);
 
 // p of pass B: from the state (where pass A left it) or, without error feedback, the gradient itself
 template <bool EF>

@@ -102,6 +102,7 @@ struct mc_ctx {
     uint32_t max_tiles = 0;
     size_t max_live = 0;
     double *d_partial = nullptr;
+    double *d_slots = nullptr;          // a double per tile, empty between calls (fill_slot)
     uint64_t *d_arrive = nullptr;       // per group: blocks of small groups that have put their partial, over all calls
     uint32_t wait_looks = kWaitLooks;   // of the small quantizer groups' blocks (mc_set_barrier_spin_limit)
     SparseScratch sparse{};
@@ -294,6 +295,11 @@ static int set_up(mc_ctx *ctx, bool all, bool own)
         for (int b = 0; b < BLK_KINDS; ++b) if ((rc = grab_copy(ctx, &ctx->d_block_group[b], block_group[b])) != MC_OK) return rc;
     }
     if (!grab(ctx, &ctx->d_partial, 3 * std::max(tiles, all ? all_tiles : 0) * sizeof(double))) return MC_ERR_ALLOC;
+    if (!is_sparse(cfg->algo)) {
+        const size_t bytes = std::max(tiles, all ? all_tiles : 0) * sizeof(double);
+        if (!grab(ctx, &ctx->d_slots, bytes)) return MC_ERR_ALLOC;
+        if (hipMemset(ctx->d_slots, 0xFF, bytes) != hipSuccess) return MC_ERR_DEVICE;
+    }
     if ((rc = grab_zeroed(ctx, &ctx->d_arrive, y * kArriveStride * sizeof(uint64_t))) != MC_OK) return rc;
     if ((rc = grab_zeroed(ctx, &ctx->d_status, sizeof(int))) != MC_OK) return rc;
     if (is_sparse(cfg->algo)) {
@@ -741,7 +747,9 @@ static void dense_compress(const mc_config &cfg, const LaunchCtx &lc, const SRC 
     // most_tiles: of any of the groups.  Small ones combine their partial sums in the kernel that makes them.
     // (While the profiler is on every step is a kernel of its own, so that its time can be read.)
     const Profiler *prof = static_cast<const Profiler *>(lc.prof);
-    const bool small = src.arrive && most_tiles <= kSmallTiles && !(prof && prof->on);
+    // (OneBit's three sums take a collector more registers than its streaming pass has.)
+    const bool apart = !src.arrive || (prof && prof->on), small = !apart && most_tiles <= kSmallTiles;
+    const Combine how = apart ? COMBINE_AFTER : small ? COMBINE_LAST : cfg.algo == MC_ALGO_ONEBIT ? COMBINE_AFTER : COMBINE_COLLECT;
     const bool ef = cfg.use_ef != 0;
     const uint32_t levels = qsgd_levels(cfg), algo = (uint32_t)cfg.algo;
     switch (cfg.algo) {
@@ -749,24 +757,24 @@ static void dense_compress(const mc_config &cfg, const LaunchCtx &lc, const SRC 
     case MC_ALGO_ONEBIT:
     {
         const bool means = cfg.algo == MC_ALGO_ONEBIT;
-        launch_sign_compress(lc, means ? SIGN_MEANS : SIGN_EF, src, tiles, ef, 0.0f, algo, small);
-        if (!small) launch_scalar_finalize(lc, src, groups, means ? RED_MEANS : RED_MEAN_ABS, algo, 0, ef);
+        launch_sign_compress(lc, means ? SIGN_MEANS : SIGN_EF, src, tiles, groups, ef, 0.0f, algo, how);
+        if (how == COMBINE_AFTER) launch_scalar_finalize(lc, src, groups, means ? RED_MEANS : RED_MEAN_ABS, algo, 0, ef);
     }
         break;
     case MC_ALGO_SIGNSGD:
     case MC_ALGO_SIGNUM:
-        launch_sign_compress(lc, cfg.algo == MC_ALGO_SIGNSGD ? SIGN_PLAIN : SIGN_MOMENTUM, src, tiles, ef, cfg.dgc_momentum, algo, false);
+        launch_sign_compress(lc, cfg.algo == MC_ALGO_SIGNSGD ? SIGN_PLAIN : SIGN_MOMENTUM, src, tiles, groups, ef, cfg.dgc_momentum, algo, COMBINE_AFTER);
         break;
     case MC_ALGO_QSGD:
         if (small) { launch_quantize_small(lc, RED_L2, src, tiles, ef, levels, cfg.seed, worker, iter_lo, looks); break; }
-        launch_accum_reduce(lc, src, tiles, ef, RED_L2, levels, cfg.seed);
-        launch_scalar_finalize(lc, src, groups, RED_L2, algo, levels, false);
+        launch_accum_reduce(lc, src, tiles, groups, ef, RED_L2, levels, cfg.seed, how);
+        if (how == COMBINE_AFTER) launch_scalar_finalize(lc, src, groups, RED_L2, algo, levels, false);
         launch_qsgd_encode(lc, src, tiles, ef, levels, cfg.seed, worker, iter_lo);
         break;
     case MC_ALGO_TERNGRAD:
         if (small) { launch_quantize_small(lc, RED_MAX_ABS, src, tiles, ef, 0, cfg.seed, worker, iter_lo, looks); break; }
-        launch_accum_reduce(lc, src, tiles, ef, RED_MAX_ABS, 0, cfg.seed);
-        launch_scalar_finalize(lc, src, groups, RED_MAX_ABS, algo, 0, false);
+        launch_accum_reduce(lc, src, tiles, groups, ef, RED_MAX_ABS, 0, cfg.seed, how);
+        if (how == COMBINE_AFTER) launch_scalar_finalize(lc, src, groups, RED_MAX_ABS, algo, 0, false);
         launch_tern_encode(lc, src, tiles, ef, cfg.seed, worker, iter_lo);
         break;
     default:
@@ -778,7 +786,7 @@ static void dense_compress(const mc_config &cfg, const LaunchCtx &lc, const SRC 
 static void empty_compress(const mc_config &cfg, const LaunchCtx &lc, PayloadHeader *hdr)
 {
     const bool votes = cfg.algo == MC_ALGO_SIGNSGD || cfg.algo == MC_ALGO_SIGNUM;
-    launch_scalar_finalize(lc, OneCompress{GroupView{}, nullptr, hdr, nullptr, nullptr}, 1, votes ? RED_ONE : -1, (uint32_t)cfg.algo, qsgd_levels(cfg), false);
+    launch_scalar_finalize(lc, OneCompress{GroupView{}, nullptr, hdr, nullptr, nullptr, nullptr, nullptr}, 1, votes ? RED_ONE : -1, (uint32_t)cfg.algo, qsgd_levels(cfg), false);
 }
 static SparseCall sparse_call(const mc_ctx *ctx, uint32_t worker, uint64_t iter)
 {
@@ -815,7 +823,7 @@ static int compress_impl(mc_ctx *ctx, int32_t group, uint32_t worker, uint64_t i
     if (!is_sparse(cfg.algo)) {
         // (the static entry point may not rely on what an earlier call left in its array: no count of arrivals)
         uint64_t *arrive = partial == ctx->d_partial ? ctx->d_arrive + (size_t)group * kArriveStride : nullptr;
-        dense_compress(cfg, lc, OneCompress{gv, sf, hdr, partial, arrive}, tiles_in(n), 1, tiles_in(n), worker, (uint32_t)iter, ctx->wait_looks);
+        dense_compress(cfg, lc, OneCompress{gv, sf, hdr, partial, arrive, ctx->d_slots, ctx->d_status}, tiles_in(n), 1, tiles_in(n), worker, (uint32_t)iter, ctx->wait_looks);
         return check_launch();
     }
     SparseScratch sp = ctx->sparse;
@@ -886,7 +894,7 @@ static int compress_all(mc_ctx *ctx, uint32_t worker, uint64_t iter, const float
         const SparseBlocks nb{ctx->all_blocks[BLK_TILE], ctx->all_blocks[BLK_SELECT], ctx->all_blocks[BLK_EMIT],
                               !ctx->all_select_small || ctx->prof.on ? 0u : one_each ? (uint32_t)y : ctx->all_blocks[BLK_EMIT]};
         launch_sparse_compress(lc, cfg.algo, AllSparse{tb, sp, ctx->last_group, one_each}, nb, ef, sparse_call(ctx, worker, iter));
-    } else dense_compress(cfg, lc, AllCompress{tb, ctx->d_partial, ctx->d_arrive}, ctx->all_blocks[BLK_TILE], (uint32_t)y, ctx->max_tiles, worker,
+    } else dense_compress(cfg, lc, AllCompress{tb, ctx->d_partial, ctx->d_arrive, ctx->d_slots, ctx->d_status, ctx->all_blocks[BLK_TILE]}, ctx->all_blocks[BLK_TILE], (uint32_t)y, ctx->max_tiles, worker,
                         (uint32_t)iter, ctx->wait_looks);
     for (size_t j = 0; j < y; ++j) if (ctx->groups[j].n == 0) empty_compress(cfg, lc, static_cast<PayloadHeader *>(payloads[j]));
     return check_launch();

@@ -104,6 +104,13 @@ constexpr uint32_t kSpreadTiles = 512;
 constexpr uint32_t kSpreadSumTiles = 128;
 __host__ __device__ inline uint32_t tiles_in(uint32_t n) { return (uint32_t)(((uint64_t)n + kTile - 1) / kTile); }
 
+// How the blocks' partial sums become the group's scalars: by a kernel after this one; by the block of a small group that arrives last; by a block
+// of the same launch that waits for them (a collector).
+enum Combine { COMBINE_AFTER = 0, COMBINE_LAST = 1, COMBINE_COLLECT = 2 };
+// Blocks of a launch that collect, each for every kCollectors-th group: few enough that the collectors of a good number of launches side
+// by side leave room for what they wait for.
+constexpr uint32_t kCollectors = 64;
+
 // A dense compressor's job.  The state's header lies in front of st, the payload's body behind hdr.
 struct CompressJob {
     GroupView g;
@@ -111,6 +118,7 @@ struct CompressJob {
     PayloadHeader *hdr;
     double *partial;              // one double per tile (OneBit: three arrays of one per tile)
     uint64_t *arrive;             // the group's count of blocks that have their partial ready (small groups); the word behind it: handed_over
+    double *slots;                // one double per tile, empty between calls: partials on their way to a collector
     uint32_t tile, ntiles;
     __device__ __forceinline__ StateHeader *state_header() const { return reinterpret_cast<StateHeader *>(st) - 1; }
     __device__ __forceinline__ uint8_t *body() const { return reinterpret_cast<uint8_t *>(hdr) + kHeaderBytes; }
@@ -122,13 +130,22 @@ struct OneCompress {
     PayloadHeader *hdr;
     double *partial;
     uint64_t *arrive;             // null: the call may not rely on what an earlier one left (mc_compress_static)
-    __device__ __forceinline__ CompressJob group_job(uint32_t) const { return {g, st, hdr, partial, arrive, 0u, tiles_in(g.n)}; }
-    __device__ __forceinline__ CompressJob job() const { return {g, st, hdr, partial, arrive, my_tile_index(), gridDim.x}; }
+    double *slots;
+    int *status;
+    __device__ __forceinline__ uint32_t tiles() const { return tiles_in(g.n); }
+    __device__ __forceinline__ uint32_t groups() const { return 1u; }
+    __device__ __forceinline__ CompressJob group_job(uint32_t) const { return {g, st, hdr, partial, arrive, slots, 0u, tiles()}; }
+    __device__ __forceinline__ CompressJob job() const { return {g, st, hdr, partial, arrive, slots, tiles() - 1u - blockIdx.x, tiles()}; }
 };
 struct AllCompress {              // list: tensors, then y states, then y payloads
     GroupTable tb;
     double *partial;
     uint64_t *arrive;             // kArriveStride words per group
+    double *slots;
+    int *status;
+    uint32_t all_tiles;
+    __device__ __forceinline__ uint32_t tiles() const { return all_tiles; }
+    __device__ __forceinline__ uint32_t groups() const { return tb.y; }
     __device__ __forceinline__ CompressJob group_job(uint32_t q) const
     {
         CompressJob j;
@@ -139,13 +156,14 @@ struct AllCompress {              // list: tensors, then y states, then y payloa
         j.hdr = reinterpret_cast<PayloadHeader *>(ld_uniform(tb.list + tb.live + tb.y + q));
         j.partial = partial + 3u * (size_t)ld_uniform(&c->first[BLK_TILE]);
         j.arrive = arrive + (size_t)q * kArriveStride;
+        j.slots = slots + ld_uniform(&c->first[BLK_TILE]);
         j.tile = 0u;
         j.ntiles = tiles_in(j.g.n);
         return j;
     }
     __device__ __forceinline__ CompressJob job() const
     {
-        const uint32_t block = my_tile_index(), q = ld_uniform(tb.block_group[BLK_TILE] + block);
+        const uint32_t block = all_tiles - 1u - blockIdx.x, q = ld_uniform(tb.block_group[BLK_TILE] + block);
         CompressJob j = group_job(q);
         j.tile = block - ld_uniform(&tb.groups[q].first[BLK_TILE]);
         return j;
@@ -285,13 +303,13 @@ inline void launch(void (*kernel)(P...), dim3 grid, dim3 block, hipStream_t stre
 void launch_upload_ptrs(const LaunchCtx &lc, const uintptr_t *host, uintptr_t *dev, uint32_t count);
 void launch_expand_ptrs(const LaunchCtx &lc, const GroupView &g, uintptr_t *chunk_addr);
 void launch_expand_all(const LaunchCtx &lc, const GroupTable &tb, uint32_t tiles, uintptr_t *chunk_addr);
-// small: every group has at most kSmallTiles tiles and src.arrive counts
-template <class SRC> void launch_sign_compress(const LaunchCtx &lc, int mode, const SRC &src, uint32_t tiles, bool ef, float beta, uint32_t algo, bool small);
+// how: COMBINE_LAST where every group has at most kSmallTiles tiles and src.arrive counts; COMBINE_COLLECT with src.slots
+template <class SRC> void launch_sign_compress(const LaunchCtx &lc, int mode, const SRC &src, uint32_t tiles, uint32_t groups, bool ef, float beta, uint32_t algo, Combine how);
 template <class SRC> void launch_quantize_small(const LaunchCtx &lc, int mode, const SRC &src, uint32_t tiles, bool ef, uint32_t levels, uint64_t seed,
                                                 uint32_t worker, uint32_t iter_lo, uint32_t looks);
 template <class SRC> void launch_scalar_finalize(const LaunchCtx &lc, const SRC &src, uint32_t groups, int mode, uint32_t algo, uint32_t levels,
                                                  bool keep);
-template <class SRC> void launch_accum_reduce(const LaunchCtx &lc, const SRC &src, uint32_t tiles, bool ef, int mode, uint32_t levels, uint64_t seed);
+template <class SRC> void launch_accum_reduce(const LaunchCtx &lc, const SRC &src, uint32_t tiles, uint32_t groups, bool ef, int mode, uint32_t levels, uint64_t seed, Combine how);
 template <class SRC> void launch_qsgd_encode(const LaunchCtx &lc, const SRC &src, uint32_t tiles, bool ef, uint32_t levels, uint64_t seed,
                                              uint32_t worker, uint32_t iter_lo);
 template <class SRC> void launch_tern_encode(const LaunchCtx &lc, const SRC &src, uint32_t tiles, bool ef, uint64_t seed, uint32_t worker, uint32_t iter_lo);
