@@ -1374,7 +1374,10 @@ __device__ __forceinline__ void add_terns(float (&acc)[32], uint32_t nz, uint32_
 // Whether that gives what an addition of 0, +s or -s gives: s / 2 has to be exact, and 0 times it has to be 0.
 __device__ __forceinline__ bool halves_exactly(float s) { return 0.5f * s + 0.5f * s == s && fabsf(s) < __builtin_inff(); }
 
-template <bool TERN, class SRC>
+// MORE: more than kPlaneBatch workers, in a kernel of its own (80 registers, 6 wavefronts per SIMD, only when asked for; with both in one kernel 81,
+// and the sums of up to eight workers 1 to 3 % slower).
+template <bool TERN, bool MORE, class SRC>
+__attribute__((amdgpu_waves_per_eu(TERN ? 4 : 6)))
 __global__ __launch_bounds__(kBlock) void plane_decompress_k(SRC src, int W, float alpha, int *status, int algo, int kind)
 {
     __shared__ float table[TERN ? 1 : 256];
@@ -1426,8 +1429,8 @@ __global__ __launch_bounds__(kBlock) void plane_decompress_k(SRC src, int W, flo
             plane_levels(x.scale[b], x.scale_lo[b], kind, hi, lo);
             sum = b < W ? sum + (((t >> b) & 1u) ? hi : lo) : sum;
         }
-        if (W <= kPlaneBatch && kind == PLANE_VOTE) sum = vote_of(sum);
-        table[t] = W <= kPlaneBatch ? alpha * sum : sum;
+        if (!MORE && kind == PLANE_VOTE) sum = vote_of(sum);
+        table[t] = MORE ? sum : alpha * sum;
         __syncthreads();
         if (wbase >= out.n) return;
 #pragma unroll
@@ -1444,36 +1447,46 @@ __global__ __launch_bounds__(kBlock) void plane_decompress_k(SRC src, int W, flo
     }
     // the further workers (TernGrad: all), one by one
 #pragma unroll 1
-    for (int w0 = TERN ? 0 : kPlaneBatch; w0 < W; w0 += kPlaneBatch) {
+    for (int w0 = TERN ? 0 : kPlaneBatch; w0 < (MORE ? W : TERN ? 1 : 0); w0 += kPlaneBatch) {
         if (w0) fetch(w0, x);
+        // (One decision for the batch: with one per worker every worker's sums were copied to other registers, half a
+        // move per element, next to two instructions that add it.)
         if (TERN) {
             bool exact = true;
 #pragma unroll
             for (int b = 0; b < kPlaneBatch; ++b) exact = exact && halves_exactly(x.scale[b]);
+            if (exact) {
 #pragma unroll
-            for (int b = 0; b < kPlaneBatch; ++b) {
-                if (w0 + b >= W) break;
-                if (exact) { add_terns(acc, x.word[b], x.second[b], 0.5f * x.scale[b]); continue; }
+                for (int b = 0; b < kPlaneBatch; ++b) if (w0 + b < W) add_terns(acc, x.word[b], x.second[b], 0.5f * x.scale[b]);
+            } else {
 #pragma unroll
-                for (int e = 0; e < 32; ++e) acc[e] = acc[e] + tern_term(x.word[b], x.second[b], e, x.scale[b]);
+                for (int b = 0; b < kPlaneBatch; ++b) {
+                    if (w0 + b >= W) break;
+#pragma unroll
+                    for (int e = 0; e < 32; ++e) acc[e] = acc[e] + tern_term(x.word[b], x.second[b], e, x.scale[b]);
+                }
             }
         } else {
             bool signs = kind != PLANE_MEANS;
             if (kind == PLANE_SCALE)
 #pragma unroll
                 for (int b = 0; b < kPlaneBatch; ++b) signs = signs && x.scale[b] == x.scale[b];      // (a NaN would keep its sign)
+            if (signs) {
 #pragma unroll
-            for (int b = 0; b < kPlaneBatch; ++b) {
-                if (w0 + b >= W) break;
-                float hi, lo;
-                plane_levels(x.scale[b], x.scale_lo[b], kind, hi, lo);
-                if (signs) { add_signs(acc, x.word[b], hi); continue; }
+                for (int b = 0; b < kPlaneBatch; ++b) if (w0 + b < W) add_signs(acc, x.word[b], kind == PLANE_VOTE ? 1.0f : x.scale[b]);
+            } else {
 #pragma unroll
-                for (int e = 0; e < 32; ++e) acc[e] = acc[e] + plane_term(x.word[b], e, hi, lo);
+                for (int b = 0; b < kPlaneBatch; ++b) {
+                    if (w0 + b >= W) break;
+                    float hi, lo;
+                    plane_levels(x.scale[b], x.scale_lo[b], kind, hi, lo);
+#pragma unroll
+                    for (int e = 0; e < 32; ++e) acc[e] = acc[e] + plane_term(x.word[b], e, hi, lo);
+                }
             }
         }
     }
-    if (W > kPlaneBatch || TERN) {
+    if (MORE || TERN) {
 #pragma unroll
         for (int e = 0; e < 32; ++e) acc[e] = alpha * (!TERN && kind == PLANE_VOTE ? vote_of(acc[e]) : acc[e]);
     }
@@ -1517,11 +1530,15 @@ void launch_dense_decompress(const LaunchCtx &lc, int algo, const SRC &src, uint
     case MC_ALGO_ONEBIT:
     case MC_ALGO_SIGNSGD:
     case MC_ALGO_SIGNUM:
-        MC_LAUNCH((plane_decompress_k<false, SRC>), grid, block, lc, src, W, alpha, status, algo,
-                  algo == MC_ALGO_EFSIGN ? PLANE_SCALE : algo == MC_ALGO_ONEBIT ? PLANE_MEANS : PLANE_VOTE);
+    {
+        const int kind = algo == MC_ALGO_EFSIGN ? PLANE_SCALE : algo == MC_ALGO_ONEBIT ? PLANE_MEANS : PLANE_VOTE;
+        if (W > kPlaneBatch) MC_LAUNCH((plane_decompress_k<false, true, SRC>), grid, block, lc, src, W, alpha, status, algo, kind);
+        else MC_LAUNCH((plane_decompress_k<false, false, SRC>), grid, block, lc, src, W, alpha, status, algo, kind);
         break;
+    }
     case MC_ALGO_TERNGRAD:
-        MC_LAUNCH((plane_decompress_k<true, SRC>), grid, block, lc, src, W, alpha, status, algo, PLANE_SCALE);
+        if (W > kPlaneBatch) MC_LAUNCH((plane_decompress_k<true, true, SRC>), grid, block, lc, src, W, alpha, status, algo, PLANE_SCALE);
+        else MC_LAUNCH((plane_decompress_k<true, false, SRC>), grid, block, lc, src, W, alpha, status, algo, PLANE_SCALE);
         break;
     case MC_ALGO_QSGD: MC_LAUNCH((dense_decompress_k<MC_ALGO_QSGD, SRC>), grid, block, lc, src, W, alpha, levels, status); break;
     default: MC_LAUNCH((dense_decompress_k<MC_ALGO_FP16, SRC>), grid, block, lc, src, W, alpha, levels, status); break;
