@@ -363,47 +363,51 @@ __global__ __launch_bounds__(kTile / S) void sign_compress_k(SRC src, float beta
     }
 }
 
+// a collector for each group, or for every kCollectors-th
+template <class SRC>
+static uint32_t collectors(const SRC &src) { return std::min(src.groups(), kCollectors); }
+
 template <int MODE, bool EF, int HOW, class SRC>
-static void sign_compress_t(const LaunchCtx &lc, const SRC &src, uint32_t tiles, uint32_t groups, float beta, uint32_t algo)
+static void sign_compress_t(const LaunchCtx &lc, const SRC &src, uint32_t tiles, float beta, uint32_t algo)
 {
     constexpr uint32_t most = MODE == SIGN_EF || MODE == SIGN_MEANS ? kSpreadSumTiles : kSpreadTiles;
-    const dim3 grid(tiles + (HOW == COMBINE_COLLECT ? std::min(groups, kCollectors) : 0u));
+    const dim3 grid(tiles + (HOW == COMBINE_COLLECT ? collectors(src) : 0u));
     if (tiles <= most) MC_LAUNCH((sign_compress_k<MODE, EF, SRC, HOW, kSpreadSteps>), grid, dim3(kSpread), lc, src, beta, algo);
     else MC_LAUNCH((sign_compress_k<MODE, EF, SRC, HOW>), grid, dim3(kBlock), lc, src, beta, algo);
 }
 template <int MODE, bool EF, class SRC>
-static void sign_compress_how(const LaunchCtx &lc, const SRC &src, uint32_t tiles, uint32_t groups, uint32_t algo, Combine how)
+static void sign_compress_sums(const LaunchCtx &lc, const SRC &src, uint32_t tiles, uint32_t algo, bool small)
 {
-    if (how == COMBINE_LAST) { sign_compress_t<MODE, EF, COMBINE_LAST>(lc, src, tiles, groups, 0.0f, algo); return; }
-    if constexpr (MODE == SIGN_EF) if (how == COMBINE_COLLECT) { sign_compress_t<MODE, EF, COMBINE_COLLECT>(lc, src, tiles, groups, 0.0f, algo); return; }
-    sign_compress_t<MODE, EF, COMBINE_AFTER>(lc, src, tiles, groups, 0.0f, algo);
+    if (small) { sign_compress_t<MODE, EF, COMBINE_LAST>(lc, src, tiles, 0.0f, algo); return; }
+    if constexpr (MODE == SIGN_EF) if (src.slots) { sign_compress_t<MODE, EF, COMBINE_COLLECT>(lc, src, tiles, 0.0f, algo); return; }
+    sign_compress_t<MODE, EF, COMBINE_AFTER>(lc, src, tiles, 0.0f, algo);
 }
 
 template <class SRC>
-void launch_sign_compress(const LaunchCtx &lc, int mode, const SRC &src, uint32_t tiles, uint32_t groups, bool ef, float beta, uint32_t algo, Combine how)
+void launch_sign_compress(const LaunchCtx &lc, int mode, const SRC &src, uint32_t tiles, bool ef, float beta, uint32_t algo, bool small)
 {
     if (tiles == 0) return;
     prof_begin(lc, K_EFSIGN_COMPRESS);
     switch (mode) {
     case SIGN_EF:
-        if (ef) sign_compress_how<SIGN_EF, true>(lc, src, tiles, groups, algo, how);
-        else sign_compress_how<SIGN_EF, false>(lc, src, tiles, groups, algo, how);
+        if (ef) sign_compress_sums<SIGN_EF, true>(lc, src, tiles, algo, small);
+        else sign_compress_sums<SIGN_EF, false>(lc, src, tiles, algo, small);
         break;
     case SIGN_MEANS:
-        if (ef) sign_compress_how<SIGN_MEANS, true>(lc, src, tiles, groups, algo, how);
-        else sign_compress_how<SIGN_MEANS, false>(lc, src, tiles, groups, algo, how);
+        if (ef) sign_compress_sums<SIGN_MEANS, true>(lc, src, tiles, algo, small);
+        else sign_compress_sums<SIGN_MEANS, false>(lc, src, tiles, algo, small);
         break;
     case SIGN_PLAIN:
-        sign_compress_t<SIGN_PLAIN, false, COMBINE_AFTER>(lc, src, tiles, groups, beta, algo);
+        sign_compress_t<SIGN_PLAIN, false, COMBINE_AFTER>(lc, src, tiles, beta, algo);
         break;
     default:
-        sign_compress_t<SIGN_MOMENTUM, true, COMBINE_AFTER>(lc, src, tiles, groups, beta, algo);
+        sign_compress_t<SIGN_MOMENTUM, true, COMBINE_AFTER>(lc, src, tiles, beta, algo);
         break;
     }
     prof_end(lc, K_EFSIGN_COMPRESS);
 }
-template void launch_sign_compress<OneCompress>(const LaunchCtx &, int, const OneCompress &, uint32_t, uint32_t, bool, float, uint32_t, Combine);
-template void launch_sign_compress<AllCompress>(const LaunchCtx &, int, const AllCompress &, uint32_t, uint32_t, bool, float, uint32_t, Combine);
+template void launch_sign_compress<OneCompress>(const LaunchCtx &, int, const OneCompress &, uint32_t, bool, float, uint32_t, bool);
+template void launch_sign_compress<AllCompress>(const LaunchCtx &, int, const AllCompress &, uint32_t, bool, float, uint32_t, bool);
 
 // ---------------------------------------------------------------------------
 // One block per group: combine the per-block partials in a fixed order (bit-reproducible
@@ -627,27 +631,27 @@ __global__ __launch_bounds__(kBlock) void accum_reduce_k(SRC src, uint32_t level
 }
 
 template <bool EF, int MODE, class SRC>
-static void accum_reduce_t(const LaunchCtx &lc, const SRC &src, uint32_t tiles, uint32_t groups, uint32_t levels, uint64_t seed, Combine how)
+static void accum_reduce_t(const LaunchCtx &lc, const SRC &src, uint32_t tiles, uint32_t levels, uint64_t seed)
 {
-    if (how == COMBINE_COLLECT) MC_LAUNCH((accum_reduce_k<EF, MODE, SRC, COMBINE_COLLECT>), dim3(tiles + std::min(groups, kCollectors)), dim3(kBlock), lc, src, levels, seed);
+    if (src.slots) MC_LAUNCH((accum_reduce_k<EF, MODE, SRC, COMBINE_COLLECT>), dim3(tiles + collectors(src)), dim3(kBlock), lc, src, levels, seed);
     else MC_LAUNCH((accum_reduce_k<EF, MODE, SRC, COMBINE_AFTER>), dim3(tiles), dim3(kBlock), lc, src, levels, seed);
 }
 template <class SRC>
-void launch_accum_reduce(const LaunchCtx &lc, const SRC &src, uint32_t tiles, uint32_t groups, bool ef, int mode, uint32_t levels, uint64_t seed, Combine how)
+void launch_accum_reduce(const LaunchCtx &lc, const SRC &src, uint32_t tiles, bool ef, int mode, uint32_t levels, uint64_t seed)
 {
     if (tiles == 0) return;
     prof_begin(lc, K_ACCUM_REDUCE);
     if (mode == RED_L2) {
-        if (ef) accum_reduce_t<true, RED_L2>(lc, src, tiles, groups, levels, seed, how);
-        else accum_reduce_t<false, RED_L2>(lc, src, tiles, groups, levels, seed, how);
+        if (ef) accum_reduce_t<true, RED_L2>(lc, src, tiles, levels, seed);
+        else accum_reduce_t<false, RED_L2>(lc, src, tiles, levels, seed);
     } else {
-        if (ef) accum_reduce_t<true, RED_MAX_ABS>(lc, src, tiles, groups, levels, seed, how);
-        else accum_reduce_t<false, RED_MAX_ABS>(lc, src, tiles, groups, levels, seed, how);
+        if (ef) accum_reduce_t<true, RED_MAX_ABS>(lc, src, tiles, levels, seed);
+        else accum_reduce_t<false, RED_MAX_ABS>(lc, src, tiles, levels, seed);
     }
     prof_end(lc, K_ACCUM_REDUCE);
 }
-template void launch_accum_reduce<OneCompress>(const LaunchCtx &, const OneCompress &, uint32_t, uint32_t, bool, int, uint32_t, uint64_t, Combine);
-template void launch_accum_reduce<AllCompress>(const LaunchCtx &, const AllCompress &, uint32_t, uint32_t, bool, int, uint32_t, uint64_t, Combine);
+template void launch_accum_reduce<OneCompress>(const LaunchCtx &, const OneCompress &, uint32_t, bool, int, uint32_t, uint64_t);
+template void launch_accum_reduce<AllCompress>(const LaunchCtx &, const AllCompress &, uint32_t, bool, int, uint32_t, uint64_t);
 
 // p of pass B: from the state (where pass A left it) or, without error feedback, the gradient itself
 template <bool EF>
@@ -1520,9 +1524,8 @@ __global__ __launch_bounds__(kBlock) void plane_decompress_k(SRC src, int W, flo
 }
 
 template <class SRC>
-void launch_dense_decompress(const LaunchCtx &lc, int algo, const SRC &src, uint32_t blocks, int W, float alpha, uint32_t levels, int *status)
+static void dense_decompress_t(const LaunchCtx &lc, int algo, const SRC &src, uint32_t blocks, int W, float alpha, uint32_t levels, int *status)
 {
-    if (blocks == 0) return;
     dim3 grid(blocks + SRC::kCheckers), block(kBlock);           // (the first ones check the headers)
     prof_begin(lc, K_DENSE_DECOMPRESS);
     switch (algo) {
@@ -1532,18 +1535,25 @@ void launch_dense_decompress(const LaunchCtx &lc, int algo, const SRC &src, uint
     case MC_ALGO_SIGNUM:
     {
         const int kind = algo == MC_ALGO_EFSIGN ? PLANE_SCALE : algo == MC_ALGO_ONEBIT ? PLANE_MEANS : PLANE_VOTE;
-        if (W > kPlaneBatch) MC_LAUNCH((plane_decompress_k<false, true, SRC>), grid, block, lc, src, W, alpha, status, algo, kind);
-        else MC_LAUNCH((plane_decompress_k<false, false, SRC>), grid, block, lc, src, W, alpha, status, algo, kind);
+        if constexpr (SRC::kRoom > kPlaneBatch) if (W > kPlaneBatch) { MC_LAUNCH((plane_decompress_k<false, true, SRC>), grid, block, lc, src, W, alpha, status, algo, kind); break; }
+        MC_LAUNCH((plane_decompress_k<false, false, SRC>), grid, block, lc, src, W, alpha, status, algo, kind);
         break;
     }
     case MC_ALGO_TERNGRAD:
-        if (W > kPlaneBatch) MC_LAUNCH((plane_decompress_k<true, true, SRC>), grid, block, lc, src, W, alpha, status, algo, PLANE_SCALE);
-        else MC_LAUNCH((plane_decompress_k<true, false, SRC>), grid, block, lc, src, W, alpha, status, algo, PLANE_SCALE);
+        if constexpr (SRC::kRoom > kPlaneBatch) if (W > kPlaneBatch) { MC_LAUNCH((plane_decompress_k<true, true, SRC>), grid, block, lc, src, W, alpha, status, algo, PLANE_SCALE); break; }
+        MC_LAUNCH((plane_decompress_k<true, false, SRC>), grid, block, lc, src, W, alpha, status, algo, PLANE_SCALE);
         break;
     case MC_ALGO_QSGD: MC_LAUNCH((dense_decompress_k<MC_ALGO_QSGD, SRC>), grid, block, lc, src, W, alpha, levels, status); break;
     default: MC_LAUNCH((dense_decompress_k<MC_ALGO_FP16, SRC>), grid, block, lc, src, W, alpha, levels, status); break;
     }
     prof_end(lc, K_DENSE_DECOMPRESS);
+}
+template <class SRC>
+void launch_dense_decompress(const LaunchCtx &lc, int algo, const SRC &src, uint32_t blocks, int W, float alpha, uint32_t levels, int *status)
+{
+    if (blocks == 0) return;
+    if constexpr (std::is_same_v<SRC, OneDecompress>) if (W <= kFewRoom) { dense_decompress_t(lc, algo, with_few(src), blocks, W, alpha, levels, status); return; }
+    dense_decompress_t(lc, algo, src, blocks, W, alpha, levels, status);
 }
 template void launch_dense_decompress<OneDecompress>(const LaunchCtx &, int, const OneDecompress &, uint32_t, int, float, uint32_t, int *);
 template void launch_dense_decompress<AllDecompress>(const LaunchCtx &, int, const AllDecompress &, uint32_t, int, float, uint32_t, int *);

@@ -2217,14 +2217,20 @@ __global__ __launch_bounds__(kBlock) void sparse_decompress_k(int algo, SRC src,
 }
 
 template <class SRC>
-void launch_sparse_decompress(const LaunchCtx &lc, int algo, const SRC &src, uint32_t tiles, int W, float alpha, int *status, bool capped)
+static void sparse_decompress_t(const LaunchCtx &lc, int algo, const SRC &src, uint32_t tiles, int W, float alpha, int *status, bool capped)
 {
-    if (tiles == 0) return;
     prof_begin(lc, K_SPARSE_DECOMPRESS);
     const dim3 grid(tiles + SRC::kCheckers), block(kBlock);         // (the first blocks check the headers)
     if (W <= kFewWorkers) MC_LAUNCH((sparse_decompress_k<SRC, true>), grid, block, lc, algo, src, W, alpha, status, capped ? 1 : 0);
     else MC_LAUNCH((sparse_decompress_k<SRC, false>), grid, block, lc, algo, src, W, alpha, status, capped ? 1 : 0);
     prof_end(lc, K_SPARSE_DECOMPRESS);
+}
+template <class SRC>
+void launch_sparse_decompress(const LaunchCtx &lc, int algo, const SRC &src, uint32_t tiles, int W, float alpha, int *status, bool capped)
+{
+    if (tiles == 0) return;
+    if constexpr (std::is_same_v<SRC, OneDecompress>) if (W <= kFewRoom) { sparse_decompress_t(lc, algo, with_few(src), tiles, W, alpha, status, capped); return; }
+    sparse_decompress_t(lc, algo, src, tiles, W, alpha, status, capped);
 }
 template void launch_sparse_decompress<OneDecompress>(const LaunchCtx &, int, const OneDecompress &, uint32_t, int, float, int *, bool);
 template void launch_sparse_decompress<AllDecompress>(const LaunchCtx &, int, const AllDecompress &, uint32_t, int, float, int *, bool);

@@ -741,15 +741,16 @@ static void decompress_launch(mc_ctx *ctx, const LaunchCtx &lc, const SRC &src, 
 
 // The kernels of a dense compressor over one group or all: `tiles` blocks of 4096 elements, `groups` groups.
 template <class SRC>
-static void dense_compress(const mc_config &cfg, const LaunchCtx &lc, const SRC &src, uint32_t tiles, uint32_t groups, uint32_t most_tiles, uint32_t worker,
+static void dense_compress(const mc_config &cfg, const LaunchCtx &lc, SRC src, uint32_t tiles, uint32_t groups, uint32_t most_tiles, uint32_t worker,
                            uint32_t iter_lo, uint32_t looks)
 {
     // most_tiles: of any of the groups.  Small ones combine their partial sums in the kernel that makes them.
     // (While the profiler is on every step is a kernel of its own, so that its time can be read.)
     const Profiler *prof = static_cast<const Profiler *>(lc.prof);
-    // (OneBit's three sums take a collector more registers than its streaming pass has.)
     const bool apart = !src.arrive || (prof && prof->on), small = !apart && most_tiles <= kSmallTiles;
-    const Combine how = apart ? COMBINE_AFTER : small ? COMBINE_LAST : cfg.algo == MC_ALGO_ONEBIT ? COMBINE_AFTER : COMBINE_COLLECT;
+    // (OneBit's three sums take a collector more registers than its streaming pass has.)
+    const bool after = apart || (!small && cfg.algo == MC_ALGO_ONEBIT);
+    if (after) src.slots = nullptr;
     const bool ef = cfg.use_ef != 0;
     const uint32_t levels = qsgd_levels(cfg), algo = (uint32_t)cfg.algo;
     switch (cfg.algo) {
@@ -757,24 +758,24 @@ static void dense_compress(const mc_config &cfg, const LaunchCtx &lc, const SRC 
     case MC_ALGO_ONEBIT:
     {
         const bool means = cfg.algo == MC_ALGO_ONEBIT;
-        launch_sign_compress(lc, means ? SIGN_MEANS : SIGN_EF, src, tiles, groups, ef, 0.0f, algo, how);
-        if (how == COMBINE_AFTER) launch_scalar_finalize(lc, src, groups, means ? RED_MEANS : RED_MEAN_ABS, algo, 0, ef);
+        launch_sign_compress(lc, means ? SIGN_MEANS : SIGN_EF, src, tiles, ef, 0.0f, algo, small);
+        if (after) launch_scalar_finalize(lc, src, groups, means ? RED_MEANS : RED_MEAN_ABS, algo, 0, ef);
     }
         break;
     case MC_ALGO_SIGNSGD:
     case MC_ALGO_SIGNUM:
-        launch_sign_compress(lc, cfg.algo == MC_ALGO_SIGNSGD ? SIGN_PLAIN : SIGN_MOMENTUM, src, tiles, groups, ef, cfg.dgc_momentum, algo, COMBINE_AFTER);
+        launch_sign_compress(lc, cfg.algo == MC_ALGO_SIGNSGD ? SIGN_PLAIN : SIGN_MOMENTUM, src, tiles, ef, cfg.dgc_momentum, algo, false);
         break;
     case MC_ALGO_QSGD:
         if (small) { launch_quantize_small(lc, RED_L2, src, tiles, ef, levels, cfg.seed, worker, iter_lo, looks); break; }
-        launch_accum_reduce(lc, src, tiles, groups, ef, RED_L2, levels, cfg.seed, how);
-        if (how == COMBINE_AFTER) launch_scalar_finalize(lc, src, groups, RED_L2, algo, levels, false);
+        launch_accum_reduce(lc, src, tiles, ef, RED_L2, levels, cfg.seed);
+        if (after) launch_scalar_finalize(lc, src, groups, RED_L2, algo, levels, false);
         launch_qsgd_encode(lc, src, tiles, ef, levels, cfg.seed, worker, iter_lo);
         break;
     case MC_ALGO_TERNGRAD:
         if (small) { launch_quantize_small(lc, RED_MAX_ABS, src, tiles, ef, 0, cfg.seed, worker, iter_lo, looks); break; }
-        launch_accum_reduce(lc, src, tiles, groups, ef, RED_MAX_ABS, 0, cfg.seed, how);
-        if (how == COMBINE_AFTER) launch_scalar_finalize(lc, src, groups, RED_MAX_ABS, algo, 0, false);
+        launch_accum_reduce(lc, src, tiles, ef, RED_MAX_ABS, 0, cfg.seed);
+        if (after) launch_scalar_finalize(lc, src, groups, RED_MAX_ABS, algo, 0, false);
         launch_tern_encode(lc, src, tiles, ef, cfg.seed, worker, iter_lo);
         break;
     default:
@@ -936,17 +937,17 @@ int mc_decompress_sum(mc_ctx *ctx, int32_t group, const void *const *payloads, i
     const Group &G = *gp;
     if (G.t1 > G.t0 && !out_ptrs) return MC_ERR_INVALID_ARG;
     for (int32_t rel : G.live) if (!out_ptrs[rel] || (reinterpret_cast<uintptr_t>(out_ptrs[rel]) & 3u)) return MC_ERR_INVALID_ARG;
-    PayloadPtrs pl{};
-    for (int32_t w = 0; w < W; ++w) {
-        if (!payloads[w] || (reinterpret_cast<uintptr_t>(payloads[w]) & 15u)) return MC_ERR_INVALID_ARG;
-        pl.p[w] = static_cast<const uint8_t *>(payloads[w]);
-    }
-    for (int32_t w = W; w < kMaxWorkers; ++w) pl.p[w] = pl.p[0];      // (kernels read the addresses of several workers at once)
+    for (int32_t w = 0; w < W; ++w) if (!payloads[w] || (reinterpret_cast<uintptr_t>(payloads[w]) & 15u)) return MC_ERR_INVALID_ARG;
     if (G.n == 0) return MC_OK;
     LaunchCtx lc{static_cast<hipStream_t>(stream), &ctx->prof, nullptr, nullptr};
     (void)hipGetLastError();
     GroupView gv = group_view(ctx, lc, group, G, reinterpret_cast<const void *const *>(out_ptrs));
-    decompress_launch(ctx, lc, OneDecompress{gv, pl, G.k}, tiles_in(G.n), plane_blocks(G.n), W, alpha);
+    OneDecompress src;
+    src.out = gv;
+    src.k = G.k;
+    for (int32_t w = 0; w < (W <= kFewRoom ? kFewRoom : kMaxWorkers); ++w)
+        src.pl[w] = static_cast<const uint8_t *>(payloads[w < W ? w : 0]);      // (kernels read the addresses of several workers at once)
+    decompress_launch(ctx, lc, src, tiles_in(G.n), plane_blocks(G.n), W, alpha);
     return check_launch();
 }
 

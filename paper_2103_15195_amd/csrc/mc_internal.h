@@ -42,7 +42,6 @@ __host__ __device__ inline size_t dgc_u_offset(uint32_t n) { return ((size_t)n +
 enum DeviceFlag { FLAG_PAYLOAD = 1, FLAG_GAVE_UP = 2 };
 __device__ __forceinline__ void raise_flag(int *status, DeviceFlag f) { atomicMax(status, (int)f); }
 
-struct PayloadPtrs { const uint8_t *p[kMaxWorkers]; };
 struct PtrChunk { uintptr_t p[256]; };
 
 // ---- which group a block works on -----------------------------------------------------------------------------
@@ -130,10 +129,10 @@ struct OneCompress {
     PayloadHeader *hdr;
     double *partial;
     uint64_t *arrive;             // null: the call may not rely on what an earlier one left (mc_compress_static)
-    double *slots;
+    double *slots;                // null: a kernel after this one combines the partials
     int *status;
     __device__ __forceinline__ uint32_t tiles() const { return tiles_in(g.n); }
-    __device__ __forceinline__ uint32_t groups() const { return 1u; }
+    __host__ __device__ __forceinline__ uint32_t groups() const { return 1u; }
     __device__ __forceinline__ CompressJob group_job(uint32_t) const { return {g, st, hdr, partial, arrive, slots, 0u, tiles()}; }
     __device__ __forceinline__ CompressJob job() const { return {g, st, hdr, partial, arrive, slots, tiles() - 1u - blockIdx.x, tiles()}; }
 };
@@ -145,7 +144,7 @@ struct AllCompress {              // list: tensors, then y states, then y payloa
     int *status;
     uint32_t all_tiles;
     __device__ __forceinline__ uint32_t tiles() const { return all_tiles; }
-    __device__ __forceinline__ uint32_t groups() const { return tb.y; }
+    __host__ __device__ __forceinline__ uint32_t groups() const { return tb.y; }
     __device__ __forceinline__ CompressJob group_job(uint32_t q) const
     {
         CompressJob j;
@@ -189,34 +188,48 @@ struct Expected {
     }
 };
 
-// A decompress-and-sum's job: the output, the payloads of the group, and this block's number among the group's.
-struct OneDecompress {
+// A decompress-and-sum's job: the output, the payloads of the group, and this block's number among the group's.  kRoom: the most workers that the
+// source may have.
+// ROOM: payloads that there is room for.  The arguments of a launch are written across the bus: those for 64 workers took a call 0.6 us
+// longer than those for eight (3.3 instead of 2.7 us for the launch of a kernel that does nothing).
+constexpr int kFewRoom = 8;
+template <int ROOM>
+struct DecompressOf {
     GroupView out;
-    PayloadPtrs pl;
+    const uint8_t *pl[ROOM];
     uint64_t k;
     struct Job {
         GroupView out;
-        const OneDecompress *src;
+        const DecompressOf *src;
         uint64_t k;
         uint32_t block;
         // the payloads of workers w0 .. w0 + N - 1 (w0: a multiple of N); behind the last worker's some other one
         template <int N> __device__ __forceinline__ void payloads(int w0, int, const uint8_t *(&p)[N]) const
         {
 #pragma unroll
-            for (int b = 0; b < N; ++b) p[b] = src->pl.p[w0 + b];
+            for (int b = 0; b < N; ++b) p[b] = src->pl[w0 + b];
             hold(p);
         }
     };
     template <int KIND> __device__ __forceinline__ Job job() const { return {out, this, k, my_tile_index()}; }
+    static constexpr int kRoom = ROOM;
     static constexpr uint32_t kCheckers = 1;      // blocks that look at the headers
     __device__ __forceinline__ void check(const Expected &e, int W, int *status) const
     {
-        if ((int)threadIdx.x < W) e.check(pl.p[threadIdx.x], out.n, k, status);
+        if ((int)threadIdx.x < W) e.check(pl[threadIdx.x], out.n, k, status);
     }
 };
+using OneDecompress = DecompressOf<kMaxWorkers>;
+inline DecompressOf<kFewRoom> with_few(const OneDecompress &src)
+{
+    DecompressOf<kFewRoom> few{src.out, {}, src.k};
+    for (int w = 0; w < kFewRoom; ++w) few.pl[w] = src.pl[w];
+    return few;
+}
 struct AllDecompress {            // list: tensors, then the W payloads of group 0, of group 1, ...
     GroupTable tb;
     int W;
+    static constexpr int kRoom = kMaxWorkers;
     struct Job {
         GroupView out;
         const uintptr_t *pl;
@@ -303,13 +316,13 @@ inline void launch(void (*kernel)(P...), dim3 grid, dim3 block, hipStream_t stre
 void launch_upload_ptrs(const LaunchCtx &lc, const uintptr_t *host, uintptr_t *dev, uint32_t count);
 void launch_expand_ptrs(const LaunchCtx &lc, const GroupView &g, uintptr_t *chunk_addr);
 void launch_expand_all(const LaunchCtx &lc, const GroupTable &tb, uint32_t tiles, uintptr_t *chunk_addr);
-// how: COMBINE_LAST where every group has at most kSmallTiles tiles and src.arrive counts; COMBINE_COLLECT with src.slots
-template <class SRC> void launch_sign_compress(const LaunchCtx &lc, int mode, const SRC &src, uint32_t tiles, uint32_t groups, bool ef, float beta, uint32_t algo, Combine how);
+// small: every group has at most kSmallTiles tiles and src.arrive counts.  src.slots: partials that are not combined so go to collectors
+template <class SRC> void launch_sign_compress(const LaunchCtx &lc, int mode, const SRC &src, uint32_t tiles, bool ef, float beta, uint32_t algo, bool small);
 template <class SRC> void launch_quantize_small(const LaunchCtx &lc, int mode, const SRC &src, uint32_t tiles, bool ef, uint32_t levels, uint64_t seed,
                                                 uint32_t worker, uint32_t iter_lo, uint32_t looks);
 template <class SRC> void launch_scalar_finalize(const LaunchCtx &lc, const SRC &src, uint32_t groups, int mode, uint32_t algo, uint32_t levels,
                                                  bool keep);
-template <class SRC> void launch_accum_reduce(const LaunchCtx &lc, const SRC &src, uint32_t tiles, uint32_t groups, bool ef, int mode, uint32_t levels, uint64_t seed, Combine how);
+template <class SRC> void launch_accum_reduce(const LaunchCtx &lc, const SRC &src, uint32_t tiles, bool ef, int mode, uint32_t levels, uint64_t seed);
 template <class SRC> void launch_qsgd_encode(const LaunchCtx &lc, const SRC &src, uint32_t tiles, bool ef, uint32_t levels, uint64_t seed,
                                              uint32_t worker, uint32_t iter_lo);
 template <class SRC> void launch_tern_encode(const LaunchCtx &lc, const SRC &src, uint32_t tiles, bool ef, uint64_t seed, uint32_t worker, uint32_t iter_lo);
