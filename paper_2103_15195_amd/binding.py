@@ -1,6 +1,7 @@
 """Thin ctypes binding of libmergecomp.so (the C ABI in include/mergecomp.h).
 
-Argument marshalling only: every step of the path runs in the HIP kernels.
+Argument marshalling only: every step of the path runs in the HIP kernels.  The hot calls go through a small
+extension module (csrc/fastcall.cpp) in the forms that a hot loop passes, through ctypes otherwise.
 PyTorch is used for device memory and streams; tensors are passed by
 ``data_ptr()``.  There is no CPU fallback: if the library has not been built the
 import fails.
@@ -55,6 +56,15 @@ class McError(RuntimeError):
 _lib = None
 
 
+def _fastcall():
+    try:
+        from . import _fastcall as module
+    except ImportError as e:
+        raise ImportError(f"{os.path.join(_HERE, '_fastcall.so')}: {e}; run `python -c 'import __graft_entry__ as g; g.build()'` "
+                          "(or paper_2103_15195_amd/build.py) first") from e
+    return module
+
+
 def lib():
     """The loaded library; raises if it has not been built (no fallback path exists)."""
     global _lib
@@ -102,6 +112,8 @@ def lib():
         L.mc_strerror.argtypes = [C.c_int]
         L.mc_strerror.restype = C.c_char_p
         L.mc_version.restype = C.c_char_p
+        L.fast = _fastcall().Calls(C.Array, *[C.cast(f, C.c_void_p).value for f in (
+            L.mc_compress, L.mc_compress_static, L.mc_decompress_sum, L.mc_compress_groups, L.mc_decompress_sum_groups)])
         _lib = L
     return _lib
 
@@ -143,7 +155,7 @@ def _current_stream() -> int:
         import torch
         torch.cuda.current_stream()              # initialises the device if nothing has yet
         get, device = (getattr(torch._C, name, None) for name in ("_cuda_getCurrentRawStream", "_cuda_getDevice"))
-        _raw_stream = (lambda: get(device())) if get and device else (lambda: torch.cuda.current_stream().cuda_stream)
+        _raw_stream = _fastcall().RawStream(get, device) if get and device else (lambda: torch.cuda.current_stream().cuda_stream)
     return _raw_stream()
 
 
@@ -203,12 +215,16 @@ class Context:
         nm = (C.c_int64 * max(len(self.numel), 1))(*self.numel)
         bd = (C.c_int32 * len(self.bounds))(*self.bounds)
         self._h = C.c_void_p()
+        self._at = 0                             # the same as an int
         _check(lib().mc_ctx_create(C.byref(self._h), C.byref(self.cfg), nm, len(self.numel), bd, self.y), "mc_ctx_create")
+        self._at = self._h.value
+        self._fast = lib().fast
 
     def close(self) -> None:
         if getattr(self, "_h", None):
             lib().mc_ctx_destroy(self._h)
             self._h = None
+            self._at = 0
 
     def __del__(self):
         try:
@@ -232,35 +248,55 @@ class Context:
     def state_bytes(self, group: int) -> int:
         return int(lib().mc_state_bytes(self._h, group))
 
-    # the two hot calls --------------------------------------------------------
+    # the hot calls --------------------------------------------------------------
+    # (the fast route returns None, and has done nothing, where an argument is not of the form it takes)
     def mc_compress(self, group: int, worker: int, it: int, grads: Sequence, state, payload, stream=None) -> None:
-        _check(lib().mc_compress(self._h, group, worker, it, _ptr_array(grads),
-                                 None if state is None else state.data_ptr(), payload.data_ptr(),
-                                 _stream_handle(stream)), "mc_compress")
+        rc = self._fast.compress(self._at, group, worker, it, grads, state, payload, _raw_stream) if stream is None else None
+        if rc is None:
+            rc = lib().mc_compress(self._h, group, worker, it, _ptr_array(grads),
+                                   None if state is None else state.data_ptr(), payload.data_ptr(),
+                                   _stream_handle(stream))
+        if rc:
+            raise McError(rc, "mc_compress")
 
     def mc_compress_static(self, group: int, worker: int, it: int, grads: Sequence, state, payload, stream=None) -> None:
         """mc_compress with the reduction partials in the library's static device array (allocates nothing)."""
-        _check(lib().mc_compress_static(self._h, group, worker, it, _ptr_array(grads),
-                                        None if state is None else state.data_ptr(), payload.data_ptr(),
-                                        _stream_handle(stream)), "mc_compress_static")
+        rc = self._fast.compress_static(self._at, group, worker, it, grads, state, payload, _raw_stream) if stream is None else None
+        if rc is None:
+            rc = lib().mc_compress_static(self._h, group, worker, it, _ptr_array(grads),
+                                          None if state is None else state.data_ptr(), payload.data_ptr(),
+                                          _stream_handle(stream))
+        if rc:
+            raise McError(rc, "mc_compress_static")
 
     def mc_decompress_sum(self, group: int, payloads: Sequence, alpha: float, outs: Sequence, stream=None) -> None:
-        W = len(payloads)
-        _check(lib().mc_decompress_sum(self._h, group, _ptr_array(payloads), W, alpha, _ptr_array(outs),
-                                       _stream_handle(stream)), "mc_decompress_sum")
+        rc = self._fast.decompress(self._at, group, payloads, alpha, outs, _raw_stream) if stream is None else None
+        if rc is None:
+            W = len(payloads)
+            rc = lib().mc_decompress_sum(self._h, group, _ptr_array(payloads), W, alpha, _ptr_array(outs),
+                                         _stream_handle(stream))
+        if rc:
+            raise McError(rc, "mc_decompress_sum")
 
-    # state helpers --------------------------------------------------------------
     def mc_compress_groups(self, worker: int, it: int, grads_all, states, payloads, stream=None) -> None:
         """All groups of one worker in one call; tensor sequences (or ptr_array()s of them): the model's gradients,
         one state and one payload per group."""
-        _check(lib().mc_compress_groups(self._h, worker, it, ptr_array(grads_all), None if states is None else ptr_array(states),
-                                        ptr_array(payloads), _stream_handle(stream)), "mc_compress_groups")
+        rc = self._fast.compress_groups(self._at, worker, it, grads_all, states, payloads, _raw_stream) if stream is None else None
+        if rc is None:
+            rc = lib().mc_compress_groups(self._h, worker, it, ptr_array(grads_all), None if states is None else ptr_array(states),
+                                          ptr_array(payloads), _stream_handle(stream))
+        if rc:
+            raise McError(rc, "mc_compress_groups")
 
     def mc_decompress_sum_groups(self, payloads, W: int, alpha: float, outs_all, stream=None) -> None:
         """payloads: W * y entries, worker-major (payloads[w * y + j])."""
-        _check(lib().mc_decompress_sum_groups(self._h, ptr_array(payloads), W, alpha, ptr_array(outs_all), _stream_handle(stream)),
-               "mc_decompress_sum_groups")
+        rc = self._fast.decompress_groups(self._at, payloads, W, alpha, outs_all, _raw_stream) if stream is None else None
+        if rc is None:
+            rc = lib().mc_decompress_sum_groups(self._h, ptr_array(payloads), W, alpha, ptr_array(outs_all), _stream_handle(stream))
+        if rc:
+            raise McError(rc, "mc_decompress_sum_groups")
 
+    # state helpers --------------------------------------------------------------
     def mc_state_export_residual(self, group: int, state, e_out, stream=None) -> None:
         _check(lib().mc_state_export_residual(self._h, group, state.data_ptr(), e_out.data_ptr(),
                                               _stream_handle(stream)), "mc_state_export_residual")

@@ -1,13 +1,16 @@
-"""Builds libmergecomp.so (the C-ABI HIP library) in-tree with hipcc for gfx950."""
+"""Builds libmergecomp.so (the C-ABI HIP library) in-tree with hipcc for gfx950, and _fastcall.so (the binding's hot calls) with the
+host compiler."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmergecomp.so")
+FASTCALL = os.path.join(HERE, "_fastcall.so")
 SOURCES = ["mc_api.hip", "kernels_dense.hip", "kernels_sparse.hip"]
 
 # -ffp-contract=off: the residual updates must round every fp32 operation on its own
@@ -19,18 +22,22 @@ HIPCC_FLAGS = [
 ]
 
 
-def build(verbose: bool = False) -> str:
-    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    cmd = [hipcc] + HIPCC_FLAGS + ["-o", LIB] + [os.path.join(CSRC, s) for s in SOURCES]
+def _run(cmd, verbose: bool) -> None:
     if verbose:
         print(" ".join(cmd), flush=True)
     res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     # the host pass warns that it does not know the packed-fp32 target feature: harmless
     out = "\n".join(l for l in res.stdout.splitlines() if "packed-fp32-ops" not in l)
     if res.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + out)
+        raise RuntimeError(f"{cmd[0]} failed:\n" + out)
     if verbose and out.strip():
         print(out)
+
+
+def build(verbose: bool = False) -> str:
+    _run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I" + sysconfig.get_paths()["include"],
+          "-o", FASTCALL, os.path.join(CSRC, "fastcall.cpp")], verbose)
+    _run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")] + HIPCC_FLAGS + ["-o", LIB] + [os.path.join(CSRC, s) for s in SOURCES], verbose)
     return LIB
 
 
