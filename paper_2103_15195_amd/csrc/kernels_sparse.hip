@@ -171,11 +171,23 @@ __device__ __forceinline__ void put_candidates(const Chunk &c, const uint32_t (&
 // wavefront's instructions.  (Compress, 33 / 34 000 / 200 000 / 2 M elements, with one copy of the window on the first two: Top-k
 // 11.9 / 11.8 / 17.0 / 20.4 -> 9.1 / 10.2 / 15.4 / 19.2 us, DGC 12.6 / 12.0 / 16.7 / 21.7 -> 9.0 / 10.3 / 14.9 / 19.9, Rand-k 18.8 / 16.7 /
 // 20.7 / 24.1 -> 15.1 / 14.4 / 18.3 / 22.1.)
-template <int ALGO, bool EF, class SRC, int S = kSteps>
-__global__ __launch_bounds__(kTile / S) void sparse_accum_k(SRC src, float momentum, RngKey rng, SampleRule smp)
+// SMALL: the whole compress of groups of at most kOneBlockTiles tiles, in launches of at most kSameTiles.  In the block of a group that is done
+// last with the streaming pass the selection follows, as lean_small_k has it: a kernel that starts behind another one takes 1 us of the device
+// and 2.6 of the host, a die's lines written to memory and a count of the blocks that are done take less.  No block waits for another.  (A word more for the plain kernel's arguments took 0.3 us of a call.)
+// (Compress, two kernels -> one.  Top-k 1 % of 1 / 4 / 8 tiles 10.1 / 10.1 / 10.2 -> 8.5 / 8.9 / 9.2 us, 5 % 10.1 / 10.9 / 12.4 -> 8.8 / 10.0 / 11.4; DGC 1 % 10.1 /
+// 10.1 / 10.3 -> 8.9 / 9.3 / 9.5; Rand-k 1 % 19.2 / 20.7 / 20.5 -> 17.8 / 20.0 / 19.8; four groups of 1 / 4 tiles in one call, Top-k 14.1 / 14.1 -> 11.3 /
+// 11.4, and with the decompression of four workers 19.2 / 18.6 -> 15.7 / 15.5.  Larger groups lose what the launch saves to the tail's
+// wait for the slowest block: four groups of 12 / 16 / 18 tiles, both directions, 18.4 / 18.9 / 18.9 -> 18.5 / 19.8 / 19.9.)
+constexpr int kRoundTiles = 4096;      // tiles per round of the slow routes' compaction: 256 blocks of 16 wavefronts at most
+template <int ALGO, bool EF, int MOST>
+__device__ __forceinline__ void small_tail(SparseJob job, RngKey rng, uint32_t sync_blocks, int *status, uint32_t *hist, uint32_t *pfx, uint32_t *small);
+template <int ALGO, bool EF, class SRC, int S = kSteps, bool SMALL = false>
+__global__ __launch_bounds__(kTile / S) void sparse_accum_k(SRC src, float momentum, RngKey rng, std::conditional_t<SMALL, int *, SampleRule> last)
 {
     constexpr int kThreads = kTile / S, kWaves = kThreads / kWave, kQuarters = kSteps / S;      // wavefronts per chunk: one, or four
-    __shared__ uint32_t hist[kBinsW];
+    SampleRule smp{0u, 0u, 0u};
+    if constexpr (!SMALL) smp = last;
+    __shared__ __attribute__((aligned(16))) uint32_t hist[kBinsW];
     __shared__ uint32_t wcnt[kWaves];
     for (int b = threadIdx.x; b < kBinsW; b += kThreads) hist[b] = 0u;
     __syncthreads();
@@ -191,9 +203,10 @@ __global__ __launch_bounds__(kTile / S) void sparse_accum_k(SRC src, float momen
     if (order == 0 && threadIdx.x == 0) sc.arrive[0] = sc.arrive[kArriveWindow] = 0u;       // and nobody waits at a grid-wide barrier of that call any more
     // The radix levels are cleared by the kernels that use them -- unless a call gave up at a barrier (MC_ERR_DEVICE):
     // what it left behind must not enter this call's counts.  (A group of fewer tiles than it takes blocks to clear them at
-    // once goes round again.)
-    for (uint32_t i = order * (uint32_t)kThreads + threadIdx.x; i < (uint32_t)(kHistOpen - kHist1); i += job.blocks * (uint32_t)kThreads)
-        sc.hist[kHist1 + i] = 0u;
+    // once goes round again; a tail of one block keeps the levels in LDS.)
+    if (!SMALL)
+        for (uint32_t i = order * (uint32_t)kThreads + threadIdx.x; i < (uint32_t)(kHistOpen - kHist1); i += job.blocks * (uint32_t)kThreads)
+            sc.hist[kHist1 + i] = 0u;
     uint32_t run = 0;
     uint32_t bits[S];
     uint64_t flag[S];
@@ -268,6 +281,29 @@ __global__ __launch_bounds__(kTile / S) void sparse_accum_k(SRC src, float momen
     // (A group of few tiles has no crowd at its bins: one copy then, the only one that a kernel for small groups reads.)
     flush_fine(hist, sc.hist + kHistW + (job.blocks <= (uint32_t)kSmallSelTiles ? 0u : order % kWinCopies) * kBinsW, kBinsW - 1);
     if (threadIdx.x == kThreads - 1 && hist[kBinsW - 1]) atomicAdd(&sc.hist[kHistOpen + (order & (kOpenCopies - 1))], hist[kBinsW - 1]);
+    if constexpr (SMALL) {
+        static_assert(kThreads == 1024 && kBinsW >= kBins1, "the tail's block and histogram");
+        __shared__ uint32_t pfx[2 * kRoundTiles], small[64];
+        uint32_t *done = sc.arrive + kArriveDone;
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            const uint32_t before = __hip_atomic_fetch_add(done, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+            if (before == job.blocks - 1u) {
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+                *done = 0u;                      // (for the next call)
+            }
+            small[0] = before;
+        }
+        __syncthreads();
+        const uint32_t before = (uint32_t)__builtin_amdgcn_readfirstlane((int)small[0]);
+        if (before != job.blocks - 1u) return;
+        __syncthreads();
+        SparseJob tail = job;
+        tail.block = 0u;
+        tail.blocks = 1u;
+        small_tail<ALGO, EF, (int)kOneBlockTiles>(tail, rng, 1u, last, hist, pfx, small);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1161,7 +1197,6 @@ __device__ __forceinline__ void each_key(const GroupView &g, const float *st, co
     }
 }
 
-constexpr int kRoundTiles = 4096;      // tiles per round of the slow routes' compaction: 256 blocks of 16 wavefronts at most
 
 // The routes that need more than the window: all radix levels still open, the per-tile counts and the ordered
 // compaction, as steps of the first `blocks` blocks of the group's select blocks (which the device holds at once).
@@ -1771,19 +1806,16 @@ constexpr int kFewRounds = 2, kManyRounds = 16;
 constexpr uint32_t kFewCands = (uint32_t)kFewRounds * kSelThreads, kManyCands = (uint32_t)kManyRounds * kSelThreads;
 static_assert(kSmallSelTiles * kWavesPerBlock == 128 && kManyCands <= 0xFFFFu, "");
 
-template <int ALGO, bool EF, class SRC>
-__global__ __launch_bounds__(kSelThreads) void lean_small_k(SRC src, RngKey rng, uint32_t sync_blocks, int *status)
+// job: small_sel_blocks() blocks, of which the first one selects and emits.  MOST: tiles that the group may have.
+template <int ALGO, bool EF, int MOST>
+__device__ __forceinline__ void small_tail(SparseJob job, RngKey rng, uint32_t sync_blocks, int *status, uint32_t *hist /* LDS: kBins1, */,
+                                           uint32_t *pfx /* 2 * kRoundTiles (slow routes), */, uint32_t *small /* 64 words */)
 {
-    __shared__ __attribute__((aligned(16))) uint32_t hist[kBins1];
-    __shared__ uint32_t pfx[2 * kRoundTiles];    // (slow routes)
-    __shared__ uint32_t small[64];
     __shared__ uint32_t wtot[kSelWaves], verdict[8];
     __shared__ uint32_t from[kSmallSelTiles * kWavesPerBlock + 1];      // candidates of the group before each chunk
     __shared__ uint32_t kept[kSmallSelTiles];    // entries in each tile
     __shared__ uint32_t clears;
-    const SparseJob job = src.small_job();
     const uint32_t n = job.g.n;
-    if (job.block >= job.blocks) return;
     const uint32_t t = threadIdx.x, lane = t & 63u, wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const SparseScratch &sc = job.sc;
     const uint32_t k = (uint32_t)job.k, ntiles = tiles_in(n);
@@ -1834,14 +1866,14 @@ __global__ __launch_bounds__(kSelThreads) void lean_small_k(SRC src, RngKey rng,
         };
         auto chunk = [&](int r) { return chunks[r / 4] >> (8 * (r % 4)) & 0xFFu; };
         if (job.block == 0 && N - 1u < kManyCands) {
-            if (!MANY) {                         // by bisection: seven looks a round
+            if (!MANY) {                         // by bisection: seven looks a round, or five
 #pragma unroll
                 for (int r = 0; r < ROUNDS; ++r) {
                     if ((uint32_t)r < rounds) {
                         const uint32_t p = min(first + 64u * r, N - 1u);
                         uint32_t ch = 0;         // the last chunk that starts at or before p
 #pragma unroll
-                        for (uint32_t step = kWavesPerBlock * kSmallSelTiles / 2; step >= 1; step >>= 1) if (from[ch + step] <= p) ch += step;
+                        for (uint32_t step = kWavesPerBlock * MOST / 2; step >= 1; step >>= 1) if (from[ch + step] <= p) ch += step;
                         load(r, ch, p - from[ch]);
                     }
                 }
@@ -1927,15 +1959,29 @@ __global__ __launch_bounds__(kSelThreads) void lean_small_k(SRC src, RngKey rng,
 }
 
 template <int ALGO, bool EF, class SRC>
+__global__ __launch_bounds__(kSelThreads) void lean_small_k(SRC src, RngKey rng, uint32_t sync_blocks, int *status)
+{
+    __shared__ __attribute__((aligned(16))) uint32_t hist[kBins1];
+    __shared__ uint32_t pfx[2 * kRoundTiles], small[64];
+    const SparseJob job = src.small_job();
+    if (job.block >= job.blocks) return;
+    small_tail<ALGO, EF, kSmallSelTiles>(job, rng, sync_blocks, status, hist, pfx, small);
+}
+
+template <int ALGO, bool EF, class SRC>
 static void sparse_compress_t(const LaunchCtx &lc, const SRC &src, const SparseBlocks &nb, const SparseCall &call)
 {
     const RngKey rng{call.seed, call.worker, call.iter_lo};
+    // the slow routes run on blocks that the device holds at once: one per compute unit
+    const uint32_t sync = std::max(1u, std::min(call.sync_blocks, (uint32_t)(kRoundTiles / kSelWaves)));
+    if (nb.same) {
+        MC_LAUNCH((sparse_accum_k<ALGO, EF, SRC, kSpreadSteps, true>), dim3(nb.tiles), dim3(kSpread), lc, src, call.momentum, rng, call.status);      // (the profiler is off)
+        return;
+    }
     prof_begin(lc, K_SPARSE_ACCUM);
     if (nb.tiles <= kSpreadTiles) MC_LAUNCH((sparse_accum_k<ALGO, EF, SRC, kSpreadSteps>), dim3(nb.tiles), dim3(kSpread), lc, src, call.momentum, rng, (SampleRule{0u, 0u, 0u}));
     else MC_LAUNCH((sparse_accum_k<ALGO, EF, SRC>), dim3(nb.tiles), dim3(kBlock), lc, src, call.momentum, rng, (SampleRule{0u, 0u, 0u}));
     prof_end(lc, K_SPARSE_ACCUM);
-    // the slow routes run on blocks that the device holds at once: one per compute unit
-    const uint32_t sync = std::max(1u, std::min(call.sync_blocks, (uint32_t)(kRoundTiles / kSelWaves)));
     if (nb.small) {
         MC_LAUNCH((lean_small_k<ALGO, EF, SRC>), dim3(nb.small), dim3(kSelThreads), lc, src, rng, sync, call.status);      // (the profiler is off)
         return;

@@ -844,7 +844,7 @@ static int compress_impl(mc_ctx *ctx, int32_t group, uint32_t worker, uint64_t i
         call.sample_need = m ? std::max<uint64_t>(1, (uint64_t)(((unsigned __int128)m * cfg.ratio_ppm) / 1000000u)) : 0;
     }
     SparseBlocks nb = sparse_blocks(n);
-    if (selects_small(n, G.k) && !(prof && prof->on)) nb.small = small_sel_blocks(nb.tiles);
+    if (selects_small(n, G.k) && !(prof && prof->on)) { nb.small = small_sel_blocks(nb.tiles); nb.same = nb.small == 1u; }
     launch_sparse_compress(lc, cfg.algo, OneSparse{gv, sf, hdr, G.k, sp}, nb, ef, call);
     return check_launch();
 }
@@ -892,8 +892,11 @@ static int compress_all(mc_ctx *ctx, uint32_t worker, uint64_t iter, const float
         ctx->last_hint = last.hint;
         ctx->last_sel = last.sel;
         const bool one_each = small_sel_blocks(ctx->max_tiles) <= 1u;
-        const SparseBlocks nb{ctx->all_blocks[BLK_TILE], ctx->all_blocks[BLK_SELECT], ctx->all_blocks[BLK_EMIT],
-                              !ctx->all_select_small || ctx->prof.on ? 0u : one_each ? (uint32_t)y : ctx->all_blocks[BLK_EMIT]};
+        SparseBlocks nb{ctx->all_blocks[BLK_TILE], ctx->all_blocks[BLK_SELECT], ctx->all_blocks[BLK_EMIT]};
+        if (ctx->all_select_small && !ctx->prof.on) {
+            nb.small = one_each ? (uint32_t)y : nb.emit;
+            nb.same = one_each && nb.tiles <= kSameTiles;
+        }
         launch_sparse_compress(lc, cfg.algo, AllSparse{tb, sp, ctx->last_group, one_each}, nb, ef, sparse_call(ctx, worker, iter));
     } else dense_compress(cfg, lc, AllCompress{tb, ctx->d_partial, ctx->d_arrive, ctx->d_slots, ctx->d_status, ctx->all_blocks[BLK_TILE]}, ctx->all_blocks[BLK_TILE], (uint32_t)y, ctx->max_tiles, worker,
                         (uint32_t)iter, ctx->wait_looks);

@@ -389,8 +389,10 @@ __host__ __device__ inline SparseScratch scratch_of(const SparseScratch &all, ui
 constexpr int kSelTiles = 16, kEmitTiles = kWavesPerBlock;     // tiles per block of the select and the emit kernel
 // Blocks of a group that lean_small_k, which is both for small groups, runs the slow routes on.  (Up to 8 tiles one block, which needs
 // no barriers, is ahead: 8 tiles, a refill and a rise in turn, Top-k 41.7 us, two blocks 45.2; 16 tiles 54.4, four blocks 49.1.)
-__host__ __device__ constexpr uint32_t small_sel_blocks(uint32_t tiles) { return tiles == 0u ? 0u : tiles <= 8u ? 1u : (tiles + kEmitTiles - 1u) / kEmitTiles; }
+constexpr uint32_t kOneBlockTiles = 8;
+__host__ __device__ constexpr uint32_t small_sel_blocks(uint32_t tiles) { return tiles == 0u ? 0u : tiles <= kOneBlockTiles ? 1u : (tiles + kEmitTiles - 1u) / kEmitTiles; }
 constexpr int kArriveWindow = 1;                               // word behind SparseScratch::arrive: blocks of lean_small_k that have read the window
+constexpr int kArriveDone = 2;                                 // ... of sparse_accum_k, where the selection follows, that are done (0 between calls)
 
 // A sparsifier's job: `block` is this block's number among the group's `blocks` of its kind (tiles: handed out last first).
 struct SparseJob {
@@ -459,7 +461,14 @@ struct SparseCall {
 constexpr int kSmallSelTiles = 32;
 constexpr uint32_t kSmallKept = 6144;
 inline bool selects_small(uint32_t n, uint64_t k) { return tiles_in(n) <= (uint32_t)kSmallSelTiles && k <= kSmallKept; }
-struct SparseBlocks { uint32_t tiles, select, emit, small = 0; };          // blocks of each kind that the launches cover; small: those of lean_small_k, if all groups are such
+// Tiles of a launch of sparse_accum_k with the selection.  (Beyond, a compute unit has room for one of its blocks, or for two of the streaming pass: Top-k compress of
+// 64 groups of 1 / 3 / 5 tiles, two kernels 16.4 / 13.6 / 15.2 us, one 14.8 / 14.2 / 21.0.)
+constexpr uint32_t kSameTiles = 64;
+struct SparseBlocks {             // blocks of each kind that the launches cover
+    uint32_t tiles, select, emit;
+    uint32_t small = 0;           // those of lean_small_k, if all groups are such
+    bool same = false;            // ... and sparse_accum_k does their work
+};
 inline SparseBlocks sparse_blocks(uint32_t n)
 {
     const uint32_t t = tiles_in(n);
