@@ -1172,25 +1172,30 @@ template void launch_fp16_compress<AllCompress>(const LaunchCtx &, const AllComp
 // so the mapping changes no result: every element still adds its workers' values in worker order.
 // (Measured, 8 workers, 25.6 M elements: QSGD 62.9 -> 54.6 us.  The same mapping with 8-byte loads
 // made FP16 slower, 80.3 -> 82.5..85 us with 2, 4 or 8 workers per batch, so FP16 stays plain.)
-template <int ALGO, class SRC>
-__global__ __launch_bounds__(kBlock) void dense_decompress_k(SRC src, int W, float alpha, uint32_t levels, int *status)
+// S: elements per lane, 16, or 4 on a launch of few tiles (kSpreadDecodeTiles).  Those are bound by one wavefront's chain of instructions and
+// waits: a quarter of the additions each, and with the registers that frees, eight workers in a batch -- every batch waits for its scales and
+// codes anew.  (1 / 64 / 256 tiles, QSGD, 4 workers 4.7 / 4.8 / 5.4 -> 3.9 / 3.9 / 4.2 us, 8 workers 6.3 / 6.5 / 7.4 -> 4.2 / 4.5 / 5.2, 16 workers 9.9 / 10.4 /
+// 11.8 -> 6.5 / 7.0 / 8.0; FP16, 8 workers 5.9 / 6.1 / 6.8 -> 4.0 / 4.2 / 5.3.  One worker is bound by the launch.)
+template <int ALGO, class SRC, int S = kSteps>
+__global__ __launch_bounds__(kTile / S) void dense_decompress_k(SRC src, int W, float alpha, uint32_t levels, int *status)
 {
     static_assert(ALGO == MC_ALGO_QSGD || ALGO == MC_ALGO_FP16, "one code per element");
-    constexpr int kBatch = 4;
-    if (blockIdx.x < SRC::kCheckers) { src.check({ALGO, false, false}, W, status); return; }
+    constexpr int kBatch = S == kSteps ? 4 : 8, kWords = S / 4;
+    if (blockIdx.x < SRC::kCheckers) { if (S == kSteps || threadIdx.x < (uint32_t)kBlock) src.check({ALGO, false, false}, W, status); return; }
     const auto job = src.template job<BLK_TILE>();
     const GroupView &out = job.out;
-    const Chunk c = my_chunk(out.n, job.block);
+    const Chunk c = my_chunk<S>(out.n, job.block);
     if (c.base >= out.n) return;
     const uintptr_t entry = chunk_entry(out, c);
     if (ALGO == MC_ALGO_QSGD && !(entry & 15u)) {               // an address (even), and 16-byte aligned
         const uint32_t rot = chunk_rotation(entry);             // a multiple of 4 here
-        uint32_t at[4];                                         // first of the lane's four elements in step m
+        const uint32_t part = c.base & (uint32_t)(kChunk - 1), chunk = c.base - part;      // (part: 0 unless a wavefront holds a quarter)
+        uint32_t at[kWords];                                    // first of the lane's four elements in step m
 #pragma unroll
-        for (int m = 0; m < 4; ++m) at[m] = (256u * m + 4u * c.lane + rot) & (uint32_t)(kChunk - 1);
-        float acc[4][4];
+        for (int m = 0; m < kWords; ++m) at[m] = (part + 256u * m + 4u * c.lane + rot) & (uint32_t)(kChunk - 1);
+        float acc[kWords][4];
 #pragma unroll
-        for (int m = 0; m < 4; ++m)
+        for (int m = 0; m < kWords; ++m)
 #pragma unroll
             for (int e = 0; e < 4; ++e) acc[m][e] = 0.0f;
         for (int w0 = 0; w0 < W; w0 += kBatch) {
@@ -1202,12 +1207,12 @@ __global__ __launch_bounds__(kBlock) void dense_decompress_k(SRC src, int W, flo
                 scale[b] = 0.0f;
                 if (w0 + b < W) scale[b] = ld_uniform(&reinterpret_cast<const PayloadHeader *>(pl[b])->scale);
             }
-            uint32_t cw[kBatch][4];
+            uint32_t cw[kBatch][kWords];
 #pragma unroll
             for (int b = 0; b < kBatch; ++b) {
-                const global_ptr<const uint8_t> codes = in_global(pl[b]) + kHeaderBytes + c.base;
+                const global_ptr<const uint8_t> codes = in_global(pl[b]) + kHeaderBytes + chunk;
 #pragma unroll
-                for (int m = 0; m < 4; ++m) cw[b][m] = w0 + b < W ? __builtin_nontemporal_load((global_ptr<const uint32_t>)(codes + at[m])) : 0u;
+                for (int m = 0; m < kWords; ++m) cw[b][m] = w0 + b < W ? __builtin_nontemporal_load((global_ptr<const uint32_t>)(codes + at[m])) : 0u;
             }
             hold(scale);
 #pragma unroll
@@ -1215,7 +1220,7 @@ __global__ __launch_bounds__(kBlock) void dense_decompress_k(SRC src, int W, flo
                 if (w0 + b < W) {
                     const float q = (float)((double)scale[b] / (double)(float)levels);
 #pragma unroll
-                    for (int m = 0; m < 4; ++m)
+                    for (int m = 0; m < kWords; ++m)
 #pragma unroll
                         for (int e = 0; e < 4; ++e) acc[m][e] = acc[m][e] + (float)(int8_t)(cw[b][m] >> (8 * e)) * q;
                 }
@@ -1223,15 +1228,15 @@ __global__ __launch_bounds__(kBlock) void dense_decompress_k(SRC src, int W, flo
         }
         const global_ptr<float> p = in_global(reinterpret_cast<float *>(entry));
 #pragma unroll
-        for (int m = 0; m < 4; ++m) {
+        for (int m = 0; m < kWords; ++m) {
             float4v v = {alpha * acc[m][0], alpha * acc[m][1], alpha * acc[m][2], alpha * acc[m][3]};
             __builtin_nontemporal_store(v, (global_ptr<float4v>)(p + at[m]));
         }
         return;
     }
-    float acc[kSteps];
+    float acc[S];
 #pragma unroll
-    for (int j = 0; j < kSteps; ++j) acc[j] = 0.0f;
+    for (int j = 0; j < S; ++j) acc[j] = 0.0f;
     for (int w0 = 0; w0 < W; w0 += kBatch) {
         const uint8_t *pl[kBatch];
         job.template payloads<kBatch>(w0, W, pl);
@@ -1242,7 +1247,7 @@ __global__ __launch_bounds__(kBlock) void dense_decompress_k(SRC src, int W, flo
             if (w0 + b < W) scale[b] = ld_uniform(&reinterpret_cast<const PayloadHeader *>(pl[b])->scale);
         }
         if (ALGO == MC_ALGO_QSGD) {
-            int8_t cd[kBatch][kSteps];
+            int8_t cd[kBatch][S];
 #pragma unroll
             for (int b = 0; b < kBatch; ++b) {
                 if (w0 + b < W) load_flat<int8_t>(reinterpret_cast<const int8_t *>(pl[b] + kHeaderBytes), c, out.n, cd[b], (int8_t)0);
@@ -1253,11 +1258,11 @@ __global__ __launch_bounds__(kBlock) void dense_decompress_k(SRC src, int W, flo
                 if (w0 + b < W) {
                     const float q = (float)((double)scale[b] / (double)(float)levels);
 #pragma unroll
-                    for (int j = 0; j < kSteps; ++j) acc[j] = acc[j] + (float)cd[b][j] * q;
+                    for (int j = 0; j < S; ++j) acc[j] = acc[j] + (float)cd[b][j] * q;
                 }
             }
         } else {   // FP16
-            _Float16 hv[kBatch][kSteps];
+            _Float16 hv[kBatch][S];
 #pragma unroll
             for (int b = 0; b < kBatch; ++b) {
                 if (w0 + b < W) load_flat<_Float16>(reinterpret_cast<const _Float16 *>(pl[b] + kHeaderBytes), c, out.n, hv[b], (_Float16)0.0f);
@@ -1266,13 +1271,13 @@ __global__ __launch_bounds__(kBlock) void dense_decompress_k(SRC src, int W, flo
             for (int b = 0; b < kBatch; ++b) {
                 if (w0 + b < W) {
 #pragma unroll
-                    for (int j = 0; j < kSteps; ++j) acc[j] = acc[j] + (float)hv[b][j];
+                    for (int j = 0; j < S; ++j) acc[j] = acc[j] + (float)hv[b][j];
                 }
             }
         }
     }
 #pragma unroll
-    for (int j = 0; j < kSteps; ++j) acc[j] = alpha * acc[j];
+    for (int j = 0; j < S; ++j) acc[j] = alpha * acc[j];
     store_seg(out, c, acc, entry);
 }
 
@@ -1543,8 +1548,14 @@ static void dense_decompress_t(const LaunchCtx &lc, int algo, const SRC &src, ui
         if constexpr (SRC::kRoom > kPlaneBatch) if (W > kPlaneBatch) { MC_LAUNCH((plane_decompress_k<true, true, SRC>), grid, block, lc, src, W, alpha, status, algo, PLANE_SCALE); break; }
         MC_LAUNCH((plane_decompress_k<true, false, SRC>), grid, block, lc, src, W, alpha, status, algo, PLANE_SCALE);
         break;
-    case MC_ALGO_QSGD: MC_LAUNCH((dense_decompress_k<MC_ALGO_QSGD, SRC>), grid, block, lc, src, W, alpha, levels, status); break;
-    default: MC_LAUNCH((dense_decompress_k<MC_ALGO_FP16, SRC>), grid, block, lc, src, W, alpha, levels, status); break;
+    case MC_ALGO_QSGD:
+        if (blocks <= kSpreadDecodeTiles) MC_LAUNCH((dense_decompress_k<MC_ALGO_QSGD, SRC, kSpreadSteps>), grid, dim3(kSpread), lc, src, W, alpha, levels, status);
+        else MC_LAUNCH((dense_decompress_k<MC_ALGO_QSGD, SRC>), grid, block, lc, src, W, alpha, levels, status);
+        break;
+    default:
+        if (blocks <= kSpreadDecodeTiles) MC_LAUNCH((dense_decompress_k<MC_ALGO_FP16, SRC, kSpreadSteps>), grid, dim3(kSpread), lc, src, W, alpha, levels, status);
+        else MC_LAUNCH((dense_decompress_k<MC_ALGO_FP16, SRC>), grid, block, lc, src, W, alpha, levels, status);
+        break;
     }
     prof_end(lc, K_DENSE_DECOMPRESS);
 }

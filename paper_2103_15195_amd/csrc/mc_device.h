@@ -283,21 +283,22 @@ __device__ __forceinline__ void load_seg(const GroupView &g, const Chunk &c, flo
 // 102 MB fill takes 16 us aligned and 22 us not, the plane decompress kernel 27 and 32 us -- while loads
 // are not sensitive.  Rotating lanes to aligned windows did not pay in these kernels.  Tensors whose flat
 // offset is a multiple of 16 elements keep the aligned rate.)
-__device__ __forceinline__ void store_seg(const GroupView &g, const Chunk &c, const float (&v)[kSteps], uintptr_t entry)
+template <int S>
+__device__ __forceinline__ void store_seg(const GroupView &g, const Chunk &c, const float (&v)[S], uintptr_t entry)
 {
     if (!(entry & 1u)) {
-        const global_ptr<float> p = in_global(reinterpret_cast<float *>(entry)) + c.lane;
+        const global_ptr<float> p = in_global(reinterpret_cast<float *>(entry)) + (S == kSteps ? 0u : c.base & (uint32_t)(kChunk - 1)) + c.lane;
 #pragma unroll
-        for (int j = 0; j < kSteps; ++j) __builtin_nontemporal_store(v[j], p + 64 * j);
+        for (int j = 0; j < S; ++j) __builtin_nontemporal_store(v[j], p + 64 * j);
     } else {
         const uint32_t s0 = (uint32_t)(entry >> 1);
-        if (each_step_of_chunk<true, kSteps>(g, c, tensors_of_chunk(g, s0), [&](int j, uintptr_t at) {
+        if (each_step_of_chunk<true, S>(g, c, tensors_of_chunk(g, s0), [&](int j, uintptr_t at) {
                 if (c.base + 64 * j + c.lane < g.n) *in_global(reinterpret_cast<float *>(at)) = v[j];
             })) return;
-        for_each_tensor_of_chunk(g, c, s0, [&](uint32_t beg, uint32_t end, uintptr_t ptr) {
+        for_each_tensor_of_chunk<S>(g, c, s0, [&](uint32_t beg, uint32_t end, uintptr_t ptr) {
             const global_ptr<float> p = in_global(reinterpret_cast<float *>(ptr));
 #pragma unroll
-            for (int j = 0; j < kSteps; ++j) {
+            for (int j = 0; j < S; ++j) {
                 const uint32_t i = c.base + 64 * j + c.lane;
                 if (i >= beg && i < end) p[i - beg] = v[j];
             }

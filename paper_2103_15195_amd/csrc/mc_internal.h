@@ -101,6 +101,10 @@ constexpr uint32_t kSpreadTiles = 512;
 // ... and EF-Sign and OneBit, which sum p in the order of the other form: 400 000 / 1 M / 2 M elements, EF-Sign 8.1 / 8.7 / 10.0 and
 // 7.8 / 8.8 / 10.4, OneBit 9.8 / 10.5 / 11.8 and 9.6 / 10.5 / 13.0.
 constexpr uint32_t kSpreadSumTiles = 128;
+// ... and the decompress-and-sum of one code per element: a block per compute unit.  Of 256 / 400 / 500 tiles in one tensor, QSGD, 1 worker 4.1 / 4.3 /
+// 4.4 and 3.9 / 4.6 / 5.2 us, 8 workers 7.4 / 7.6 / 7.5 and 5.2 / 6.7 / 7.1; FP16, 1 worker 4.1 / 4.5 / 4.5 and 4.2 / 4.2 / 4.3, 8 workers 6.8 /
+// 8.1 / 8.6 and 5.3 / 7.1 / 7.6.
+constexpr uint32_t kSpreadDecodeTiles = 256;
 __host__ __device__ inline uint32_t tiles_in(uint32_t n) { return (uint32_t)(((uint64_t)n + kTile - 1) / kTile); }
 
 // How the blocks' partial sums become the group's scalars: by a kernel after this one; by the block of a small group that arrives last; by a block
