@@ -1528,6 +1528,102 @@ __global__ __launch_bounds__(kBlock) void plane_decompress_k(SRC src, int W, flo
     }
 }
 
+// The same on few tiles, where the time is one wavefront's chain: four times as many wavefronts, a lane holds eight elements, one byte of every
+// worker's plane, and one transpose; every term is added as what it is.  (8 / 32 / 128 blocks, EF-Sign, 1 worker 5.1 / 5.1 / 5.3 -> 4.2 / 4.3 / 4.6 us, 8
+// workers 5.1 / 5.2 / 5.7 -> 4.7 / 4.9 / 5.3, 16 workers 7.1 / 7.1 / 7.7 -> 6.4 / 6.4 / 6.7; in 60 tensors, where a wavefront of 2048 elements walks over the
+// tensors of its two chunks one after the other, 1 worker 6.3 / 6.4 / 6.6 -> 4.7 / 4.7 / 5.1, 8 workers 6.4 / 6.4 / 6.7 -> 5.1 / 5.3 / 5.7; TernGrad there,
+// 4 workers 6.4 / 6.3 / 6.6 -> 4.8 / 4.8 / 5.1.)
+constexpr int kByteSteps = 8, kByteWave = 64 * kByteSteps, kByteThreads = kSignTile / kByteSteps;
+template <bool TERN, class SRC>
+__global__ __launch_bounds__(kByteThreads) void plane_spread_k(SRC src, int W, float alpha, int *status, int algo, int kind)
+{
+    __shared__ float table[TERN ? 1 : 256];
+    __shared__ float stage[kByteThreads / 64][kByteWave + 64];
+    const uint32_t t = threadIdx.x;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63u;
+    if (blockIdx.x < SRC::kCheckers) { if (t < (uint32_t)kBlock) src.check({(uint32_t)algo, false, false}, W, status); return; }
+    const auto job = src.template job<BLK_PLANE>();
+    const GroupView &out = job.out;
+    const uint32_t wbase = job.block * (uint32_t)kSignTile + wave * (uint32_t)kByteWave;
+    const uint32_t nbytes = 4u * ((out.n + 31u) >> 5);
+    const uint32_t at = (wbase >> 3) + lane;
+    float scale[kPlaneBatch], scale_lo[kPlaneBatch];
+    uint32_t bits[kPlaneBatch], second[kPlaneBatch];
+    auto fetch = [&](int w0) {
+        const uint8_t *pl[kPlaneBatch];
+        job.template payloads<kPlaneBatch>(w0, W, pl);
+#pragma unroll
+        for (int b = 0; b < kPlaneBatch; ++b) {
+            const PayloadHeader *h = reinterpret_cast<const PayloadHeader *>(pl[b]);
+            scale[b] = scale_lo[b] = 0.0f;
+            if (w0 + b < W) {
+                if (TERN || kind != PLANE_VOTE) scale[b] = ld_uniform(&h->scale);
+                if (!TERN && kind == PLANE_MEANS) scale_lo[b] = __uint_as_float(ld_uniform(&h->pad[0]));
+            }
+        }
+#pragma unroll
+        for (int b = 0; b < kPlaneBatch; ++b) {
+            bits[b] = second[b] = 0u;
+            if (w0 + b < W && at < nbytes) {
+                const global_ptr<const uint8_t> plane = in_global(pl[b]) + kHeaderBytes;
+                bits[b] = plane[at];
+                if (TERN) second[b] = plane[nbytes + at];
+            }
+        }
+        hold(scale);
+        if (!TERN) hold(scale_lo);
+    };
+    fetch(0);
+    float acc[kByteSteps];
+    if (!TERN) {
+        if (t < 256u) {
+            float sum = 0.0f;
+#pragma unroll
+            for (int b = 0; b < kPlaneBatch; ++b) {
+                float hi, lo;
+                plane_levels(scale[b], scale_lo[b], kind, hi, lo);
+                sum = b < W ? sum + (((t >> b) & 1u) ? hi : lo) : sum;
+            }
+            table[t] = sum;
+        }
+        __syncthreads();
+        if (wbase >= out.n) return;
+        const uint32_t lo = bits[0] | bits[1] << 8 | bits[2] << 16 | bits[3] << 24, hi = bits[4] | bits[5] << 8 | bits[6] << 16 | bits[7] << 24;
+        const uint64_t m = transpose8x8((uint64_t)lo | (uint64_t)hi << 32);      // (row = worker, column = element)
+#pragma unroll
+        for (int e = 0; e < kByteSteps; ++e) acc[e] = table[(uint32_t)(m >> (8 * e)) & 0xFFu];
+    } else {
+        if (wbase >= out.n) return;
+#pragma unroll
+        for (int e = 0; e < kByteSteps; ++e) acc[e] = 0.0f;
+    }
+#pragma unroll 1
+    for (int w0 = TERN ? 0 : kPlaneBatch; w0 < W; w0 += kPlaneBatch) {
+        if (w0) fetch(w0);
+#pragma unroll
+        for (int b = 0; b < kPlaneBatch; ++b) {
+            if (w0 + b >= W) break;
+            float hi, lo;
+            plane_levels(scale[b], scale_lo[b], kind, hi, lo);
+#pragma unroll
+            for (int e = 0; e < kByteSteps; ++e) acc[e] = acc[e] + (TERN ? tern_term(bits[b], second[b], e, scale[b]) : plane_term(bits[b], e, hi, lo));
+        }
+    }
+    // through LDS, skewed, so that the stores are 256 contiguous bytes per wave instruction
+    float *mine = stage[wave];
+#pragma unroll
+    for (int e = 0; e < kByteSteps; ++e) mine[(kByteSteps + 1) * lane + e] = alpha * (!TERN && kind == PLANE_VOTE ? vote_of(acc[e]) : acc[e]);
+    __builtin_amdgcn_wave_barrier();
+    const Chunk c{wbase, lane, out.n - wbase >= (uint32_t)kByteWave};
+    float v[kByteSteps];
+#pragma unroll
+    for (int j = 0; j < kByteSteps; ++j) {
+        const uint32_t i = 64u * j + lane;
+        v[j] = mine[i + i / kByteSteps];
+    }
+    store_seg(out, c, v, chunk_entry(out, c));
+}
+
 template <class SRC>
 static void dense_decompress_t(const LaunchCtx &lc, int algo, const SRC &src, uint32_t blocks, int W, float alpha, uint32_t levels, int *status)
 {
@@ -1540,11 +1636,13 @@ static void dense_decompress_t(const LaunchCtx &lc, int algo, const SRC &src, ui
     case MC_ALGO_SIGNUM:
     {
         const int kind = algo == MC_ALGO_EFSIGN ? PLANE_SCALE : algo == MC_ALGO_ONEBIT ? PLANE_MEANS : PLANE_VOTE;
+        if (blocks <= kSpreadPlanes) { MC_LAUNCH((plane_spread_k<false, SRC>), grid, dim3(kByteThreads), lc, src, W, alpha, status, algo, kind); break; }
         if constexpr (SRC::kRoom > kPlaneBatch) if (W > kPlaneBatch) { MC_LAUNCH((plane_decompress_k<false, true, SRC>), grid, block, lc, src, W, alpha, status, algo, kind); break; }
         MC_LAUNCH((plane_decompress_k<false, false, SRC>), grid, block, lc, src, W, alpha, status, algo, kind);
         break;
     }
     case MC_ALGO_TERNGRAD:
+        if (blocks <= kSpreadPlanes) { MC_LAUNCH((plane_spread_k<true, SRC>), grid, dim3(kByteThreads), lc, src, W, alpha, status, algo, PLANE_SCALE); break; }
         if constexpr (SRC::kRoom > kPlaneBatch) if (W > kPlaneBatch) { MC_LAUNCH((plane_decompress_k<true, true, SRC>), grid, block, lc, src, W, alpha, status, algo, PLANE_SCALE); break; }
         MC_LAUNCH((plane_decompress_k<true, false, SRC>), grid, block, lc, src, W, alpha, status, algo, PLANE_SCALE);
         break;

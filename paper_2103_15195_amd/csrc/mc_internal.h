@@ -105,6 +105,10 @@ constexpr uint32_t kSpreadSumTiles = 128;
 // 4.4 and 3.9 / 4.6 / 5.2 us, 8 workers 7.4 / 7.6 / 7.5 and 5.2 / 6.7 / 7.1; FP16, 1 worker 4.1 / 4.5 / 4.5 and 4.2 / 4.2 / 4.3, 8 workers 6.8 /
 // 8.1 / 8.6 and 5.3 / 7.1 / 7.6.
 constexpr uint32_t kSpreadDecodeTiles = 256;
+// ... and of bit planes, in blocks of 8192 elements, with the blocks that check the headers one per compute unit.  Of 128 / 250 / 300 / 400 blocks in one
+// tensor, EF-Sign, 1 worker 5.3 / 5.5 / 6.2 / 6.5 and 4.6 / 4.8 / 6.4 / 6.8 us, 8 workers 5.7 / 6.4 / 6.6 / 7.1 and 5.3 / 6.0 / 7.8 / 8.2; TernGrad, 8 workers
+// 5.9 / 6.3 / 6.9 / 6.9 and 5.8 / 6.0 / 7.8 / 7.8.
+constexpr uint32_t kSpreadPlanes = 240;
 __host__ __device__ inline uint32_t tiles_in(uint32_t n) { return (uint32_t)(((uint64_t)n + kTile - 1) / kTile); }
 
 // How the blocks' partial sums become the group's scalars: by a kernel after this one; by the block of a small group that arrives last; by a block
