@@ -286,22 +286,27 @@ int mc_state_export_residual(mc_ctx *ctx, int32_t group, const void *state, floa
 int mc_state_import_residual(mc_ctx *ctx, int32_t group, const float *e_in, void *state, void *stream);
 
 /* Synchronises the context's device and returns MC_OK, MC_ERR_PAYLOAD if any
- * mc_decompress_sum since the last call saw a mismatching header, or MC_ERR_DEVICE if a
- * sparsifier's mc_compress gave up waiting at a grid-wide barrier of its rare selection routes
- * (the blocks of that kernel wait for each other, at most about two seconds, which needs them all
- * resident: other work that holds the GPU's compute units for that long can cause it; the
- * payload of that call is then incomplete and its error-feedback state unspecified -- import a
- * residual again before the next call; the context itself stays usable; where both happened, this is what
- * is returned).  Clears the flag. */
+ * mc_decompress_sum since the last call saw a mismatching header, or MC_ERR_DEVICE if a call gave up waiting:
+ *   Top-k, DGC, Rand-k   at a grid-wide barrier of the rare selection routes, whose blocks wait for each other
+ *                        and all have to be resident;
+ *   EF-Sign, QSGD, TernGrad, groups of more than 2^18 elements   in the block that combines the other blocks' partial
+ *                        sums, all of which start before it.
+ * Such a wait takes at most about two seconds: other work that holds the GPU's compute units for that long can cause
+ * this.  The payload of that call is then incomplete (the latter schemes': without a valid header, so that
+ * mc_decompress_sum reports it) and its error-feedback state unspecified -- import a residual again before the next call.
+ * The context itself stays usable; EF-Sign, QSGD and TernGrad on such groups only from this call on: until then their
+ * payloads have no valid header either.  Where both happened, this is what is returned.  Clears the flag. */
 int mc_last_device_status(mc_ctx *ctx);
 
 /* For tests of the error path above: how often a block looks at a grid-wide barrier before it gives up
  * (0 = the default, 2^21 looks of about a microsecond; 1 = after the first look, which makes every
  * mc_compress that takes one of the rare routes on more than one block report MC_ERR_DEVICE while all its
- * kernels still end normally).  QSGD and TernGrad: how often a block of a group of at most 2^18 elements
+ * kernels still end normally).  EF-Sign, QSGD and TernGrad: how often the block that combines the partial sums of a
+ * group of more than 2^18 elements looks for them (likewise: 1 makes it report MC_ERR_DEVICE unless they are all there).
+ * QSGD and TernGrad, besides: how often a block of a group of at most 2^18 elements
  * looks for the other blocks' partial sums (0 = the default, 2^10) before it leaves its share to the block
  * that comes last; the results are the same and no error arises.  Applies to the calls issued afterwards.
- * Errors: MC_ERR_INVALID_ARG (null, an algorithm that does not wait). */
+ * Errors: MC_ERR_INVALID_ARG (null, a context whose calls do not wait: EF-Sign's without such a group among them). */
 int mc_set_barrier_spin_limit(mc_ctx *ctx, uint32_t polls);
 
 /* Diagnostic for the sparsifiers (Top-k, DGC, Rand-k; Section 5.1 names their selection as the

@@ -146,14 +146,17 @@ __device__ __forceinline__ double combine_partials(const double *partial, uint32
 }
 
 // ---- other groups: a collector ---------------------------------------------------------------------------------------
-// The launch's last blocks wait for the partials, which is a store that goes past the die's cache, and combine them as
-// scalar_finalize_k would.  A slot is empty (all ones, which no sum is) until its tile's block has filled it, and the collector empties it
+// The launch's last blocks wait for the partials and combine them as scalar_finalize_k would.  The partials are stored
+// past the die's cache, each into a slot that is empty (all ones, which no sum is) until its tile's block has filled it, and the collector empties it
 // again, so that there is nothing to count.  It looks at the last tiles first, which are the first to be done, and when the last
 // block has stored its partial it takes about two trips to memory more, where a kernel of its own took a boundary, a start and the loads of all
-// partials.  (Compress and decompress-and-sum, that kernel -> collectors: 25.6 M elements, EF-Sign 79.8 -> 78.2 us, in 161 groups 79.6 -> 78.1, QSGD
+// partials.
+// (Compress and decompress-and-sum, that kernel -> collectors: 25.6 M elements, EF-Sign 79.8 -> 78.2 us, in 161 groups 79.6 -> 78.1, QSGD
 // in three groups 123.9 -> 122.3; 44.5 M, 16 workers, EF-Sign 142.3 -> 140.5; 10 M, TernGrad 46.5 -> 45.6.)
+// A collector waits for blocks that start before it, and which wait for nothing.  Should that not come to an end all the same, it
+// leaves after `looks` looks and flags it: from then on slots may hold what a call before has left, and no call on such groups sends a valid header
+// until mc_last_device_status has reported it and emptied the slots.
 constexpr uint64_t kEmptySlot = ~0ull;
-constexpr uint32_t kSlotLooks = 1u << 22;        // of about a microsecond: no call that is in order with the others of its context comes near it
 __device__ __forceinline__ void fill_slot(double *p, double v)
 {
     const uint64_t x = __builtin_bit_cast(uint64_t, v);
@@ -161,16 +164,19 @@ __device__ __forceinline__ void fill_slot(double *p, double v)
 }
 constexpr int kFinalThreads = 1024;
 // The sum (maximum) of n slots, in scalar_finalize_k's order: what each of its threads adds is added by itself, THREADS of the
-// block's threads standing for kFinalThreads.
+// block's threads standing for kFinalThreads.  False: not to be had.
 template <int THREADS, bool MAX>
-__device__ __forceinline__ double collect(double *slots, uint32_t n, double *red /* LDS, a word per wavefront of kFinalThreads */, int *status)
+__device__ __forceinline__ bool collect(const CompressJob &job, int *status, uint32_t limit, double *red /* LDS, a word per wavefront of kFinalThreads */,
+                                        bool *vain /* LDS */, double &sum)
 {
     constexpr int kEach = kFinalThreads / THREADS, kLoads = 4;
-    uint64_t *const from = reinterpret_cast<uint64_t *>(slots);
+    uint64_t *const from = reinterpret_cast<uint64_t *>(job.slots);
+    const uint32_t n = job.ntiles;
+    const int flagged = __hip_atomic_load(status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);      // (looked at behind the partials)
     double acc[kEach];
 #pragma unroll
     for (int v = 0; v < kEach; ++v) acc[v] = 0.0;
-    uint32_t looks = 0;
+    uint32_t looks = *vain ? limit + 1u : 0u;
     for (uint32_t top = (n + kFinalThreads - 1u) / kFinalThreads; top > 0u; top = top > (uint32_t)(kLoads / kEach) ? top - (uint32_t)(kLoads / kEach) : 0u) {
         uint64_t x[kLoads];
         auto at = [&](int l) {                   // load l: round (the highest first), share; n and more: none
@@ -183,8 +189,8 @@ __device__ __forceinline__ double collect(double *slots, uint32_t n, double *red
             for (int l = 0; l < kLoads; ++l) x[l] = at(l) < n ? __hip_atomic_load(from + at(l), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0ull;
 #pragma unroll
             for (int l = 0; l < kLoads; ++l) missing = missing || x[l] == kEmptySlot;
-            if (!missing) break;
-            if (looks++ >= kSlotLooks) { raise_flag(status, FLAG_GAVE_UP); break; }
+            if (!missing || looks > limit) break;
+            if (looks++ == limit) { raise_flag(status, FLAG_GAVE_UP); break; }
             __builtin_amdgcn_s_sleep(1);
         }
 #pragma unroll
@@ -204,23 +210,33 @@ __device__ __forceinline__ double collect(double *slots, uint32_t n, double *red
         }
         if ((threadIdx.x & 63u) == 0) red[v * (THREADS / 64) + (int)(threadIdx.x >> 6)] = s;
     }
+    if (__builtin_amdgcn_ballot_w64(flagged == FLAG_GAVE_UP || looks > limit) != 0ull) *vain = true;
     __syncthreads();
-    double t = red[0];
+    sum = red[0];
 #pragma unroll 4
-    for (int w = 1; w < kFinalThreads / 64; ++w) t = MAX ? fmax(t, red[w]) : t + red[w];
-    __syncthreads();                             // (the collector may have another group)
-    return t;
+    for (int w = 1; w < kFinalThreads / 64; ++w) sum = MAX ? fmax(sum, red[w]) : sum + red[w];
+    return !*vain;
 }
-// body(group's job) for the groups of this collector, the last ones first
-template <class SRC, class Body>
+// body(group's job, sum, or not valid) for the groups of this collector, the last ones first
+template <int THREADS, bool MAX, class SRC, class Body>
 __device__ __forceinline__ void each_collected(const SRC &src, Body body)
 {
+    __shared__ double red[kFinalThreads / 64];
+    __shared__ bool vain;                        // whether a scalar was not to be had: no later one is, then
+    if (threadIdx.x == 0) vain = false;
+    __syncthreads();
     const uint32_t collectors = gridDim.x - src.tiles(), y = src.groups();
     for (uint32_t q = blockIdx.x - src.tiles(); q < y; q += collectors) {
         const CompressJob job = src.group_job(y - 1u - q);
-        if (job.ntiles) body(job);
+        if (!job.ntiles) continue;
+        double sum = 0.0;
+        const bool valid = collect<THREADS, MAX>(job, src.status, src.looks, red, &vain, sum);
+        body(job, sum, valid);
+        __syncthreads();                         // (red)
     }
 }
+// the header of a payload whose scalar is not to be had: no payload's
+__device__ __forceinline__ void put_no_header(PayloadHeader *hdr) { *hdr = PayloadHeader{}; }
 
 // HOW = COMBINE_LAST: the group's last block to arrive combines the partials and writes the headers, instead of a kernel after this one.
 // (EF-Sign compress, 1 .. 64 tiles: 8.0 -> 5.6 .. 5.9 us, OneBit 8.6 .. 9.2 -> 6.2 .. 7.5: a launch and a kernel boundary less.
@@ -236,19 +252,16 @@ __global__ __launch_bounds__(kTile / S) void sign_compress_k(SRC src, float beta
     __shared__ double red3[MODE == SIGN_MEANS ? 3 : 1][kWaves];
     constexpr bool kHeld = S != kSteps && (MODE == SIGN_EF || MODE == SIGN_MEANS);
     __shared__ float held[kHeld ? kTile : 1];    // p of the tile, to be summed in the order of the other form
+    auto publish = [&](const CompressJob &of, double sum, bool valid) {
+        if (threadIdx.x) return;
+        if (!valid) { put_no_header(of.hdr); return; }
+        const float scale = mean_abs(sum, of.g.n);
+        put_plain_header(of.hdr, algo, of.g.n, scale);
+        if (EF) of.state_header()->scale = scale;        // (every block of the group has read the last call's)
+    };
     if constexpr (HOW == COMBINE_COLLECT) {
         static_assert(MODE == SIGN_EF, "one sum");
-        __shared__ double sums[kFinalThreads / 64];
-        if (blockIdx.x >= src.tiles()) {
-            each_collected(src, [&](const CompressJob &of) {
-                const float scale = mean_abs(collect<kTile / S, false>(of.slots, of.ntiles, sums, src.status), of.g.n);
-                if (threadIdx.x == 0) {
-                    put_plain_header(of.hdr, algo, of.g.n, scale);
-                    if (EF) of.state_header()->scale = scale;        // (every block of the group has read the last call's)
-                }
-            });
-            return;
-        }
+        if (blockIdx.x >= src.tiles()) { each_collected<kTile / S, false>(src, publish); return; }
     }
     const CompressJob job = src.job();
     const GroupView &g = job.g;
@@ -603,15 +616,13 @@ __global__ __launch_bounds__(kBlock) void accum_reduce_k(SRC src, uint32_t level
 {
     __shared__ double red[kWavesPerBlock];
     __shared__ float redf[kWavesPerBlock];
+    auto publish = [&](const CompressJob &of, double x, bool valid) {
+        if (threadIdx.x) return;
+        if (valid) put_plain_header(of.hdr, MODE == RED_L2 ? MC_ALGO_QSGD : MC_ALGO_TERNGRAD, of.g.n, MODE == RED_L2 ? (float)sqrt(x) : (float)x, 0.0f, levels);
+        else put_no_header(of.hdr);
+    };
     if constexpr (HOW == COMBINE_COLLECT) {
-        __shared__ double sums[kFinalThreads / 64];
-        if (blockIdx.x >= src.tiles()) {
-            each_collected(src, [&](const CompressJob &of) {
-                const double x = collect<kBlock, MODE == RED_MAX_ABS>(of.slots, of.ntiles, sums, src.status);
-                if (threadIdx.x == 0) put_plain_header(of.hdr, MODE == RED_L2 ? MC_ALGO_QSGD : MC_ALGO_TERNGRAD, of.g.n, MODE == RED_L2 ? (float)sqrt(x) : (float)x, 0.0f, levels);
-            });
-            return;
-        }
+        if (blockIdx.x >= src.tiles()) { each_collected<kBlock, MODE == RED_MAX_ABS>(src, publish); return; }
     }
     const CompressJob job = src.job();
     const Chunk c = my_chunk(job.g.n, job.tile);

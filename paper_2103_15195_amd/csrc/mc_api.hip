@@ -103,8 +103,10 @@ struct mc_ctx {
     size_t max_live = 0;
     double *d_partial = nullptr;
     double *d_slots = nullptr;          // a double per tile, empty between calls (fill_slot)
+    size_t slot_bytes = 0;
     uint64_t *d_arrive = nullptr;       // per group: blocks of small groups that have put their partial, over all calls
     uint32_t wait_looks = kWaitLooks;   // of the small quantizer groups' blocks (mc_set_barrier_spin_limit)
+    uint32_t collect_looks = kCollectLooks;      // of the collectors (the same)
     SparseScratch sparse{};
     uint32_t *d_hints = nullptr;        // candidate-filter hints: kHintWorkers per group (worker id modulo that)
     const uint32_t *last_hint = nullptr; // the record the most recent sparse mc_compress used (mc_select_stats)
@@ -296,9 +298,9 @@ static int set_up(mc_ctx *ctx, bool all, bool own)
     }
     if (!grab(ctx, &ctx->d_partial, 3 * std::max(tiles, all ? all_tiles : 0) * sizeof(double))) return MC_ERR_ALLOC;
     if (!is_sparse(cfg->algo)) {
-        const size_t bytes = std::max(tiles, all ? all_tiles : 0) * sizeof(double);
-        if (!grab(ctx, &ctx->d_slots, bytes)) return MC_ERR_ALLOC;
-        if (hipMemset(ctx->d_slots, 0xFF, bytes) != hipSuccess) return MC_ERR_DEVICE;
+        ctx->slot_bytes = std::max(tiles, all ? all_tiles : 0) * sizeof(double);
+        if (!grab(ctx, &ctx->d_slots, ctx->slot_bytes)) return MC_ERR_ALLOC;
+        if (hipMemset(ctx->d_slots, 0xFF, ctx->slot_bytes) != hipSuccess) return MC_ERR_DEVICE;
     }
     if ((rc = grab_zeroed(ctx, &ctx->d_arrive, y * kArriveStride * sizeof(uint64_t))) != MC_OK) return rc;
     if ((rc = grab_zeroed(ctx, &ctx->d_status, sizeof(int))) != MC_OK) return rc;
@@ -787,7 +789,7 @@ static void dense_compress(const mc_config &cfg, const LaunchCtx &lc, SRC src, u
 static void empty_compress(const mc_config &cfg, const LaunchCtx &lc, PayloadHeader *hdr)
 {
     const bool votes = cfg.algo == MC_ALGO_SIGNSGD || cfg.algo == MC_ALGO_SIGNUM;
-    launch_scalar_finalize(lc, OneCompress{GroupView{}, nullptr, hdr, nullptr, nullptr, nullptr, nullptr}, 1, votes ? RED_ONE : -1, (uint32_t)cfg.algo, qsgd_levels(cfg), false);
+    launch_scalar_finalize(lc, OneCompress{GroupView{}, nullptr, hdr, nullptr, nullptr, nullptr, nullptr, 0u}, 1, votes ? RED_ONE : -1, (uint32_t)cfg.algo, qsgd_levels(cfg), false);
 }
 static SparseCall sparse_call(const mc_ctx *ctx, uint32_t worker, uint64_t iter)
 {
@@ -824,7 +826,7 @@ static int compress_impl(mc_ctx *ctx, int32_t group, uint32_t worker, uint64_t i
     if (!is_sparse(cfg.algo)) {
         // (the static entry point may not rely on what an earlier call left in its array: no count of arrivals)
         uint64_t *arrive = partial == ctx->d_partial ? ctx->d_arrive + (size_t)group * kArriveStride : nullptr;
-        dense_compress(cfg, lc, OneCompress{gv, sf, hdr, partial, arrive, ctx->d_slots, ctx->d_status}, tiles_in(n), 1, tiles_in(n), worker, (uint32_t)iter, ctx->wait_looks);
+        dense_compress(cfg, lc, OneCompress{gv, sf, hdr, partial, arrive, ctx->d_slots, ctx->d_status, ctx->collect_looks}, tiles_in(n), 1, tiles_in(n), worker, (uint32_t)iter, ctx->wait_looks);
         return check_launch();
     }
     SparseScratch sp = ctx->sparse;
@@ -898,7 +900,7 @@ static int compress_all(mc_ctx *ctx, uint32_t worker, uint64_t iter, const float
             nb.same = one_each && nb.tiles <= kSameTiles;
         }
         launch_sparse_compress(lc, cfg.algo, AllSparse{tb, sp, ctx->last_group, one_each}, nb, ef, sparse_call(ctx, worker, iter));
-    } else dense_compress(cfg, lc, AllCompress{tb, ctx->d_partial, ctx->d_arrive, ctx->d_slots, ctx->d_status, ctx->all_blocks[BLK_TILE]}, ctx->all_blocks[BLK_TILE], (uint32_t)y, ctx->max_tiles, worker,
+    } else dense_compress(cfg, lc, AllCompress{tb, ctx->d_partial, ctx->d_arrive, ctx->d_slots, ctx->d_status, ctx->collect_looks, ctx->all_blocks[BLK_TILE]}, ctx->all_blocks[BLK_TILE], (uint32_t)y, ctx->max_tiles, worker,
                         (uint32_t)iter, ctx->wait_looks);
     for (size_t j = 0; j < y; ++j) if (ctx->groups[j].n == 0) empty_compress(cfg, lc, static_cast<PayloadHeader *>(payloads[j]));
     return check_launch();
@@ -1046,7 +1048,11 @@ int mc_last_device_status(mc_ctx *ctx)
     DeviceGuard on(ctx->device);
     if (hipDeviceSynchronize() != hipSuccess) return MC_ERR_DEVICE;
     if (hipMemcpy(&flag, ctx->d_status, sizeof(int), hipMemcpyDeviceToHost) != hipSuccess) return MC_ERR_DEVICE;
-    if (flag && hipMemset(ctx->d_status, 0, sizeof(int)) != hipSuccess) return MC_ERR_DEVICE;
+    if (flag) {
+        // (partial sums that came after their call had given up; nothing of the context runs)
+        if (flag == FLAG_GAVE_UP && ctx->d_slots && hipMemset(ctx->d_slots, 0xFF, ctx->slot_bytes) != hipSuccess) return MC_ERR_DEVICE;
+        if (hipMemset(ctx->d_status, 0, sizeof(int)) != hipSuccess || hipDeviceSynchronize() != hipSuccess) return MC_ERR_DEVICE;
+    }
     return flag == FLAG_GAVE_UP ? MC_ERR_DEVICE : flag ? MC_ERR_PAYLOAD : MC_OK;
 }
 
@@ -1084,10 +1090,13 @@ int mc_select_stats(mc_ctx *ctx, mc_select_counts *out, int32_t reset)
 int mc_set_barrier_spin_limit(mc_ctx *ctx, uint32_t polls)
 {
     if (!ctx) return MC_ERR_INVALID_ARG;
+    const int algo = ctx->cfg.algo;
     // polls = 1: give up after the first look
-    if (is_sparse(ctx->cfg.algo)) ctx->sparse.spin_limit = polls ? polls - 1u : kBarrierSpinLimit;
-    else if (ctx->cfg.algo == MC_ALGO_QSGD || ctx->cfg.algo == MC_ALGO_TERNGRAD) ctx->wait_looks = polls ? polls - 1u : kWaitLooks;
-    else return MC_ERR_INVALID_ARG;
+    if (is_sparse(algo)) { ctx->sparse.spin_limit = polls ? polls - 1u : kBarrierSpinLimit; return MC_OK; }
+    const bool quantizer = algo == MC_ALGO_QSGD || algo == MC_ALGO_TERNGRAD;
+    if (!quantizer && !(algo == MC_ALGO_EFSIGN && ctx->max_tiles > kSmallTiles)) return MC_ERR_INVALID_ARG;
+    ctx->wait_looks = polls ? polls - 1u : kWaitLooks;
+    ctx->collect_looks = polls ? polls - 1u : kCollectLooks;
     return MC_OK;
 }
 

@@ -117,6 +117,7 @@ enum Combine { COMBINE_AFTER = 0, COMBINE_LAST = 1, COMBINE_COLLECT = 2 };
 // Blocks of a launch that collect, each for every kCollectors-th group: few enough that the collectors of a good number of launches side
 // by side leave room for what they wait for.
 constexpr uint32_t kCollectors = 64;
+constexpr uint32_t kCollectLooks = 1u << 21;     // looks of about a microsecond before a collector gives up: no launch that has the device comes near it
 
 // A dense compressor's job.  The state's header lies in front of st, the payload's body behind hdr.
 struct CompressJob {
@@ -139,6 +140,7 @@ struct OneCompress {
     uint64_t *arrive;             // null: the call may not rely on what an earlier one left (mc_compress_static)
     double *slots;                // null: a kernel after this one combines the partials
     int *status;
+    uint32_t looks;
     __device__ __forceinline__ uint32_t tiles() const { return tiles_in(g.n); }
     __host__ __device__ __forceinline__ uint32_t groups() const { return 1u; }
     __device__ __forceinline__ CompressJob group_job(uint32_t) const { return {g, st, hdr, partial, arrive, slots, 0u, tiles()}; }
@@ -150,6 +152,7 @@ struct AllCompress {              // list: tensors, then y states, then y payloa
     uint64_t *arrive;             // kArriveStride words per group
     double *slots;
     int *status;
+    uint32_t looks;
     uint32_t all_tiles;
     __device__ __forceinline__ uint32_t tiles() const { return all_tiles; }
     __host__ __device__ __forceinline__ uint32_t groups() const { return tb.y; }
@@ -324,7 +327,7 @@ inline void launch(void (*kernel)(P...), dim3 grid, dim3 block, hipStream_t stre
 void launch_upload_ptrs(const LaunchCtx &lc, const uintptr_t *host, uintptr_t *dev, uint32_t count);
 void launch_expand_ptrs(const LaunchCtx &lc, const GroupView &g, uintptr_t *chunk_addr);
 void launch_expand_all(const LaunchCtx &lc, const GroupTable &tb, uint32_t tiles, uintptr_t *chunk_addr);
-// small: every group has at most kSmallTiles tiles and src.arrive counts.  src.slots: partials that are not combined so go to collectors
+// small: every group has at most kSmallTiles tiles and src.arrive counts.  src.slots: otherwise COMBINE_COLLECT
 template <class SRC> void launch_sign_compress(const LaunchCtx &lc, int mode, const SRC &src, uint32_t tiles, bool ef, float beta, uint32_t algo, bool small);
 template <class SRC> void launch_quantize_small(const LaunchCtx &lc, int mode, const SRC &src, uint32_t tiles, bool ef, uint32_t levels, uint64_t seed,
                                                 uint32_t worker, uint32_t iter_lo, uint32_t looks);

@@ -61,3 +61,52 @@ def test_an_abandoned_call_leaves_no_counts_behind(tiles):
         assert ctx.mc_last_select_route() == B.MC_SELECT_DENSE
     assert ctx.mc_last_device_status() == B.MC_OK
     ctx.close()
+
+
+@pytest.mark.parametrize("ef", [0, 1])
+@pytest.mark.parametrize("numel", [[65 * 4096], [1500 * 4096 + 5], [65 * 4096, 0, 7, 700 * 4096 + 5]])
+@pytest.mark.parametrize("algo", ["efsign", "qsgd", "terngrad"])
+def test_partial_sums_that_came_too_late_enter_no_later_call(algo, numel, ef):
+    """EF-Sign, QSGD and TernGrad on groups of more than 2^18 elements, whose combining block left before the other blocks' sums were there: the
+    payloads say so, also of the calls until the status has been read, and from then on calls are those of a context that always waited."""
+    y, large = len(numel), [j for j, n in enumerate(numel) if n > 2 ** 18]
+    held = []
+    for _ in range(2):
+        ctx = B.Context(algo, numel, list(range(y + 1)), use_ef=ef, seed=5)
+        held.append((ctx, [torch.zeros(ctx.state_bytes(j), dtype=torch.uint8, device=H.DEV) for j in range(y)],
+                     [torch.full((ctx.payload_bytes(j),), 0xAB, dtype=torch.uint8, device=H.DEV) for j in range(y)]))
+    (got, state, payload), (want, _, _) = held
+    gen = torch.Generator(device=H.DEV).manual_seed(len(numel))
+
+    def call(ctxs, it, together):
+        grads = [torch.empty(n, device=H.DEV).normal_(generator=gen) * 2.0 ** it for n in numel]
+        for c, s, p in ctxs:
+            if together:
+                c.mc_compress_groups(1, it, grads, s if ef else None, p)
+            else:
+                for j in range(y):
+                    c.mc_compress(j, 1, it, grads[j:j + 1], s[j] if ef else None, p[j])
+
+    for round in range(2):
+        together = round == 0
+        got.mc_set_barrier_spin_limit(1)
+        call(held[:1], 0, together)
+        got.mc_set_barrier_spin_limit(0)
+        assert all(O.header(payload[j].cpu().numpy())["magic"] == 0 for j in large)
+        call(held[:1], 1, not together)          # not read yet
+        assert all(O.header(payload[j].cpu().numpy())["magic"] == 0 for j in large)
+        assert got.mc_last_device_status() == B.MC_ERR_DEVICE
+        assert got.mc_last_device_status() == B.MC_OK
+        out = [torch.zeros(numel[large[0]], device=H.DEV)]
+        got.mc_decompress_sum(large[0], [payload[large[0]]], 1.0, out)
+        assert got.mc_last_device_status() == B.MC_ERR_PAYLOAD
+        for c, s, _ in held:                     # "import a residual again"
+            for j in range(y if ef else 0):
+                if numel[j]:
+                    c.mc_state_import_residual(j, torch.linspace(-1.0, 1.0, numel[j], device=H.DEV), s[j])
+        for it in range(2, 5):
+            call(held, it, it % 2 == 0)
+            for a, b in zip(held[0][2] + (held[0][1] if ef else []), held[1][2] + (held[1][1] if ef else [])):
+                assert torch.equal(a, b), (round, it)
+        assert got.mc_last_device_status() == B.MC_OK
+    got.close(); want.close()

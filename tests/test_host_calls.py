@@ -104,6 +104,20 @@ def test_who_takes_a_limit_on_waits(host, algo):
     ctx.close()
 
 
+@pytest.mark.parametrize("numel,waits", [([64 * TILE], False), ([64 * TILE + 1], True), ([100, 65 * TILE], True), ([100, 64 * TILE], False)])
+def test_efsign_takes_a_limit_where_its_blocks_wait(host, numel, waits):
+    """... which is where one of them combines the partial sums of a group of more than 64 tiles."""
+    ctx = B.Context("efsign", numel, list(range(len(numel) + 1)))
+    if waits:
+        ctx.mc_set_barrier_spin_limit(1)
+        ctx.mc_set_barrier_spin_limit(0)
+    else:
+        with pytest.raises(B.McError) as e:
+            ctx.mc_set_barrier_spin_limit(1)
+        assert e.value.status == B.MC_ERR_INVALID_ARG
+    ctx.close()
+
+
 def groups_call(ctx, n):
     """mc_compress_groups and mc_decompress_sum_groups (two workers) with buffers that do not overlap."""
     at = 1 << 40
