@@ -131,6 +131,17 @@ __device__ __forceinline__ uint64_t arrive_at(uint64_t *count)
 // The other end: after the count has been seen complete, before the partials are read.  (They bypass the caches, so nothing
 // has to be invalidated; but relaxed loads of different addresses are otherwise free to be moved before the count's.)
 __device__ __forceinline__ void all_arrived() { __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup"); }
+// the wavefront that put the block's partials: whether all of the group's blocks have put theirs
+__device__ __forceinline__ bool arrives_last(const CompressJob &job)
+{
+    uint64_t before = 0;
+    if (threadIdx.x == 0) before = arrive_at(job.arrive);
+    before = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)before) |
+             ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(before >> 32)) << 32);
+    if (before % job.ntiles != job.ntiles - 1u) return false;
+    all_arrived();
+    return true;
+}
 // one wavefront, N <= 64 partials: their sum (maximum) in the order of scalar_finalize_k, in all lanes
 template <bool MAX>
 __device__ __forceinline__ double combine_partials(const double *partial, uint32_t N)
@@ -145,14 +156,15 @@ __device__ __forceinline__ double combine_partials(const double *partial, uint32
     return acc;
 }
 
-// ---- other groups: a collector ---------------------------------------------------------------------------------------
-// The launch's last blocks wait for the partials and combine them as scalar_finalize_k would.  The partials are stored
+// ---- launches with larger groups: collectors -------------------------------------------------------------------------
+// A launch's last blocks wait for the partials of the groups of more than 64 tiles and combine them as scalar_finalize_k would.  The partials are stored
 // past the die's cache, each into a slot that is empty (all ones, which no sum is) until its tile's block has filled it, and the collector empties it
 // again, so that there is nothing to count.  It looks at the last tiles first, which are the first to be done, and when the last
 // block has stored its partial it takes about two trips to memory more, where a kernel of its own took a boundary, a start and the loads of all
-// partials.
+// partials.  Groups of up to 64 tiles in such a launch are combined by the block that arrives last, and nobody waits.
 // (Compress and decompress-and-sum, that kernel -> collectors: 25.6 M elements, EF-Sign 79.8 -> 78.2 us, in 161 groups 79.6 -> 78.1, QSGD
-// in three groups 123.9 -> 122.3; 44.5 M, 16 workers, EF-Sign 142.3 -> 140.5; 10 M, TernGrad 46.5 -> 45.6.)
+// in three groups 123.9 -> 122.3; 44.5 M, 16 workers, EF-Sign 142.3 -> 140.5; 10 M, TernGrad 46.5 -> 45.6.  Compress of 400 groups of 1000 elements / 2000 of
+// 256, and one of 1.6 M: EF-Sign, that kernel 13.8 / 28.0 us, collectors for all groups 22.0 / 72.5, now 10.2 / 14.9; QSGD 21.3 / 38.4, 29.6 / 81.7, 17.5 / 25.3.)
 // A collector waits for blocks that start before it, and which wait for nothing.  Should that not come to an end all the same, it
 // leaves after `looks` looks and flags it: from then on slots may hold what a call before has left, and no call on such groups sends a valid header
 // until mc_last_device_status has reported it and emptied the slots.
@@ -225,15 +237,28 @@ __device__ __forceinline__ void each_collected(const SRC &src, Body body)
     __shared__ bool vain;                        // whether a scalar was not to be had: no later one is, then
     if (threadIdx.x == 0) vain = false;
     __syncthreads();
-    const uint32_t collectors = gridDim.x - src.tiles(), y = src.groups();
+    const uint32_t collectors = gridDim.x - src.tiles(), y = src.collected();
     for (uint32_t q = blockIdx.x - src.tiles(); q < y; q += collectors) {
-        const CompressJob job = src.group_job(y - 1u - q);
-        if (!job.ntiles) continue;
+        const CompressJob job = src.collected_job(q);
         double sum = 0.0;
         const bool valid = collect<THREADS, MAX>(job, src.status, src.looks, red, &vain, sum);
         body(job, sum, valid);
         __syncthreads();                         // (red)
     }
+}
+// A tile's partial is there, in the block's first thread.  True, in one wavefront, if this block has the group's scalar to write.
+template <bool MAX>
+__device__ __forceinline__ bool hand_in(const CompressJob &job, double mine, double &sum)
+{
+    if (job.ntiles > kSmallTiles) {
+        if (threadIdx.x == 0) fill_slot(job.slots + job.tile, mine);
+        return false;
+    }
+    if (threadIdx.x >= 64u) return false;
+    if (threadIdx.x == 0) put_partial(job.partial + job.tile, mine);
+    if (!arrives_last(job)) return false;
+    sum = combine_partials<MAX>(job.partial, job.ntiles);
+    return true;
 }
 // the header of a payload whose scalar is not to be had: no payload's
 __device__ __forceinline__ void put_no_header(PayloadHeader *hdr) { *hdr = PayloadHeader{}; }
@@ -334,10 +359,11 @@ __global__ __launch_bounds__(kTile / S) void sign_compress_k(SRC src, float beta
     }
     if (MODE == SIGN_EF) {
         double t = block_sum<kWaves>(acc, red);
-        if (threadIdx.x == 0) {
-            if (HOW == COMBINE_LAST) put_partial(job.partial + job.tile, t);
-            else if (HOW == COMBINE_COLLECT) fill_slot(job.slots + job.tile, t);
-            else job.partial[job.tile] = t;
+        if constexpr (HOW == COMBINE_COLLECT) {
+            double sum;
+            if (hand_in<false>(job, t, sum)) publish(job, sum, true);
+        } else if (threadIdx.x == 0) {
+            if (HOW == COMBINE_LAST) put_partial(job.partial + job.tile, t); else job.partial[job.tile] = t;
         }
     }
     if (MODE == SIGN_MEANS) {       // the three sums behind one pair of barriers, each combined in block_sum's order
@@ -356,12 +382,7 @@ __global__ __launch_bounds__(kTile / S) void sign_compress_k(SRC src, float beta
         }
     }
     if (HOW == COMBINE_LAST && threadIdx.x < 64) {             // the wavefront that put the partials
-        uint64_t before = 0;
-        if (threadIdx.x == 0) before = arrive_at(job.arrive);
-        before = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)before) |
-                 ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(before >> 32)) << 32);
-        if (before % job.ntiles != job.ntiles - 1u) return;
-        all_arrived();
+        if (!arrives_last(job)) return;
         const uint32_t N = job.ntiles, n = g.n;
         const double a = combine_partials<false>(job.partial, N);
         float hi, lo = 0.0f;
@@ -376,9 +397,9 @@ __global__ __launch_bounds__(kTile / S) void sign_compress_k(SRC src, float beta
     }
 }
 
-// a collector for each group, or for every kCollectors-th
+// a collector for each group of more than 64 tiles, or for every kCollectors-th
 template <class SRC>
-static uint32_t collectors(const SRC &src) { return std::min(src.groups(), kCollectors); }
+static uint32_t collectors(const SRC &src) { return std::min(src.collected(), kCollectors); }
 
 template <int MODE, bool EF, int HOW, class SRC>
 static void sign_compress_t(const LaunchCtx &lc, const SRC &src, uint32_t tiles, float beta, uint32_t algo)
@@ -638,7 +659,10 @@ __global__ __launch_bounds__(kBlock) void accum_reduce_k(SRC src, uint32_t level
         }
     }
     const double t = MODE == RED_L2 ? block_sum(acc, red) : (double)block_max(mx, redf);
-    if (threadIdx.x == 0) { if (HOW == COMBINE_COLLECT) fill_slot(job.slots + job.tile, t); else job.partial[job.tile] = t; }
+    if constexpr (HOW == COMBINE_COLLECT) {
+        double x;
+        if (hand_in<MODE == RED_MAX_ABS>(job, t, x)) publish(job, x, true);
+    } else if (threadIdx.x == 0) job.partial[job.tile] = t;
 }
 
 template <bool EF, int MODE, class SRC>

@@ -105,6 +105,8 @@ struct mc_ctx {
     double *d_slots = nullptr;          // a double per tile, empty between calls (fill_slot)
     size_t slot_bytes = 0;
     uint64_t *d_arrive = nullptr;       // per group: blocks of small groups that have put their partial, over all calls
+    uint32_t *d_large = nullptr;        // groups of more than kSmallTiles tiles, the last ones first
+    uint32_t large_groups = 0;
     uint32_t wait_looks = kWaitLooks;   // of the small quantizer groups' blocks (mc_set_barrier_spin_limit)
     uint32_t collect_looks = kCollectLooks;      // of the collectors (the same)
     SparseScratch sparse{};
@@ -295,6 +297,10 @@ static int set_up(mc_ctx *ctx, bool all, bool own)
         }
         if ((rc = grab_copy(ctx, &ctx->d_groups, table)) != MC_OK) return rc;
         for (int b = 0; b < BLK_KINDS; ++b) if ((rc = grab_copy(ctx, &ctx->d_block_group[b], block_group[b])) != MC_OK) return rc;
+        std::vector<uint32_t> large;
+        for (size_t j = y; j-- > 0 && !is_sparse(cfg->algo);) if (tiles_in(ctx->groups[j].n) > kSmallTiles) large.push_back((uint32_t)j);
+        ctx->large_groups = (uint32_t)large.size();
+        if ((rc = grab_copy(ctx, &ctx->d_large, large)) != MC_OK) return rc;
     }
     if (!grab(ctx, &ctx->d_partial, 3 * std::max(tiles, all ? all_tiles : 0) * sizeof(double))) return MC_ERR_ALLOC;
     if (!is_sparse(cfg->algo)) {
@@ -900,7 +906,8 @@ static int compress_all(mc_ctx *ctx, uint32_t worker, uint64_t iter, const float
             nb.same = one_each && nb.tiles <= kSameTiles;
         }
         launch_sparse_compress(lc, cfg.algo, AllSparse{tb, sp, ctx->last_group, one_each}, nb, ef, sparse_call(ctx, worker, iter));
-    } else dense_compress(cfg, lc, AllCompress{tb, ctx->d_partial, ctx->d_arrive, ctx->d_slots, ctx->d_status, ctx->collect_looks, ctx->all_blocks[BLK_TILE]}, ctx->all_blocks[BLK_TILE], (uint32_t)y, ctx->max_tiles, worker,
+    } else dense_compress(cfg, lc, AllCompress{tb, ctx->d_partial, ctx->d_arrive, ctx->d_slots, ctx->d_status, ctx->collect_looks, ctx->all_blocks[BLK_TILE],
+                                                  ctx->large_groups, ctx->d_large}, ctx->all_blocks[BLK_TILE], (uint32_t)y, ctx->max_tiles, worker,
                         (uint32_t)iter, ctx->wait_looks);
     for (size_t j = 0; j < y; ++j) if (ctx->groups[j].n == 0) empty_compress(cfg, lc, static_cast<PayloadHeader *>(payloads[j]));
     return check_launch();

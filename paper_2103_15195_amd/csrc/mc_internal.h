@@ -111,10 +111,10 @@ constexpr uint32_t kSpreadDecodeTiles = 256;
 constexpr uint32_t kSpreadPlanes = 240;
 __host__ __device__ inline uint32_t tiles_in(uint32_t n) { return (uint32_t)(((uint64_t)n + kTile - 1) / kTile); }
 
-// How the blocks' partial sums become the group's scalars: by a kernel after this one; by the block of a small group that arrives last; by a block
-// of the same launch that waits for them (a collector).
+// How the blocks' partial sums become the group's scalars: by a kernel after this one; by the block of a small group that arrives last; by that one, or
+// in a larger group by a block of the same launch that waits for them (a collector).
 enum Combine { COMBINE_AFTER = 0, COMBINE_LAST = 1, COMBINE_COLLECT = 2 };
-// Blocks of a launch that collect, each for every kCollectors-th group: few enough that the collectors of a good number of launches side
+// Blocks of a launch that collect, each for every kCollectors-th of the larger groups: few enough that the collectors of a good number of launches side
 // by side leave room for what they wait for.
 constexpr uint32_t kCollectors = 64;
 constexpr uint32_t kCollectLooks = 1u << 21;     // looks of about a microsecond before a collector gives up: no launch that has the device comes near it
@@ -142,8 +142,9 @@ struct OneCompress {
     int *status;
     uint32_t looks;
     __device__ __forceinline__ uint32_t tiles() const { return tiles_in(g.n); }
-    __host__ __device__ __forceinline__ uint32_t groups() const { return 1u; }
+    __host__ __device__ __forceinline__ uint32_t collected() const { return 1u; }
     __device__ __forceinline__ CompressJob group_job(uint32_t) const { return {g, st, hdr, partial, arrive, slots, 0u, tiles()}; }
+    __device__ __forceinline__ CompressJob collected_job(uint32_t) const { return group_job(0u); }
     __device__ __forceinline__ CompressJob job() const { return {g, st, hdr, partial, arrive, slots, tiles() - 1u - blockIdx.x, tiles()}; }
 };
 struct AllCompress {              // list: tensors, then y states, then y payloads
@@ -153,9 +154,11 @@ struct AllCompress {              // list: tensors, then y states, then y payloa
     double *slots;
     int *status;
     uint32_t looks;
-    uint32_t all_tiles;
+    uint32_t all_tiles, large_groups;
+    const uint32_t *large;        // the groups of more than kSmallTiles tiles, the last ones first
     __device__ __forceinline__ uint32_t tiles() const { return all_tiles; }
-    __host__ __device__ __forceinline__ uint32_t groups() const { return tb.y; }
+    __host__ __device__ __forceinline__ uint32_t collected() const { return large_groups; }
+    __device__ __forceinline__ CompressJob collected_job(uint32_t q) const { return group_job(ld_uniform(large + q)); }
     __device__ __forceinline__ CompressJob group_job(uint32_t q) const
     {
         CompressJob j;
