@@ -289,8 +289,8 @@ int mc_state_import_residual(mc_ctx *ctx, int32_t group, const float *e_in, void
  * mc_decompress_sum since the last call saw a mismatching header, or MC_ERR_DEVICE if a call gave up waiting:
  *   Top-k, DGC, Rand-k   at a grid-wide barrier of the rare selection routes, whose blocks wait for each other
  *                        and all have to be resident;
- *   EF-Sign, QSGD, TernGrad, groups of more than 2^18 elements   in the block that combines the other blocks' partial
- *                        sums, all of which start before it.
+ *   EF-Sign, QSGD, TernGrad, groups of more than 2^18 elements (and at most 12288 * 4096)   in the block that combines
+ *                        the other blocks' partial sums, all of which start before it.
  * Such a wait takes at most about two seconds: other work that holds the GPU's compute units for that long can cause
  * this.  The payload of that call is then incomplete (the latter schemes': without a valid header, so that
  * mc_decompress_sum reports it) and its error-feedback state unspecified -- import a residual again before the next call.

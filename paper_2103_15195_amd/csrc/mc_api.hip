@@ -757,7 +757,7 @@ static void dense_compress(const mc_config &cfg, const LaunchCtx &lc, SRC src, u
     const Profiler *prof = static_cast<const Profiler *>(lc.prof);
     const bool apart = !src.arrive || (prof && prof->on), small = !apart && most_tiles <= kSmallTiles;
     // (OneBit's three sums take a collector more registers than its streaming pass has.)
-    const bool after = apart || (!small && cfg.algo == MC_ALGO_ONEBIT);
+    const bool after = apart || (!small && (cfg.algo == MC_ALGO_ONEBIT || most_tiles > kCollectTiles));
     if (after) src.slots = nullptr;
     const bool ef = cfg.use_ef != 0;
     const uint32_t levels = qsgd_levels(cfg), algo = (uint32_t)cfg.algo;

@@ -117,6 +117,11 @@ enum Combine { COMBINE_AFTER = 0, COMBINE_LAST = 1, COMBINE_COLLECT = 2 };
 // Blocks of a launch that collect, each for every kCollectors-th of the larger groups: few enough that the collectors of a good number of launches side
 // by side leave room for what they wait for.
 constexpr uint32_t kCollectors = 64;
+// They are used where the largest group has at most so many tiles.  A collector reads 1024 partials at a time, each time with a wait of its own among
+// the other blocks' traffic, and falls behind on a larger group.  (Compress of 8000 / 10 864 / 20 000 / 40 000 tiles, a kernel after the pass and a
+// collector: EF-Sign without error feedback 24.9 / 32.3 / 56.5 / 112.2 and 24.4 / 32.6 / 59.6 / 121.6 us, with it, from 10 864, 86.5 / 154.3 / 306.6 and 84.8 / 154.6 /
+// 311.8; TernGrad without 47.3 / 64.2 / 111.0 / 216.5 and 46.8 / 63.8 / 113.7 / 223.9, with it 112.3 / 200.6 / 423.0 and 110.5 / 199.6 / 435.1.)
+constexpr uint32_t kCollectTiles = 12288;
 constexpr uint32_t kCollectLooks = 1u << 21;     // looks of about a microsecond before a collector gives up: no launch that has the device comes near it
 
 // A dense compressor's job.  The state's header lies in front of st, the payload's body behind hdr.

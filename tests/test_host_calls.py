@@ -130,6 +130,22 @@ def groups_call(ctx, n):
     ctx.mc_decompress_sum_groups(payloads, 2, 1.0, grads, stream=0)
 
 
+@pytest.mark.parametrize("algo", ["efsign", "qsgd", "terngrad"])
+@pytest.mark.parametrize("tiles,kernels", [(12288, 0), (12289, 1)])
+def test_sums_of_very_large_groups_have_a_kernel_of_their_own(host, algo, tiles, kernels):
+    """... by itself and beside others in one call: a block of the launch that makes the sums falls behind it there."""
+    for numel in ([tiles * TILE], [100, tiles * TILE - 1, 70 * TILE]):
+        ctx = B.Context(algo, numel, list(range(len(numel) + 1)))
+        host.nd_reset(NO_LIMIT)
+        if len(numel) == 1:
+            ctx.mc_compress(0, 0, 0, [Buffer(1 << 40)], Buffer(1 << 41), Buffer(1 << 42), stream=0)
+        else:
+            at = [[Buffer((b << 44) + (j << 36)) for j in range(3)] for b in (1, 2, 3)]
+            ctx.mc_compress_groups(0, 0, *at, stream=0)
+        assert launches(host, "finalize") == [kernels]
+        ctx.close()
+
+
 @pytest.mark.parametrize("algo", ["topk", "randk", "dgc", "efsign"])
 def test_a_context_does_without_what_there_is_no_room_for(host, algo):
     """A context of many groups allocates more than its calls for one group need.  Where the device has no room for that, it is
