@@ -909,9 +909,11 @@ template void launch_tern_encode<AllCompress>(const LaunchCtx &, const AllCompre
 __device__ __forceinline__ uint64_t hand_over(const CompressJob &job, uint64_t all)
 {
     const uint64_t bit = 1ull << job.tile;
-    __hip_atomic_fetch_or(job.handed_over(), bit, __ATOMIC_SEQ_CST, __HIP_MEMORY_SCOPE_AGENT);      // (p in the state has to be seen with it)
-    if (__hip_atomic_load(job.arrive, __ATOMIC_SEQ_CST, __HIP_MEMORY_SCOPE_AGENT) < all) return 0;
-    return __hip_atomic_fetch_and(job.handed_over(), ~bit, __ATOMIC_SEQ_CST, __HIP_MEMORY_SCOPE_AGENT) & bit;
+    release_to_device();                         // (p in the state has to be seen with it)
+    (void)__hip_atomic_fetch_or(job.handed_over(), bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    release_to_device();                         // (done before the count is looked at)
+    if (__hip_atomic_load(job.arrive, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < all) return 0;
+    return __hip_atomic_fetch_and(job.handed_over(), ~bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & bit;
 }
 
 // The chip is nearly idle on such groups and a block takes as long as one wavefront's instructions do, so a tile is spread over

@@ -288,7 +288,8 @@ __global__ __launch_bounds__(kTile / S) void sparse_accum_k(SRC src, float momen
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
         if (threadIdx.x == 0) {
-            const uint32_t before = __hip_atomic_fetch_add(done, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+            release_to_device();
+            const uint32_t before = __hip_atomic_fetch_add(done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (before == job.blocks - 1u) {
                 __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
                 *done = 0u;                      // (for the next call)
@@ -908,7 +909,8 @@ __device__ __forceinline__ bool grid_barrier(uint32_t *arrive, uint32_t blocks, 
     __syncthreads();
     if (blocks == 1u) return true;
     if (threadIdx.x == 0 && !*dead) {
-        __hip_atomic_fetch_add(arrive, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+        release_to_device();
+        __hip_atomic_fetch_add(arrive, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         const uint32_t target = round * blocks;
         uint32_t spins = 0;
         // polled without acquire semantics: an acquire at agent scope invalidates the die's L2, and two hundred waiting

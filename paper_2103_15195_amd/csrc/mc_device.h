@@ -404,6 +404,15 @@ __device__ __forceinline__ float block_max(float x, float *lds4)
     return t;
 }
 
+// Release at the scope of the device, by one thread behind a barrier: what the block has stored is in memory, where other dies read it.
+// The write-back of the die's cache is waited for by an instruction of its own: the wait that the fence brings is dropped where the compiler knows of
+// nothing else that the wavefront has under way.
+__device__ __forceinline__ void release_to_device()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    __builtin_amdgcn_s_waitcnt(0);
+}
+
 // number of set bits of a ballot below this lane
 __device__ __forceinline__ uint32_t lanes_below(uint64_t ballot)
 {
