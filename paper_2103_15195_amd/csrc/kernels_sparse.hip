@@ -285,6 +285,9 @@ __global__ __launch_bounds__(kTile / S) void sparse_accum_k(SRC src, float momen
         static_assert(kThreads == 1024 && kBinsW >= kBins1, "the tail's block and histogram");
         __shared__ uint32_t pfx[2 * kRoundTiles], small[64];
         uint32_t *done = sc.arrive + kArriveDone;
+        // Every wavefront's stores and counts are in the die's cache before the barrier.  (The fence keeps them in front of the wait, which is an
+        // instruction to the compiler and nothing more.)
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
         if (threadIdx.x == 0) {
