@@ -1,7 +1,8 @@
 """Thin ctypes binding of libmergecomp.so (the C ABI in include/mergecomp.h).
 
 Argument marshalling only: every step of the path runs in the HIP kernels.  The hot calls go through a small
-extension module (csrc/fastcall.cpp) in the forms that a hot loop passes, through ctypes otherwise.
+extension module (csrc/fastcall.cpp) in the forms that a hot loop passes, through ctypes otherwise, and all calls if the
+module has not been built, with a warning.
 PyTorch is used for device memory and streams; tensors are passed by
 ``data_ptr()``.  There is no CPU fallback: if the library has not been built the
 import fails.
@@ -10,6 +11,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import warnings
 from typing import List, Optional, Sequence
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
@@ -65,6 +67,15 @@ def _fastcall():
     return module
 
 
+class _NoFastCalls:
+    """Stands for the module's calls where there is no module: no argument is in a form that it takes."""
+
+    @staticmethod
+    def compress(*args):
+        return None
+    compress_static = decompress = compress_groups = decompress_groups = compress
+
+
 def lib():
     """The loaded library; raises if it has not been built (no fallback path exists)."""
     global _lib
@@ -112,8 +123,12 @@ def lib():
         L.mc_strerror.argtypes = [C.c_int]
         L.mc_strerror.restype = C.c_char_p
         L.mc_version.restype = C.c_char_p
-        L.fast = _fastcall().Calls(C.Array, *[C.cast(f, C.c_void_p).value for f in (
-            L.mc_compress, L.mc_compress_static, L.mc_decompress_sum, L.mc_compress_groups, L.mc_decompress_sum_groups)])
+        try:
+            L.fast = _fastcall().Calls(C.Array, *[C.cast(f, C.c_void_p).value for f in (
+                L.mc_compress, L.mc_compress_static, L.mc_decompress_sum, L.mc_compress_groups, L.mc_decompress_sum_groups)])
+        except ImportError as e:
+            warnings.warn(f"calls go through ctypes, which takes a small call about 1 us longer: {e}")
+            L.fast = _NoFastCalls()
         _lib = L
     return _lib
 
@@ -155,7 +170,13 @@ def _current_stream() -> int:
         import torch
         torch.cuda.current_stream()              # initialises the device if nothing has yet
         get, device = (getattr(torch._C, name, None) for name in ("_cuda_getCurrentRawStream", "_cuda_getDevice"))
-        _raw_stream = _fastcall().RawStream(get, device) if get and device else (lambda: torch.cuda.current_stream().cuda_stream)
+        if get and device:
+            try:
+                _raw_stream = _fastcall().RawStream(get, device)
+            except ImportError:
+                _raw_stream = lambda: get(device())
+        else:
+            _raw_stream = lambda: torch.cuda.current_stream().cuda_stream
     return _raw_stream()
 
 

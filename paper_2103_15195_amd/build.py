@@ -1,11 +1,12 @@
 """Builds libmergecomp.so (the C-ABI HIP library) in-tree with hipcc for gfx950, and _fastcall.so (the binding's hot calls) with the
-host compiler."""
+host compiler, if there is one and it finds Python's headers: the binding does without it."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
 import sysconfig
+import warnings
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
@@ -34,10 +35,22 @@ def _run(cmd, verbose: bool) -> None:
         print(out)
 
 
+def build_fastcall(verbose: bool = False) -> bool:
+    """The extension module; without it, a warning and False."""
+    try:
+        _run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I" + sysconfig.get_paths()["include"],
+              "-o", FASTCALL, os.path.join(CSRC, "fastcall.cpp")], verbose)
+    except (OSError, RuntimeError) as e:
+        if os.path.exists(FASTCALL):             # (of other sources than the library's)
+            os.remove(FASTCALL)
+        warnings.warn(f"{os.path.basename(FASTCALL)} was not built, all calls go through ctypes: {e}")
+        return False
+    return True
+
+
 def build(verbose: bool = False) -> str:
-    _run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I" + sysconfig.get_paths()["include"],
-          "-o", FASTCALL, os.path.join(CSRC, "fastcall.cpp")], verbose)
     _run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")] + HIPCC_FLAGS + ["-o", LIB] + [os.path.join(CSRC, s) for s in SOURCES], verbose)
+    build_fastcall(verbose)
     return LIB
 
 

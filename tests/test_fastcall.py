@@ -73,3 +73,47 @@ def test_other_forms_are_left_to_ctypes(calls):
     assert not seen
     with pytest.raises(TypeError):
         B._fastcall().Calls(C.Array, 1, 2, 3)
+
+
+@pytest.fixture
+def no_module(monkeypatch):
+    """The package without its extension module."""
+    import sys
+
+    import paper_2103_15195_amd as package
+    monkeypatch.setitem(sys.modules, package.__name__ + "._fastcall", None)
+    monkeypatch.delattr(package, "_fastcall", raising=False)
+
+
+def test_the_binding_does_without_the_module(no_module, monkeypatch):
+    with pytest.raises(ImportError):
+        B._fastcall()
+    monkeypatch.setattr(B, "_lib", None)
+    with pytest.warns(UserWarning, match="ctypes"):
+        fast = B.lib().fast
+    args = (8, 0, 0, 0, None, None, None, None)
+    assert [getattr(fast, name)(*args) for name in ("compress", "compress_static", "decompress", "compress_groups", "decompress_groups")] == [None] * 5
+    assert B.mc_partition([3, 4, 5], 2) == [0, 2, 3]
+
+
+def test_the_stream_is_found_without_the_module(no_module, monkeypatch):
+    import torch
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: None)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda d: 0x100 + d, raising=False)
+    monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 3, raising=False)
+    monkeypatch.setattr(B, "_raw_stream", None)
+    assert B._current_stream() == 0x103
+
+
+@pytest.mark.parametrize("compiler", ["/nowhere/to/be/found", "false"])
+def test_the_library_is_built_where_the_module_cannot_be(monkeypatch, tmp_path, compiler):
+    from paper_2103_15195_amd import build as hip_build
+    ran = []
+    run = hip_build._run
+    monkeypatch.setattr(hip_build, "_run", lambda cmd, verbose: ran.append(cmd[0]) if "hipcc" in cmd[0] else run(cmd, verbose))
+    monkeypatch.setattr(hip_build, "FASTCALL", str(tmp_path / "_fastcall.so"))
+    monkeypatch.setenv("CXX", compiler)
+    monkeypatch.setenv("HIPCC", "hipcc")
+    with pytest.warns(UserWarning, match="ctypes"):
+        assert hip_build.build() == hip_build.LIB
+    assert ran == ["hipcc"]

@@ -146,6 +146,31 @@ def test_sums_of_very_large_groups_have_a_kernel_of_their_own(host, algo, tiles,
         ctx.close()
 
 
+@pytest.mark.filterwarnings("ignore:calls go through ctypes")
+def test_calls_without_the_extension_module(built, monkeypatch, request):
+    """The same calls, and the same refusals, where only the library has been built."""
+    import sys
+
+    import paper_2103_15195_amd as package
+    monkeypatch.setitem(sys.modules, package.__name__ + "._fastcall", None)
+    monkeypatch.delattr(package, "_fastcall", raising=False)
+    host = request.getfixturevalue("host")
+    assert B.lib().fast.compress() is None
+    for algo in B.ALGO_IDS:
+        test_who_takes_a_limit_on_waits(host, algo)
+    for algo in ("efsign", "qsgd", "topk"):
+        host.nd_reset(NO_LIMIT)
+        ctx = B.Context(algo, [100, 5000], [0, 1, 2])
+        groups_call(ctx, [100, 5000])
+        assert launches(host, "compress", "decompress") == [1, 1]
+        ctx.mc_compress(1, 0, 0, [Buffer(1 << 40)], Buffer(1 << 41), Buffer(1 << 42), stream=0)
+        ctx.mc_decompress_sum(1, [Buffer(1 << 42)], 1.0, [Buffer(1 << 40)], stream=0)
+        assert launches(host, "compress", "decompress") == [2, 2]
+        with pytest.raises(B.McError):
+            ctx.mc_compress(2, 0, 0, [Buffer(1 << 40)], Buffer(1 << 41), Buffer(1 << 42), stream=0)
+        ctx.close()
+
+
 @pytest.mark.parametrize("algo", ["topk", "randk", "dgc", "efsign"])
 def test_a_context_does_without_what_there_is_no_room_for(host, algo):
     """A context of many groups allocates more than its calls for one group need.  Where the device has no room for that, it is
