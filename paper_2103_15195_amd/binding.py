@@ -62,7 +62,7 @@ def _fastcall():
     try:
         from . import _fastcall as module
     except ImportError as e:
-        raise ImportError(f"{os.path.join(_HERE, '_fastcall.so')}: {e}; run `python -c 'import __graft_entry__ as g; g.build()'` "
+        raise ImportError(f"{os.path.join(_HERE, '_fastcall')}: {e}; run `python -c 'import __graft_entry__ as g; g.build()'` "
                           "(or paper_2103_15195_amd/build.py) first") from e
     return module
 

@@ -1,4 +1,4 @@
-"""Builds libmergecomp.so (the C-ABI HIP library) in-tree with hipcc for gfx950, and _fastcall.so (the binding's hot calls) with the
+"""Builds libmergecomp.so (the C-ABI HIP library) in-tree with hipcc for gfx950, and _fastcall (the binding's hot calls) with the
 host compiler, if there is one and it finds Python's headers: the binding does without it."""
 from __future__ import annotations
 
@@ -11,7 +11,7 @@ import warnings
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmergecomp.so")
-FASTCALL = os.path.join(HERE, "_fastcall.so")
+FASTCALL = os.path.join(HERE, "_fastcall" + sysconfig.get_config_var("EXT_SUFFIX"))      # (other interpreters' layouts differ: none but this one loads it)
 SOURCES = ["mc_api.hip", "kernels_dense.hip", "kernels_sparse.hip"]
 
 # -ffp-contract=off: the residual updates must round every fp32 operation on its own
@@ -37,6 +37,9 @@ def _run(cmd, verbose: bool) -> None:
 
 def build_fastcall(verbose: bool = False) -> bool:
     """The extension module; without it, a warning and False."""
+    untagged = os.path.join(os.path.dirname(FASTCALL), "_fastcall.so")          # (which any interpreter would load)
+    if os.path.exists(untagged):
+        os.remove(untagged)
     try:
         _run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I" + sysconfig.get_paths()["include"],
               "-o", FASTCALL, os.path.join(CSRC, "fastcall.cpp")], verbose)

@@ -111,9 +111,23 @@ def test_the_library_is_built_where_the_module_cannot_be(monkeypatch, tmp_path, 
     ran = []
     run = hip_build._run
     monkeypatch.setattr(hip_build, "_run", lambda cmd, verbose: ran.append(cmd[0]) if "hipcc" in cmd[0] else run(cmd, verbose))
-    monkeypatch.setattr(hip_build, "FASTCALL", str(tmp_path / "_fastcall.so"))
+    monkeypatch.setattr(hip_build, "FASTCALL", str(tmp_path / "_fastcall.tag.so"))
     monkeypatch.setenv("CXX", compiler)
     monkeypatch.setenv("HIPCC", "hipcc")
     with pytest.warns(UserWarning, match="ctypes"):
         assert hip_build.build() == hip_build.LIB
     assert ran == ["hipcc"]
+
+
+def test_the_module_is_this_interpreters(monkeypatch, tmp_path):
+    import importlib.machinery
+    import os
+
+    from paper_2103_15195_amd import build as hip_build
+    assert B._fastcall().__file__ == hip_build.FASTCALL
+    tag = os.path.basename(hip_build.FASTCALL)[len("_fastcall"):]
+    assert tag == importlib.machinery.EXTENSION_SUFFIXES[0] != ".so"
+    (tmp_path / "_fastcall.so").write_text("of another interpreter")
+    monkeypatch.setattr(hip_build, "FASTCALL", str(tmp_path / ("_fastcall" + tag)))
+    assert hip_build.build_fastcall()
+    assert os.listdir(tmp_path) == ["_fastcall" + tag]
