@@ -40,8 +40,10 @@ def test_the_scalars_of_a_kernel_of_its_own(algo, numel, ef):
 
 
 @pytest.mark.parametrize("ef", [0, 1])
-@pytest.mark.parametrize("numel", [[64 * TILE, 65 * TILE, 1, 64 * TILE + 1, 63 * TILE - 1, TILE, TILE + 1], [257] * 300 + [130 * TILE] + [3 * TILE] * 20])
+@pytest.mark.parametrize("numel", [[64 * TILE, 65 * TILE, 1, 64 * TILE + 1, 63 * TILE - 1, TILE, TILE + 1], [257] * 300 + [130 * TILE] + [3 * TILE] * 20,
+                                   [64 * TILE + 1 + 59 * j for j in range(70)]])
 @pytest.mark.parametrize("algo", ["efsign", "qsgd", "terngrad"])
 def test_groups_of_both_kinds_in_one_call(algo, numel, ef):
-    """Groups of at most 64 tiles beside larger ones: their last block to arrive combines their sums, in calls of their own and in one call, by turns."""
+    """Groups of at most 64 tiles beside larger ones: their last block to arrive combines their sums, in calls of their own and in one call, by turns;
+    and more larger groups than there are blocks to collect for them."""
     test_the_scalars_of_a_kernel_of_its_own(algo, numel, ef)

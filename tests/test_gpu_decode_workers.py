@@ -178,3 +178,59 @@ def test_long_runs_of_few_workers(W, n_run):
         got, want = torch.cat(out).cpu().numpy(), O.decompress_sum(sent, n, 0.25)
         assert np.array_equal(got.view(np.uint32), want.view(np.uint32)), (side, c, d, astray, size)
     assert ctx.mc_last_device_status() == B.MC_OK
+
+
+# A launch of so many blocks that a wavefront holds all it can: more than 240 of 8192 elements (bit planes), 256 of 4096 (one code per element)
+RAGGED = [1, 37, 1000, 3, 5000, 64, 1023, 1025, 2, 2048, 4095]
+LARGE = {"planes": 240 * 8192 + 1, "codes": 256 * 4096 + 1}
+
+
+def check_large(algo, kind, workers, n, off):
+    """One group of many ragged tensors in front of and behind a large one, by itself and in one call with another group."""
+    sizes = RAGGED * 3 + [0] + RAGGED[::-1] * 3
+    sizes[len(RAGGED) * 3] = n - sum(sizes)
+    ef = 0 if algo == "signsgd" else 1
+    cfg = O.Config(B.ALGO_IDS[algo], use_ef=ef, seed=1)
+    ctx = B.Context(algo, sizes + [70], [0, len(sizes), len(sizes) + 1], use_ef=ef, seed=1)
+    rng = np.random.default_rng([n, off, list(ODD).index(kind)])
+    sent = []
+    for m in (n, 70):
+        sent.append([])
+        for w in range(min(max(workers), 9)):
+            p, _ = O.compress(cfg, rng.standard_normal(m).astype(np.float32), O.new_state(cfg, m) if ef else None, worker=w)
+            if kind != "plain":
+                p[SCALE:SCALE + 4] = np.array([ODD[kind][w % len(ODD[kind])]], np.float32).view(np.uint8)
+                if algo == "onebit":
+                    p[SCALE_LO:SCALE_LO + 4] = np.array([ODD[kind][(w + 1) % len(ODD[kind])]], np.float32).view(np.uint8)
+            sent[-1].append(p)
+    dev = [[torch.from_numpy(p).to(DEV) for p in ps] for ps in sent]
+    for W in workers:
+        pick = [w % len(sent[0]) for w in range(W)]
+        want = np.concatenate([O.decompress_sum([sent[j][w] for w in pick], m, 0.5) for j, m in enumerate((n, 70))])
+        for together in (False, True):
+            outs = [torch.full((m + 4,), 5.0, device=DEV)[off:off + m] for m in sizes + [70]]
+            if together:
+                ctx.mc_decompress_sum_groups([dev[j][w] for w in pick for j in range(2)], W, 0.5, outs)
+            else:
+                ctx.mc_decompress_sum(0, [dev[0][w] for w in pick], 0.5, outs[:-1])
+                ctx.mc_decompress_sum(1, [dev[1][w] for w in pick], 0.5, outs[-1:])
+            got = torch.cat(outs).cpu().numpy()
+            gone = np.isnan(want)
+            assert np.array_equal(np.isnan(got), gone), (W, together)
+            assert np.array_equal(got.view(np.uint32)[~gone], want.view(np.uint32)[~gone]), (W, together)
+    assert ctx.mc_last_device_status() == B.MC_OK
+    ctx.close()
+
+
+@pytest.mark.parametrize("kind,off", [("plain", 0), ("plain", 2), ("tiny", 1), ("inf", 3), ("nan", 0)])
+@pytest.mark.parametrize("algo", ["efsign", "onebit", "terngrad", "signsgd", "signum"])
+def test_numbers_of_workers_of_many_planes(algo, kind, off):
+    if kind != "plain" and algo in ("signsgd", "signum"):
+        pytest.skip("no scale that the decode multiplies with")
+    check_large(algo, kind, (1, 3, 8, 9, 17, 64), LARGE["planes"], off)
+
+
+@pytest.mark.parametrize("off", [0, 1, 2, 3])
+@pytest.mark.parametrize("algo", ["qsgd", "fp16"])
+def test_numbers_of_workers_of_many_codes(algo, off):
+    check_large(algo, "plain", (1, 3, 4, 5, 9, 17), LARGE["codes"], off)
