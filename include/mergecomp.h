@@ -352,8 +352,8 @@ int mc_select_stats(mc_ctx *ctx, mc_select_counts *out, int32_t reset);
  * run one kernel per step (same results): EF-Sign, OneBit, QSGD and TernGrad on groups of at most 2^18 elements, which
  * they otherwise compress in a single kernel, and Top-k, DGC and Rand-k on groups of at most 2^17 elements and 6144 kept
  * entries, whose selection is otherwise one kernel and not two, up to 2^15 elements the streaming pass's.  EF-Sign, QSGD and
- * TernGrad on larger groups run the kernel that combines the partial sums, which is otherwise a block of the pass that
- * makes them.  What these kernels take, only an outside profiler shows.
+ * TernGrad on larger groups run the kernel that combines the partial sums, which is otherwise (up to 12288 * 4096
+ * elements) a block of the pass that makes them.  What these kernels take, only an outside profiler shows.
  *   mc_profile_select    bit i of the mask: time kernel slot i while enabled (default: all slots)
  *   mc_profile_kernels   number of kernel slots
  *   mc_profile_read      name (static string), launches and total milliseconds of slot `id`

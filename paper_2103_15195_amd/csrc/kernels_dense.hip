@@ -7,7 +7,7 @@
 // lane-consecutive 4-byte accesses (256 contiguous bytes per wave instruction),
 // sign / ternary planes are packed with 64-lane ballots, group scalars are
 // reduced per block in LDS and combined by the kernel itself: in groups of at most 64 tiles by the block that arrives last, in
-// others by a block that waits for them (OneBit: a one-block kernel after it).
+// others by a block that waits for them (OneBit, and very large groups: a one-block kernel after it).
 #include <algorithm>
 #include <cstddef>
 
@@ -1211,8 +1211,10 @@ template void launch_fp16_compress<AllCompress>(const LaunchCtx &, const AllComp
 // made FP16 slower, 80.3 -> 82.5..85 us with 2, 4 or 8 workers per batch, so FP16 stays plain.)
 // S: elements per lane, 16, or 4 on a launch of few tiles (kSpreadDecodeTiles).  Those are bound by one wavefront's chain of instructions and
 // waits: a quarter of the additions each, and with the registers that frees, eight workers in a batch -- every batch waits for its scales and
-// codes anew.  (1 / 64 / 256 tiles, QSGD, 4 workers 4.7 / 4.8 / 5.4 -> 3.9 / 3.9 / 4.2 us, 8 workers 6.3 / 6.5 / 7.4 -> 4.2 / 4.5 / 5.2, 16 workers 9.9 / 10.4 /
-// 11.8 -> 6.5 / 7.0 / 8.0; FP16, 8 workers 5.9 / 6.1 / 6.8 -> 4.0 / 4.2 / 5.3.  One worker is bound by the launch.)
+// codes anew.  (Device time, 1 / 120 / 238 tiles in one tensor: QSGD, 1 worker 2.8 / 3.1 / 3.4 -> 2.8 / 3.2 / 3.5 us, 4 workers 3.0 / 3.7 / 4.0 -> 3.1 / 3.8 / 4.0,
+// 8 workers 3.8 / 5.0 / 5.2 -> 3.7 / 4.3 / 4.7, 16 workers 5.5 / 7.4 / 7.9 -> 5.3 / 6.2 / 6.7; FP16, 1 worker 2.8 / 3.3 / 3.6 -> 3.0 / 3.3 / 3.6, 8 workers 4.2 / 6.1 / 6.7
+// -> 3.4 / 4.8 / 5.3.  238 tiles in 60 tensors: QSGD, 1 / 8 workers 5.0 / 8.3 -> 4.3 / 6.3.  The rule does not look at the tenth of a microsecond that one
+// worker's codes lose in one tensor.)
 template <int ALGO, class SRC, int S = kSteps>
 __global__ __launch_bounds__(kTile / S) void dense_decompress_k(SRC src, int W, float alpha, uint32_t levels, int *status)
 {
@@ -1566,10 +1568,11 @@ __global__ __launch_bounds__(kBlock) void plane_decompress_k(SRC src, int W, flo
 }
 
 // The same on few tiles, where the time is one wavefront's chain: four times as many wavefronts, a lane holds eight elements, one byte of every
-// worker's plane, and one transpose; every term is added as what it is.  (8 / 32 / 128 blocks, EF-Sign, 1 worker 5.1 / 5.1 / 5.3 -> 4.2 / 4.3 / 4.6 us, 8
-// workers 5.1 / 5.2 / 5.7 -> 4.7 / 4.9 / 5.3, 16 workers 7.1 / 7.1 / 7.7 -> 6.4 / 6.4 / 6.7; in 60 tensors, where a wavefront of 2048 elements walks over the
-// tensors of its two chunks one after the other, 1 worker 6.3 / 6.4 / 6.6 -> 4.7 / 4.7 / 5.1, 8 workers 6.4 / 6.4 / 6.7 -> 5.1 / 5.3 / 5.7; TernGrad there,
-// 4 workers 6.4 / 6.3 / 6.6 -> 4.8 / 4.8 / 5.1.)
+// worker's plane, and one transpose; every term is added as what it is.  (Device time, 1 / 120 / 238 blocks in one tensor: EF-Sign, 1 worker 4.1 / 4.8 / 5.1 -> 3.7 / 4.3 /
+// 4.7 us, 4 workers 4.2 / 4.8 / 5.0 -> 3.9 / 4.5 / 4.8, 8 workers 4.3 / 4.8 / 5.2 -> 4.3 / 4.9 / 5.3, 16 workers 6.3 / 6.9 / 7.3 -> 5.9 / 6.6 / 7.0; TernGrad, 1 worker 3.6 / 4.2 / 4.5 ->
+// 3.2 / 3.8 / 4.1, 4 workers 4.0 / 4.6 / 4.9 -> 3.8 / 4.4 / 4.8, 8 workers 4.5 / 5.1 / 5.4 -> 4.6 / 5.2 / 5.5, 16 workers 6.4 / 7.0 / 7.3 -> 6.7 / 7.4 / 7.6.  One block of 60 tensors, where a
+// wavefront of 2048 elements walks over the tensors of its two chunks one after the other: EF-Sign, 1 / 8 / 16 workers 6.6 / 6.8 / 8.9 -> 4.9 / 5.5 / 7.2, TernGrad
+// 6.1 / 7.1 / 9.0 -> 4.3 / 5.9 / 8.2.  The rule does not look at what many workers' planes lose in one tensor.)
 constexpr int kByteSteps = 8, kByteWave = 64 * kByteSteps, kByteThreads = kSignTile / kByteSteps;
 template <bool TERN, class SRC>
 __global__ __launch_bounds__(kByteThreads) void plane_spread_k(SRC src, int W, float alpha, int *status, int algo, int kind)

@@ -174,10 +174,10 @@ __device__ __forceinline__ void put_candidates(const Chunk &c, const uint32_t (&
 // SMALL: the whole compress of groups of at most kOneBlockTiles tiles, in launches of at most kSameTiles.  In the block of a group that is done
 // last with the streaming pass the selection follows, as lean_small_k has it: a kernel that starts behind another one takes 1 us of the device
 // and 2.6 of the host, a die's lines written to memory and a count of the blocks that are done take less.  No block waits for another.  (A word more for the plain kernel's arguments took 0.3 us of a call.)
-// (Compress, two kernels -> one.  Top-k 1 % of 1 / 4 / 8 tiles 10.1 / 10.1 / 10.2 -> 8.5 / 8.9 / 9.2 us, 5 % 10.1 / 10.9 / 12.4 -> 8.8 / 10.0 / 11.4; DGC 1 % 10.1 /
-// 10.1 / 10.3 -> 8.9 / 9.3 / 9.5; Rand-k 1 % 19.2 / 20.7 / 20.5 -> 17.8 / 20.0 / 19.8; four groups of 1 / 4 tiles in one call, Top-k 14.1 / 14.1 -> 11.3 /
-// 11.4, and with the decompression of four workers 19.2 / 18.6 -> 15.7 / 15.5.  Larger groups lose what the launch saves to the tail's
-// wait for the slowest block: four groups of 12 / 16 / 18 tiles, both directions, 18.4 / 18.9 / 18.9 -> 18.5 / 19.8 / 19.9.)
+// (Compress, two kernels -> one, device time, without the launch that the host saves.  Top-k 1 % of 1 / 4 / 8 tiles 9.5 / 9.7 / 9.8 -> 8.8 / 9.3 / 9.7 us, 5 % 9.6 /
+// 10.8 / 12.2 -> 9.0 / 10.3 / 11.9; DGC 1 % 9.8 / 10.1 / 10.3 -> 9.3 / 9.7 / 10.1; Rand-k 1 % 10.3 / 11.1 / 11.5 -> 9.9 / 11.2 / 11.7; seven groups of 1 / 4 / 8 tiles in
+// one call, Top-k 10.9 / 11.0 / 11.1 -> 9.9 / 10.0 / 10.6, Rand-k 12.4 / 12.8 / 13.3 -> 11.2 / 12.1 / 12.8.  Larger groups lose what the launch saves to the tail's
+// wait for the slowest block: four groups of 12 / 16 / 18 tiles, both directions, 18.4 / 18.9 / 18.9 -> 18.5 / 19.8 / 19.9, and 0.2 more since the write-back is waited for.)
 constexpr int kRoundTiles = 4096;      // tiles per round of the slow routes' compaction: 256 blocks of 16 wavefronts at most
 template <int ALGO, bool EF, int MOST>
 __device__ __forceinline__ void small_tail(SparseJob job, RngKey rng, uint32_t sync_blocks, int *status, uint32_t *hist, uint32_t *pfx, uint32_t *small);
